@@ -64,9 +64,11 @@ AggOptions& agg_options();
 int launch_zero(void* p, size_t bytes, hipStream_t stream);
 
 // internal launchers (no argument validation; the C entry points did it)
+// keep_sign: which outputs are positive is decided by float32 sums with k in ascending order, however the products are
+// formed (a training step goes by it: see train.hip)
 int launch_transform(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh,
                      const float* W, const float* b, bool relu, float* Z, int64_t ldz,
-                     hipStream_t stream, const float* mask = nullptr, int64_t ldm = 0);
+                     hipStream_t stream, const float* mask = nullptr, int64_t ldm = 0, bool keep_sign = false);
 
 struct AggCall {
     const retexo_plan* plan;

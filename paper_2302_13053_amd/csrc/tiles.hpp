@@ -4,10 +4,19 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kTileK = 16;    // K extent of one LDS tile
+
+// f(0), f(1), .. f(N - 1) with the index as a constant: register arrays are only ever indexed by constants
+template <int... I, class F>
+__device__ __forceinline__ void each_index(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void each(F&& f) { each_index(std::make_integer_sequence<int, N>{}, f); }
 
 // Four consecutive floats starting at base[off], fetched without a branch: an
 // element that is not wanted (or would be out of range) is fetched from base[0]
@@ -35,83 +44,257 @@ __device__ __forceinline__ void zero4(int wanted, float (&r)[4])
 }
 
 
-// ---------------------------------------------------------------------------
-// Software-pipelined K loop of one workgroup tile (four waves, fp32 32x32x2 MFMA).
-//
-// One wave keeps a matrix core busy only if nothing else in its instruction
-// stream takes longer than one MFMA (64 cycles).  The loop therefore cuts all
-// staging work into pieces of about that size and places them between the MFMAs
-// of the wave that does them; sched_barrier pins the order.  Per K step (kTileK
-// columns = 8 k-steps of 2):
-//   after the first MFMA of every k-step: LDS reads of the next k-step's operands
-//   after the second MFMA of k-steps 0..2: put(buf ^ 1, 0..2), one third each of
-//       "write tile t+1 from the staging registers to the other LDS buffer"
-//   after the second MFMA of k-steps 3, 4: fetch(t + 2, 0 / 1), the two halves of
-//       "load tile t+2 into the staging registers" (so a global load has a whole K
-//       step of MFMAs to arrive)
-//   between k-steps 6 and 7 (operands of 7 already in registers): the one barrier,
-//       then the reads of the next tile's first operands behind k-step 7's MFMAs.
-// Contract on entry: tile 0 is in LDS buffer 0 and a barrier has passed; tile 1
-// (if nk > 1) is in the caller's staging registers.  LDS tiles are k-major:
-// As[buf][k][row of the workgroup tile], Bs[buf][k][column]; a0 / b0 are the first
-// row / column of this wave's TM x TN block of 32 x 32 accumulators.  last_steps:
-// k-steps of the last tile that hold data (a K extent that is not a multiple of
-// kTileK leaves the others zero-filled; they are skipped).
-// ---------------------------------------------------------------------------
 #define RETEXO_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-template <int TM, int TN, int LDA, int LDB, class Put, class Fetch>
-__device__ __forceinline__ void mfma_k_loop(f32x16 (&acc)[TM][TN], const float (*As)[kTileK][LDA],
-                                            const float (*Bs)[kTileK][LDB], int nk, int a0, int b0, int lane,
-                                            Put&& put, Fetch&& fetch, int last_steps = kTileK / 2)
+// ---------------------------------------------------------------------------
+// float32 products on the bf16 matrix cores.
+//
+// A float32 is the sum of three bf16 values: hi = round(x), mid = round(x - hi), lo = x - hi - mid.  Both
+// differences are exact, and the three 8-bit significands with their signs cover all 24 bits, so nothing of x is
+// lost.  Of the nine partial products of a * b the six with at least one hi or two mid are computed, each exact in
+// float32 and added up in float32 by the matrix core; the three left out (mid*lo, lo*mid, lo*lo) are below 2^-24 of
+// the product.  v_mfma_f32_32x32x16_bf16 does sixteen k in the time in which v_mfma_f32_32x32x2_f32 does one: six
+// of them against eight.
+//
+// The five small products have a running sum of their own, added to that of hi*hi at the end: the matrix core rounds the
+// sum after every eight k (and drops what lies 25 bits below the largest term), so with small products on the large sum
+// it would be rounded twelve times per sixteen k, where the float32 instruction rounds once per k that is not zero;
+// this way it is twice.  (All six onto one sum: 512 rectified columns 3.2e-7 off the same in 64 bits in the 2-norm,
+// the float32 instruction 2.8e-7.  Small sums of sixteen k added to the large one each time: as exact, 11 % slower.)
+//
+// Where the split is no longer exact the float32 instructions take over, one 32 x 32 tile at a time (see
+// `redo_tile`): infinities and NaN (their remainders are NaN), values that round to infinity in bf16, sums that
+// overflow, and operands so small that mid and lo fall below the smallest bf16 numbers.
+// ---------------------------------------------------------------------------
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes at any float's address
+
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 {
-    constexpr int NSTEP = kTileK / 2;
-    static_assert(NSTEP == 8, "the schedule below is written for 8 k-steps");
-    const int lrow = lane & 31, lk = lane >> 5;
-    float af[2][TM], bf[2][TN];
-    auto frag = [&](int buf, int s, int slot) {       // operands of k-step s -> register set slot
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ float bf16_low(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float bf16_high(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+
+// Two floats -> pair q of their hi, mid and lo parts.
+template <class V>
+__device__ __forceinline__ void split_pair(float x0, float x1, int q, V (&part)[3])
+{
+    const uint32_t hi = bf16_pair(x0, x1);
+    const float r0 = x0 - bf16_low(hi), r1 = x1 - bf16_high(hi);
+    const uint32_t mid = bf16_pair(r0, r1);
+    part[0][q] = hi;
+    part[1][q] = mid;
+    part[2][q] = bf16_pair(r0 - bf16_low(mid), r1 - bf16_high(mid));
+}
+
+// Whether any of a wave's 32 x 32 sums formed from split operands cannot be trusted: not finite, or so small (but not
+// zero) that the operands may have lost their low parts.  bf16 goes down to 2^-133, so an operand keeps its 24
+// bits from about 2^-110 on; the line is drawn at sums below 2^-104.  With `near` > 0 also where a sum plus `bias` lies
+// within `near` of zero (a caller that goes by the sign).
+__device__ __forceinline__ bool redo_tile(const f32x16& acc, float bias, float near)
+{
+    uint32_t top = 0, low = 0xffffffffu;          // largest magnitude; smallest one minus one (zero wraps round)
+    bool close = false;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) af[slot][i] = As[buf][2 * s + lk][a0 + i * 32 + lrow];
+    for (int r = 0; r < 16; ++r) {
+        const float x = acc[r];
+        const uint32_t m = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
+        top = m > top ? m : top;
+        low = m - 1 < low ? m - 1 : low;
+        close |= __builtin_fabsf(x + bias) < near;
+    }
+    return __any(close || top >= 0x7f800000u || low < 0x0b800000u - 1);
+}
+
+// LDS image of one K tile of a workgroup: 16-byte units of eight k of one row (of A) or column (of B),
+// [part][k / 8][row], first A's BM rows, then B's BN.  The four units of padding per plane put the two k halves of a row,
+// which neighbouring lanes write, into different banks; a matrix instruction's operand (lane l: row l % 32,
+// k half l / 32) is 32 consecutive units.
+template <int BM, int BN> struct SplitTile {
+    static constexpr int LA = BM + 4, LB = BN + 4;
+    static constexpr int units = 6 * (LA + LB);
+    static __device__ __forceinline__ int a(int part, int half, int row) { return (part * 2 + half) * LA + row; }
+    static __device__ __forceinline__ int b(int part, int half, int col) { return 6 * LA + (part * 2 + half) * LB + col; }
+};
+
+// Staging of an operand whose rows run along k (element (k, c) at src[k * ld + c]): a wave takes pieces of 64
+// columns by KW k (one coalesced load per k), so every lane ends up with KW consecutive k of its column: eight where
+// the workgroup's waves share the BW columns x 16 k of a tile evenly that way, else four.  (32 columns are staged
+// twice, by two waves each with the same values.)  Columns past the end repeat the last one (their products are never
+// stored); rows from k_end on count as zero.
+// The work on a piece comes in micro steps for split_k_loop: KW / 2 steps that split a pair, one that writes the
+// parts to LDS, one that fetches the piece of the next tile.
+template <int BW, int WAVES> struct KMajorStage {
+    static constexpr int KW = BW >= 64 && BW / 32 % WAVES == 0 ? 8 : 4;
+    static constexpr int chunks = BW == 32 ? WAVES : BW / 64 * (kTileK / KW);
+    static constexpr int count = (chunks + WAVES - 1) / WAVES;
+    static constexpr int steps = KW / 2 + 2;                        // micro steps per piece
+    typedef uint32_t part_t __attribute__((ext_vector_type(KW / 2)));
+    const float* src;
+    int64_t ld, k0, k_end;
+    int wave, lane;
+    uint32_t col[count];              // byte offset of this lane's (clamped) column, per piece
+    float r[count][KW];
+    part_t part[3];
+
+    __device__ __forceinline__ int chunk(int i) const { return wave + WAVES * i; }
+    __device__ __forceinline__ bool mine(int i) const { return chunks % WAVES == 0 || chunk(i) < chunks; }
+    __device__ __forceinline__ int kk(int i) const             // first k of the piece inside the tile
+    {
+        return BW == 32 ? ((wave & 1) * 2 + (lane >> 5)) * 4 : chunk(i) / (BW / 64) * KW;
+    }
+    __device__ __forceinline__ int local(int i) const { return BW == 32 ? lane & 31 : (chunk(i) % (BW / 64)) * 64 + lane; }
+
+    __device__ __forceinline__ void init(const float* s, int64_t ld_, int64_t k_begin, int64_t k_end_, int c0, int c_end, int wave_, int lane_)
+    {
+        src = s; ld = ld_; k0 = k_begin; k_end = k_end_; wave = wave_; lane = lane_;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bf[slot][j] = Bs[buf][2 * s + lk][b0 + j * 32 + lrow];
-    };
-    frag(0, 0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        const bool more = kt + 1 < nk;        // the staging registers hold tile kt + 1
-        const bool more2 = kt + 2 < nk;
-#pragma unroll
-        for (int s = 0; s < NSTEP; ++s) {
-            if (!more && s >= last_steps) break;   // the rest of a partial last tile is zeros: adds nothing, changes no bit
-            const int cur = s & 1;
-            int q = 0;                        // MFMAs issued in this k-step
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[cur][i], bf[cur][j], acc[i][j], 0, 0, 0);
-                    RETEXO_SCHED_FENCE();
-                    if (q == 0) {
-                        if (s + 1 < NSTEP) frag(buf, s + 1, cur ^ 1);
-                        RETEXO_SCHED_FENCE();
-                    }
-                    if (q == (TM * TN > 1 ? 1 : 0)) {
-                        if (s <= 2 && more) put(buf ^ 1, s);
-                        if (s == 3 && more2) fetch(kt + 2, 0);
-                        if (s == 4 && more2) fetch(kt + 2, 1);
-                        RETEXO_SCHED_FENCE();
-                    }
-                    ++q;
-                }
-            }
-            if (s == NSTEP - 2) {
-                // every wave has read its last operands of this tile and written its share of the next one;
-                // the barrier waits for LDS traffic only, global loads stay in flight across it
-                __syncthreads();
-                RETEXO_SCHED_FENCE();
-                if (more) frag(buf ^ 1, 0, 0);
-                RETEXO_SCHED_FENCE();
-            }
+        for (int i = 0; i < count; ++i) {
+            const int c = c0 + local(i);
+            col[i] = 4u * (uint32_t)(c < c_end ? c : c_end - 1);
         }
     }
+    // The row's address is the same for all lanes and is formed in scalar registers (the empty asm keeps the compiler from
+    // turning every row into a pointer of its own that each tile has to advance: thirty 64-bit additions per tile, and
+    // spilled scalar registers).
+    typedef const __attribute__((address_space(1))) char* global_t;
+    static __device__ __forceinline__ float at(uint64_t row, uint32_t offset)
+    {
+        return *reinterpret_cast<const __attribute__((address_space(1))) float*>(reinterpret_cast<global_t>(row) + offset);
+    }
+    template <int i>
+    __device__ __forceinline__ void fetch(int kt)
+    {
+        if (!mine(i)) return;
+        const int64_t k = k0 + (int64_t)kt * kTileK + (BW == 32 ? 0 : kk(i));
+        const uint64_t first = reinterpret_cast<uint64_t>(src + k * ld);
+        uint32_t low = __builtin_amdgcn_readfirstlane((uint32_t)first), high = __builtin_amdgcn_readfirstlane((uint32_t)(first >> 32));
+        asm("" : "+s"(low), "+s"(high));
+        const uint64_t row = (uint64_t)high << 32 | low;
+        const uint32_t c = col[i];
+        const uint64_t pitch = 4 * (uint64_t)ld;
+        const bool whole = k0 + (int64_t)(kt + 1) * kTileK <= k_end;
+        if constexpr (BW == 32) {                              // the half-waves stage different k
+            const uint32_t piece = (uint32_t)kk(i);
+#pragma unroll
+            for (int q = 0; q < KW; ++q)
+                r[i][q] = whole || k + piece + q < k_end ? *reinterpret_cast<const float*>(row + (piece + q) * pitch + c) : 0.0f;
+        } else if (whole) {
+#pragma unroll
+            for (int q = 0; q < KW; ++q) r[i][q] = at(row + q * pitch, c);
+        } else {
+#pragma unroll
+            for (int q = 0; q < KW; ++q) r[i][q] = k + q < k_end ? at(row + q * pitch, c) : 0.0f;
+        }
+    }
+    // plane(part, k half, column) -> 16-byte unit of `base`; sign: 0, or the sign bit to stage the operand negated
+    template <int M, class Plane>
+    __device__ __forceinline__ void micro(u32x4* base, Plane&& plane, uint32_t sign, bool more, int kt)
+    {
+        constexpr int i = M / steps, st = M % steps;
+        if (!mine(i)) return;
+        if constexpr (st < KW / 2) {
+            const uint32_t x0 = __builtin_bit_cast(uint32_t, r[i][2 * st]), x1 = __builtin_bit_cast(uint32_t, r[i][2 * st + 1]);
+            split_pair(__builtin_bit_cast(float, x0 ^ sign), __builtin_bit_cast(float, x1 ^ sign), st, part);
+        } else if constexpr (st == KW / 2) {
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                u32x4* unit = base + plane(s, kk(i) >> 3, local(i));
+                *reinterpret_cast<part_t*>(reinterpret_cast<char*>(unit) + (KW == 4 ? (kk(i) & 4) * 2 : 0)) = part[s];
+            }
+        } else {
+            if (more) fetch<i>(kt);
+        }
+    }
+};
+
+// ---------------------------------------------------------------------------
+// Software-pipelined K loop of one workgroup tile (six bf16 products per 32 x 32 x 16 block).
+//
+// A matrix core is kept busy only if what else a wave does fits between its matrix instructions (32 cycles each,
+// two waves per SIMD).  So the staging work of a K tile is cut into `MICROS` steps of about ten instructions, spread
+// over the matrix instructions before the tile's barrier; sched_barrier pins the order.  micro(m, buf, kt): step m of
+// "split the staged pieces (tile kt) into LDS buffer `buf`, and fetch those of tile kt + 1 in their place", whose loads
+// so have one K tile of matrix instructions to arrive.
+// Columns of the wave's tile are worked through one after the other with B's operands a column ahead.
+// The one barrier of a K tile stands before its last column, whose operands are already in registers: behind that
+// barrier the next tile's first operands are read as soon as their registers are free.
+// Contract on entry: tile 0 is in LDS buffer 0 and a barrier has passed; tile 1's pieces (if nk > 1) are staged.
+// a0 / b0: first row / column of this wave's 32 x 32 TN block of accumulators.
+// ---------------------------------------------------------------------------
+template <int TN, int BM, int BN, int MICROS, class Micro>
+__device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __restrict__ lds, int nk, int a0, int b0,
+                                             int lane, Micro&& micro)
+{
+    using T = SplitTile<BM, BN>;
+    constexpr int SLOTS = TN == 1 ? 1 : TN % 2 ? TN : 2;      // register sets of B operands: a column ahead, also across tiles
+    constexpr int HI = 0, MID = 1, LO = 2;
+    constexpr int pa[6] = {HI, HI, HI, LO, MID, MID}, pb[6] = {HI, LO, MID, HI, MID, HI};
+    constexpr int G = (TN > 1 ? TN - 1 : 1) * 6;              // matrix instructions before the barrier
+    const int lrow = lane & 31, lk = lane >> 5;
+    bf16x8 af[3], bf[SLOTS][3];
+    f32x16 small[TN];                                         // sums of all products but hi*hi
+    auto read_a = [&](int buf, int part) {
+        af[part] = __builtin_bit_cast(bf16x8, lds[buf * T::units + T::a(part, lk, a0 + lrow)]);
+    };
+    auto read_b = [&](int buf, int j, int slot) {
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+            bf[slot][part] = __builtin_bit_cast(bf16x8, lds[buf * T::units + T::b(part, lk, b0 + j * 32 + lrow)]);
+    };
+    read_b(0, 0, 0);
+    read_a(0, HI);
+    read_a(0, LO);
+    read_a(0, MID);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) small[j][r] = 0.0f;
+    auto tile = [&](int kt, auto more_tag) {
+        constexpr bool more = decltype(more_tag)::value;
+        const int buf = kt & 1;
+        each<TN * 6>([&](auto at) {
+            constexpr int g = decltype(at)::value, j = g / 6, p = g % 6;
+            constexpr bool last = TN > 1 && j == TN - 1;
+            if constexpr (last && more && p == 0) {
+                // every wave has read its operands of this tile and written its share of the next one
+                __syncthreads();
+                RETEXO_SCHED_FENCE();
+                read_b(buf ^ 1, 0, 0);
+            }
+            f32x16& sum = p == 0 ? acc[j] : small[j];
+            sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[pa[p]], bf[j % SLOTS][pb[p]], sum, 0, 0, 0);
+            RETEXO_SCHED_FENCE();
+            if constexpr (p == 0 && j + 1 < TN) read_b(buf, j + 1, (j + 1) % SLOTS);
+            if constexpr (last && more) {
+                if constexpr (p == 2) read_a(buf ^ 1, HI);
+                if constexpr (p == 3) read_a(buf ^ 1, LO);
+                if constexpr (p == 5) read_a(buf ^ 1, MID);
+            }
+            if constexpr (!last && more) {
+                constexpr int m0 = g * MICROS / G, m1 = (g + 1) * MICROS / G;
+                each<m1 - m0>([&](auto m) { micro(std::integral_constant<int, m0 + decltype(m)::value>{}, buf ^ 1, kt + 1); });
+            }
+            RETEXO_SCHED_FENCE();
+        });
+        if constexpr (TN == 1 && more) {
+            __syncthreads();
+            RETEXO_SCHED_FENCE();
+            read_b(buf ^ 1, 0, 0);
+            read_a(buf ^ 1, HI);
+            read_a(buf ^ 1, LO);
+            read_a(buf ^ 1, MID);
+        }
+    };
+    for (int kt = 0; kt + 1 < nk; ++kt) tile(kt, std::true_type{});
+    if (nk > 0) tile(nk - 1, std::false_type{});
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] += small[j][r];
 }

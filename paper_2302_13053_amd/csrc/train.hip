@@ -15,323 +15,137 @@
 // The two weight gradients are "TN" products whose contraction runs over the
 // nodes (hundreds of thousands), with a small output.  wgrad_kernel splits the
 // node range over many workgroups, each producing a partial [M, Nq] tile with
-// the same fp32 MFMA tile loop as the transform (both operands are already
-// k-major in memory, so their tiles are plain 16-byte copies into LDS), and a
-// second kernel adds the partials in a fixed order: deterministic, and more
-// accurate than one long fp32 accumulation.
+// the same split-bf16 tile loop as the transform, and a second kernel adds the
+// partials in a fixed order: deterministic, and more accurate than one long
+// fp32 accumulation.
 #include "common.hpp"
 #include "tiles.hpp"
 
 namespace {
 
-constexpr int BK = kTileK;
 constexpr int kThreads = 256;
 
 // ---------------------------------------------------------------------------
 // part[z][m][n] = sum over k in chunk z of P[k][m] * Q[k][n]
 // ---------------------------------------------------------------------------
 
-// Partial tile of one wave -> part[z]: accumulator element r of lane l is row 8*(r/4) + 4*(l/32) + r%4,
-// column l%32 of its 32 x 32 tile.
-template <int TM, int TN>
-__device__ __forceinline__ void write_partial(const f32x16 (&acc)[TM][TN], int M, int Nq, int row_base, int col_base,
-                                              int lane, float* __restrict__ out)
-{
-    const int lrow = lane & 31, lk = lane >> 5;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int col = col_base + j * 32 + lrow;
-        if (col >= Nq) continue;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int row0 = row_base + i * 32 + 4 * lk;
-            float* p = out + (int64_t)row0 * Nq + col;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ro = 8 * (r / 4) + (r % 4);
-                if (row0 + ro < M) p[(int64_t)ro * Nq] = acc[i][j][r];
-            }
-        }
-    }
-}
-
-// Aligned operands (rows of P and Q are 16-byte multiples at 16-byte aligned addresses, M >= 4, Nq >= 4):
-// the software-pipelined K loop shared with the dense transform.  Columns past M / Nq are clamped to the
-// last four (their products land in partials that are never stored); only a partial last K tile of a
-// chunk takes a checked, zero-filling fetch.
-template <int BM, int BN, int WGM, int WGN>
-__global__ __launch_bounds__(256, 2) void wgrad_pipe_kernel(
+// Both operands run along k, so both are staged by columns (KMajorStage) and multiplied by the split K loop shared
+// with the dense transform; 128 x BN outputs per workgroup, 32 rows and up to 128 columns per wave, any alignment and
+// leading dimension.
+template <int BN> constexpr int wgrad_waves = BN > 128 ? 8 : 4;
+template <int BN>
+__global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 : 2) void wgrad_kernel(
     int64_t K, int M, int Nq, const float* __restrict__ P, int64_t ldp,
     const float* __restrict__ Q, int64_t ldq, int64_t k_chunk, float* __restrict__ part)
 {
-    static_assert(WGM * WGN == 4, "four waves per workgroup");
-    constexpr int TM = BM / (32 * WGM);
-    constexpr int TN = BN / (32 * WGN);
-    constexpr int LDA = BM + 4;
-    constexpr int LDB = BN + 4;
-    constexpr int A_F4 = BM * BK / 4 / 256;
-    constexpr int B_F4 = (BN * BK / 4 + 255) / 256;
-    constexpr bool B_PART = BN * BK / 4 % 256 != 0;
-    static_assert(A_F4 >= 1 && BM * BK / 4 % 256 == 0, "tile shape");
+    constexpr int BM = 128, WAVES = wgrad_waves<BN>, WN = BN / (WAVES / 4), TN = WN / 32;
+    using T = SplitTile<BM, BN>;
+    using PStage = KMajorStage<BM, WAVES>;
+    using QStage = KMajorStage<BN, WAVES>;
+    __shared__ u32x4 lds[2 * T::units];
 
-    __shared__ float As[2][BK][LDA];
-    __shared__ float Bs[2][BK][LDB];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int a0 = wave % 4 * 32, b0 = wave / 4 * WN;    // the wave's rows and columns of the tile
+    const int lrow = lane & 31, lk = lane >> 5;
     const int m0 = blockIdx.x * BM;
     const int n0 = blockIdx.y * BN;
     const int64_t k_begin = (int64_t)blockIdx.z * k_chunk;
     const int64_t k_end = min(K, k_begin + k_chunk);
 
-    f32x16 acc[TM][TN];
+    f32x16 acc[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
 
-    const int nk = k_end > k_begin ? (int)((k_end - k_begin + BK - 1) / BK) : 0;
+    // every other chunk is summed with its sign turned and turned back at the end: the matrix core's bf16 additions lean
+    // to one side a little, and over the thousands of chunks of a large graph that would add up
+    const uint32_t sign = (blockIdx.z & 1) << 31;
+    const int nk = k_end > k_begin ? (int)((k_end - k_begin + kTileK - 1) / kTileK) : 0;
     if (nk > 0) {
-        const int k_tail = (int)((k_end - k_begin) % BK);      // > 0: the chunk's last tile is partial
-        const float* pa[A_F4];
-        const float* pb[B_F4];
-        int ka[A_F4], kb[B_F4];                                // row of the thread's piece inside a tile
-#pragma unroll
-        for (int i = 0; i < A_F4; ++i) {
-            const int id = tid + i * 256;
-            const int kk = id / (BM / 4), m4 = id % (BM / 4);
-            int m = m0 + m4 * 4;
-            m = m < M - 4 ? m : M - 4;
-            pa[i] = P + (k_begin + kk) * ldp + m;
-            ka[i] = kk;
-        }
-#pragma unroll
-        for (int i = 0; i < B_F4; ++i) {
-            const int id = tid + i * 256;
-            const int kk = (id / (BN / 4)) % BK, n4 = id % (BN / 4);
-            int n = n0 + n4 * 4;
-            n = n < Nq - 4 ? n : Nq - 4;
-            pb[i] = Q + (k_begin + kk) * ldq + n;
-            kb[i] = kk;
-        }
-        const int64_t step_a = (int64_t)BK * ldp, step_b = (int64_t)BK * ldq;
-        f32x4 ra[A_F4], rb[B_F4];
-
-        auto fetch_a = [&](int kt) {
-            if (k_tail && kt == nk - 1) {
-#pragma unroll
-                for (int i = 0; i < A_F4; ++i) {
-                    const bool in = ka[i] < k_tail;
-                    const f32x4 t = *reinterpret_cast<const f32x4*>(in ? pa[i] : P);
-                    ra[i] = in ? t : f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < A_F4; ++i) ra[i] = *reinterpret_cast<const f32x4*>(pa[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < A_F4; ++i) pa[i] += step_a;
+        PStage sp;
+        QStage sq;
+        sp.init(P, ldp, k_begin, k_end, m0, M, wave, lane);
+        sq.init(Q, ldq, k_begin, k_end, n0, Nq, wave, lane);
+        constexpr int A_MICROS = PStage::count * PStage::steps;
+        constexpr int MICROS = A_MICROS + QStage::count * QStage::steps;
+        auto micro = [&](auto step, int buf, int kt) {
+            constexpr int m = decltype(step)::value;
+            u32x4* base = lds + buf * T::units;
+            const bool more = kt + 1 < nk;
+            if constexpr (m < A_MICROS)
+                sp.template micro<m>(base, [](int s, int half, int c) { return T::a(s, half, c); }, sign, more, kt + 1);
+            else
+                sq.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, 0u, more, kt + 1);
         };
-        auto fetch_b = [&](int kt) {
-            if (k_tail && kt == nk - 1) {
-#pragma unroll
-                for (int i = 0; i < B_F4; ++i) {
-                    const bool in = kb[i] < k_tail;
-                    const f32x4 t = *reinterpret_cast<const f32x4*>(in ? pb[i] : Q);
-                    rb[i] = in ? t : f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < B_F4; ++i) rb[i] = *reinterpret_cast<const f32x4*>(pb[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < B_F4; ++i) pb[i] += step_b;
-        };
-        auto put_a = [&](int buf, int i) {
-            const int id = tid + i * 256;
-            const int kk = id / (BM / 4), m4 = id % (BM / 4);
-            *reinterpret_cast<f32x4*>(&As[buf][kk][m4 * 4]) = ra[i];
-        };
-        auto put_b = [&](int buf, int i) {
-            const int id = tid + i * 256;
-            if (B_PART && id >= BN * BK / 4) return;
-            const int kk = id / (BN / 4), n4 = id % (BN / 4);
-            *reinterpret_cast<f32x4*>(&Bs[buf][kk][n4 * 4]) = rb[i];
-        };
-
-        fetch_a(0);
-        fetch_b(0);
-#pragma unroll
-        for (int i = 0; i < A_F4; ++i) put_a(0, i);
-#pragma unroll
-        for (int i = 0; i < B_F4; ++i) put_b(0, i);
-        if (nk > 1) { fetch_a(1); fetch_b(1); }
+        each<PStage::count>([&](auto i) { sp.template fetch<decltype(i)::value>(0); });
+        each<QStage::count>([&](auto i) { sq.template fetch<decltype(i)::value>(0); });
+        each<MICROS>([&](auto m) { micro(m, 0, 0); });
         __syncthreads();
-
-        auto put = [&](int buf, int third) {
-            if (third == 0) {
-#pragma unroll
-                for (int x = 0; x < A_F4; ++x) put_a(buf, x);
-            } else if (third == 1) {
-                put_b(buf, 0);
-            } else {
-#pragma unroll
-                for (int x = 1; x < B_F4; ++x) put_b(buf, x);
-            }
-        };
-        auto fetch = [&](int kt, int half) {
-            if (half == 0) fetch_a(kt);
-            else fetch_b(kt);
-        };
-        mfma_k_loop<TM, TN, LDA, LDB>(acc, As, Bs, nk, wm * TM * 32, wn * TN * 32, lane, put, fetch);
+        split_k_loop<TN, BM, BN, MICROS>(acc, lds, nk, a0, b0, lane, micro);
     }
-    write_partial<TM, TN>(acc, M, Nq, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, part + (int64_t)blockIdx.z * M * Nq);
+
+    // accumulator element r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its 32 x 32 tile
+    float* out = part + (int64_t)blockIdx.z * M * Nq;
+    const int row0 = m0 + a0 + 4 * lk;
+    each<TN>([&](auto at) {
+        constexpr int j = decltype(at)::value;
+        const int col = n0 + b0 + j * 32 + lrow;
+        float turn = sign ? -1.0f : 1.0f;
+        if (redo_tile(acc[j], 0.0f, 0.0f)) {
+            // the tile once more with the float32 instruction, operands straight from memory
+            const float* pp = P + min(m0 + a0 + lrow, M - 1);
+            const float* qp = Q + min(col, Nq - 1);
+            f32x16 x;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+            for (int64_t k = k_begin + lk; k - lk < k_end; k += 2) {
+                const bool in = k < k_end;
+                const int64_t kc = in ? k : k_begin;
+                const float a = pp[kc * ldp], b = qp[kc * ldq];
+                x = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a : 0.0f, in ? b : 0.0f, x, 0, 0, 0);
+            }
+            acc[j] = x;
+            turn = 1.0f;
+        }
+        if (col >= Nq) return;
+        float* p = out + (int64_t)row0 * Nq + col;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int ro = 8 * (r / 4) + (r % 4);
+            if (row0 + ro < M) p[(int64_t)ro * Nq] = turn * acc[j][r];
+        }
+    });
 }
 
-// Any shape: every element fetched under its own check.
-template <int BM, int BN, int WGM, int WGN, bool PV, bool QV>
-__global__ __launch_bounds__(256, 2) void wgrad_kernel(
-    int64_t K, int M, int Nq, const float* __restrict__ P, int64_t ldp,
-    const float* __restrict__ Q, int64_t ldq, int64_t k_chunk, float* __restrict__ part)
-{
-    static_assert(WGM * WGN == 4, "four waves per workgroup");
-    constexpr int TM = BM / (32 * WGM);
-    constexpr int TN = BN / (32 * WGN);
-    constexpr int LDA = BM + 4;
-    constexpr int LDB = BN + 4;
-    constexpr int A_F4 = (BM * BK / 4 + 255) / 256;
-    constexpr int B_F4 = (BN * BK / 4 + 255) / 256;
-
-    __shared__ float As[2][BK][LDA];
-    __shared__ float Bs[2][BK][LDB];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int m0 = blockIdx.x * BM;
-    const int n0 = blockIdx.y * BN;
-    const int64_t k_begin = (int64_t)blockIdx.z * k_chunk;
-    const int64_t k_end = min(K, k_begin + k_chunk);
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    float ra[A_F4][4], rb[B_F4][4];
-    int wa[A_F4], wb[B_F4];
-
-    auto load_tiles = [&](int kt) {
-#pragma unroll
-        for (int i = 0; i < A_F4; ++i) {
-            const int id = tid + i * 256;
-            if (BM * BK / 4 % 256 != 0 && id >= BM * BK / 4) continue;
-            const int kk = id / (BM / 4), m4 = id % (BM / 4);
-            const int64_t k = k_begin + (int64_t)kt * BK + kk;
-            const int m = m0 + m4 * 4;
-            wa[i] = k < k_end ? M - m : 0;
-            load4<PV>(P, k * ldp + m, wa[i], ra[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < B_F4; ++i) {
-            const int id = tid + i * 256;
-            if (BN * BK / 4 % 256 != 0 && id >= BN * BK / 4) continue;
-            const int kk = id / (BN / 4), n4 = id % (BN / 4);
-            const int64_t k = k_begin + (int64_t)kt * BK + kk;
-            const int n = n0 + n4 * 4;
-            wb[i] = k < k_end ? Nq - n : 0;
-            load4<QV>(Q, k * ldq + n, wb[i], rb[i]);
-        }
-    };
-    auto store_tiles = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < A_F4; ++i) {
-            const int id = tid + i * 256;
-            if (BM * BK / 4 % 256 != 0 && id >= BM * BK / 4) continue;
-            const int kk = id / (BM / 4), m4 = id % (BM / 4);
-            zero4<PV>(wa[i], ra[i]);
-            f32x4 t = {ra[i][0], ra[i][1], ra[i][2], ra[i][3]};
-            *reinterpret_cast<f32x4*>(&As[buf][kk][m4 * 4]) = t;
-        }
-#pragma unroll
-        for (int i = 0; i < B_F4; ++i) {
-            const int id = tid + i * 256;
-            if (BN * BK / 4 % 256 != 0 && id >= BN * BK / 4) continue;
-            const int kk = id / (BN / 4), n4 = id % (BN / 4);
-            zero4<QV>(wb[i], rb[i]);
-            f32x4 t = {rb[i][0], rb[i][1], rb[i][2], rb[i][3]};
-            *reinterpret_cast<f32x4*>(&Bs[buf][kk][n4 * 4]) = t;
-        }
-    };
-
-    const int lrow = lane & 31, lk = lane >> 5;
-    const int nk = (int)((k_end - k_begin + BK - 1) / BK);
-    if (nk > 0) {
-        load_tiles(0);
-        store_tiles(0);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load_tiles(kt + 1);
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            float af[TM], bf[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = As[buf][kk + lk][wm * TM * 32 + i * 32 + lrow];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bf[j] = Bs[buf][kk + lk][wn * TN * 32 + j * 32 + lrow];
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
-        }
-        if (kt + 1 < nk) store_tiles(buf ^ 1);
-        __syncthreads();
-    }
-
-    write_partial<TM, TN>(acc, M, Nq, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, part + (int64_t)blockIdx.z * M * Nq);
-}
-
-// out[m][n] = sum_z part[z][m][n] for n < n_keep (partials are Nq wide).  A workgroup owns 64 outputs; its four
-// waves each add a quarter of the z range with four running sums (z mod 4), and the sixteen sums of an output
-// are combined in a fixed order: the result does not depend on the launch, and with few outputs and hundreds of
-// partials (a classifier's gradient) the additions no longer wait for one load at a time.
-__global__ __launch_bounds__(kThreads) void reduce_partials(
-    int S, int M, int Nq, int n_keep, const float* __restrict__ part, float* __restrict__ out)
+// out[i] = sum_z part[z][i], i < total.  A workgroup owns 64 outputs; its four waves each add a quarter of the z
+// range with four running sums (z mod 4), and the sixteen sums of an output are combined in a fixed order: the
+// result does not depend on the launch, and with few outputs and hundreds of partials (a classifier's gradient) the
+// additions do not wait for one load at a time.
+__global__ __launch_bounds__(kThreads) void reduce_partials(int S, int64_t total, const float* __restrict__ part,
+                                                            float* __restrict__ out)
 {
     __shared__ float sh[kThreads / 64][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + lane;
-    const bool live = i < (int64_t)M * n_keep;
     float s = 0.0f;
-    if (live) {
-        const int m = (int)(i / n_keep), n = (int)(i % n_keep);
+    if (i < total) {
         const int per = (S + 3) / 4;
         const int z0 = wave * per, z1 = min(S, z0 + per);
-        const float* p = part + (int64_t)m * Nq + n;
-        const int64_t pitch = (int64_t)M * Nq;
+        const float* p = part + i;
         float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         int z = z0;
         for (; z + 4 <= z1; z += 4) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) q[k] += p[(int64_t)(z + k) * pitch];
+            for (int k = 0; k < 4; ++k) q[k] += p[(int64_t)(z + k) * total];
         }
-        for (int k = 0; z < z1; ++z, ++k) q[k] += p[(int64_t)z * pitch];
+        for (int k = 0; z < z1; ++z, ++k) q[k] += p[(int64_t)z * total];
         s = (q[0] + q[1]) + (q[2] + q[3]);
     }
     sh[wave][lane] = s;
     __syncthreads();
-    if (wave == 0 && live) out[i] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+    if (wave == 0 && i < total) out[i] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
 }
 
 struct TrainHeader {
@@ -568,7 +382,7 @@ Split choose_split(int64_t K, int64_t M, int64_t Nq, int bn)
     if (S > max_s) S = max_s;
     if (S < 1) S = 1;
     int64_t chunk = (K + S - 1) / S;
-    chunk = (chunk + BK - 1) / BK * BK;
+    chunk = (chunk + kTileK - 1) / kTileK * kTileK;
     S = (K + chunk - 1) / chunk;
     if (S < 1) S = 1;
     return {(int)S, chunk};
@@ -576,38 +390,23 @@ Split choose_split(int64_t K, int64_t M, int64_t Nq, int bn)
 
 int bn_for(int64_t Nq) { return Nq <= 32 ? 32 : Nq <= 64 ? 64 : Nq <= 128 ? 128 : 256; }
 
-template <int BN, int WGM, int WGN>
-void launch_wgrad_bn(int64_t K, int64_t M, int64_t Nq, const float* P, int64_t ldp, const float* Q, int64_t ldq,
-                     Split sp, float* part, hipStream_t stream)
-{
-    const bool pv = (uintptr_t)P % 16 == 0 && ldp % 4 == 0 && M % 4 == 0;
-    const bool qv = (uintptr_t)Q % 16 == 0 && ldq % 4 == 0 && Nq % 4 == 0;
-    dim3 grid((unsigned)((M + 127) / 128), (unsigned)((Nq + BN - 1) / BN), (unsigned)sp.S);
-    if (pv && qv && M >= 4 && Nq >= 4)
-        wgrad_pipe_kernel<128, BN, WGM, WGN><<<grid, dim3(256), 0, stream>>>(K, (int)M, (int)Nq, P, ldp, Q, ldq, sp.k_chunk, part);
-    else if (pv && qv)
-        wgrad_kernel<128, BN, WGM, WGN, true, true><<<grid, dim3(256), 0, stream>>>(K, (int)M, (int)Nq, P, ldp, Q, ldq, sp.k_chunk, part);
-    else if (pv)
-        wgrad_kernel<128, BN, WGM, WGN, true, false><<<grid, dim3(256), 0, stream>>>(K, (int)M, (int)Nq, P, ldp, Q, ldq, sp.k_chunk, part);
-    else if (qv)
-        wgrad_kernel<128, BN, WGM, WGN, false, true><<<grid, dim3(256), 0, stream>>>(K, (int)M, (int)Nq, P, ldp, Q, ldq, sp.k_chunk, part);
-    else
-        wgrad_kernel<128, BN, WGM, WGN, false, false><<<grid, dim3(256), 0, stream>>>(K, (int)M, (int)Nq, P, ldp, Q, ldq, sp.k_chunk, part);
-}
-
-// out[M][n_keep] = P^T Q, Q being Nq (>= n_keep) columns wide
-void wgrad(int64_t K, int64_t M, int64_t Nq, int64_t n_keep, const float* P, int64_t ldp, const float* Q,
-           int64_t ldq, float* part, float* out, hipStream_t stream)
+// out[M][Nq] = P^T Q
+void wgrad(int64_t K, int64_t M, int64_t Nq, const float* P, int64_t ldp, const float* Q, int64_t ldq, float* part,
+           float* out, hipStream_t stream)
 {
     const int bn = bn_for(Nq);
     const Split sp = choose_split(K, M, Nq, bn);
-    if (bn == 32) launch_wgrad_bn<32, 4, 1>(K, M, Nq, P, ldp, Q, ldq, sp, part, stream);
-    else if (bn == 64) launch_wgrad_bn<64, 4, 1>(K, M, Nq, P, ldp, Q, ldq, sp, part, stream);
-    else if (bn == 128) launch_wgrad_bn<128, 2, 2>(K, M, Nq, P, ldp, Q, ldq, sp, part, stream);
-    else launch_wgrad_bn<256, 2, 2>(K, M, Nq, P, ldp, Q, ldq, sp, part, stream);
-    const int64_t total = M * n_keep;
-    reduce_partials<<<dim3((unsigned)((total + 63) / 64)), dim3(kThreads), 0, stream>>>(
-        sp.S, (int)M, (int)Nq, (int)n_keep, part, out);
+    dim3 grid((unsigned)((M + 127) / 128), (unsigned)((Nq + bn - 1) / bn), (unsigned)sp.S);
+    auto go = [&](auto width) {
+        constexpr int BN = decltype(width)::value;
+        wgrad_kernel<BN><<<grid, dim3(64 * wgrad_waves<BN>), 0, stream>>>(K, (int)M, (int)Nq, P, ldp, Q, ldq, sp.k_chunk, part);
+    };
+    if (bn == 32)       go(std::integral_constant<int, 32>{});
+    else if (bn == 64)  go(std::integral_constant<int, 64>{});
+    else if (bn == 128) go(std::integral_constant<int, 128>{});
+    else                go(std::integral_constant<int, 256>{});
+    const int64_t total = M * Nq;
+    reduce_partials<<<dim3((unsigned)((total + 63) / 64)), dim3(kThreads), 0, stream>>>(sp.S, total, part, out);
 }
 
 void colsum(int64_t N, int64_t C, const float* D, int64_t ld, float* part, float* out, hipStream_t stream)
@@ -729,7 +528,9 @@ int layer_grad_impl(int64_t N, int64_t D_in, int64_t H, int64_t C,
     const float* feat = d_X;        // input of the classifier product
     int64_t ldfeat = ldx, dfeat = D_in;
     if (H > 0) {
-        if (int e = launch_transform(N, D_in, H, d_X, ldx, d_W1, d_b1, true, A, t.ldh, stream)) return e;
+        // Which units are on goes into every gradient behind them; units whose sum is within rounding of zero are
+        // decided by the float32 sums, so that a model trains the same however the products are formed.
+        if (int e = launch_transform(N, D_in, H, d_X, ldx, d_W1, d_b1, true, A, t.ldh, stream, nullptr, 0, true)) return e;
         if (p_drop > 0.0f) {
             const uint32_t threshold = (uint32_t)((double)p_drop * 4294967296.0);
             const int64_t quads = N * ((H + 3) / 4);
@@ -752,7 +553,7 @@ int layer_grad_impl(int64_t N, int64_t D_in, int64_t H, int64_t C,
     // classifier (or only) layer: weight and bias gradients
     float* gW_top = H > 0 ? d_gWc : d_gW1;
     float* gb_top = H > 0 ? d_gbc : d_gb1;
-    wgrad(N, dfeat, t.ldc, C, feat, ldfeat, L, t.ldc, part, gW_top, stream);
+    wgrad(N, dfeat, C, feat, ldfeat, L, t.ldc, part, gW_top, stream);
     colsum(N, C, L, t.ldc, colpart, gb_top, stream);
 
     if (H > 0) {
@@ -764,8 +565,7 @@ int layer_grad_impl(int64_t N, int64_t D_in, int64_t H, int64_t C,
         transpose_kernel<<<dim3((unsigned)((tot + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
             (int)H, (int)C, (int)t.ldc, d_Wc, WcT, keep_scale);
         if (int e = launch_transform(N, t.ldc, H, L, t.ldc, WcT, nullptr, false, dA, t.ldh, stream, A, t.ldh)) return e;
-        // (padding columns of dA only produce partial columns that reduce_partials never reads)
-        wgrad(N, D_in, t.ldh, H, d_X, ldx, dA, t.ldh, part, d_gW1, stream);
+        wgrad(N, D_in, H, d_X, ldx, dA, t.ldh, part, d_gW1, stream);
         colsum(N, H, dA, t.ldh, colpart, d_gb1, stream);
         if (d_gX) {
             // dL/dX = dA W1^T, contracted over exactly H columns (dA's padding columns are not written)
@@ -857,7 +657,7 @@ extern "C" int retexo_transform_backward(int64_t N, int64_t D_in, int64_t D_out,
         return RETEXO_OK;
     }
     char* ws = (char*)d_workspace;
-    wgrad(N, D_in, D_out, D_out, d_H, ldh, d_dZ, lddz, (float*)(ws + t.part), d_gW, stream);
+    wgrad(N, D_in, D_out, d_H, ldh, d_dZ, lddz, (float*)(ws + t.part), d_gW, stream);
     if (d_gb) colsum(N, D_out, d_dZ, lddz, (float*)(ws + t.colpart), d_gb, stream);
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
     return RETEXO_OK;

@@ -2,38 +2,40 @@
 // the f of Eq. 1, evaluated for every node once a layer has been trained.
 //
 // This is the one dense contraction on the path, so it runs on the matrix
-// cores in full fp32 (v_mfma_f32_32x32x2_f32: a 32x32 output tile, two k per
-// instruction, fp32 multiply and accumulate) — reduced-precision matrix
-// formats would not meet the 1e-5 bound.
+// cores: every float32 as three bf16 values, six exact products of them per
+// product, summed in float32 (tiles.hpp).  What is left out is below the
+// rounding of a float32 sum, and the sum itself is rounded less often.  Error
+// against 64 bits (2-norm, normal inputs; v_mfma_f32_32x32x2_f32, which carried
+// this product before, in brackets): K = 100 0.6e-7 (1.8e-7), K = 256 0.9e-7
+// (2.9e-7), K = 1204 2.0e-7 (6.2e-7), K = 2866 3.3e-7 (9.6e-7); 512 rectified
+// columns 1.0e-7 (2.8e-7).
 //
-// Tiling.  A workgroup of 4 waves owns a BM x BN output tile with BN >= D_out
-// whenever D_out <= 256, so H — by far the larger operand — is read from HBM
-// exactly once.  The K loop moves BK = 16 columns of H and rows of W per step
-// through LDS, both stored k-major so that the MFMA operand of lane l
-// (row l%32, k = l/32) is a conflict-free consecutive read.
+// Tiling.  A workgroup owns a 128 x BN output tile with BN >= D_out whenever
+// D_out <= 256, so H — by far the larger operand — is read from HBM exactly
+// once.  The K loop moves 16 columns of H and rows of W per step through LDS, as
+// bf16 parts in the layout of the matrix operands.  Tiles wider than 128 run
+// eight waves, one workgroup per CU (212 registers, 75 KB of LDS), narrower ones
+// four waves and two to four workgroups.  W is split by every workgroup again: the
+// call has no scratch memory to keep its parts in.
 //
-// Schedule.  One wave keeps a matrix core busy only if nothing else in its
-// instruction stream takes longer than one MFMA (64 cycles), so all staging
-// work is cut into pieces of that size and placed between the MFMAs of the
-// wave that does it: the operand reads of the next k-step after the first MFMA
-// of a step, then one slice per step of "write the next tile to the other LDS
-// buffer" and "fetch the tile after that into registers".  Global loads
-// therefore have a whole K step of MFMAs (4096 cycles) to arrive, and the one
-// barrier per K step sits between the last two k-steps, whose operands are
-// already in registers.  Sources are clamped instead of checked (rows past the
-// end repeat the last row, columns past D_out repeat the last four), so the
-// loop carries no selects; only a partial last K tile takes a checked form
-// (and the k-steps of it that hold nothing but zero fill are skipped: D_in =
-// 100 issues 50 k-steps, not 56).  Bias and ReLU are applied to the
-// accumulators on the way out: through this wave's piece of the dead tiles in
-// LDS and from there as 16-byte pieces of rows where the output allows it,
-// otherwise through one pointer per 32x32 tile that walks down the rows.
+// What bounds the wide tiles is power and the change between loading and storing:
+// the matrix instructions run at a clock of about 1.5 GHz (GRBM_GUI_ACTIVE), the
+// same launch on zeros is 25 % faster, and a bf16 library product of 8192^3
+// reaches 1210-1270 TFLOP/s where this kernel issues 900-1000.  Measured (float32
+// instructions before): 2,449,029 x 256 -> 256 2.15 ms = 149 TFLOP/s (2.60 ms),
+// 232,965 x 1204 -> 256 0.87 ms = 166 (1.28), 2,449,029 x 256 -> 188 1.74 ms (1.98),
+// 232,965 x 512 -> 41 0.137 ms = 3.8 TB/s (0.171), 100,000 x 512 -> 128 94 us (150).
 //
-// W rows that are not multiples of 16 bytes (41, 47, 7 output columns) keep
-// this kernel and fetch W, the small operand, element by element; H rows that
-// cannot be fetched as aligned 16-byte pieces take the simple kernel below it
-// (same arithmetic, same order, checked scalar loads).  Matrices of few rows
-// take the few-rows kernel at the end (K split over the waves of a workgroup).
+// Sources are clamped instead of checked (rows past the end repeat the last
+// row, columns past D_out the last column), so the loop carries no selects;
+// only a partial last K tile takes a checked form.  Loads are four bytes wide
+// (W) or 16 bytes at any float's address (H), so every alignment and leading
+// dimension takes this kernel, in one order of arithmetic.  Bias and ReLU are
+// applied to the accumulators on the way out: through this wave's piece of the
+// dead tiles in LDS and from there as 16-byte pieces of rows where the output
+// allows it, otherwise through one pointer per 32x32 tile that walks down the
+// rows.  Matrices of few rows take the few-rows kernel at the end (K split over
+// the waves of a workgroup).
 #include "common.hpp"
 #include "tiles.hpp"
 
@@ -41,13 +43,11 @@
 
 namespace {
 
-constexpr int BK = kTileK;
-
 // Bias, ReLU, optional mask and store of the accumulators of one wave.
 // Accumulator element r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its tile.
 // Only the last row block of the matrix checks rows.
-template <int TM, int TN, bool MASKED>
-__device__ __forceinline__ void write_out(const f32x16 (&acc)[TM][TN], const float (&bv)[TN], int64_t N, int D_out,
+template <int TN, bool MASKED>
+__device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (&bv)[TN], int64_t N, int D_out,
                                           int64_t row_base, int col_base, int lane, int relu,
                                           float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm,
                                           bool whole_block)
@@ -59,28 +59,25 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TM][TN], const flo
         for (int j = 0; j < TN; ++j) {
             const int col = col_base + j * 32 + lrow;
             if (col >= D_out) continue;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int64_t row0 = row_base + i * 32 + 4 * lk;
-                float* p = Z + row0 * ldz + col;
-                float mv[16];
-                if constexpr (MASKED) {
-                    // backward of a ReLU layer: the value passes only where the forward activation was positive
-                    const float* pm = mask + row0 * ldm + col;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int ro = 8 * (r / 4) + (r % 4);
-                        mv[r] = (FULL || row0 + ro < N) ? pm[ro * ldm] : 0.0f;
-                    }
-                }
+            const int64_t row0 = row_base + 4 * lk;
+            float* p = Z + row0 * ldz + col;
+            float mv[16];
+            if constexpr (MASKED) {
+                // backward of a ReLU layer: the value passes only where the forward activation was positive
+                const float* pm = mask + row0 * ldm + col;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int ro = 8 * (r / 4) + (r % 4);
-                    float x = acc[i][j][r] + bv[j];
-                    if (relu) x = fmaxf(x, 0.0f);
-                    if constexpr (MASKED) x = mv[r] > 0.0f ? x : 0.0f;
-                    if (FULL || row0 + ro < N) p[ro * ldz] = x;
+                    mv[r] = (FULL || row0 + ro < N) ? pm[ro * ldm] : 0.0f;
                 }
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int ro = 8 * (r / 4) + (r % 4);
+                float x = acc[j][r] + bv[j];
+                if (relu) x = fmaxf(x, 0.0f);
+                if constexpr (MASKED) x = mv[r] > 0.0f ? x : 0.0f;
+                if (FULL || row0 + ro < N) p[ro * ldz] = x;
             }
         }
     };
@@ -92,8 +89,8 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TM][TN], const flo
 // D_out multiples of four): each 32 x CW block of results goes through this wave's own piece of LDS (T, 32 rows
 // of CW + 4 floats; the K loop's tiles are dead by then) and leaves as whole 16-byte pieces of rows, four times
 // fewer store instructions, each covering full cache lines.  Same values as write_out.
-template <int TM, int TN, int CW, bool MASKED>
-__device__ __forceinline__ void write_out_rows(const f32x16 (&acc)[TM][TN], const float (&bv)[TN], int64_t N, int D_out,
+template <int TN, int CW, bool MASKED>
+__device__ __forceinline__ void write_out_rows(const f32x16 (&acc)[TN], const float (&bv)[TN], int64_t N, int D_out,
                                                int64_t row_base, int col_base, int lane, int relu,
                                                float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm,
                                                float* __restrict__ T)
@@ -106,353 +103,167 @@ __device__ __forceinline__ void write_out_rows(const f32x16 (&acc)[TM][TN], cons
     const int lrow = lane & 31, lk = lane >> 5;
     const int c4 = (lane % LPR) * 4, rsub = lane / LPR;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int j0 = 0; j0 < TN; j0 += JT) {
 #pragma unroll
-        for (int j0 = 0; j0 < TN; j0 += JT) {
+        for (int jj = 0; jj < JT; ++jj)
 #pragma unroll
-            for (int jj = 0; jj < JT; ++jj)
+            for (int r = 0; r < 16; ++r) {
+                const int ro = 8 * (r / 4) + (r % 4) + 4 * lk;
+                float x = acc[j0 + jj][r] + bv[j0 + jj];
+                if (relu) x = fmaxf(x, 0.0f);
+                T[ro * P + jj * 32 + lrow] = x;
+            }
+        const int col = col_base + j0 * 32 + c4;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int ro = 8 * (r / 4) + (r % 4) + 4 * lk;
-                    float x = acc[i][j0 + jj][r] + bv[j0 + jj];
-                    if (relu) x = fmaxf(x, 0.0f);
-                    T[ro * P + jj * 32 + lrow] = x;
+        for (int s = 0; s < 32 / RPI; ++s) {
+            const int rr = s * RPI + rsub;
+            f32x4 v = *reinterpret_cast<const f32x4*>(&T[rr * P + c4]);
+            const int64_t row = row_base + rr;
+            if (row < N && col < D_out) {
+                if constexpr (MASKED) {
+                    const f32x4 m = *reinterpret_cast<const f32x4*>(mask + row * ldm + col);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = m[q] > 0.0f ? v[q] : 0.0f;
                 }
-            const int col = col_base + j0 * 32 + c4;
-#pragma unroll
-            for (int s = 0; s < 32 / RPI; ++s) {
-                const int rr = s * RPI + rsub;
-                f32x4 v = *reinterpret_cast<const f32x4*>(&T[rr * P + c4]);
-                const int64_t row = row_base + i * 32 + rr;
-                if (row < N && col < D_out) {
-                    if constexpr (MASKED) {
-                        const f32x4 m = *reinterpret_cast<const f32x4*>(mask + row * ldm + col);
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) v[q] = m[q] > 0.0f ? v[q] : 0.0f;
-                    }
-                    *reinterpret_cast<f32x4*>(Z + row * ldz + col) = v;
-                }
+                *reinterpret_cast<f32x4*>(Z + row * ldz + col) = v;
             }
         }
     }
 }
 
-// Aligned shapes: H rows are multiples of 16 bytes at 16-byte aligned addresses.  WVEC: so are the rows of W
-// (D_out % 4 == 0, D_out >= 4); otherwise W — the small operand, resident in L2 — is fetched element by element
-// (same tiles, same order of arithmetic), which lets classifier-width outputs (41, 47, 7 columns) use this kernel
-// and its two-tiles-ahead prefetch of H instead of the simple kernel below.
+// The block kernel: 128 x BN outputs per workgroup, 32 rows and up to 128 columns per wave (whose two running sums then
+// take 128 registers): four waves, or eight for the tiles wider than 128; any alignment and leading dimension.
 // ZVEC: the output (and the mask) allow 16-byte stores, see write_out_rows.
-template <int BM, int BN, int WGM, int WGN, bool MASKED, bool WVEC = true, bool ZVEC = false>
-__global__ __launch_bounds__(256, 2) void transform_kernel(
+template <int BN> constexpr int transform_waves = BN > 128 ? 8 : 4;
+template <int BN, bool MASKED, bool ZVEC>
+__global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 : 2) void transform_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
-    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm)
+    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm, int keep_sign)
 {
-    static_assert(WGM * WGN == 4, "four waves per workgroup");
-    constexpr int TM = BM / (32 * WGM);
-    constexpr int TN = BN / (32 * WGN);
-    constexpr int LDA = BM + 2;
-    constexpr int LDB = BN + 4;
-    constexpr int A_F4 = BM * BK / 4 / 256;
-    constexpr int B_F4 = (BN * BK / 4 + 255) / 256;
-    constexpr bool B_PART = BN * BK / 4 % 256 != 0;
-    static_assert(A_F4 >= 1, "tile shape");
-    // row-wise epilogue: 64 columns per pass where the tiles leave room for four waves' 32 x 68 blocks, else 32
-    constexpr int CW = (TN % 2 == 0 && 2 * BK * (LDA + LDB) >= 4 * 32 * 68) ? 64 : 32;
-    static_assert(2 * BK * (LDA + LDB) >= 4 * 32 * (CW + 4), "the epilogue's blocks fit in the tiles' memory");
-
-    __shared__ __align__(16) float lds[2 * BK * (LDA + LDB)];
-    float (*As)[BK][LDA] = reinterpret_cast<float (*)[BK][LDA]>(lds);
-    float (*Bs)[BK][LDB] = reinterpret_cast<float (*)[BK][LDB]>(lds + 2 * BK * LDA);
+    constexpr int BM = 128, WAVES = transform_waves<BN>, WN = BN / (WAVES / 4), TN = WN / 32;
+    using T = SplitTile<BM, BN>;
+    using WStage = KMajorStage<BN, WAVES>;
+    constexpr int HW = BM * kTileK / (64 * WAVES);       // floats of H a thread stages
+    // row-wise epilogue: 64 columns per pass where the tiles leave room for every wave's 32 x 68 block, else 32
+    constexpr int CW = (TN % 2 == 0 && 2 * T::units * 4 >= WAVES * 32 * 68) ? 64 : 32;
+    static_assert(2 * T::units * 4 >= WAVES * 32 * (CW + 4), "the epilogue's blocks fit in the tiles' memory");
+    __shared__ u32x4 lds[2 * T::units];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int a0 = wave % 4 * 32, b0 = wave / 4 * WN;    // the wave's rows and columns of the tile
     const int64_t m0 = (int64_t)blockIdx.x * BM;
     const int n0 = blockIdx.y * BN;
-    const int lrow = lane & 31;
+    const int lrow = lane & 31, lk = lane >> 5;
 
-    f32x16 acc[TM][TN];
+    f32x16 acc[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
 
-    // per-thread source pointers; rows past the end and columns past D_out are clamped to the
-    // last valid ones (their products land in outputs that are never stored)
-    const float* pa[A_F4];
-    const float* pb[B_F4];
-    int ka[A_F4], kb[B_F4];                   // k offset of the thread's element inside a tile
+    // H: a thread stages HW consecutive k of one row (rows past the end repeat the last one, never stored)
+    const int hr = tid / (kTileK / HW), hk = tid % (kTileK / HW) * HW;
+    const float* ph = H + (m0 + hr < N ? m0 + hr : N - 1) * ldh;
+    float ra[HW];
+    auto fetch_h = [&](int kt) {
+        const int k = kt * kTileK + hk;
+        if ((kt + 1) * kTileK <= D_in) {
 #pragma unroll
-    for (int i = 0; i < A_F4; ++i) {
-        const int id = tid + i * 256;
-        const int r = id / 4, k4 = id % 4;
-        int64_t row = m0 + r;
-        row = row < N ? row : N - 1;
-        pa[i] = H + row * ldh + k4 * 4;
-        ka[i] = k4 * 4;
-    }
-    int cb[B_F4][4];                          // !WVEC: column offsets of the four elements from pb (clamped to the last column)
+            for (int v = 0; v < HW / 4; ++v) {
+                const f32x4 t = *reinterpret_cast<const f32x4_any*>(ph + k + 4 * v);
 #pragma unroll
-    for (int i = 0; i < B_F4; ++i) {
-        const int id = tid + i * 256;
-        const int kk = (id / (BN / 4)) % BK, n4 = id % (BN / 4);
-        int n = n0 + n4 * 4;
-        if constexpr (WVEC) {
-            n = n < D_out - 4 ? n : D_out - 4;
-            pb[i] = W + (int64_t)kk * D_out + n;
-        } else {
-            pb[i] = W + (int64_t)kk * D_out;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) cb[i][q] = n + q < D_out ? n + q : D_out - 1;
-        }
-        kb[i] = kk;
-    }
-    const int64_t step_b = (int64_t)BK * D_out;
-
-    f32x4 ra[A_F4], rb[B_F4];
-    const int nk = (D_in + BK - 1) / BK;
-    const int k_tail = D_in % BK;             // > 0: the last tile is partly outside the matrix
-
-    // fetch tile kt into the staging registers; the partial last tile takes the checked form
-    auto fetch_a = [&](int kt) {
-        if (k_tail && kt == nk - 1) {
-#pragma unroll
-            for (int i = 0; i < A_F4; ++i) {
-                const bool in = ka[i] < k_tail;
-                const f32x4 t = *reinterpret_cast<const f32x4*>(in ? pa[i] : H);
-                ra[i] = in ? t : f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int q = 0; q < 4; ++q) ra[4 * v + q] = t[q];
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < A_F4; ++i) ra[i] = *reinterpret_cast<const f32x4*>(pa[i]);
+            for (int q = 0; q < HW; ++q) ra[q] = k + q < D_in ? ph[k + q] : 0.0f;
         }
-#pragma unroll
-        for (int i = 0; i < A_F4; ++i) pa[i] += BK;
     };
-    auto fetch_b = [&](int kt) {
-        if constexpr (!WVEC) {
-            const bool tail = k_tail && kt == nk - 1;
-#pragma unroll
-            for (int i = 0; i < B_F4; ++i) {
-                const bool in = !tail || kb[i] < k_tail;
-                const float* row = in ? pb[i] : W;
-                f32x4 t;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) t[q] = row[cb[i][q]];
-                rb[i] = in ? t : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        } else if (k_tail && kt == nk - 1) {
-#pragma unroll
-            for (int i = 0; i < B_F4; ++i) {
-                const bool in = kb[i] < k_tail;
-                const f32x4 t = *reinterpret_cast<const f32x4*>(in ? pb[i] : W);
-                rb[i] = in ? t : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < B_F4; ++i) rb[i] = *reinterpret_cast<const f32x4*>(pb[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < B_F4; ++i) pb[i] += step_b;
-    };
-    auto put_a = [&](int buf, int i) {
-        const int id = tid + i * 256;
-        const int r = id / 4, k4 = id % 4;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) As[buf][k4 * 4 + q][r] = ra[i][q];
-    };
-    auto put_b = [&](int buf, int i) {
-        const int id = tid + i * 256;
-        if (B_PART && id >= BN * BK / 4) return;
-        const int kk = id / (BN / 4), n4 = id % (BN / 4);
-        *reinterpret_cast<f32x4*>(&Bs[buf][kk][n4 * 4]) = rb[i];
-    };
+    WStage sw;
+    sw.init(W, D_out, 0, D_in, n0, D_out, wave, lane);
 
     float bv[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const int col = n0 + wn * TN * 32 + j * 32 + lrow;
+        const int col = n0 + b0 + j * 32 + lrow;
         bv[j] = (bias && col < D_out) ? bias[col] : 0.0f;
     }
 
-    // prologue: tile 0 -> LDS, tile 1 -> staging registers
-    fetch_a(0);
-    fetch_b(0);
+    const int nk = (D_in + kTileK - 1) / kTileK;
+    constexpr int A_MICROS = HW / 2 + 2, MICROS = A_MICROS + WStage::count * WStage::steps;
+    typedef uint32_t part_t __attribute__((ext_vector_type(HW / 2)));
+    part_t part_h[3];
+    auto micro = [&](auto step, int buf, int kt) {
+        constexpr int m = decltype(step)::value;
+        u32x4* base = lds + buf * T::units;
+        if constexpr (m >= A_MICROS) {
+            sw.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, 0u, kt + 1 < nk, kt + 1);
+        } else if constexpr (m < HW / 2) {
+            split_pair(ra[2 * m], ra[2 * m + 1], m, part_h);
+        } else if constexpr (m == HW / 2) {
 #pragma unroll
-    for (int i = 0; i < A_F4; ++i) put_a(0, i);
-#pragma unroll
-    for (int i = 0; i < B_F4; ++i) put_b(0, i);
-    if (nk > 1) { fetch_a(1); fetch_b(1); }
-    __syncthreads();
-
-    // thirds of "staged tile -> LDS": the A pieces, the first B piece, the other B pieces
-    auto put = [&](int buf, int third) {
-        if (third == 0) {
-            put_a(buf, 0);
-            if (A_F4 > 1) put_a(buf, 1);
-        } else if (third == 1) {
-#pragma unroll
-            for (int x = 2; x < A_F4; ++x) put_a(buf, x);
-            put_b(buf, 0);
+            for (int s = 0; s < 3; ++s)
+                *reinterpret_cast<part_t*>(reinterpret_cast<char*>(base + T::a(s, hk >> 3, hr)) + (hk & 7) * 2) = part_h[s];
         } else {
-#pragma unroll
-            for (int x = 1; x < B_F4; ++x) put_b(buf, x);
+            if (kt + 1 < nk) fetch_h(kt + 1);
         }
     };
-    auto fetch = [&](int kt, int half) {
-        if (half == 0) fetch_a(kt);
-        else fetch_b(kt);
-    };
-    mfma_k_loop<TM, TN, LDA, LDB>(acc, As, Bs, nk, wm * TM * 32, wn * TN * 32, lane, put, fetch,
-                                  k_tail ? (k_tail + 1) / 2 : BK / 2);
+    fetch_h(0);
+    each<WStage::count>([&](auto i) { sw.template fetch<decltype(i)::value>(0); });
+    each<MICROS>([&](auto m) { micro(m, 0, 0); });
+    __syncthreads();
+    split_k_loop<TN, BM, BN, MICROS>(acc, lds, nk, a0, b0, lane, micro);
+
+    // how close to zero a sum is decided by the float32 instruction: 2^-18 of the wave's largest one, twenty times what
+    // the two were seen apart
+    float near = 0.0f;
+    if (keep_sign) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) near = fmaxf(near, __builtin_fabsf(acc[j][r]));
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) near = fmaxf(near, __shfl_xor(near, m, 64));
+        near *= 0x1p-18f;
+    }
+    each<TN>([&](auto at) {
+        constexpr int j = decltype(at)::value;
+        if (!redo_tile(acc[j], bv[j], near)) return;
+        // the tile once more with the float32 instruction, operands straight from memory, k in ascending pairs
+        const int64_t row = m0 + a0 + lrow;
+        const int col = n0 + b0 + j * 32 + lrow;
+        const float* hp = H + (row < N ? row : N - 1) * ldh;
+        const float* wp = W + (col < D_out ? col : D_out - 1);
+        f32x16 x;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+        constexpr int U = 8;
+        for (int k0 = 0; k0 < D_in; k0 += 2 * U) {
+            float a[U], b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + 2 * u + lk;
+                const bool in = k < D_in;
+                const float av = hp[in ? k : 0], bw = wp[(int64_t)(in ? k : 0) * D_out];
+                a[u] = in ? av : 0.0f;
+                b[u] = in ? bw : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], x, 0, 0, 0);
+        }
+        acc[j] = x;
+    });
 
     if constexpr (ZVEC) {
         __syncthreads();                      // every wave is done with the last tile
-        write_out_rows<TM, TN, CW, MASKED>(acc, bv, N, D_out, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, relu, Z, ldz,
-                                           mask, ldm, lds + wave * 32 * (CW + 4));
+        write_out_rows<TN, CW, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm,
+                                       reinterpret_cast<float*>(lds) + wave * 32 * (CW + 4));
     } else {
-        write_out<TM, TN, MASKED>(acc, bv, N, D_out, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, relu, Z, ldz, mask, ldm,
-                                  m0 + BM <= N);
+        write_out<TN, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm, m0 + BM <= N);
     }
-}
-
-// Any shape: every element is fetched under its own check (HV / WV: the rows of H / W still allow 16-byte
-// loads), the next K step's loads are issued before this step's MFMAs and written to the other LDS
-// buffer after them.
-template <int BM, int BN, int WGM, int WGN, bool HV, bool WV, bool MASKED>
-__global__ __launch_bounds__(256, 2) void transform_generic_kernel(
-    int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
-    const float* __restrict__ W, const float* __restrict__ bias, int relu,
-    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm)
-{
-    static_assert(WGM * WGN == 4, "four waves per workgroup");
-    constexpr int TM = BM / (32 * WGM);      // 32x32 MFMA tiles per wave along M
-    constexpr int TN = BN / (32 * WGN);      // and along N
-    constexpr int LDA = BM + 2;              // LDS row pitches (floats): see the A-tile mapping below
-    constexpr int LDB = BN + 4;
-    constexpr int A_F4 = BM * BK / 4 / 256;  // float4 loads per thread per step
-    constexpr int B_F4 = (BN * BK / 4 + 255) / 256;
-    static_assert(A_F4 >= 1, "tile too small");
-
-    __shared__ float As[2][BK][LDA];
-    __shared__ float Bs[2][BK][LDB];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN;
-    const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int n0 = blockIdx.y * BN;
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    float ra[A_F4][4], rb[B_F4][4];
-    int wa[A_F4], wb[B_F4];                  // how many of the four are real (see load4)
-
-    // A tile: thread -> (row = id / 4, k4 = id % 4): four lanes read the 64 contiguous bytes of
-    // a row, and with a row pitch of BM + 2 floats the transposing LDS writes of each half-wave
-    // (4 k-rows x 8 rows) fall into 32 different banks
-    auto load_a = [&](int kt) {
-#pragma unroll
-        for (int i = 0; i < A_F4; ++i) {
-            const int id = tid + i * 256;
-            const int r = id / 4, k4 = id % 4;
-            const int64_t row = m0 + r;
-            const int k = kt * BK + k4 * 4;
-            wa[i] = row < N ? D_in - k : 0;                   // may be <= 0 or > 4
-            load4<HV>(H, row * ldh + k, wa[i], ra[i]);
-        }
-    };
-    // B tile: thread -> (k = id / (BN/4), n4 = id % (BN/4))
-    auto load_b = [&](int kt) {
-#pragma unroll
-        for (int i = 0; i < B_F4; ++i) {
-            const int id = tid + i * 256;
-            if (BN * BK / 4 % 256 != 0 && id >= BN * BK / 4) continue;
-            const int kk = id / (BN / 4), n4 = id % (BN / 4);
-            const int k = kt * BK + kk;
-            const int n = n0 + n4 * 4;
-            wb[i] = k < D_in ? D_out - n : 0;
-            load4<WV>(W, (int64_t)k * D_out + n, wb[i], rb[i]);
-        }
-    };
-    auto store_tiles = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < A_F4; ++i) {
-            const int id = tid + i * 256;
-            const int r = id / 4, k4 = id % 4;
-            zero4<HV>(wa[i], ra[i]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) As[buf][k4 * 4 + q][r] = ra[i][q];
-        }
-#pragma unroll
-        for (int i = 0; i < B_F4; ++i) {
-            const int id = tid + i * 256;
-            if (BN * BK / 4 % 256 != 0 && id >= BN * BK / 4) continue;
-            const int kk = id / (BN / 4), n4 = id % (BN / 4);
-            zero4<WV>(wb[i], rb[i]);
-            f32x4 t = {rb[i][0], rb[i][1], rb[i][2], rb[i][3]};
-            *reinterpret_cast<f32x4*>(&Bs[buf][kk][n4 * 4]) = t;
-        }
-    };
-
-    const int lrow = lane & 31, lk = lane >> 5;
-    // bias of this lane's output columns, fetched up front so that the stores at the end wait for nothing
-    float bv[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int col = n0 + wn * TN * 32 + j * 32 + lrow;
-        bv[j] = (bias && col < D_out) ? bias[col] : 0.0f;
-    }
-
-    const int nk = (D_in + BK - 1) / BK;
-    load_a(0);
-    load_b(0);
-    store_tiles(0);
-    __syncthreads();
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) { load_a(kt + 1); load_b(kt + 1); }
-        // operand fragments are double-buffered in registers: the LDS reads of k-step s+1 are issued
-        // before the MFMAs of k-step s
-        float af[2][TM], bf[2][TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) af[0][i] = As[buf][lk][wm * TM * 32 + i * 32 + lrow];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bf[0][j] = Bs[buf][lk][wn * TN * 32 + j * 32 + lrow];
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            const int cur = (kk >> 1) & 1;
-            if (kk + 2 < BK) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) af[cur ^ 1][i] = As[buf][kk + 2 + lk][wm * TM * 32 + i * 32 + lrow];
-#pragma unroll
-                for (int j = 0; j < TN; ++j) bf[cur ^ 1][j] = Bs[buf][kk + 2 + lk][wn * TN * 32 + j * 32 + lrow];
-            }
-            RETEXO_SCHED_FENCE();                    // keep those reads ahead of this step's MFMAs
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[cur][i], bf[cur][j], acc[i][j], 0, 0, 0);
-        }
-        if (kt + 1 < nk) store_tiles(buf ^ 1);
-        __syncthreads();
-    }
-
-    write_out<TM, TN, MASKED>(acc, bv, N, D_out, m0 + wm * TM * 32, n0 + wn * TN * 32, lane, relu, Z, ldz, mask, ldm,
-                              m0 + BM <= N);
 }
 
 // Few rows: a matrix with so few 128-row blocks that they would leave most compute units idle (a citation
@@ -596,28 +407,17 @@ __global__ void bias_rows_kernel(int64_t N, int D_out, const float* __restrict__
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, bool MASKED>
+template <int BN, bool MASKED>
 void launch(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh, const float* W,
-            const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm,
+            const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm, bool keep_sign,
             hipStream_t stream)
 {
-    // 16-byte loads need aligned rows and widths that are multiples of four floats
-    const bool hv = (uintptr_t)H % 16 == 0 && ldh % 4 == 0 && D_in % 4 == 0;
-    const bool wv = (uintptr_t)W % 16 == 0 && D_out % 4 == 0;
-    dim3 grid((unsigned)((N + BM - 1) / BM), (unsigned)((D_out + BN - 1) / BN));
-    const int r = relu ? 1 : 0;
+    const dim3 grid((unsigned)((N + 127) / 128), (unsigned)((D_out + BN - 1) / BN)), block(64 * transform_waves<BN>);
+    const int r = relu ? 1 : 0, ks = keep_sign ? 1 : 0;
     const bool zv = (uintptr_t)Z % 16 == 0 && ldz % 4 == 0 && D_out % 4 == 0 &&
                     (!MASKED || ((uintptr_t)mask % 16 == 0 && ldm % 4 == 0));
-    if (hv && wv && zv)
-        transform_kernel<BM, BN, WGM, WGN, MASKED, true, true><<<grid, dim3(256), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
-    else if (hv && wv)
-        transform_kernel<BM, BN, WGM, WGN, MASKED><<<grid, dim3(256), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
-    else if (hv)
-        transform_kernel<BM, BN, WGM, WGN, MASKED, false><<<grid, dim3(256), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
-    else if (wv)
-        transform_generic_kernel<BM, BN, WGM, WGN, false, true, MASKED><<<grid, dim3(256), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
-    else
-        transform_generic_kernel<BM, BN, WGM, WGN, false, false, MASKED><<<grid, dim3(256), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+    if (zv) transform_kernel<BN, MASKED, true><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, ks);
+    else    transform_kernel<BN, MASKED, false><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, ks);
 }
 
 template <bool MASKED>
@@ -646,7 +446,7 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
 
 template <bool MASKED>
 void launch_by_width(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh, const float* W,
-                     const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm,
+                     const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm, bool keep_sign,
                      hipStream_t stream)
 {
     const int64_t bn = D_out <= 32 ? 32 : D_out <= 64 ? 64 : D_out <= 128 ? 128 : D_out <= 192 ? 192 : 256;
@@ -654,18 +454,21 @@ void launch_by_width(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
         launch_few_rows<MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
         return;
     }
-    if (D_out <= 32)       launch<128, 32, 4, 1, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
-    else if (D_out <= 64)  launch<128, 64, 4, 1, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
-    else if (D_out <= 128) launch<128, 128, 2, 2, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
-    else if (D_out <= 192) launch<128, 192, 2, 2, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
-    else                   launch<128, 256, 2, 2, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
+    auto go = [&](auto width) {
+        launch<decltype(width)::value, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, stream);
+    };
+    if (bn == 32)       go(std::integral_constant<int, 32>{});
+    else if (bn == 64)  go(std::integral_constant<int, 64>{});
+    else if (bn == 128) go(std::integral_constant<int, 128>{});
+    else if (bn == 192) go(std::integral_constant<int, 192>{});
+    else                go(std::integral_constant<int, 256>{});
 }
 
 }  // namespace
 
 int launch_transform(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh,
                      const float* W, const float* b, bool relu, float* Z, int64_t ldz,
-                     hipStream_t stream, const float* mask, int64_t ldm)
+                     hipStream_t stream, const float* mask, int64_t ldm, bool keep_sign)
 {
     if (N == 0 || D_out == 0) return RETEXO_OK;
     if (D_in == 0) {
@@ -674,8 +477,8 @@ int launch_transform(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
             N, (int)D_out, b, relu ? 1 : 0, Z, ldz, mask, ldm);
         return hipGetLastError() != hipSuccess ? RETEXO_E_HIP : RETEXO_OK;
     }
-    if (mask) launch_by_width<true>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
-    else      launch_by_width<false>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
+    if (mask) launch_by_width<true>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, stream);
+    else      launch_by_width<false>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, stream);
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
     return RETEXO_OK;
 }
