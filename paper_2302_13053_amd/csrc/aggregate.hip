@@ -52,6 +52,8 @@ struct AggArgs {
     const float* er_from;  // a_dst [heads, Dh]; the kernel forms <a_dst, z_v> from row v itself (pipelined kernel, one slab)
     int64_t row_begin;     // range of plan order handled by this launch
     int64_t row_count;
+    int64_t heavy_rows;    // rows at the head of the plan order with a workgroup each, and the workgroups of those
+    int64_t heavy_items;   // rows (agg_linear_kernel, whose one launch covers all rows)
     int64_t F;
     int nslab;
     int slab_major;
@@ -79,22 +81,30 @@ struct AggArgs {
 
 // ---------------------------------------------------------------------------
 // sum / mean / gcn_sym, and (MAXOP) the element-wise maximum
-//   NW == 1: kLightWaves independent (row, slab) items per workgroup
-//   NW  > 1: the NW waves of a workgroup share one (row, slab) item
+//
+// One launch covers both classes of rows: the first a.heavy_items workgroups share one (row, slab) item among their
+// eight waves (interleaved 64-entry tiles, combined through LDS in wave order), the others hold eight independent
+// items.  Long rows so start first and the short ones fill the chip beside them; two launches one after the other cost
+// small graphs the longer of both times twice.
+// Entries are fetched U at a time, the rest of a tile as one shorter batch (the count is the same for all lanes): a
+// row of five entries waits for memory once, not once for four and once more.  Bound by memory latency on small graphs
+// (19,717 rows, 108,393 entries, 256 columns: see long_rows) and by the gathers' bytes on large ones.
 // ---------------------------------------------------------------------------
-template <int VEC, int NC, int NW, bool MAXOP>
-__global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_linear_kernel(AggArgs a)
+template <int VEC, int NC, bool MAXOP>
+__global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
 {
+    constexpr int U = NC * VEC <= 8 ? 8 : 4;          // entries in flight per lane: up to 64 registers
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t items = a.row_count * a.nslab;
-    const int64_t item = (NW == 1) ? (int64_t)blockIdx.x * kLightWaves + wave : (int64_t)blockIdx.x;
-    if (item >= items) return;        // NW > 1: uniform over the workgroup
+    const bool heavy = blockIdx.x < a.heavy_items;    // uniform over the workgroup
+    const int64_t rows = heavy ? a.heavy_rows : a.n_rows - a.heavy_rows;
+    const int64_t item = heavy ? (int64_t)blockIdx.x : ((int64_t)blockIdx.x - a.heavy_items) * kHeavyWaves + wave;
+    if (item >= rows * a.nslab) return;
     int64_t slot;
     int slab;
-    if (a.slab_major) { slab = (int)(item / a.row_count); slot = item % a.row_count; }
+    if (a.slab_major) { slab = (int)(item / rows); slot = item % rows; }
     else              { slot = item / a.nslab; slab = (int)(item % a.nslab); }
-    const int v = __builtin_amdgcn_readfirstlane(a.order[a.row_begin + slot]);
+    const int v = __builtin_amdgcn_readfirstlane(a.order[heavy ? slot : a.heavy_rows + slot]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v + 1]);
 
@@ -110,51 +120,44 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_linear_
     const float* zl = a.Z + col0;
     const bool weighted = a.wsrc != nullptr;
 
-    for (int base = lo + 64 * (NW == 1 ? 0 : wave); base < hi; base += 64 * NW) {
+    const int first = heavy ? 64 * wave : 0, step = heavy ? 64 * kHeavyWaves : 64;
+    for (int base = lo + first; base < hi; base += step) {
         const int e = base + lane;
         const int my_u = e < hi ? a.col_idx[e] : 0;
         const float my_w = weighted ? (e < hi ? a.wsrc[my_u] : 0.0f) : 1.0f;
         const int cnt = min(64, hi - base);
-        int j = 0;
-        for (; j + kUnroll <= cnt; j += kUnroll) {
-            float z[kUnroll][NC][VEC];
-            float w[kUnroll];
+        auto batch = [&](int j, auto whole_tag) {
+            constexpr bool WHOLE = decltype(whole_tag)::value;
+            float z[U][NC][VEC];
 #pragma unroll
-            for (int t = 0; t < kUnroll; ++t) {
+            for (int t = 0; t < U; ++t) {
+                if (!WHOLE && j + t >= cnt) break;
                 const int u = bcast_i(my_u, j + t);
-                w[t] = bcast_f(my_w, j + t);
                 const float* zr = zl + (int64_t)u * a.ldz;
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
                     if (act[c]) load_row<VEC>(zr + c * 64 * VEC, z[t][c]);
             }
 #pragma unroll
-            for (int t = 0; t < kUnroll; ++t)
+            for (int t = 0; t < U; ++t) {
+                if (!WHOLE && j + t >= cnt) break;
+                const float w = bcast_f(my_w, j + t);
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
                     if (act[c]) {
 #pragma unroll
                         for (int k = 0; k < VEC; ++k)
-                            acc[c][k] = MAXOP ? fmaxf(acc[c][k], z[t][c][k]) : fmaf(w[t], z[t][c][k], acc[c][k]);
+                            acc[c][k] = MAXOP ? fmaxf(acc[c][k], z[t][c][k]) : fmaf(w, z[t][c][k], acc[c][k]);
                     }
-        }
-        for (; j < cnt; ++j) {
-            const int u = bcast_i(my_u, j);
-            const float w = bcast_f(my_w, j);
-            const float* zr = zl + (int64_t)u * a.ldz;
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                if (act[c]) {
-                    float z[VEC];
-                    load_row<VEC>(zr + c * 64 * VEC, z);
-#pragma unroll
-                    for (int k = 0; k < VEC; ++k) acc[c][k] = MAXOP ? fmaxf(acc[c][k], z[k]) : fmaf(w, z[k], acc[c][k]);
-                }
-        }
+            }
+        };
+        int j = 0;
+        for (; j + U <= cnt; j += U) batch(j, std::true_type{});
+        if (j < cnt) batch(j, std::false_type{});
     }
 
-    if constexpr (NW > 1) {
-        __shared__ float red[NW][NC * VEC][64];
+    __shared__ float red[kHeavyWaves][NC * VEC][64];
+    if (heavy) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -167,7 +170,8 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_linear_
             for (int k = 0; k < VEC; ++k) {
                 float s = red[0][c * VEC + k][lane];
 #pragma unroll
-                for (int w = 1; w < NW; ++w) s = MAXOP ? fmaxf(s, red[w][c * VEC + k][lane]) : s + red[w][c * VEC + k][lane];
+                for (int w = 1; w < kHeavyWaves; ++w)
+                    s = MAXOP ? fmaxf(s, red[w][c * VEC + k][lane]) : s + red[w][c * VEC + k][lane];
                 acc[c][k] = s;
             }
     }
@@ -1172,22 +1176,13 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
 // host side
 // ---------------------------------------------------------------------------
 template <int VEC, int NC, bool MAXOP>
-void launch_linear_pair(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t stream)
+void launch_linear(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t stream)
 {
-    if (n_heavy > 0) {
-        AggArgs a = base;
-        a.row_begin = 0;
-        a.row_count = n_heavy;
-        const int64_t blocks = n_heavy * a.nslab;
-        agg_linear_kernel<VEC, NC, kHeavyWaves, MAXOP><<<dim3((unsigned)blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
-    }
-    if (N > n_heavy) {
-        AggArgs a = base;
-        a.row_begin = n_heavy;
-        a.row_count = N - n_heavy;
-        const int64_t blocks = (a.row_count * a.nslab + kLightWaves - 1) / kLightWaves;
-        agg_linear_kernel<VEC, NC, 1, MAXOP><<<dim3((unsigned)blocks), dim3(64 * kLightWaves), 0, stream>>>(a);
-    }
+    AggArgs a = base;
+    a.heavy_rows = n_heavy;
+    a.heavy_items = n_heavy * a.nslab;
+    const int64_t blocks = a.heavy_items + ((N - n_heavy) * a.nslab + kHeavyWaves - 1) / kHeavyWaves;
+    agg_linear_kernel<VEC, NC, MAXOP><<<dim3((unsigned)blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
 }
 
 template <int LPG, bool WEIGHTED, bool OFF32>
@@ -1495,9 +1490,9 @@ void dispatch_gat_fast(int nc, bool train, const AggArgs& a, int64_t nh, int64_t
 template <int VEC, bool MAXOP>
 void dispatch_linear_nc(int nc, const AggArgs& a, int64_t nh, int64_t N, hipStream_t s)
 {
-    if (nc == 1) launch_linear_pair<VEC, 1, MAXOP>(a, nh, N, s);
-    else if (nc == 2) launch_linear_pair<VEC, 2, MAXOP>(a, nh, N, s);
-    else launch_linear_pair<VEC, 3, MAXOP>(a, nh, N, s);
+    if (nc == 1) launch_linear<VEC, 1, MAXOP>(a, nh, N, s);
+    else if (nc == 2) launch_linear<VEC, 2, MAXOP>(a, nh, N, s);
+    else launch_linear<VEC, 3, MAXOP>(a, nh, N, s);
 }
 
 template <int VEC>
@@ -1694,6 +1689,8 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     a.er_from = nullptr;
     a.row_begin = 0;
     a.row_count = 0;
+    a.heavy_rows = 0;
+    a.heavy_items = 0;
     a.F = c.F;
     a.nslab = (int)((c.F + slab_w - 1) / slab_w);
     a.slab_major = opt.slab_major < 0 ? 1 : (int)opt.slab_major;
@@ -1716,10 +1713,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     a.save_neg = nullptr;
     a.ld_pos = 0;
 
-    // rows at or above the heavy threshold (rounded up to a tabulated one)
-    int64_t n_heavy = 0;
-    for (int i = 0; i < 8; ++i)
-        if (kPlanThresholds[i] >= opt.heavy_degree) { n_heavy = p->rows_at_least[i]; break; }
+    int64_t n_heavy = long_rows(p, c.F);
 
     // narrow slabs (32/64/128 columns) use the grouped gather; they need float4 gathers
     // (the maximum is only implemented on whole rows)
@@ -1741,7 +1735,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
             // long-row class by the length of a row's share of one range
             const int64_t want = opt.narrow_heavy * parts;
             n_heavy = 0;
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < kPlanThresholdCount; ++i)
                 if (kPlanThresholds[i] >= want || kPlanThresholds[i] >= 16384) {
                     n_heavy = p->rows_at_least[i];
                     break;

@@ -983,10 +983,8 @@ int launch_aggregate_backward(const AggBackwardCall& c, hipStream_t stream)
         launch_gat_scores(N, F, c.heads, c.Z, c.ldz, c.attn_src, c.attn_dst, (float*)(ws + w.el), (float*)(ws + w.er), stream);
     }
 
-    int64_t n_heavy = 0;
     const AggOptions& opt = agg_options();
-    for (int i = 0; i < 8; ++i)
-        if (kPlanThresholds[i] >= opt.heavy_degree) { n_heavy = p->rows_at_least[i]; break; }
+    const int64_t n_heavy = long_rows(p, F);
 
     // 16-byte gathers need every table aligned, rows padded to whole vectors and F a multiple of 4
     // (the inner products must not see padding columns)

@@ -1006,9 +1006,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     a.first = 1;
     a.last = 1;
 
-    int64_t n_heavy = 0;
-    for (int i = 0; i < 8; ++i)
-        if (kPlanThresholds[i] >= opt.heavy_degree) { n_heavy = p->rows_at_least[i]; break; }
+    const int64_t n_heavy = long_rows(p, F);
 
     const int max_nc = 2;
     int nc = (int)((F + 64 * E - 1) / (64 * E));
@@ -1033,7 +1031,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
         if (parts > 1) a.part_ptr = p->part_ptr;
         // rows whose share of one range is long get a workgroup each
         int64_t n_long = 0;
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < kPlanThresholdCount; ++i)
             if (kPlanThresholds[i] >= opt.narrow_heavy * parts || kPlanThresholds[i] >= 16384) {
                 n_long = p->rows_at_least[i];
                 break;

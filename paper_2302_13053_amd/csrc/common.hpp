@@ -35,17 +35,20 @@ struct retexo_plan {
     int64_t part_span = 0;
     int32_t max_degree = 0;
     // number of rows with deg >= threshold[i], thresholds fixed in plan.hip
-    int64_t rows_at_least[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int64_t rows_at_least[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     void* block = nullptr;          // the one device allocation behind deg, dinv, order, part_ptr
     void* build_scratch = nullptr;
 };
 
-constexpr int kPlanThresholds[8] = {1, 256, 512, 1024, 2048, 4096, 8192, 16384};
+constexpr int kPlanThresholdCount = 9;
+constexpr int kPlanThresholds[kPlanThresholdCount] = {64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384};
+
+constexpr int64_t kHeavyDegree = 2048;
 
 struct AggOptions {
     int64_t slab_cols = 0;      // 0 = auto
     int64_t slab_major = -1;    // -1 = auto
-    int64_t heavy_degree = 2048;
+    int64_t heavy_degree = kHeavyDegree;   // the default stands for "at most this": see long_rows
     int64_t max_vec = 4;        // cap on floats per lane per gather (experiments)
     int64_t gat_fast = 1;       // pipelined edge-softmax kernel (0: the plain one)
     int64_t gat_flash = 1;      // ordinary rows: source scores from the gathered rows (0: from the table)
@@ -58,6 +61,24 @@ struct AggOptions {
     int64_t csr_sorted_keys = 0;  // 1: retexo_csr_from_coo always takes the sorted-key construction (tests)
 };
 AggOptions& agg_options();
+
+// Rows (the first of the schedule) that get a workgroup of their own in the whole-row kernels, in an aggregation of F
+// columns.  One wave walks a row at four to eight entries per memory latency (about 0.7 us), so a row of d entries takes
+// 0.1 to 0.2 us * d whatever else runs, while the whole call needs nnz * F * 4 bytes at about 6 TB/s: the longest row
+// left to one wave is held to about a quarter of that, 64 entries at the least (a workgroup's own start and
+// combination cost about as much) and 2048 at the most.  On a citation graph of 108,393 entries and 256 columns the
+// longest row's 320 entries alone took 57 us of an aggregation that needs 20.
+static inline int64_t long_rows(const retexo_plan* p, int64_t F)
+{
+    int64_t at_least = agg_options().heavy_degree;
+    if (at_least == kHeavyDegree) {
+        at_least = (p->nnz * F) >> 20;
+        at_least = at_least < 64 ? 64 : at_least > kHeavyDegree ? kHeavyDegree : at_least;
+    }
+    for (int i = 0; i < kPlanThresholdCount; ++i)
+        if (kPlanThresholds[i] >= at_least) return p->rows_at_least[i];
+    return 0;
+}
 
 // Zero `bytes` (a multiple of 4) at `p` with a small kernel.  The stream-ordered entry points use this
 // instead of memset nodes so that a caller can record them into a HIP graph.

@@ -92,13 +92,13 @@ __global__ __launch_bounds__(kThreads) void split_rows_kernel(
 }
 
 // counts[i] = number of rows with degree >= thresholds[i]; keys are sorted descending
-struct Thresholds { int t[8]; };
+struct Thresholds { int t[kPlanThresholdCount]; };
 
 __global__ void count_at_least(int64_t N, const uint32_t* __restrict__ keys_desc, Thresholds th,
                                int64_t* counts)
 {
     const int i = threadIdx.x;
-    if (i >= 8) return;
+    if (i >= kPlanThresholdCount) return;
     const uint32_t t = (uint32_t)th.t[i];
     int64_t lo = 0, hi = N;                 // first index with key < t
     while (lo < hi) {
@@ -106,11 +106,11 @@ __global__ void count_at_least(int64_t N, const uint32_t* __restrict__ keys_desc
         if (keys_desc[mid] >= t) lo = mid + 1; else hi = mid;
     }
     counts[i] = lo;
-    if (i == 0) counts[8] = N > 0 ? (int64_t)keys_desc[0] : 0;   // max degree
+    if (i == 0) counts[kPlanThresholdCount] = N > 0 ? (int64_t)keys_desc[0] : 0;   // max degree
 }
 
 struct Readback {
-    int64_t counts[9];
+    int64_t counts[kPlanThresholdCount + 1];      // ... and the largest degree
     int64_t nnz;
     uint32_t bad;
     uint32_t pad;
@@ -178,7 +178,7 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
         RETEXO_HIP_TRY(rocprim::radix_sort_pairs_desc(sc + L.s_tmp, sort_bytes, kin, kout, ids, p->order, (size_t)N,
                                                       0u, 32u, stream));
         Thresholds th;
-        for (int i = 0; i < 8; ++i) th.t[i] = kPlanThresholds[i];
+        for (int i = 0; i < kPlanThresholdCount; ++i) th.t[i] = kPlanThresholds[i];
         count_at_least<<<dim3(1), dim3(64), 0, stream>>>(N, kout, th, rb->counts);
     }
     if (L.split) {
@@ -197,8 +197,8 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
     RETEXO_HIP_TRY(hipMemcpyAsync(&h, rb, sizeof(h), hipMemcpyDeviceToHost, stream));
     RETEXO_HIP_TRY(hipStreamSynchronize(stream));
     if (h.bad) return RETEXO_E_CSR;
-    for (int i = 0; i < 8; ++i) p->rows_at_least[i] = h.counts[i];
-    p->max_degree = (int32_t)h.counts[8];
+    for (int i = 0; i < kPlanThresholdCount; ++i) p->rows_at_least[i] = h.counts[i];
+    p->max_degree = (int32_t)h.counts[kPlanThresholdCount];
     return RETEXO_OK;
 }
 

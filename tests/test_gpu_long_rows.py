@@ -1,0 +1,92 @@
+"""Rows with a workgroup of their own beside rows with one wave, in one launch: lengths around the batch sizes, the tile of 64
+entries and the threshold (64 on graphs of this size), against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2302_13053_amd import binding as B
+from paper_2302_13053_amd import harness as Hn
+from paper_2302_13053_amd import workloads as wl
+from parity import assert_close, assert_cond_close
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = {
+    "mixed": [0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 62, 63, 64, 65, 127, 128, 129, 511, 512, 513, 600],
+    "all long": [64, 70, 128, 400, 576, 577],
+    "none long": [1, 0, 63, 8, 3, 33],
+    "one row": [513],
+}
+
+
+def graph(name):
+    lengths = LENGTHS[name]
+    n = 700
+    rng = np.random.Generator(np.random.Philox(key=len(lengths)))
+    deg = np.zeros(n, np.int64)
+    if name == "all long":
+        n = len(lengths)
+        deg = np.array(lengths, np.int64)
+        n_src = 600
+    else:
+        n_src = n
+        at = rng.permutation(n)[:len(lengths)]
+        deg[at] = lengths
+    if name == "all long":               # every row of the graph is long: columns repeat over the few nodes there are
+        ci = np.concatenate([np.sort(rng.integers(0, n, d)) for d in deg]).astype(np.int32)
+    else:
+        ci = np.concatenate([np.sort(rng.permutation(n_src)[:d]) for d in deg]).astype(np.int32)
+    rp = np.zeros(n + 1, np.int64)
+    rp[1:] = np.cumsum(deg)
+    g = Hn.DeviceGraph(n, int(rp[-1]), Hn.dev(rp), Hn.dev(ci if ci.size else np.zeros(1, np.int32)))
+    return Hn.make_plan(g, validate=True), rp, ci
+
+
+@pytest.mark.parametrize("name", list(LENGTHS))
+@pytest.mark.parametrize("F", [1, 31, 128, 256, 257, 500, 1433])
+@pytest.mark.parametrize("mode", ["mean", "sum", "gcn_sym", "max"])
+def test_row_classes_in_one_launch(name, F, mode):
+    g, rp, ci = graph(name)
+    ld = wl.pad_ld(F) if F != 31 else 31
+    Z = wl.random_matrix(g.n_nodes, F, F, ld=ld)
+    got = Hn.aggregate(g, mode, Hn.dev(Z), F, concat=True).cpu().numpy()[:, :2 * F]
+    want = oracle.aggregate(mode, rp, ci, Z, F, self_concat=True)
+    if mode == "max":
+        assert np.array_equal(got.astype(np.float64), want)
+    else:
+        # a sum of 600 terms in float32: 600 roundings of 2^-24 of the terms' size at worst is 3.6e-5, 1.5e-6 as they fall
+        assert_cond_close(got, want, oracle.aggregate_abs(mode, rp, ci, Z, F, self_concat=True), what=name)
+    again = Hn.aggregate(g, mode, Hn.dev(Z), F, concat=True).cpu().numpy()[:, :2 * F]
+    assert np.array_equal(got, again)
+    g.destroy()
+
+
+@pytest.mark.parametrize("name", list(LENGTHS))
+@pytest.mark.parametrize("heads,dh", [(4, 16), (4, 47), (1, 64), (8, 5)])
+def test_edge_softmax_row_classes(name, heads, dh):
+    g, rp, ci = graph(name)
+    F = heads * dh
+    Z = wl.random_matrix(g.n_nodes, F, F, ld=wl.pad_ld(F))
+    a = [wl.random_matrix(heads, dh, k) * np.float32(0.2) for k in (1, 2)]
+    got = Hn.aggregate(g, "gat_softmax", Hn.dev(Z), F, heads=heads, a_src=Hn.dev(a[0]), a_dst=Hn.dev(a[1]))
+    want = oracle.aggregate("gat_softmax", rp, ci, Z, F, heads=heads, a_src=a[0], a_dst=a[1])
+    # a softmax average of 600 rows of at least 40 columns: no worse than the sums above, and rows of robust magnitude
+    assert_close(got.cpu().numpy()[:, :F], want, what=name)
+    g.destroy()
+
+
+def test_default_threshold_is_an_upper_bound():
+    # the same graph with the classes drawn elsewhere: the same sums in another order
+    g, rp, ci = graph("mixed")
+    Z = wl.random_matrix(g.n_nodes, 96, 1)
+    first = Hn.aggregate(g, "sum", Hn.dev(Z), 96).clone()
+    try:
+        B.check(B.retexo_set_option("agg_heavy_degree", 1 << 20), "set_option")      # no long rows at all
+        other = Hn.aggregate(g, "sum", Hn.dev(Z), 96)
+    finally:
+        B.check(B.retexo_set_option("agg_heavy_degree", 2048), "set_option")
+    mag = oracle.aggregate_abs("sum", rp, ci, Z, 96)
+    assert_cond_close(first.cpu().numpy()[:, :96], other.cpu().numpy()[:, :96].astype(np.float64), mag, what="classes")
+    assert not torch.equal(first[:, :96], other[:, :96])       # 600 entries in eight interleaved sums round differently
+    g.destroy()
