@@ -18,32 +18,6 @@ __device__ __forceinline__ void each_index(std::integer_sequence<int, I...>, F&&
 template <int N, class F>
 __device__ __forceinline__ void each(F&& f) { each_index(std::make_integer_sequence<int, N>{}, f); }
 
-// Four consecutive floats starting at base[off], fetched without a branch: an
-// element that is not wanted (or would be out of range) is fetched from base[0]
-// instead; zero4 later replaces it by zero.  Keeping the replacement out of the
-// load lets all loads of a K step stay in flight behind the MFMAs of the
-// previous step.
-//   VEC: the four are one aligned 16-byte load and are wanted all or none
-template <bool VEC>
-__device__ __forceinline__ void load4(const float* __restrict__ base, int64_t off, int wanted, float (&r)[4])
-{
-    if constexpr (VEC) {
-        const f32x4 t = *reinterpret_cast<const f32x4*>(base + (wanted >= 4 ? off : 0));
-        r[0] = t.x; r[1] = t.y; r[2] = t.z; r[3] = t.w;
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) r[q] = base[q < wanted ? off + q : 0];
-    }
-}
-
-template <bool VEC>
-__device__ __forceinline__ void zero4(int wanted, float (&r)[4])
-{
-#pragma unroll
-    for (int q = 0; q < 4; ++q) r[q] = (VEC ? wanted >= 4 : q < wanted) ? r[q] : 0.0f;
-}
-
-
 #define RETEXO_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 // ---------------------------------------------------------------------------
@@ -94,21 +68,18 @@ __device__ __forceinline__ void split_pair(float x0, float x1, int q, V (&part)[
 
 // Whether any of a wave's 32 x 32 sums formed from split operands cannot be trusted: not finite, or so small (but not
 // zero) that the operands may have lost their low parts.  bf16 goes down to 2^-133, so an operand keeps its 24
-// bits from about 2^-110 on; the line is drawn at sums below 2^-104.  With `near` > 0 also where a sum plus `bias` lies
-// within `near` of zero (a caller that goes by the sign).
-__device__ __forceinline__ bool redo_tile(const f32x16& acc, float bias, float near)
+// bits from about 2^-110 on; the line is drawn at sums below 2^-104.
+__device__ __forceinline__ bool redo_tile(const f32x16& acc)
 {
     uint32_t top = 0, low = 0xffffffffu;          // largest magnitude; smallest one minus one (zero wraps round)
-    bool close = false;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float x = acc[r];
         const uint32_t m = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
         top = m > top ? m : top;
         low = m - 1 < low ? m - 1 : low;
-        close |= __builtin_fabsf(x + bias) < near;
     }
-    return __any(close || top >= 0x7f800000u || low < 0x0b800000u - 1);
+    return __any(top >= 0x7f800000u || low < 0x0b800000u - 1);
 }
 
 // LDS image of one K tile of a workgroup: 16-byte units of eight k of one row (of A) or column (of B),
@@ -219,8 +190,8 @@ template <int BW, int WAVES> struct KMajorStage {
 // A matrix core is kept busy only if what else a wave does fits between its matrix instructions (32 cycles each,
 // two waves per SIMD).  So the staging work of a K tile is cut into `MICROS` steps of about ten instructions, spread
 // over the matrix instructions before the tile's barrier; sched_barrier pins the order.  micro(m, buf, kt): step m of
-// "split the staged pieces (tile kt) into LDS buffer `buf`, and fetch those of tile kt + 1 in their place", whose loads
-// so have one K tile of matrix instructions to arrive.
+// "split the staged pieces (tile kt) into LDS buffer `buf` = kt % 2, and fetch those of a later tile in their place",
+// whose loads so have at least one K tile of matrix instructions to arrive.  One-column tiles pass `buf` as a constant.
 // Columns of the wave's tile are worked through one after the other with B's operands a column ahead.
 // The one barrier of a K tile stands before its last column, whose operands are already in registers: behind that
 // barrier the next tile's first operands are read as soon as their registers are free.
@@ -255,9 +226,8 @@ __device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __r
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) small[j][r] = 0.0f;
-    auto tile = [&](int kt, auto more_tag) {
+    auto tile = [&](int kt, auto more_tag, auto buf, auto next) {
         constexpr bool more = decltype(more_tag)::value;
-        const int buf = kt & 1;
         each<TN * 6>([&](auto at) {
             constexpr int g = decltype(at)::value, j = g / 6, p = g % 6;
             constexpr bool last = TN > 1 && j == TN - 1;
@@ -265,34 +235,51 @@ __device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __r
                 // every wave has read its operands of this tile and written its share of the next one
                 __syncthreads();
                 RETEXO_SCHED_FENCE();
-                read_b(buf ^ 1, 0, 0);
+                read_b(next, 0, 0);
             }
             f32x16& sum = p == 0 ? acc[j] : small[j];
             sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[pa[p]], bf[j % SLOTS][pb[p]], sum, 0, 0, 0);
             RETEXO_SCHED_FENCE();
             if constexpr (p == 0 && j + 1 < TN) read_b(buf, j + 1, (j + 1) % SLOTS);
             if constexpr (last && more) {
-                if constexpr (p == 2) read_a(buf ^ 1, HI);
-                if constexpr (p == 3) read_a(buf ^ 1, LO);
-                if constexpr (p == 5) read_a(buf ^ 1, MID);
+                if constexpr (p == 2) read_a(next, HI);
+                if constexpr (p == 3) read_a(next, LO);
+                if constexpr (p == 5) read_a(next, MID);
             }
             if constexpr (!last && more) {
                 constexpr int m0 = g * MICROS / G, m1 = (g + 1) * MICROS / G;
-                each<m1 - m0>([&](auto m) { micro(std::integral_constant<int, m0 + decltype(m)::value>{}, buf ^ 1, kt + 1); });
+                each<m1 - m0>([&](auto m) { micro(std::integral_constant<int, m0 + decltype(m)::value>{}, next, kt + 1); });
             }
             RETEXO_SCHED_FENCE();
         });
         if constexpr (TN == 1 && more) {
             __syncthreads();
             RETEXO_SCHED_FENCE();
-            read_b(buf ^ 1, 0, 0);
-            read_a(buf ^ 1, HI);
-            read_a(buf ^ 1, LO);
-            read_a(buf ^ 1, MID);
+            read_b(next, 0, 0);
+            read_a(next, HI);
+            read_a(next, LO);
+            read_a(next, MID);
         }
     };
-    for (int kt = 0; kt + 1 < nk; ++kt) tile(kt, std::true_type{});
-    if (nk > 0) tile(nk - 1, std::false_type{});
+    if constexpr (TN == 1) {
+        // (unrolled over both buffers, which the wider tiles have no registers for)
+        constexpr std::integral_constant<int, 0> even{};
+        constexpr std::integral_constant<int, 1> odd{};
+        int kt = 0;
+        for (; kt + 2 < nk; kt += 2) {
+            tile(kt, std::true_type{}, even, odd);
+            tile(kt + 1, std::true_type{}, odd, even);
+        }
+        if (kt + 1 < nk) {
+            tile(kt, std::true_type{}, even, odd);
+            tile(kt + 1, std::false_type{}, odd, even);
+        } else if (kt < nk) {
+            tile(kt, std::false_type{}, even, odd);
+        }
+    } else {
+        for (int kt = 0; kt + 1 < nk; ++kt) tile(kt, std::true_type{}, kt & 1, (kt & 1) ^ 1);
+        if (nk > 0) tile(nk - 1, std::false_type{}, (nk - 1) & 1, nk & 1);
+    }
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll

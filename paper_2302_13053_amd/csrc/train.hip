@@ -70,7 +70,7 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
         sq.init(Q, ldq, k_begin, k_end, n0, Nq, wave, lane);
         constexpr int A_MICROS = PStage::count * PStage::steps;
         constexpr int MICROS = A_MICROS + QStage::count * QStage::steps;
-        auto micro = [&](auto step, int buf, int kt) {
+        auto micro = [&](auto step, auto buf, int kt) {
             constexpr int m = decltype(step)::value;
             u32x4* base = lds + buf * T::units;
             const bool more = kt + 1 < nk;
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
         };
         each<PStage::count>([&](auto i) { sp.template fetch<decltype(i)::value>(0); });
         each<QStage::count>([&](auto i) { sq.template fetch<decltype(i)::value>(0); });
-        each<MICROS>([&](auto m) { micro(m, 0, 0); });
+        each<MICROS>([&](auto m) { micro(m, std::integral_constant<int, 0>{}, 0); });
         __syncthreads();
         split_k_loop<TN, BM, BN, MICROS>(acc, lds, nk, a0, b0, lane, micro);
     }
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
         constexpr int j = decltype(at)::value;
         const int col = n0 + b0 + j * 32 + lrow;
         float turn = sign ? -1.0f : 1.0f;
-        if (redo_tile(acc[j], 0.0f, 0.0f)) {
+        if (redo_tile(acc[j])) {
             // the tile once more with the float32 instruction, operands straight from memory
             const float* pp = P + min(m0 + a0 + lrow, M - 1);
             const float* qp = Q + min(col, Nq - 1);
@@ -184,45 +184,80 @@ __device__ __forceinline__ float wsum(float x)
     return x;
 }
 
-constexpr int kXentRows = 64;     // nodes per workgroup of the loss kernel (16 per wave)
+constexpr int kXentRows = 16;     // nodes per workgroup of the loss kernel (4 per wave)
 
-// One wave per node at a time.  L[v, 0:C] holds the logits on entry and d loss / d logits on
-// exit (zero for unlabelled nodes and in the padding columns C..ld).  Per-workgroup loss sums
-// go to loss_part[blockIdx.x] (unscaled).
+// L[v, 0:C] holds the logits on entry and d loss / d logits on exit (zero for unlabelled nodes and in the padding
+// columns C..ld).  Per-workgroup loss sums go to loss_part[blockIdx.x] (unscaled).
+// A wave takes four nodes; where a row fits its lanes (NARROW: ld <= 64) all four at once, so that the loads and the
+// chains of wave reductions of four rows run side by side: bound by the streaming of L then, before by those chains
+// (232,965 x 41 92 -> 63 us, 2,708 x 7, which 16 rows per wave gave 43 workgroups, 25 -> 5 us).
+template <bool NARROW>
 __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     int64_t N, int C, float* __restrict__ L, int64_t ld, const int32_t* __restrict__ labels,
     const TrainHeader* hdr, float* __restrict__ loss_part)
 {
     __shared__ float wl[4];
+    constexpr int R = kXentRows / 4;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nl = hdr->n_labelled;
+    const float inv = nl > 0 ? 1.0f / (float)nl : 0.0f;
+    const int64_t v0 = (int64_t)blockIdx.x * kXentRows + wave * R;
     float loss = 0.0f;
-    for (int r = wave; r < kXentRows; r += 4) {
-        const int64_t v = (int64_t)blockIdx.x * kXentRows + r;
-        if (v >= N) break;
-        float* row = L + v * ld;
-        const int y = labels[v];
-        const float scale = (y >= 0 && nl > 0) ? 1.0f / (float)nl : 0.0f;
-        float m = -INFINITY;
-        for (int j = lane; j < C; j += 64) m = fmaxf(m, row[j]);
-        m = wmax(m);
-        // s: the softmax denominator; so: its part from the classes other than the label.  The label's
-        // gradient p_y - 1 is formed as -so / s: for a confidently classified node p_y is close to one and
-        // the subtraction would leave only a few correct digits of what is then the whole gradient.
-        float s = 0.0f, so = 0.0f;
-        for (int j = lane; j < C; j += 64) {
-            const float e = expf(row[j] - m);
-            s += e;
-            so += j == y ? 0.0f : e;
+    // s: the softmax denominator; so: its part from the classes other than the label.  The label's
+    // gradient p_y - 1 is formed as -so / s: for a confidently classified node p_y is close to one and
+    // the subtraction would leave only a few correct digits of what is then the whole gradient.
+    if constexpr (NARROW) {
+        float x[R], m[R], e[R], s[R], so[R];
+        int y[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t v = v0 + r < N ? v0 + r : N - 1;
+            y[r] = labels[v];
+            x[r] = lane < C ? L[v * ld + lane] : -INFINITY;
         }
-        s = wsum(s);
-        so = wsum(so);
-        const float rest = so / s;                 // 1 - p_y
-        if (y >= 0 && y < C) loss += rest <= 0.5f ? -log1pf(-rest) : -(row[y] - m - logf(s));
-        for (int j = lane; j < ld; j += 64) {
-            float g = 0.0f;
-            if (j < C) g = (j == y ? -rest : expf(row[j] - m) / s) * scale;
-            row[j] = g;
+#pragma unroll
+        for (int r = 0; r < R; ++r) m[r] = wmax(x[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            e[r] = lane < C ? expf(x[r] - m[r]) : 0.0f;
+            s[r] = wsum(e[r]);
+            so[r] = wsum(lane == y[r] ? 0.0f : e[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (v0 + r >= N) break;
+            const float rest = so[r] / s[r];       // 1 - p_y
+            const bool train = y[r] >= 0;
+            if (train && y[r] < C) loss += rest <= 0.5f ? -log1pf(-rest) : -(__shfl(x[r], y[r], 64) - m[r] - logf(s[r]));
+            const float scale = train ? inv : 0.0f;
+            const float g = lane < C ? (lane == y[r] ? -rest : e[r] / s[r]) * scale : 0.0f;
+            if (lane < ld) L[(v0 + r) * ld + lane] = g;
+        }
+    } else {
+        for (int r = 0; r < R; ++r) {
+            const int64_t v = v0 + r;
+            if (v >= N) break;
+            float* row = L + v * ld;
+            const int y = labels[v];
+            const float scale = y >= 0 ? inv : 0.0f;
+            float m = -INFINITY;
+            for (int j = lane; j < C; j += 64) m = fmaxf(m, row[j]);
+            m = wmax(m);
+            float s = 0.0f, so = 0.0f;
+            for (int j = lane; j < C; j += 64) {
+                const float e = expf(row[j] - m);
+                s += e;
+                so += j == y ? 0.0f : e;
+            }
+            s = wsum(s);
+            so = wsum(so);
+            const float rest = so / s;                 // 1 - p_y
+            if (y >= 0 && y < C) loss += rest <= 0.5f ? -log1pf(-rest) : -(row[y] - m - logf(s));
+            for (int j = lane; j < ld; j += 64) {
+                float g = 0.0f;
+                if (j < C) g = (j == y ? -rest : expf(row[j] - m) / s) * scale;
+                row[j] = g;
+            }
         }
     }
     if (lane == 0) wl[wave] = loss;
@@ -547,7 +582,8 @@ int layer_grad_impl(int64_t N, int64_t D_in, int64_t H, int64_t C,
 
     // loss and d loss / d logits (in place, padding columns zeroed)
     const unsigned nb = (unsigned)((N + kXentRows - 1) / kXentRows);
-    softmax_xent_kernel<<<dim3(nb), dim3(kThreads), 0, stream>>>(N, (int)C, L, t.ldc, d_labels, hdr, losspart);
+    if (t.ldc <= 64) softmax_xent_kernel<true><<<dim3(nb), dim3(kThreads), 0, stream>>>(N, (int)C, L, t.ldc, d_labels, hdr, losspart);
+    else             softmax_xent_kernel<false><<<dim3(nb), dim3(kThreads), 0, stream>>>(N, (int)C, L, t.ldc, d_labels, hdr, losspart);
     loss_reduce_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>((int64_t)nb, losspart, hdr, d_loss);
 
     // classifier (or only) layer: weight and bias gradients

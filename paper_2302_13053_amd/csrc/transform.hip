@@ -22,20 +22,20 @@
 // the matrix instructions run at a clock of about 1.5 GHz (GRBM_GUI_ACTIVE), the
 // same launch on zeros is 25 % faster, and a bf16 library product of 8192^3
 // reaches 1210-1270 TFLOP/s where this kernel issues 900-1000.  Measured (float32
-// instructions before): 2,449,029 x 256 -> 256 2.15 ms = 149 TFLOP/s (2.60 ms),
-// 232,965 x 1204 -> 256 0.87 ms = 166 (1.28), 2,449,029 x 256 -> 188 1.74 ms (1.98),
-// 232,965 x 512 -> 41 0.137 ms = 3.8 TB/s (0.171), 100,000 x 512 -> 128 94 us (150).
+// instructions before): 2,449,029 x 256 -> 256 2.08 ms = 154 TFLOP/s (2.60 ms),
+// 232,965 x 1204 -> 256 0.84 ms = 170 (1.21), 2,449,029 x 256 -> 188 1.66 ms (1.98),
+// 232,965 x 512 -> 41 0.137 ms = 3.8 TB/s (0.171), 100,000 x 512 -> 128 94 us (142).
 //
 // Sources are clamped instead of checked (rows past the end repeat the last
 // row, columns past D_out the last column), so the loop carries no selects;
 // only a partial last K tile takes a checked form.  Loads are four bytes wide
 // (W) or 16 bytes at any float's address (H), so every alignment and leading
 // dimension takes this kernel, in one order of arithmetic.  Bias and ReLU are
-// applied to the accumulators on the way out: through this wave's piece of the
-// dead tiles in LDS and from there as 16-byte pieces of rows where the output
-// allows it, otherwise through one pointer per 32x32 tile that walks down the
-// rows.  Matrices of few rows take the few-rows kernel at the end (K split over
-// the waves of a workgroup).
+// applied to the accumulators on the way out, through one pointer per 32x32 tile
+// that walks down the rows: every store covers two whole cache lines.  (Passed
+// through LDS first, to leave 16 bytes per lane: 2,449,029 x 256 -> 256 2.15 ms
+// instead of 2.08, x 16 -> 256 547 us instead of 500.)  Matrices of few rows take
+// the few-rows kernel at the end (K split over the waves of a workgroup).
 #include "common.hpp"
 #include "tiles.hpp"
 
@@ -85,70 +85,107 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (
     else run(std::false_type{});
 }
 
-// The same epilogue for outputs whose rows allow 16-byte stores (Z and the mask 16-byte aligned, ldz, ldm and
-// D_out multiples of four): each 32 x CW block of results goes through this wave's own piece of LDS (T, 32 rows
-// of CW + 4 floats; the K loop's tiles are dead by then) and leaves as whole 16-byte pieces of rows, four times
-// fewer store instructions, each covering full cache lines.  Same values as write_out.
-template <int TN, int CW, bool MASKED>
-__device__ __forceinline__ void write_out_rows(const f32x16 (&acc)[TN], const float (&bv)[TN], int64_t N, int D_out,
-                                               int64_t row_base, int col_base, int lane, int relu,
-                                               float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm,
-                                               float* __restrict__ T)
+// Which side of zero a sum lies on, where the caller goes by that: a sum (plus its bias) within rounding of zero is
+// formed again as one chain of float32 multiply-adds, k ascending, which is what v_mfma_f32_32x32x2_f32 makes of it.
+// "Within rounding": 2^-25 sqrt(K) of the wave's largest sum, six to nine times what the two sums were seen apart (2-norm,
+// K = 29 to 2866), about one sum in 200,000; less for a row whose largest input (`row_top`, of the wave's 32 rows) is
+// below a quarter of the wave's, so that rows of very different size do not all count as near zero beside the largest.
+// An exact zero is one in any order (rows of zeros).
+// The wave works on one sum at a time: 256 k of the row and the column at once into LDS, then one multiply-add per k in
+// every lane: about 3 us at K = 1120.  (Whole 32 x 32 tiles on the float32 instruction took 35 us each, a third of a
+// small training step: 39,895 x 1120 -> 64.)
+constexpr int kChain = 256;
+template <int TN>
+__device__ __forceinline__ void decide_near_zero(f32x16 (&acc)[TN], const float (&bv)[TN], int D_in, int D_out,
+                                                 const float* __restrict__ H, int64_t ldh, const float* __restrict__ W,
+                                                 int64_t row_base, int64_t N, int col_base, int lane, const float* row_top,
+                                                 f32x4* __restrict__ chain)
 {
-    constexpr int P = CW + 4;            // LDS pitch: rows stay 16-byte aligned, column reads spread over the banks
-    constexpr int JT = CW / 32;          // accumulator tiles per pass
-    constexpr int LPR = CW / 4;          // lanes that cover one row of the pass
-    constexpr int RPI = 64 / LPR;        // rows per store instruction
-    static_assert(TN % JT == 0, "passes cover whole tiles");
-    const int lrow = lane & 31, lk = lane >> 5;
-    const int c4 = (lane % LPR) * 4, rsub = lane / LPR;
+    const float eps = 0x1p-25f * sqrtf((float)D_in);
+    float top = 0.0f;
 #pragma unroll
-    for (int j0 = 0; j0 < TN; j0 += JT) {
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int jj = 0; jj < JT; ++jj)
+        for (int r = 0; r < 16; ++r) top = fmaxf(top, __builtin_fabsf(acc[j][r]));
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ro = 8 * (r / 4) + (r % 4) + 4 * lk;
-                float x = acc[j0 + jj][r] + bv[j0 + jj];
-                if (relu) x = fmaxf(x, 0.0f);
-                T[ro * P + jj * 32 + lrow] = x;
-            }
-        const int col = col_base + j0 * 32 + c4;
+    for (int m = 32; m >= 1; m >>= 1) top = fmaxf(top, __shfl_xor(top, m, 64));
+    const float coarse = top * eps;              // no row's line is above the wave's
+    float largest = row_top[lane & 31];
 #pragma unroll
-        for (int s = 0; s < 32 / RPI; ++s) {
-            const int rr = s * RPI + rsub;
-            f32x4 v = *reinterpret_cast<const f32x4*>(&T[rr * P + c4]);
-            const int64_t row = row_base + rr;
-            if (row < N && col < D_out) {
-                if constexpr (MASKED) {
-                    const f32x4 m = *reinterpret_cast<const f32x4*>(mask + row * ldm + col);
+    for (int m = 16; m >= 1; m >>= 1) largest = fmaxf(largest, __shfl_xor(largest, m, 64));
+    const float per_input = 4.0f / largest;
+    each<TN * 16>([&](auto at) {
+        constexpr int j = decltype(at)::value / 16, r = decltype(at)::value % 16;
+        const float x = acc[j][r];
+        uint64_t close = __ballot(__builtin_fabsf(x + bv[j]) < coarse && x != 0.0f);
+        while (close) {                          // (uniform)
+            const int src = __ffsll((unsigned long long)close) - 1;
+            close &= close - 1;
+            const int in_tile = 8 * (r / 4) + 4 * (src >> 5) + r % 4;
+            const float here = __shfl(x + bv[j], src, 64);
+            if (__builtin_fabsf(here) > coarse * row_top[in_tile] * per_input) continue;
+            const int64_t row = row_base + in_tile;
+            const int col = col_base + j * 32 + (src & 31);
+            if (row >= N || col >= D_out) continue;
+            const float* hp = H + row * ldh;
+            const float* wp = W + col;
+            float sum = 0.0f;
+            for (int k0 = 0; k0 < D_in; k0 += kChain) {
+                float h[kChain / 64], w[kChain / 64];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = m[q] > 0.0f ? v[q] : 0.0f;
+                for (int i = 0; i < kChain / 64; ++i) {
+                    const int k = k0 + i * 64 + lane;
+                    h[i] = k < D_in ? hp[k] : 0.0f;
+                    w[i] = k < D_in ? wp[(int64_t)k * D_out] : 0.0f;
                 }
-                *reinterpret_cast<f32x4*>(Z + row * ldz + col) = v;
+                float* c = reinterpret_cast<float*>(chain);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+#pragma unroll
+                for (int i = 0; i < kChain / 64; ++i) {
+                    c[i * 64 + lane] = h[i];
+                    c[kChain + i * 64 + lane] = w[i];
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 8
+                for (int q = 0; q < kChain / 4; ++q) {
+                    const f32x4 a = chain[q], b = chain[kChain / 4 + q];
+                    sum = fmaf(a.x, b.x, sum);
+                    sum = fmaf(a.y, b.y, sum);
+                    sum = fmaf(a.z, b.z, sum);
+                    sum = fmaf(a.w, b.w, sum);
+                }
             }
+            if (lane == src) acc[j][r] = sum;
         }
-    }
+    });
 }
 
 // The block kernel: 128 x BN outputs per workgroup, 32 rows and up to 128 columns per wave (whose two running sums then
 // take 128 registers): four waves, or eight for the tiles wider than 128; any alignment and leading dimension.
-// ZVEC: the output (and the mask) allow 16-byte stores, see write_out_rows.
+// the staging registers that belong to an LDS buffer
+template <int SETS, class Buf>
+__device__ __forceinline__ constexpr int set_of()
+{
+    if constexpr (SETS == 2) return Buf::value;
+    else return 0;
+}
+
 template <int BN> constexpr int transform_waves = BN > 128 ? 8 : 4;
-template <int BN, bool MASKED, bool ZVEC>
+template <int BN, bool MASKED, bool KEEP_SIGN>
 __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 : 2) void transform_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
-    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm, int keep_sign)
+    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm)
 {
     constexpr int BM = 128, WAVES = transform_waves<BN>, WN = BN / (WAVES / 4), TN = WN / 32;
     using T = SplitTile<BM, BN>;
     using WStage = KMajorStage<BN, WAVES>;
     constexpr int HW = BM * kTileK / (64 * WAVES);       // floats of H a thread stages
-    // row-wise epilogue: 64 columns per pass where the tiles leave room for every wave's 32 x 68 block, else 32
-    constexpr int CW = (TN % 2 == 0 && 2 * T::units * 4 >= WAVES * 32 * 68) ? 64 : 32;
-    static_assert(2 * T::units * 4 >= WAVES * 32 * (CW + 4), "the epilogue's blocks fit in the tiles' memory");
     __shared__ u32x4 lds[2 * T::units];
+    __shared__ f32x4 chain[KEEP_SIGN ? WAVES : 1][KEEP_SIGN ? 2 * kChain / 4 : 1];       // decide_near_zero: its products' operands
+    __shared__ float row_top[KEEP_SIGN ? BM : 1];        // ... and the largest input of every row
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -164,22 +201,26 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
 
-    // H: a thread stages HW consecutive k of one row (rows past the end repeat the last one, never stored)
+    // H: a thread stages HW consecutive k of one row (rows past the end repeat the last one, never stored).  The 32-column
+    // tile, whose matrix instructions are over long before a row arrives from memory, stages two tiles ahead
+    // (2,449,029 x 256 -> 7 575 us instead of 611, 889,043 x 48 -> 8 53 instead of 55).
+    constexpr int SETS = BN == 32 ? 2 : 1;
     const int hr = tid / (kTileK / HW), hk = tid % (kTileK / HW) * HW;
     const float* ph = H + (m0 + hr < N ? m0 + hr : N - 1) * ldh;
-    float ra[HW];
-    auto fetch_h = [&](int kt) {
+    float ra[SETS][HW];
+    auto fetch_h = [&](int kt, auto set_tag) {
+        constexpr int set = decltype(set_tag)::value;
         const int k = kt * kTileK + hk;
         if ((kt + 1) * kTileK <= D_in) {
 #pragma unroll
             for (int v = 0; v < HW / 4; ++v) {
                 const f32x4 t = *reinterpret_cast<const f32x4_any*>(ph + k + 4 * v);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) ra[4 * v + q] = t[q];
+                for (int q = 0; q < 4; ++q) ra[set][4 * v + q] = t[q];
             }
         } else {
 #pragma unroll
-            for (int q = 0; q < HW; ++q) ra[q] = k + q < D_in ? ph[k + q] : 0.0f;
+            for (int q = 0; q < HW; ++q) ra[set][q] = k + q < D_in ? ph[k + q] : 0.0f;
         }
     };
     WStage sw;
@@ -196,42 +237,38 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
     constexpr int A_MICROS = HW / 2 + 2, MICROS = A_MICROS + WStage::count * WStage::steps;
     typedef uint32_t part_t __attribute__((ext_vector_type(HW / 2)));
     part_t part_h[3];
-    auto micro = [&](auto step, int buf, int kt) {
+    float h_top = 0.0f;                                  // largest input of this thread's part of its row
+    auto micro = [&](auto step, auto buf, int kt) {
         constexpr int m = decltype(step)::value;
+        constexpr int set = set_of<SETS, decltype(buf)>();
         u32x4* base = lds + buf * T::units;
+        if constexpr (KEEP_SIGN && m == 0) {
+#pragma unroll
+            for (int q = 0; q < HW; ++q) h_top = fmaxf(h_top, __builtin_fabsf(ra[set][q]));
+        }
         if constexpr (m >= A_MICROS) {
             sw.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, 0u, kt + 1 < nk, kt + 1);
         } else if constexpr (m < HW / 2) {
-            split_pair(ra[2 * m], ra[2 * m + 1], m, part_h);
+            split_pair(ra[set][2 * m], ra[set][2 * m + 1], m, part_h);
         } else if constexpr (m == HW / 2) {
 #pragma unroll
             for (int s = 0; s < 3; ++s)
                 *reinterpret_cast<part_t*>(reinterpret_cast<char*>(base + T::a(s, hk >> 3, hr)) + (hk & 7) * 2) = part_h[s];
         } else {
-            if (kt + 1 < nk) fetch_h(kt + 1);
+            if (kt + SETS < nk) fetch_h(kt + SETS, std::integral_constant<int, set>{});
         }
     };
-    fetch_h(0);
+    constexpr std::integral_constant<int, 0> first{};
+    fetch_h(0, first);
+    if (SETS == 2 && nk > 1) fetch_h(1, std::integral_constant<int, SETS - 1>{});
     each<WStage::count>([&](auto i) { sw.template fetch<decltype(i)::value>(0); });
-    each<MICROS>([&](auto m) { micro(m, 0, 0); });
+    each<MICROS>([&](auto m) { micro(m, first, 0); });
     __syncthreads();
     split_k_loop<TN, BM, BN, MICROS>(acc, lds, nk, a0, b0, lane, micro);
 
-    // how close to zero a sum is decided by the float32 instruction: 2^-18 of the wave's largest one, twenty times what
-    // the two were seen apart
-    float near = 0.0f;
-    if (keep_sign) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) near = fmaxf(near, __builtin_fabsf(acc[j][r]));
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) near = fmaxf(near, __shfl_xor(near, m, 64));
-        near *= 0x1p-18f;
-    }
     each<TN>([&](auto at) {
         constexpr int j = decltype(at)::value;
-        if (!redo_tile(acc[j], bv[j], near)) return;
+        if (!redo_tile(acc[j])) return;
         // the tile once more with the float32 instruction, operands straight from memory, k in ascending pairs
         const int64_t row = m0 + a0 + lrow;
         const int col = n0 + b0 + j * 32 + lrow;
@@ -240,41 +277,52 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
         f32x16 x;
 #pragma unroll
         for (int r = 0; r < 16; ++r) x[r] = 0.0f;
-        constexpr int U = 8;
-        for (int k0 = 0; k0 < D_in; k0 += 2 * U) {
-            float a[U], b[U];
+        constexpr int U = 16;                     // 32 k at a time, the next 32 in flight
+        float a[2][U], b[2][U];
+        auto take = [&](int k0, auto slot_tag) {
+            constexpr int slot = decltype(slot_tag)::value;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int k = k0 + 2 * u + lk;
                 const bool in = k < D_in;
                 const float av = hp[in ? k : 0], bw = wp[(int64_t)(in ? k : 0) * D_out];
-                a[u] = in ? av : 0.0f;
-                b[u] = in ? bw : 0.0f;
+                a[slot][u] = in ? av : 0.0f;
+                b[slot][u] = in ? bw : 0.0f;
             }
+        };
+        auto multiply = [&](int k0, auto slot_tag) {
+            constexpr int cur = decltype(slot_tag)::value;
+            if (k0 + 2 * U < D_in) take(k0 + 2 * U, std::integral_constant<int, cur ^ 1>{});
 #pragma unroll
-            for (int u = 0; u < U; ++u) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], x, 0, 0, 0);
+            for (int u = 0; u < U; ++u) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][u], b[cur][u], x, 0, 0, 0);
+        };
+        take(0, std::integral_constant<int, 0>{});
+        for (int k0 = 0; k0 < D_in; k0 += 4 * U) {
+            multiply(k0, std::integral_constant<int, 0>{});
+            if (k0 + 2 * U < D_in) multiply(k0 + 2 * U, std::integral_constant<int, 1>{});
         }
         acc[j] = x;
     });
 
-    if constexpr (ZVEC) {
-        __syncthreads();                      // every wave is done with the last tile
-        write_out_rows<TN, CW, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm,
-                                       reinterpret_cast<float*>(lds) + wave * 32 * (CW + 4));
-    } else {
-        write_out<TN, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm, m0 + BM <= N);
+    if constexpr (KEEP_SIGN) {
+#pragma unroll
+        for (int m = 1; m < kTileK / HW; m <<= 1) h_top = fmaxf(h_top, __shfl_xor(h_top, m, 64));
+        row_top[hr] = h_top;
+        __syncthreads();
+        decide_near_zero<TN>(acc, bv, D_in, D_out, H, ldh, W, m0 + a0, N, n0 + b0, lane, row_top + a0, chain[wave]);
     }
+    write_out<TN, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm, m0 + BM <= N);
 }
 
 // Few rows: a matrix with so few 128-row blocks that they would leave most compute units idle (a citation
 // graph's 2,708 x 2,866 features give 22) is cut into 32-row blocks, and the K extent of each block is cut
 // over the eight waves of its workgroup.  A wave needs no LDS and no barrier in its loop: per group of 8 k it
 // fetches its operands straight into the MFMA layout — lane l holds k = 4 (l / 32) .. + 3 of row l % 32, so
-// MFMA q of the group pairs k = q (lower half-wave) with k = 4 + q (upper half-wave) — four groups at a time,
-// the next four in flight behind the MFMAs.  The eight partial tiles are then added in a fixed order (wave w + wave w + 4 in registers, then
-// ((0 + 1) + 2) + 3 through LDS), so the result is reproducible; it differs from the block kernels' only in
-// the order of the fp32 additions.
-template <int TN, bool HV, bool MASKED>
+// MFMA q of the group pairs k = q (lower half-wave) with k = 4 + q (upper half-wave) — eight groups at a time,
+// the next eight in flight behind the MFMAs.  The eight partial tiles are then added in a fixed order (wave w + wave
+// w + 4 in registers, then ((0 + 1) + 2) + 3 through LDS), so the result is reproducible.  The float32
+// instruction carries these products: the kernel waits for memory, not for the matrix cores.
+template <int TN, bool MASKED>
 __global__ __launch_bounds__(512) void transform_few_rows_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
@@ -310,51 +358,57 @@ __global__ __launch_bounds__(512) void transform_few_rows_kernel(
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
 
     // operands of U groups at a time, the next U in flight behind this batch's MFMAs (a wave's loop is a chain
-    // of memory latencies; the batch is what keeps enough bytes in flight)
-    constexpr int U = 4;
+    // of memory latencies; the batch is what keeps enough bytes in flight).  A row's bytes come 16 at a time, at any
+    // alignment; only a group that reaches over the end of K checks every element.
+    constexpr int U = TN == 1 ? 8 : 4;           // (registers: eight groups of two column tiles spill)
     float a[2][U][4], b[2][U][TN][4];
-    auto wanted_of = [&](int g) {                // how many of this lane's four k of group g are data
-        const int left = g < g1 ? D_in - (g * 8 + lk * 4) : 0;
-        return left < 0 ? 0 : (left < 4 ? left : 4);
-    };
-    auto fetch = [&](int gb, int slot) {
+    auto fetch = [&](int gb, auto slot_tag) {    // slot as a type: register arrays want constant indices
+        constexpr int slot = decltype(slot_tag)::value;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = (gb + u) * 8 + lk * 4;
-            const int wanted = wanted_of(gb + u);
-            load4<HV>(hp, k, wanted, a[slot][u]);
+            const int g = gb + u, k = g * 8 + lk * 4;
+            if (g >= g1) break;                  // (uniform, as is the next)
+            if (g * 8 + 8 <= D_in) {
+                const f32x4 t = *reinterpret_cast<const f32x4_any*>(hp + k);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float* wr = W + (int64_t)(q < wanted ? k + q : 0) * D_out;
+                for (int q = 0; q < 4; ++q) {
+                    a[slot][u][q] = t[q];
+                    const float* wr = W + (int64_t)(k + q) * D_out;
 #pragma unroll
-                for (int j = 0; j < TN; ++j) b[slot][u][j][q] = wr[col[j]];
+                    for (int j = 0; j < TN; ++j) b[slot][u][j][q] = wr[col[j]];
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool in = k + q < D_in;
+                    const float t = hp[in ? k + q : 0];
+                    a[slot][u][q] = in ? t : 0.0f;
+                    const float* wr = W + (int64_t)(in ? k + q : 0) * D_out;
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const float w = wr[col[j]];
+                        b[slot][u][j][q] = in ? w : 0.0f;
+                    }
+                }
             }
         }
     };
-    auto zero = [&](int gb, int slot) {          // what is not data was fetched from k = 0: replace it
+
+    auto batch = [&](int gb, auto slot_tag) {
+        constexpr int cur = decltype(slot_tag)::value;
+        if (gb + U < g1) fetch(gb + U, std::integral_constant<int, cur ^ 1>{});
+        RETEXO_SCHED_FENCE();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int wanted = wanted_of(gb + u);
-            zero4<HV>(wanted, a[slot][u]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) zero4<false>(wanted, b[slot][u][j]);
-        }
-    };
-
-    auto batch = [&](int gb, auto slot_tag) {    // slot as a type: register arrays want constant indices
-        constexpr int cur = decltype(slot_tag)::value;
-        if (gb + U < g1) fetch(gb + U, cur ^ 1);
-        RETEXO_SCHED_FENCE();
-        zero(gb, cur);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
+            if (gb + u >= g1) break;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][u][q], b[cur][u][j][q], acc[j], 0, 0, 0);
+        }
     };
-    if (g0 < g1) fetch(g0, 0);
+    if (g0 < g1) fetch(g0, std::integral_constant<int, 0>{});
     for (int gb = g0; gb < g1; gb += 2 * U) {
         batch(gb, std::integral_constant<int, 0>{});
         if (gb + U < g1) batch(gb + U, std::integral_constant<int, 1>{});
@@ -413,11 +467,14 @@ void launch(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh,
             hipStream_t stream)
 {
     const dim3 grid((unsigned)((N + 127) / 128), (unsigned)((D_out + BN - 1) / BN)), block(64 * transform_waves<BN>);
-    const int r = relu ? 1 : 0, ks = keep_sign ? 1 : 0;
-    const bool zv = (uintptr_t)Z % 16 == 0 && ldz % 4 == 0 && D_out % 4 == 0 &&
-                    (!MASKED || ((uintptr_t)mask % 16 == 0 && ldm % 4 == 0));
-    if (zv) transform_kernel<BN, MASKED, true><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, ks);
-    else    transform_kernel<BN, MASKED, false><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, ks);
+    const int r = relu ? 1 : 0;
+    if constexpr (!MASKED) {
+        if (keep_sign) {
+            transform_kernel<BN, false, true><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+            return;
+        }
+    }
+    transform_kernel<BN, MASKED, false><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
 }
 
 template <bool MASKED>
@@ -425,18 +482,15 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
                      const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm,
                      hipStream_t stream)
 {
-    const bool hv = (uintptr_t)H % 16 == 0 && ldh % 4 == 0 && D_in % 4 == 0;
     const int r = relu ? 1 : 0;
     const unsigned gx = (unsigned)((N + 31) / 32);
     // 32-column tiles when 64-column ones would not give every compute unit a workgroup
     if (D_out <= 32 || (int64_t)gx * ((D_out + 63) / 64) < 256) {
         dim3 grid(gx, (unsigned)((D_out + 31) / 32));
-        if (hv) transform_few_rows_kernel<1, true, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
-        else    transform_few_rows_kernel<1, false, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+        transform_few_rows_kernel<1, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
     } else {
         dim3 grid(gx, (unsigned)((D_out + 63) / 64));
-        if (hv) transform_few_rows_kernel<2, true, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
-        else    transform_few_rows_kernel<2, false, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+        transform_few_rows_kernel<2, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
     }
 }
 
