@@ -18,10 +18,12 @@
 //
 // Both halves of the numbering are monotone in the global id, so a renumbered
 // row is its inner entries (ascending) followed by its boundary entries
-// (ascending): a stable two-way split inside each row, no per-row sort.
+// (ascending): a stable two-way split inside each row, no per-row sort.  The
+// lists are a stable split of the nodes by peer in the same way: blocks of 256
+// nodes count their members of every list, a scan over (list, block) places
+// them, and every block writes its own.
 #include <cstring>
 
-#include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_reduce.hpp>
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/iterator/counting_iterator.hpp>
@@ -52,37 +54,64 @@ __device__ __forceinline__ uint64_t wave_or(uint64_t x)
     return x;
 }
 
-// one wave per global row: an inner row marks the foreign endpoints of its entries as boundary
-// nodes and collects the set of workers it touches
+// state of a node while its share is derived: its owner, and whether it was found to be a boundary node
+constexpr uint32_t kBoundary = 0x80000000u;
+
+__global__ __launch_bounds__(kThreads) void state_kernel(int64_t N, const int32_t* __restrict__ part, int n_parts,
+                                                         uint32_t* __restrict__ state, ShareHeader* hdr)
+{
+    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (v >= N) return;
+    const int q = part[v];
+    const bool bad = q < 0 || q >= n_parts;
+    if (bad) atomicOr(&hdr->bad_part, 1u);
+    state[v] = bad ? 0xffffu : (uint32_t)q;       // (no worker has that id; the call ends in an error)
+}
+
+// One wave per global row: an inner row marks the foreign endpoints of its entries as boundary nodes, collects the set of
+// workers it touches and counts its inner entries (columns_kernel then needs one pass).
+// Bound by the gathers of one word per entry, so owner and mark share that word (a node is marked by the first rows that
+// meet it, after that the mark is only read: 21 million stores to the Reddit-shaped graph's 0.17 million nodes were most
+// of this kernel's time), and four tiles of 64 entries are in flight per wave.  Worker 0 of 4 there: 415 -> 230 us
+// (eight in flight: 209, sixteen: 199, but short rows then issue that many empty tiles).
+constexpr int kAhead = 4;
 __global__ __launch_bounds__(kThreads) void mark_kernel(
     int64_t N, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    const int32_t* __restrict__ part, int n_parts, int p, uint32_t* __restrict__ halo_flag,
-    uint64_t* __restrict__ mask, ShareHeader* hdr)
+    int p, uint32_t* state, uint64_t* __restrict__ mask, uint32_t* __restrict__ inner_entries)
 {
     const int lane = threadIdx.x & 63;
     const int64_t v = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
     if (v >= N) return;
-    const int pv = part[v];
-    if (pv < 0 || pv >= n_parts) {
-        if (lane == 0) atomicOr(&hdr->bad_part, 1u);
-        if (lane == 0) mask[v] = 0;
-        return;
-    }
     uint64_t m = 0;
-    if (pv == p) {
+    uint32_t inner = 0;
+    if ((state[v] & 0xffffu) == (uint32_t)p) {
         const int64_t lo = row_ptr[v], hi = row_ptr[v + 1];
-        for (int64_t e = lo + lane; e < hi; e += 64) {
-            const int32_t u = col_idx[e];
-            const int q = part[u];
-            if (q < 0 || q >= n_parts) continue;          // reported by u's own wave
-            if (q != p) {
-                halo_flag[u] = 1u;                        // every writer stores the same value
-                m |= 1ull << q;
+        for (int64_t e0 = lo; e0 < hi; e0 += 64 * kAhead) {
+            int32_t u[kAhead];
+            uint32_t st[kAhead];
+#pragma unroll
+            for (int t = 0; t < kAhead; ++t) {
+                const int64_t e = e0 + 64 * t + lane;
+                u[t] = e < hi ? col_idx[e] : -1;
+            }
+#pragma unroll
+            for (int t = 0; t < kAhead; ++t) st[t] = u[t] >= 0 ? state[u[t]] : 0xffffu;
+#pragma unroll
+            for (int t = 0; t < kAhead; ++t) {
+                const uint32_t q = st[t] & 0xffffu;
+                inner += (uint32_t)__popcll(__ballot(q == (uint32_t)p));
+                if (q != (uint32_t)p && q != 0xffffu) {
+                    m |= 1ull << q;
+                    if (!(st[t] & kBoundary)) state[u[t]] = st[t] | kBoundary;      // every writer stores the same value
+                }
             }
         }
         m = wave_or(m);
     }
-    if (lane == 0) mask[v] = m;
+    if (lane == 0) {
+        mask[v] = m;
+        inner_entries[v] = inner;
+    }
 }
 
 struct IsInner {
@@ -96,9 +125,9 @@ struct InnerRowLength {
     int p;
     __device__ int64_t operator()(int64_t v) const { return part[v] == p ? row_ptr[v + 1] - row_ptr[v] : 0; }
 };
-struct PeerCount {
-    const uint64_t* mask;
-    __device__ uint32_t operator()(int64_t v) const { return (uint32_t)__popcll(mask[v]); }
+struct IsBoundary {
+    const uint32_t* state;
+    __device__ uint32_t operator()(int64_t v) const { return state[v] >> 31; }
 };
 struct LocalRowLength {               // row length of local node i (0 for boundary nodes and for i == n_local)
     const int32_t* local_ids;
@@ -112,43 +141,96 @@ struct LocalRowLength {               // row length of local node i (0 for bound
     }
 };
 
-// totals of the three exclusive scans (last scan value + last element), N >= 1
-__global__ void totals_kernel(int64_t N, const int32_t* __restrict__ part, int p,
-                              const uint32_t* __restrict__ rank_in, const uint32_t* __restrict__ halo_flag,
-                              const uint32_t* __restrict__ rank_halo, const uint32_t* __restrict__ key_off,
-                              const uint64_t* __restrict__ mask, ShareHeader* hdr)
+// The 2 * n_parts lists (list q: what peer q is sent, list n_parts + q: what it sends): members per block of kThreads
+// nodes, counts[list * blocks + block].  A wave counts its 64 nodes with one ballot per list.
+__device__ __forceinline__ uint64_t list_members(int list, int n_parts, uint64_t m, uint32_t st)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    hdr->n_inner = (int64_t)rank_in[N - 1] + (part[N - 1] == p ? 1 : 0);
-    hdr->n_halo = (int64_t)rank_halo[N - 1] + (int64_t)halo_flag[N - 1];
-    hdr->n_send = (int64_t)key_off[N - 1] + __popcll(mask[N - 1]);
+    return __ballot(list < n_parts ? (m >> list) & 1ull : (st & kBoundary) && (st & 0xffffu) == (uint32_t)(list - n_parts));
+}
+__global__ __launch_bounds__(kThreads) void list_count_kernel(int64_t N, int n_parts, const uint32_t* __restrict__ state,
+                                                              const uint64_t* __restrict__ mask, int64_t blocks,
+                                                              uint32_t* __restrict__ counts)
+{
+    __shared__ uint32_t sh[kThreads / 64][2 * kMaxWorkers];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const uint64_t m = v < N ? mask[v] : 0ull;
+    const uint32_t st = v < N ? state[v] : 0u;
+    for (int l = 0; l < 2 * n_parts; ++l) {
+        const uint32_t c = (uint32_t)__popcll(list_members(l, n_parts, m, st));
+        if (lane == 0) sh[wave][l] = c;
+    }
+    __syncthreads();
+    for (int l = threadIdx.x; l < 2 * n_parts; l += kThreads)
+        counts[(int64_t)l * blocks + blockIdx.x] = (sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l]);
 }
 
-// local numbering, global ids and degrees of the local nodes, and (for inner nodes) the offset
-// of their (peer, node) keys
-__global__ __launch_bounds__(kThreads) void number_kernel(
-    int64_t N, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ part, int p,
-    const uint32_t* __restrict__ rank_in, const uint32_t* __restrict__ halo_flag,
-    const uint32_t* __restrict__ rank_halo, int64_t n_inner, int32_t* __restrict__ to_local,
-    int32_t* __restrict__ local_ids, int32_t* __restrict__ global_deg)
+// totals of the scans (last scan value + last element), N >= 1; the lists' offsets are their first blocks' positions
+__global__ __launch_bounds__(kThreads) void totals_kernel(int64_t N, const int32_t* __restrict__ part, int p, int n_parts,
+                                                          const uint32_t* __restrict__ rank_in, const uint32_t* __restrict__ state,
+                                                          const uint32_t* __restrict__ rank_halo, int64_t blocks,
+                                                          const uint32_t* __restrict__ list_at, ShareHeader* hdr)
 {
-    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (v >= N) return;
-    int64_t l = -1;
-    if (part[v] == p) l = rank_in[v];
-    else if (halo_flag[v]) l = n_inner + rank_halo[v];
-    to_local[v] = (int32_t)l;
-    if (l >= 0) {
-        local_ids[l] = (int32_t)v;
-        global_deg[l] = (int32_t)(row_ptr[v + 1] - row_ptr[v]);
+    const int64_t n_halo = (int64_t)rank_halo[N - 1] + (int64_t)(state[N - 1] >> 31);
+    const int64_t n_send = list_at[(int64_t)n_parts * blocks];
+    for (int l = threadIdx.x; l <= n_parts; l += kThreads) {
+        hdr->send_off[l] = list_at[(int64_t)l * blocks];
+        hdr->recv_off[l] = l == n_parts ? n_halo : (int64_t)list_at[(int64_t)(n_parts + l) * blocks] - n_send;
+    }
+    if (threadIdx.x == 0) {
+        hdr->n_inner = (int64_t)rank_in[N - 1] + (part[N - 1] == p ? 1 : 0);
+        hdr->n_halo = n_halo;
+        hdr->n_send = n_send;
     }
 }
 
-// one wave per inner local row: renumber the global row; inner entries first, then boundary
-// entries, each group in its original (ascending) order
+// local numbering, global ids and degrees of the local nodes, and the members of the lists: a wave's members of a list go
+// behind those of the waves and blocks before it
+__global__ __launch_bounds__(kThreads) void number_kernel(
+    int64_t N, const int64_t* __restrict__ row_ptr, int p, int n_parts,
+    const uint32_t* __restrict__ rank_in, const uint32_t* __restrict__ state, const uint64_t* __restrict__ mask,
+    const uint32_t* __restrict__ rank_halo, int64_t n_inner, int64_t n_send, int64_t blocks,
+    const uint32_t* __restrict__ list_at, int32_t* __restrict__ to_local,
+    int32_t* __restrict__ local_ids, int32_t* __restrict__ global_deg, int32_t* __restrict__ send_ids,
+    int32_t* __restrict__ recv_ids)
+{
+    __shared__ uint32_t sh[kThreads / 64][2 * kMaxWorkers];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t st = v < N ? state[v] : 0u;
+    const uint64_t m = v < N ? mask[v] : 0ull;
+    int64_t l = -1;
+    if (v < N) {
+        if ((st & 0xffffu) == (uint32_t)p) l = rank_in[v];
+        else if (st & kBoundary) l = n_inner + rank_halo[v];
+        to_local[v] = (int32_t)l;
+        if (l >= 0) {
+            local_ids[l] = (int32_t)v;
+            global_deg[l] = (int32_t)(row_ptr[v + 1] - row_ptr[v]);
+        }
+    }
+    for (int q = 0; q < 2 * n_parts; ++q) {
+        const uint32_t c = (uint32_t)__popcll(list_members(q, n_parts, m, st));
+        if (lane == 0) sh[wave][q] = c;
+    }
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1;
+    for (int q = 0; q < 2 * n_parts; ++q) {
+        const uint64_t members = list_members(q, n_parts, m, st);
+        if (!((members >> lane) & 1ull)) continue;
+        int64_t at = (int64_t)list_at[(int64_t)q * blocks + blockIdx.x] + __popcll(members & below);
+        for (int w = 0; w < wave; ++w) at += sh[w][q];
+        if (q < n_parts) send_ids[at] = (int32_t)l;
+        else recv_ids[at - n_send] = (int32_t)l;
+    }
+}
+
+// One wave per inner local row: renumber the global row; inner entries first, then boundary entries, each group in its
+// original (ascending) order.  Four tiles of 64 entries in flight, as in mark_kernel (worker 0 of 4 of the Reddit-shaped
+// graph: 457 -> 192 us; half of it was a pass that counted the inner entries first).
 __global__ __launch_bounds__(kThreads) void columns_kernel(
     int64_t n_inner, const int32_t* __restrict__ local_ids, const int64_t* __restrict__ row_ptr,
-    const int32_t* __restrict__ col_idx, const int32_t* __restrict__ to_local,
+    const int32_t* __restrict__ col_idx, const int32_t* __restrict__ to_local, const uint32_t* __restrict__ inner_entries,
     const int64_t* __restrict__ local_row_ptr, int32_t* __restrict__ local_col)
 {
     const int lane = threadIdx.x & 63;
@@ -157,69 +239,25 @@ __global__ __launch_bounds__(kThreads) void columns_kernel(
     const int64_t v = local_ids[i];
     const int64_t lo = row_ptr[v], hi = row_ptr[v + 1], base = local_row_ptr[i];
     const uint64_t below = (1ull << lane) - 1;
-    int64_t inner_total = 0;
-    for (int64_t e0 = lo; e0 < hi; e0 += 64) {
-        const int64_t e = e0 + lane;
-        const bool in = e < hi && to_local[col_idx[e]] < n_inner;
-        inner_total += __popcll(__ballot(in));
-    }
-    int64_t done_in = 0, done_out = 0;
-    for (int64_t e0 = lo; e0 < hi; e0 += 64) {
-        const int64_t e = e0 + lane;
-        const bool valid = e < hi;
-        const int32_t l = valid ? to_local[col_idx[e]] : 0;
-        const bool in = valid && l < n_inner;
-        const bool out = valid && !in;
-        const uint64_t bin = __ballot(in), bout = __ballot(out);
-        if (in) local_col[base + done_in + __popcll(bin & below)] = l;
-        if (out) local_col[base + inner_total + done_out + __popcll(bout & below)] = l;
-        done_in += __popcll(bin);
-        done_out += __popcll(bout);
-    }
-}
-
-// keys (kind, peer, local id): kind 0 = send (one key per (inner node, peer it touches)),
-// kind 1 = receive (one key per boundary node, peer = its owner)
-__global__ __launch_bounds__(kThreads) void keys_kernel(
-    int64_t n_inner, int64_t n_halo, const int32_t* __restrict__ local_ids,
-    const int32_t* __restrict__ part, const uint64_t* __restrict__ mask,
-    const uint32_t* __restrict__ key_off, int64_t n_send, uint64_t* __restrict__ keys)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n_inner) {
-        const int64_t v = local_ids[i];
-        uint64_t m = mask[v];
-        int64_t k = key_off[v];
-        while (m) {
-            const int q = __ffsll((unsigned long long)m) - 1;
-            m &= m - 1;
-            keys[k++] = ((uint64_t)q << 32) | (uint64_t)i;
+    int64_t at_in = base, at_out = base + inner_entries[v];
+    for (int64_t e0 = lo; e0 < hi; e0 += 64 * kAhead) {
+        int32_t u[kAhead], l[kAhead];
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) {
+            const int64_t e = e0 + 64 * t + lane;
+            u[t] = e < hi ? col_idx[e] : -1;
         }
-    } else if (i < n_inner + n_halo) {
-        const int q = part[local_ids[i]];
-        keys[n_send + (i - n_inner)] = (1ull << 40) | ((uint64_t)q << 32) | (uint64_t)i;
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void lists_kernel(
-    int64_t n_send, int64_t n_halo, const uint64_t* __restrict__ keys, int n_parts,
-    int32_t* __restrict__ send_ids, int32_t* __restrict__ recv_ids, ShareHeader* hdr)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n_send) send_ids[i] = (int32_t)(keys[i] & 0xffffffffu);
-    else if (i < n_send + n_halo) recv_ids[i - n_send] = (int32_t)(keys[i] & 0xffffffffu);
-    // offsets: first key of each (kind, peer) group, by binary search
-    if (i <= 2 * (int64_t)n_parts + 1) {
-        const int kind = i > n_parts ? 1 : 0;
-        const int q = (int)(kind ? i - n_parts - 1 : i);
-        const uint64_t want = ((uint64_t)kind << 40) | ((uint64_t)q << 32);
-        int64_t lo = 0, hi = n_send + n_halo;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (keys[mid] < want) lo = mid + 1; else hi = mid;
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) l[t] = u[t] >= 0 ? to_local[u[t]] : 0;
+#pragma unroll
+        for (int t = 0; t < kAhead; ++t) {
+            const bool valid = u[t] >= 0, in = valid && l[t] < n_inner, out = valid && !in;
+            const uint64_t bin = __ballot(in), bout = __ballot(out);
+            if (in) local_col[at_in + __popcll(bin & below)] = l[t];
+            if (out) local_col[at_out + __popcll(bout & below)] = l[t];
+            at_in += __popcll(bin);
+            at_out += __popcll(bout);
         }
-        if (kind) hdr->recv_off[q] = lo - n_send;
-        else hdr->send_off[q] = lo;
     }
 }
 
@@ -260,13 +298,15 @@ __global__ __launch_bounds__(kThreads) void set_degrees_kernel(int64_t N, const 
 }
 
 struct Layout {
-    int64_t header, mask, halo_flag, rank_in, rank_halo, key_off, to_local, keys_a, keys_b, tmp, total;
+    int64_t header, mask, state, rank_in, rank_halo, inner_entries, to_local, counts, list_at, tmp, blocks, total;
     size_t tmp_bytes;
 };
 
-int make_layout(int64_t N, int64_t send_capacity, Layout& L)
+int make_layout(int64_t N, int n_parts, Layout& L)
 {
-    const int64_t n = N > 0 ? N : 1, K = send_capacity + n;
+    const int64_t n = N > 0 ? N : 1;
+    L.blocks = (n + kThreads - 1) / kThreads;
+    const int64_t lists = 2 * (int64_t)n_parts * L.blocks + 1;
     size_t a = 0, b = 0, c = 0, d = 0;
     auto it32 = rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0), IsInner{nullptr, 0});
     auto it64 = rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0),
@@ -277,21 +317,21 @@ int make_layout(int64_t N, int64_t send_capacity, Layout& L)
                                 rocprim::plus<int64_t>(), (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
     if (rocprim::reduce(nullptr, c, it64, (int64_t*)nullptr, (int64_t)0, (size_t)n, rocprim::plus<int64_t>(),
                         (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
-    if (rocprim::radix_sort_keys(nullptr, d, (uint64_t*)nullptr, (uint64_t*)nullptr, (size_t)K, 0u, 41u,
-                                 (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
+    if (rocprim::exclusive_scan(nullptr, d, (uint32_t*)nullptr, (uint32_t*)nullptr, 0u, (size_t)lists, rocprim::plus<uint32_t>(),
+                                (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
     L.tmp_bytes = a > b ? a : b;
     if (c > L.tmp_bytes) L.tmp_bytes = c;
     if (d > L.tmp_bytes) L.tmp_bytes = d;
     int64_t off = 0;
     L.header = off;    off += align_up((int64_t)sizeof(ShareHeader), 256);
     L.mask = off;      off += align_up(8 * n, 256);
-    L.halo_flag = off; off += align_up(4 * n, 256);
+    L.state = off;     off += align_up(4 * n, 256);
     L.rank_in = off;   off += align_up(4 * n, 256);
     L.rank_halo = off; off += align_up(4 * n, 256);
-    L.key_off = off;   off += align_up(4 * n, 256);
+    L.inner_entries = off; off += align_up(4 * n, 256);
     L.to_local = off;  off += align_up(4 * n, 256);
-    L.keys_a = off;    off += align_up(8 * K, 256);
-    L.keys_b = off;    off += align_up(8 * K, 256);
+    L.counts = off;    off += align_up(4 * lists, 256);
+    L.list_at = off;   off += align_up(4 * lists, 256);
     L.tmp = off;       off += align_up((int64_t)L.tmp_bytes, 256);
     L.total = off;
     return RETEXO_OK;
@@ -319,7 +359,7 @@ extern "C" int64_t retexo_partition_workspace_bytes(int64_t N, int n_parts, int6
     if (n_parts < 1 || n_parts > kMaxWorkers) return RETEXO_E_SIZE;
     if (N * (int64_t)(n_parts - 1) >= (1ll << 31)) return RETEXO_E_SIZE;     // 32-bit offsets of the send keys
     Layout L;
-    if (int s = make_layout(N, send_capacity, L)) return s;
+    if (int s = make_layout(N, n_parts, L)) return s;
     return L.total;
 }
 
@@ -338,42 +378,45 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     if (!h_sizes) return RETEXO_E_NULL;
     if (N > 0 && (!d_row_ptr || !d_part)) return RETEXO_E_NULL;
     Layout L;
-    if (int s = make_layout(N, send_capacity, L)) return s;
+    if (int s = make_layout(N, n_parts, L)) return s;
     if (!d_workspace || ((uintptr_t)d_workspace & 255) || workspace_bytes < L.total) return RETEXO_E_WORKSPACE;
 
     hipStream_t stream = (hipStream_t)stream_;
     char* ws = (char*)d_workspace;
     ShareHeader* hdr = (ShareHeader*)(ws + L.header);
     uint64_t* mask = (uint64_t*)(ws + L.mask);
-    uint32_t* halo_flag = (uint32_t*)(ws + L.halo_flag);
+    uint32_t* state = (uint32_t*)(ws + L.state);
     uint32_t* rank_in = (uint32_t*)(ws + L.rank_in);
     uint32_t* rank_halo = (uint32_t*)(ws + L.rank_halo);
-    uint32_t* key_off = (uint32_t*)(ws + L.key_off);
+    uint32_t* inner_entries = (uint32_t*)(ws + L.inner_entries);
     int32_t* to_local = (int32_t*)(ws + L.to_local);
-    uint64_t* keys_a = (uint64_t*)(ws + L.keys_a);
-    uint64_t* keys_b = (uint64_t*)(ws + L.keys_b);
+    uint32_t* counts = (uint32_t*)(ws + L.counts);
+    uint32_t* list_at = (uint32_t*)(ws + L.list_at);
     void* tmp = ws + L.tmp;
 
     RETEXO_HIP_TRY(hipMemsetAsync(hdr, 0, sizeof(ShareHeader), stream));
+    const dim3 node_grid((unsigned)L.blocks);
     if (N > 0) {
-        RETEXO_HIP_TRY(hipMemsetAsync(halo_flag, 0, (size_t)N * 4, stream));
+        state_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(N, d_part, n_parts, state, hdr);
         const int rows_per_block = kThreads / 64;
         mark_kernel<<<dim3((unsigned)((N + rows_per_block - 1) / rows_per_block)), dim3(kThreads), 0, stream>>>(
-            N, d_row_ptr, d_col_idx, d_part, n_parts, part, halo_flag, mask, hdr);
+            N, d_row_ptr, d_col_idx, part, state, mask, inner_entries);
         auto count = rocprim::make_counting_iterator<int64_t>(0);
         size_t tb = L.tmp_bytes;
         RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, rocprim::make_transform_iterator(count, IsInner{d_part, part}),
                                                rank_in, 0u, (size_t)N, rocprim::plus<uint32_t>(), stream));
         tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, halo_flag, rank_halo, 0u, (size_t)N,
-                                               rocprim::plus<uint32_t>(), stream));
+        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, rocprim::make_transform_iterator(count, IsBoundary{state}), rank_halo,
+                                               0u, (size_t)N, rocprim::plus<uint32_t>(), stream));
+        list_count_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(N, n_parts, state, mask, L.blocks, counts);
         tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, rocprim::make_transform_iterator(count, PeerCount{mask}),
-                                               key_off, 0u, (size_t)N, rocprim::plus<uint32_t>(), stream));
+        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, counts, list_at, 0u, (size_t)(2 * n_parts * L.blocks + 1),
+                                               rocprim::plus<uint32_t>(), stream));
         tb = L.tmp_bytes;
         RETEXO_HIP_TRY(rocprim::reduce(tmp, tb, rocprim::make_transform_iterator(count, InnerRowLength{d_part, d_row_ptr, part}),
                                        &hdr->nnz_local, (int64_t)0, (size_t)N, rocprim::plus<int64_t>(), stream));
-        totals_kernel<<<dim3(1), dim3(64), 0, stream>>>(N, d_part, part, rank_in, halo_flag, rank_halo, key_off, mask, hdr);
+        totals_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(N, d_part, part, n_parts, rank_in, state, rank_halo, L.blocks,
+                                                              list_at, hdr);
     }
     ShareHeader h;
     RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
@@ -393,8 +436,9 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     if ((h.n_send > 0 && !d_send_ids) || (h.n_halo > 0 && !d_recv_ids)) return RETEXO_E_NULL;
 
     if (N > 0) {
-        number_kernel<<<dim3((unsigned)((N + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
-            N, d_row_ptr, d_part, part, rank_in, halo_flag, rank_halo, h.n_inner, to_local, d_local_ids, d_global_deg);
+        number_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(
+            N, d_row_ptr, part, n_parts, rank_in, state, mask, rank_halo, h.n_inner, h.n_send, L.blocks, list_at, to_local,
+            d_local_ids, d_global_deg, d_send_ids, d_recv_ids);
     }
     {
         auto len = rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0),
@@ -406,22 +450,9 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     if (h.n_inner > 0) {
         const int rows_per_block = kThreads / 64;
         columns_kernel<<<dim3((unsigned)((h.n_inner + rows_per_block - 1) / rows_per_block)), dim3(kThreads), 0, stream>>>(
-            h.n_inner, d_local_ids, d_row_ptr, d_col_idx, to_local, d_local_row_ptr, d_local_col_idx);
-    }
-    const int64_t K = h.n_send + h.n_halo;
-    if (K > 0) {
-        keys_kernel<<<dim3((unsigned)((n_local + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
-            h.n_inner, h.n_halo, d_local_ids, d_part, mask, key_off, h.n_send, keys_a);
-        size_t tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::radix_sort_keys(tmp, tb, keys_a, keys_b, (size_t)K, 0u, 41u, stream));
-    }
-    {
-        const int64_t work = K > 2 * (int64_t)n_parts + 2 ? K : 2 * (int64_t)n_parts + 2;
-        lists_kernel<<<dim3((unsigned)((work + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
-            h.n_send, h.n_halo, keys_b, n_parts, d_send_ids, d_recv_ids, hdr);
+            h.n_inner, d_local_ids, d_row_ptr, d_col_idx, to_local, inner_entries, d_local_row_ptr, d_local_col_idx);
     }
     RETEXO_HIP_TRY(hipGetLastError());
-    RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
     RETEXO_HIP_TRY(hipStreamSynchronize(stream));
     for (int q = 0; q <= n_parts; ++q) {
         h_send_offsets[q] = h.send_off[q];
