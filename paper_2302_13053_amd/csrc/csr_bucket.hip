@@ -11,7 +11,7 @@
 //
 //   hist     every workgroup counts its share of the entries per row range ("bin", 2^s rows) in LDS
 //   colsum   adds the workgroups' counts
-//   plan     one workgroup: prefix sums over the bins, buckets = runs of bins of about kTarget
+//   plan     one workgroup: prefix sums over the bins, buckets = runs of bins of about `target`
 //            entries (never more than kRowSpan rows), groups = runs of 256 buckets
 //   part1    entries -> their group   (skipped when there is only one group)
 //   part2    entries -> their bucket, packed as (row - first row of the bucket) << cbits | col
@@ -44,7 +44,9 @@ constexpr int kGroupBuckets = 256;       // buckets per group
 constexpr int kMaxGroups = 1024;
 constexpr int kMaxBuckets = kGroupBuckets * kMaxGroups;
 constexpr int kBucketMax = 10240;        // entries a bucket can hold in LDS (10 per thread)
-constexpr int kTarget = kBucketMax / 2;  // entries a bucket is filled to
+constexpr int kTargetMax = 7168;         // entries a bucket is filled to in a large graph
+constexpr int kTargetMin = 1024;         // ... and in a small one
+constexpr int kTargetBuckets = 160;      // buckets a graph is spread over before they are filled further
 constexpr int kRowSpan = 1024;           // rows per bucket at most (one per thread of the sort)
 constexpr int kSortBins = kBucketMax / 4 + kRowSpan;   // bins of the LDS split: a row of c entries gets < max(1, c/4)
 constexpr int kStack = 400;              // key ranges waiting in an oversized bucket (6 levels x 63 + 1)
@@ -188,18 +190,17 @@ struct PlanArrays {
                               // block at which the next group starts, 16 = none) << 10
 };
 
-// A bin starts a bucket when the entries before it cross a multiple of kTarget, when it is the
+// A bin starts a bucket when the entries before it cross a multiple of `target`, when it is the
 // first bin of a window of `span_bins` bins (so that a bucket never holds more than kRowSpan rows
-// and its rows pack into 32 - cbits bits), or when it or its predecessor is a bin of at least
-// kTarget entries (large bins stand alone).
+// and its rows pack into 32 - cbits bits), or when it and its predecessor do not fit one bucket.
 __device__ __forceinline__ bool starts_bucket(int bin, uint32_t off, uint32_t prev_off, uint32_t cnt, uint32_t prev_cnt,
-                                              int span_bins)
+                                              int span_bins, uint32_t target)
 {
-    return bin == 0 || off / kTarget != prev_off / kTarget || bin % span_bins == 0 || cnt >= (uint32_t)kTarget ||
-           prev_cnt >= (uint32_t)kTarget;
+    return bin == 0 || off / target != prev_off / target || bin % span_bins == 0 ||
+           cnt + prev_cnt > (uint32_t)kBucketMax;
 }
 
-__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, const uint32_t* __restrict__ bin_count,
+__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, uint32_t target, const uint32_t* __restrict__ bin_count,
                                                         PlanArrays a, uint32_t bucket_capacity, BucketHeader* hdr)
 {
     __shared__ uint32_t cnts[kMaxBins];            // the bin counts, read three times
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
         for (int b = b0; b < b1; ++b) {
             const uint32_t cnt = cnts[b], pc = b > 0 ? cnts[b - 1] : 0u;
             a.bin_off[b] = o;
-            starts += starts_bucket(b, o, o - pc, cnt, pc, span_bins) ? 1u : 0u;
+            starts += starts_bucket(b, o, o - pc, cnt, pc, span_bins, target) ? 1u : 0u;
             o += cnt;
         }
     }
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
         uint32_t o = off;
         for (int b = b0; b < b1; ++b) {
             const uint32_t cnt = cnts[b], pc = b > 0 ? cnts[b - 1] : 0u;
-            if (starts_bucket(b, o, o - pc, cnt, pc, span_bins)) {
+            if (starts_bucket(b, o, o - pc, cnt, pc, span_bins, target)) {
                 a.bucket_bin0[id] = (uint32_t)b;
                 a.bucket_off[id] = o;
                 a.bucket_cursor[id] = o;
@@ -833,7 +834,7 @@ int column_bits(int64_t N)
 static_assert(sizeof(BucketHeader) <= 256, "the header has 256 bytes of the workspace");
 
 struct BucketLayout {
-    int cbits, s, nbins, span_bins, hist_blocks;
+    int cbits, s, nbins, span_bins, target, hist_blocks;
     int64_t M, n_items, items_per_block, bucket_bound;
     bool two_level;
     int64_t header, counts, bin_count, bin_off, bucket_bin0, bucket_off, bucket_cursor, bucket_total, bucket_out,
@@ -852,8 +853,16 @@ bool make_bucket_layout(int64_t n_pairs, int64_t N, int add_self_loops, BucketLa
     const int64_t span_rows = (1ll << (32 - L.cbits)) < kRowSpan ? (1ll << (32 - L.cbits)) : kRowSpan;
     L.span_bins = (int)(span_rows >> L.s);
     if (L.span_bins < 1 || L.nbins > kMaxBins) return false;
-    // worst case of starts_bucket: one start per kTarget entries, two per large bin, one per row window
-    L.bucket_bound = 3 * (L.M / kTarget) + L.nbins / L.span_bins + 4;
+    // The sort of a bucket costs much the same half full as full (twenty barriers, its scans), so a large graph's are
+    // filled to 0.7 of what fits: 57.5 million pairs over 233 thousand nodes 1410 us at half, 1315 at 0.7, 1360 at 0.8
+    // (there some no longer fit); whole constructions of 30 to 50 million pairs gain 8 to 10 %.  A small graph would then
+    // leave CUs idle and wait for a full bucket's sort, so it is spread over kTargetBuckets first (as many as keep the
+    // bound of a graph of 0.4 million entries within one group): 3 to 5 % from 7 thousand to 5 million entries.
+    const int64_t spread = L.M / kTargetBuckets;
+    L.target = spread > kTargetMax ? kTargetMax : spread < kTargetMin ? kTargetMin : (int)spread;
+    // worst case of starts_bucket: one start per `target` entries, one per pair of neighbours above kBucketMax (every
+    // entry is in two pairs), one per row window
+    L.bucket_bound = L.M / L.target + 2 * L.M / kBucketMax + L.nbins / L.span_bins + 4;
     if (L.bucket_bound > kMaxBuckets) return false;
     L.two_level = L.bucket_bound > kGroupBuckets;
     int64_t hb = (L.n_items + 16383) / 16384;
@@ -912,7 +921,7 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
         n_pairs, d_src, d_dst, N, L.n_items, L.items_per_block, L.s, L.nbins, u32(L.counts), hdr);
     colsum_kernel<<<dim3((unsigned)((L.nbins + 255) / 256), kColsumSlices), dim3(256), 0, stream>>>(
         L.hist_blocks, L.nbins, u32(L.counts), u32(L.bin_count));
-    plan_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(L.nbins, L.span_bins, u32(L.bin_count), pa,
+    plan_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(L.nbins, L.span_bins, (uint32_t)L.target, u32(L.bin_count), pa,
                                                         (uint32_t)L.bucket_bound, hdr);
     const unsigned item_tiles = (unsigned)((L.n_items + kItemsPerTile - 1) / kItemsPerTile);
     if (L.M > 0) {
