@@ -337,7 +337,9 @@ def bench_workload(index, args):
         # what the matrix cores are issued: whole 32-column accumulator tiles (41 columns run as 64), k in pairs
         cols = next((t for t in (32, 64, 128, 192, 256) if st.d_out <= t), 256 * -(-st.d_out // 256))
         fl_issued = 2.0 * n * (st.d_in + st.d_in % 2) * cols
-        balance = MFMA_F32_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBS          # flop per byte where the two bounds meet
+        # the products run on the bf16 matrix cores (three parts per float32), so these fractions of the fp32
+        # instruction's peak, kept for comparison, may pass 1
+        balance = MFMA_F32_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBS          # flop per byte where the two bounds would meet
         transforms.append({"stage": "%s%d" % (st.kind, i), "shape": "%d x %d -> %d" % (n, st.d_in, st.d_out),
                            "ms_alone": tms, "TFLOP/s": fl / tms / 1e9, "frac_fp32_mfma": fl / tms / 1e9 / MFMA_F32_PEAK_TFLOPS,
                            "issued_TFLOP/s": fl_issued / tms / 1e9,

@@ -67,8 +67,8 @@ AggOptions& agg_options();
 // 0.1 to 0.2 us * d whatever else runs, while the whole call needs nnz * F * 4 bytes at about 6 TB/s: the longest row
 // left to one wave is held to about a quarter of that, but 64 entries at the least (a workgroup's own start and
 // combination cost about as much), twice the mean row (where most rows are as long, one wave each fills the chip:
-// 4,393 rows of 220 entries with a workgroup each took 334 us for what takes 205) and 2048 at the most.  On a citation graph of 108,393 entries and 256 columns the
-// longest row's 320 entries alone took 57 us of an aggregation that needs 20.
+// 4,393 rows of 220 entries with a workgroup each took 334 us for what takes 205) and 2048 at the most.  On a citation
+// graph of 108,393 entries and 256 columns the longest row's 320 entries alone took 57 us of an aggregation that needs 20.
 static inline int64_t long_rows(const retexo_plan* p, int64_t F)
 {
     int64_t at_least = agg_options().heavy_degree;

@@ -43,6 +43,7 @@ constexpr int kTileEntries = 8192;       // entries per part2 tile
 constexpr int kGroupBuckets = 256;       // buckets per group
 constexpr int kMaxGroups = 1024;
 constexpr int kMaxBuckets = kGroupBuckets * kMaxGroups;
+constexpr int64_t kMaxEntries = 447000000;   // more were never built this way: they take the sorted keys
 constexpr int kBucketMax = 10240;        // entries a bucket can hold in LDS (10 per thread)
 constexpr int kTargetMax = 7168;         // entries a bucket is filled to in a large graph
 constexpr int kTargetMin = 1024;         // ... and in a small one
@@ -847,6 +848,7 @@ bool make_bucket_layout(int64_t n_pairs, int64_t N, int add_self_loops, BucketLa
     L.cbits = column_bits(N);
     if (L.cbits > 23) return false;                          // rows of a bucket must pack into 32 - cbits bits
     L.M = 2 * n_pairs + (add_self_loops ? N : 0);
+    if (L.M > kMaxEntries) return false;
     L.n_items = n_pairs + (add_self_loops ? N : 0);
     L.s = L.cbits > 15 ? L.cbits - 15 : 0;
     L.nbins = (int)((N + (1ll << L.s) - 1) >> L.s);          // <= kMaxBins
