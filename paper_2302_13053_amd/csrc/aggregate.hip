@@ -1713,7 +1713,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     a.save_neg = nullptr;
     a.ld_pos = 0;
 
-    int64_t n_heavy = long_rows(p, c.F);
+    int64_t n_heavy = long_rows(p, c.F, gat);
 
     // narrow slabs (32/64/128 columns) use the grouped gather; they need float4 gathers
     // (the maximum is only implemented on whole rows)

@@ -984,7 +984,7 @@ int launch_aggregate_backward(const AggBackwardCall& c, hipStream_t stream)
     }
 
     const AggOptions& opt = agg_options();
-    const int64_t n_heavy = long_rows(p, F);
+    const int64_t n_heavy = long_rows(p, F, true);
 
     // 16-byte gathers need every table aligned, rows padded to whole vectors and F a multiple of 4
     // (the inner products must not see padding columns)

@@ -1006,7 +1006,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     a.first = 1;
     a.last = 1;
 
-    const int64_t n_heavy = long_rows(p, F);
+    const int64_t n_heavy = long_rows(p, F, true);
 
     const int max_nc = 2;
     int nc = (int)((F + 64 * E - 1) / (64 * E));

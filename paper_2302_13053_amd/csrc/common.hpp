@@ -69,12 +69,16 @@ AggOptions& agg_options();
 // combination cost about as much), twice the mean row (where most rows are as long, one wave each fills the chip:
 // 4,393 rows of 220 entries with a workgroup each took 334 us for what takes 205) and 2048 at the most.  On a citation
 // graph of 108,393 entries and 256 columns the longest row's 320 entries alone took 57 us of an aggregation that needs 20.
-static inline int64_t long_rows(const retexo_plan* p, int64_t F)
+// Kernels that need a launch of their own for the long rows, one after the other (own_launch), pay for it with a launch
+// and with the time in which the long rows run alone: the line lies four times as high for the smallest, twice otherwise
+// (edge softmax and its backward with the lower line: 3,130 nodes of 5 entries 126 -> 138 us, 7,687 of 194 303 -> 326).
+static inline int64_t long_rows(const retexo_plan* p, int64_t F, bool own_launch)
 {
     int64_t at_least = agg_options().heavy_degree;
     if (at_least == kHeavyDegree) {
-        at_least = (p->nnz * F) >> 20;
-        const int64_t least = p->N > 0 && 2 * p->nnz / p->N > 64 ? 2 * p->nnz / p->N : 64;
+        const int64_t mean = p->N > 0 ? p->nnz / p->N : 0, floor = own_launch ? 256 : 64;
+        at_least = (p->nnz * F) >> (own_launch ? 19 : 20);
+        const int64_t above_mean = (own_launch ? 4 : 2) * mean, least = above_mean > floor ? above_mean : floor;
         at_least = at_least < least ? least : at_least;
         at_least = at_least > kHeavyDegree ? kHeavyDegree : at_least;
     }
