@@ -36,9 +36,13 @@ __device__ __forceinline__ void each(F&& f) { each_index(std::make_integer_seque
 // this way it is twice.  (All six onto one sum: 512 rectified columns 3.2e-7 off the same in 64 bits in the 2-norm,
 // the float32 instruction 2.8e-7.  Small sums of sixteen k added to the large one each time: as exact, 11 % slower.)
 //
-// Where the split is no longer exact the float32 instructions take over, one 32 x 32 tile at a time (see
-// `redo_tile`): infinities and NaN (their remainders are NaN), values that round to infinity in bf16, sums that
-// overflow, and operands so small that mid and lo fall below the smallest bf16 numbers.
+// Both operands are multiplied by 2^24 before they are split and the sums by 2^-48 at the end, which changes no bit of
+// an ordinary result.  The last bit of the smallest float32 (2^-149) is then 2^-125, a normal bf16 number, so that no
+// operand loses its mid and lo parts, however small it is (unscaled, one below 2^-110 did: 32 products of operands of
+// about 2^-124 and 2^40 were 5.6e-4 off), and whatever the matrix core does with values below its normal range, it does
+// 2^-174 below the result.  At the other end operands from 2^104 on and sums from 2^80 on overflow.
+// Where they do, and for infinities and NaN (their remainders are NaN), the float32 instructions take over, one 32 x 32
+// tile at a time (see `redo_tile`).
 // ---------------------------------------------------------------------------
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -54,10 +58,15 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 __device__ __forceinline__ float bf16_low(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float bf16_high(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 
-// Two floats -> pair q of their hi, mid and lo parts.
+constexpr float kSplitScale = 0x1p24f;          // of either operand
+constexpr float kSplitUnscale = 0x1p-48f;       // of a sum of products
+
+// Two floats, times `scale` (kSplitScale or its negative) -> pair q of their hi, mid and lo parts.
 template <class V>
-__device__ __forceinline__ void split_pair(float x0, float x1, int q, V (&part)[3])
+__device__ __forceinline__ void split_pair(float x0, float x1, float scale, int q, V (&part)[3])
 {
+    x0 *= scale;
+    x1 *= scale;
     const uint32_t hi = bf16_pair(x0, x1);
     const float r0 = x0 - bf16_low(hi), r1 = x1 - bf16_high(hi);
     const uint32_t mid = bf16_pair(r0, r1);
@@ -66,20 +75,17 @@ __device__ __forceinline__ void split_pair(float x0, float x1, int q, V (&part)[
     part[2][q] = bf16_pair(r0 - bf16_low(mid), r1 - bf16_high(mid));
 }
 
-// Whether any of a wave's 32 x 32 sums formed from split operands cannot be trusted: not finite, or so small (but not
-// zero) that the operands may have lost their low parts.  bf16 goes down to 2^-133, so an operand keeps its 24
-// bits from about 2^-110 on; the line is drawn at sums below 2^-104.
+// Whether any of a wave's 32 x 32 sums formed from split operands is not finite: then it cannot be trusted.
 __device__ __forceinline__ bool redo_tile(const f32x16& acc)
 {
-    uint32_t top = 0, low = 0xffffffffu;          // largest magnitude; smallest one minus one (zero wraps round)
+    uint32_t top = 0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float x = acc[r];
         const uint32_t m = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
         top = m > top ? m : top;
-        low = m - 1 < low ? m - 1 : low;
     }
-    return __any(top >= 0x7f800000u || low < 0x0b800000u - 1);
+    return __any(top >= 0x7f800000u);
 }
 
 // LDS image of one K tile of a workgroup: 16-byte units of eight k of one row (of A) or column (of B),
@@ -163,15 +169,14 @@ template <int BW, int WAVES> struct KMajorStage {
             for (int q = 0; q < KW; ++q) r[i][q] = k + q < k_end ? at(row + q * pitch, c) : 0.0f;
         }
     }
-    // plane(part, k half, column) -> 16-byte unit of `base`; sign: 0, or the sign bit to stage the operand negated
+    // plane(part, k half, column) -> 16-byte unit of `base`; scale: kSplitScale, or its negative to stage the operand negated
     template <int M, class Plane>
-    __device__ __forceinline__ void micro(u32x4* base, Plane&& plane, uint32_t sign, bool more, int kt)
+    __device__ __forceinline__ void micro(u32x4* base, Plane&& plane, float scale, bool more, int kt)
     {
         constexpr int i = M / steps, st = M % steps;
         if (!mine(i)) return;
         if constexpr (st < KW / 2) {
-            const uint32_t x0 = __builtin_bit_cast(uint32_t, r[i][2 * st]), x1 = __builtin_bit_cast(uint32_t, r[i][2 * st + 1]);
-            split_pair(__builtin_bit_cast(float, x0 ^ sign), __builtin_bit_cast(float, x1 ^ sign), st, part);
+            split_pair(r[i][2 * st], r[i][2 * st + 1], scale, st, part);
         } else if constexpr (st == KW / 2) {
 #pragma unroll
             for (int s = 0; s < 3; ++s) {
@@ -196,7 +201,7 @@ template <int BW, int WAVES> struct KMajorStage {
 // The one barrier of a K tile stands before its last column, whose operands are already in registers: behind that
 // barrier the next tile's first operands are read as soon as their registers are free.
 // Contract on entry: tile 0 is in LDS buffer 0 and a barrier has passed; tile 1's pieces (if nk > 1) are staged.
-// a0 / b0: first row / column of this wave's 32 x 32 TN block of accumulators.
+// a0 / b0: first row / column of this wave's 32 x 32 TN block of accumulators, which leave with kSplitScale^2 in them.
 // ---------------------------------------------------------------------------
 template <int TN, int BM, int BN, int MICROS, class Micro>
 __device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __restrict__ lds, int nk, int a0, int b0,

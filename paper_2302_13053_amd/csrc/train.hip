@@ -61,7 +61,8 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
 
     // every other chunk is summed with its sign turned and turned back at the end: the matrix core's bf16 additions lean
     // to one side a little, and over the thousands of chunks of a large graph that would add up
-    const uint32_t sign = (blockIdx.z & 1) << 31;
+    const bool turned = blockIdx.z & 1;
+    const float scale_p = turned ? -kSplitScale : kSplitScale;
     const int nk = k_end > k_begin ? (int)((k_end - k_begin + kTileK - 1) / kTileK) : 0;
     if (nk > 0) {
         PStage sp;
@@ -75,9 +76,9 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
             u32x4* base = lds + buf * T::units;
             const bool more = kt + 1 < nk;
             if constexpr (m < A_MICROS)
-                sp.template micro<m>(base, [](int s, int half, int c) { return T::a(s, half, c); }, sign, more, kt + 1);
+                sp.template micro<m>(base, [](int s, int half, int c) { return T::a(s, half, c); }, scale_p, more, kt + 1);
             else
-                sq.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, 0u, more, kt + 1);
+                sq.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, kSplitScale, more, kt + 1);
         };
         each<PStage::count>([&](auto i) { sp.template fetch<decltype(i)::value>(0); });
         each<QStage::count>([&](auto i) { sq.template fetch<decltype(i)::value>(0); });
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
     each<TN>([&](auto at) {
         constexpr int j = decltype(at)::value;
         const int col = n0 + b0 + j * 32 + lrow;
-        float turn = sign ? -1.0f : 1.0f;
+        float turn = turned ? -kSplitUnscale : kSplitUnscale;
         if (redo_tile(acc[j])) {
             // the tile once more with the float32 instruction, operands straight from memory
             const float* pp = P + min(m0 + a0 + lrow, M - 1);

@@ -247,9 +247,9 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
             for (int q = 0; q < HW; ++q) h_top = fmaxf(h_top, __builtin_fabsf(ra[set][q]));
         }
         if constexpr (m >= A_MICROS) {
-            sw.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, 0u, kt + 1 < nk, kt + 1);
+            sw.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, kSplitScale, kt + 1 < nk, kt + 1);
         } else if constexpr (m < HW / 2) {
-            split_pair(ra[set][2 * m], ra[set][2 * m + 1], m, part_h);
+            split_pair(ra[set][2 * m], ra[set][2 * m + 1], kSplitScale, m, part_h);
         } else if constexpr (m == HW / 2) {
 #pragma unroll
             for (int s = 0; s < 3; ++s)
@@ -268,7 +268,11 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
 
     each<TN>([&](auto at) {
         constexpr int j = decltype(at)::value;
-        if (!redo_tile(acc[j])) return;
+        if (!redo_tile(acc[j])) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][r] *= kSplitUnscale;
+            return;
+        }
         // the tile once more with the float32 instruction, operands straight from memory, k in ascending pairs
         const int64_t row = m0 + a0 + lrow;
         const int col = n0 + b0 + j * 32 + lrow;

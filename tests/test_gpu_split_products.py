@@ -76,8 +76,8 @@ def test_infinities_nan_and_overflow_come_out_as_float32_sums_give_them():
 
 @pytest.mark.parametrize("scale_h,scale_w", [(-118, 0), (-60, -60), (0, -122), (-126, 20), (100, 20), (-100, 110)])
 def test_scales_at_the_ends_of_the_range(scale_h, scale_w):
-    # rows far below the range in which bf16 keeps three parts, and far above: float32 holds 24 bits of them (results of
-    # 2^-120 and more here), so the bound stays the one of ordinary rows
+    # operands and results towards the ends of float32's range: float32 holds 24 bits of them (results of 2^-120 and more
+    # here), so the bound stays the one of ordinary rows
     n, d_in, d_out = 200, 50, 40
     H = np.ldexp(wl.random_matrix(n, d_in, 8), scale_h)
     W = np.ldexp(wl.random_matrix(d_in, d_out, 9), scale_w)
@@ -85,6 +85,26 @@ def test_scales_at_the_ends_of_the_range(scale_h, scale_w):
     want = H.astype(np.float64) @ W.astype(np.float64)
     s = np.ldexp(1.0, -(scale_h + scale_w))
     assert_close(Z * s, want * s, what="scales 2^%d, 2^%d" % (scale_h, scale_w))
+
+
+@pytest.mark.parametrize("scale_h,scale_w", [(-118, 40), (-120, 30), (-124, 40), (-126, 60), (-130, 100), (-143, 100),
+                                             (40, -124), (30, -120), (100, -140)])
+def test_small_operands_beside_large_ones_keep_all_their_bits(scale_h, scale_w):
+    # an operand far below the range in which bf16 keeps three parts, lifted by its partner to an ordinary sum (smaller
+    # than float32's normal range at (-130, 100), (-143, 100): the operand then has fewer bits, and these count)
+    n, d_in, d_out = 200, 50, 40
+    H = np.ldexp(wl.random_matrix(n, d_in, 8), scale_h)
+    W = np.ldexp(wl.random_matrix(d_in, d_out, 9), scale_w)
+    H64, s = H.astype(np.float64), np.ldexp(1.0, -(scale_h + scale_w))
+    Z = Hn.transform(Hn.dev(H), d_in, Hn.dev(W), None, False).cpu().numpy()[:, :d_out].astype(np.float64)
+    want = H64 @ W.astype(np.float64)
+    assert_close(Z * s, want * s, what="forward, scales 2^%d, 2^%d" % (scale_h, scale_w))
+    assert norm_error(Z * s, want * s) <= 2.0 ** -24 * 8 * np.sqrt(d_in / 16.0)
+    G = np.ldexp(wl.random_matrix(n, d_out, 5), scale_w)
+    gW = Hn.transform_backward(Hn.dev(H), d_in, Hn.dev(G), d_out)[0].cpu().numpy().astype(np.float64)
+    want = H64.T @ G.astype(np.float64)
+    assert_close(gW * s, want * s, what="weight gradient, scales 2^%d, 2^%d" % (scale_h, scale_w))
+    assert norm_error(gW * s, want * s) <= 2.0 ** -24 * 8 * np.sqrt(n / 16.0)
 
 
 def test_zero_rows_stay_zero_and_small_terms_do_not_disturb():
