@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
         constexpr int j = decltype(at)::value;
         const int col = n0 + b0 + j * 32 + lrow;
         float turn = turned ? -kSplitUnscale : kSplitUnscale;
-        if (redo_tile(acc[j])) {
+        if (k_end - k_begin == 1 || redo_tile(acc[j])) {          // (a single product is rounded once by the float32 instruction)
             // the tile once more with the float32 instruction, operands straight from memory
             const float* pp = P + min(m0 + a0 + lrow, M - 1);
             const float* qp = Q + min(col, Nq - 1);

@@ -268,7 +268,8 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
 
     each<TN>([&](auto at) {
         constexpr int j = decltype(at)::value;
-        if (!redo_tile(acc[j])) {
+        // (one input column: the float32 instruction rounds its one product once, the split's two sums twice)
+        if (D_in > 1 && !redo_tile(acc[j])) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[j][r] *= kSplitUnscale;
             return;

@@ -107,6 +107,17 @@ def test_small_operands_beside_large_ones_keep_all_their_bits(scale_h, scale_w):
     assert norm_error(gW * s, want * s) <= 2.0 ** -24 * 8 * np.sqrt(n / 16.0)
 
 
+@pytest.mark.parametrize("n,d_out", [(1, 1), (130, 33), (300, 257)])
+def test_single_products_are_rounded_once(n, d_out):
+    # one input column, and the gradient of one node: float32 products, each correctly rounded
+    H, W = wl.random_matrix(n, 1, 21), wl.random_matrix(1, d_out, 22)
+    Z = Hn.transform(Hn.dev(H), 1, Hn.dev(W), None, False).cpu().numpy()[:, :d_out]
+    assert np.array_equal(Z, H[:, :1] * W)
+    x, g = wl.random_matrix(1, 300, 23, ld=300), wl.random_matrix(1, d_out, 24)
+    gW = Hn.transform_backward(Hn.dev(x), 300, Hn.dev(g), d_out)[0].cpu().numpy()
+    assert np.array_equal(gW, x.T * g)
+
+
 def test_zero_rows_stay_zero_and_small_terms_do_not_disturb():
     n, d_in, d_out = 260, 48, 33
     H = wl.random_matrix(n, d_in, 10)
