@@ -87,7 +87,7 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (
 
 // Which side of zero a sum lies on, where the caller goes by that: a sum (plus its bias) within rounding of zero is
 // formed again as one chain of float32 multiply-adds, k ascending, which is what v_mfma_f32_32x32x2_f32 makes of it.
-// "Within rounding": 2^-25 sqrt(K) of the wave's largest sum, six to nine times what the two sums were seen apart (2-norm,
+// "Within rounding": 2^-25 sqrt(K) of the wave's largest finite sum, six to nine times what the two sums were seen apart (2-norm,
 // K = 29 to 2866), about one sum in 200,000; less for a row whose largest input (`row_top`, of the wave's 32 rows) is
 // below a quarter of the wave's, so that rows of very different size do not all count as near zero beside the largest.
 // An exact zero is one in any order (rows of zeros).
@@ -102,15 +102,17 @@ __device__ __forceinline__ void decide_near_zero(f32x16 (&acc)[TN], const float 
                                                  f32x4* __restrict__ chain)
 {
     const float eps = 0x1p-25f * sqrtf((float)D_in);
+    // what is not finite says nothing about the size of the others
+    auto finite = [](float x) { return __builtin_fabsf(x) < INFINITY ? __builtin_fabsf(x) : 0.0f; };
     float top = 0.0f;
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) top = fmaxf(top, __builtin_fabsf(acc[j][r]));
+        for (int r = 0; r < 16; ++r) top = fmaxf(top, finite(acc[j][r]));
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) top = fmaxf(top, __shfl_xor(top, m, 64));
     const float coarse = top * eps;              // no row's line is above the wave's
-    float largest = row_top[lane & 31];
+    float largest = finite(row_top[lane & 31]);
 #pragma unroll
     for (int m = 16; m >= 1; m >>= 1) largest = fmaxf(largest, __shfl_xor(largest, m, 64));
     const float per_input = 4.0f / largest;
