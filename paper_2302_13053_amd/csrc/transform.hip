@@ -85,82 +85,146 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (
     else run(std::false_type{});
 }
 
+// One 32 x 32 tile by the float32 instruction, operands straight from memory, k in ascending pairs: 2 U k at a time, the
+// next 2 U in flight.
+template <int U>
+__device__ __forceinline__ f32x16 float32_tile(int64_t row_base, int col_base, int64_t N, int D_in, int D_out,
+                                               const float* __restrict__ H, int64_t ldh, const float* __restrict__ W, int lane)
+{
+    const int lrow = lane & 31, lk = lane >> 5;
+    const int64_t row = row_base + lrow;
+    const int col = col_base + lrow;
+    const float* hp = H + (row < N ? row : N - 1) * ldh;
+    const float* wp = W + (col < D_out ? col : D_out - 1);
+    f32x16 x;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+    float a[2][U], b[2][U];
+    auto take = [&](int k0, auto slot_tag) {
+        constexpr int slot = decltype(slot_tag)::value;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 2 * u + lk;
+            const bool in = k < D_in;
+            const float av = hp[in ? k : 0], bw = wp[(int64_t)(in ? k : 0) * D_out];
+            a[slot][u] = in ? av : 0.0f;
+            b[slot][u] = in ? bw : 0.0f;
+        }
+    };
+    auto multiply = [&](int k0, auto slot_tag) {
+        constexpr int cur = decltype(slot_tag)::value;
+        if (k0 + 2 * U < D_in) take(k0 + 2 * U, std::integral_constant<int, cur ^ 1>{});
+#pragma unroll
+        for (int u = 0; u < U; ++u) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][u], b[cur][u], x, 0, 0, 0);
+    };
+    take(0, std::integral_constant<int, 0>{});
+    for (int k0 = 0; k0 < D_in; k0 += 4 * U) {
+        multiply(k0, std::integral_constant<int, 0>{});
+        if (k0 + 2 * U < D_in) multiply(k0 + 2 * U, std::integral_constant<int, 1>{});
+    }
+    return x;
+}
+
 // Which side of zero a sum lies on, where the caller goes by that: a sum (plus its bias) within rounding of zero is
 // formed again as one chain of float32 multiply-adds, k ascending, which is what v_mfma_f32_32x32x2_f32 makes of it.
-// "Within rounding": 2^-25 sqrt(K) of the wave's largest finite sum, six to nine times what the two sums were seen apart (2-norm,
-// K = 29 to 2866), about one sum in 200,000; less for a row whose largest input (`row_top`, of the wave's 32 rows) is
-// below a quarter of the wave's, so that rows of very different size do not all count as near zero beside the largest.
+// "Within rounding": 2^-25 sqrt(K) of the wave's largest finite sum, six to nine times what the two sums were seen apart
+// (2-norm, K = 29 to 2866), about one sum in 200,000; less for a row whose largest input (`row_top`, of the wave's 32
+// rows) or a column whose largest weight (`col_top`, of the wave's columns) is below a quarter of the wave's, so that rows
+// and units of very different size do not all count as near zero beside the largest.
 // An exact zero is one in any order (rows of zeros).
 // The wave works on one sum at a time: 256 k of the row and the column at once into LDS, then one multiply-add per k in
-// every lane: about 3 us at K = 1120.  (Whole 32 x 32 tiles on the float32 instruction took 35 us each, a third of a
-// small training step: 39,895 x 1120 -> 64.)
+// every lane: about 3 us at K = 1120.  A 32 x 32 tile with more than kSingles of them takes the float32 instruction as a
+// whole, 35 us at that K (which for every tile was a third of a small training step: 39,895 x 1120 -> 64).
+// A step with every second unit's weights at 1e-6 of the others' took 11 ms there without `col_top` and the whole tiles,
+// 0.25 ms with them; rows between 1e-6 and 1e6 of the mean 0.36 and 0.25.
 constexpr int kChain = 256;
+constexpr int kSingles = 10;
 template <int TN>
 __device__ __forceinline__ void decide_near_zero(f32x16 (&acc)[TN], const float (&bv)[TN], int D_in, int D_out,
                                                  const float* __restrict__ H, int64_t ldh, const float* __restrict__ W,
                                                  int64_t row_base, int64_t N, int col_base, int lane, const float* row_top,
-                                                 f32x4* __restrict__ chain)
+                                                 const float* col_top, f32x4* __restrict__ chain)
 {
-    const float eps = 0x1p-25f * sqrtf((float)D_in);
     // what is not finite says nothing about the size of the others
     auto finite = [](float x) { return __builtin_fabsf(x) < INFINITY ? __builtin_fabsf(x) : 0.0f; };
-    float top = 0.0f;
+    auto wave_largest = [](float x) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+        for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m, 64));
+        return x;
+    };
+    float top = 0.0f, weight = 0.0f;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) top = fmaxf(top, finite(acc[j][r]));
+        weight = fmaxf(weight, finite(col_top[j * 32 + (lane & 31)]));
+    }
+    top = wave_largest(top);
+    weight = wave_largest(weight);
+    const float input = wave_largest(finite(row_top[lane & 31]));
+    auto share = [](float x, float largest) { return x > 0.0f ? fminf(1.0f, 4.0f * (x / largest)) : 0.0f; };
+    const float coarse = top * (0x1p-25f * sqrtf((float)D_in));
+    const int64_t rows_left = N - row_base;
+    float line[16];                              // of this lane's sums, by row
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) top = fmaxf(top, __shfl_xor(top, m, 64));
-    const float coarse = top * eps;              // no row's line is above the wave's
-    float largest = finite(row_top[lane & 31]);
+    for (int r = 0; r < 16; ++r) {
+        const int in_tile = 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
+        line[r] = in_tile < rows_left ? coarse * share(row_top[in_tile], input) : 0.0f;
+    }
+    each<TN>([&](auto at) {
+        constexpr int j = decltype(at)::value;
+        const int col = col_base + j * 32 + (lane & 31);
+        const float unit = col < D_out ? share(col_top[j * 32 + (lane & 31)], weight) : 0.0f;
+        auto near = [&](int r) {
+            return __ballot(__builtin_fabsf(acc[j][r] + bv[j]) < line[r] * unit && acc[j][r] != 0.0f);
+        };
+        int count = 0;
 #pragma unroll
-    for (int m = 16; m >= 1; m >>= 1) largest = fmaxf(largest, __shfl_xor(largest, m, 64));
-    const float per_input = 4.0f / largest;
-    each<TN * 16>([&](auto at) {
-        constexpr int j = decltype(at)::value / 16, r = decltype(at)::value % 16;
-        const float x = acc[j][r];
-        uint64_t close = __ballot(__builtin_fabsf(x + bv[j]) < coarse && x != 0.0f);
-        while (close) {                          // (uniform)
-            const int src = __ffsll((unsigned long long)close) - 1;
-            close &= close - 1;
-            const int in_tile = 8 * (r / 4) + 4 * (src >> 5) + r % 4;
-            const float here = __shfl(x + bv[j], src, 64);
-            if (__builtin_fabsf(here) > coarse * row_top[in_tile] * per_input) continue;
-            const int64_t row = row_base + in_tile;
-            const int col = col_base + j * 32 + (src & 31);
-            if (row >= N || col >= D_out) continue;
-            const float* hp = H + row * ldh;
-            const float* wp = W + col;
-            float sum = 0.0f;
-            for (int k0 = 0; k0 < D_in; k0 += kChain) {
-                float h[kChain / 64], w[kChain / 64];
-#pragma unroll
-                for (int i = 0; i < kChain / 64; ++i) {
-                    const int k = k0 + i * 64 + lane;
-                    h[i] = k < D_in ? hp[k] : 0.0f;
-                    w[i] = k < D_in ? wp[(int64_t)k * D_out] : 0.0f;
-                }
-                float* c = reinterpret_cast<float*>(chain);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-#pragma unroll
-                for (int i = 0; i < kChain / 64; ++i) {
-                    c[i * 64 + lane] = h[i];
-                    c[kChain + i * 64 + lane] = w[i];
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 8
-                for (int q = 0; q < kChain / 4; ++q) {
-                    const f32x4 a = chain[q], b = chain[kChain / 4 + q];
-                    sum = fmaf(a.x, b.x, sum);
-                    sum = fmaf(a.y, b.y, sum);
-                    sum = fmaf(a.z, b.z, sum);
-                    sum = fmaf(a.w, b.w, sum);
-                }
-            }
-            if (lane == src) acc[j][r] = sum;
+        for (int r = 0; r < 16; ++r) count += __popcll(near(r));
+        if (count == 0) return;                  // (uniform, as is the next)
+        if (count > kSingles) {
+            acc[j] = float32_tile<TN == 1 ? 8 : 16>(row_base, col_base + j * 32, N, D_in, D_out, H, ldh, W, lane);
+            return;
         }
+        each<16>([&](auto element) {
+            constexpr int r = decltype(element)::value;
+            uint64_t close = near(r);
+            while (close) {
+                const int src = __ffsll((unsigned long long)close) - 1;
+                close &= close - 1;
+                const float* hp = H + (row_base + 8 * (r / 4) + 4 * (src >> 5) + r % 4) * ldh;
+                const float* wp = W + (col_base + j * 32 + (src & 31));
+                float sum = 0.0f;
+                for (int k0 = 0; k0 < D_in; k0 += kChain) {
+                    float h[kChain / 64], w[kChain / 64];
+#pragma unroll
+                    for (int i = 0; i < kChain / 64; ++i) {
+                        const int k = k0 + i * 64 + lane;
+                        h[i] = k < D_in ? hp[k] : 0.0f;
+                        w[i] = k < D_in ? wp[(int64_t)k * D_out] : 0.0f;
+                    }
+                    float* c = reinterpret_cast<float*>(chain);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+#pragma unroll
+                    for (int i = 0; i < kChain / 64; ++i) {
+                        c[i * 64 + lane] = h[i];
+                        c[kChain + i * 64 + lane] = w[i];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 8
+                    for (int q = 0; q < kChain / 4; ++q) {
+                        const f32x4 a = chain[q], b = chain[kChain / 4 + q];
+                        sum = fmaf(a.x, b.x, sum);
+                        sum = fmaf(a.y, b.y, sum);
+                        sum = fmaf(a.z, b.z, sum);
+                        sum = fmaf(a.w, b.w, sum);
+                    }
+                }
+                if (lane == src) acc[j][r] = sum;
+            }
+        });
     });
 }
 
@@ -186,8 +250,6 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
     using WStage = KMajorStage<BN, WAVES>;
     constexpr int HW = BM * kTileK / (64 * WAVES);       // floats of H a thread stages
     __shared__ u32x4 lds[2 * T::units];
-    __shared__ f32x4 chain[KEEP_SIGN ? WAVES : 1][KEEP_SIGN ? 2 * kChain / 4 : 1];       // decide_near_zero: its products' operands
-    __shared__ float row_top[KEEP_SIGN ? BM : 1];        // ... and the largest input of every row
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -195,7 +257,7 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
     const int a0 = wave % 4 * 32, b0 = wave / 4 * WN;    // the wave's rows and columns of the tile
     const int64_t m0 = (int64_t)blockIdx.x * BM;
     const int n0 = blockIdx.y * BN;
-    const int lrow = lane & 31, lk = lane >> 5;
+    const int lrow = lane & 31;
 
     f32x16 acc[TN];
 #pragma unroll
@@ -240,6 +302,7 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
     typedef uint32_t part_t __attribute__((ext_vector_type(HW / 2)));
     part_t part_h[3];
     float h_top = 0.0f;                                  // largest input of this thread's part of its row
+    float w_top[WStage::count] = {};                     // ... and weight of its columns
     auto micro = [&](auto step, auto buf, int kt) {
         constexpr int m = decltype(step)::value;
         constexpr int set = set_of<SETS, decltype(buf)>();
@@ -247,6 +310,13 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
         if constexpr (KEEP_SIGN && m == 0) {
 #pragma unroll
             for (int q = 0; q < HW; ++q) h_top = fmaxf(h_top, __builtin_fabsf(ra[set][q]));
+        }
+        if constexpr (KEEP_SIGN && m >= A_MICROS && (m - A_MICROS) % WStage::steps == 0) {
+            constexpr int i = (m - A_MICROS) / WStage::steps;
+            if (sw.mine(i)) {
+#pragma unroll
+                for (int q = 0; q < WStage::KW; ++q) w_top[i] = fmaxf(w_top[i], __builtin_fabsf(sw.r[i][q]));
+            }
         }
         if constexpr (m >= A_MICROS) {
             sw.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, kSplitScale, kt + 1 < nk, kt + 1);
@@ -276,47 +346,26 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
             for (int r = 0; r < 16; ++r) acc[j][r] *= kSplitUnscale;
             return;
         }
-        // the tile once more with the float32 instruction, operands straight from memory, k in ascending pairs
-        const int64_t row = m0 + a0 + lrow;
-        const int col = n0 + b0 + j * 32 + lrow;
-        const float* hp = H + (row < N ? row : N - 1) * ldh;
-        const float* wp = W + (col < D_out ? col : D_out - 1);
-        f32x16 x;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = 0.0f;
-        constexpr int U = 16;                     // 32 k at a time, the next 32 in flight
-        float a[2][U], b[2][U];
-        auto take = [&](int k0, auto slot_tag) {
-            constexpr int slot = decltype(slot_tag)::value;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int k = k0 + 2 * u + lk;
-                const bool in = k < D_in;
-                const float av = hp[in ? k : 0], bw = wp[(int64_t)(in ? k : 0) * D_out];
-                a[slot][u] = in ? av : 0.0f;
-                b[slot][u] = in ? bw : 0.0f;
-            }
-        };
-        auto multiply = [&](int k0, auto slot_tag) {
-            constexpr int cur = decltype(slot_tag)::value;
-            if (k0 + 2 * U < D_in) take(k0 + 2 * U, std::integral_constant<int, cur ^ 1>{});
-#pragma unroll
-            for (int u = 0; u < U; ++u) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][u], b[cur][u], x, 0, 0, 0);
-        };
-        take(0, std::integral_constant<int, 0>{});
-        for (int k0 = 0; k0 < D_in; k0 += 4 * U) {
-            multiply(k0, std::integral_constant<int, 0>{});
-            if (k0 + 2 * U < D_in) multiply(k0 + 2 * U, std::integral_constant<int, 1>{});
-        }
-        acc[j] = x;
+        acc[j] = float32_tile<TN == 1 ? 8 : 16>(m0 + a0, n0 + b0 + j * 32, N, D_in, D_out, H, ldh, W, lane);
     });
 
     if constexpr (KEEP_SIGN) {
 #pragma unroll
         for (int m = 1; m < kTileK / HW; m <<= 1) h_top = fmaxf(h_top, __shfl_xor(h_top, m, 64));
+        // the tiles' memory: largest input of every row, largest weight of every column, operands of the waves' chains
+        float* row_top = reinterpret_cast<float*>(lds);
+        float* col_top = row_top + BM;
+        f32x4* chain = reinterpret_cast<f32x4*>(lds) + (BM + BN) / 4 + wave * (2 * kChain / 4);
+        static_assert(2 * T::units >= (BM + BN) / 4 + WAVES * (2 * kChain / 4), "they fit there");
+        __syncthreads();                                 // every wave is done with the last tile
         row_top[hr] = h_top;
+        if (tid < BN) col_top[tid] = 0.0f;
         __syncthreads();
-        decide_near_zero<TN>(acc, bv, D_in, D_out, H, ldh, W, m0 + a0, N, n0 + b0, lane, row_top + a0, chain[wave]);
+#pragma unroll
+        for (int i = 0; i < WStage::count; ++i)          // (numbers that are not negative order as their bits do)
+            if (sw.mine(i)) atomicMax(reinterpret_cast<uint32_t*>(col_top + sw.local(i)), __builtin_bit_cast(uint32_t, w_top[i]));
+        __syncthreads();
+        decide_near_zero<TN>(acc, bv, D_in, D_out, H, ldh, W, m0 + a0, N, n0 + b0, lane, row_top + a0, col_top + b0, chain);
     }
     write_out<TN, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm, m0 + BM <= N);
 }
