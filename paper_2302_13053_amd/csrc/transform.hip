@@ -131,7 +131,10 @@ __device__ __forceinline__ f32x16 float32_tile(int64_t row_base, int col_base, i
 // (2-norm, K = 29 to 2866), about one sum in 200,000; less for a row whose largest input (`row_top`, of the wave's 32
 // rows) or a column whose largest weight (`col_top`, of the wave's columns) is below a quarter of the wave's, so that rows
 // and units of very different size do not all count as near zero beside the largest.
-// An exact zero is one in any order (rows of zeros).
+// A sum of exactly zero stays zero: no product, or products that cancel in pairs once they are split (which a chain of
+// float32 multiply-adds may leave a rounding of; the exact sum is zero or below 2^-24 of its terms).  The two cannot be
+// told apart here, and forming the first again costs steps over sparse inputs and pruned weights dearly: 232,965 x 1204 ->
+// 256 with 2 % of the inputs and 10 % of the weights left 7.1 ms instead of 2.0.
 // The wave works on one sum at a time: 256 k of the row and the column at once into LDS, then one multiply-add per k in
 // every lane: about 3 us at K = 1120.  A 32 x 32 tile with more than kSingles of them takes the float32 instruction as a
 // whole, 35 us at that K (which for every tile was a third of a small training step: 39,895 x 1120 -> 64).

@@ -107,3 +107,31 @@ def test_near_zero_units_are_on_where_the_float32_sum_is_positive(weak):
         B.check(B.retexo_set_option("transform_few_blocks", 128), "set_option")
     assert_close(gW1.cpu().numpy(), X.astype(np.float64).T @ dA, what="gW1")
     assert_close(gb1.cpu().numpy()[None, :], dA.sum(0)[None, :], what="gb1")
+
+
+def test_units_whose_products_cancel_exactly_are_off():
+    # two equal inputs with opposite weights: zero, where a chain of float32 multiply-adds would leave the rounding of the
+    # first product, positive about half the time
+    n, hid, cls = 300, 64, 5
+    rng = np.random.Generator(np.random.Philox(key=18))
+    X = np.repeat(rng.standard_normal((n, 1), dtype=np.float32), 2, axis=1)
+    W1 = np.repeat(rng.standard_normal((1, hid), dtype=np.float32), 2, axis=0)
+    W1[1] = -W1[1]
+    W1[:, ::2] = np.abs(W1[:, ::2])                        # every second unit is an ordinary one (of two equal weights)
+    on = X.astype(np.float64) @ W1.astype(np.float64) > 0
+    assert 0 < on.mean() < 0.5
+    Wc = rng.standard_normal((hid, cls), dtype=np.float32)
+    y = rng.integers(0, cls, n).astype(np.int32)
+    L = np.where(on, X.astype(np.float64) @ W1.astype(np.float64), 0.0) @ Wc.astype(np.float64)
+    P = np.exp(L - L.max(1, keepdims=True))
+    P /= P.sum(1, keepdims=True)
+    P[np.arange(n), y] -= 1.0
+    dA = np.where(on, (P / n) @ Wc.astype(np.float64).T, 0.0)
+    d, zero = Hn.dev, lambda k: torch.zeros(k, device="cuda")
+    B.check(B.retexo_set_option("transform_few_blocks", 0), "set_option")
+    try:
+        _, gW1, gb1, _, _ = Hn.layer_grad(d(X), 2, d(y), d(W1), zero(hid), d(Wc), zero(cls))
+    finally:
+        B.check(B.retexo_set_option("transform_few_blocks", 128), "set_option")
+    assert_close(gW1.cpu().numpy(), X.astype(np.float64).T @ dA, what="gW1")
+    assert_close(gb1.cpu().numpy()[None, :], dA.sum(0)[None, :], what="gb1")
