@@ -88,6 +88,43 @@ __device__ __forceinline__ bool redo_tile(const f32x16& acc)
     return __any(top >= 0x7f800000u);
 }
 
+// One 32 x 32 tile by the float32 instruction, operands straight from memory: `a` is this lane's row (lane % 32), element k
+// at a[k * a_step], `b` its column.  k in ascending pairs, 2 U of them at a time with the next 2 U in flight (one pair at a
+// time, a weight gradient with an infinite input waited for memory a thousand times over: 232,965 x 1204 -> 256 2.8 ms, so
+// 2.0, 0.9 without the infinity; 1,000,000 x 2000 -> 32 5.6, 3.5 and 1.8; twice as many at a time is no faster).
+template <int U>
+__device__ __forceinline__ f32x16 float32_tile(const float* a, int64_t a_step, const float* b, int64_t b_step, int K, int lane)
+{
+    const int lk = lane >> 5;
+    f32x16 x;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+    float va[2][U], vb[2][U];
+    auto take = [&](int k0, auto slot_tag) {
+        constexpr int slot = decltype(slot_tag)::value;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 2 * u + lk;
+            const bool in = k < K;
+            const float av = a[(in ? k : 0) * a_step], bv = b[(in ? k : 0) * b_step];
+            va[slot][u] = in ? av : 0.0f;
+            vb[slot][u] = in ? bv : 0.0f;
+        }
+    };
+    auto multiply = [&](int k0, auto slot_tag) {
+        constexpr int cur = decltype(slot_tag)::value;
+        if (k0 + 2 * U < K) take(k0 + 2 * U, std::integral_constant<int, cur ^ 1>{});
+#pragma unroll
+        for (int u = 0; u < U; ++u) x = __builtin_amdgcn_mfma_f32_32x32x2f32(va[cur][u], vb[cur][u], x, 0, 0, 0);
+    };
+    take(0, std::integral_constant<int, 0>{});
+    for (int k0 = 0; k0 < K; k0 += 4 * U) {
+        multiply(k0, std::integral_constant<int, 0>{});
+        if (k0 + 2 * U < K) multiply(k0 + 2 * U, std::integral_constant<int, 1>{});
+    }
+    return x;
+}
+
 // LDS image of one K tile of a workgroup: 16-byte units of eight k of one row (of A) or column (of B),
 // [part][k / 8][row], first A's BM rows, then B's BN.  The four units of padding per plane put the two k halves of a row,
 // which neighbouring lanes write, into different banks; a matrix instruction's operand (lane l: row l % 32,

@@ -95,19 +95,8 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
         const int col = n0 + b0 + j * 32 + lrow;
         float turn = turned ? -kSplitUnscale : kSplitUnscale;
         if (k_end - k_begin == 1 || redo_tile(acc[j])) {          // (a single product is rounded once by the float32 instruction)
-            // the tile once more with the float32 instruction, operands straight from memory
-            const float* pp = P + min(m0 + a0 + lrow, M - 1);
-            const float* qp = Q + min(col, Nq - 1);
-            f32x16 x;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) x[r] = 0.0f;
-            for (int64_t k = k_begin + lk; k - lk < k_end; k += 2) {
-                const bool in = k < k_end;
-                const int64_t kc = in ? k : k_begin;
-                const float a = pp[kc * ldp], b = qp[kc * ldq];
-                x = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a : 0.0f, in ? b : 0.0f, x, 0, 0, 0);
-            }
-            acc[j] = x;
+            acc[j] = float32_tile<BN <= 64 ? 8 : 16>(P + k_begin * ldp + min(m0 + a0 + lrow, M - 1), ldp,
+                                                     Q + k_begin * ldq + min(col, Nq - 1), ldq, (int)(k_end - k_begin), lane);
             turn = 1.0f;
         }
         if (col >= Nq) return;

@@ -85,46 +85,6 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (
     else run(std::false_type{});
 }
 
-// One 32 x 32 tile by the float32 instruction, operands straight from memory, k in ascending pairs: 2 U k at a time, the
-// next 2 U in flight.
-template <int U>
-__device__ __forceinline__ f32x16 float32_tile(int64_t row_base, int col_base, int64_t N, int D_in, int D_out,
-                                               const float* __restrict__ H, int64_t ldh, const float* __restrict__ W, int lane)
-{
-    const int lrow = lane & 31, lk = lane >> 5;
-    const int64_t row = row_base + lrow;
-    const int col = col_base + lrow;
-    const float* hp = H + (row < N ? row : N - 1) * ldh;
-    const float* wp = W + (col < D_out ? col : D_out - 1);
-    f32x16 x;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] = 0.0f;
-    float a[2][U], b[2][U];
-    auto take = [&](int k0, auto slot_tag) {
-        constexpr int slot = decltype(slot_tag)::value;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = k0 + 2 * u + lk;
-            const bool in = k < D_in;
-            const float av = hp[in ? k : 0], bw = wp[(int64_t)(in ? k : 0) * D_out];
-            a[slot][u] = in ? av : 0.0f;
-            b[slot][u] = in ? bw : 0.0f;
-        }
-    };
-    auto multiply = [&](int k0, auto slot_tag) {
-        constexpr int cur = decltype(slot_tag)::value;
-        if (k0 + 2 * U < D_in) take(k0 + 2 * U, std::integral_constant<int, cur ^ 1>{});
-#pragma unroll
-        for (int u = 0; u < U; ++u) x = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][u], b[cur][u], x, 0, 0, 0);
-    };
-    take(0, std::integral_constant<int, 0>{});
-    for (int k0 = 0; k0 < D_in; k0 += 4 * U) {
-        multiply(k0, std::integral_constant<int, 0>{});
-        if (k0 + 2 * U < D_in) multiply(k0 + 2 * U, std::integral_constant<int, 1>{});
-    }
-    return x;
-}
-
 // Which side of zero a sum lies on, where the caller goes by that: a sum (plus its bias) within rounding of zero is
 // formed again as one chain of float32 multiply-adds, k ascending, which is what v_mfma_f32_32x32x2_f32 makes of it.
 // "Within rounding": 2^-25 sqrt(K) of the wave's largest finite sum, six to nine times what the two sums were seen apart
@@ -186,7 +146,8 @@ __device__ __forceinline__ void decide_near_zero(f32x16 (&acc)[TN], const float 
         for (int r = 0; r < 16; ++r) count += __popcll(near(r));
         if (count == 0) return;                  // (uniform, as is the next)
         if (count > kSingles) {
-            acc[j] = float32_tile<TN == 1 ? 8 : 16>(row_base, col_base + j * 32, N, D_in, D_out, H, ldh, W, lane);
+            acc[j] = float32_tile<TN == 1 ? 8 : 16>(H + min(row_base + (lane & 31), N - 1) * ldh, 1, W + min(col, D_out - 1), D_out,
+                                                   D_in, lane);
             return;
         }
         each<16>([&](auto element) {
@@ -349,7 +310,8 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
             for (int r = 0; r < 16; ++r) acc[j][r] *= kSplitUnscale;
             return;
         }
-        acc[j] = float32_tile<TN == 1 ? 8 : 16>(m0 + a0, n0 + b0 + j * 32, N, D_in, D_out, H, ldh, W, lane);
+        acc[j] = float32_tile<TN == 1 ? 8 : 16>(H + min(m0 + a0 + lrow, N - 1) * ldh, 1, W + min(n0 + b0 + j * 32 + lrow, D_out - 1),
+                                                D_out, D_in, lane);
     });
 
     if constexpr (KEEP_SIGN) {

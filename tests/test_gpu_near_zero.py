@@ -135,3 +135,14 @@ def test_units_whose_products_cancel_exactly_are_off():
         B.check(B.retexo_set_option("transform_few_blocks", 128), "set_option")
     assert_close(gW1.cpu().numpy(), X.astype(np.float64).T @ dA, what="gW1")
     assert_close(gb1.cpu().numpy()[None, :], dA.sum(0)[None, :], what="gb1")
+
+
+def test_an_infinite_input_leaves_the_weight_gradient_its_time():
+    # the tiles it reaches are formed by the float32 instruction, over two thousand nodes each
+    n, d_in, d_out = 232965, 1204, 256
+    H, G = torch.randn((n, 1216), device="cuda"), torch.randn((n, d_out), device="cuda")
+    ws = Hn.ws_tensor(B.retexo_transform_backward_workspace_bytes(n, d_in, d_out))
+    call = lambda: Hn.transform_backward(H, d_in, G, d_out, ws)
+    ordinary = best_time(call)
+    H[n // 2, 7] = np.inf
+    assert best_time(call) < 2.5 * ordinary
