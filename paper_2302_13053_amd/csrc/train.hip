@@ -94,9 +94,13 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
         constexpr int j = decltype(at)::value;
         const int col = n0 + b0 + j * 32 + lrow;
         float turn = turned ? -kSplitUnscale : kSplitUnscale;
-        if (k_end - k_begin == 1 || redo_tile(acc[j])) {          // (a single product is rounded once by the float32 instruction)
-            acc[j] = float32_tile<BN <= 64 ? 8 : 16>(P + k_begin * ldp + min(m0 + a0 + lrow, M - 1), ldp,
-                                                     Q + k_begin * ldq + min(col, Nq - 1), ldq, (int)(k_end - k_begin), lane);
+        const float* pp = P + k_begin * ldp + min(m0 + a0 + lrow, M - 1);
+        const float* qp = Q + k_begin * ldq + min(col, Nq - 1);
+        if (k_end - k_begin == 1) {          // (a single product is rounded once by the float32 instruction)
+            acc[j] = float32_tile<1>(pp, ldp, qp, ldq, 1, lane);
+            turn = 1.0f;
+        } else if (redo_tile(acc[j])) {
+            acc[j] = float32_tile<BN <= 64 ? 8 : 16>(pp, ldp, qp, ldq, (int)(k_end - k_begin), lane);
             turn = 1.0f;
         }
         if (col >= Nq) return;

@@ -304,14 +304,16 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
 
     each<TN>([&](auto at) {
         constexpr int j = decltype(at)::value;
-        // (one input column: the float32 instruction rounds its one product once, the split's two sums twice)
-        if (D_in > 1 && !redo_tile(acc[j])) {
+        const float* hp = H + min(m0 + a0 + lrow, N - 1) * ldh;
+        const float* wp = W + min(n0 + b0 + j * 32 + lrow, D_out - 1);
+        if (D_in == 1) {              // the float32 instruction rounds the one product once, the split's two sums twice
+            acc[j] = float32_tile<1>(hp, 1, wp, D_out, 1, lane);
+        } else if (redo_tile(acc[j])) {
+            acc[j] = float32_tile<TN == 1 ? 8 : 16>(hp, 1, wp, D_out, D_in, lane);
+        } else {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[j][r] *= kSplitUnscale;
-            return;
         }
-        acc[j] = float32_tile<TN == 1 ? 8 : 16>(H + min(m0 + a0 + lrow, N - 1) * ldh, 1, W + min(n0 + b0 + j * 32 + lrow, D_out - 1),
-                                                D_out, D_in, lane);
     });
 
     if constexpr (KEEP_SIGN) {
