@@ -140,10 +140,13 @@ template <int BM, int BN> struct SplitTile {
 // columns by KW k (one coalesced load per k), so every lane ends up with KW consecutive k of its column: eight where
 // the workgroup's waves share the BW columns x 16 k of a tile evenly that way, else four.  (32 columns are staged
 // twice, by two waves each with the same values.)  Columns past the end repeat the last one (their products are never
-// stored); rows from k_end on count as zero.
+// stored); rows from k_end on repeat the last row and count as zero, which is seen to when they are split: a load whose
+// value is looked at where it is issued waits for itself and for all loads before it.
+// SETS: tiles held in registers.  Waits count loads in the order of their issue, so where one operand is fetched two tiles
+// ahead, the other is too.
 // The work on a piece comes in micro steps for split_k_loop: KW / 2 steps that split a pair, one that writes the
-// parts to LDS, one that fetches the piece of the next tile.
-template <int BW, int WAVES> struct KMajorStage {
+// parts to LDS, one that fetches the piece of a later tile.
+template <int BW, int WAVES, int SETS = 1> struct KMajorStage {
     static constexpr int KW = BW >= 64 && BW / 32 % WAVES == 0 ? 8 : 4;
     static constexpr int chunks = BW == 32 ? WAVES : BW / 64 * (kTileK / KW);
     static constexpr int count = (chunks + WAVES - 1) / WAVES;
@@ -153,7 +156,8 @@ template <int BW, int WAVES> struct KMajorStage {
     int64_t ld, k0, k_end;
     int wave, lane;
     uint32_t col[count];              // byte offset of this lane's (clamped) column, per piece
-    float r[count][KW];
+    uint64_t lane_at;                 // BW == 32: byte offset of this lane's first element from the tile's first row
+    float r[SETS][count][KW];
     part_t part[3];
 
     __device__ __forceinline__ int chunk(int i) const { return wave + WAVES * i; }
@@ -172,16 +176,18 @@ template <int BW, int WAVES> struct KMajorStage {
             const int c = c0 + local(i);
             col[i] = 4u * (uint32_t)(c < c_end ? c : c_end - 1);
         }
+        if constexpr (BW == 32) lane_at = col[0] + 4 * (uint64_t)ld * (uint32_t)kk(0);
     }
     // The row's address is the same for all lanes and is formed in scalar registers (the empty asm keeps the compiler from
     // turning every row into a pointer of its own that each tile has to advance: thirty 64-bit additions per tile, and
     // spilled scalar registers).
     typedef const __attribute__((address_space(1))) char* global_t;
-    static __device__ __forceinline__ float at(uint64_t row, uint32_t offset)
+    static __device__ __forceinline__ float at(uint64_t row, uint64_t offset)
     {
         return *reinterpret_cast<const __attribute__((address_space(1))) float*>(reinterpret_cast<global_t>(row) + offset);
     }
-    template <int i>
+    // EDGE: the tile may reach over the end
+    template <int i, int set, bool EDGE>
     __device__ __forceinline__ void fetch(int kt)
     {
         if (!mine(i)) return;
@@ -190,30 +196,36 @@ template <int BW, int WAVES> struct KMajorStage {
         uint32_t low = __builtin_amdgcn_readfirstlane((uint32_t)first), high = __builtin_amdgcn_readfirstlane((uint32_t)(first >> 32));
         asm("" : "+s"(low), "+s"(high));
         const uint64_t row = (uint64_t)high << 32 | low;
-        const uint32_t c = col[i];
         const uint64_t pitch = 4 * (uint64_t)ld;
-        const bool whole = k0 + (int64_t)(kt + 1) * kTileK <= k_end;
-        if constexpr (BW == 32) {                              // the half-waves stage different k
-            const uint32_t piece = (uint32_t)kk(i);
+        if constexpr (!EDGE) {
 #pragma unroll
-            for (int q = 0; q < KW; ++q)
-                r[i][q] = whole || k + piece + q < k_end ? *reinterpret_cast<const float*>(row + (piece + q) * pitch + c) : 0.0f;
-        } else if (whole) {
-#pragma unroll
-            for (int q = 0; q < KW; ++q) r[i][q] = at(row + q * pitch, c);
+            for (int q = 0; q < KW; ++q) {
+                if constexpr (BW == 32) r[set][i][q] = at(row + q * pitch, lane_at);       // (the half-waves stage different k)
+                else r[set][i][q] = at(row + q * pitch, col[i]);
+            }
         } else {
+            const int left = (int)(k_end - 1 - k);             // the last row there is, from k on (may lie before it)
 #pragma unroll
-            for (int q = 0; q < KW; ++q) r[i][q] = k + q < k_end ? at(row + q * pitch, c) : 0.0f;
+            for (int q = 0; q < KW; ++q) {
+                if constexpr (BW == 32) r[set][i][q] = at(row, col[0] + (uint64_t)min(kk(i) + q, left) * pitch);
+                else r[set][i][q] = at(row + (uint64_t)(int64_t)min(q, left) * pitch, col[i]);
+            }
         }
     }
-    // plane(part, k half, column) -> 16-byte unit of `base`; scale: kSplitScale, or its negative to stage the operand negated
-    template <int M, class Plane>
-    __device__ __forceinline__ void micro(u32x4* base, Plane&& plane, float scale, bool more, int kt)
+    // plane(part, k half, column) -> 16-byte unit of `base`; scale: kSplitScale, or its negative to stage the operand
+    // negated; kt: the staged tile
+    template <int M, int set, bool EDGE, class Plane>
+    __device__ __forceinline__ void micro(u32x4* base, Plane&& plane, float scale, int kt, int nk)
     {
         constexpr int i = M / steps, st = M % steps;
         if (!mine(i)) return;
+        if constexpr (EDGE && st == 0) {
+            const int left = (int)(k_end - k0 - (int64_t)kt * kTileK) - kk(i);
+#pragma unroll
+            for (int q = 0; q < KW; ++q) r[set][i][q] = q < left ? r[set][i][q] : 0.0f;
+        }
         if constexpr (st < KW / 2) {
-            split_pair(r[i][2 * st], r[i][2 * st + 1], scale, st, part);
+            split_pair(r[set][i][2 * st], r[set][i][2 * st + 1], scale, st, part);
         } else if constexpr (st == KW / 2) {
 #pragma unroll
             for (int s = 0; s < 3; ++s) {
@@ -221,28 +233,40 @@ template <int BW, int WAVES> struct KMajorStage {
                 *reinterpret_cast<part_t*>(reinterpret_cast<char*>(unit) + (KW == 4 ? (kk(i) & 4) * 2 : 0)) = part[s];
             }
         } else {
-            if (more) fetch<i>(kt);
+            if (!EDGE || kt + SETS < nk) fetch<i, set, EDGE>(kt + SETS);
         }
     }
 };
+
+// the staging registers that belong to an LDS buffer
+template <int SETS, class Buf>
+__device__ __forceinline__ constexpr int set_of()
+{
+    if constexpr (SETS == 2) return Buf::value;
+    else return 0;
+}
 
 // ---------------------------------------------------------------------------
 // Software-pipelined K loop of one workgroup tile (six bf16 products per 32 x 32 x 16 block).
 //
 // A matrix core is kept busy only if what else a wave does fits between its matrix instructions (32 cycles each,
 // two waves per SIMD).  So the staging work of a K tile is cut into `MICROS` steps of about ten instructions, spread
-// over the matrix instructions before the tile's barrier; sched_barrier pins the order.  micro(m, buf, kt): step m of
-// "split the staged pieces (tile kt) into LDS buffer `buf` = kt % 2, and fetch those of a later tile in their place",
+// over the matrix instructions before the tile's barrier; sched_barrier pins the order.  micro(m, buf, kt, edge): step m
+// of "split the staged pieces (tile kt) into LDS buffer `buf` = kt % 2, and fetch those of tile kt + SETS in their place",
 // whose loads so have at least one K tile of matrix instructions to arrive.  One-column tiles pass `buf` as a constant.
+// Only the last tile may be partial: the steady loop ends where that one would be fetched, and holds no branch (which
+// would leave the number of loads in flight unknown, so that every use waits for more of them than it needs: 232,965 x
+// 1204 -> 256 847 us with the checks in the loop, 805 without).
 // Columns of the wave's tile are worked through one after the other with B's operands a column ahead.
 // The one barrier of a K tile stands before its last column, whose operands are already in registers: behind that
 // barrier the next tile's first operands are read as soon as their registers are free.
-// Contract on entry: tile 0 is in LDS buffer 0 and a barrier has passed; tile 1's pieces (if nk > 1) are staged.
+// Contract on entry: tile 0 is in LDS buffer 0 and a barrier has passed; the next tiles' pieces (if there are any) are staged.
 // a0 / b0: first row / column of this wave's 32 x 32 TN block of accumulators, which leave with kSplitScale^2 in them.
 // ---------------------------------------------------------------------------
-template <int TN, int BM, int BN, int MICROS, class Micro>
-__device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __restrict__ lds, int nk, int a0, int b0,
-                                             int lane, Micro&& micro)
+// nk: tiles; n_whole: those that are whole.
+template <int TN, int BM, int BN, int MICROS, int SETS, class Micro>
+__device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __restrict__ lds, int nk, int n_whole, int a0,
+                                             int b0, int lane, Micro&& micro)
 {
     using T = SplitTile<BM, BN>;
     constexpr int SLOTS = TN == 1 ? 1 : TN % 2 ? TN : 2;      // register sets of B operands: a column ahead, also across tiles
@@ -268,7 +292,9 @@ __device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __r
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) small[j][r] = 0.0f;
-    auto tile = [&](int kt, auto more_tag, auto buf, auto next) {
+    constexpr std::true_type go_on{}, edge{};
+    constexpr std::false_type finish{}, steady{};
+    auto tile = [&](int kt, auto more_tag, auto buf, auto next, auto edge_tag) {
         constexpr bool more = decltype(more_tag)::value;
         each<TN * 6>([&](auto at) {
             constexpr int g = decltype(at)::value, j = g / 6, p = g % 6;
@@ -290,7 +316,7 @@ __device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __r
             }
             if constexpr (!last && more) {
                 constexpr int m0 = g * MICROS / G, m1 = (g + 1) * MICROS / G;
-                each<m1 - m0>([&](auto m) { micro(std::integral_constant<int, m0 + decltype(m)::value>{}, next, kt + 1); });
+                each<m1 - m0>([&](auto m) { micro(std::integral_constant<int, m0 + decltype(m)::value>{}, next, kt + 1, edge_tag); });
             }
             RETEXO_SCHED_FENCE();
         });
@@ -308,19 +334,25 @@ __device__ __forceinline__ void split_k_loop(f32x16 (&acc)[TN], const u32x4* __r
         constexpr std::integral_constant<int, 0> even{};
         constexpr std::integral_constant<int, 1> odd{};
         int kt = 0;
+        for (; kt + 2 + SETS < n_whole; kt += 2) {
+            tile(kt, go_on, even, odd, steady);
+            tile(kt + 1, go_on, odd, even, steady);
+        }
         for (; kt + 2 < nk; kt += 2) {
-            tile(kt, std::true_type{}, even, odd);
-            tile(kt + 1, std::true_type{}, odd, even);
+            tile(kt, go_on, even, odd, edge);
+            tile(kt + 1, go_on, odd, even, edge);
         }
         if (kt + 1 < nk) {
-            tile(kt, std::true_type{}, even, odd);
-            tile(kt + 1, std::false_type{}, odd, even);
+            tile(kt, go_on, even, odd, edge);
+            tile(kt + 1, finish, odd, even, edge);
         } else if (kt < nk) {
-            tile(kt, std::false_type{}, even, odd);
+            tile(kt, finish, even, odd, edge);
         }
     } else {
-        for (int kt = 0; kt + 1 < nk; ++kt) tile(kt, std::true_type{}, kt & 1, (kt & 1) ^ 1);
-        if (nk > 0) tile(nk - 1, std::false_type{}, (nk - 1) & 1, nk & 1);
+        int kt = 0;
+        for (; kt + 1 + SETS < n_whole; ++kt) tile(kt, go_on, kt & 1, (kt & 1) ^ 1, steady);
+        for (; kt + 1 < nk; ++kt) tile(kt, go_on, kt & 1, (kt & 1) ^ 1, edge);
+        if (nk > 0) tile(nk - 1, finish, (nk - 1) & 1, nk & 1, edge);
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j)

@@ -194,25 +194,18 @@ __device__ __forceinline__ void decide_near_zero(f32x16 (&acc)[TN], const float 
 
 // The block kernel: 128 x BN outputs per workgroup, 32 rows and up to 128 columns per wave (whose two running sums then
 // take 128 registers): four waves, or eight for the tiles wider than 128; any alignment and leading dimension.
-// the staging registers that belong to an LDS buffer
-template <int SETS, class Buf>
-__device__ __forceinline__ constexpr int set_of()
-{
-    if constexpr (SETS == 2) return Buf::value;
-    else return 0;
-}
-
 template <int BN> constexpr int transform_waves = BN > 128 ? 8 : 4;
 template <int BN, bool MASKED, bool KEEP_SIGN>
-__global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 : 2) void transform_kernel(
+__global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void transform_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
     float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm)
 {
     constexpr int BM = 128, WAVES = transform_waves<BN>, WN = BN / (WAVES / 4), TN = WN / 32;
     using T = SplitTile<BM, BN>;
-    using WStage = KMajorStage<BN, WAVES>;
-    constexpr int HW = BM * kTileK / (64 * WAVES);       // floats of H a thread stages
+    constexpr int SETS = BN == 32 ? 2 : 1;               // tiles staged in registers
+    using WStage = KMajorStage<BN, WAVES, SETS>;
+    constexpr int HP = BM * kTileK / (64 * WAVES) / 4;   // 16-byte pieces of H that a thread stages
     __shared__ u32x4 lds[2 * T::units];
 
     const int tid = threadIdx.x;
@@ -229,26 +222,24 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
 
-    // H: a thread stages HW consecutive k of one row (rows past the end repeat the last one, never stored).  The 32-column
-    // tile, whose matrix instructions are over long before a row arrives from memory, stages two tiles ahead
-    // (2,449,029 x 256 -> 7 575 us instead of 611, 889,043 x 48 -> 8 53 instead of 55).
-    constexpr int SETS = BN == 32 ? 2 : 1;
-    const int hr = tid / (kTileK / HW), hk = tid % (kTileK / HW) * HW;
-    const float* ph = H + (m0 + hr < N ? m0 + hr : N - 1) * ldh;
-    float ra[SETS][HW];
-    auto fetch_h = [&](int kt, auto set_tag) {
+    // H: a thread stages HP pieces of four consecutive k, of rows 16 WAVES apart: four lanes fetch the 64 bytes of a row
+    // that a tile holds (rows past the end repeat the last one, never stored).  The 32-column tile, whose matrix
+    // instructions are over long before a row arrives from memory, stages two tiles of both operands ahead (2,449,029 x 256
+    // -> 7 536 us, 300,000 x 2000 -> 32 513; two of H behind one of W 578 and 578, all one tile ahead 611 and more).
+    const int hr = tid / 4, hk = tid % 4 * 4;
+    const float* ph[HP];
+#pragma unroll
+    for (int v = 0; v < HP; ++v) ph[v] = H + min(m0 + hr + 16 * WAVES * v, N - 1) * ldh + hk;
+    f32x4 ra[SETS][HP];
+    auto fetch_h = [&](int kt, int v, auto set_tag, auto edge) {
         constexpr int set = decltype(set_tag)::value;
-        const int k = kt * kTileK + hk;
-        if ((kt + 1) * kTileK <= D_in) {
-#pragma unroll
-            for (int v = 0; v < HW / 4; ++v) {
-                const f32x4 t = *reinterpret_cast<const f32x4_any*>(ph + k + 4 * v);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) ra[set][4 * v + q] = t[q];
-            }
+        const float* p = ph[v] + kt * kTileK;
+        if (!decltype(edge)::value || (kt + 1) * kTileK <= D_in) {
+            ra[set][v] = *reinterpret_cast<const f32x4_any*>(p);
         } else {
+            const int last = D_in - 1 - kt * kTileK - hk;        // the row's last element, from p on (may lie before it)
 #pragma unroll
-            for (int q = 0; q < HW; ++q) ra[set][q] = k + q < D_in ? ph[k + q] : 0.0f;
+            for (int q = 0; q < 4; ++q) ra[set][v][q] = p[min(q, last)];
         }
     };
     WStage sw;
@@ -262,45 +253,55 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
     }
 
     const int nk = (D_in + kTileK - 1) / kTileK;
-    constexpr int A_MICROS = HW / 2 + 2, MICROS = A_MICROS + WStage::count * WStage::steps;
-    typedef uint32_t part_t __attribute__((ext_vector_type(HW / 2)));
+    constexpr int A_MICROS = HP * 4, MICROS = A_MICROS + WStage::count * WStage::steps;
+    typedef uint32_t part_t __attribute__((ext_vector_type(2)));
     part_t part_h[3];
-    float h_top = 0.0f;                                  // largest input of this thread's part of its row
+    float h_top[HP] = {};                                // largest input of this thread's parts of its rows
     float w_top[WStage::count] = {};                     // ... and weight of its columns
-    auto micro = [&](auto step, auto buf, int kt) {
+    auto micro = [&](auto step, auto buf, int kt, auto edge) {
         constexpr int m = decltype(step)::value;
+        constexpr bool EDGE = decltype(edge)::value;
         constexpr int set = set_of<SETS, decltype(buf)>();
         u32x4* base = lds + buf * T::units;
-        if constexpr (KEEP_SIGN && m == 0) {
+        if constexpr (EDGE && m < A_MICROS && m % 4 == 0) {          // what lies past the row's end counts as zero (see KMajorStage)
 #pragma unroll
-            for (int q = 0; q < HW; ++q) h_top = fmaxf(h_top, __builtin_fabsf(ra[set][q]));
+            for (int q = 0; q < 4; ++q) ra[set][m / 4][q] = kt * kTileK + hk + q < D_in ? ra[set][m / 4][q] : 0.0f;
+        }
+        if constexpr (KEEP_SIGN && m < A_MICROS && m % 4 == 0) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) h_top[m / 4] = fmaxf(h_top[m / 4], __builtin_fabsf(ra[set][m / 4][q]));
         }
         if constexpr (KEEP_SIGN && m >= A_MICROS && (m - A_MICROS) % WStage::steps == 0) {
             constexpr int i = (m - A_MICROS) / WStage::steps;
             if (sw.mine(i)) {
 #pragma unroll
-                for (int q = 0; q < WStage::KW; ++q) w_top[i] = fmaxf(w_top[i], __builtin_fabsf(sw.r[i][q]));
+                for (int q = 0; q < WStage::KW; ++q) w_top[i] = fmaxf(w_top[i], __builtin_fabsf(sw.r[set][i][q]));
             }
         }
         if constexpr (m >= A_MICROS) {
-            sw.template micro<m - A_MICROS>(base, [](int s, int half, int c) { return T::b(s, half, c); }, kSplitScale, kt + 1 < nk, kt + 1);
-        } else if constexpr (m < HW / 2) {
-            split_pair(ra[set][2 * m], ra[set][2 * m + 1], kSplitScale, m, part_h);
-        } else if constexpr (m == HW / 2) {
+            sw.template micro<m - A_MICROS, set, EDGE>(base, [](int s, int half, int c) { return T::b(s, half, c); }, kSplitScale, kt, nk);
+        } else if constexpr (m % 4 < 2) {
+            split_pair(ra[set][m / 4][m % 4 * 2], ra[set][m / 4][m % 4 * 2 + 1], kSplitScale, m % 4, part_h);
+        } else if constexpr (m % 4 == 2) {
 #pragma unroll
             for (int s = 0; s < 3; ++s)
-                *reinterpret_cast<part_t*>(reinterpret_cast<char*>(base + T::a(s, hk >> 3, hr)) + (hk & 7) * 2) = part_h[s];
+                *reinterpret_cast<part_t*>(reinterpret_cast<char*>(base + T::a(s, hk >> 3, hr + 16 * WAVES * (m / 4))) + (hk & 4) * 2) = part_h[s];
         } else {
-            if (kt + SETS < nk) fetch_h(kt + SETS, std::integral_constant<int, set>{});
+            if (!EDGE || kt + SETS < nk) fetch_h(kt + SETS, m / 4, std::integral_constant<int, set>{}, edge);
         }
     };
     constexpr std::integral_constant<int, 0> first{};
-    fetch_h(0, first);
-    if (SETS == 2 && nk > 1) fetch_h(1, std::integral_constant<int, SETS - 1>{});
-    each<WStage::count>([&](auto i) { sw.template fetch<decltype(i)::value>(0); });
-    each<MICROS>([&](auto m) { micro(m, first, 0); });
+    constexpr std::true_type edge{};
+    auto fetch_all = [&](int kt, auto set_tag) {
+#pragma unroll
+        for (int v = 0; v < HP; ++v) fetch_h(kt, v, set_tag, edge);
+        each<WStage::count>([&](auto i) { sw.template fetch<decltype(i)::value, decltype(set_tag)::value, true>(kt); });
+    };
+    fetch_all(0, first);
+    if (SETS == 2 && nk > 1) fetch_all(1, std::integral_constant<int, SETS - 1>{});
+    each<MICROS>([&](auto m) { micro(m, first, 0, edge); });
     __syncthreads();
-    split_k_loop<TN, BM, BN, MICROS>(acc, lds, nk, a0, b0, lane, micro);
+    split_k_loop<TN, BM, BN, MICROS, SETS>(acc, lds, nk, D_in / kTileK, a0, b0, lane, micro);
 
     each<TN>([&](auto at) {
         constexpr int j = decltype(at)::value;
@@ -317,15 +318,17 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 32 ? 4 : BN <= 64 ?
     });
 
     if constexpr (KEEP_SIGN) {
-#pragma unroll
-        for (int m = 1; m < kTileK / HW; m <<= 1) h_top = fmaxf(h_top, __shfl_xor(h_top, m, 64));
         // the tiles' memory: largest input of every row, largest weight of every column, operands of the waves' chains
         float* row_top = reinterpret_cast<float*>(lds);
         float* col_top = row_top + BM;
         f32x4* chain = reinterpret_cast<f32x4*>(lds) + (BM + BN) / 4 + wave * (2 * kChain / 4);
         static_assert(2 * T::units >= (BM + BN) / 4 + WAVES * (2 * kChain / 4), "they fit there");
         __syncthreads();                                 // every wave is done with the last tile
-        row_top[hr] = h_top;
+#pragma unroll
+        for (int v = 0; v < HP; ++v) {
+            h_top[v] = fmaxf(h_top[v], __shfl_xor(h_top[v], 1, 64));
+            row_top[hr + 16 * WAVES * v] = fmaxf(h_top[v], __shfl_xor(h_top[v], 2, 64));
+        }
         if (tid < BN) col_top[tid] = 0.0f;
         __syncthreads();
 #pragma unroll

@@ -41,6 +41,22 @@ def test_forward_and_weight_gradient_against_64_bits(n, d_in, d_out, pitch):
     assert norm_error(gW.cpu().numpy().astype(np.float64), want) <= 2.0 ** -24 * 8 * max(1.0, np.sqrt(n / 16.0))
 
 
+@pytest.mark.parametrize("k", [2, 14, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 79, 80, 81, 95, 96, 97, 112, 127])
+@pytest.mark.parametrize("width", [5, 40, 100, 190, 256])
+def test_every_number_of_tiles_along_k(k, width):
+    # whole and partial last tiles behind none to eight others: the steady loop, its end and the tiles fetched ahead; the
+    # same number of nodes behind a weight gradient
+    H, W = wl.random_matrix(260, k, k + width, ld=k + 1), wl.random_matrix(k, width, width)
+    H[:, k:] = np.nan
+    Z = Hn.transform(Hn.dev(H), k, Hn.dev(W), None, False).cpu().numpy()[:, :width].astype(np.float64)
+    want = H[:, :k].astype(np.float64) @ W.astype(np.float64)
+    assert norm_error(Z, want) <= 2.0 ** -24 * 8 * max(1.0, np.sqrt(k / 16.0))
+    P, G = wl.random_matrix(k, 150, 3, ld=151), wl.random_matrix(k, width, 5)
+    gW = Hn.transform_backward(Hn.dev(P), 150, Hn.dev(G), width)[0].cpu().numpy().astype(np.float64)
+    want = P[:, :150].astype(np.float64).T @ G.astype(np.float64)
+    assert norm_error(gW, want) <= 2.0 ** -24 * 8 * max(1.0, np.sqrt(k / 16.0))
+
+
 def test_infinities_nan_and_overflow_come_out_as_float32_sums_give_them():
     n, d_in, d_out = 300, 40, 70
     H = wl.random_matrix(n, d_in, 3)
