@@ -193,18 +193,36 @@ struct PlanArrays {
 
 // A bin starts a bucket when the entries before it enter another window of about `target`, when it is the
 // first bin of a window of `span_bins` bins (so that a bucket never holds more than kRowSpan rows
-// and its rows pack into 32 - cbits bits), or when it and its predecessor do not fit one bucket.
+// and its rows pack into 32 - cbits bits), or when it does not fit behind the bins before it in its
+// window: it then reaches over the window's end, the next bin lies in another one, and the bucket
+// holds it alone.  So only a bin that does not fit by itself makes a bucket that does not (those are
+// worked through in key ranges, which a graph of few buckets waits for: 169,343 nodes of skewed
+// degrees, 1.2 million pairs, 212 us where a bin was only looked at with its neighbour, 172 so).
 // per_entry = floor(2^32 / target): the windows are up to 7e-6 longer than `target`, and a bin's is one multiplication (the
 // divisions took 4 us of a construction of 150: one workgroup goes through the bins).
+constexpr int kLookBack = 8;                     // bins; where the window holds more before it, its start counts
 __device__ __forceinline__ uint32_t window_of(uint32_t off, uint32_t per_entry) { return __umulhi(off, per_entry); }
-__device__ __forceinline__ bool starts_bucket(int bin, uint32_t off, uint32_t prev_off, uint32_t cnt, uint32_t prev_cnt,
-                                              int span_bins, uint32_t per_entry)
+__device__ __forceinline__ bool starts_bucket(int bin, uint32_t off, const uint32_t* cnts, int span_bins, uint32_t target,
+                                              uint32_t per_entry)
 {
-    return bin == 0 || window_of(off, per_entry) != window_of(prev_off, per_entry) || bin % span_bins == 0 ||
-           cnt + prev_cnt > (uint32_t)kBucketMax;
+    if (bin == 0 || bin % span_bins == 0) return true;
+    const uint32_t w = window_of(off, per_entry), cnt = cnts[bin];
+    if (w != window_of(off - cnts[bin - 1], per_entry)) return true;
+    uint32_t first = w * target;                 // no later than the first bin of the window
+    if (off - first + cnt <= (uint32_t)kBucketMax) return false;
+    uint32_t o = off;
+    for (int back = 1; back <= kLookBack; ++back) {
+        const uint32_t before = bin >= back ? o - cnts[bin - back] : 0u;
+        if (bin < back || window_of(before, per_entry) != w) {
+            first = o;
+            break;
+        }
+        o = before;
+    }
+    return off - first + cnt > (uint32_t)kBucketMax;
 }
 
-__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, uint32_t per_entry, const uint32_t* __restrict__ bin_count,
+__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, uint32_t target, uint32_t per_entry, const uint32_t* __restrict__ bin_count,
                                                         PlanArrays a, uint32_t bucket_capacity, BucketHeader* hdr)
 {
     __shared__ uint32_t cnts[kMaxBins];            // the bin counts, read three times
@@ -222,9 +240,9 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
     {
         uint32_t o = off;
         for (int b = b0; b < b1; ++b) {
-            const uint32_t cnt = cnts[b], pc = b > 0 ? cnts[b - 1] : 0u;
+            const uint32_t cnt = cnts[b];
             a.bin_off[b] = o;
-            starts += starts_bucket(b, o, o - pc, cnt, pc, span_bins, per_entry) ? 1u : 0u;
+            starts += starts_bucket(b, o, cnts, span_bins, target, per_entry) ? 1u : 0u;
             o += cnt;
         }
     }
@@ -238,8 +256,8 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
     {
         uint32_t o = off;
         for (int b = b0; b < b1; ++b) {
-            const uint32_t cnt = cnts[b], pc = b > 0 ? cnts[b - 1] : 0u;
-            if (starts_bucket(b, o, o - pc, cnt, pc, span_bins, per_entry)) {
+            const uint32_t cnt = cnts[b];
+            if (starts_bucket(b, o, cnts, span_bins, target, per_entry)) {
                 a.bucket_bin0[id] = (uint32_t)b;
                 a.bucket_off[id] = o;
                 a.bucket_cursor[id] = o;
@@ -865,9 +883,10 @@ bool make_bucket_layout(int64_t n_pairs, int64_t N, int add_self_loops, BucketLa
     // bound of a graph of 0.4 million entries within one group): 3 to 5 % from 7 thousand to 5 million entries.
     const int64_t spread = L.M / kTargetBuckets;
     L.target = spread > kTargetMax ? kTargetMax : spread < kTargetMin ? kTargetMin : (int)spread;
-    // worst case of starts_bucket: one start per `target` entries, one per pair of neighbours above kBucketMax (every
-    // entry is in two pairs), one per row window
-    L.bucket_bound = L.M / L.target + 2 * L.M / kBucketMax + L.nbins / L.span_bins + 4;
+    // worst case of starts_bucket: one start per window, one more for a bin that reaches over the end of its window (at most
+    // one in each, of more than kBucketMax - 1 - target entries), one per row window
+    const int64_t windows = L.M / L.target, reach = L.M / (kBucketMax - 1 - L.target);
+    L.bucket_bound = windows + (windows < reach ? windows : reach) + L.nbins / L.span_bins + 4;
     if (L.bucket_bound > kMaxBuckets) return false;
     L.two_level = L.bucket_bound > kGroupBuckets;
     int64_t hb = (L.n_items + 16383) / 16384;
@@ -926,7 +945,7 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
         n_pairs, d_src, d_dst, N, L.n_items, L.items_per_block, L.s, L.nbins, u32(L.counts), hdr);
     colsum_kernel<<<dim3((unsigned)((L.nbins + 255) / 256), kColsumSlices), dim3(256), 0, stream>>>(
         L.hist_blocks, L.nbins, u32(L.counts), u32(L.bin_count));
-    plan_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(L.nbins, L.span_bins, (uint32_t)((1ull << 32) / (uint64_t)L.target), u32(L.bin_count), pa,
+    plan_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(L.nbins, L.span_bins, (uint32_t)L.target, (uint32_t)((1ull << 32) / (uint64_t)L.target), u32(L.bin_count), pa,
                                                         (uint32_t)L.bucket_bound, hdr);
     const unsigned item_tiles = (unsigned)((L.n_items + kItemsPerTile - 1) / kItemsPerTile);
     if (L.M > 0) {
