@@ -468,11 +468,13 @@ double retexo_gamma(double B, double R, double H0, double sum_H, double sum_C, d
  * values per process, read by every launch: set them from a single thread while no other thread
  * is inside the library, and restore the default afterwards.  Production callers never need them.
  * name: "agg_slab_cols" (0 = auto), "agg_slab_major" (-1 auto / 0 / 1),
- *       "agg_heavy_degree" (rows at least this long get a whole workgroup; 2048, the default, stands for at most 2048:
- *       shorter rows do on graphs so small that one wave on its longest row would outlast all others),
+ *       "agg_heavy_degree" (rows at least this long, rounded up to 1, 64, 128, .. 16384, get a whole workgroup; 2048, the
+ *       default, stands for at most 2048: where one wave on its longest row would outlast all others, shorter rows do, by
+ *       a rule on the entries and columns of the call, so that a call over some of the columns need not add up in the
+ *       order of one over all; 2047 pins 2048 itself),
  *       "agg_parts" (source-id ranges walked one after the other: -1 auto, 1 off, 2/4/8/16),
  *       "agg_narrow_heavy" (narrow slabs: rows whose share of ONE source range is at least this
- *       long get a whole workgroup; default 1024),
+ *       long get a whole workgroup, rounded up alike; default 1024),
  *       "agg_max_vec" (cap on floats per lane per gather),
  *       "agg_gat_fast" (0: plain edge-softmax kernel), "agg_gat_flash" (0: ordinary rows read the
  *       source scores from the table instead of computing them from the gathered rows),

@@ -35,13 +35,13 @@ struct retexo_plan {
     int64_t part_span = 0;
     int32_t max_degree = 0;
     // number of rows with deg >= threshold[i], thresholds fixed in plan.hip
-    int64_t rows_at_least[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    int64_t rows_at_least[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     void* block = nullptr;          // the one device allocation behind deg, dinv, order, part_ptr
     void* build_scratch = nullptr;
 };
 
-constexpr int kPlanThresholdCount = 9;
-constexpr int kPlanThresholds[kPlanThresholdCount] = {64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384};
+constexpr int kPlanThresholdCount = 10;
+constexpr int kPlanThresholds[kPlanThresholdCount] = {1, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384};
 
 constexpr int64_t kHeavyDegree = 2048;
 
@@ -79,7 +79,7 @@ static inline int64_t long_rows(const retexo_plan* p, int64_t F, bool own_launch
         const int64_t mean = p->N > 0 ? p->nnz / p->N : 0, floor = own_launch ? 256 : 64;
         at_least = (p->nnz * F) >> (own_launch ? 19 : 20);
         const int64_t above_mean = (own_launch ? 4 : 2) * mean, least = above_mean > floor ? above_mean : floor;
-        at_least = at_least < least ? least : at_least;
+        at_least = at_least < least ? least : at_least;       // (64 or more)
         at_least = at_least > kHeavyDegree ? kHeavyDegree : at_least;
     }
     for (int i = 0; i < kPlanThresholdCount; ++i)

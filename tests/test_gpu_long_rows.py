@@ -102,3 +102,27 @@ def test_default_threshold_is_an_upper_bound():
     assert_cond_close(first.cpu().numpy()[:, :96], other.cpu().numpy()[:, :96].astype(np.float64), mag, what="classes")
     assert not torch.equal(first[:, :96], other[:, :96])       # 600 entries in eight interleaved sums round differently
     g.destroy()
+
+
+def test_every_row_can_be_given_a_workgroup():
+    # rows of 40 entries in slabs of 32 columns: a workgroup each with the line at one entry, bundled with the line at 64;
+    # the two add up in other orders
+    n, F = 500, 96
+    rng = np.random.Generator(np.random.Philox(key=40))
+    rp = np.arange(n + 1, dtype=np.int64) * 40
+    ci = np.concatenate([np.sort(rng.permutation(n)[:40]) for _ in range(n)]).astype(np.int32)
+    g = Hn.make_plan(Hn.DeviceGraph(n, int(rp[-1]), Hn.dev(rp), Hn.dev(ci)), validate=True)
+    Z = wl.random_matrix(n, F, 41)
+    want, mag = oracle.aggregate("sum", rp, ci, Z, F), oracle.aggregate_abs("sum", rp, ci, Z, F)
+    got = {}
+    try:
+        B.check(B.retexo_set_option("agg_slab_cols", 32), "set_option")
+        for line in (1, 64):
+            B.check(B.retexo_set_option("agg_narrow_heavy", line), "set_option")
+            got[line] = Hn.aggregate(g, "sum", Hn.dev(Z), F).cpu().numpy()[:, :F]
+            assert_cond_close(got[line], want, mag, what="line at %d" % line)
+    finally:
+        B.check(B.retexo_set_option("agg_slab_cols", 0), "set_option")
+        B.check(B.retexo_set_option("agg_narrow_heavy", 1024), "set_option")
+    assert not np.array_equal(got[1], got[64])
+    g.destroy()
