@@ -16,7 +16,7 @@ Prints one JSON line.  Extra objects:
   roofline      the dominant kernel (the widest aggregation) against the 8 TB/s HBM peak;
                 frac is measured-traffic bytes / time / peak and cannot exceed 1, the
                 gather-model and compulsory figures stand beside it
-  transforms    every dense transform timed alone against the fp32 matrix-core peak
+  transforms    every dense transform timed alone: its rate, what it issues on the bf16 matrix cores, and HBM
   cpu_baseline  the CPU oracle timed on the same workload
 """
 from __future__ import annotations
@@ -37,7 +37,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-MFMA_F32_PEAK_TFLOPS = 157.3
+MFMA_BF16_PEAK_TFLOPS = 2500.0
 
 
 def parse():
@@ -322,7 +322,7 @@ def bench_workload(index, args):
         "edge_features_per_s": float(nnz) * F / (agg_ms * 1e-3),
     }
 
-    # ---- every dense transform alone, against the fp32 matrix-core peak (skinny outputs: against HBM)
+    # ---- every dense transform alone, against the bf16 matrix cores that carry it and against HBM
     transforms = []
     for i, st in enumerate(w.stages):
         if not st.w:
@@ -334,16 +334,14 @@ def bench_workload(index, args):
         fl = 2.0 * n * st.d_in * st.d_out
         by = 4.0 * (n * st.d_in + n * st.d_out + st.d_in * st.d_out)
         ai = fl / by
-        # what the matrix cores are issued: whole 32-column accumulator tiles (41 columns run as 64), k in pairs
+        # what the matrix cores are issued by the block kernel: six bf16 products per float32 product, whole tiles of
+        # columns (41 run as 64) and of sixteen k
         cols = next((t for t in (32, 64, 128, 192, 256) if st.d_out <= t), 256 * -(-st.d_out // 256))
-        fl_issued = 2.0 * n * (st.d_in + st.d_in % 2) * cols
-        # the products run on the bf16 matrix cores (three parts per float32), so these fractions of the fp32
-        # instruction's peak, kept for comparison, may pass 1
-        balance = MFMA_F32_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBS          # flop per byte where the two bounds would meet
+        fl_issued = 6 * 2.0 * n * (-(-st.d_in // 16) * 16) * cols
+        balance = MFMA_BF16_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBS         # issued flop per byte where the two bounds meet
         transforms.append({"stage": "%s%d" % (st.kind, i), "shape": "%d x %d -> %d" % (n, st.d_in, st.d_out),
-                           "ms_alone": tms, "TFLOP/s": fl / tms / 1e9, "frac_fp32_mfma": fl / tms / 1e9 / MFMA_F32_PEAK_TFLOPS,
-                           "issued_TFLOP/s": fl_issued / tms / 1e9,
-                           "frac_fp32_mfma_issued": fl_issued / tms / 1e9 / MFMA_F32_PEAK_TFLOPS,
+                           "ms_alone": tms, "TFLOP/s": fl / tms / 1e9, "issued_bf16_TFLOP/s": fl_issued / tms / 1e9,
+                           "frac_bf16_mfma_issued": fl_issued / tms / 1e9 / MFMA_BF16_PEAK_TFLOPS,
                            "GB/s": by / tms / 1e6, "frac_hbm": by / tms / 1e6 / HBM_PEAK_GBS,
                            "flop_per_byte": ai, "flop_per_byte_issued": fl_issued / by,
                            "bound": "mfma" if fl_issued / by >= balance else "hbm"})
@@ -412,7 +410,7 @@ def extras(out, w, pipe, args, timer, reps, di, Zin, agg_out, ws, agg_ms):
         tms = timer.ms(train_once, reps)
         tfl = (4.0 * n * st.d_in * st.d_out + 6.0 * n * st.d_out * n_cls) / tms / 1e9
         out["train_step"] = {"layer": "%d->%d (ReLU) + classifier %d->%d" % (st.d_in, st.d_out, st.d_out, n_cls),
-                             "ms": tms, "TFLOP/s": tfl, "frac_fp32_mfma": tfl / MFMA_F32_PEAK_TFLOPS,
+                             "ms": tms, "TFLOP/s": tfl,
                              "loss_first": float(losses[0].cpu()[0]), "loss_last": float(losses[-1].cpu()[0]),
                              "sgd_steps": reps + 1}
         draw = [0]

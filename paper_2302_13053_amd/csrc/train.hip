@@ -5,7 +5,7 @@
 // H_m x H_K) and softmax cross-entropy over the labelled nodes; the last layer
 // is the classification function itself (H == 0 here).
 //
-//      A      = ReLU(X W1 + b1)          transform kernel (fp32 MFMA)
+//      A      = ReLU(X W1 + b1)          transform kernel (float32 in three bf16 parts)
 //      logits = A Wc + bc                transform kernel
 //      dL     = (softmax(logits) - onehot(label)) / n_labelled, 0 for unlabelled nodes
 //      gWc    = A^T dL,  gbc = colsum(dL)
@@ -404,8 +404,8 @@ struct Split { int S; int64_t k_chunk; };
 Split choose_split(int64_t K, int64_t M, int64_t Nq, int bn)
 {
     const int64_t tiles = ((M + 127) / 128) * ((Nq + bn - 1) / bn);
-    // the widest tile runs two workgroups per CU: at most 1024 workgroups are exactly two rounds of the 512
-    // slots (one more workgroup would add a third round for it alone)
+    // at most 1024 workgroups: four rounds of the 256 that the widest tile (eight waves) has room for, two of the 128-column
+    // tile's 512 (one more workgroup would add a round for it alone)
     int64_t S = 1024 / tiles;
     const int64_t max_s = (K + 255) / 256;                  // at least 256 nodes per chunk
     if (S > max_s) S = max_s;
@@ -590,7 +590,7 @@ int layer_grad_impl(int64_t N, int64_t D_in, int64_t H, int64_t C,
         // back through the classifier, the dropout (its scale rides on the transposed classifier, its mask is
         // part of "A > 0") and the ReLU, then the layer's own gradients
         // (the contraction runs over the padded width of dL: its padding columns and the padding rows
-        // of the transposed classifier are zero, and a multiple of four keeps the loads 16 bytes wide)
+        // of the transposed classifier are zero)
         const int64_t tot = H * t.ldc;
         transpose_kernel<<<dim3((unsigned)((tot + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
             (int)H, (int)C, (int)t.ldc, d_Wc, WcT, keep_scale);

@@ -19,22 +19,23 @@
 // call has no scratch memory to keep its parts in.
 //
 // What bounds the wide tiles is power and the change between loading and storing:
-// the matrix instructions run at a clock of about 1.5 GHz (GRBM_GUI_ACTIVE), the
-// same launch on zeros is 25 % faster, and a bf16 library product of 8192^3
-// reaches 1210-1270 TFLOP/s where this kernel issues 900-1000.  Measured (float32
-// instructions before): 2,449,029 x 256 -> 256 2.08 ms = 154 TFLOP/s (2.60 ms),
-// 232,965 x 1204 -> 256 0.84 ms = 170 (1.21), 2,449,029 x 256 -> 188 1.66 ms (1.98),
-// 232,965 x 512 -> 41 0.137 ms = 3.8 TB/s (0.171), 100,000 x 512 -> 128 94 us (142).
+// under them the chip runs at about 1.5 GHz, the same launch on zeros is a quarter
+// faster, and a bf16 library product of 8192^3 reaches 1210-1270 TFLOP/s where
+// this kernel issues 960-1070.  Measured (float32 instructions before):
+// 2,449,029 x 256 -> 256 2.01 ms = 160 TFLOP/s (2.62 ms), 232,965 x 1204 -> 256
+// 0.805 ms = 178 (1.20), 2,449,029 x 256 -> 188 1.69 ms (2.01), 232,965 x 512 -> 41
+// 0.136 ms = 3.8 TB/s (0.182), 100,000 x 512 -> 128 93 us (134), 40,000 x 2866 ->
+// 64 157 us (345).
 //
 // Sources are clamped instead of checked (rows past the end repeat the last
 // row, columns past D_out the last column), so the loop carries no selects;
-// only a partial last K tile takes a checked form.  Loads are four bytes wide
+// only the last tiles of K, which may be partial, have a form of their own.  Loads are four bytes wide
 // (W) or 16 bytes at any float's address (H), so every alignment and leading
 // dimension takes this kernel, in one order of arithmetic.  Bias and ReLU are
 // applied to the accumulators on the way out, through one pointer per 32x32 tile
 // that walks down the rows: every store covers two whole cache lines.  (Passed
 // through LDS first, to leave 16 bytes per lane: 2,449,029 x 256 -> 256 2.15 ms
-// instead of 2.08, x 16 -> 256 547 us instead of 500.)  Matrices of few rows take
+// where this was 2.08, x 16 -> 256 547 us and 500.)  Matrices of few rows take
 // the few-rows kernel at the end (K split over the waves of a workgroup).
 #include "common.hpp"
 #include "tiles.hpp"

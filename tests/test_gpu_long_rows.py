@@ -126,3 +126,26 @@ def test_every_row_can_be_given_a_workgroup():
         B.check(B.retexo_set_option("agg_narrow_heavy", 1024), "set_option")
     assert not np.array_equal(got[1], got[64])
     g.destroy()
+
+
+@pytest.mark.parametrize("name", list(LENGTHS))
+@pytest.mark.parametrize("F", [31, 128, 700])
+@pytest.mark.parametrize("mode", ["mean", "gcn_sym", "max", "gat_softmax"])
+def test_default_line(name, F, mode):
+    # the line that the size of the call draws, not the one the fixture pins
+    B.check(B.retexo_set_option("agg_heavy_degree", 2048), "set_option")
+    g, rp, ci = graph(name)
+    Z = wl.random_matrix(g.n_nodes, F, F, ld=wl.pad_ld(F))
+    a = wl.random_matrix(1, F, 1) * np.float32(0.02)
+    kw = dict(heads=1, a_src=a, a_dst=a) if mode == "gat_softmax" else {}
+    dev = {k: Hn.dev(v) if k != "heads" else v for k, v in kw.items()}
+    got = Hn.aggregate(g, mode, Hn.dev(Z), F, **dev).cpu().numpy()[:, :F]
+    want = oracle.aggregate(mode, rp, ci, Z, F, **kw)
+    if mode == "max":
+        assert np.array_equal(got.astype(np.float64), want)
+    elif mode == "gat_softmax":
+        assert_close(got, want, what=name)
+    else:
+        assert_cond_close(got, want, oracle.aggregate_abs(mode, rp, ci, Z, F),
+                          tol=600 * 2.0 ** -24 if name == "all long" else 1e-5, what=name)
+    g.destroy()

@@ -190,3 +190,20 @@ def test_training_decides_units_near_zero_by_the_float32_sum():
     _, gW1, gb1, _, _ = Hn.layer_grad(d(X), d_in, d(y), d(W1), d(b1), d(Wc), d(bc))
     assert_close(gW1.cpu().numpy(), X.astype(np.float64).T @ dA, what="gW1")
     assert_close(gb1.cpu().numpy()[None, :], dA.sum(0)[None, :], what="gb1")
+
+
+def test_weight_gradient_of_a_large_first_layer_against_64_bits():
+    # 1204 x 256 outputs over 232,965 nodes, a thousand chunks' partial sums: the measured training step's first gradient,
+    # without the unit decisions that keep that one from having a value in 64 bits
+    n, d_in, d_out = 232965, 1204, 256
+    g = torch.Generator(device="cuda").manual_seed(11)
+    X = torch.empty((n, 1216), device="cuda").normal_(generator=g)
+    G = torch.empty((n, d_out), device="cuda").normal_(generator=g) * 1e-3
+    gW, gb = Hn.transform_backward(X, d_in, G, d_out)
+    want = torch.zeros((d_in, d_out), dtype=torch.float64, device="cuda")
+    for i in range(0, n, 20000):
+        want += X[i:i + 20000, :d_in].double().T @ G[i:i + 20000].double()
+    # a chunk's float32 sum of 2,300 products and the sum of a hundred chunks: about sqrt(2,300) roundings of 2^-25 each
+    assert float((gW.double() - want).norm() / want.norm()) <= 48 * 2.0 ** -25
+    assert float((gW.double() - want).abs().max() / want.pow(2).mean().sqrt()) <= 6 * 48 * 2.0 ** -25
+    assert float((gb.double() - G.double().sum(0)).norm() / G.double().sum(0).norm()) <= 48 * 2.0 ** -25
