@@ -877,8 +877,9 @@ bool make_bucket_layout(int64_t n_pairs, int64_t N, int add_self_loops, BucketLa
     L.span_bins = (int)(span_rows >> L.s);
     if (L.span_bins < 1 || L.nbins > kMaxBins) return false;
     // The sort of a bucket costs much the same half full as full (twenty barriers, its scans), so a large graph's are
-    // filled to 0.7 of what fits: 57.5 million pairs over 233 thousand nodes 1410 us at half, 1315 at 0.7, 1360 at 0.8
-    // (there some no longer fit); whole constructions of 30 to 50 million pairs gain 8 to 10 %.  A small graph would then
+    // filled to 0.7 of what fits: 57.5 million pairs over 233 thousand nodes 1410 us at half, 1315 at 0.7, 1360 at 0.8 (when
+    // several bins could still overfill a bucket; 1290 at 0.7 since); whole constructions of 30 to 50 million pairs gain 8
+    // to 10 %.  A small graph would then
     // leave CUs idle and wait for a full bucket's sort, so it is spread over kTargetBuckets first (as many as keep the
     // bound of a graph of 0.4 million entries within one group): 3 to 5 % from 7 thousand to 5 million entries.
     const int64_t spread = L.M / kTargetBuckets;

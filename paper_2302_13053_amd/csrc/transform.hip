@@ -18,14 +18,15 @@
 // four waves and two to four workgroups.  W is split by every workgroup again: the
 // call has no scratch memory to keep its parts in.
 //
-// What bounds the wide tiles is power and the change between loading and storing:
-// under them the chip runs at about 1.5 GHz, the same launch on zeros is a quarter
-// faster, and a bf16 library product of 8192^3 reaches 1210-1270 TFLOP/s where
-// this kernel issues 960-1070.  Measured (float32 instructions before):
-// 2,449,029 x 256 -> 256 2.01 ms = 160 TFLOP/s (2.62 ms), 232,965 x 1204 -> 256
-// 0.805 ms = 178 (1.20), 2,449,029 x 256 -> 188 1.69 ms (2.01), 232,965 x 512 -> 41
-// 0.136 ms = 3.8 TB/s (0.182), 100,000 x 512 -> 128 93 us (134), 40,000 x 2866 ->
-// 64 157 us (345).
+// What bounds the wide tiles is power, the splitting between the matrix
+// instructions and the change between loading and storing: a single launch runs at
+// 1.8-1.9 of 2.4 GHz with the matrix cores busy half of its cycles (GRBM_GUI_ACTIVE,
+// SQ_VALU_MFMA_BUSY_CYCLES), the same launch on zeros is a quarter faster, and a bf16
+// library product of 8192^3 reaches 1210-1280 TFLOP/s where this kernel issues
+// 960-1110.  Measured (float32 instructions before): 2,449,029 x 256 -> 256 2.01 ms =
+// 160 TFLOP/s (2.62 ms), 232,965 x 1204 -> 256 0.805 ms = 178 (1.20), 2,449,029 x 256
+// -> 188 1.69 ms (2.01), 232,965 x 512 -> 41 0.136 ms = 3.8 TB/s (0.182), 100,000 x
+// 512 -> 128 93 us (134), 40,000 x 2866 -> 64 157 us (345).
 //
 // Sources are clamped instead of checked (rows past the end repeat the last
 // row, columns past D_out the last column), so the loop carries no selects;
