@@ -39,8 +39,8 @@ __device__ __forceinline__ void each(F&& f) { each_index(std::make_integer_seque
 // Both operands are multiplied by 2^24 before they are split and the sums by 2^-48 at the end, which changes no bit of
 // an ordinary result.  The last bit of the smallest float32 (2^-149) is then 2^-125, a normal bf16 number, so that no
 // operand loses its mid and lo parts, however small it is (unscaled, one below 2^-110 did: 32 products of operands of
-// about 2^-124 and 2^40 were 5.6e-4 off), and whatever the matrix core does with values below its normal range, it does
-// 2^-174 below the result.  At the other end operands from 2^104 on and sums from 2^80 on overflow.
+// about 2^-124 and 2^40 were 5.6e-4 off), and what the matrix core does with sums below its normal range stays below
+// 2^-174 of the unscaled ones.  At the other end operands from 2^104 on and sums from 2^80 on overflow.
 // Where they do, and for infinities and NaN (their remainders are NaN), the float32 instructions take over, one 32 x 32
 // tile at a time (see `redo_tile`).
 // ---------------------------------------------------------------------------

@@ -14,7 +14,7 @@
 // D_out <= 256, so H — by far the larger operand — is read from HBM exactly
 // once.  The K loop moves 16 columns of H and rows of W per step through LDS, as
 // bf16 parts in the layout of the matrix operands.  Tiles wider than 128 run
-// eight waves, one workgroup per CU (212 registers, 75 KB of LDS), narrower ones
+// eight waves, one workgroup per CU (217 registers, 228 where signs are decided, 75 KB of LDS), narrower ones
 // four waves and two to four workgroups.  W is split by every workgroup again: the
 // call has no scratch memory to keep its parts in.
 //
@@ -30,9 +30,12 @@
 //
 // Sources are clamped instead of checked (rows past the end repeat the last
 // row, columns past D_out the last column), so the loop carries no selects;
-// only the last tiles of K, which may be partial, have a form of their own.  Loads are four bytes wide
-// (W) or 16 bytes at any float's address (H), so every alignment and leading
-// dimension takes this kernel, in one order of arithmetic.  Bias and ReLU are
+// only the last tiles of K, which may be partial, have a form of their own.
+// Loads are four bytes wide (W) or 16 bytes at any float's address (H), so every
+// alignment and leading dimension takes this kernel, in one order of arithmetic.
+// Short rows into narrow outputs are within a few per cent of what they took on the
+// float32 instruction, not below it: 1,000,000 x 64 -> 32 79.5 us (75.7),
+// 889,043 x 48 -> 8 51.5 (49.5), 300,000 x 8 -> 128 36.8 (35.3).  Bias and ReLU are
 // applied to the accumulators on the way out, through one pointer per 32x32 tile
 // that walks down the rows: every store covers two whole cache lines.  (Passed
 // through LDS first, to leave 16 bytes per lane: 2,449,029 x 256 -> 256 2.15 ms
