@@ -12,9 +12,6 @@
 // decreasing degree (stable: equal degrees stay in id order) and the number of
 // rows at or above a few degree thresholds.
 #include <cstring>
-
-#include <rocprim/device/device_radix_sort.hpp>
-
 #include <new>
 
 #include "common.hpp"
@@ -23,20 +20,347 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__global__ __launch_bounds__(kThreads) void degree_kernel(
-    int64_t N, int64_t nnz, const int64_t* __restrict__ row_ptr, int32_t* __restrict__ deg,
-    float* __restrict__ dinv, uint32_t* __restrict__ sort_key, int32_t* __restrict__ ids,
-    uint32_t* bad)
+// What the host reads back.
+struct Readback {
+    int64_t counts[kPlanThresholdCount + 1];      // rows of at least kPlanThresholds[i] entries ... and the largest degree
+    uint32_t bad;
+    uint32_t pad;
+};
+
+// ---------------------------------------------------------------------------
+// The schedule order: a stable counting sort of the degrees, largest first (equal degrees stay in id order), one
+// digit of the degree at a time, lowest digit first.
+//
+// Bound by launches and latencies, not bytes (12 bytes per row): a general 32-bit radix sort took 3 to 19 dependent
+// launches here, where a power-law graph's degrees have 15 significant bits and a citation graph's 8.  Stability
+// inside a workgroup without a sort: every wave owns a consecutive piece of the rows and counters of its own, a row's
+// rank among the 64 that the wave looks at is the number of lower lanes with the same digit (one ballot per bit),
+// and the pieces' counters are made offsets in the order of the pieces.
+// ---------------------------------------------------------------------------
+constexpr int kOrderThreads = 1024;
+constexpr int kOrderWaves = kOrderThreads / 64;
+
+// lanes (of those with `have`) whose digit equals this lane's
+template <int BITS>
+__device__ __forceinline__ uint64_t same_digit(uint32_t d, bool have)
 {
-    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (v >= N) return;
-    const int64_t lo = row_ptr[v], hi = row_ptr[v + 1];
-    int64_t d = hi - lo;
-    if (d < 0 || d > 0x7fffffff || (v == 0 && lo != 0) || (v == N - 1 && hi != nnz)) { atomicOr(bad, 1u); d = 0; }
-    deg[v] = (int32_t)d;
-    dinv[v] = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
-    sort_key[v] = (uint32_t)d;
-    ids[v] = (int32_t)v;
+    uint64_t m = __ballot(have);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const uint64_t set = __ballot(have && ((d >> b) & 1u));
+        m &= ((d >> b) & 1u) ? set : ~set;
+    }
+    return m;
+}
+
+// The lane's position behind counters[d] in the order of the lanes; the counter moves past all of them.  Called by whole
+// waves, with counters of the wave's own; a wave's LDS operations keep their order, the fences hold the compiler to it.
+template <int BITS, typename C>
+__device__ __forceinline__ uint32_t take_position(C* counters, uint32_t d, bool have)
+{
+    const uint64_t m = same_digit<BITS>(d, have);
+    const int lane = threadIdx.x & 63;
+    const uint32_t below = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+    uint32_t at = 0;
+    if (have) at = counters[d];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (have && below == 0) counters[d] = (C)(at + (uint32_t)__popcll(m));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return at + below;
+}
+
+// inclusive prefix sum over the workgroup of kOrderThreads; sc: kOrderWaves words, free again on return
+__device__ __forceinline__ uint32_t order_scan(uint32_t v, uint32_t* sc)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t t = __shfl_up(v, d, 64);
+        if (lane >= d) v += t;
+    }
+    if (lane == 63) sc[wave] = v;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) v += sc[w];
+    __syncthreads();
+    return v;
+}
+
+// degree of row v; what cannot be one counts as bad and as zero
+__device__ __forceinline__ int32_t row_degree(int64_t v, int64_t N, int64_t nnz, const int64_t* __restrict__ row_ptr, bool& bad)
+{
+    const int64_t lo = row_ptr[v], hi = row_ptr[v + 1], d = hi - lo;
+    if (d < 0 || d > 0x7fffffff || (v == 0 && lo != 0) || (v == N - 1 && hi != nnz)) {
+        bad = true;
+        return 0;
+    }
+    return (int32_t)d;
+}
+
+struct Thresholds { int t[kPlanThresholdCount]; };
+
+// A workgroup's rows: counts at the thresholds, largest degree, and whether one was bad.
+struct RowStats {
+    uint32_t at_least[kPlanThresholdCount];
+    uint32_t largest, bad;
+};
+__device__ __forceinline__ void add_row(RowStats& st, int32_t d, const Thresholds& th)
+{
+#pragma unroll
+    for (int i = 0; i < kPlanThresholdCount; ++i) st.at_least[i] += d >= th.t[i] ? 1u : 0u;
+    st.largest = max(st.largest, (uint32_t)d);
+}
+// the threads' sums into `all` (LDS, zeroed before the last barrier); a barrier follows
+__device__ __forceinline__ void gather_stats(const RowStats& st, RowStats* all)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < kPlanThresholdCount; ++i) {
+        uint32_t c = st.at_least[i];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) c += __shfl_xor(c, m, 64);
+        if (lane == 0 && c) atomicAdd(&all->at_least[i], c);
+    }
+    uint32_t top = st.largest;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) top = max(top, __shfl_xor(top, m, 64));
+    if (lane == 0) atomicMax(&all->largest, top);
+    if (st.bad) atomicOr(&all->bad, 1u);
+    __syncthreads();
+}
+
+// Small graphs, N <= kSmallRows: degrees, normalisers, order and counts in one launch by one workgroup, degrees and
+// ids in LDS (136 KB), 8 bits of the degree per pass and no more passes than the largest degree has.
+// 2,708 rows: 6 launches and 30 us of a plan's 85 before; 16,384 rows: see kSmallRows.
+constexpr int kSmallRows = 4096;
+constexpr int kSmallSteps = kSmallRows / kOrderThreads;
+struct SmallShared {
+    uint32_t deg[kSmallRows];
+    uint16_t ids[2][kSmallRows];
+    uint16_t counters[kOrderWaves][256];         // (positions stay below 2^16)
+    uint32_t sc[kOrderWaves];
+    RowStats all;
+};
+__global__ __launch_bounds__(kOrderThreads) void small_order_kernel(
+    int N, int64_t nnz, const int64_t* __restrict__ row_ptr, int32_t* __restrict__ deg, float* __restrict__ dinv,
+    int32_t* __restrict__ order, Thresholds th, Readback* rb)
+{
+    __shared__ SmallShared sh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid < (int)(sizeof(RowStats) / 4)) reinterpret_cast<uint32_t*>(&sh.all)[tid] = 0u;
+    __syncthreads();
+    RowStats st = {};
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < kSmallSteps; ++j) {
+        const int v = j * kOrderThreads + tid;
+        if (v < N) {
+            const int32_t d = row_degree(v, N, nnz, row_ptr, bad);
+            sh.deg[v] = (uint32_t)d;
+            deg[v] = d;
+            dinv[v] = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
+            add_row(st, d, th);
+        }
+    }
+    st.bad = bad ? 1u : 0u;
+    gather_stats(st, &sh.all);
+    const uint32_t largest = sh.all.largest;
+    if (tid <= kPlanThresholdCount) rb->counts[tid] = tid < kPlanThresholdCount ? sh.all.at_least[tid] : largest;
+    if (tid == 0) rb->bad = sh.all.bad;
+
+    const int steps = (N + kOrderThreads - 1) / kOrderThreads;
+    const int piece = wave * steps * 64;                     // first of the wave's steps * 64 positions
+    for (int shift = 0, pass = 0; shift == 0 || (shift < 32 && largest >> shift); shift += 8, ++pass) {
+        const uint16_t* from = sh.ids[pass & 1];
+        uint16_t* to = sh.ids[(pass & 1) ^ 1];
+        const bool last = shift + 8 >= 32 || (largest >> (shift + 8)) == 0;
+        auto id_at = [&](int p) { return pass == 0 ? (uint32_t)p : (uint32_t)from[p]; };
+        auto digit = [&](uint32_t id) { return 255u - ((sh.deg[id] >> shift) & 255u); };      // largest first
+        uint32_t* c32 = reinterpret_cast<uint32_t*>(sh.counters);
+        for (int i = tid; i < kOrderWaves * 128; i += kOrderThreads) c32[i] = 0u;
+        __syncthreads();
+        for (int j = 0; j < steps; ++j) {
+            const int p = piece + j * 64 + lane;
+            const bool have = p < N;
+            take_position<8>(sh.counters[wave], have ? digit(id_at(p)) : 0u, have);
+        }
+        __syncthreads();
+        uint32_t mine = 0;
+        if (tid < 256) {
+            for (int w = 0; w < kOrderWaves; ++w) mine += sh.counters[w][tid];
+        }
+        uint32_t at = order_scan(mine, sh.sc) - mine;
+        if (tid < 256) {
+            for (int w = 0; w < kOrderWaves; ++w) {
+                const uint32_t c = sh.counters[w][tid];
+                sh.counters[w][tid] = (uint16_t)at;
+                at += c;
+            }
+        }
+        __syncthreads();
+        for (int j = 0; j < steps; ++j) {
+            const int p = piece + j * 64 + lane;
+            const bool have = p < N;
+            const uint32_t id = have ? id_at(p) : 0u;
+            const uint32_t q = take_position<8>(sh.counters[wave], have ? digit(id) : 0u, have);
+            if (have) {
+                if (last) order[q] = (int32_t)id;
+                else to[q] = (uint16_t)id;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Larger graphs: up to kOrderBlocks workgroups of consecutive rows, two launches per digit of 10 bits: every
+// workgroup counts its rows' digits, then every workgroup adds up the counts before its own and moves its rows.
+// The first launch also makes the degrees; its largest says which digit is the last (later launches find nothing
+// to do).  A whole plan of 19,717 rows 90 -> 45 us, 232,965 155 -> 95, 2,449,029 229 -> 180.  128 workgroups, since each
+// reads every workgroup's counts (64: 85 us and 247), of at least 2,048 rows, or 1,024 up to 32,768 rows (100,000 rows in
+// pieces of 1,024: 83 us, of 2,048: 72).
+constexpr int kOrderBits = 10, kOrderBins = 1 << kOrderBits;
+static_assert(kOrderBins == kOrderThreads, "one bin per thread");
+constexpr int kOrderBlocks = 128;
+struct OrderArgs {
+    int64_t N, per_block;                // per_block: multiple of kOrderThreads
+    int passes;                          // digits that a row of nnz entries has
+    const int32_t* deg;
+    uint2* pairs[2];                     // (degree, id) between the passes
+    int32_t* order;
+    uint32_t* counts;                    // [blocks][kOrderBins]
+    RowStats* stats;                     // [blocks]
+};
+
+__device__ __forceinline__ uint32_t order_digit(uint32_t d, int shift) { return (kOrderBins - 1) - ((d >> shift) & (kOrderBins - 1)); }
+
+__global__ __launch_bounds__(kOrderThreads) void degree_kernel(
+    OrderArgs a, int64_t nnz, const int64_t* __restrict__ row_ptr, int32_t* __restrict__ deg, float* __restrict__ dinv,
+    Thresholds th)
+{
+    __shared__ uint32_t hist[kOrderBins];
+    __shared__ RowStats all;
+    const int tid = threadIdx.x;
+    hist[tid] = 0u;
+    if (tid < (int)(sizeof(RowStats) / 4)) reinterpret_cast<uint32_t*>(&all)[tid] = 0u;
+    __syncthreads();
+    const int64_t begin = (int64_t)blockIdx.x * a.per_block, end = min(begin + a.per_block, a.N);
+    RowStats st = {};
+    bool bad = false;
+#pragma unroll 4
+    for (int64_t v = begin + tid; v < end; v += kOrderThreads) {
+        const int32_t d = row_degree(v, a.N, nnz, row_ptr, bad);
+        deg[v] = d;
+        dinv[v] = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
+        add_row(st, d, th);
+        atomicAdd(&hist[order_digit((uint32_t)d, 0)], 1u);
+    }
+    st.bad = bad ? 1u : 0u;
+    gather_stats(st, &all);
+    a.counts[(int64_t)blockIdx.x * kOrderBins + tid] = hist[tid];
+    if (tid < (int)(sizeof(RowStats) / 4))
+        reinterpret_cast<uint32_t*>(&a.stats[blockIdx.x])[tid] = reinterpret_cast<uint32_t*>(&all)[tid];
+}
+
+// largest degree of all workgroups' rows, uniform; a barrier has passed when the call returns
+__device__ __forceinline__ uint32_t largest_degree(const RowStats* stats, int blocks, uint32_t* sc)
+{
+    uint32_t top = (int)threadIdx.x < blocks ? stats[threadIdx.x].largest : 0u;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) top = max(top, __shfl_xor(top, m, 64));
+    if ((threadIdx.x & 63) == 0) sc[threadIdx.x >> 6] = top;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < (kOrderBlocks + 63) / 64; ++w) top = max(top, sc[w]);
+    __syncthreads();
+    return top;
+}
+
+// digits of the second and later passes
+__global__ __launch_bounds__(kOrderThreads) void order_count_kernel(OrderArgs a, int pass)
+{
+    __shared__ uint32_t hist[kOrderBins];
+    __shared__ uint32_t sc[kOrderWaves];
+    const int tid = threadIdx.x, shift = pass * kOrderBits;
+    if ((largest_degree(a.stats, gridDim.x, sc) >> shift) == 0) return;       // the pass before was the last
+    hist[tid] = 0u;
+    __syncthreads();
+    const int64_t begin = (int64_t)blockIdx.x * a.per_block, end = min(begin + a.per_block, a.N);
+    const uint2* from = a.pairs[(pass & 1) ^ 1];
+#pragma unroll 4
+    for (int64_t i = begin + tid; i < end; i += kOrderThreads) atomicAdd(&hist[order_digit(from[i].x, shift)], 1u);
+    __syncthreads();
+    a.counts[(int64_t)blockIdx.x * kOrderBins + tid] = hist[tid];
+}
+
+__global__ __launch_bounds__(kOrderThreads) void order_move_kernel(OrderArgs a, int pass, Readback* rb)
+{
+    __shared__ uint32_t counters[kOrderWaves][kOrderBins];
+    __shared__ uint32_t sc[kOrderWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, shift = pass * kOrderBits;
+    const int blocks = gridDim.x;
+    const uint32_t largest = largest_degree(a.stats, blocks, sc);
+    if (pass == 0 && blockIdx.x == 0 && tid <= kPlanThresholdCount + 1) {
+        if (tid < kPlanThresholdCount) {
+            int64_t c = 0;
+            for (int b = 0; b < blocks; ++b) c += a.stats[b].at_least[tid];
+            rb->counts[tid] = c;
+        } else if (tid == kPlanThresholdCount) {
+            rb->counts[tid] = largest;
+        } else {
+            uint32_t bad = 0;
+            for (int b = 0; b < blocks; ++b) bad |= a.stats[b].bad;
+            rb->bad = bad;
+        }
+    }
+    if (pass > 0 && (largest >> shift) == 0) return;
+    // (a row_ptr that is refused may claim more entries in a row than there are: the order is a permutation all the same)
+    const bool last = pass + 1 == a.passes || (largest >> (shift + kOrderBits)) == 0;
+    for (int i = tid; i < kOrderWaves * kOrderBins; i += kOrderThreads) (&counters[0][0])[i] = 0u;
+    // rows of bin tid: in the workgroups before this one, and in all
+    uint32_t before = 0, all = 0;
+#pragma unroll 16
+    for (int b = 0; b < blocks; ++b) {
+        const uint32_t c = a.counts[(int64_t)b * kOrderBins + tid];
+        if (b < (int)blockIdx.x) before += c;
+        all += c;
+    }
+    uint32_t at = order_scan(all, sc) - all + before;        // (its barriers also separate the zeroes from the counts)
+
+    const int64_t per_wave = a.per_block / kOrderWaves;      // multiple of 64
+    const int64_t begin = (int64_t)blockIdx.x * a.per_block + wave * per_wave, end = min(begin + per_wave, a.N);
+    const uint2* from = a.pairs[(pass & 1) ^ 1];
+    uint2* to = a.pairs[pass & 1];
+    auto entry = [&](int64_t i) { return pass == 0 ? make_uint2((uint32_t)a.deg[i], (uint32_t)i) : from[i]; };
+#pragma unroll 4
+    for (int64_t i = begin + lane; i < end; i += 64) atomicAdd(&counters[wave][order_digit(entry(i).x, shift)], 1u);
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kOrderWaves; ++w) {
+        const uint32_t c = counters[w][tid];
+        counters[w][tid] = at;
+        at += c;
+    }
+    __syncthreads();
+    constexpr int AHEAD = 4;                                 // rows in flight per lane
+    for (int64_t i0 = begin; i0 < end; i0 += 64 * AHEAD) {
+        uint2 e[AHEAD];
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t) {
+            const int64_t i = i0 + 64 * t + lane;
+            e[t] = i < end ? entry(i) : make_uint2(0u, 0u);
+        }
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t) {
+            if (i0 + 64 * t >= end) break;                   // (uniform)
+            const bool have = i0 + 64 * t + lane < end;
+            const uint32_t q = take_position<kOrderBits>(counters[wave], order_digit(e[t].x, shift), have);
+            if (have) {
+                if (last) a.order[q] = (int32_t)e[t].y;
+                else to[q] = e[t];
+            }
+        }
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void check_columns(
@@ -91,40 +415,13 @@ __global__ __launch_bounds__(kThreads) void split_rows_kernel(
     }
 }
 
-// counts[i] = number of rows with degree >= thresholds[i]; keys are sorted descending
-struct Thresholds { int t[kPlanThresholdCount]; };
-
-__global__ void count_at_least(int64_t N, const uint32_t* __restrict__ keys_desc, Thresholds th,
-                               int64_t* counts)
-{
-    const int i = threadIdx.x;
-    if (i >= kPlanThresholdCount) return;
-    const uint32_t t = (uint32_t)th.t[i];
-    int64_t lo = 0, hi = N;                 // first index with key < t
-    while (lo < hi) {
-        const int64_t mid = lo + ((hi - lo) >> 1);
-        if (keys_desc[mid] >= t) lo = mid + 1; else hi = mid;
-    }
-    counts[i] = lo;
-    if (i == 0) counts[kPlanThresholdCount] = N > 0 ? (int64_t)keys_desc[0] : 0;   // max degree
-}
-
-struct Readback {
-    int64_t counts[kPlanThresholdCount + 1];      // ... and the largest degree
-    int64_t nnz;
-    uint32_t bad;
-    uint32_t pad;
-};
-
-}  // namespace
-
-namespace {
-
 struct PlanLayout {
     bool split;
     int64_t o_deg, o_dinv, o_order, o_part, keep_bytes;            // what the plan keeps
-    int64_t s_kin, s_kout, s_ids, s_rb, s_tmp, scratch_bytes;      // what only its construction needs
-    size_t sort_bytes;
+    int64_t s_rb, s_pairs, s_counts, s_stats, scratch_bytes;       // what only its construction needs
+    bool small;
+    int passes, blocks;                                            // of the order sort
+    int64_t per_block;
 };
 
 int plan_layout(int64_t N, int64_t nnz, unsigned flags, PlanLayout& L)
@@ -140,19 +437,19 @@ int plan_layout(int64_t N, int64_t nnz, unsigned flags, PlanLayout& L)
     L.o_order = 2 * L.o_dinv;
     L.o_part = 3 * L.o_dinv;
     L.keep_bytes = L.o_part + (L.split ? align_up(4 * N * (kMaxParts + 1), 256) : 0);
-    L.sort_bytes = 0;
-    if (N > 0 &&
-        rocprim::radix_sort_pairs_desc(nullptr, L.sort_bytes, (uint32_t*)nullptr, (uint32_t*)nullptr,
-                                       (int32_t*)nullptr, (int32_t*)nullptr, (size_t)N, 0u, 32u,
-                                       (hipStream_t)0) != hipSuccess)
-        return RETEXO_E_HIP;
-    // scratch: keys_in, keys_out, ids_in, readback block, sort temp
-    L.s_kin = 0;
-    L.s_kout = align_up(4 * n1, 256);
-    L.s_ids = 2 * L.s_kout;
-    L.s_rb = 3 * L.s_kout;
-    L.s_tmp = L.s_rb + 256;
-    L.scratch_bytes = L.s_tmp + align_up((int64_t)L.sort_bytes, 256) + 256;
+    // scratch: readback block, and for larger graphs the pairs, counts and sums of the order sort
+    L.small = N <= kSmallRows;
+    const int64_t share = (N + kOrderBlocks - 1) / kOrderBlocks;
+    L.per_block = align_up(N > 32768 && share < 2048 ? 2048 : share, kOrderThreads);
+    L.blocks = (int)((N + L.per_block - 1) / L.per_block);
+    L.passes = 1;
+    while (L.passes * kOrderBits < 31 && nnz >> (L.passes * kOrderBits)) ++L.passes;       // digits that a degree can have
+    L.s_rb = 0;
+    L.s_pairs = 256;
+    const int64_t pairs = L.small ? 0 : align_up(8 * n1, 256);
+    L.s_counts = L.s_pairs + pairs * (L.passes > 2 ? 2 : 1);
+    L.s_stats = L.s_counts + (L.small ? 0 : 4ll * L.blocks * kOrderBins);
+    L.scratch_bytes = L.s_stats + (L.small ? 0 : align_up((int64_t)sizeof(RowStats) * L.blocks, 256)) + 256;
     return RETEXO_OK;
 }
 
@@ -165,21 +462,31 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
     p->dinv = (float*)((char*)keep + L.o_dinv);
     p->order = (int32_t*)((char*)keep + L.o_order);
     char* sc = (char*)scratch;
-    uint32_t* kin = (uint32_t*)(sc + L.s_kin);
-    uint32_t* kout = (uint32_t*)(sc + L.s_kout);
-    int32_t* ids = (int32_t*)(sc + L.s_ids);
     Readback* rb = (Readback*)(sc + L.s_rb);
-
-    RETEXO_HIP_TRY(hipMemsetAsync(rb, 0, sizeof(Readback), stream));
-    if (N > 0) {
-        degree_kernel<<<dim3((unsigned)((N + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
-            N, nnz, p->row_ptr, p->deg, p->dinv, kin, ids, &rb->bad);
-        size_t sort_bytes = L.sort_bytes;
-        RETEXO_HIP_TRY(rocprim::radix_sort_pairs_desc(sc + L.s_tmp, sort_bytes, kin, kout, ids, p->order, (size_t)N,
-                                                      0u, 32u, stream));
-        Thresholds th;
-        for (int i = 0; i < kPlanThresholdCount; ++i) th.t[i] = kPlanThresholds[i];
-        count_at_least<<<dim3(1), dim3(64), 0, stream>>>(N, kout, th, rb->counts);
+    Thresholds th;
+    for (int i = 0; i < kPlanThresholdCount; ++i) th.t[i] = kPlanThresholds[i];
+    if (N == 0) {
+        RETEXO_HIP_TRY(hipMemsetAsync(rb, 0, sizeof(Readback), stream));
+    } else if (L.small) {
+        small_order_kernel<<<dim3(1), dim3(kOrderThreads), 0, stream>>>((int)N, nnz, p->row_ptr, p->deg, p->dinv, p->order,
+                                                                        th, rb);
+    } else {
+        OrderArgs a;
+        a.N = N;
+        a.per_block = L.per_block;
+        a.passes = L.passes;
+        a.deg = p->deg;
+        a.pairs[0] = (uint2*)(sc + L.s_pairs);
+        a.pairs[1] = (uint2*)(sc + L.s_pairs + (L.passes > 2 ? align_up(8 * N, 256) : 0));
+        a.order = p->order;
+        a.counts = (uint32_t*)(sc + L.s_counts);
+        a.stats = (RowStats*)(sc + L.s_stats);
+        const dim3 grid((unsigned)L.blocks), block(kOrderThreads);
+        degree_kernel<<<grid, block, 0, stream>>>(a, nnz, p->row_ptr, p->deg, p->dinv, th);
+        for (int pass = 0; pass < L.passes; ++pass) {
+            if (pass > 0) order_count_kernel<<<grid, block, 0, stream>>>(a, pass);
+            order_move_kernel<<<grid, block, 0, stream>>>(a, pass, rb);
+        }
     }
     if (L.split) {
         // needs only the schedule order, so it runs before the host looks at the counts
