@@ -439,7 +439,7 @@ int plan_layout(int64_t N, int64_t nnz, unsigned flags, PlanLayout& L)
     L.keep_bytes = L.o_part + (L.split ? align_up(4 * N * (kMaxParts + 1), 256) : 0);
     // scratch: readback block, and for larger graphs the pairs, counts and sums of the order sort
     L.small = N <= kSmallRows;
-    const int64_t share = (N + kOrderBlocks - 1) / kOrderBlocks;
+    const int64_t share = (n1 + kOrderBlocks - 1) / kOrderBlocks;
     L.per_block = align_up(N > 32768 && share < 2048 ? 2048 : share, kOrderThreads);
     L.blocks = (int)((N + L.per_block - 1) / L.per_block);
     L.passes = 1;
