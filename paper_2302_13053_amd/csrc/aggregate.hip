@@ -72,6 +72,7 @@ struct AggArgs {
     int part_lo, part_hi;
     int first;             // first range of the walk: start from zero, write the self copy
     int last;              // last range: apply the mean / gcn scaling
+    uint32_t table_bytes;  // Z up to the end of its last row's last vector (grouped kernels, below 4 GiB)
     // edge softmax, kept for the backward pass (TRAIN kernels only):
     f32x4* save_stats;     // [N, HP] {row maximum, 1/sum, share of the sum with p > 0, share with p <= 0}
     float* save_pos;       // [N, ld_pos] the part of the aggregate that comes from entries with p > 0
@@ -215,16 +216,15 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
 // xor-shuffles when the row is done.  Same ownership rules as above: one wave
 // (or one workgroup for long rows) writes an output element, in a fixed order.
 // ---------------------------------------------------------------------------
-// One 64-edge tile of the grouped gather.  Each lane holds the byte offset of
-// one neighbour's row (and its gcn weight); step t hands entry t*G + g to group
-// g with a wave shuffle.  All loads of a batch of up to 8 steps are issued
-// before their FMAs, and nothing in the batch branches: lanes past the end of
-// a partial tile fetch a valid address (offset 0) and have the loaded values
-// replaced by zero; lanes past the row width fetch the last valid vector of
-// the slab and simply never store.
-//   OFF32: every row offset fits 32 bits, so the gather is base + 32-bit offset
-template <int LPG, bool FULL, bool WEIGHTED, bool OFF32>
-__device__ __forceinline__ void grouped_tile(const char* zbase, uint32_t colbytes, int64_t rowbytes,
+// One 64-edge tile of the grouped gather.  Each lane holds one neighbour: the byte offset of its row (kNoEntry past the
+// end of a partial tile) or, for tables of 4 GiB and more, its id, and its gcn weight.  Step t hands entry t*G + g to
+// group g with a wave shuffle.  All loads of a batch of up to 8 steps are issued before their FMAs, and nothing in the
+// batch branches.
+//   OFF32: every row offset fits 32 bits, so the table is a buffer and what does not exist fetches nothing (load_entry);
+//   otherwise lanes past the end fetch a valid address (id 0) and have the loaded values replaced by zero, and lanes past
+//   the row width fetch the last valid vector of the slab and never store
+template <int LPG, bool WEIGHTED, bool OFF32>
+__device__ __forceinline__ void grouped_tile(const char* zbase, table_t table, uint32_t colbytes, int64_t rowbytes,
                                              uint32_t my_off, int my_u, float my_w, int cnt, int g,
                                              float (&acc)[4])
 {
@@ -233,27 +233,24 @@ __device__ __forceinline__ void grouped_tile(const char* zbase, uint32_t colbyte
     constexpr int U = STEPS < 8 ? STEPS : 8;
 #pragma unroll
     for (int t0 = 0; t0 < STEPS; t0 += U) {
-        if (!FULL && t0 * G >= cnt) break;
+        if (t0 * G >= cnt) break;
         f32x4 z[U];
         float w[U];
 #pragma unroll
         for (int t = 0; t < U; ++t) {
             const int j = (t0 + t) * G + g;
             if constexpr (OFF32) {
-                const uint32_t off = (uint32_t)__shfl((int)my_off, j, 64) + colbytes;
-                z[t] = *reinterpret_cast<const f32x4*>(zbase + off);
+                z[t] = __builtin_bit_cast(f32x4, load_entry(table, (uint32_t)__shfl((int)my_off, j, 64), colbytes));
             } else {
                 const int u = __shfl(my_u, j, 64);
                 z[t] = *reinterpret_cast<const f32x4*>(zbase + (int64_t)u * rowbytes + colbytes);
-            }
-            if constexpr (WEIGHTED) w[t] = __shfl(my_w, j, 64);
-            if constexpr (!FULL) {
                 const bool ok = j < cnt;
                 z[t].x = ok ? z[t].x : 0.0f;
                 z[t].y = ok ? z[t].y : 0.0f;
                 z[t].z = ok ? z[t].z : 0.0f;
                 z[t].w = ok ? z[t].w : 0.0f;
             }
+            if constexpr (WEIGHTED) w[t] = __shfl(my_w, j, 64);
         }
 #pragma unroll
         for (int t = 0; t < U; ++t) {
@@ -302,10 +299,9 @@ __global__ __launch_bounds__(64 * NW) void agg_grouped_kernel(AggArgs a)
     const bool act = col < a.F;
     const bool writer = act && g == 0 && wave == 0;
     const int valid = (int)min((int64_t)4, a.F - col);
-    // lanes past the row width gather the slab's last valid vector instead (never stored)
-    const int64_t gcol = act ? col : ((a.F - 1) / 4) * 4;
     const char* zbase = reinterpret_cast<const char*>(a.Z);
-    const uint32_t colbytes = (uint32_t)(gcol * 4);
+    const table_t table = buffer_table(a.Z, OFF32 ? a.table_bytes : 0u);
+    const uint32_t colbytes = act ? (uint32_t)(col * 4) : OFF32 ? kNoEntry : (uint32_t)((a.F - 1) / 4 * 16);
     const int64_t rowbytes = a.ldz * 4;
     float* orow = a.out + (int64_t)v * a.ldo;
 
@@ -336,11 +332,8 @@ __global__ __launch_bounds__(64 * NW) void agg_grouped_kernel(AggArgs a)
             nxt_w = WEIGHTED ? (en < hi ? a.wsrc[nxt_u] : 0.0f) : 1.0f;
         }
         const int cnt = min(64, hi - base);
-        const uint32_t my_off = OFF32 ? (uint32_t)my_u * (uint32_t)rowbytes : 0u;
-        if (cnt == 64)
-            grouped_tile<LPG, true, WEIGHTED, OFF32>(zbase, colbytes, rowbytes, my_off, my_u, my_w, cnt, g, acc);
-        else
-            grouped_tile<LPG, false, WEIGHTED, OFF32>(zbase, colbytes, rowbytes, my_off, my_u, my_w, cnt, g, acc);
+        const uint32_t my_off = base + lane < hi ? (uint32_t)my_u * (uint32_t)rowbytes : kNoEntry;
+        grouped_tile<LPG, WEIGHTED, OFF32>(zbase, table, colbytes, rowbytes, my_off, my_u, my_w, cnt, g, acc);
     }
     // combine the lane groups, then the waves (in wave order)
 #pragma unroll
@@ -435,9 +428,10 @@ __global__ __launch_bounds__(64 * kLightWaves) void agg_rowgroup_kernel(AggArgs 
     const bool act = col < a.F;
     const bool writer = act && has_row;
     const int valid = (int)min((int64_t)4, a.F - col);
-    const int64_t gcol = act ? col : ((a.F - 1) / 4) * 4;
     const char* zbase = reinterpret_cast<const char*>(a.Z);
-    const uint32_t colbytes = (uint32_t)(gcol * 4);
+    constexpr bool BUFFER = OFF32 && WEIGHTED;
+    const table_t table = buffer_table(a.Z, BUFFER ? a.table_bytes : 0u);
+    const uint32_t colbytes = act ? (uint32_t)(col * 4) : BUFFER ? kNoEntry : 0u;
     const int64_t rowbytes = a.ldz * 4;
     float* orow = a.out + (int64_t)v * a.ldo;
 
@@ -468,7 +462,7 @@ __global__ __launch_bounds__(64 * kLightWaves) void agg_rowgroup_kernel(AggArgs 
     typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));      // 4-byte aligned 16-byte load
     int nxt_u[IPL];
     float nxt_w[IPL];
-    auto fetch_ids = [&](int first) {       // entries first + 4 li .. + 3 of this group's row; past its end: id 0
+    auto fetch_ids = [&](int first) {       // entries first + 4 li .. + 3 of this group's row; past its end: -1
         const int nb = first + IPL * li;
         if (nb + IPL <= len) {
 #pragma unroll
@@ -478,7 +472,7 @@ __global__ __launch_bounds__(64 * kLightWaves) void agg_rowgroup_kernel(AggArgs 
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < IPL; ++k) nxt_u[k] = nb + k < len ? a.col_idx[lo + nb + k] : 0;
+            for (int k = 0; k < IPL; ++k) nxt_u[k] = nb + k < len ? a.col_idx[lo + nb + k] : -1;
         }
         if constexpr (WEIGHTED) {
 #pragma unroll
@@ -495,7 +489,7 @@ __global__ __launch_bounds__(64 * kLightWaves) void agg_rowgroup_kernel(AggArgs 
         for (int k = 0; k < IPL; ++k) {
             my_u[k] = nxt_u[k];
             my_w[k] = WEIGHTED ? nxt_w[k] : 0.0f;
-            my_off[k] = OFF32 ? (uint32_t)my_u[k] * (uint32_t)rowbytes : 0u;
+            my_off[k] = my_u[k] >= 0 ? (uint32_t)my_u[k] * (uint32_t)rowbytes : kNoEntry;
         }
         fetch_ids(s0 + BLOCK);              // the next block, a whole block ahead of its use
         // steps of U entries; the gathers of step st + 1 are issued before those of step st are added up, so a
@@ -503,27 +497,26 @@ __global__ __launch_bounds__(64 * kLightWaves) void agg_rowgroup_kernel(AggArgs 
         constexpr int T = BLOCK / U;
         f32x4 z[2][U];
         float w[2][U];
-        // e0: first entry of the step in the block, c0: the same counted from the start of the row's share.  Lanes
-        // whose group has no such entry (a shorter row of the bundle, or columns past the row width) issue no
-        // load at all: the kernel keeps the address units busy 96 % of its time, and a sixth of the gathers of a
-        // bundle are such fillers.
+        // e0: first entry of the step in the block, c0: the same counted from the start of the row's share.  What a
+        // group does not have (a shorter row of the bundle, columns past the row width) is not fetched: the kernel keeps
+        // the address units busy 96 % of its time, and a sixth of the gathers of a bundle would be such fillers.  With
+        // weights, whose gathers and permutes fill the vector units too, it is an offset past the table's end (F = 256
+        // gcn_sym on the Reddit-shaped graph 9.42 -> 8.84 ms); without, lanes that are switched off are the cheaper
+        // (F = 602 mean 14.57 ms, 14.67 as offsets).
         auto issue = [&](int e0, int c0, f32x4 (&zz)[U], float (&ww)[U]) {
             const bool all = act && c0 + U <= minlen && has_row;       // no filler in this step for this lane
 #pragma unroll
             for (int t = 0; t < U; ++t) {
                 const int e = e0 + t;              // entry of the block: lane e / IPL, component e % IPL
-                const bool ok = all || (act && c0 + t < len);
-                const char* src;
-                if constexpr (OFF32) {
-                    const uint32_t off =
-                        (uint32_t)__builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), (int)my_off[e % IPL]) + colbytes;
-                    src = zbase + off;
+                const int from = OFF32 ? (int)my_off[e % IPL] : my_u[e % IPL];
+                const int at = __builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), from);
+                if constexpr (BUFFER) {
+                    zz[t] = __builtin_bit_cast(f32x4, load_entry(table, (uint32_t)at, colbytes));
                 } else {
-                    const int u = __builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), my_u[e % IPL]);
-                    src = zbase + (int64_t)u * rowbytes + colbytes;
+                    const char* src = OFF32 ? zbase + ((uint32_t)at + colbytes) : zbase + (int64_t)at * rowbytes + colbytes;
+                    zz[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    if (all || (act && c0 + t < len)) zz[t] = *reinterpret_cast<const f32x4*>(src);
                 }
-                zz[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                if (ok) zz[t] = *reinterpret_cast<const f32x4*>(src);
                 if constexpr (WEIGHTED)
                     ww[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), __float_as_int(my_w[e % IPL])));
             }
@@ -1749,6 +1742,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
             a.last = k == parts - 1;
             const bool wtd = a.wsrc != nullptr;
             const bool off32 = (N * c.ldz + c.F) * 4 < (1ll << 32) && !opt.wide_offsets;
+            a.table_bytes = off32 ? (uint32_t)(((N - 1) * c.ldz + align_up(c.F, 4)) * 4) : 0u;
             if (narrow == 32) dispatch_grouped<8>(a, n_heavy, N, wtd, off32, stream);
             else if (narrow == 64) dispatch_grouped<16>(a, n_heavy, N, wtd, off32, stream);
             else dispatch_grouped<32>(a, n_heavy, N, wtd, off32, stream);

@@ -20,7 +20,6 @@ namespace {
 
 enum { FMT_BF16 = RETEXO_STORE_BF16, FMT_FP16 = RETEXO_STORE_FP16 };
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));    // sixteen bytes of stored elements, kept as integers
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 template <int FMT>
@@ -52,6 +51,23 @@ __device__ __forceinline__ void decode8(const u32x4& raw, float (&v)[8])
     }
 }
 
+// acc += w * the eight stored elements; without weights IEEE half still goes through the multiply-add, which converts on
+// the way (v_fma_mix_f32; a conversion and an addition otherwise): `w` is then one, held in a register on purpose
+template <int FMT, bool WEIGHTED>
+__device__ __forceinline__ void add8(const u32x4& raw, float w, float (&acc)[8])
+{
+    float z[8];
+    decode8<FMT>(raw, z);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = WEIGHTED || FMT == FMT_FP16 ? fmaf(w, z[k], acc[k]) : acc[k] + z[k];
+}
+__device__ __forceinline__ float register_one()
+{
+    float one = 1.0f;
+    asm("" : "+v"(one));
+    return one;
+}
+
 template <int FMT>
 __device__ __forceinline__ uint16_t encode1(float x)
 {
@@ -67,14 +83,29 @@ __device__ __forceinline__ uint16_t encode1(float x)
     }
 }
 
-template <int FMT>
+// One row per wave (rows in turn), VEC consecutive columns per lane: 16-byte reads and 8-byte writes where rows allow
+// them.  Bound by its bytes: Reddit-shaped table, 232,965 x 602, 344 -> 149 us = 5.6 TB/s
+// (one element per thread, with a division, before).
+template <int FMT, int VEC>
 __global__ __launch_bounds__(256) void store_rows_kernel(int64_t N, int64_t F, const float* __restrict__ src,
                                                           int64_t lds, uint16_t* __restrict__ dst, int64_t ldd)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= N * F) return;
-    const int64_t r = i / F, c = i % F;
-    dst[r * ldd + c] = encode1<FMT>(src[r * lds + c]);
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * 4;
+    for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < N; r += waves) {
+        const float* from = src + r * lds;
+        uint16_t* to = dst + r * ldd;
+        for (int64_t c = lane * VEC; c < F; c += 64 * VEC) {
+            if (VEC == 4 && c + 4 <= F) {
+                const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(from + c));
+                const u32x2 y = {(uint32_t)encode1<FMT>(x.x) | (uint32_t)encode1<FMT>(x.y) << 16,
+                                 (uint32_t)encode1<FMT>(x.z) | (uint32_t)encode1<FMT>(x.w) << 16};
+                *reinterpret_cast<u32x2*>(to + c) = y;
+            } else {
+                for (int64_t k = c; k < c + VEC && k < F; ++k) to[k] = encode1<FMT>(from[k]);
+            }
+        }
+    }
 }
 
 // row loads of E stored elements per lane (E = 8: one 16-byte load; 4: one 8-byte load; 1: one 2-byte load)
@@ -154,6 +185,7 @@ struct StoredArgs {
     int64_t n_rows;
     int part_lo, part_hi;
     int first, last;
+    uint32_t table_bytes;    // up to the end of the last row's last vector (narrow slabs: below 4 GiB)
 };
 
 // ---------------------------------------------------------------------------
@@ -264,13 +296,21 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void stored_line
 // ---------------------------------------------------------------------------
 // sum / mean / gcn_sym on 64-column slabs: one row per 8-lane group, eight elements per lane, so a
 // gathered row-slab is one 128-byte line.  Launched once per group of source-id ranges: the running
-// sum is kept in `out` between launches.  Branch-free inner loop: lanes past the end of a row gather
-// the row's first neighbour with weight zero.
+// sum is kept in `out` between launches.
+//
+// Bound by the address units and, with two instructions per element, nearly as much by the vector units.  So an
+// entry that a lane's row does not have is an offset past the table's end (a sixth of a bundle's gathers are such fillers),
+// which costs neither a fetch nor an instruction (zero bits decode to +0 in both formats), sums without weights hand round
+// no weights, and the next step's gathers are issued before the current ones are added up.
+// Reddit-shaped graph, 602 columns, bf16, four ranges: 2.17 -> 1.94 ms per range, long rows 0.335 -> 0.297, the whole mean
+// 10.36 -> 9.05 ms with the store; gcn_sym 13.0 -> 11.9.  What is left is the L2 requests and misses of the gathers (18.8 TB/s; the
+// float32 kernel 20.1) and the running sums, twice its bytes per slab.  Steps of eight entries: the same within 0.5 %, in 117
+// registers instead of 85.
 // ---------------------------------------------------------------------------
 template <int FMT, bool WEIGHTED>
 __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(StoredArgs a)
 {
-    constexpr int LPG = 8, G = 64 / LPG, U = 8;
+    constexpr int LPG = 8, G = 64 / LPG, U = 4;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t bundles = (a.row_count + G - 1) / G;
@@ -294,22 +334,17 @@ __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(Store
         }
     }
     const int len = hi - lo;
-    int maxlen = len, minlen = len;
+    int maxlen = len;
 #pragma unroll
-    for (int m = LPG; m < 64; m <<= 1) {
-        maxlen = max(maxlen, __shfl_xor(maxlen, m, 64));
-        minlen = min(minlen, __shfl_xor(minlen, m, 64));
-    }
+    for (int m = LPG; m < 64; m <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, m, 64));
     maxlen = __builtin_amdgcn_readfirstlane(maxlen);
-    minlen = __builtin_amdgcn_readfirstlane(minlen);
 
     const int64_t col = (int64_t)slab * 64 + li * 8;
     const bool act = col < a.F;
     const bool writer = act && has_row;
     const int valid = (int)min((int64_t)8, a.F - col);
-    const int64_t gcol = act ? col : 0;
-    const char* zbase = reinterpret_cast<const char*>(a.Z);
-    const uint32_t colbytes = (uint32_t)(gcol * 2);
+    const table_t table = buffer_table(a.Z, a.table_bytes);
+    const uint32_t colbytes = act ? (uint32_t)(col * 2) : kNoEntry;
     const uint32_t rowbytes = (uint32_t)(a.ldz * 2);
     float* orow = a.out + (int64_t)v * a.ldo;
 
@@ -354,58 +389,47 @@ __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(Store
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < IPL; ++k) nxt_u[k] = nb + k < len ? a.col_idx[lo + nb + k] : 0;
+            for (int k = 0; k < IPL; ++k) nxt_u[k] = nb + k < len ? a.col_idx[lo + nb + k] : -1;
         }
+        if constexpr (WEIGHTED) {
 #pragma unroll
-        for (int k = 0; k < IPL; ++k) nxt_w[k] = nb + k < len ? (WEIGHTED ? a.wsrc[nxt_u[k]] : 1.0f) : 0.0f;
+            for (int k = 0; k < IPL; ++k) nxt_w[k] = nb + k < len ? a.wsrc[nxt_u[k]] : 0.0f;
+        }
     };
+    const float one = WEIGHTED ? 1.0f : register_one();
     fetch_ids(0);
     for (int s0 = 0; s0 < maxlen; s0 += BLOCK) {
         uint32_t my_off[IPL];
         float my_w[IPL];
 #pragma unroll
         for (int k = 0; k < IPL; ++k) {
-            my_off[k] = (uint32_t)nxt_u[k] * rowbytes;
-            my_w[k] = nxt_w[k];
+            my_off[k] = nxt_u[k] >= 0 ? (uint32_t)nxt_u[k] * rowbytes : kNoEntry;
+            my_w[k] = WEIGHTED ? nxt_w[k] : 0.0f;
         }
         fetch_ids(s0 + BLOCK);
+        constexpr int T = BLOCK / U;
+        u32x4 raw[2][U];
+        float w[2][U];
+        // e0: first entry of the step in the block
+        auto issue = [&](int e0, u32x4 (&rr)[U], float (&ww)[U]) {
 #pragma unroll
-        for (int q = 0; q < IPL; ++q) {
-            const int c0 = s0 + q * LPG;
-            if (c0 >= maxlen) break;                     // (uniform)
-            const bool full = c0 + LPG <= minlen;        // every group still has LPG entries: nothing to mask
-#pragma unroll
-            for (int i0 = 0; i0 < LPG; i0 += U) {
-                u32x4 raw[U];
-                float w[U];
-#pragma unroll
-                for (int t = 0; t < U; ++t) {
-                    const int e = q * LPG + i0 + t;
-                    const uint32_t off =
-                        (uint32_t)__builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), (int)my_off[e % IPL]) + colbytes;
-                    raw[t] = *reinterpret_cast<const u32x4*>(zbase + off);
-                    w[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), __float_as_int(my_w[e % IPL])));
-                }
-                if (!full) {
-                    // entries past the end of this group's row gathered row 0: clear their bits (both formats
-                    // decode zero bits to +0), so that nothing of an unrelated row can reach the sum
-#pragma unroll
-                    for (int t = 0; t < U; ++t) {
-                        const uint32_t keep = c0 + i0 + t < len ? 0xffffffffu : 0u;
-                        raw[t].x &= keep;
-                        raw[t].y &= keep;
-                        raw[t].z &= keep;
-                        raw[t].w &= keep;
-                    }
-                }
-#pragma unroll
-                for (int t = 0; t < U; ++t) {
-                    float z[8];
-                    decode8<FMT>(raw[t], z);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) acc[k] = fmaf(w[t], z[k], acc[k]);
-                }
+            for (int t = 0; t < U; ++t) {
+                const int e = e0 + t;
+                rr[t] = load_entry(table, (uint32_t)__builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), (int)my_off[e % IPL]), colbytes);
+                if constexpr (WEIGHTED)
+                    ww[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(gaddr + 4 * (e / IPL), __float_as_int(my_w[e % IPL])));
+                else
+                    ww[t] = one;
             }
+        };
+        issue(0, raw[0], w[0]);
+#pragma unroll
+        for (int st = 0; st < T; ++st) {
+            const int c0 = s0 + st * U;
+            if (c0 >= maxlen) break;                     // (uniform)
+            if (st + 1 < T && c0 + U < maxlen) issue((st + 1) * U, raw[(st + 1) & 1], w[(st + 1) & 1]);
+#pragma unroll
+            for (int t = 0; t < U; ++t) add8<FMT, WEIGHTED>(raw[st & 1][t], w[st & 1][t], acc);
         }
     }
     if (!writer) return;
@@ -456,46 +480,37 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_grouped_kernel(Stored
     const int64_t col = (int64_t)slab * 64 + li * 8;
     const bool act = col < a.F;
     const int valid = (int)min((int64_t)8, a.F - col);
-    const char* zbase = reinterpret_cast<const char*>(a.Z);
-    const uint32_t colbytes = (uint32_t)((act ? col : 0) * 2);
+    const table_t table = buffer_table(a.Z, a.table_bytes);
+    const uint32_t colbytes = act ? (uint32_t)(col * 2) : kNoEntry;
     const uint32_t rowbytes = (uint32_t)(a.ldz * 2);
     const int gaddr = (lane - li) * 4;
 
     float acc[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+    // the ids (and weights) of a wave's next tile are requested before the current tile's rows
+    const float one = WEIGHTED ? 1.0f : register_one();
+    int nxt_u = 0;
+    float nxt_w = 0.0f;
+    auto fetch_id = [&](int e) {
+        nxt_u = e < hi ? a.col_idx[e] : -1;
+        if constexpr (WEIGHTED) nxt_w = e < hi ? a.wsrc[nxt_u] : 0.0f;
+    };
+    fetch_id(lo + 64 * wave + lane);
     for (int base = lo + 64 * wave; base < hi; base += 64 * kHeavyWaves) {
-        const int e = base + lane;
-        const bool ok = e < hi;
-        const int my_u = ok ? a.col_idx[e] : 0;
-        const float my_w = ok ? (WEIGHTED ? a.wsrc[my_u] : 1.0f) : 0.0f;
-        const uint32_t my_off = (uint32_t)my_u * rowbytes;
-        const bool full = base + 64 <= hi;
+        const uint32_t my_off = nxt_u >= 0 ? (uint32_t)nxt_u * rowbytes : kNoEntry;
+        const float my_w = nxt_w;
+        fetch_id(base + 64 * kHeavyWaves + lane);
         u32x4 raw[U];
         float w[U];
 #pragma unroll
         for (int t = 0; t < U; ++t) {
-            const uint32_t off = (uint32_t)__builtin_amdgcn_ds_bpermute(gaddr + 4 * t, (int)my_off) + colbytes;
-            raw[t] = *reinterpret_cast<const u32x4*>(zbase + off);
-            w[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(gaddr + 4 * t, __float_as_int(my_w)));
-        }
-        if (!full) {
-#pragma unroll
-            for (int t = 0; t < U; ++t) {
-                const uint32_t keep = base + (lane - li) + t < hi ? 0xffffffffu : 0u;
-                raw[t].x &= keep;
-                raw[t].y &= keep;
-                raw[t].z &= keep;
-                raw[t].w &= keep;
-            }
+            raw[t] = load_entry(table, (uint32_t)__builtin_amdgcn_ds_bpermute(gaddr + 4 * t, (int)my_off), colbytes);
+            if constexpr (WEIGHTED) w[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(gaddr + 4 * t, __float_as_int(my_w)));
+            else w[t] = one;
         }
 #pragma unroll
-        for (int t = 0; t < U; ++t) {
-            float z[8];
-            decode8<FMT>(raw[t], z);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) acc[k] = fmaf(w[t], z[k], acc[k]);
-        }
+        for (int t = 0; t < U; ++t) add8<FMT, WEIGHTED>(raw[t], w[t], acc);
     }
     // the eight groups of a wave, then the eight waves
 #pragma unroll
@@ -1005,6 +1020,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     a.part_hi = 0;
     a.first = 1;
     a.last = 1;
+    a.table_bytes = 0;
 
     const int64_t n_heavy = long_rows(p, F, true);
 
@@ -1021,6 +1037,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     if (opt.slab_cols > 64) narrow = false;
     if (opt.slab_cols == 64 && linear_sum && wide && off32) narrow = true;
     if (narrow) {
+        a.table_bytes = (uint32_t)(((N - 1) * c.ldz + align_up(F, 8)) * 2);
         a.nslab = (int)((F + 63) / 64);
         int parts = (int)opt.parts;
         if (parts < 0) {
@@ -1126,11 +1143,12 @@ int launch_store_rows(int storage, int64_t N, int64_t F, const float* src, int64
                       hipStream_t stream)
 {
     if (N == 0 || F == 0) return RETEXO_OK;
-    const dim3 grid((unsigned)((N * F + 255) / 256));
-    if (storage == RETEXO_STORE_BF16)
-        store_rows_kernel<FMT_BF16><<<grid, dim3(256), 0, stream>>>(N, F, src, lds, (uint16_t*)dst, ldd);
-    else
-        store_rows_kernel<FMT_FP16><<<grid, dim3(256), 0, stream>>>(N, F, src, lds, (uint16_t*)dst, ldd);
+    const int64_t blocks = (N + 3) / 4;
+    const dim3 grid((unsigned)(blocks < 16384 ? blocks : 16384));
+    const bool wide = lds % 4 == 0 && ldd % 4 == 0 && (uintptr_t)src % 16 == 0 && (uintptr_t)dst % 8 == 0;
+    auto go = [&](auto kernel) { kernel<<<grid, dim3(256), 0, stream>>>(N, F, src, lds, (uint16_t*)dst, ldd); };
+    if (storage == RETEXO_STORE_BF16) { if (wide) go(store_rows_kernel<FMT_BF16, 4>); else go(store_rows_kernel<FMT_BF16, 1>); }
+    else { if (wide) go(store_rows_kernel<FMT_FP16, 4>); else go(store_rows_kernel<FMT_FP16, 1>); }
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
     return RETEXO_OK;
 }

@@ -62,6 +62,21 @@ __device__ __forceinline__ void store_row(float* p, const float (&v)[VEC], int v
 template <typename T>
 __device__ __forceinline__ T ldg_stream(const T* p) { return __builtin_nontemporal_load(p); }
 
+// A table below 4 GiB as a buffer: a 16-byte load at an offset past its end fetches nothing and returns zeros.  So an entry
+// that does not exist is an offset (kNoEntry, which stays the largest under the saturating addition of a column offset)
+// and costs neither a comparison nor a cleared register in the loops that gather.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr uint32_t kNoEntry = 0xffffffffu;
+typedef __amdgpu_buffer_rsrc_t table_t;
+__device__ __forceinline__ table_t buffer_table(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 load_entry(table_t t, uint32_t row, uint32_t col)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(t, __builtin_elementwise_add_sat(row, col), 0, 0);
+}
+
 __device__ __forceinline__ float wave_max(float x)
 {
 #pragma unroll
