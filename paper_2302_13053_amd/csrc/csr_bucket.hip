@@ -18,11 +18,11 @@
 //            (both moves stage a tile in LDS ordered by destination, reserve the destination ranges
 //             with one atomic per destination and tile, and write runs)
 //   sort     one workgroup per bucket: entries counted per row, every row given a number of column
-//            bins proportional to its length (so that a bin holds 4 to 8 entries whatever the
+//            bins proportional to its length (so that a bin holds 1 or 2 entries whatever the
 //            degree), LDS counting split into those bins, rank by comparison inside a bin,
 //            drop repeats, count the kept entries per row;
-//            a bucket that does not fit LDS is worked through in key ranges, the ranges split
-//            until each fits (a single long row, a clustered row range, many repeats: all end)
+//            a bucket that does not fit LDS is marked in a bit map or worked through in key ranges, the ranges
+//            split until each fits (a single long row, a clustered row range, many repeats: all end)
 //   total    one workgroup: prefix sums over the buckets' entry counts -> nnz
 //   emit     one workgroup per bucket: row offsets of its rows, columns to their final place
 //            (nothing is written when an id was out of range or the capacity is too small)
@@ -41,7 +41,7 @@ constexpr int kMaxHistBlocks = 256;
 constexpr int kItemsPerTile = 4096;      // pairs per part1 tile (two entries each)
 constexpr int kTileEntries = 8192;       // entries per part2 tile
 constexpr int kGroupBuckets = 256;       // buckets per group
-constexpr int kMaxGroups = 1024;
+constexpr int kMaxGroups = 768;           // (part1's tables and its tile fit a CU twice)
 constexpr int kMaxBuckets = kGroupBuckets * kMaxGroups;
 constexpr int64_t kMaxEntries = 447000000;   // more were never built this way: they take the sorted keys
 constexpr int kBucketMax = 10240;        // entries a bucket can hold in LDS (10 per thread)
@@ -49,7 +49,7 @@ constexpr int kTargetMax = 7168;         // entries a bucket is filled to in a l
 constexpr int kTargetMin = 1024;         // ... and in a small one
 constexpr int kTargetBuckets = 160;      // buckets a graph is spread over before they are filled further
 constexpr int kRowSpan = 1024;           // rows per bucket at most (one per thread of the sort)
-constexpr int kSortBins = kBucketMax / 4 + kRowSpan;   // bins of the LDS split: a row of c entries gets < max(1, c/4)
+constexpr int kSortBins = kBucketMax + kRowSpan;         // bins of the LDS split: a row of c entries gets max(1, c/2 to c)
 constexpr int kStack = 400;              // key ranges waiting in an oversized bucket (6 levels x 63 + 1)
 
 struct BucketHeader {       // start of the workspace
@@ -60,6 +60,7 @@ struct BucketHeader {       // start of the workspace
     uint32_t n_groups;
     uint32_t part2_tiles;
     uint32_t internal;      // a construction invariant failed (never expected)
+    uint32_t one_word;      // the rows of every group are few enough: part1's entries take one word (plan)
 };
 
 
@@ -106,10 +107,10 @@ __device__ __forceinline__ int find_segment(const uint32_t* table, int n, uint32
     return lo;
 }
 
-// arr[idx] += 1 for every lane with `active` set.  When all of them name the same element (a long row, a
+// arr[idx] += one for every lane with `active` set.  When all of them name the same element (a long row, a
 // clustered range) the wave adds their number once instead of queueing up on one LDS address.
 // Call with the whole wave (the loop around it must be uniform per wave).
-__device__ __forceinline__ void lds_count(uint32_t* arr, uint32_t idx, bool active)
+__device__ __forceinline__ void lds_count(uint32_t* arr, uint32_t idx, bool active, uint32_t one = 1u)
 {
     const uint64_t act = __ballot(active);
     if (!act) return;
@@ -118,28 +119,49 @@ __device__ __forceinline__ void lds_count(uint32_t* arr, uint32_t idx, bool acti
     const uint32_t first = __shfl(idx, leader, 64);
     const uint64_t same = __ballot(active && idx == first);
     if (same == act) {
-        if (lane == leader) atomicAdd(&arr[first], (uint32_t)__popcll(act));
+        if (lane == leader) atomicAdd(&arr[first], (uint32_t)__popcll(act) * one);
     } else if (active) {
-        atomicAdd(&arr[idx], 1u);
+        atomicAdd(&arr[idx], one);
     }
 }
 
-// item i of the input: pair i for i < n_pairs, afterwards the self-loop of node i - n_pairs.
-// Returns the number of entries it yields (0, 1 or 2) as (r0,c0), (r1,c1).
-__device__ __forceinline__ int item_entries(int64_t i, int64_t n_pairs, const int32_t* __restrict__ src,
-                                            const int32_t* __restrict__ dst, int64_t N, bool& bad,
-                                            uint32_t& r0, uint32_t& c0, uint32_t& r1, uint32_t& c1)
-{
-    if (i < n_pairs) {
-        const uint32_t u = (uint32_t)src[i], v = (uint32_t)dst[i];
-        if (u >= (uint64_t)N || v >= (uint64_t)N) { bad = true; return 0; }
-        if (u == v) return 0;                       // self pairs are dropped; self-loops come from the items below
-        r0 = u; c0 = v; r1 = v; c1 = u;
-        return 2;
+// Items i, i + kThreads, ... (COUNT of them, those below `end`): pair i for i < n_pairs, afterwards the self-loop of node
+// i - n_pairs.  All loads are issued before the first is used.
+template <int COUNT>
+struct Items {
+    uint32_t u[COUNT], v[COUNT];
+    uint32_t entries;                                    // two bits per item: 0, 1 or 2 entries (u,v), (v,u)
+    __device__ __forceinline__ void load(int64_t i0, int64_t end, int64_t n_pairs, const int32_t* __restrict__ src,
+                                         const int32_t* __restrict__ dst)
+    {
+#pragma unroll
+        for (int t = 0; t < COUNT; ++t) {
+            const int64_t i = i0 + t * kThreads;
+            const bool pair = i < end && i < n_pairs;
+            u[t] = pair ? (uint32_t)src[i] : 0u;
+            v[t] = pair ? (uint32_t)dst[i] : 0u;
+        }
     }
-    r0 = c0 = (uint32_t)(i - n_pairs);
-    return 1;
-}
+    __device__ __forceinline__ void look(int64_t i0, int64_t end, int64_t n_pairs, int64_t N, bool& bad)
+    {
+        entries = 0u;
+#pragma unroll
+        for (int t = 0; t < COUNT; ++t) {
+            const int64_t i = i0 + t * kThreads;
+            if (i >= end) continue;
+            if (i >= n_pairs) {
+                u[t] = v[t] = (uint32_t)(i - n_pairs);
+                entries |= 1u << (2 * t);
+            } else if (u[t] >= (uint64_t)N || v[t] >= (uint64_t)N) {
+                bad = true;
+            } else if (u[t] != v[t]) {                   // self pairs are dropped
+                entries |= 2u << (2 * t);
+            }
+        }
+    }
+    __device__ __forceinline__ bool first(int t) const { return (entries >> (2 * t)) & 3u; }
+    __device__ __forceinline__ bool second(int t) const { return (entries >> (2 * t)) & 2u; }
+};
 
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void hist_kernel(
@@ -152,11 +174,17 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(
     const int64_t begin = (int64_t)blockIdx.x * items_per_block;
     const int64_t end = begin + items_per_block < n_items ? begin + items_per_block : n_items;
     bool bad = false;
-    for (int64_t i = begin + threadIdx.x; i < end; i += kThreads) {
-        uint32_t r0, c0, r1, c1;
-        const int k = item_entries(i, n_pairs, src, dst, N, bad, r0, c0, r1, c1);
-        if (k >= 1) atomicAdd(&hist[r0 >> s], 1u);
-        if (k == 2) atomicAdd(&hist[r1 >> s], 1u);
+    // (one workgroup per CU, so the pairs in flight are what hides the memory: one per thread 168 us on the Reddit-shaped
+    // graph, eight 105)
+    Items<8> it;
+    for (int64_t i0 = begin + threadIdx.x; i0 < end; i0 += 8 * kThreads) {
+        it.load(i0, end, n_pairs, src, dst);
+        it.look(i0, end, n_pairs, N, bad);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (it.first(t)) atomicAdd(&hist[it.u[t] >> s], 1u);
+            if (it.second(t)) atomicAdd(&hist[it.v[t] >> s], 1u);
+        }
     }
     if (bad) atomicOr(&hdr->bad_id, 1u);
     __syncthreads();
@@ -179,7 +207,6 @@ __global__ __launch_bounds__(256) void colsum_kernel(int nblocks, int nbins, con
 }
 
 struct PlanArrays {
-    uint32_t* bin_off;        // [nbins + 1] entries before each bin
     uint32_t* bucket_bin0;    // [n_buckets + 1] first bin of each bucket
     uint32_t* bucket_off;     // [n_buckets + 1] entries before each bucket
     uint32_t* bucket_cursor;  // [n_buckets] part2's write positions
@@ -222,7 +249,7 @@ __device__ __forceinline__ bool starts_bucket(int bin, uint32_t off, const uint3
     return off - first + cnt > (uint32_t)kBucketMax;
 }
 
-__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, uint32_t target, uint32_t per_entry, const uint32_t* __restrict__ bin_count,
+__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, int group_bins, uint32_t target, uint32_t per_entry, const uint32_t* __restrict__ bin_count,
                                                         PlanArrays a, uint32_t bucket_capacity, BucketHeader* hdr)
 {
     __shared__ uint32_t cnts[kMaxBins];            // the bin counts, read three times
@@ -241,12 +268,10 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
         uint32_t o = off;
         for (int b = b0; b < b1; ++b) {
             const uint32_t cnt = cnts[b];
-            a.bin_off[b] = o;
             starts += starts_bucket(b, o, cnts, span_bins, target, per_entry) ? 1u : 0u;
             o += cnt;
         }
     }
-    if (threadIdx.x == 0) a.bin_off[nbins] = total;
     uint32_t n_buckets;
     uint32_t id = block_scan_excl<kWaves>(starts, sc, n_buckets);
     if (n_buckets > bucket_capacity) {             // cannot happen: the host sized the arrays for the worst case
@@ -274,14 +299,15 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
         hdr->n_groups = n_groups;
     }
     __syncthreads();                               // the bucket arrays are complete
-    // one group per thread (n_groups <= kMaxGroups = kThreads)
+    // one group per thread (n_groups <= kMaxGroups <= kThreads)
     const uint32_t g = threadIdx.x;
-    uint32_t tiles = 0;
+    uint32_t tiles = 0, bins_here = 0;
     if (g < n_groups) {
         const uint32_t first = g * kGroupBuckets;
         const uint32_t last = first + kGroupBuckets < n_buckets ? first + kGroupBuckets : n_buckets;
         const uint32_t lo = a.bucket_off[first], hi = a.bucket_off[last];
         a.group_bin0[g] = a.bucket_bin0[first];
+        bins_here = a.bucket_bin0[last] - a.bucket_bin0[first];
         a.group_off[g] = lo;
         a.group_cursor[g] = lo;
         tiles = (hi - lo + kTileEntries - 1) / kTileEntries;
@@ -289,11 +315,13 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
     uint32_t n_tiles;
     const uint32_t t0 = block_scan_excl<kWaves>(tiles, sc, n_tiles);
     if (g < n_groups) a.group_tile0[g] = t0;
+    const int wide = __syncthreads_or(bins_here > (uint32_t)group_bins);
     if (threadIdx.x == 0) {
         a.group_bin0[n_groups] = (uint32_t)nbins;
         a.group_off[n_groups] = total;
         a.group_tile0[n_groups] = n_tiles;
         hdr->part2_tiles = n_tiles;
+        hdr->one_word = wide ? 0u : 1u;
     }
     __syncthreads();                               // the group arrays are complete
     // A group other than the last holds 256 buckets, i.e. at least 256 bins, so a block of 16 bins meets at most
@@ -310,21 +338,30 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
 }
 
 // ---------------------------------------------------------------------------
-// part1: the entries of one tile of items go to their groups as (row, col) pairs.
+// part1: the entries of one tile of items go to their groups, as (row, col) pairs or, where every group spans few enough
+// rows, as one word (row - first row of the group) << cbits | col.  Bound by its bytes and part2's, which reads them: the
+// Reddit-shaped graph's 117 million entries 415 -> 296 us here and 462 -> 312 there (372 and 409 with two words: the rest
+// is all loads of a tile issued before the first is used).
 __global__ __launch_bounds__(kThreads) void part1_kernel(
     int64_t n_pairs, const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t N, int64_t n_items, int s,
-    const uint16_t* __restrict__ coarse_group, uint32_t* group_cursor, uint32_t* __restrict__ rows_out,
+    int cbits, const uint16_t* __restrict__ coarse_group, const uint32_t* __restrict__ group_bin0, uint32_t* group_cursor, uint32_t* __restrict__ rows_out,
     uint32_t* __restrict__ cols_out, const BucketHeader* hdr)
 {
     constexpr int IPT = kItemsPerTile / kThreads;          // items per thread
     __shared__ uint32_t toff[kMaxGroups + 1];
     __shared__ uint32_t base[kMaxGroups];
+    __shared__ uint32_t first_row[kMaxGroups];
     __shared__ uint32_t srow[2 * kItemsPerTile], scol[2 * kItemsPerTile];
     __shared__ uint32_t sc[2 * kWaves + 1];
     __shared__ uint16_t coarse[kMaxBins / 16];
     if (hdr->bad_id || hdr->internal) return;
+    const int64_t i0 = (int64_t)blockIdx.x * kItemsPerTile + threadIdx.x;
+    Items<IPT> it;
+    it.load(i0, n_items, n_pairs, src, dst);
     const int G = (int)hdr->n_groups;
+    const bool one_word = hdr->one_word != 0;
     for (int i = threadIdx.x; i <= G; i += kThreads) toff[i] = 0u;
+    if ((int)threadIdx.x < G) first_row[threadIdx.x] = group_bin0[threadIdx.x] << s;
     for (int c = threadIdx.x; c < kMaxBins / 16; c += kThreads) coarse[c] = coarse_group[c];
     __syncthreads();
     // the group of a bin: that of its block's first bin, or the next one from the recorded offset on
@@ -337,21 +374,20 @@ __global__ __launch_bounds__(kThreads) void part1_kernel(
     constexpr uint32_t kNone = 0xffffffffu;
     uint32_t er[2 * IPT], ec[2 * IPT], erank[2 * IPT], eg[2 * IPT];
     bool bad = false;
+    it.look(i0, n_items, n_pairs, N, bad);
 #pragma unroll
     for (int k = 0; k < IPT; ++k) {
-        const int64_t i = (int64_t)blockIdx.x * kItemsPerTile + k * kThreads + threadIdx.x;
-        uint32_t r0 = 0, c0 = 0, r1 = 0, c1 = 0;
-        const int cnt = i < n_items ? item_entries(i, n_pairs, src, dst, N, bad, r0, c0, r1, c1) : 0;
-        er[2 * k] = r0; ec[2 * k] = c0; er[2 * k + 1] = r1; ec[2 * k + 1] = c1;
+        er[2 * k] = ec[2 * k + 1] = it.u[k];
+        ec[2 * k] = er[2 * k + 1] = it.v[k];
         eg[2 * k] = eg[2 * k + 1] = kNone;
         erank[2 * k] = erank[2 * k + 1] = 0u;
-        if (cnt >= 1) {
-            const int g = group_of(r0 >> s);
+        if (it.first(k)) {
+            const int g = group_of(it.u[k] >> s);
             eg[2 * k] = (uint32_t)g;
             erank[2 * k] = atomicAdd(&toff[g], 1u);
         }
-        if (cnt == 2) {
-            const int g = group_of(r1 >> s);
+        if (it.second(k)) {
+            const int g = group_of(it.v[k] >> s);
             eg[2 * k + 1] = (uint32_t)g;
             erank[2 * k + 1] = atomicAdd(&toff[g], 1u);
         }
@@ -367,6 +403,22 @@ __global__ __launch_bounds__(kThreads) void part1_kernel(
     }
     if (threadIdx.x == 0) toff[G] = total;
     __syncthreads();
+    if (one_word) {
+        // a word holds the whole entry; its group (below 1024) goes to the write loop beside it
+#pragma unroll
+        for (int k = 0; k < 2 * IPT; ++k)
+            if (eg[k] != kNone) {
+                const uint32_t p = toff[eg[k]] + erank[k];
+                srow[p] = (er[k] - first_row[eg[k]]) << cbits | ec[k];
+                scol[p] = eg[k];
+            }
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < total; j += kThreads) {
+            const uint32_t g = scol[j];
+            rows_out[base[g] + (j - toff[g])] = srow[j];
+        }
+        return;
+    }
     // ids are below 2^23, so the nine high bits of a staged row and the high bit of a staged column are free:
     // they carry the entry's group (below 1024) to the write loop
 #pragma unroll
@@ -428,10 +480,11 @@ __global__ __launch_bounds__(kThreads) void part2_kernel(
         __syncthreads();
     }
 
+    const bool one_word = hdr->one_word != 0;
+    const uint32_t group_row = bin_first << s;
     // slot k: one entry (FROM_PAIRS: slots 2k / 2k+1 are the entries of the thread's k-th item); bucket kNone = unused
     constexpr uint32_t kNone = 0xffffffffu;
     uint32_t ev[EPT], erank[EPT], eb[EPT];
-    bool bad = false;
     auto take = [&](uint32_t r, uint32_t c, uint32_t& v, uint32_t& lb_out, uint32_t& rank) {
         const int lb = direct ? (int)bin_lb[(r >> s) - bin_first] : find_segment(bb0, nb, r >> s);
         v = ((r - (bb0[lb] << s)) << cbits) | c;
@@ -441,19 +494,29 @@ __global__ __launch_bounds__(kThreads) void part2_kernel(
 #pragma unroll
     for (int k = 0; k < EPT; ++k) { ev[k] = 0u; erank[k] = 0u; eb[k] = kNone; }
     if constexpr (FROM_PAIRS) {
+        const int64_t i0 = (int64_t)blockIdx.x * kItemsPerTile + threadIdx.x;
+        bool bad = false;
+        Items<EPT / 2> it;
+        it.load(i0, n_items, n_pairs, src, dst);
+        it.look(i0, n_items, n_pairs, N, bad);
 #pragma unroll
         for (int k = 0; k < EPT / 2; ++k) {
-            const int64_t i = (int64_t)blockIdx.x * kItemsPerTile + k * kThreads + threadIdx.x;
-            uint32_t r0 = 0, c0 = 0, r1 = 0, c1 = 0;
-            const int cnt = i < n_items ? item_entries(i, n_pairs, src, dst, N, bad, r0, c0, r1, c1) : 0;
-            if (cnt >= 1) take(r0, c0, ev[2 * k], eb[2 * k], erank[2 * k]);
-            if (cnt == 2) take(r1, c1, ev[2 * k + 1], eb[2 * k + 1], erank[2 * k + 1]);
+            if (it.first(k)) take(it.u[k], it.v[k], ev[2 * k], eb[2 * k], erank[2 * k]);
+            if (it.second(k)) take(it.v[k], it.u[k], ev[2 * k + 1], eb[2 * k + 1], erank[2 * k + 1]);
         }
     } else {
+        uint32_t w[EPT], c[EPT];
 #pragma unroll
         for (int k = 0; k < EPT; ++k) {
             const uint32_t e = e_begin + k * kThreads + threadIdx.x;
-            if (e < e_end) take(rows_in[e], cols_in[e], ev[k], eb[k], erank[k]);
+            w[k] = e < e_end ? rows_in[e] : 0u;
+            c[k] = !one_word && e < e_end ? cols_in[e] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) {
+            if (e_begin + k * kThreads + threadIdx.x >= e_end) continue;
+            if (one_word) take(group_row + (w[k] >> cbits), w[k] & ((1u << cbits) - 1u), ev[k], eb[k], erank[k]);
+            else take(w[k], c[k], ev[k], eb[k], erank[k]);
         }
     }
     __syncthreads();
@@ -485,119 +548,121 @@ __global__ __launch_bounds__(kThreads) void part2_kernel(
 constexpr int kSortThreads = 1024;       // threads of the sort kernel (512 with twice the keys per thread measured 15 % slower)
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortKeys = kBucketMax / kSortThreads;     // keys per thread
-constexpr int kSortRows = kRowSpan / kSortThreads;       // rows per thread
 constexpr uint32_t kMerged = 255u;       // "bits" of a key range that was put together from small pieces (never split)
+constexpr int kBinWords = kSortBins / 2 + 1;             // two 16-bit counters per word, one past the last
+constexpr int kMapBits = 19;             // bits of the map that a dense oversized bucket is marked in at a time
+typedef uint16_t __attribute__((may_alias)) half_t;
 struct SortShared {
     uint32_t keys[kBucketMax + 4];       // (the rank loop looks at four keys at a time)
-    uint32_t bins[kSortBins + 1];
-    uint32_t rowraw[kRowSpan];           // entries per row in the keys being sorted (sizes the row's bins)
+    uint32_t bins[kBinWords];
+    uint32_t rowmeta[kRowSpan];          // entries of a row in the keys being sorted, then: its first bin | column shift << 16
     uint32_t rowcnt[kRowSpan];           // entries kept per row so far
-    uint32_t rowmeta[kRowSpan];          // first bin of the row | (column shift of its bins << 16)
     uint32_t stk_lo[kStack], stk_hi[kStack], stk_bits[kStack], stk_cnt[kStack];
     uint32_t sc[2 * kSortWaves + 1];
+    uint32_t kept[kSortKeys * kSortWaves];
     uint32_t n, sp;
 };
+static_assert(sizeof(SortShared) <= 81920, "two workgroups per CU");
+static_assert(kBucketMax + 4 + kBinWords + kRowSpan >= (1 << kMapBits) / 32, "keys, bins and rowmeta together hold the map");
+static_assert(kRowSpan <= kSortThreads, "one row per thread");
 
-// Sort the n <= kBucketMax keys in sh.keys, drop repeats, append the columns to out[out_cursor ...) and add
+// Sort the n <= kBucketMax keys load(0 .. n), drop repeats, append the columns to out[out_cursor ...) and add
 // the kept entries to the per-row counts.  Returns the number of kept keys (uniform over the workgroup).
-// On entry all threads have passed a barrier after the last write to sh.keys; on return sh.keys is free.
-// Kept out of line on purpose.  The kernel runs two workgroups per CU (64 registers per lane); as a called
-// function this body gets a register allocation of its own and the caller's few live values cross the call
-// through scratch memory (about 1.7 GB each way per construction, visible in the byte counters).  Inlined under
-// the same cap it spills 13 registers inside its loops and the kernel is 7 % slower; inlined without the cap
-// (one workgroup per CU) 30 % slower.
-__device__ __noinline__ uint32_t sort_and_emit(SortShared& sh, uint32_t n, int nrows, int cbits,
-                                                  uint32_t* __restrict__ out, uint32_t out_cursor)
+// On entry all threads have passed a barrier after the last write to `sh`; on return its keys are free.
+//
+// Bound by LDS operations (some fifteen per key) and the barriers between the phases, not by bytes.  A row of c
+// entries gets 2^lg column bins, c/2 to c of them, so that a bin holds one or two keys when the columns are spread evenly and
+// a key's rank inside its bin takes one look at four neighbours; two 16-bit counters share a word, which is what lets two
+// workgroups fit a CU.  The keys come straight from memory into registers, and go straight out: repeats are left
+// out by ballots over the sorted order.
+// Reddit-shaped graph (16,000 buckets of 7,168, and the oversized ones below): 1,285 us with bins of four to eight keys,
+// staged and compacted in LDS by a function of its own whose saved registers went through memory; now 820 (850 with bins
+// of two to four).
+template <typename Load>
+__device__ __forceinline__ uint32_t sort_keys(SortShared& sh, Load load, uint32_t n, int nrows, int cbits,
+                                              uint32_t* __restrict__ out, uint32_t out_cursor)
 {
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t cmask = (1u << cbits) - 1u;
-    for (int i = tid; i < nrows; i += kSortThreads) sh.rowraw[i] = 0u;
-    for (int i = tid; i <= kSortBins; i += kSortThreads) sh.bins[i] = 0u;
-    __syncthreads();
-    uint32_t k[kSortKeys], r[kSortKeys];
+    const half_t* bin_at = reinterpret_cast<const half_t*>(sh.bins);
+    uint32_t k[kSortKeys];
 #pragma unroll
-    for (int j = 0; j < kSortKeys; ++j) {                      // every lane runs every step (lds_count needs whole waves)
+    for (int j = 0; j < kSortKeys; ++j) {                      // all in flight before the first is used
         const uint32_t i = tid + j * kSortThreads;
-        const bool have = i < n;
-        k[j] = have ? sh.keys[i] : 0u;
-        lds_count(sh.rowraw, k[j] >> cbits, have);
+        k[j] = i < n ? load(i) : 0u;
+    }
+    // a row has at most max(1, its entries) bins
+    const uint32_t words = (n + (uint32_t)nrows) / 2 + 1;
+    for (uint32_t i = tid; i < words; i += kSortThreads) sh.bins[i] = 0u;
+    if (tid < nrows) sh.rowmeta[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSortKeys; ++j) {                      // (lds_count needs whole waves)
+        if ((uint32_t)(j * kSortThreads) >= n) break;
+        lds_count(sh.rowmeta, k[j] >> cbits, tid + j * kSortThreads < n);
     }
     __syncthreads();
-    // a row of c entries gets 2^lg bins, 2^lg = the power of two at or above c, over 8 (at least one):
-    // between c/8 and c/4 bins, so that a bin holds 4 to 8 entries when the columns are spread evenly
     {
-        uint32_t lg[kSortRows], nsub = 0;
-#pragma unroll
-        for (int j = 0; j < kSortRows; ++j) {
-            const int row = tid * kSortRows + j;
-            lg[j] = 0u;
-            if (row < nrows) {
-                const uint32_t c = sh.rowraw[row];
-                lg[j] = c <= 8u ? 0u : (uint32_t)(32 - __clz(c - 1u)) - 3u;
-                lg[j] = lg[j] > (uint32_t)cbits ? (uint32_t)cbits : lg[j];
-                nsub += 1u << lg[j];
-            }
+        uint32_t c = 0, lg = 0, nsub = 0;
+        if (tid < nrows) {
+            c = sh.rowmeta[tid];
+            lg = c <= 2u ? 0u : (uint32_t)(32 - __clz(c - 1u)) - 1u;
+            lg = lg > (uint32_t)cbits ? (uint32_t)cbits : lg;
+            nsub = 1u << lg;
         }
-        uint32_t nbins_total;                                  // <= kSortBins
-        uint32_t first = block_scan_excl<kSortWaves>(nsub, sh.sc, nbins_total);
-#pragma unroll
-        for (int j = 0; j < kSortRows; ++j) {
-            const int row = tid * kSortRows + j;
-            if (row < nrows) {
-                sh.rowmeta[row] = first | (((uint32_t)cbits - lg[j]) << 16);
-                first += 1u << lg[j];
-            }
+        uint32_t nbins_total;                                  // <= n + nrows
+        const uint32_t first = block_scan_excl<kSortWaves>(nsub, sh.sc, nbins_total);
+        if (tid < nrows) {
+            sh.rowmeta[tid] = first | (((uint32_t)cbits - lg) << 16);
+            sh.rowcnt[tid] += c;                               // the repeats among them are taken off below
         }
     }
     __syncthreads();
     // counting split; the atomic's old value is the rank inside the bin
-    uint32_t bin[kSortKeys];
+    auto bin_of = [&](uint32_t key) {
+        const uint32_t meta = sh.rowmeta[key >> cbits];
+        return (meta & 0xffffu) + ((key & cmask) >> (meta >> 16));
+    };
+    uint32_t at[kSortKeys];                                    // bin | rank inside it << 16
 #pragma unroll
     for (int j = 0; j < kSortKeys; ++j) {
-        const uint32_t i = tid + j * kSortThreads;
-        if (i < n) {
-            const uint32_t meta = sh.rowmeta[k[j] >> cbits];
-            bin[j] = (meta & 0xffffu) + ((k[j] & cmask) >> (meta >> 16));
-            r[j] = atomicAdd(&sh.bins[bin[j]], 1u);
+        if (tid + j * kSortThreads < n) {
+            const uint32_t b = bin_of(k[j]), shift = (b & 1u) * 16u;
+            at[j] = b | ((atomicAdd(&sh.bins[b >> 1], 1u << shift) >> shift) << 16);
         }
     }
     __syncthreads();
     {
-        constexpr int BPT = (kSortBins + kSortThreads - 1) / kSortThreads;
-        uint32_t c[BPT], sum = 0;
+        constexpr int WPT = (kBinWords + kSortThreads - 1) / kSortThreads;
+        const uint32_t per = (words + kSortThreads - 1) / kSortThreads, w0 = tid * per;
+        uint32_t c[WPT], sum = 0;
 #pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            const int b = tid * BPT + j;
-            c[j] = b < kSortBins ? sh.bins[b] : 0u;
-            sum += c[j];
+        for (int j = 0; j < WPT; ++j) {
+            c[j] = (uint32_t)j < per && w0 + j < words ? sh.bins[w0 + j] : 0u;
+            sum += (c[j] & 0xffffu) + (c[j] >> 16);
         }
         uint32_t total;
         uint32_t o = block_scan_excl<kSortWaves>(sum, sh.sc, total);
 #pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            const int b = tid * BPT + j;
-            if (b < kSortBins) sh.bins[b] = o;
-            o += c[j];
+        for (int j = 0; j < WPT; ++j) {
+            const uint32_t mid = o + (c[j] & 0xffffu);
+            if ((uint32_t)j < per && w0 + j < words) sh.bins[w0 + j] = o | (mid << 16);
+            o = mid + (c[j] >> 16);
         }
-        if (tid == 0) sh.bins[kSortBins] = total;
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kSortKeys; ++j) {
-        const uint32_t i = tid + j * kSortThreads;
-        if (i < n) sh.keys[sh.bins[bin[j]] + r[j]] = k[j];
-    }
+    for (int j = 0; j < kSortKeys; ++j)
+        if (tid + j * kSortThreads < n) sh.keys[bin_at[at[j] & 0xffffu] + (at[j] >> 16)] = k[j];
     __syncthreads();
-    // rank inside the bin by comparison (a bin holds a few keys); equal keys keep their order of position
-    uint32_t fp[kSortKeys];
+    // rank inside the bin by comparison; equal keys keep their order of position
 #pragma unroll
     for (int j = 0; j < kSortKeys; ++j) {
         const uint32_t p = tid + j * kSortThreads;
         if (p < n) {
             const uint32_t key = sh.keys[p];
-            const uint32_t meta = sh.rowmeta[key >> cbits];
-            const uint32_t d = (meta & 0xffffu) + ((key & cmask) >> (meta >> 16));
-            const uint32_t q0 = sh.bins[d], q1 = sh.bins[d + 1];
+            const uint32_t d = bin_of(key);
+            const uint32_t q0 = bin_at[d], q1 = bin_at[d + 1];
             uint32_t below = 0;
             for (uint32_t q = q0; q < q1; q += 4) {          // four independent reads per step (the array is padded)
                 const uint32_t o0 = sh.keys[q], o1 = sh.keys[q + 1], o2 = sh.keys[q + 2], o3 = sh.keys[q + 3];
@@ -607,54 +672,220 @@ __device__ __noinline__ uint32_t sort_and_emit(SortShared& sh, uint32_t n, int n
                 below += (q + 3 < q1 && (o3 < key || (o3 == key && q + 3 < p))) ? 1u : 0u;
             }
             k[j] = key;
-            fp[j] = q0 + below;
+            at[j] = q0 + below;
         }
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kSortKeys; ++j)
-        if (tid + j * kSortThreads < n) sh.keys[fp[j]] = k[j];
+        if (tid + j * kSortThreads < n) sh.keys[at[j]] = k[j];
     __syncthreads();
-    // keep the first key of every run of equal keys: each thread takes a contiguous piece, reads what it keeps
-    // into registers, and after the prefix sum writes it back compacted; rows are counted run by run
-    const uint32_t per = (n + kSortThreads - 1) / kSortThreads;          // <= kSortKeys
-    const uint32_t p0 = tid * per < n ? tid * per : n;
-    const uint32_t p1 = p0 + per < n ? p0 + per : n;
-    uint32_t kept = 0, keep_mask = 0;
-    {
-        uint32_t prev = p0 > 0 ? sh.keys[p0 - 1] : 0u;
-        uint32_t cur_row = 0xffffffffu, run = 0;
+    // keep the first key of every run of equal keys; the pieces of 64 that the waves look at are numbered in key order
+    uint32_t keep = 0, before[kSortKeys];
 #pragma unroll
-        for (int j = 0; j < kSortKeys; ++j) {
-            const uint32_t p = p0 + j;
-            if (p < p1) {
-                const uint32_t key = sh.keys[p];
-                k[j] = key;
-                if (p == 0 || key != prev) {
-                    keep_mask |= 1u << j;
-                    ++kept;
-                    const uint32_t row = key >> cbits;
-                    if (row != cur_row) {
-                        if (run) atomicAdd(&sh.rowcnt[cur_row], run);
-                        cur_row = row;
-                        run = 0;
-                    }
-                    ++run;
-                }
-                prev = key;
-            }
-        }
-        if (run) atomicAdd(&sh.rowcnt[cur_row], run);
+    for (int j = 0; j < kSortKeys; ++j) {
+        const uint32_t i = tid + j * kSortThreads;
+        const bool have = i < n;
+        k[j] = have ? sh.keys[i] : 0u;
+        const bool first = have && (i == 0 || sh.keys[i - 1] != k[j]);
+        const uint64_t m = __ballot(first);
+        before[j] = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        keep |= first ? 1u << j : 0u;
+        if (lane == 0) sh.kept[j * kSortWaves + wave] = (uint32_t)__popcll(m);
+        lds_count(sh.rowcnt, k[j] >> cbits, have && !first, (uint32_t)-1);
     }
-    uint32_t total;
-    const uint32_t excl = block_scan_excl<kSortWaves>(kept, sh.sc, total);  // its barriers separate the reads from the writes
-#pragma unroll
-    for (int j = 0; j < kSortKeys; ++j)
-        if (keep_mask & (1u << j)) sh.keys[excl + (uint32_t)__popc(keep_mask & ((1u << j) - 1u))] = k[j];
     __syncthreads();
-    for (uint32_t i = tid; i < total; i += kSortThreads) out[out_cursor + i] = sh.keys[i] & cmask;
+    // every wave adds up all pieces' counts: three per lane
+    constexpr int PIECES = kSortKeys * kSortWaves, PPL = (PIECES + 63) / 64;
+    uint32_t c[PPL], sum = 0;
+#pragma unroll
+    for (int t = 0; t < PPL; ++t) {
+        c[t] = lane * PPL + t < PIECES ? sh.kept[lane * PPL + t] : 0u;
+        sum += c[t];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t t = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += t;
+    }
+    uint32_t lead[PPL];                                        // kept keys before each of the lane's pieces
+    lead[0] = incl - sum;
+#pragma unroll
+    for (int t = 1; t < PPL; ++t) lead[t] = lead[t - 1] + c[t - 1];
+#pragma unroll
+    for (int j = 0; j < kSortKeys; ++j) {
+        const int piece = j * kSortWaves + wave, from = piece / PPL, which = piece % PPL;      // (uniform)
+        uint32_t base = lead[0];
+#pragma unroll
+        for (int t = 1; t < PPL; ++t) base = which == t ? lead[t] : base;
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, from);
+        if (keep & (1u << j)) out[out_cursor + base + before[j]] = k[j] & cmask;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     __syncthreads();
     return total;
+}
+
+// A bucket that does not fit, i.e. one bin whose rows alone hold more.
+//
+// Dense ones (up to 512 possible keys per entry) are marked in a map of 2^19 bits at a time, which drops the repeats and
+// puts the rest in order by itself; every stretch of the map reads all entries again (from L2).
+// The others are worked through in key ranges [lo, hi], lowest first: a range that fits is gathered and sorted; one
+// that does not is an aligned block of 2^bits keys, which is counted in 64 pieces by its next key bits; neighbouring
+// pieces are put together into ranges that fit, and a piece that still does not fit is split again (or is a single
+// repeated key).  Each level removes 6 key bits, so the stack stays below kStack.
+// Out of line: its registers and the sort's copy in it are then no concern of the buckets that fit.
+// Reddit-shaped graph, 667 such buckets of eight rows: the sort kernel 1,024 us with key ranges alone, 820 with the map.
+__device__ __noinline__ uint32_t sort_oversized(SortShared& sh, BucketHeader* hdr, const uint32_t* __restrict__ in, uint32_t E,
+                                                int nrows, int cbits, uint32_t* __restrict__ out)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t out_cursor = 0;
+    // the bits that the bucket's keys really use (its rows, then the columns)
+    const uint32_t kb = (uint32_t)cbits + (nrows > 1 ? 32u - (uint32_t)__clz((uint32_t)(nrows - 1)) : 0u);
+    if (cbits >= 5 && (uint64_t)E << 9 >= 1ull << kb) {
+        constexpr uint32_t WORDS = (1u << kMapBits) / 32, PER_WAVE = WORDS / kSortWaves;
+        uint32_t* map = sh.keys;                             // runs on into bins and rowmeta
+        const uint32_t stretches = kb > (uint32_t)kMapBits ? 1u << (kb - kMapBits) : 1u;
+        constexpr int AHEAD = 8;
+        for (uint32_t st = 0; st < stretches; ++st) {
+            for (uint32_t i = tid; i < WORDS; i += kSortThreads) map[i] = 0u;
+            __syncthreads();
+            for (uint32_t i0 = tid; i0 < E; i0 += AHEAD * kSortThreads) {
+                uint32_t key[AHEAD];
+#pragma unroll
+                for (int t = 0; t < AHEAD; ++t) {
+                    const uint32_t i = i0 + t * kSortThreads;
+                    key[t] = i < E ? in[i] : 0xffffffffu;
+                }
+#pragma unroll
+                for (int t = 0; t < AHEAD; ++t)
+                    if (i0 + t * kSortThreads < E && key[t] >> kMapBits == st)
+                        atomicOr(&map[(key[t] & ((1u << kMapBits) - 1u)) >> 5], 1u << (key[t] & 31u));
+            }
+            __syncthreads();
+            // a wave's words are consecutive; 64 of them at a time, one per lane
+            uint32_t mine = 0;
+            for (uint32_t w = lane; w < PER_WAVE; w += 64) mine += (uint32_t)__popc(map[wave * PER_WAVE + w]);
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
+            if (lane == 0) sh.sc[wave] = mine;
+            __syncthreads();
+            uint32_t at = out_cursor, all = 0;
+#pragma unroll
+            for (int w = 0; w < kSortWaves; ++w) {
+                const uint32_t c = sh.sc[w];
+                at += w < wave ? c : 0u;
+                all += c;
+            }
+            for (uint32_t w0 = 0; w0 < PER_WAVE; w0 += 64) {
+                const uint32_t word = wave * PER_WAVE + w0 + lane;
+                uint32_t bits = map[word];
+                const uint32_t c = (uint32_t)__popc(bits);
+                const uint32_t key0 = (st << kMapBits) + (word << 5);
+                uint32_t incl = c;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const uint32_t t = __shfl_up(incl, d, 64);
+                    if (lane >= d) incl += t;
+                }
+                const uint32_t step = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                if (cbits >= 11) {                           // the 2,048 keys of a step are of one row
+                    if (lane == 0 && step) atomicAdd(&sh.rowcnt[key0 >> cbits], step);
+                } else if (c) {
+                    atomicAdd(&sh.rowcnt[key0 >> cbits], c);
+                }
+                for (uint32_t o = at + incl - c; bits; ++o, bits &= bits - 1u)
+                    out[o] = (key0 + (uint32_t)__builtin_ctz(bits)) & ((1u << cbits) - 1u);
+                at += step;
+            }
+            out_cursor += all;
+            __syncthreads();
+        }
+        return out_cursor;
+    }
+    if (tid == 0) {
+        sh.stk_lo[0] = 0u;
+        sh.stk_hi[0] = kb >= 32u ? 0xffffffffu : (1u << kb) - 1u;
+        sh.stk_bits[0] = kb >= 32u ? 32u : kb;
+        sh.stk_cnt[0] = E;
+        sh.sp = 1u;
+    }
+    __syncthreads();
+    for (;;) {
+        const uint32_t sp = sh.sp;
+        if (sp == 0) break;
+        const uint32_t lo = sh.stk_lo[sp - 1], hi = sh.stk_hi[sp - 1], bits = sh.stk_bits[sp - 1],
+                       cnt = sh.stk_cnt[sp - 1];
+        __syncthreads();
+        if (tid == 0) { sh.sp = sp - 1; sh.n = 0u; }
+        __syncthreads();
+        if (cnt > (uint32_t)kBucketMax && bits == 0u) {
+            // more than a bucketful of one and the same key: it is kept once
+            if (tid == 0) {
+                out[out_cursor] = lo & ((1u << cbits) - 1u);
+                atomicAdd(&sh.rowcnt[lo >> cbits], 1u);
+            }
+            out_cursor += 1;
+            __syncthreads();
+            continue;
+        }
+        if (cnt > (uint32_t)kBucketMax) {
+            const uint32_t cb = bits > 6u ? bits - 6u : 0u;
+            const int nchild = 1 << (bits - cb);
+            if (tid < 64) sh.bins[tid] = 0u;
+            __syncthreads();
+            for (uint32_t i0 = (uint32_t)(tid - lane); i0 < E; i0 += kSortThreads) {  // uniform per wave
+                const uint32_t i = i0 + lane;
+                const uint32_t key = i < E ? in[i] : 0u;
+                const bool match = i < E && key >= lo && key <= hi;
+                lds_count(sh.bins, match ? (key - lo) >> cb : 0u, match);
+            }
+            __syncthreads();
+            if (tid == 0) {
+                // highest keys first, so that the lowest range is on top of the stack
+                uint32_t top = sh.sp;
+                auto push = [&](int c0, int c1, uint32_t b_, uint32_t n_) {      // pieces c0..c1
+                    if (top >= (uint32_t)kStack) { hdr->internal = 1u; return; }  // cannot happen (6 levels x 64)
+                    sh.stk_lo[top] = lo + ((uint32_t)c0 << cb);
+                    sh.stk_hi[top] = c1 == nchild - 1 ? hi : lo + ((uint32_t)(c1 + 1) << cb) - 1u;
+                    sh.stk_bits[top] = b_;
+                    sh.stk_cnt[top] = n_;
+                    ++top;
+                };
+                int ch = nchild - 1;
+                while (ch >= 0) {
+                    if (sh.bins[ch] > (uint32_t)kBucketMax) { push(ch, ch, cb, sh.bins[ch]); --ch; continue; }
+                    const int c1 = ch;
+                    uint32_t sum = 0;
+                    while (ch >= 0 && sum + sh.bins[ch] <= (uint32_t)kBucketMax) { sum += sh.bins[ch]; --ch; }
+                    if (sum) push(ch + 1, c1, kMerged, sum);
+                }
+                sh.sp = top;
+            }
+            __syncthreads();
+            continue;
+        }
+        // the range fits: gather its keys
+        for (uint32_t i0 = (uint32_t)(tid - lane); i0 < E; i0 += kSortThreads) {      // uniform per wave
+            const uint32_t i = i0 + lane;
+            const uint32_t key = i < E ? in[i] : 0u;
+            const bool match = i < E && key >= lo && key <= hi;
+            const uint64_t mask = __ballot(match);
+            if (mask) {
+                const int leader = __ffsll((unsigned long long)mask) - 1;
+                uint32_t at = 0;
+                if (lane == leader) at = atomicAdd(&sh.n, (uint32_t)__popcll(mask));
+                at = __shfl(at, leader, 64);
+                if (match) sh.keys[at + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = key;
+            }
+        }
+        __syncthreads();
+        const uint32_t n = sh.n;                               // == cnt
+        out_cursor += sort_keys(sh, [&](uint32_t i) { return sh.keys[i]; }, n, nrows, cbits, out, out_cursor);
+    }
+    return out_cursor;
 }
 
 __global__ __launch_bounds__(kSortThreads, 8) void sort_kernel(
@@ -666,128 +897,22 @@ __global__ __launch_bounds__(kSortThreads, 8) void sort_kernel(
     if (hdr->bad_id || hdr->internal) return;
     const uint32_t b = blockIdx.x;
     if (b >= hdr->n_buckets) return;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const uint32_t e0 = bucket_off[b], E = bucket_off[b + 1] - e0;
     const int64_t row0 = (int64_t)bucket_bin0[b] << s;
     int64_t row1 = (int64_t)bucket_bin0[b + 1] << s;
     row1 = row1 < N ? row1 : N;
     const int nrows = (int)(row1 - row0);                    // <= kRowSpan
-    for (int i = tid; i < nrows; i += kSortThreads) sh.rowcnt[i] = 0u;
+    if (tid < nrows) sh.rowcnt[tid] = 0u;
     const uint32_t* in = packed + e0;
     uint32_t* out = cols_tmp + e0;
-    uint32_t out_cursor = 0;
-
-    // A bucket that fits is loaded and sorted in one go.  One that does not is worked through in key ranges
-    // [lo, hi], lowest first: a range that fits is gathered and sorted; one that does not is an aligned block
-    // of 2^bits keys, which is counted in 64 pieces by its next key bits; neighbouring pieces are put together
-    // into ranges that fit, and a piece that still does not fit is split again (or is a single repeated key).
-    // Each level removes 6 key bits, so the stack stays below kStack.
-    const bool fits = E <= (uint32_t)kBucketMax;
-    if (fits) {
-        uint32_t v[kSortKeys];
-#pragma unroll
-        for (int j = 0; j < kSortKeys; ++j) {                // all loads in flight before the first is used
-            const uint32_t i = tid + j * kSortThreads;
-            v[j] = i < E ? in[i] : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < kSortKeys; ++j) {
-            const uint32_t i = tid + j * kSortThreads;
-            if (i < E) sh.keys[i] = v[j];
-        }
-        if (tid == 0) sh.sp = 0u;
-    } else if (tid == 0) {
-        // the walk starts at the bits the bucket's keys really use (its rows, then the columns): a bucket of
-        // eight hot rows would otherwise spend three counting passes on key bits that are all zero
-        const uint32_t kb = (uint32_t)cbits + (nrows > 1 ? 32u - (uint32_t)__clz((uint32_t)(nrows - 1)) : 0u);
-        sh.stk_lo[0] = 0u;
-        sh.stk_hi[0] = kb >= 32u ? 0xffffffffu : (1u << kb) - 1u;
-        sh.stk_bits[0] = kb >= 32u ? 32u : kb;
-        sh.stk_cnt[0] = E;
-        sh.sp = 1u;
-    }
+    uint32_t kept = 0;
     __syncthreads();
-    for (bool first = true;; first = false) {
-        uint32_t n;
-        if (fits) {
-            if (!first || E == 0) break;
-            n = E;
-        } else {
-            const uint32_t sp = sh.sp;
-            if (sp == 0) break;
-            const uint32_t lo = sh.stk_lo[sp - 1], hi = sh.stk_hi[sp - 1], bits = sh.stk_bits[sp - 1],
-                           cnt = sh.stk_cnt[sp - 1];
-            __syncthreads();
-            if (tid == 0) { sh.sp = sp - 1; sh.n = 0u; }
-            __syncthreads();
-            if (cnt > (uint32_t)kBucketMax && bits == 0u) {
-                // more than a bucketful of one and the same key: it is kept once
-                if (tid == 0) {
-                    out[out_cursor] = lo & ((1u << cbits) - 1u);
-                    atomicAdd(&sh.rowcnt[lo >> cbits], 1u);
-                }
-                out_cursor += 1;
-                __syncthreads();
-                continue;
-            }
-            if (cnt > (uint32_t)kBucketMax) {
-                const uint32_t cb = bits > 6u ? bits - 6u : 0u;
-                const int nchild = 1 << (bits - cb);
-                if (tid < 64) sh.bins[tid] = 0u;
-                __syncthreads();
-                for (uint32_t i0 = (uint32_t)(tid - lane); i0 < E; i0 += kSortThreads) {  // uniform per wave
-                    const uint32_t i = i0 + lane;
-                    const uint32_t key = i < E ? in[i] : 0u;
-                    const bool match = i < E && key >= lo && key <= hi;
-                    lds_count(sh.bins, match ? (key - lo) >> cb : 0u, match);
-                }
-                __syncthreads();
-                if (tid == 0) {
-                    // highest keys first, so that the lowest range is on top of the stack
-                    uint32_t top = sh.sp;
-                    auto push = [&](int c0, int c1, uint32_t b_, uint32_t n_) {      // pieces c0..c1
-                        if (top >= (uint32_t)kStack) { hdr->internal = 1u; return; }  // cannot happen (6 levels x 64)
-                        sh.stk_lo[top] = lo + ((uint32_t)c0 << cb);
-                        sh.stk_hi[top] = c1 == nchild - 1 ? hi : lo + ((uint32_t)(c1 + 1) << cb) - 1u;
-                        sh.stk_bits[top] = b_;
-                        sh.stk_cnt[top] = n_;
-                        ++top;
-                    };
-                    int ch = nchild - 1;
-                    while (ch >= 0) {
-                        if (sh.bins[ch] > (uint32_t)kBucketMax) { push(ch, ch, cb, sh.bins[ch]); --ch; continue; }
-                        const int c1 = ch;
-                        uint32_t sum = 0;
-                        while (ch >= 0 && sum + sh.bins[ch] <= (uint32_t)kBucketMax) { sum += sh.bins[ch]; --ch; }
-                        if (sum) push(ch + 1, c1, kMerged, sum);
-                    }
-                    sh.sp = top;
-                }
-                __syncthreads();
-                continue;
-            }
-            // the range fits: gather its keys
-            for (uint32_t i0 = (uint32_t)(tid - lane); i0 < E; i0 += kSortThreads) {      // uniform per wave
-                const uint32_t i = i0 + lane;
-                const uint32_t key = i < E ? in[i] : 0u;
-                const bool match = i < E && key >= lo && key <= hi;
-                const uint64_t mask = __ballot(match);
-                if (mask) {
-                    const int leader = __ffsll((unsigned long long)mask) - 1;
-                    uint32_t at = 0;
-                    if (lane == leader) at = atomicAdd(&sh.n, (uint32_t)__popcll(mask));
-                    at = __shfl(at, leader, 64);
-                    if (match) sh.keys[at + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull))] = key;
-                }
-            }
-            __syncthreads();
-            n = sh.n;                                          // == cnt
-        }
-        out_cursor += sort_and_emit(sh, n, nrows, cbits, out, out_cursor);
-    }
+    if (E > (uint32_t)kBucketMax) kept = sort_oversized(sh, hdr, in, E, nrows, cbits, out);
+    else if (E > 0) kept = sort_keys(sh, [&](uint32_t i) { return in[i]; }, E, nrows, cbits, out, 0u);
     __syncthreads();
-    for (int i = tid; i < nrows; i += kSortThreads) row_unique[row0 + i] = (int32_t)sh.rowcnt[i];
-    if (tid == 0) bucket_total[b] = out_cursor;
+    if (tid < nrows) row_unique[row0 + tid] = (int32_t)sh.rowcnt[tid];
+    if (tid == 0) bucket_total[b] = kept;
 }
 
 __global__ __launch_bounds__(kThreads) void total_kernel(BucketHeader* hdr, const uint32_t* __restrict__ bucket_total,
@@ -842,8 +967,19 @@ __global__ __launch_bounds__(256) void emit_kernel(
         o += c[j];
     }
     if (b == n - 1 && threadIdx.x == 0) row_ptr[N] = hdr->nnz;
+    // sixteen bytes at a time where the destination allows them (the source is at any word)
     const uint32_t* from = cols_tmp + bucket_off[b];
-    for (uint32_t i = threadIdx.x; i < count; i += 256) col_idx[out0 + i] = (int32_t)from[i];
+    int32_t* to = col_idx + out0;
+    const uint32_t odd = (uint32_t)(-(intptr_t)((uintptr_t)to >> 2) & 3), head = odd < count ? odd : count;
+    if (threadIdx.x < head) to[threadIdx.x] = (int32_t)from[threadIdx.x];
+    const uint32_t quads = (count - head) / 4;
+    typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t words4_any __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll 4
+    for (uint32_t q = threadIdx.x; q < quads; q += 256)
+        *reinterpret_cast<words4*>(to + head + 4 * q) = *reinterpret_cast<const words4_any*>(from + head + 4 * q);
+    const uint32_t tail = head + 4 * quads + threadIdx.x;
+    if (tail < count) to[tail] = (int32_t)from[tail];
 }
 
 int column_bits(int64_t N)
@@ -859,7 +995,7 @@ struct BucketLayout {
     int cbits, s, nbins, span_bins, target, hist_blocks;
     int64_t M, n_items, items_per_block, bucket_bound;
     bool two_level;
-    int64_t header, counts, bin_count, bin_off, bucket_bin0, bucket_off, bucket_cursor, bucket_total, bucket_out,
+    int64_t header, counts, bin_count, bucket_bin0, bucket_off, bucket_cursor, bucket_total, bucket_out,
         group_bin0, group_off, group_cursor, group_tile0, coarse_group, buf_a, buf_b, buf_c, row_unique, total;
 };
 
@@ -900,7 +1036,6 @@ bool make_bucket_layout(int64_t n_pairs, int64_t N, int add_self_loops, BucketLa
     L.header = take(256);
     L.bin_count = take(4ll * L.nbins);                       // (zeroed together with the header)
     L.counts = take(4ll * L.hist_blocks * L.nbins);
-    L.bin_off = take(4ll * (L.nbins + 1));
     L.bucket_bin0 = take(4 * (L.bucket_bound + 1));
     L.bucket_off = take(4 * (L.bucket_bound + 1));
     L.bucket_cursor = take(4 * L.bucket_bound);
@@ -937,7 +1072,7 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
     char* ws = (char*)d_workspace;
     BucketHeader* hdr = (BucketHeader*)(ws + L.header);
     auto u32 = [&](int64_t at) { return (uint32_t*)(ws + at); };
-    PlanArrays pa{u32(L.bin_off), u32(L.bucket_bin0), u32(L.bucket_off), u32(L.bucket_cursor),
+    PlanArrays pa{u32(L.bucket_bin0), u32(L.bucket_off), u32(L.bucket_cursor),
                   u32(L.group_bin0), u32(L.group_off), u32(L.group_cursor), u32(L.group_tile0),
                   (uint16_t*)(ws + L.coarse_group)};
 
@@ -946,13 +1081,13 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
         n_pairs, d_src, d_dst, N, L.n_items, L.items_per_block, L.s, L.nbins, u32(L.counts), hdr);
     colsum_kernel<<<dim3((unsigned)((L.nbins + 255) / 256), kColsumSlices), dim3(256), 0, stream>>>(
         L.hist_blocks, L.nbins, u32(L.counts), u32(L.bin_count));
-    plan_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(L.nbins, L.span_bins, (uint32_t)L.target, (uint32_t)((1ull << 32) / (uint64_t)L.target), u32(L.bin_count), pa,
+    plan_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(L.nbins, L.span_bins, (int)((1ll << (32 - L.cbits)) >> L.s), (uint32_t)L.target, (uint32_t)((1ull << 32) / (uint64_t)L.target), u32(L.bin_count), pa,
                                                         (uint32_t)L.bucket_bound, hdr);
     const unsigned item_tiles = (unsigned)((L.n_items + kItemsPerTile - 1) / kItemsPerTile);
     if (L.M > 0) {
         if (L.two_level) {
             part1_kernel<<<dim3(item_tiles), dim3(kThreads), 0, stream>>>(
-                n_pairs, d_src, d_dst, N, L.n_items, L.s, pa.coarse_group, pa.group_cursor, u32(L.buf_a), u32(L.buf_b), hdr);
+                n_pairs, d_src, d_dst, N, L.n_items, L.s, L.cbits, pa.coarse_group, pa.group_bin0, pa.group_cursor, u32(L.buf_a), u32(L.buf_b), hdr);
             const unsigned tiles = (unsigned)((L.M + kTileEntries - 1) / kTileEntries + kMaxGroups);
             part2_kernel<false><<<dim3(tiles), dim3(kThreads), 0, stream>>>(
                 n_pairs, d_src, d_dst, N, L.n_items, L.s, L.cbits, u32(L.buf_a), u32(L.buf_b), pa.group_off,
