@@ -29,6 +29,8 @@
 //
 // Integer arithmetic only.  The order in which atomics hand out positions inside a bucket is
 // arbitrary, but the sorted, repeat-free result is not, so the output is bitwise reproducible.
+#include <type_traits>
+
 #include "common.hpp"
 #include "csr_bucket.hpp"
 
@@ -38,6 +40,9 @@ constexpr int kThreads = 1024;           // hist, plan, part1, part2, sort, tota
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxBins = 32768;          // row ranges the histogram distinguishes
 constexpr int kMaxHistBlocks = 256;
+constexpr int kSmallBins = 4096;         // row ranges of a small graph, whose items one workgroup counts and plans
+constexpr int64_t kSmallItems = 196608;  // 190,000 pairs: 103 us, 111 in several workgroups; 220,000: 108 and 106
+constexpr int kFewBuckets = 1024;        // so many that every workgroup of emit adds up their counts by itself
 constexpr int kItemsPerTile = 4096;      // pairs per part1 tile (two entries each)
 constexpr int kTileEntries = 8192;       // entries per part2 tile
 constexpr int kGroupBuckets = 256;       // buckets per group
@@ -249,26 +254,58 @@ __device__ __forceinline__ bool starts_bucket(int bin, uint32_t off, const uint3
     return off - first + cnt > (uint32_t)kBucketMax;
 }
 
-__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, int group_bins, uint32_t target, uint32_t per_entry, const uint32_t* __restrict__ bin_count,
+// COUNT: a small graph, counted here as well (hist, colsum, the clearing of the header and this kernel were four launches: a
+// construction over 2,708 nodes and 5,429 pairs 80 -> 57 us, 19,717 and 44,338 106 -> 67); there is one group then, and no part1.
+template <bool COUNT>
+__global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins, int group_bins, uint32_t target, uint32_t per_entry,
+                                                        const uint32_t* __restrict__ bin_count, int64_t n_pairs,
+                                                        const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                                        int64_t N, int64_t n_items, int s,
                                                         PlanArrays a, uint32_t bucket_capacity, BucketHeader* hdr)
 {
-    __shared__ uint32_t cnts[kMaxBins];            // the bin counts, read three times
+    __shared__ uint32_t cnts[COUNT ? kSmallBins : kMaxBins];      // the bin counts, read three times
     __shared__ uint32_t sc[2 * kWaves + 1];
-    if (hdr->bad_id) return;
-    for (int b = threadIdx.x; b < nbins; b += kThreads) cnts[b] = bin_count[b];
-    __syncthreads();
-    const int per = (nbins + kThreads - 1) / kThreads;
-    const int b0 = threadIdx.x * per < nbins ? threadIdx.x * per : nbins, b1 = b0 + per < nbins ? b0 + per : nbins;
+    if constexpr (COUNT) {
+        for (int b = threadIdx.x; b < nbins; b += kThreads) cnts[b] = 0u;
+        if (threadIdx.x == 0) *hdr = BucketHeader{};
+        __syncthreads();
+        bool bad = false;
+        Items<8> it;
+        for (int64_t i0 = threadIdx.x; i0 < n_items; i0 += 8 * kThreads) {
+            it.load(i0, n_items, n_pairs, src, dst);
+            it.look(i0, n_items, n_pairs, N, bad);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                if (it.first(t)) atomicAdd(&cnts[it.u[t] >> s], 1u);
+                if (it.second(t)) atomicAdd(&cnts[it.v[t] >> s], 1u);
+            }
+        }
+        if (__syncthreads_or(bad)) {
+            if (threadIdx.x == 0) hdr->bad_id = 1u;
+            return;
+        }
+    } else {
+        if (hdr->bad_id) return;
+        for (int b = threadIdx.x; b < nbins; b += kThreads) cnts[b] = bin_count[b];
+        __syncthreads();
+    }
+    // (an odd number of bins per thread: neighbouring threads then read different LDS banks)
+    const int per = ((nbins + kThreads - 1) / kThreads) | 1;
+    const int b0 = (int)threadIdx.x * per < nbins ? (int)threadIdx.x * per : nbins, b1 = b0 + per < nbins ? b0 + per : nbins;
     uint32_t sum = 0;
     for (int b = b0; b < b1; ++b) sum += cnts[b];
     uint32_t total;
     uint32_t off = block_scan_excl<kWaves>(sum, sc, total);
     uint32_t starts = 0;
+    uint64_t which = 0;                            // which of the thread's bins (at most 33) start a bucket
     {
         uint32_t o = off;
         for (int b = b0; b < b1; ++b) {
             const uint32_t cnt = cnts[b];
-            starts += starts_bucket(b, o, cnts, span_bins, target, per_entry) ? 1u : 0u;
+            if (starts_bucket(b, o, cnts, span_bins, target, per_entry)) {
+                ++starts;
+                which |= 1ull << (b - b0);
+            }
             o += cnt;
         }
     }
@@ -281,14 +318,13 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
     {
         uint32_t o = off;
         for (int b = b0; b < b1; ++b) {
-            const uint32_t cnt = cnts[b];
-            if (starts_bucket(b, o, cnts, span_bins, target, per_entry)) {
+            if ((which >> (b - b0)) & 1u) {
                 a.bucket_bin0[id] = (uint32_t)b;
                 a.bucket_off[id] = o;
                 a.bucket_cursor[id] = o;
                 ++id;
             }
-            o += cnt;
+            o += cnts[b];
         }
     }
     const uint32_t n_groups = (n_buckets + kGroupBuckets - 1) / kGroupBuckets;
@@ -298,6 +334,7 @@ __global__ __launch_bounds__(kThreads) void plan_kernel(int nbins, int span_bins
         hdr->n_buckets = n_buckets;
         hdr->n_groups = n_groups;
     }
+    if (COUNT) return;
     __syncthreads();                               // the bucket arrays are complete
     // one group per thread (n_groups <= kMaxGroups <= kThreads)
     const uint32_t g = threadIdx.x;
@@ -936,21 +973,45 @@ __global__ __launch_bounds__(kThreads) void total_kernel(BucketHeader* hdr, cons
     }
 }
 
+// SUM: few buckets, whose counts every workgroup adds up itself (total's launch took 5 us of a small graph's construction).
+template <bool SUM>
 __global__ __launch_bounds__(256) void emit_kernel(
-    const BucketHeader* hdr, const uint32_t* __restrict__ bucket_off, const uint32_t* __restrict__ bucket_bin0,
+    BucketHeader* hdr, const uint32_t* __restrict__ bucket_off, const uint32_t* __restrict__ bucket_bin0,
     const uint32_t* __restrict__ bucket_out, const uint32_t* __restrict__ cols_tmp, const int32_t* __restrict__ row_unique,
+    const uint32_t* __restrict__ bucket_total, int64_t col_capacity,
     int s, int64_t N, int64_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx)
 {
     constexpr int RPT = kRowSpan / 256;                      // rows per thread
     __shared__ uint32_t sc[2 * 4 + 1];
-    if (hdr->bad_id || hdr->internal || hdr->overflow) return;
+    if (hdr->bad_id || hdr->internal || (!SUM && hdr->overflow)) return;
     const uint32_t b = blockIdx.x, n = hdr->n_buckets;
     if (b >= n) return;
+    uint32_t out0, nnz;
+    if constexpr (SUM) {
+        uint32_t c[kFewBuckets / 256], before = 0, all = 0;
+#pragma unroll
+        for (int j = 0; j < kFewBuckets / 256; ++j) {
+            const uint32_t i = threadIdx.x + j * 256;
+            c[j] = i < n ? bucket_total[i] : 0u;
+            before += i < b ? c[j] : 0u;
+            all += c[j];
+        }
+        (void)block_scan_excl<4>(before, sc, out0);
+        (void)block_scan_excl<4>(all, sc, nnz);
+        if (b == 0 && threadIdx.x == 0) {
+            hdr->nnz = (int64_t)nnz;
+            hdr->overflow = (int64_t)nnz > col_capacity ? 1u : 0u;
+        }
+        if ((int64_t)nnz > col_capacity) return;
+    } else {
+        out0 = bucket_out[b];
+        nnz = (uint32_t)hdr->nnz;
+    }
     const int64_t row0 = (int64_t)bucket_bin0[b] << s;
     int64_t row1 = (int64_t)bucket_bin0[b + 1] << s;
     row1 = row1 < N ? row1 : N;
     const int nrows = (int)(row1 - row0);
-    const uint32_t out0 = bucket_out[b], count = bucket_out[b + 1] - out0;
+    const uint32_t count = SUM ? bucket_total[b] : bucket_out[b + 1] - out0;
     uint32_t c[RPT], sum = 0;
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
@@ -966,7 +1027,7 @@ __global__ __launch_bounds__(256) void emit_kernel(
         if (i < nrows) row_ptr[row0 + i] = (int64_t)o;
         o += c[j];
     }
-    if (b == n - 1 && threadIdx.x == 0) row_ptr[N] = hdr->nnz;
+    if (b == n - 1 && threadIdx.x == 0) row_ptr[N] = (int64_t)nnz;
     // sixteen bytes at a time where the destination allows them (the source is at any word)
     const uint32_t* from = cols_tmp + bucket_off[b];
     int32_t* to = col_idx + out0;
@@ -994,7 +1055,7 @@ static_assert(sizeof(BucketHeader) <= 256, "the header has 256 bytes of the work
 struct BucketLayout {
     int cbits, s, nbins, span_bins, target, hist_blocks;
     int64_t M, n_items, items_per_block, bucket_bound;
-    bool two_level;
+    bool two_level, small;
     int64_t header, counts, bin_count, bucket_bin0, bucket_off, bucket_cursor, bucket_total, bucket_out,
         group_bin0, group_off, group_cursor, group_tile0, coarse_group, buf_a, buf_b, buf_c, row_unique, total;
 };
@@ -1007,11 +1068,6 @@ bool make_bucket_layout(int64_t n_pairs, int64_t N, int add_self_loops, BucketLa
     L.M = 2 * n_pairs + (add_self_loops ? N : 0);
     if (L.M > kMaxEntries) return false;
     L.n_items = n_pairs + (add_self_loops ? N : 0);
-    L.s = L.cbits > 15 ? L.cbits - 15 : 0;
-    L.nbins = (int)((N + (1ll << L.s) - 1) >> L.s);          // <= kMaxBins
-    const int64_t span_rows = (1ll << (32 - L.cbits)) < kRowSpan ? (1ll << (32 - L.cbits)) : kRowSpan;
-    L.span_bins = (int)(span_rows >> L.s);
-    if (L.span_bins < 1 || L.nbins > kMaxBins) return false;
     // The sort of a bucket costs much the same half full as full (twenty barriers, its scans), so a large graph's are
     // filled to 0.7 of what fits: 57.5 million pairs over 233 thousand nodes 1410 us at half, 1315 at 0.7, 1360 at 0.8 (when
     // several bins could still overfill a bucket; 1290 at 0.7 since); whole constructions of 30 to 50 million pairs gain 8
@@ -1020,10 +1076,22 @@ bool make_bucket_layout(int64_t n_pairs, int64_t N, int add_self_loops, BucketLa
     // bound of a graph of 0.4 million entries within one group): 3 to 5 % from 7 thousand to 5 million entries.
     const int64_t spread = L.M / kTargetBuckets;
     L.target = spread > kTargetMax ? kTargetMax : spread < kTargetMin ? kTargetMin : (int)spread;
-    // worst case of starts_bucket: one start per window, one more for a bin that reaches over the end of its window (at most
-    // one in each, of more than kBucketMax - 1 - target entries), one per row window
-    const int64_t windows = L.M / L.target, reach = L.M / (kBucketMax - 1 - L.target);
-    L.bucket_bound = windows + (windows < reach ? windows : reach) + L.nbins / L.span_bins + 4;
+    // Row ranges ("bins") of 2^s rows: at most kMaxBins, or kSmallBins of a graph that one workgroup counts and plans, up to
+    // where its counting takes as long as the launches that it saves.
+    auto bins = [&](int most_bits) {
+        L.s = L.cbits > most_bits ? L.cbits - most_bits : 0;
+        L.nbins = (int)((N + (1ll << L.s) - 1) >> L.s);
+        const int64_t span_rows = (1ll << (32 - L.cbits)) < kRowSpan ? (1ll << (32 - L.cbits)) : kRowSpan;
+        L.span_bins = (int)(span_rows >> L.s);
+        // worst case of starts_bucket: one start per window, one more for a bin that reaches over the end of its window (at
+        // most one in each, of more than kBucketMax - 1 - target entries), one per row window
+        const int64_t windows = L.M / L.target, reach = L.M / (kBucketMax - 1 - L.target);
+        if (L.span_bins >= 1) L.bucket_bound = windows + (windows < reach ? windows : reach) + L.nbins / L.span_bins + 4;
+        return L.span_bins >= 1;
+    };
+    static_assert(kMaxBins == 1 << 15 && kSmallBins == 1 << 12, "bits of the bins");
+    L.small = L.n_items <= kSmallItems && bins(12) && L.bucket_bound <= kGroupBuckets;
+    if (!L.small && (!bins(15) || L.nbins > kMaxBins)) return false;
     if (L.bucket_bound > kMaxBuckets) return false;
     L.two_level = L.bucket_bound > kGroupBuckets;
     int64_t hb = (L.n_items + 16383) / 16384;
@@ -1076,13 +1144,22 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
                   u32(L.group_bin0), u32(L.group_off), u32(L.group_cursor), u32(L.group_tile0),
                   (uint16_t*)(ws + L.coarse_group)};
 
-    RETEXO_HIP_TRY(hipMemsetAsync(hdr, 0, (size_t)(L.counts - L.header), stream));      // header and bin counts
-    hist_kernel<<<dim3((unsigned)L.hist_blocks), dim3(kThreads), 0, stream>>>(
-        n_pairs, d_src, d_dst, N, L.n_items, L.items_per_block, L.s, L.nbins, u32(L.counts), hdr);
-    colsum_kernel<<<dim3((unsigned)((L.nbins + 255) / 256), kColsumSlices), dim3(256), 0, stream>>>(
-        L.hist_blocks, L.nbins, u32(L.counts), u32(L.bin_count));
-    plan_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(L.nbins, L.span_bins, (int)((1ll << (32 - L.cbits)) >> L.s), (uint32_t)L.target, (uint32_t)((1ull << 32) / (uint64_t)L.target), u32(L.bin_count), pa,
-                                                        (uint32_t)L.bucket_bound, hdr);
+    auto plan = [&](auto count) {
+        plan_kernel<decltype(count)::value><<<dim3(1), dim3(kThreads), 0, stream>>>(
+            L.nbins, L.span_bins, (int)((1ll << (32 - L.cbits)) >> L.s), (uint32_t)L.target,
+            (uint32_t)((1ull << 32) / (uint64_t)L.target), u32(L.bin_count), n_pairs, d_src, d_dst, N, L.n_items, L.s, pa,
+            (uint32_t)L.bucket_bound, hdr);
+    };
+    if (L.small) {
+        plan(std::true_type{});
+    } else {
+        RETEXO_HIP_TRY(hipMemsetAsync(hdr, 0, (size_t)(L.counts - L.header), stream));      // header and bin counts
+        hist_kernel<<<dim3((unsigned)L.hist_blocks), dim3(kThreads), 0, stream>>>(
+            n_pairs, d_src, d_dst, N, L.n_items, L.items_per_block, L.s, L.nbins, u32(L.counts), hdr);
+        colsum_kernel<<<dim3((unsigned)((L.nbins + 255) / 256), kColsumSlices), dim3(256), 0, stream>>>(
+            L.hist_blocks, L.nbins, u32(L.counts), u32(L.bin_count));
+        plan(std::false_type{});
+    }
     const unsigned item_tiles = (unsigned)((L.n_items + kItemsPerTile - 1) / kItemsPerTile);
     if (L.M > 0) {
         if (L.two_level) {
@@ -1101,10 +1178,17 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
     sort_kernel<<<dim3((unsigned)L.bucket_bound), dim3(kSortThreads), 0, stream>>>(
         hdr, pa.bucket_off, pa.bucket_bin0, u32(L.buf_c), u32(L.buf_a), (int32_t*)(ws + L.row_unique),
         u32(L.bucket_total), L.cbits, L.s, N);
-    total_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(hdr, u32(L.bucket_total), u32(L.bucket_out), col_capacity);
-    emit_kernel<<<dim3((unsigned)L.bucket_bound), dim3(256), 0, stream>>>(
-        hdr, pa.bucket_off, pa.bucket_bin0, u32(L.bucket_out), u32(L.buf_a), (const int32_t*)(ws + L.row_unique),
-        L.s, N, d_row_ptr, d_col_idx);
+    auto emit = [&](auto sum) {
+        emit_kernel<decltype(sum)::value><<<dim3((unsigned)L.bucket_bound), dim3(256), 0, stream>>>(
+            hdr, pa.bucket_off, pa.bucket_bin0, u32(L.bucket_out), u32(L.buf_a), (const int32_t*)(ws + L.row_unique),
+            u32(L.bucket_total), col_capacity, L.s, N, d_row_ptr, d_col_idx);
+    };
+    if (L.bucket_bound <= kFewBuckets) {
+        emit(std::true_type{});
+    } else {
+        total_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(hdr, u32(L.bucket_total), u32(L.bucket_out), col_capacity);
+        emit(std::false_type{});
+    }
     RETEXO_HIP_TRY(hipGetLastError());
     BucketHeader h;
     RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
