@@ -23,11 +23,9 @@
 // nodes count their members of every list, a scan over (list, block) places
 // them, and every block writes its own.
 #include <cstring>
+#include <type_traits>
 
-#include <rocprim/device/device_reduce.hpp>
 #include <rocprim/device/device_scan.hpp>
-#include <rocprim/iterator/counting_iterator.hpp>
-#include <rocprim/iterator/transform_iterator.hpp>
 
 #include "common.hpp"
 
@@ -54,18 +52,56 @@ __device__ __forceinline__ uint64_t wave_or(uint64_t x)
     return x;
 }
 
+__device__ __forceinline__ uint32_t wave_or(uint32_t x)
+{
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) x |= __shfl_xor(x, m, 64);
+    return x;
+}
+
 // state of a node while its share is derived: its owner, and whether it was found to be a boundary node
 constexpr uint32_t kBoundary = 0x80000000u;
+constexpr uint32_t kNobody = 0xffffu;         // (no worker has that id)
 
+// Graphs of up to some hundred thousand nodes keep what is looked up per entry in LDS, one workgroup per CU (mark_lds_kernel,
+// columns_lds_kernel): the owners in a power of two of bits each beside one bit per boundary node, and later sixteen bytes per 32
+// nodes that give a node's local id.  Gathering a word per entry from L2 instead is bound by the L2 requests, and is what
+// larger graphs do (mark_kernel, columns_kernel).
+constexpr int kLdsThreads = 1024;
+constexpr int kLdsWaves = kLdsThreads / 64;
+constexpr int kLdsBlocks = 256;               // one per CU
+constexpr int kTableWords = 36864;            // 144 KB
+constexpr int kListRows = 2560;               // rows of one workgroup
+constexpr int64_t kTableNodes = 32 * (kTableWords / 4);          // 294,912: nodes of columns_lds_kernel
+// Smaller graphs are bound by launches and latencies, which one workgroup per CU makes longer: both kernels 11 us over 2,000
+// nodes and 20,000 pairs, 6 over 40,000 and 400,000, even at 100,000 nodes and a million pairs.
+constexpr int64_t kMarkNodes = 65536;
+constexpr int64_t kTableEntries = 1 << 20;    // (the entries are not known before the nodes are marked)
+int owner_bits(int n_parts) { return n_parts <= 2 ? 1 : n_parts <= 4 ? 2 : n_parts <= 16 ? 4 : 8; }
+bool owners_fit(int64_t N, int n_parts)
+{
+    const int64_t words = (N * owner_bits(n_parts) + 31) / 32 + (N + 31) / 32;
+    return N >= kMarkNodes && words <= kTableWords && (N + kLdsBlocks - 1) / kLdsBlocks <= kListRows;
+}
+
+// `bits` != 0: also the owners packed that many bits each (a worker that does not exist as zero, the call then ends in an
+// error), and the boundary bits cleared
 __global__ __launch_bounds__(kThreads) void state_kernel(int64_t N, const int32_t* __restrict__ part, int n_parts,
-                                                         uint32_t* __restrict__ state, ShareHeader* hdr)
+                                                         uint32_t* __restrict__ state, int bits, uint32_t* __restrict__ owners,
+                                                         uint32_t* __restrict__ boundary, ShareHeader* hdr)
 {
     const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (v >= N) return;
-    const int q = part[v];
+    const int q = v < N ? part[v] : 0;
     const bool bad = q < 0 || q >= n_parts;
     if (bad) atomicOr(&hdr->bad_part, 1u);
-    state[v] = bad ? 0xffffu : (uint32_t)q;       // (no worker has that id; the call ends in an error)
+    if (v < N) state[v] = bad ? 0xffffu : (uint32_t)q;       // (no worker has that id; the call ends in an error)
+    if (bits) {
+        const int per = 32 / bits;                           // nodes per word
+        uint32_t w = (bad ? 0u : (uint32_t)q) << ((threadIdx.x % per) * bits);
+        for (int m = 1; m < per; m <<= 1) w |= __shfl_xor(w, m, 64);
+        if (v < N && threadIdx.x % per == 0) owners[v / per] = w;
+        if (v < N && threadIdx.x % 32 == 0) boundary[v / 32] = 0u;
+    }
 }
 
 // One wave per global row: an inner row marks the foreign endpoints of its entries as boundary nodes, collects the set of
@@ -114,112 +150,292 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(
     }
 }
 
-struct IsInner {
-    const int32_t* part;
-    int p;
-    __device__ uint32_t operator()(int64_t v) const { return part[v] == p ? 1u : 0u; }
+// The rows that a workgroup of the LDS kernels works on: short ones are handed to its waves one by one, long ones (a wave would
+// still be at work on one when all others are done) are shared by all waves afterwards.
+constexpr int64_t kLongRow = 2048;
+struct RowList {
+    uint16_t rows[kListRows];                    // short rows from the front, long rows from the back
+    uint32_t n_short, n_long, next;
 };
-struct InnerRowLength {
-    const int32_t* part;
-    const int64_t* row_ptr;
-    int p;
-    __device__ int64_t operator()(int64_t v) const { return part[v] == p ? row_ptr[v + 1] - row_ptr[v] : 0; }
-};
-struct IsBoundary {
-    const uint32_t* state;
-    __device__ uint32_t operator()(int64_t v) const { return state[v] >> 31; }
-};
-struct LocalRowLength {               // row length of local node i (0 for boundary nodes and for i == n_local)
-    const int32_t* local_ids;
-    const int64_t* row_ptr;
-    int64_t n_inner;
-    __device__ int64_t operator()(int64_t i) const
-    {
-        if (i >= n_inner) return 0;
-        const int64_t v = local_ids[i];
-        return row_ptr[v + 1] - row_ptr[v];
-    }
-};
-
-// The 2 * n_parts lists (list q: what peer q is sent, list n_parts + q: what it sends): members per block of kThreads
-// nodes, counts[list * blocks + block].  A wave counts its 64 nodes with one ballot per list.
-__device__ __forceinline__ uint64_t list_members(int list, int n_parts, uint64_t m, uint32_t st)
+__device__ __forceinline__ void list_rows(RowList& l, int64_t first, int64_t end, bool mine, int64_t at, int64_t length)
 {
-    return __ballot(list < n_parts ? (m >> list) & 1ull : (st & kBoundary) && (st & 0xffffu) == (uint32_t)(list - n_parts));
+    // whole waves: at = the lane's row (or past the end)
+    const int lane = threadIdx.x & 63;
+    const bool have = at < end && mine;
+    const uint64_t s = __ballot(have && length <= kLongRow), g = __ballot(have && length > kLongRow);
+    uint32_t s0 = 0, g0 = 0;
+    if (lane == 0) {
+        if (s) s0 = atomicAdd(&l.n_short, (uint32_t)__popcll(s));
+        if (g) g0 = atomicAdd(&l.n_long, (uint32_t)__popcll(g));
+    }
+    s0 = __shfl(s0, 0, 64);
+    g0 = __shfl(g0, 0, 64);
+    const uint64_t below = (1ull << lane) - 1;
+    if ((s >> lane) & 1ull) l.rows[s0 + __popcll(s & below)] = (uint16_t)(at - first);
+    if ((g >> lane) & 1ull) l.rows[kListRows - 1 - (g0 + __popcll(g & below))] = (uint16_t)(at - first);
 }
-__global__ __launch_bounds__(kThreads) void list_count_kernel(int64_t N, int n_parts, const uint32_t* __restrict__ state,
-                                                              const uint64_t* __restrict__ mask, int64_t blocks,
-                                                              uint32_t* __restrict__ counts)
+__device__ __forceinline__ uint32_t next_row(RowList& l)
 {
-    __shared__ uint32_t sh[kThreads / 64][2 * kMaxWorkers];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const uint64_t m = v < N ? mask[v] : 0ull;
-    const uint32_t st = v < N ? state[v] : 0u;
-    for (int l = 0; l < 2 * n_parts; ++l) {
-        const uint32_t c = (uint32_t)__popcll(list_members(l, n_parts, m, st));
-        if (lane == 0) sh[wave][l] = c;
-    }
+    uint32_t k = 0;
+    if ((threadIdx.x & 63) == 0) k = atomicAdd(&l.next, 1u);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)__shfl(k, 0, 64));
+}
+
+// mark_kernel with the owners in LDS; a workgroup marks its rows' boundary nodes there too and adds them to all others' at
+// the end.  Bound by reading the inner rows' columns.  Worker 0 of 4 of the Reddit-shaped graph: 231 -> 76 us.
+constexpr int kLdsAhead = 8;
+template <int BITS>
+__global__ __launch_bounds__(kLdsThreads) void mark_lds_kernel(
+    int64_t N, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx, int p,
+    const uint32_t* __restrict__ owners, uint32_t* __restrict__ boundary, uint64_t* __restrict__ mask,
+    uint32_t* __restrict__ inner_entries)
+{
+    constexpr int PER = 32 / BITS;
+    __shared__ uint32_t table[kTableWords];
+    __shared__ RowList list;
+    __shared__ uint64_t all_mask;
+    __shared__ uint32_t all_inner;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int words = (int)((N + PER - 1) / PER), marks = (int)((N + 31) / 32);
+    uint32_t* marked = table + words;
+    for (int i = tid; i < words; i += kLdsThreads) table[i] = owners[i];
+    for (int i = tid; i < marks; i += kLdsThreads) marked[i] = 0u;
+    if (tid == 0) list.n_short = list.n_long = list.next = 0u;
     __syncthreads();
-    for (int l = threadIdx.x; l < 2 * n_parts; l += kThreads)
-        counts[(int64_t)l * blocks + blockIdx.x] = (sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l]);
-}
-
-// totals of the scans (last scan value + last element), N >= 1; the lists' offsets are their first blocks' positions
-__global__ __launch_bounds__(kThreads) void totals_kernel(int64_t N, const int32_t* __restrict__ part, int p, int n_parts,
-                                                          const uint32_t* __restrict__ rank_in, const uint32_t* __restrict__ state,
-                                                          const uint32_t* __restrict__ rank_halo, int64_t blocks,
-                                                          const uint32_t* __restrict__ list_at, ShareHeader* hdr)
-{
-    const int64_t n_halo = (int64_t)rank_halo[N - 1] + (int64_t)(state[N - 1] >> 31);
-    const int64_t n_send = list_at[(int64_t)n_parts * blocks];
-    for (int l = threadIdx.x; l <= n_parts; l += kThreads) {
-        hdr->send_off[l] = list_at[(int64_t)l * blocks];
-        hdr->recv_off[l] = l == n_parts ? n_halo : (int64_t)list_at[(int64_t)(n_parts + l) * blocks] - n_send;
-    }
-    if (threadIdx.x == 0) {
-        hdr->n_inner = (int64_t)rank_in[N - 1] + (part[N - 1] == p ? 1 : 0);
-        hdr->n_halo = n_halo;
-        hdr->n_send = n_send;
-    }
-}
-
-// local numbering, global ids and degrees of the local nodes, and the members of the lists: a wave's members of a list go
-// behind those of the waves and blocks before it
-__global__ __launch_bounds__(kThreads) void number_kernel(
-    int64_t N, const int64_t* __restrict__ row_ptr, int p, int n_parts,
-    const uint32_t* __restrict__ rank_in, const uint32_t* __restrict__ state, const uint64_t* __restrict__ mask,
-    const uint32_t* __restrict__ rank_halo, int64_t n_inner, int64_t n_send, int64_t blocks,
-    const uint32_t* __restrict__ list_at, int32_t* __restrict__ to_local,
-    int32_t* __restrict__ local_ids, int32_t* __restrict__ global_deg, int32_t* __restrict__ send_ids,
-    int32_t* __restrict__ recv_ids)
-{
-    __shared__ uint32_t sh[kThreads / 64][2 * kMaxWorkers];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const uint32_t st = v < N ? state[v] : 0u;
-    const uint64_t m = v < N ? mask[v] : 0ull;
-    int64_t l = -1;
-    if (v < N) {
-        if ((st & 0xffffu) == (uint32_t)p) l = rank_in[v];
-        else if (st & kBoundary) l = n_inner + rank_halo[v];
-        to_local[v] = (int32_t)l;
-        if (l >= 0) {
-            local_ids[l] = (int32_t)v;
-            global_deg[l] = (int32_t)(row_ptr[v + 1] - row_ptr[v]);
+    auto owner = [&](uint32_t u) { return (table[u / PER] >> (u % PER * BITS)) & ((1u << BITS) - 1u); };
+    const int64_t per = (N + gridDim.x - 1) / gridDim.x, first = blockIdx.x * per, end = min(first + per, N);
+    for (int64_t r0 = first + (tid - lane); r0 < end; r0 += kLdsThreads) {
+        const int64_t v = r0 + lane;
+        const bool mine = v < end && owner((uint32_t)v) == (uint32_t)p;
+        list_rows(list, first, end, mine, v, mine ? row_ptr[v + 1] - row_ptr[v] : 0);
+        if (v < end && !mine) {
+            mask[v] = 0ull;
+            inner_entries[v] = 0u;
         }
     }
-    for (int q = 0; q < 2 * n_parts; ++q) {
-        const uint32_t c = (uint32_t)__popcll(list_members(q, n_parts, m, st));
-        if (lane == 0) sh[wave][q] = c;
+    __syncthreads();
+    // the entries [lo, hi) of one row, `step` waves taking batches in turn from batch k on
+    typedef std::conditional_t<BITS == 8, uint64_t, uint32_t> mask_t;        // (up to 16 workers otherwise)
+    mask_t m;
+    uint32_t inner;
+    auto batch = [&](int64_t e0, int64_t hi, auto tiles) {
+        constexpr int T = decltype(tiles)::value;
+        int32_t u[T];
+        uint32_t q[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) u[t] = e0 + 64 * t + lane < hi ? col_idx[e0 + 64 * t + lane] : -1;
+#pragma unroll
+        for (int t = 0; t < T; ++t) q[t] = owner((uint32_t)max(u[t], 0));
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const bool out = u[t] >= 0 && q[t] != (uint32_t)p;
+            inner += (uint32_t)__popcll(__ballot(u[t] >= 0 && !out));
+            if (out) atomicOr(&marked[u[t] >> 5], 1u << (u[t] & 31));
+            m |= out ? (mask_t)1 << q[t] : (mask_t)0;
+        }
+    };
+    auto walk = [&](int64_t lo, int64_t hi, int k, int step) {
+        m = 0;
+        inner = 0;
+        constexpr int SPAN = 64 * kLdsAhead;
+        int64_t e0 = lo + (int64_t)SPAN * k;
+        for (; hi - e0 > SPAN / 2; e0 += (int64_t)SPAN * step) batch(e0, hi, std::integral_constant<int, kLdsAhead>{});
+        if (hi - e0 > 128) batch(e0, hi, std::integral_constant<int, kLdsAhead / 2>{});
+        else if (hi > e0) batch(e0, hi, std::integral_constant<int, 2>{});
+        m = wave_or(m);
+    };
+    const uint32_t n_short = list.n_short, n_long = list.n_long;
+    // (the next row's place is looked up while the current one is walked through)
+    auto ask = [&](uint32_t k, int64_t& v, int64_t& lo, int64_t& hi) {
+        v = first + (k < n_short ? list.rows[k] : 0);
+        lo = k < n_short ? row_ptr[v] : 0;
+        hi = k < n_short ? row_ptr[v + 1] : 0;
+    };
+    int64_t v, lo, hi;
+    uint32_t k = next_row(list);
+    ask(k, v, lo, hi);
+    while (k < n_short) {
+        int64_t v2, lo2, hi2;
+        k = next_row(list);
+        ask(k, v2, lo2, hi2);
+        walk(lo, hi, 0, 1);
+        if (lane == 0) {
+            mask[v] = m;
+            inner_entries[v] = inner;
+        }
+        v = v2;
+        lo = lo2;
+        hi = hi2;
+    }
+    for (uint32_t l = 0; l < n_long; ++l) {
+        v = first + list.rows[kListRows - 1 - l];
+        __syncthreads();
+        if (tid == 0) {
+            all_mask = 0ull;
+            all_inner = 0u;
+        }
+        __syncthreads();
+        walk(row_ptr[v], row_ptr[v + 1], wave, kLdsWaves);
+        if (lane == 0) {
+            atomicOr((unsigned long long*)&all_mask, (unsigned long long)m);
+            atomicAdd(&all_inner, inner);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            mask[v] = all_mask;
+            inner_entries[v] = all_inner;
+        }
     }
     __syncthreads();
+    for (int i = tid; i < marks; i += kLdsThreads)
+        if (marked[i]) atomicOr(&boundary[i], marked[i]);
+}
+
+// The 2 * n_parts lists (list q: what peer q is sent, list n_parts + q: what it sends), the inner and the boundary nodes:
+// members per block of kThreads nodes, counts[list * blocks + block].  A wave counts its 64 nodes with one ballot per
+// list.  The inner rows' entries are added up per block beside them, so that one scan and one more pass over the nodes give all
+// numbers and places (three scans and a sum over the nodes were ten launches, 45 us of the Reddit-shaped graph's share).
+constexpr int kMaxLists = 2 * kMaxWorkers + 2;
+__device__ __forceinline__ uint64_t list_members(int list, int n_parts, int p, uint64_t m, uint32_t st)
+{
+    // st of a lane without a node: kNobody
+    if (list < n_parts) return __ballot((m >> list) & 1ull);
+    if (list < 2 * n_parts) return __ballot((st & kBoundary) && (st & 0xffffu) == (uint32_t)(list - n_parts));
+    return __ballot(list == 2 * n_parts ? (st & 0xffffu) == (uint32_t)p : (st & kBoundary) != 0u);
+}
+// `boundary`: the bits of mark_lds_kernel, which go into the states here; else NULL
+__global__ __launch_bounds__(kThreads) void list_count_kernel(int64_t N, int n_parts, int p, const int64_t* __restrict__ row_ptr,
+                                                              uint32_t* __restrict__ state,
+                                                              const uint32_t* __restrict__ boundary,
+                                                              const uint64_t* __restrict__ mask, int64_t blocks,
+                                                              uint32_t* __restrict__ counts, int64_t* __restrict__ block_entries)
+{
+    __shared__ uint32_t sh[kThreads / 64][kMaxLists];
+    __shared__ int64_t entries[kThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const uint64_t m = v < N ? mask[v] : 0ull;
+    uint32_t st = v < N ? state[v] : kNobody;
+    if (boundary && v < N) {
+        if ((boundary[v >> 5] >> (v & 31)) & 1u) st |= kBoundary;
+        state[v] = st;
+    }
+    for (int l = 0; l < 2 * n_parts + 2; ++l) {
+        const uint32_t c = (uint32_t)__popcll(list_members(l, n_parts, p, m, st));
+        if (lane == 0) sh[wave][l] = c;
+    }
+    int64_t e = v < N && (st & 0xffffu) == (uint32_t)p ? row_ptr[v + 1] - row_ptr[v] : 0;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) e += __shfl_xor((long long)e, d, 64);
+    if (lane == 0) entries[wave] = e;
+    __syncthreads();
+    for (int l = threadIdx.x; l < 2 * n_parts + 2; l += kThreads)
+        counts[(int64_t)l * blocks + blockIdx.x] = (sh[0][l] + sh[1][l]) + (sh[2][l] + sh[3][l]);
+    if (threadIdx.x == 0) block_entries[blockIdx.x] = (entries[0] + entries[1]) + (entries[2] + entries[3]);
+}
+
+// the header's sizes, N >= 1: a list's offset is its first block's position; block_entries becomes its exclusive prefix sum
+__global__ __launch_bounds__(kLdsThreads) void totals_kernel(int n_parts, int64_t blocks, const uint32_t* __restrict__ list_at,
+                                                             int64_t* __restrict__ block_entries, ShareHeader* hdr)
+{
+    __shared__ int64_t sums[kLdsWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto at = [&](int l) { return list_at[(int64_t)l * blocks]; };         // (differences are exact modulo 2^32)
+    for (int l = tid; l <= n_parts; l += kLdsThreads) {
+        hdr->send_off[l] = at(l);
+        hdr->recv_off[l] = (int64_t)(at(n_parts + l) - at(n_parts));
+    }
+    if (tid == 0) {
+        hdr->n_inner = (int64_t)(at(2 * n_parts + 1) - at(2 * n_parts));
+        hdr->n_halo = (int64_t)(at(2 * n_parts + 2) - at(2 * n_parts + 1));
+        hdr->n_send = at(n_parts);
+    }
+    int64_t before = 0;
+    for (int64_t b0 = 0; b0 < blocks; b0 += kLdsThreads) {
+        const int64_t mine = b0 + tid < blocks ? block_entries[b0 + tid] : 0;
+        int64_t incl = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int64_t t = __shfl_up((long long)incl, d, 64);
+            if (lane >= d) incl += t;
+        }
+        if (lane == 63) sums[wave] = incl;
+        __syncthreads();
+        int64_t all = 0;
+        for (int w = 0; w < kLdsWaves; ++w) {
+            if (w < wave) incl += sums[w];
+            all += sums[w];
+        }
+        if (b0 + tid < blocks) block_entries[b0 + tid] = before + incl - mine;
+        before += all;
+        __syncthreads();
+    }
+    if (tid == 0) hdr->nnz_local = before;
+}
+
+// local numbering, global ids, degrees and row offsets of the local nodes, and the members of the lists: a wave's members of a
+// list go behind those of the waves and blocks before it
+__global__ __launch_bounds__(kThreads) void number_kernel(
+    int64_t N, const int64_t* __restrict__ row_ptr, int p, int n_parts,
+    const uint32_t* __restrict__ state, const uint64_t* __restrict__ mask,
+    int64_t n_inner, int64_t n_local, int64_t nnz_local, int64_t n_send, int64_t blocks,
+    const uint32_t* __restrict__ list_at, const int64_t* __restrict__ entries_before,
+    int32_t* __restrict__ to_local, uint4* __restrict__ table,
+    int32_t* __restrict__ local_ids, int64_t* __restrict__ local_row_ptr, int32_t* __restrict__ global_deg,
+    int32_t* __restrict__ send_ids, int32_t* __restrict__ recv_ids)
+{
+    __shared__ uint32_t sh[kThreads / 64][kMaxLists];
+    __shared__ int64_t entries[kThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t st = v < N ? state[v] : kNobody;
+    const uint64_t m = v < N ? mask[v] : 0ull;
+    const bool inner = (st & 0xffffu) == (uint32_t)p, halo = (st & kBoundary) != 0u;
+    for (int q = 0; q < 2 * n_parts + 2; ++q) {
+        const uint32_t c = (uint32_t)__popcll(list_members(q, n_parts, p, m, st));
+        if (lane == 0) sh[wave][q] = c;
+    }
+    const int64_t deg = v < N ? row_ptr[v + 1] - row_ptr[v] : 0;
+    int64_t incl = inner ? deg : 0;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int64_t t = __shfl_up((long long)incl, d, 64);
+        if (lane >= d) incl += t;
+    }
+    if (lane == 63) entries[wave] = incl;
+    __syncthreads();
     const uint64_t below = (1ull << lane) - 1;
-    for (int q = 0; q < 2 * n_parts; ++q) {
-        const uint64_t members = list_members(q, n_parts, m, st);
-        if (!((members >> lane) & 1ull)) continue;
-        int64_t at = (int64_t)list_at[(int64_t)q * blocks + blockIdx.x] + __popcll(members & below);
+    // position of the lane among the members of a list
+    auto place = [&](int q, uint64_t members) {
+        uint32_t at = list_at[(int64_t)q * blocks + blockIdx.x] + (uint32_t)__popcll(members & below);
         for (int w = 0; w < wave; ++w) at += sh[w][q];
+        return at;
+    };
+    const uint64_t ins = list_members(2 * n_parts, n_parts, p, m, st), outs = list_members(2 * n_parts + 1, n_parts, p, m, st);
+    const uint32_t before_in = place(2 * n_parts, ins) - list_at[(int64_t)2 * n_parts * blocks];
+    const int64_t before_out = n_inner + (int64_t)(place(2 * n_parts + 1, outs) - list_at[(int64_t)(2 * n_parts + 1) * blocks]);
+    const int64_t l = inner ? (int64_t)before_in : halo ? before_out : -1;
+    if (v < N) {
+        if (!table) to_local[v] = (int32_t)l;
+        if (l >= 0) {
+            int64_t first = nnz_local;                       // (boundary rows are empty)
+            if (inner) {
+                first = entries_before[blockIdx.x] + incl - deg;
+                for (int w = 0; w < wave; ++w) first += entries[w];
+            }
+            local_ids[l] = (int32_t)v;
+            local_row_ptr[l] = first;
+            global_deg[l] = (int32_t)deg;
+        }
+        // per 32 nodes: which are inner, inner ids before them, which are boundary nodes, boundary ids before them
+        if (table && (lane & 31) == 0)
+            table[v >> 5] = make_uint4((uint32_t)(ins >> lane), before_in, (uint32_t)(outs >> lane), (uint32_t)before_out);
+    }
+    if (v == 0) local_row_ptr[n_local] = nnz_local;
+    for (int q = 0; q < 2 * n_parts; ++q) {
+        const uint64_t members = list_members(q, n_parts, p, m, st);
+        if (!((members >> lane) & 1ull)) continue;
+        const int64_t at = place(q, members);
         if (q < n_parts) send_ids[at] = (int32_t)l;
         else recv_ids[at - n_send] = (int32_t)l;
     }
@@ -261,6 +477,103 @@ __global__ __launch_bounds__(kThreads) void columns_kernel(
     }
 }
 
+// columns_kernel with the numbering in LDS (number_kernel's table).  A long row is cut into one piece per wave, whose inner
+// entries are counted first.  Worker 0 of 4 of the Reddit-shaped graph: 192 -> 87 us.
+__global__ __launch_bounds__(kLdsThreads) void columns_lds_kernel(
+    int64_t N, int64_t n_inner, const int32_t* __restrict__ local_ids, const int64_t* __restrict__ row_ptr,
+    const int32_t* __restrict__ col_idx, const uint4* __restrict__ numbering, const uint32_t* __restrict__ inner_entries,
+    const int64_t* __restrict__ local_row_ptr, int32_t* __restrict__ local_col)
+{
+    __shared__ uint4 table[kTableWords / 4];
+    __shared__ RowList list;
+    __shared__ uint32_t piece_inner[kLdsWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int words = (int)((N + 31) / 32);
+    for (int i = tid; i < words; i += kLdsThreads) table[i] = numbering[i];
+    if (tid == 0) list.n_short = list.n_long = list.next = 0u;
+    __syncthreads();
+    const int64_t per = (n_inner + gridDim.x - 1) / gridDim.x, first = blockIdx.x * per, end = min(first + per, n_inner);
+    for (int64_t r0 = first + (tid - lane); r0 < end; r0 += kLdsThreads) {
+        const int64_t i = r0 + lane;
+        list_rows(list, first, end, true, i, i < end ? local_row_ptr[i + 1] - local_row_ptr[i] : 0);
+    }
+    __syncthreads();
+    const uint64_t below = (1ull << lane) - 1;
+    // the entries [lo, hi) of a row, up to kLdsAhead tiles of 64 in flight
+    auto batch = [&](int64_t e0, int64_t hi, auto tiles, auto use) {
+        constexpr int T = decltype(tiles)::value;
+        int32_t u[T];
+        uint4 w[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) u[t] = e0 + 64 * t + lane < hi ? col_idx[e0 + 64 * t + lane] : -1;
+#pragma unroll
+        for (int t = 0; t < T; ++t) w[t] = table[max(u[t], 0) >> 5];
+#pragma unroll
+        for (int t = 0; t < T; ++t) use(u[t], w[t]);
+    };
+    auto walk = [&](int64_t lo, int64_t hi, auto use) {
+        constexpr int SPAN = 64 * kLdsAhead;
+        int64_t e0 = lo;
+        for (; hi - e0 > SPAN / 2; e0 += SPAN) batch(e0, hi, std::integral_constant<int, kLdsAhead>{}, use);
+        if (hi - e0 > 128) batch(e0, hi, std::integral_constant<int, kLdsAhead / 2>{}, use);
+        else if (hi > e0) batch(e0, hi, std::integral_constant<int, 2>{}, use);
+    };
+    auto place = [&](int64_t lo, int64_t hi, int64_t at_in, int64_t at_out) {
+        walk(lo, hi, [&](int32_t u, const uint4& w) {
+            const bool valid = u >= 0;
+            const uint32_t bit = 1u << (u & 31);
+            const bool in = valid && (w.x & bit), out = valid && !in;
+            const uint64_t bin = __ballot(in), bout = __ballot(out);
+            const uint32_t l = in ? w.y + __popc(w.x & (bit - 1)) : w.w + __popc(w.z & (bit - 1));
+            const int64_t at = in ? at_in + __popcll(bin & below) : at_out + __popcll(bout & below);
+            if (valid) local_col[at] = (int32_t)l;
+            at_in += __popcll(bin);
+            at_out += __popcll(bout);
+        });
+    };
+    const uint32_t n_short = list.n_short, n_long = list.n_long;
+    // (the next row's place is looked up while the current one is written)
+    struct Row {
+        int64_t lo, hi, base;
+        uint32_t inner;
+    };
+    auto ask = [&](uint32_t k) {
+        Row r = {0, 0, 0, 0u};
+        if (k < n_short) {
+            const int64_t i = first + list.rows[k], v = local_ids[i];
+            r.base = local_row_ptr[i];
+            r.lo = row_ptr[v];
+            r.hi = row_ptr[v + 1];
+            r.inner = inner_entries[v];
+        }
+        return r;
+    };
+    uint32_t k = next_row(list);
+    Row row = ask(k);
+    while (k < n_short) {
+        k = next_row(list);
+        const Row next = ask(k);
+        place(row.lo, row.hi, row.base, row.base + row.inner);
+        row = next;
+    }
+    for (uint32_t l = 0; l < n_long; ++l) {
+        const int64_t i = first + list.rows[kListRows - 1 - l], v = local_ids[i], base = local_row_ptr[i];
+        const int64_t lo = row_ptr[v], hi = row_ptr[v + 1];
+        const int64_t piece = ((hi - lo + kLdsWaves - 1) / kLdsWaves + 63) / 64 * 64;
+        const int64_t from = min(lo + piece * wave, hi), to = min(from + piece, hi);
+        uint32_t inner = 0;
+        walk(from, to, [&](int32_t u, const uint4& w) {
+            inner += (uint32_t)__popcll(__ballot(u >= 0 && ((w.x >> (u & 31)) & 1u)));
+        });
+        __syncthreads();
+        if (lane == 0) piece_inner[wave] = inner;
+        __syncthreads();
+        uint32_t before = 0;
+        for (int w = 0; w < wave; ++w) before += piece_inner[w];
+        place(from, to, base + before, base + inner_entries[v] + ((from - lo) - before));
+    }
+}
+
 // rows of a table <-> a dense buffer; one thread per VEC floats
 template <int VEC, bool SCATTER>
 __global__ __launch_bounds__(kThreads) void rows_kernel(
@@ -298,7 +611,9 @@ __global__ __launch_bounds__(kThreads) void set_degrees_kernel(int64_t N, const 
 }
 
 struct Layout {
-    int64_t header, mask, state, rank_in, rank_halo, inner_entries, to_local, counts, list_at, tmp, blocks, total;
+    bool lds_marks, lds_columns;
+    int64_t owners, boundary, table;
+    int64_t header, mask, state, block_entries, inner_entries, to_local, counts, list_at, tmp, blocks, total;
     size_t tmp_bytes;
 };
 
@@ -306,32 +621,24 @@ int make_layout(int64_t N, int n_parts, Layout& L)
 {
     const int64_t n = N > 0 ? N : 1;
     L.blocks = (n + kThreads - 1) / kThreads;
-    const int64_t lists = 2 * (int64_t)n_parts * L.blocks + 1;
-    size_t a = 0, b = 0, c = 0, d = 0;
-    auto it32 = rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0), IsInner{nullptr, 0});
-    auto it64 = rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0),
-                                                 InnerRowLength{nullptr, nullptr, 0});
-    if (rocprim::exclusive_scan(nullptr, a, it32, (uint32_t*)nullptr, 0u, (size_t)n, rocprim::plus<uint32_t>(),
+    const int64_t lists = (2 * (int64_t)n_parts + 2) * L.blocks + 1;
+    L.tmp_bytes = 0;
+    if (rocprim::exclusive_scan(nullptr, L.tmp_bytes, (uint32_t*)nullptr, (uint32_t*)nullptr, 0u, (size_t)lists, rocprim::plus<uint32_t>(),
                                 (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
-    if (rocprim::exclusive_scan(nullptr, b, it64, (int64_t*)nullptr, (int64_t)0, (size_t)(n + 1),
-                                rocprim::plus<int64_t>(), (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
-    if (rocprim::reduce(nullptr, c, it64, (int64_t*)nullptr, (int64_t)0, (size_t)n, rocprim::plus<int64_t>(),
-                        (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
-    if (rocprim::exclusive_scan(nullptr, d, (uint32_t*)nullptr, (uint32_t*)nullptr, 0u, (size_t)lists, rocprim::plus<uint32_t>(),
-                                (hipStream_t)0) != hipSuccess) return RETEXO_E_HIP;
-    L.tmp_bytes = a > b ? a : b;
-    if (c > L.tmp_bytes) L.tmp_bytes = c;
-    if (d > L.tmp_bytes) L.tmp_bytes = d;
     int64_t off = 0;
     L.header = off;    off += align_up((int64_t)sizeof(ShareHeader), 256);
     L.mask = off;      off += align_up(8 * n, 256);
     L.state = off;     off += align_up(4 * n, 256);
-    L.rank_in = off;   off += align_up(4 * n, 256);
-    L.rank_halo = off; off += align_up(4 * n, 256);
+    L.block_entries = off; off += align_up(8 * L.blocks, 256);
     L.inner_entries = off; off += align_up(4 * n, 256);
     L.to_local = off;  off += align_up(4 * n, 256);
     L.counts = off;    off += align_up(4 * lists, 256);
     L.list_at = off;   off += align_up(4 * lists, 256);
+    L.lds_marks = owners_fit(N, n_parts);
+    L.lds_columns = N <= kTableNodes;
+    L.owners = off;    off += L.lds_marks ? align_up(n, 256) : 0;                     // (at most eight bits each)
+    L.boundary = off;  off += L.lds_marks ? align_up((n + 31) / 32 * 4, 256) : 0;
+    L.table = off;     off += L.lds_columns ? align_up((n + 31) / 32 * 16, 256) : 0;
     L.tmp = off;       off += align_up((int64_t)L.tmp_bytes, 256);
     L.total = off;
     return RETEXO_OK;
@@ -386,8 +693,7 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     ShareHeader* hdr = (ShareHeader*)(ws + L.header);
     uint64_t* mask = (uint64_t*)(ws + L.mask);
     uint32_t* state = (uint32_t*)(ws + L.state);
-    uint32_t* rank_in = (uint32_t*)(ws + L.rank_in);
-    uint32_t* rank_halo = (uint32_t*)(ws + L.rank_halo);
+    int64_t* block_entries = (int64_t*)(ws + L.block_entries);
     uint32_t* inner_entries = (uint32_t*)(ws + L.inner_entries);
     int32_t* to_local = (int32_t*)(ws + L.to_local);
     uint32_t* counts = (uint32_t*)(ws + L.counts);
@@ -397,26 +703,31 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     RETEXO_HIP_TRY(hipMemsetAsync(hdr, 0, sizeof(ShareHeader), stream));
     const dim3 node_grid((unsigned)L.blocks);
     if (N > 0) {
-        state_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(N, d_part, n_parts, state, hdr);
-        const int rows_per_block = kThreads / 64;
-        mark_kernel<<<dim3((unsigned)((N + rows_per_block - 1) / rows_per_block)), dim3(kThreads), 0, stream>>>(
-            N, d_row_ptr, d_col_idx, part, state, mask, inner_entries);
-        auto count = rocprim::make_counting_iterator<int64_t>(0);
+        uint32_t* owners = (uint32_t*)(ws + L.owners);
+        uint32_t* boundary = L.lds_marks ? (uint32_t*)(ws + L.boundary) : nullptr;
+        const int bits = owner_bits(n_parts);
+        state_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(N, d_part, n_parts, state, L.lds_marks ? bits : 0, owners, boundary,
+                                                               hdr);
+        if (L.lds_marks) {
+            const dim3 grid((unsigned)((N + 15) / 16 < kLdsBlocks ? (N + 15) / 16 : kLdsBlocks));
+            auto mark = [&](auto kernel) {
+                kernel<<<grid, dim3(kLdsThreads), 0, stream>>>(N, d_row_ptr, d_col_idx, part, owners, boundary, mask, inner_entries);
+            };
+            if (bits == 1) mark(mark_lds_kernel<1>);
+            else if (bits == 2) mark(mark_lds_kernel<2>);
+            else if (bits == 4) mark(mark_lds_kernel<4>);
+            else mark(mark_lds_kernel<8>);
+        } else {
+            const int rows_per_block = kThreads / 64;
+            mark_kernel<<<dim3((unsigned)((N + rows_per_block - 1) / rows_per_block)), dim3(kThreads), 0, stream>>>(
+                N, d_row_ptr, d_col_idx, part, state, mask, inner_entries);
+        }
+        list_count_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(N, n_parts, part, d_row_ptr, state, boundary, mask, L.blocks,
+                                                                    counts, block_entries);
         size_t tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, rocprim::make_transform_iterator(count, IsInner{d_part, part}),
-                                               rank_in, 0u, (size_t)N, rocprim::plus<uint32_t>(), stream));
-        tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, rocprim::make_transform_iterator(count, IsBoundary{state}), rank_halo,
-                                               0u, (size_t)N, rocprim::plus<uint32_t>(), stream));
-        list_count_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(N, n_parts, state, mask, L.blocks, counts);
-        tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, counts, list_at, 0u, (size_t)(2 * n_parts * L.blocks + 1),
+        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, counts, list_at, 0u, (size_t)((2 * n_parts + 2) * L.blocks + 1),
                                                rocprim::plus<uint32_t>(), stream));
-        tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::reduce(tmp, tb, rocprim::make_transform_iterator(count, InnerRowLength{d_part, d_row_ptr, part}),
-                                       &hdr->nnz_local, (int64_t)0, (size_t)N, rocprim::plus<int64_t>(), stream));
-        totals_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>(N, d_part, part, n_parts, rank_in, state, rank_halo, L.blocks,
-                                                              list_at, hdr);
+        totals_kernel<<<dim3(1), dim3(kLdsThreads), 0, stream>>>(n_parts, L.blocks, list_at, block_entries, hdr);
     }
     ShareHeader h;
     RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
@@ -435,19 +746,19 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     if (h.nnz_local > 0 && !d_local_col_idx) return RETEXO_E_NULL;
     if ((h.n_send > 0 && !d_send_ids) || (h.n_halo > 0 && !d_recv_ids)) return RETEXO_E_NULL;
 
+    uint4* table = L.lds_columns && h.nnz_local >= kTableEntries ? (uint4*)(ws + L.table) : nullptr;
     if (N > 0) {
         number_kernel<<<node_grid, dim3(kThreads), 0, stream>>>(
-            N, d_row_ptr, part, n_parts, rank_in, state, mask, rank_halo, h.n_inner, h.n_send, L.blocks, list_at, to_local,
-            d_local_ids, d_global_deg, d_send_ids, d_recv_ids);
+            N, d_row_ptr, part, n_parts, state, mask, h.n_inner, n_local, h.nnz_local, h.n_send, L.blocks, list_at, block_entries,
+            to_local, table, d_local_ids, d_local_row_ptr, d_global_deg, d_send_ids, d_recv_ids);
+    } else {
+        RETEXO_HIP_TRY(hipMemsetAsync(d_local_row_ptr, 0, sizeof(int64_t), stream));
     }
-    {
-        auto len = rocprim::make_transform_iterator(rocprim::make_counting_iterator<int64_t>(0),
-                                                    LocalRowLength{d_local_ids, d_row_ptr, h.n_inner});
-        size_t tb = L.tmp_bytes;
-        RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, len, d_local_row_ptr, (int64_t)0, (size_t)(n_local + 1),
-                                               rocprim::plus<int64_t>(), stream));
-    }
-    if (h.n_inner > 0) {
+    if (h.n_inner > 0 && table) {
+        const int64_t blocks = (h.n_inner + 15) / 16;
+        columns_lds_kernel<<<dim3((unsigned)(blocks < kLdsBlocks ? blocks : kLdsBlocks)), dim3(kLdsThreads), 0, stream>>>(
+            N, h.n_inner, d_local_ids, d_row_ptr, d_col_idx, table, inner_entries, d_local_row_ptr, d_local_col_idx);
+    } else if (h.n_inner > 0) {
         const int rows_per_block = kThreads / 64;
         columns_kernel<<<dim3((unsigned)((h.n_inner + rows_per_block - 1) / rows_per_block)), dim3(kThreads), 0, stream>>>(
             h.n_inner, d_local_ids, d_row_ptr, d_col_idx, to_local, inner_entries, d_local_row_ptr, d_local_col_idx);
