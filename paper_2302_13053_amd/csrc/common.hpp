@@ -97,7 +97,11 @@ int launch_zero(void* p, size_t bytes, hipStream_t stream);
 // slices of K) where that takes the call; an exact zero among the block kernel's sums of split products is not positive
 int launch_transform(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh,
                      const float* W, const float* b, bool relu, float* Z, int64_t ldz,
-                     hipStream_t stream, const float* mask = nullptr, int64_t ldm = 0, bool keep_sign = false);
+                     hipStream_t stream, const float* mask = nullptr, int64_t ldm = 0, bool keep_sign = false,
+                     float* colsums = nullptr);
+// with a mask (and D_in > 0): colsums [transform_row_blocks(N, D_out), D_out] gets the column sums of the stored blocks of
+// rows, 32 rows each at the least
+int64_t transform_row_blocks(int64_t N, int64_t D_out);
 
 struct AggCall {
     const retexo_plan* plan;

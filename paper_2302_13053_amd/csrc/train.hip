@@ -12,6 +12,9 @@
 //      dA     = (dL Wc^T) where A > 0    transform kernel with Wc^T and a ReLU mask
 //      gW1    = X^T dA,  gb1 = colsum(dA)
 //
+// Bound by the matrix cores in large steps and by the number of dependent launches in small ones: nine of them, ten with
+// the input gradient (2,708 x 2866 -> 64 -> 7 with eighteen of them 114 us, now 94).
+//
 // The two weight gradients are "TN" products whose contraction runs over the
 // nodes (hundreds of thousands), with a small output.  wgrad_kernel splits the
 // node range over many workgroups, each producing a partial [M, Nq] tile with
@@ -117,12 +120,11 @@ __global__ __launch_bounds__(64 * wgrad_waves<BN>, BN <= 32 ? 4 : BN <= 64 ? 3 :
 // range with four running sums (z mod 4), and the sixteen sums of an output are combined in a fixed order: the
 // result does not depend on the launch, and with few outputs and hundreds of partials (a classifier's gradient) the
 // additions do not wait for one load at a time.
-__global__ __launch_bounds__(kThreads) void reduce_partials(int S, int64_t total, const float* __restrict__ part,
-                                                            float* __restrict__ out)
+__device__ __forceinline__ void reduce_partials(int64_t block, int S, int64_t total, const float* __restrict__ part,
+                                                float* __restrict__ out, float* sh)
 {
-    __shared__ float sh[kThreads / 64][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t i = block * 64 + lane;
     float s = 0.0f;
     if (i < total) {
         const int per = (S + 3) / 4;
@@ -137,32 +139,65 @@ __global__ __launch_bounds__(kThreads) void reduce_partials(int S, int64_t total
         for (int k = 0; z < z1; ++z, ++k) q[k] += p[(int64_t)z * total];
         s = (q[0] + q[1]) + (q[2] + q[3]);
     }
-    sh[wave][lane] = s;
+    sh[threadIdx.x] = s;
     __syncthreads();
-    if (wave == 0 && i < total) out[i] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+    if (wave == 0 && i < total) out[i] = (sh[lane] + sh[64 + lane]) + (sh[128 + lane] + sh[192 + lane]);
 }
 
+constexpr int kCountBlocks = 64;         // workgroups that count labelled nodes; a wave adds their counts up
 struct TrainHeader {
-    int32_t n_labelled;
-    int32_t pad[3];
+    int32_t labelled[kCountBlocks];
 };
 
-__global__ __launch_bounds__(kThreads) void count_labelled(int64_t N, const int32_t* __restrict__ labels,
-                                                           TrainHeader* hdr)
+__device__ __forceinline__ int labelled_nodes(const TrainHeader* hdr)
+{
+    int n = hdr->labelled[threadIdx.x & 63];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) n += __shfl_xor(n, m, 64);
+    return n;
+}
+
+// out [Cp, R] = scale * transpose of in [R, Cn], rows Cn..Cp of out zero
+struct Transpose {
+    int R, Cn, Cp;
+    const float* in;
+    float* out;
+    float scale;
+};
+
+// What a step needs before its products, in one launch: the first kCountBlocks workgroups count labelled nodes, the next
+// `a_blocks` transpose the classifier's weights for the way back, the others the first layer's for the input gradient.
+// (Clearing, counting and transposing were four launches of 2 to 12 us, two of them in front of the first product.)
+__global__ __launch_bounds__(kThreads) void prepare_kernel(int64_t N, const int32_t* __restrict__ labels,
+                                                           TrainHeader* hdr, unsigned a_blocks, Transpose a, Transpose b)
 {
     __shared__ int sh[kThreads / 64];
-    int cnt = 0;
-    for (int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x; v < N; v += (int64_t)gridDim.x * kThreads)
-        cnt += labels[v] >= 0;
+    if (blockIdx.x < kCountBlocks) {
+        int cnt = 0;
+        constexpr int64_t step = (int64_t)kCountBlocks * kThreads;
+        int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+        for (; v + 7 * step < N; v += 8 * step) {
+            int y[8];
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) cnt += __shfl_xor(cnt, m, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int t = 0;
-        for (int w = 0; w < kThreads / 64; ++w) t += sh[w];
-        if (t) atomicAdd(&hdr->n_labelled, t);       // integer: the total does not depend on the order
+            for (int k = 0; k < 8; ++k) y[k] = labels[v + k * step];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) cnt += y[k] >= 0;
+        }
+        for (; v < N; v += step) cnt += labels[v] >= 0;
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) cnt += __shfl_xor(cnt, m, 64);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = cnt;
+        __syncthreads();
+        if (threadIdx.x == 0) hdr->labelled[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+        return;
     }
+    const unsigned block = blockIdx.x - kCountBlocks;
+    const bool first = block < a_blocks;
+    const Transpose t = first ? a : b;
+    const int64_t i = (int64_t)(first ? block : block - a_blocks) * kThreads + threadIdx.x;
+    if (i >= (int64_t)t.R * t.Cp) return;
+    const int c = (int)(i / t.R), r = (int)(i % t.R);
+    t.out[i] = c < t.Cn ? t.scale * t.in[(int64_t)r * t.Cn + c] : 0.0f;
 }
 
 __device__ __forceinline__ float wmax(float x)
@@ -178,58 +213,110 @@ __device__ __forceinline__ float wsum(float x)
     return x;
 }
 
-constexpr int kXentRows = 16;     // nodes per workgroup of the loss kernel (4 per wave)
+// f over the values of sixteen lanes, the same in each of them
+template <class F>
+__device__ __forceinline__ float fold16(float x, F&& f)
+{
+    auto with = [&](auto ctrl) {
+        x = f(x, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true)));
+    };
+    with(std::integral_constant<int, 0xb1>{});           // lane ^ 1
+    with(std::integral_constant<int, 0x4e>{});           // lane ^ 2
+    with(std::integral_constant<int, 0x141>{});          // the other four of eight (mirrored)
+    with(std::integral_constant<int, 0x140>{});          // the other eight of sixteen
+    return x;
+}
+
+// Nodes per workgroup of the loss kernel: sixteen at a time (4 per wave), up to eight times where that leaves 2,048
+// workgroups, which is what the chip holds: there are as many partial sums of the loss and the columns to add up.
+constexpr int kXentRows = 16;
+int xent_turns(int64_t N, bool narrow)
+{
+    const int64_t t = N / (kXentRows * 2048);
+    return !narrow || t < 1 ? 1 : t > 8 ? 8 : (int)t;
+}
+bool xent_narrow(int64_t ldc) { return ldc <= 64; }
+int64_t xent_blocks(int64_t N, int64_t ldc)
+{
+    const int64_t rows = kXentRows * xent_turns(N, xent_narrow(ldc));
+    return (N + rows - 1) / rows;
+}
 
 // L[v, 0:C] holds the logits on entry and d loss / d logits on exit (zero for unlabelled nodes and in the padding
 // columns C..ld).  Per-workgroup loss sums go to loss_part[blockIdx.x] (unscaled).
-// A wave takes four nodes; where a row fits its lanes (NARROW: ld <= 64) all four at once, so that the loads and the
-// chains of wave reductions of four rows run side by side: bound by the streaming of L then, before by those chains
-// (232,965 x 41 92 -> 63 us, 2,708 x 7, which 16 rows per wave gave 43 workgroups, 25 -> 5 us).
+// A wave takes four nodes.  Where a row fits sixteen lanes of four columns (NARROW: ld <= 64) all four at once: bound by the
+// instructions of a row, of which the reductions are one set for four rows then, and so are the logarithms.  (One row over
+// the wave's lanes, 190 instructions each: 232,965 x 41 62 us, 35 now, 58 with the logarithms alone in common; the streaming
+// of L takes 25.  2,708 x 7: 5 us, 4 now.)  These rows' column sums, which the bias gradient is made of, go to
+// col_part[blockIdx.x][0:C] on the way: in a pass of their own 10 us.
 template <bool NARROW>
 __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     int64_t N, int C, float* __restrict__ L, int64_t ld, const int32_t* __restrict__ labels,
-    const TrainHeader* hdr, float* __restrict__ loss_part)
+    const TrainHeader* hdr, float* __restrict__ loss_part, int turns, float* __restrict__ col_part)
 {
     __shared__ float wl[4];
+    __shared__ __attribute__((aligned(16))) float wc[16][64];
     constexpr int R = kXentRows / 4;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nl = hdr->n_labelled;
+    const int nl = labelled_nodes(hdr);
     const float inv = nl > 0 ? 1.0f / (float)nl : 0.0f;
-    const int64_t v0 = (int64_t)blockIdx.x * kXentRows + wave * R;
+    const int64_t first = (int64_t)blockIdx.x * kXentRows * turns + wave * R;
     float loss = 0.0f;
     // s: the softmax denominator; so: its part from the classes other than the label.  The label's
     // gradient p_y - 1 is formed as -so / s: for a confidently classified node p_y is close to one and
     // the subtraction would leave only a few correct digits of what is then the whole gradient.
     if constexpr (NARROW) {
-        float x[R], m[R], e[R], s[R], so[R];
-        int y[R];
+        // sixteen lanes per row, four columns per lane (rows of the workspace start on 128-byte lines)
+        const int c0 = lane % 16 * 4;
+        float column[4] = {};
+        f32x4 next = {};
+        int next_y = -1;
+        auto fetch = [&](int64_t v) {
+            v = v < N ? v : N - 1;
+            next_y = labels[v];
+            if (c0 < ld) next = *reinterpret_cast<const f32x4*>(L + v * ld + c0);
+        };
+        auto larger = [](float a, float b) { return fmaxf(a, b); };
+        auto plus = [](float a, float b) { return a + b; };
+        const int64_t mine = first + lane / 16;
+        fetch(mine);
+        for (int t = 0; t < turns; ++t) {
+            const int64_t v = mine + (int64_t)t * kXentRows;
+            const int y = next_y;
+            float x[4], e[4];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t v = v0 + r < N ? v0 + r : N - 1;
-            y[r] = labels[v];
-            x[r] = lane < C ? L[v * ld + lane] : -INFINITY;
+            for (int k = 0; k < 4; ++k) x[k] = c0 + k < C ? next[k] : -INFINITY;
+            if (t + 1 < turns) fetch(v + kXentRows);
+            const float m = fold16(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), larger);
+            float at = 0.0f, ey = 0.0f, rest[4];         // logit and exponential of the label, the others' exponentials
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                e[k] = c0 + k < C ? expf(x[k] - m) : 0.0f;
+                const bool label = c0 + k == y && c0 + k < C;
+                at = label ? x[k] : at;
+                ey = label ? e[k] : ey;
+                rest[k] = label ? 0.0f : e[k];
+            }
+            at = fold16(at, plus);                       // (one term that is not zero)
+            ey = fold16(ey, plus);
+            const float so = fold16((rest[0] + rest[1]) + (rest[2] + rest[3]), plus);
+            const float s = so + ey;
+            const float off = so / s;                    // 1 - p_y
+            const float scale = y >= 0 ? inv : 0.0f;
+            f32x4 g;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                g[k] = c0 + k < C ? (c0 + k == y ? -off : e[k] / s) * scale : 0.0f;
+                column[k] += v < N ? g[k] : 0.0f;
+            }
+            if (v < N && c0 < ld) *reinterpret_cast<f32x4*>(L + v * ld + c0) = g;
+            if (v < N && y >= 0 && y < C) loss += off <= 0.5f ? -log1pf(-off) : -(at - m - logf(s));
         }
-#pragma unroll
-        for (int r = 0; r < R; ++r) m[r] = wmax(x[r]);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            e[r] = lane < C ? expf(x[r] - m[r]) : 0.0f;
-            s[r] = wsum(e[r]);
-            so[r] = wsum(lane == y[r] ? 0.0f : e[r]);
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (v0 + r >= N) break;
-            const float rest = so[r] / s[r];       // 1 - p_y
-            const bool train = y[r] >= 0;
-            if (train && y[r] < C) loss += rest <= 0.5f ? -log1pf(-rest) : -(__shfl(x[r], y[r], 64) - m[r] - logf(s[r]));
-            const float scale = train ? inv : 0.0f;
-            const float g = lane < C ? (lane == y[r] ? -rest : e[r] / s[r]) * scale : 0.0f;
-            if (lane < ld) L[(v0 + r) * ld + lane] = g;
-        }
+        *reinterpret_cast<f32x4*>(&wc[wave * 4 + lane / 16][c0]) = f32x4{column[0], column[1], column[2], column[3]};
+        loss = (__shfl(loss, 0, 64) + __shfl(loss, 16, 64)) + (__shfl(loss, 32, 64) + __shfl(loss, 48, 64));
     } else {
         for (int r = 0; r < R; ++r) {
-            const int64_t v = v0 + r;
+            const int64_t v = first + r;
             if (v >= N) break;
             float* row = L + v * ld;
             const int y = labels[v];
@@ -257,31 +344,83 @@ __global__ __launch_bounds__(kThreads) void softmax_xent_kernel(
     if (lane == 0) wl[wave] = loss;
     __syncthreads();
     if (threadIdx.x == 0) loss_part[blockIdx.x] = (wl[0] + wl[1]) + (wl[2] + wl[3]);
+    if (NARROW && wave == 0 && lane < C) {
+        float t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = (wc[4 * k][lane] + wc[4 * k + 1][lane]) + (wc[4 * k + 2][lane] + wc[4 * k + 3][lane]);
+        col_part[(int64_t)blockIdx.x * C + lane] = (t[0] + t[1]) + (t[2] + t[3]);
+    }
 }
 
-// loss = (sum of the partial sums, pairwise in a fixed order) / n_labelled
-__global__ __launch_bounds__(kThreads) void loss_reduce_kernel(int64_t n_part, const float* __restrict__ part,
-                                                               const TrainHeader* hdr, float* __restrict__ loss)
+// The sum of part[0], part[stride], ..: eight loads at a time, then the threads pairwise in a fixed order.  In 64 bits: the
+// last additions, between sums that have grown large, are the ones whose rounding shows (232,965 x 7 bias gradient 4.8e-8
+// off the same in 64 bits with 1,820 partial sums of 128 rows, 6.0e-8 with 2,081 of 112 in float32).
+__device__ __forceinline__ double block_sum(int64_t n, const float* __restrict__ part, int64_t stride, double* sh)
 {
-    __shared__ float sh[kThreads];
-    float s = 0.0f;
-    for (int64_t i = threadIdx.x; i < n_part; i += kThreads) s += part[i];
+    double s = 0.0;
+    int64_t i = threadIdx.x;
+    for (; i + 7 * kThreads < n; i += 8 * kThreads) {
+        float x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = part[(i + k * kThreads) * stride];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += x[k];
+    }
+    for (; i < n; i += kThreads) s += part[i * stride];
     sh[threadIdx.x] = s;
     __syncthreads();
     for (int w = kThreads / 2; w >= 1; w >>= 1) {
         if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) *loss = hdr->n_labelled > 0 ? sh[0] / (float)hdr->n_labelled : 0.0f;
+    return sh[0];
 }
 
-// Column sums in two deterministic stages.  Stage 1: a workgroup takes kColRows rows; its four
+// The last additions of a layer's gradients, in one launch: workgroup 0 the loss (if there is one to form), then one per
+// column of the bias gradient, then the weight gradient's (see reduce_partials).  Launches of a few microseconds of work
+// each, they took a third of a small step one after the other.
+struct Finish {
+    int S;                        // weight gradient: partial products, their size, and where they are
+    int64_t total;
+    const float* part;
+    float* gW;
+    int64_t B;                    // bias gradient: partial sums per column, columns (0: none)
+    int C;
+    const float* colpart;
+    float* gb;
+    int64_t n_loss;               // loss: partial sums
+    const float* losspart;
+    const TrainHeader* hdr;
+    float* loss;                  // or NULL
+};
+__global__ __launch_bounds__(kThreads) void finish_kernel(Finish f)
+{
+    __shared__ double sh[kThreads];
+    int64_t block = blockIdx.x;
+    if (f.loss) {
+        if (block == 0) {
+            const int nl = labelled_nodes(f.hdr);
+            const double s = block_sum(f.n_loss, f.losspart, 1, sh);
+            if (threadIdx.x == 0) *f.loss = nl > 0 ? (float)(s / nl) : 0.0f;
+            return;
+        }
+        --block;
+    }
+    if (block < f.C) {
+        const double s = block_sum(f.B, f.colpart + block, f.C, sh);
+        if (threadIdx.x == 0) f.gb[block] = (float)s;
+        return;
+    }
+    reduce_partials(block - f.C, f.S, f.total, f.part, f.gW, reinterpret_cast<float*>(sh));
+}
+
+// Column sums of what no kernel here has just written.  A workgroup takes kColRows rows; its four
 // waves stride the rows, lanes stride the columns, every wave keeps four running sums (four loads in
 // flight) that are combined in a fixed order, and the waves are added in order through LDS.
-// Stage 2: one workgroup per column adds the stage-1 results with a fixed tree.
+// finish_kernel adds the workgroups' results.
 constexpr int kColRows = 128;
 
-__global__ __launch_bounds__(kThreads) void colsum_stage1(int64_t N, int C, const float* __restrict__ D, int64_t ld,
+__global__ __launch_bounds__(kThreads) void colsum_kernel(int64_t N, int C, const float* __restrict__ D, int64_t ld,
                                                           float* __restrict__ part)
 {
     __shared__ float sh[4][64];
@@ -306,31 +445,6 @@ __global__ __launch_bounds__(kThreads) void colsum_stage1(int64_t N, int C, cons
             part[(int64_t)blockIdx.x * C + c] = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
         __syncthreads();
     }
-}
-__global__ __launch_bounds__(kThreads) void colsum_stage2(int B, int C, const float* __restrict__ part,
-                                                          float* __restrict__ out)
-{
-    __shared__ float sh[kThreads];
-    const int c = blockIdx.x;
-    float s = 0.0f;
-    for (int b = threadIdx.x; b < B; b += kThreads) s += part[(int64_t)b * C + c];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = kThreads / 2; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[c] = sh[0];
-}
-
-// out [Cp, R] = scale * transpose of in [R, Cn], rows Cn..Cp of out zero
-__global__ __launch_bounds__(kThreads) void transpose_kernel(int R, int Cn, int Cp, const float* __restrict__ in,
-                                                             float* __restrict__ out, float scale)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= (int64_t)R * Cp) return;
-    const int c = (int)(i / R), r = (int)(i % R);
-    out[i] = c < Cn ? scale * in[(int64_t)r * Cn + c] : 0.0f;
 }
 
 // ---------------------------------------------------------------------------
@@ -419,9 +533,9 @@ Split choose_split(int64_t K, int64_t M, int64_t Nq, int bn)
 
 int bn_for(int64_t Nq) { return Nq <= 32 ? 32 : Nq <= 64 ? 64 : Nq <= 128 ? 128 : 256; }
 
-// out[M][Nq] = P^T Q
+// f.gW[M][Nq] = P^T Q, and what else f asks for
 void wgrad(int64_t K, int64_t M, int64_t Nq, const float* P, int64_t ldp, const float* Q, int64_t ldq, float* part,
-           float* out, hipStream_t stream)
+           Finish f, hipStream_t stream)
 {
     const int bn = bn_for(Nq);
     const Split sp = choose_split(K, M, Nq, bn);
@@ -434,15 +548,17 @@ void wgrad(int64_t K, int64_t M, int64_t Nq, const float* P, int64_t ldp, const 
     else if (bn == 64)  go(std::integral_constant<int, 64>{});
     else if (bn == 128) go(std::integral_constant<int, 128>{});
     else                go(std::integral_constant<int, 256>{});
-    const int64_t total = M * Nq;
-    reduce_partials<<<dim3((unsigned)((total + 63) / 64)), dim3(kThreads), 0, stream>>>(sp.S, total, part, out);
+    f.S = sp.S;
+    f.total = M * Nq;
+    f.part = part;
+    finish_kernel<<<dim3((unsigned)((f.loss ? 1 : 0) + f.C + (f.total + 63) / 64)), dim3(kThreads), 0, stream>>>(f);
 }
 
-void colsum(int64_t N, int64_t C, const float* D, int64_t ld, float* part, float* out, hipStream_t stream)
+int64_t colsum(int64_t N, int64_t C, const float* D, int64_t ld, float* part, hipStream_t stream)
 {
-    const int B = (int)((N + kColRows - 1) / kColRows);
-    colsum_stage1<<<dim3((unsigned)B), dim3(kThreads), 0, stream>>>(N, (int)C, D, ld, part);
-    colsum_stage2<<<dim3((unsigned)C), dim3(kThreads), 0, stream>>>(B, (int)C, part, out);
+    const int64_t B = (N + kColRows - 1) / kColRows;
+    colsum_kernel<<<dim3((unsigned)B), dim3(kThreads), 0, stream>>>(N, (int)C, D, ld, part);
+    return B;
 }
 
 struct TrainLayout {
@@ -464,6 +580,7 @@ TrainLayout make_layout(int64_t N, int64_t D_in, int64_t H, int64_t C)
     t.ldc = align_up(C > 0 ? C : 1, 32);
     int64_t off = 0;
     auto take = [&](int64_t floats) { const int64_t at = off; off += align_up(floats * 4, 256); return at; };
+    static_assert(sizeof(TrainHeader) <= 256, "its place");
     t.hdr = off; off += 256;
     t.A = take(H > 0 ? n1 * t.ldh : 0);
     t.L = take(n1 * t.ldc);
@@ -479,9 +596,11 @@ TrainLayout make_layout(int64_t N, int64_t D_in, int64_t H, int64_t C)
         pf = partial_floats(N, D_in, t.ldc);
     }
     t.part = take(pf);
-    const int64_t widest = t.ldh > t.ldc ? t.ldh : t.ldc;
-    t.colpart = take(((n1 + kColRows - 1) / kColRows) * widest);
-    t.losspart = take((n1 + kXentRows - 1) / kXentRows);
+    // (of blocks of 32 rows or more behind a product, of the loss kernel's rows, or of kColRows rows)
+    const int64_t cols = (n1 + 31) / 32 * t.ldh;
+    const int64_t top = xent_narrow(t.ldc) ? xent_blocks(n1, t.ldc) * C : (n1 + kColRows - 1) / kColRows * t.ldc;
+    t.colpart = take(cols > top ? cols : top);
+    t.losspart = take(xent_blocks(n1, t.ldc));
     t.total = off;
     return t;
 }
@@ -550,8 +669,12 @@ int layer_grad_impl(int64_t N, int64_t D_in, int64_t H, int64_t C,
         return RETEXO_OK;
     }
 
-    if (launch_zero(hdr, sizeof(TrainHeader), stream)) return RETEXO_E_HIP;
-    count_labelled<<<dim3((unsigned)min((int64_t)1024, (N + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(N, d_labels, hdr);
+    // (the dropout's scale rides on the transposed classifier; the contractions over its and dL's padded width meet zeros)
+    const Transpose top = {(int)H, (int)C, H > 0 ? (int)t.ldc : 0, d_Wc, WcT, keep_scale};
+    const Transpose low = {(int)D_in, (int)W1cols, !d_gX ? 0 : H > 0 ? (int)H : (int)t.ldc, d_W1, W1T, 1.0f};
+    auto blocks_of = [](const Transpose& x) { return ((int64_t)x.R * x.Cp + kThreads - 1) / kThreads; };
+    prepare_kernel<<<dim3((unsigned)(kCountBlocks + blocks_of(top) + blocks_of(low))), dim3(kThreads), 0, stream>>>(
+        N, d_labels, hdr, (unsigned)blocks_of(top), top, low);
 
     // forward
     const float* feat = d_X;        // input of the classifier product
@@ -575,40 +698,33 @@ int layer_grad_impl(int64_t N, int64_t D_in, int64_t H, int64_t C,
         return e;
 
     // loss and d loss / d logits (in place, padding columns zeroed)
-    const unsigned nb = (unsigned)((N + kXentRows - 1) / kXentRows);
-    if (t.ldc <= 64) softmax_xent_kernel<true><<<dim3(nb), dim3(kThreads), 0, stream>>>(N, (int)C, L, t.ldc, d_labels, hdr, losspart);
-    else             softmax_xent_kernel<false><<<dim3(nb), dim3(kThreads), 0, stream>>>(N, (int)C, L, t.ldc, d_labels, hdr, losspart);
-    loss_reduce_kernel<<<dim3(1), dim3(kThreads), 0, stream>>>((int64_t)nb, losspart, hdr, d_loss);
+    const bool narrow = xent_narrow(t.ldc);
+    const int64_t nb = xent_blocks(N, t.ldc);
+    auto xent = narrow ? softmax_xent_kernel<true> : softmax_xent_kernel<false>;
+    xent<<<dim3((unsigned)nb), dim3(kThreads), 0, stream>>>(N, (int)C, L, t.ldc, d_labels, hdr, losspart, xent_turns(N, narrow), colpart);
 
     // classifier (or only) layer: weight and bias gradients
-    float* gW_top = H > 0 ? d_gWc : d_gW1;
-    float* gb_top = H > 0 ? d_gbc : d_gb1;
-    wgrad(N, dfeat, C, feat, ldfeat, L, t.ldc, part, gW_top, stream);
-    colsum(N, C, L, t.ldc, colpart, gb_top, stream);
+    Finish f = {};
+    f.n_loss = nb; f.losspart = losspart; f.hdr = hdr; f.loss = d_loss;
+    f.C = (int)C; f.colpart = colpart;
+    f.B = narrow ? nb : colsum(N, C, L, t.ldc, colpart, stream);
+    f.gW = H > 0 ? d_gWc : d_gW1;
+    f.gb = H > 0 ? d_gbc : d_gb1;
+    wgrad(N, dfeat, C, feat, ldfeat, L, t.ldc, part, f, stream);
 
     if (H > 0) {
-        // back through the classifier, the dropout (its scale rides on the transposed classifier, its mask is
-        // part of "A > 0") and the ReLU, then the layer's own gradients
-        // (the contraction runs over the padded width of dL: its padding columns and the padding rows
-        // of the transposed classifier are zero)
-        const int64_t tot = H * t.ldc;
-        transpose_kernel<<<dim3((unsigned)((tot + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
-            (int)H, (int)C, (int)t.ldc, d_Wc, WcT, keep_scale);
-        if (int e = launch_transform(N, t.ldc, H, L, t.ldc, WcT, nullptr, false, dA, t.ldh, stream, A, t.ldh)) return e;
-        wgrad(N, D_in, H, d_X, ldx, dA, t.ldh, part, d_gW1, stream);
-        colsum(N, H, dA, t.ldh, colpart, d_gb1, stream);
-        if (d_gX) {
-            // dL/dX = dA W1^T, contracted over exactly H columns (dA's padding columns are not written)
-            const int64_t tot1 = H * D_in;
-            transpose_kernel<<<dim3((unsigned)((tot1 + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
-                (int)D_in, (int)H, (int)H, d_W1, W1T, 1.0f);
+        // back through the classifier, the dropout (its mask is part of "A > 0") and the ReLU, then the layer's own gradients
+        if (int e = launch_transform(N, t.ldc, H, L, t.ldc, WcT, nullptr, false, dA, t.ldh, stream, A, t.ldh, false, colpart)) return e;
+        Finish g = {};
+        g.B = transform_row_blocks(N, H); g.C = (int)H; g.colpart = colpart;
+        g.gW = d_gW1;
+        g.gb = d_gb1;
+        wgrad(N, D_in, H, d_X, ldx, dA, t.ldh, part, g, stream);
+        // dL/dX = dA W1^T, contracted over exactly H columns (dA's padding columns are not written)
+        if (d_gX)
             if (int e = launch_transform(N, H, D_in, dA, t.ldh, W1T, nullptr, false, d_gX, ldgx, stream)) return e;
-        }
     } else if (d_gX) {
         // dL/dX = dL W1^T over the padded width of dL (its padding columns and the padding rows of W1^T are zero)
-        const int64_t tot1 = t.ldc * D_in;
-        transpose_kernel<<<dim3((unsigned)((tot1 + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
-            (int)D_in, (int)C, (int)t.ldc, d_W1, W1T, 1.0f);
         if (int e = launch_transform(N, t.ldc, D_in, L, t.ldc, W1T, nullptr, false, d_gX, ldgx, stream)) return e;
     }
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
@@ -687,8 +803,13 @@ extern "C" int retexo_transform_backward(int64_t N, int64_t D_in, int64_t D_out,
         return RETEXO_OK;
     }
     char* ws = (char*)d_workspace;
-    wgrad(N, D_in, D_out, d_H, ldh, d_dZ, lddz, (float*)(ws + t.part), d_gW, stream);
-    if (d_gb) colsum(N, D_out, d_dZ, lddz, (float*)(ws + t.colpart), d_gb, stream);
+    Finish f = {};
+    f.gW = d_gW;
+    if (d_gb) {
+        f.C = (int)D_out; f.gb = d_gb; f.colpart = (float*)(ws + t.colpart);
+        f.B = colsum(N, D_out, d_dZ, lddz, (float*)(ws + t.colpart), stream);
+    }
+    wgrad(N, D_in, D_out, d_H, ldh, d_dZ, lddz, (float*)(ws + t.part), f, stream);
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
     return RETEXO_OK;
 }

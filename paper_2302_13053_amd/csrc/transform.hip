@@ -51,11 +51,12 @@ namespace {
 // Bias, ReLU, optional mask and store of the accumulators of one wave.
 // Accumulator element r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its tile.
 // Only the last row block of the matrix checks rows.
+// MASKED: sums[c] gets the sum of the wave's 32 rows of its column c.
 template <int TN, bool MASKED>
 __device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (&bv)[TN], int64_t N, int D_out,
                                           int64_t row_base, int col_base, int lane, int relu,
                                           float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm,
-                                          bool whole_block)
+                                          bool whole_block, float* __restrict__ sums)
 {
     const int lrow = lane & 31, lk = lane >> 5;
     auto run = [&](auto full_tag) {
@@ -66,7 +67,7 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (
             if (col >= D_out) continue;
             const int64_t row0 = row_base + 4 * lk;
             float* p = Z + row0 * ldz + col;
-            float mv[16];
+            float mv[16], sum[4] = {};
             if constexpr (MASKED) {
                 // backward of a ReLU layer: the value passes only where the forward activation was positive
                 const float* pm = mask + row0 * ldm + col;
@@ -81,8 +82,16 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[TN], const float (
                 const int ro = 8 * (r / 4) + (r % 4);
                 float x = acc[j][r] + bv[j];
                 if (relu) x = fmaxf(x, 0.0f);
-                if constexpr (MASKED) x = mv[r] > 0.0f ? x : 0.0f;
+                if constexpr (MASKED) {
+                    x = mv[r] > 0.0f ? x : 0.0f;         // (rows past the end: 0)
+                    sum[r % 4] += x;
+                }
                 if (FULL || row0 + ro < N) p[ro * ldz] = x;
+            }
+            if constexpr (MASKED) {
+                const float half = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+                const float both = half + __shfl_xor(half, 32, 64);      // (both lanes hold the same column)
+                if (lk == 0) sums[j * 32 + lrow] = both;
             }
         }
     };
@@ -199,12 +208,14 @@ __device__ __forceinline__ void decide_near_zero(f32x16 (&acc)[TN], const float 
 
 // The block kernel: 128 x BN outputs per workgroup, 32 rows and up to 128 columns per wave (whose two running sums then
 // take 128 registers): four waves, or eight for the tiles wider than 128; any alignment and leading dimension.
+// MASKED (the backward of a ReLU layer) also leaves the column sums of every 128-row block, which the bias gradient is made
+// of, as long as the values are in registers: a pass of its own over them takes 45 us for 232,965 x 256.
 template <int BN> constexpr int transform_waves = BN > 128 ? 8 : 4;
 template <int BN, bool MASKED, bool KEEP_SIGN>
 __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void transform_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
-    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm)
+    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm, float* __restrict__ colsums)
 {
     constexpr int BM = 128, WAVES = transform_waves<BN>, WN = BN / (WAVES / 4), TN = WN / 32;
     using T = SplitTile<BM, BN>;
@@ -342,7 +353,15 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void tr
         __syncthreads();
         decide_near_zero<TN>(acc, bv, D_in, D_out, H, ldh, W, m0 + a0, N, n0 + b0, lane, row_top + a0, col_top + b0, chain);
     }
-    write_out<TN, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm, m0 + BM <= N);
+    float* sums = reinterpret_cast<float*>(lds);         // [4][BN], in the tiles' memory
+    if constexpr (MASKED) __syncthreads();               // every wave is done with the last tile
+    write_out<TN, MASKED>(acc, bv, N, D_out, m0 + a0, n0 + b0, lane, relu, Z, ldz, mask, ldm, m0 + BM <= N,
+                          sums + wave % 4 * BN + b0);
+    if constexpr (MASKED) {
+        __syncthreads();
+        if (tid < BN && n0 + tid < D_out)
+            colsums[(int64_t)blockIdx.x * D_out + n0 + tid] = (sums[tid] + sums[BN + tid]) + (sums[2 * BN + tid] + sums[3 * BN + tid]);
+    }
 }
 
 // Few rows: a matrix with so few 128-row blocks that they would leave most compute units idle (a citation
@@ -357,7 +376,7 @@ template <int TN, bool MASKED>
 __global__ __launch_bounds__(512) void transform_few_rows_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
-    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm)
+    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm, float* __restrict__ colsums)
 {
     constexpr int BN = TN * 32, NW = 8;
     __shared__ float part[NW / 2][32][BN];
@@ -464,6 +483,7 @@ __global__ __launch_bounds__(512) void transform_few_rows_kernel(
     if (wave < NW / 2) put(wave);
     __syncthreads();
 
+    float sum = 0.0f;                            // of this thread's outputs, which lie in one column
     for (int e = tid; e < 32 * BN; e += 512) {
         const int r = e / BN, c = e % BN;
         const int64_t orow = m0 + r;
@@ -474,6 +494,19 @@ __global__ __launch_bounds__(512) void transform_few_rows_kernel(
         if (relu) x = fmaxf(x, 0.0f);
         if constexpr (MASKED) x = mask[orow * ldm + ocol] > 0.0f ? x : 0.0f;
         Z[orow * ldz + ocol] = x;
+        sum += x;
+    }
+    if constexpr (MASKED) {                      // column sums of the 32 rows, as in the block kernel
+        __syncthreads();
+        float* sums = &part[0][0][0];            // [512 / BN][BN]
+        sums[tid] = sum;
+        __syncthreads();
+        if (tid < BN && n0 + tid < D_out) {
+            float t[4] = {};
+#pragma unroll
+            for (int i = 0; i < 512 / BN; ++i) t[i % 4] += sums[i * BN + tid];
+            colsums[(int64_t)blockIdx.x * D_out + n0 + tid] = (t[0] + t[1]) + (t[2] + t[3]);
+        }
     }
 }
 
@@ -495,53 +528,59 @@ __global__ void bias_rows_kernel(int64_t N, int D_out, const float* __restrict__
 template <int BN, bool MASKED>
 void launch(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh, const float* W,
             const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm, bool keep_sign,
-            hipStream_t stream)
+            float* colsums, hipStream_t stream)
 {
     const dim3 grid((unsigned)((N + 127) / 128), (unsigned)((D_out + BN - 1) / BN)), block(64 * transform_waves<BN>);
     const int r = relu ? 1 : 0;
     if constexpr (!MASKED) {
         if (keep_sign) {
-            transform_kernel<BN, false, true><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+            transform_kernel<BN, false, true><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
             return;
         }
     }
-    transform_kernel<BN, MASKED, false><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+    transform_kernel<BN, MASKED, false><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
 }
 
 template <bool MASKED>
 void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh, const float* W,
                      const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm,
-                     hipStream_t stream)
+                     float* colsums, hipStream_t stream)
 {
     const int r = relu ? 1 : 0;
     const unsigned gx = (unsigned)((N + 31) / 32);
     // 32-column tiles when 64-column ones would not give every compute unit a workgroup
     if (D_out <= 32 || (int64_t)gx * ((D_out + 63) / 64) < 256) {
         dim3 grid(gx, (unsigned)((D_out + 31) / 32));
-        transform_few_rows_kernel<1, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+        transform_few_rows_kernel<1, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
     } else {
         dim3 grid(gx, (unsigned)((D_out + 63) / 64));
-        transform_few_rows_kernel<2, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm);
+        transform_few_rows_kernel<2, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
     }
 }
 
 // Fewer 128-row blocks (times the column blocks) than the "transform_few_blocks" setting, 128 unless changed:
 // the few-rows kernel.  The choice depends on the shape only, never on alignment, so one shape always takes
 // one order of additions.
+int64_t block_width(int64_t D_out) { return D_out <= 32 ? 32 : D_out <= 64 ? 64 : D_out <= 128 ? 128 : D_out <= 192 ? 192 : 256; }
+bool takes_few_rows(int64_t N, int64_t D_out)
+{
+    const int64_t bn = block_width(D_out);
+    return (N + 127) / 128 * ((D_out + bn - 1) / bn) < agg_options().few_blocks;
+}
 
 template <bool MASKED>
 void launch_by_width(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh, const float* W,
                      const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm, bool keep_sign,
-                     hipStream_t stream)
+                     float* colsums, hipStream_t stream)
 {
-    const int64_t bn = D_out <= 32 ? 32 : D_out <= 64 ? 64 : D_out <= 128 ? 128 : D_out <= 192 ? 192 : 256;
-    if ((N + 127) / 128 * ((D_out + bn - 1) / bn) < agg_options().few_blocks) {
-        launch_few_rows<MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, stream);
+    if (takes_few_rows(N, D_out)) {
+        launch_few_rows<MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, colsums, stream);
         return;
     }
     auto go = [&](auto width) {
-        launch<decltype(width)::value, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, stream);
+        launch<decltype(width)::value, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, colsums, stream);
     };
+    const int64_t bn = block_width(D_out);
     if (bn == 32)       go(std::integral_constant<int, 32>{});
     else if (bn == 64)  go(std::integral_constant<int, 64>{});
     else if (bn == 128) go(std::integral_constant<int, 128>{});
@@ -551,9 +590,11 @@ void launch_by_width(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
 
 }  // namespace
 
+int64_t transform_row_blocks(int64_t N, int64_t D_out) { return takes_few_rows(N, D_out) ? (N + 31) / 32 : (N + 127) / 128; }
+
 int launch_transform(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh,
                      const float* W, const float* b, bool relu, float* Z, int64_t ldz,
-                     hipStream_t stream, const float* mask, int64_t ldm, bool keep_sign)
+                     hipStream_t stream, const float* mask, int64_t ldm, bool keep_sign, float* colsums)
 {
     if (N == 0 || D_out == 0) return RETEXO_OK;
     if (D_in == 0) {
@@ -562,8 +603,8 @@ int launch_transform(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
             N, (int)D_out, b, relu ? 1 : 0, Z, ldz, mask, ldm);
         return hipGetLastError() != hipSuccess ? RETEXO_E_HIP : RETEXO_OK;
     }
-    if (mask) launch_by_width<true>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, stream);
-    else      launch_by_width<false>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, stream);
+    if (mask) launch_by_width<true>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, colsums, stream);
+    else      launch_by_width<false>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, colsums, stream);
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
     return RETEXO_OK;
 }
