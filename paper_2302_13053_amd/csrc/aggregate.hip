@@ -53,7 +53,7 @@ struct AggArgs {
     int64_t row_begin;     // range of plan order handled by this launch
     int64_t row_count;
     int64_t heavy_rows;    // rows at the head of the plan order with a workgroup each, and the workgroups of those
-    int64_t heavy_items;   // rows (agg_linear_kernel, whose one launch covers all rows)
+    int64_t heavy_items;   // rows (kernels whose one launch covers all rows)
     int64_t F;
     int nslab;
     int slab_major;
@@ -866,27 +866,29 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_ker
 // an immediate offset (no readlane + select chain per neighbour).  Lanes past
 // the end of a tile carry the tile's first neighbour with weight zero, so every
 // gather address is valid and nothing in the loop branches per lane.
+// One launch covers both classes of rows, as in agg_linear_kernel.
 // ---------------------------------------------------------------------------
 template <int NC, int NW, int HP, bool HU, bool TRAIN>
-__global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fast_kernel(AggArgs a)
+__global__ __launch_bounds__(64 * NW) void agg_gat_fast_kernel(AggArgs a)
 {
-    constexpr int WAVES = NW == 1 ? kLightWaves : NW;
     constexpr int U = 4;
     // TRAIN: the aggregate is accumulated in two parts, entries with a non-positive score (acc) and
     // with a positive score (accp), each with its own weight per edge (zero for the other kind); the
     // backward pass needs the two parts separately, each accurate relative to its own size
     constexpr int WSETS = TRAIN ? 2 : 1;
-    __shared__ float wl[WAVES][WSETS][HP][64];
+    // weights of the waves' tiles; in the end the sums of a long row's waves
+    __shared__ float lds[NW * WSETS * 64 * (HP > NC * 4 ? HP : NC * 4)];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t items = a.row_count * a.nslab;
-    const int64_t item = (NW == 1) ? (int64_t)blockIdx.x * kLightWaves + wave : (int64_t)blockIdx.x;
-    if (item >= items) return;
+    const bool heavy = blockIdx.x < a.heavy_items;    // uniform over the workgroup
+    const int64_t rows = heavy ? a.heavy_rows : a.n_rows - a.heavy_rows;
+    const int64_t item = heavy ? (int64_t)blockIdx.x : ((int64_t)blockIdx.x - a.heavy_items) * NW + wave;
+    if (item >= rows * a.nslab) return;
     int64_t slot;
     int slab;
-    if (a.slab_major) { slab = (int)(item / a.row_count); slot = item % a.row_count; }
+    if (a.slab_major) { slab = (int)(item / rows); slot = item % rows; }
     else              { slot = item / a.nslab; slab = (int)(item % a.nslab); }
-    const int v = __builtin_amdgcn_readfirstlane(a.order[a.row_begin + slot]);
+    const int v = __builtin_amdgcn_readfirstlane(a.order[heavy ? slot : a.heavy_rows + slot]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v + 1]);
 
@@ -911,8 +913,8 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
     }
     const char* zbase = reinterpret_cast<const char*>(a.Z);
     const uint32_t rowbytes = (uint32_t)(a.ldz * 4);
-    float* myw = &wl[wave][0][0][0];
-    float* mywp = &wl[wave][WSETS - 1][0][0];
+    float* myw = lds + wave * (WSETS * HP * 64);
+    float* mywp = myw + (WSETS - 1) * HP * 64;
 
     // sp, sn: the parts of s from entries with a positive / non-positive score (kept apart so that a
     // share that is structurally zero comes out as an exact zero)
@@ -932,9 +934,9 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
         for (int c = 0; c < NC; ++c)
             zself[c] = *reinterpret_cast<const f32x4*>(zbase + (uint32_t)v * rowbytes + colbytes[c]);
     }
-    const int base0 = lo + 64 * (NW == 1 ? 0 : wave);
+    const int base0 = lo + (heavy ? 64 * wave : 0), step = heavy ? 64 * NW : 64;
 
-    for (int base = lo + 64 * (NW == 1 ? 0 : wave); base < hi; base += 64 * NW) {
+    for (int base = base0; base < hi; base += step) {
         const int e = base + lane;
         const bool valid = e < hi;
         const int cnt = min(64, hi - base);
@@ -1003,7 +1005,7 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (base != lo + 64 * (NW == 1 ? 0 : wave)) {
+        if (base != base0) {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -1067,9 +1069,11 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
         }
     }
 
-    if constexpr (NW > 1) {
-        __shared__ float red[NW][NC * 4 * WSETS][64];
-        __shared__ float mred[NW][HP], sred[NW][HP], spred[NW][HP], snred[NW][HP];
+    if (heavy) {
+        typedef float sums_t[NC * 4 * WSETS][64];
+        sums_t* red = reinterpret_cast<sums_t*>(lds);
+        __syncthreads();                                 // every wave is done with its weights
+        __shared__ float mred[NW][HP], sred[NW][HP], spred[NW][HP], snred[NW][HP], fred[NW][HP];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -1087,18 +1091,27 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
         }
         __syncthreads();
         if (wave != 0) return;
-        float f[NW][HP];
+        // every wave's factor per head, through LDS: as a register array it took 144 bytes of scratch per lane, and the
+        // registers of the save mode kernel from 116 to 142, also for the short rows
+        if (lane < NW * HP) {
+            const int w = lane / HP, h = lane % HP;
+            float mm = mred[0][h];
+#pragma unroll
+            for (int o = 1; o < NW; ++o) mm = fmaxf(mm, mred[o][h]);
+            fred[w][h] = (mred[w][h] == -INFINITY) ? 0.0f : expf(mred[w][h] - mm);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
         for (int h = 0; h < HP; ++h) {
             float mm = mred[0][h];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) mm = fmaxf(mm, mred[w][h]);
             float ss = 0.0f, pp = 0.0f, nn = 0.0f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
-                f[w][h] = (mred[w][h] == -INFINITY) ? 0.0f : expf(mred[w][h] - mm);
-                ss += sred[w][h] * f[w][h];
-                if constexpr (TRAIN) { pp += spred[w][h] * f[w][h]; nn += snred[w][h] * f[w][h]; }
+                mm = fmaxf(mm, mred[w][h]);
+                ss += sred[w][h] * fred[w][h];
+                if constexpr (TRAIN) { pp += spred[w][h] * fred[w][h]; nn += snred[w][h] * fred[w][h]; }
             }
             s[h] = ss;
             m[h] = mm;
@@ -1111,7 +1124,7 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
                 float t = 0.0f, tp = 0.0f;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
-                    const float fw = select_head<HP>(f[w], hc[c][HU ? 0 : k]);
+                    const float fw = fred[w][hc[c][HU ? 0 : k]];
                     t += red[w][c * 4 + k][lane] * fw;
                     if constexpr (TRAIN) tp += red[w][NC * 4 + c * 4 + k][lane] * fw;
                 }
@@ -1168,14 +1181,20 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fas
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+// one launch for long and short rows: the number of its workgroups
+unsigned both_classes(AggArgs& a, int64_t n_heavy, int64_t N, int waves = kHeavyWaves)
+{
+    a.heavy_rows = n_heavy;
+    a.heavy_items = n_heavy * a.nslab;
+    return (unsigned)(a.heavy_items + ((N - n_heavy) * a.nslab + waves - 1) / waves);
+}
+
 template <int VEC, int NC, bool MAXOP>
 void launch_linear(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t stream)
 {
     AggArgs a = base;
-    a.heavy_rows = n_heavy;
-    a.heavy_items = n_heavy * a.nslab;
-    const int64_t blocks = a.heavy_items + ((N - n_heavy) * a.nslab + kHeavyWaves - 1) / kHeavyWaves;
-    agg_linear_kernel<VEC, NC, MAXOP><<<dim3((unsigned)blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
+    const unsigned blocks = both_classes(a, n_heavy, N);
+    agg_linear_kernel<VEC, NC, MAXOP><<<dim3(blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
 }
 
 template <int LPG, bool WEIGHTED, bool OFF32>
@@ -1213,8 +1232,8 @@ void dispatch_grouped(const AggArgs& a, int64_t n_heavy, int64_t N, bool weighte
 }
 
 // ---------------------------------------------------------------------------
-// gat_softmax for rows of ordinary length when the whole row fits one wave
-// (F <= 256, four floats per lane) and a head is a power-of-two group of lanes:
+// gat_softmax when the whole row fits one wave (F <= 256, four floats per lane)
+// and a head is a power-of-two group of lanes:
 // the score of an entry is computed from the gathered source row itself.
 //
 // The kernels above fetch el[u] = <a_src, z_u> from a table, one 16-byte read
@@ -1228,26 +1247,31 @@ void dispatch_grouped(const AggArgs& a, int64_t n_heavy, int64_t N, bool weighte
 // exponential is one v_exp_f32.  The destination's own score <a_dst, z_v> is formed
 // the same way from row v when `attn_dst` is given (the plain forward: no score
 // kernel runs at all); with attn_dst == NULL it is read from the table (save mode).
-// NW > 1: the waves of a workgroup share one long row, take interleaved 64-entry
-// tiles and merge their (m, s, acc) triples through LDS in wave order.
+// The first a.heavy_items workgroups hold one long row each, whose interleaved
+// 64-entry tiles the eight waves share; they merge their (m, s, acc) triples
+// through LDS in wave order.  The others hold eight rows.  One launch for both: a
+// row of 17,500 entries keeps its workgroup busy for half a millisecond, in which a
+// launch of long rows alone leaves the chip idle (2,449,029 nodes, 124 million
+// entries, F = 256, save mode 21.5 + 0.65 ms, 22.0 now; plain, F = 128: 60,000 nodes
+// and 3 million entries 262 us, 167 now, 20,000 and 200,000 57 and 27).
 // ---------------------------------------------------------------------------
 // TRAIN (save mode): the aggregate is accumulated in two parts, entries with a positive score (accp) and the
 // others (acc), with the sums of their weights (sp, sn), and the row statistics are kept for the backward
 // pass; scores then stay in natural units, because the stored row maximum is used as such.
 template <int G, bool TRAIN, int NW>
-__global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_flash_kernel(
+__global__ __launch_bounds__(64 * NW) void agg_gat_flash_kernel(
     AggArgs a, const float* __restrict__ attn_src, const float* __restrict__ attn_dst, int er_stride)
 {
-    static_assert(!(TRAIN && NW > 1), "save mode keeps the long rows on the table kernel");
     constexpr int U = 4;      // entries per batch of the online softmax (2 and 8 measure the same: the kernel waits for memory)
     constexpr float kLog2e = 1.4426950408889634f;
     constexpr float kIn = TRAIN ? 1.0f : kLog2e;       // factor on the scores as they are formed
     constexpr float kEx = TRAIN ? kLog2e : 1.0f;       // factor inside the exponentials
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t slot = NW == 1 ? (int64_t)blockIdx.x * kLightWaves + wave : (int64_t)blockIdx.x;
-    if (slot >= a.row_count) return;          // NW > 1: uniform over the workgroup
-    const int v = __builtin_amdgcn_readfirstlane(a.order[a.row_begin + slot]);
+    const bool heavy = blockIdx.x < a.heavy_items;    // uniform over the workgroup
+    const int64_t slot = heavy ? (int64_t)blockIdx.x : a.heavy_rows + ((int64_t)blockIdx.x - a.heavy_items) * NW + wave;
+    if (slot >= a.n_rows) return;
+    const int v = __builtin_amdgcn_readfirstlane(a.order[slot]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v + 1]);
 
@@ -1279,7 +1303,8 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fla
 
     float m = -INFINITY, s = 0.0f, sp = 0.0f, sn = 0.0f;
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, accp = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int base = lo + (NW == 1 ? 0 : 64 * wave); base < hi; base += 64 * NW) {
+    const int step = heavy ? 64 * NW : 64;
+    for (int base = lo + (heavy ? 64 * wave : 0); base < hi; base += step) {
         const int e = base + lane;
         const bool valid = e < hi;
         const int cnt = min(64, hi - base);
@@ -1359,15 +1384,23 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fla
         }
     }
 
-    if constexpr (NW > 1) {
-        // merge the waves' running triples, in wave order
-        __shared__ float red[NW][6][64];
+    if (heavy) {
+        // merge the waves' running maxima and sums, in wave order
+        __shared__ float red[NW][TRAIN ? 12 : 6][64];
         red[wave][0][lane] = m;
         red[wave][1][lane] = s;
         red[wave][2][lane] = acc.x;
         red[wave][3][lane] = acc.y;
         red[wave][4][lane] = acc.z;
         red[wave][5][lane] = acc.w;
+        if constexpr (TRAIN) {
+            red[wave][6][lane] = sp;
+            red[wave][7][lane] = sn;
+            red[wave][8][lane] = accp.x;
+            red[wave][9][lane] = accp.y;
+            red[wave][10][lane] = accp.z;
+            red[wave][11][lane] = accp.w;
+        }
         __syncthreads();
         if (wave != 0) return;
         float mm = red[0][0][lane];
@@ -1375,6 +1408,10 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fla
         for (int w = 1; w < NW; ++w) mm = fmaxf(mm, red[w][0][lane]);
         s = 0.0f;
         acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (TRAIN) {
+            sp = sn = 0.0f;
+            accp = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float mw = red[w][0][lane];
@@ -1385,6 +1422,14 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void agg_gat_fla
             acc.y = fmaf(red[w][3][lane], f, acc.y);
             acc.z = fmaf(red[w][4][lane], f, acc.z);
             acc.w = fmaf(red[w][5][lane], f, acc.w);
+            if constexpr (TRAIN) {
+                sp = fmaf(red[w][6][lane], f, sp);
+                sn = fmaf(red[w][7][lane], f, sn);
+                accp.x = fmaf(red[w][8][lane], f, accp.x);
+                accp.y = fmaf(red[w][9][lane], f, accp.y);
+                accp.z = fmaf(red[w][10][lane], f, accp.z);
+                accp.w = fmaf(red[w][11][lane], f, accp.w);
+            }
         }
         m = mm;
     }
@@ -1450,33 +1495,23 @@ void launch_gat_pair(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_
 }
 
 template <int NC, int HP, bool HU, bool TRAIN>
-void launch_gat_fast_pair(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t stream)
+void launch_gat_fast(const AggArgs& base, int64_t n_heavy, int64_t N, int waves, hipStream_t stream)
 {
-    if (n_heavy > 0) {
-        AggArgs a = base;
-        a.row_begin = 0;
-        a.row_count = n_heavy;
-        const int64_t blocks = n_heavy * a.nslab;
-        agg_gat_fast_kernel<NC, kHeavyWaves, HP, HU, TRAIN><<<dim3((unsigned)blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
-    }
-    if (N > n_heavy) {
-        AggArgs a = base;
-        a.row_begin = n_heavy;
-        a.row_count = N - n_heavy;
-        const int64_t blocks = (a.row_count * a.nslab + kLightWaves - 1) / kLightWaves;
-        agg_gat_fast_kernel<NC, 1, HP, HU, TRAIN><<<dim3((unsigned)blocks), dim3(64 * kLightWaves), 0, stream>>>(a);
-    }
+    AggArgs a = base;
+    const unsigned blocks = both_classes(a, n_heavy, N, waves);
+    if (waves == 4) agg_gat_fast_kernel<NC, 4, HP, HU, TRAIN><<<dim3(blocks), dim3(64 * 4), 0, stream>>>(a);
+    else            agg_gat_fast_kernel<NC, 8, HP, HU, TRAIN><<<dim3(blocks), dim3(64 * 8), 0, stream>>>(a);
 }
 
 template <int HP, bool HU>
-void dispatch_gat_fast(int nc, bool train, const AggArgs& a, int64_t nh, int64_t N, hipStream_t s)
+void dispatch_gat_fast(int nc, bool train, const AggArgs& a, int64_t nh, int64_t N, int waves, hipStream_t s)
 {
     if (train) {
-        if (nc == 1) launch_gat_fast_pair<1, HP, HU, true>(a, nh, N, s);
-        else launch_gat_fast_pair<2, HP, HU, true>(a, nh, N, s);
+        if (nc == 1) launch_gat_fast<1, HP, HU, true>(a, nh, N, waves, s);
+        else launch_gat_fast<2, HP, HU, true>(a, nh, N, waves, s);
     } else {
-        if (nc == 1) launch_gat_fast_pair<1, HP, HU, false>(a, nh, N, s);
-        else launch_gat_fast_pair<2, HP, HU, false>(a, nh, N, s);
+        if (nc == 1) launch_gat_fast<1, HP, HU, false>(a, nh, N, waves, s);
+        else launch_gat_fast<2, HP, HU, false>(a, nh, N, waves, s);
     }
 }
 
@@ -1588,8 +1623,8 @@ GatRoute gat_route(const AggCall& c)
     const int hp = heads_padded(c.heads);
     const int64_t Dh = c.F / c.heads;
     const int64_t g = Dh / 4;
-    // rows of ordinary length compute the source scores from the gathered rows themselves when a head is
-    // a power-of-two group of four-float lanes; the long rows keep the table of scores
+    // the source scores are computed from the gathered rows themselves when a head is a power-of-two group of
+    // four-float lanes
     r.flash = r.vec == 4 && r.off32 && opt.gat_fast && opt.gat_flash && c.F <= 256 &&
               Dh % 4 == 0 && g <= 64 && (g & (g - 1)) == 0 && aligned_for(c.attn_src, 4, 4);
     // Otherwise, when Z is the library's own buffer and its rows have unused columns behind F, the source
@@ -1706,7 +1741,9 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     a.save_neg = nullptr;
     a.ld_pos = 0;
 
-    int64_t n_heavy = long_rows(p, c.F, gat);
+    // (the edge softmax over unaligned or very large tables has a launch of its own for the long rows)
+    const bool own_launch = gat && !(vec == 4 && opt.gat_fast && gat_route(c).off32);
+    int64_t n_heavy = long_rows(p, c.F, own_launch, gat);
 
     // narrow slabs (32/64/128 columns) use the grouped gather; they need float4 gathers
     // (the maximum is only implemented on whole rows)
@@ -1760,13 +1797,14 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
         const GatRoute route = gat_route(c);
         const bool off32 = route.off32, flash = route.flash, in_rows = route.in_rows;
         const int g = a.Dh / 4;
+        const int waves = softmax_waves(p, c.F);
         if (c.el_ready && !(in_rows && !c.save && a.nslab == 1)) return RETEXO_E_FLAGS;   // the round asked gat_fold_plan
         a.el_stride = in_rows ? c.ldz : hp;
         if (in_rows) el = const_cast<float*>(c.Z) + c.F;
         a.el = el;
         a.er = er;
         // the plain forward over rows whose scores all come from the gathered rows needs no table
-        const bool no_table = flash && !c.save && N > n_heavy && aligned_for(c.attn_dst, 4, 4);
+        const bool no_table = flash && !c.save && aligned_for(c.attn_dst, 4, 4);
         // only the pipelined kernel keeps the backward's statistics: decided before anything is launched,
         // so that the error leaves the workspace and the output untouched
         if (c.save && !(vec == 4 && off32 && opt.gat_fast)) return RETEXO_E_FLAGS;
@@ -1784,29 +1822,17 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
             a.save_neg = (float*)((char*)c.workspace + w.neg);
             a.ld_pos = w.ld_pos;
         }
-        int64_t n_table = N;          // rows [0, n_table) of the schedule go through the table kernels
-        if (flash && N > n_heavy) {
+        if (flash) {
             AggArgs f = a;
             f.nslab = 1;
-            f.row_begin = n_heavy;
-            f.row_count = N - n_heavy;
-            const dim3 grid((unsigned)((f.row_count + kLightWaves - 1) / kLightWaves)), block(64 * kLightWaves);
+            const dim3 grid(both_classes(f, n_heavy, N, waves)), block(64 * waves);
+            const float* ad = no_table ? c.attn_dst : nullptr;
             auto go = [&](auto gtag) {
                 constexpr int GG = decltype(gtag)::value;
-                if (c.save) {
-                    agg_gat_flash_kernel<GG, true, 1><<<grid, block, 0, stream>>>(f, c.attn_src, nullptr, hp);
-                } else if (no_table) {
-                    agg_gat_flash_kernel<GG, false, 1><<<grid, block, 0, stream>>>(f, c.attn_src, c.attn_dst, hp);
-                    if (n_heavy > 0) {
-                        AggArgs fh = f;
-                        fh.row_begin = 0;
-                        fh.row_count = n_heavy;
-                        agg_gat_flash_kernel<GG, false, kHeavyWaves>
-                            <<<dim3((unsigned)n_heavy), dim3(64 * kHeavyWaves), 0, stream>>>(fh, c.attn_src, c.attn_dst, hp);
-                    }
-                } else {
-                    agg_gat_flash_kernel<GG, false, 1><<<grid, block, 0, stream>>>(f, c.attn_src, nullptr, hp);
-                }
+                if (c.save && waves == 4) agg_gat_flash_kernel<GG, true, 4><<<grid, block, 0, stream>>>(f, c.attn_src, nullptr, hp);
+                else if (c.save)          agg_gat_flash_kernel<GG, true, 8><<<grid, block, 0, stream>>>(f, c.attn_src, nullptr, hp);
+                else if (waves == 4)      agg_gat_flash_kernel<GG, false, 4><<<grid, block, 0, stream>>>(f, c.attn_src, ad, hp);
+                else                      agg_gat_flash_kernel<GG, false, 8><<<grid, block, 0, stream>>>(f, c.attn_src, ad, hp);
             };
             switch (g) {
                 case 1:  go(std::integral_constant<int, 1>{}); break;
@@ -1817,13 +1843,9 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
                 case 32: go(std::integral_constant<int, 32>{}); break;
                 default: go(std::integral_constant<int, 64>{}); break;
             }
-            n_table = no_table ? 0 : n_heavy;
-        }
-        if (n_table == 0) {
-            // nothing left for the table kernels
         } else if (vec == 4 && off32 && opt.gat_fast) {
-            if (hp == 4) { if (hu) dispatch_gat_fast<4, true>(nc, c.save, a, n_heavy, n_table, stream); else dispatch_gat_fast<4, false>(nc, c.save, a, n_heavy, n_table, stream); }
-            else         { if (hu) dispatch_gat_fast<8, true>(nc, c.save, a, n_heavy, n_table, stream); else dispatch_gat_fast<8, false>(nc, c.save, a, n_heavy, n_table, stream); }
+            if (hp == 4) { if (hu) dispatch_gat_fast<4, true>(nc, c.save, a, n_heavy, N, waves, stream); else dispatch_gat_fast<4, false>(nc, c.save, a, n_heavy, N, waves, stream); }
+            else         { if (hu) dispatch_gat_fast<8, true>(nc, c.save, a, n_heavy, N, waves, stream); else dispatch_gat_fast<8, false>(nc, c.save, a, n_heavy, N, waves, stream); }
         } else if (vec == 4) {
             if (hp == 4) { if (hu) dispatch_gat_nc<4, 4, true>(nc, a, n_heavy, N, stream); else dispatch_gat_nc<4, 4, false>(nc, a, n_heavy, N, stream); }
             else         { if (hu) dispatch_gat_nc<4, 8, true>(nc, a, n_heavy, N, stream); else dispatch_gat_nc<4, 8, false>(nc, a, n_heavy, N, stream); }

@@ -52,8 +52,11 @@ struct BwdArgs {
     f32x4* nbr;            // [N, HP]  {er_v, max_v, 1/sum_v, c_v}
     float* ddst;           // [N, HP]
     float* dsrc;           // [N, HP]
-    int64_t row_begin;
+    int64_t row_begin;     // range of plan order handled by a launch ("dst" pass)
     int64_t row_count;
+    int64_t n_rows;        // all rows, and how many at the head of the plan order get a workgroup each ("src" pass,
+    int64_t heavy_rows;    // whose one launch covers all rows)
+    int waves;             // ... and the waves of its workgroups (see softmax_waves)
     int64_t F;
     int heads;
     int Dh;
@@ -391,20 +394,23 @@ __global__ __launch_bounds__(64 * kLightWaves) void gat_bwd_dst_flash_kernel(Bwd
 
 // ---------------------------------------------------------------------------
 // "src" pass: row u, gathers G_v for v in N(u) (the entries (v,u) by symmetry).
-// Writes dZ[u,:] and dsrc[u,h].
+// Writes dZ[u,:] and dsrc[u,h].  The first a.heavy_rows workgroups share one long row among their waves, the others hold
+// a row per wave: in a launch of their own the longest rows leave the chip idle (2,449,029 nodes, 124 million entries,
+// F = 256: 22.6 + 0.70 ms, 23.1 now; save mode forward and backward of 60,000 nodes and 3 million entries 1,360 us, 930 now).
 // ---------------------------------------------------------------------------
 template <int VEC, int NC, int NW, int HP, bool HU>
-__global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void gat_bwd_src_kernel(BwdArgs a)
+__global__ __launch_bounds__(64 * NW) void gat_bwd_src_kernel(BwdArgs a)
 {
-    constexpr int WAVES = NW == 1 ? kLightWaves : NW;
     constexpr int U = NC * VEC >= 16 ? 2 : kUnroll;   // rows in flight per batch (fewer when a row fills many registers)
     constexpr int Q = HU ? 1 : VEC;
-    __shared__ float wl[WAVES][2][HP][64];     // per edge of the tile: alpha_vu and alpha_vu * LeakyReLU'
+    // per edge of the waves' tiles: alpha_vu and alpha_vu * LeakyReLU'; in the end the sums of a long row's waves
+    __shared__ float lds[NW * 64 * (2 * HP > NC * VEC ? 2 * HP : NC * VEC)];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t item = (NW == 1) ? (int64_t)blockIdx.x * kLightWaves + wave : (int64_t)blockIdx.x;
-    if (item >= a.row_count) return;
-    const int u = __builtin_amdgcn_readfirstlane(a.order[a.row_begin + item]);
+    const bool heavy = blockIdx.x < a.heavy_rows;     // uniform over the workgroup
+    const int64_t item = heavy ? (int64_t)blockIdx.x : a.heavy_rows + ((int64_t)blockIdx.x - a.heavy_rows) * NW + wave;
+    if (item >= a.n_rows) return;
+    const int u = __builtin_amdgcn_readfirstlane(a.order[item]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[u]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[u + 1]);
 
@@ -429,8 +435,8 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void gat_bwd_src
             q[c][k] = 0.0f;
         }
     }
-    float* wp = &wl[wave][0][0][0];
-    float* wt = &wl[wave][1][0][0];
+    float* wp = lds + wave * (2 * HP * 64);
+    float* wt = wp + HP * 64;
 
     float elu[HP], tc[HP];
 #pragma unroll
@@ -439,7 +445,8 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void gat_bwd_src
         tc[h] = 0.0f;
     }
 
-    for (int base = lo + 64 * (NW == 1 ? 0 : wave); base < hi; base += 64 * NW) {
+    const int step = heavy ? 64 * NW : 64;
+    for (int base = lo + (heavy ? 64 * wave : 0); base < hi; base += step) {
         const int e = base + lane;
         const bool valid = e < hi;
         const int cnt = min(64, hi - base);
@@ -517,8 +524,10 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void gat_bwd_src
 #pragma unroll
     for (int h = 0; h < HP; ++h) ds[h] = head_total<NC, Q>(q, hc, h) - wave_sum(tc[h]);
 
-    if constexpr (NW > 1) {
-        __shared__ float red[NW][NC * VEC][64];
+    if (heavy) {
+        typedef float sums_t[NC * VEC][64];
+        sums_t* red = reinterpret_cast<sums_t*>(lds);
+        __syncthreads();                                 // every wave is done with its weights
         __shared__ float dred[NW][HP];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -799,22 +808,19 @@ void launch_dst_flash(const BwdArgs& a, int hp, unsigned blocks, hipStream_t str
 template <int VEC, int NC, int HP, bool HU>
 void launch_passes(const BwdArgs& base, int first_pass, int64_t n_heavy, int64_t N, hipStream_t stream, int flash_g = 0)
 {
-    for (int pass = first_pass; pass < 2; ++pass) {
+    if (first_pass == 0) {
         if (n_heavy > 0) {
             BwdArgs a = base;
             a.row_begin = 0;
             a.row_count = n_heavy;
-            if (pass == 0)
-                gat_bwd_dst_kernel<VEC, NC, kHeavyWaves, HP, HU><<<dim3((unsigned)n_heavy), dim3(64 * kHeavyWaves), 0, stream>>>(a);
-            else
-                gat_bwd_src_kernel<VEC, NC, kHeavyWaves, HP, HU><<<dim3((unsigned)n_heavy), dim3(64 * kHeavyWaves), 0, stream>>>(a);
+            gat_bwd_dst_kernel<VEC, NC, kHeavyWaves, HP, HU><<<dim3((unsigned)n_heavy), dim3(64 * kHeavyWaves), 0, stream>>>(a);
         }
         if (N > n_heavy) {
             BwdArgs a = base;
             a.row_begin = n_heavy;
             a.row_count = N - n_heavy;
             const unsigned blocks = (unsigned)((a.row_count + kLightWaves - 1) / kLightWaves);
-            if (pass == 0 && flash_g > 0) {
+            if (flash_g > 0) {
                 switch (flash_g) {
                     case 1:  launch_dst_flash<1>(a, HP, blocks, stream); break;
                     case 2:  launch_dst_flash<2>(a, HP, blocks, stream); break;
@@ -824,12 +830,14 @@ void launch_passes(const BwdArgs& base, int first_pass, int64_t n_heavy, int64_t
                     case 32: launch_dst_flash<32>(a, HP, blocks, stream); break;
                     default: launch_dst_flash<64>(a, HP, blocks, stream); break;
                 }
-            } else if (pass == 0)
+            } else {
                 gat_bwd_dst_kernel<VEC, NC, 1, HP, HU><<<dim3(blocks), dim3(64 * kLightWaves), 0, stream>>>(a);
-            else
-                gat_bwd_src_kernel<VEC, NC, 1, HP, HU><<<dim3(blocks), dim3(64 * kLightWaves), 0, stream>>>(a);
+            }
         }
     }
+    const unsigned blocks = (unsigned)(base.heavy_rows + (N - base.heavy_rows + base.waves - 1) / base.waves);
+    if (base.waves == 4) gat_bwd_src_kernel<VEC, NC, 4, HP, HU><<<dim3(blocks), dim3(64 * 4), 0, stream>>>(base);
+    else                 gat_bwd_src_kernel<VEC, NC, 8, HP, HU><<<dim3(blocks), dim3(64 * 8), 0, stream>>>(base);
 }
 
 template <int VEC, int HP, bool HU>
@@ -947,6 +955,9 @@ int launch_aggregate_backward(const AggBackwardCall& c, hipStream_t stream)
     a.dsrc = (float*)(ws + w.dsrc);
     a.row_begin = 0;
     a.row_count = 0;
+    a.n_rows = N;
+    a.heavy_rows = long_rows(p, F, false, true);
+    a.waves = softmax_waves(p, F);
     a.F = F;
     a.heads = c.heads;
     a.Dh = (int)(F / c.heads);
@@ -984,7 +995,7 @@ int launch_aggregate_backward(const AggBackwardCall& c, hipStream_t stream)
     }
 
     const AggOptions& opt = agg_options();
-    const int64_t n_heavy = long_rows(p, F, true);
+    const int64_t n_heavy = long_rows(p, F, true);       // of the "dst" pass
 
     // 16-byte gathers need every table aligned, rows padded to whole vectors and F a multiple of 4
     // (the inner products must not see padding columns)

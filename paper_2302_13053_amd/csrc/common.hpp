@@ -71,20 +71,37 @@ AggOptions& agg_options();
 // graph of 108,393 entries and 256 columns the longest row's 320 entries alone took 57 us of an aggregation that needs 20.
 // Kernels that need a launch of their own for the long rows, one after the other (own_launch), pay for it with a launch
 // and with the time in which the long rows run alone: the line lies four times as high for the smallest, twice otherwise
-// (edge softmax and its backward with the lower line: 3,130 nodes of 5 entries 126 -> 138 us, 7,687 of 194 303 -> 326).
-static inline int64_t long_rows(const retexo_plan* p, int64_t F, bool own_launch)
+// (edge softmax of 16-bit tables or unaligned rows, and the backward's first pass).  The edge softmax in one launch (`softmax`) takes the lower line as well, but for graphs whose mean row is long itself
+// (kLongMean entries): there the short rows fill the chip to the end (3,000 nodes of 150 entries, up to 300: 64 columns
+// forward and backward 140 us with the line at twice the mean and eight waves, 124 so, 123 in two launches; 20,000 of 200
+// 510, 470 and 538).
+constexpr int64_t kLongMean = 128;
+static inline int64_t long_rows(const retexo_plan* p, int64_t F, bool own_launch, bool softmax = false)
 {
     int64_t at_least = agg_options().heavy_degree;
     if (at_least == kHeavyDegree) {
         const int64_t mean = p->N > 0 ? p->nnz / p->N : 0, floor = own_launch ? 256 : 64;
         at_least = (p->nnz * F) >> (own_launch ? 19 : 20);
-        const int64_t above_mean = (own_launch ? 4 : 2) * mean, least = above_mean > floor ? above_mean : floor;
+        const int64_t above_mean = (own_launch || (softmax && mean >= kLongMean) ? 4 : 2) * mean;
+        const int64_t least = above_mean > floor ? above_mean : floor;
         at_least = at_least < least ? least : at_least;       // (64 or more)
         at_least = at_least > kHeavyDegree ? kHeavyDegree : at_least;
     }
     for (int i = 0; i < kPlanThresholdCount; ++i)
         if (kPlanThresholds[i] >= at_least) return p->rows_at_least[i];
     return 0;
+}
+
+// Waves per workgroup of the edge softmax kernels whose one launch covers both classes of rows: eight, which share a long
+// row, or four where the short rows take far longer than the longest row shared by four (0.07 us per entry, beside the
+// short ones; 2^30 floats gathered take 0.7 ms) or every row is long.  Four leave fewer registers of a compute unit unused:
+// 20 and 28 waves of the backward and the save mode kernel, 16 and 24 in workgroups of eight.  Forward and backward over
+// 1,000,000 nodes of 20 entries, 64 columns: 3.76 ms with four, 4.27 with eight (4.03 in two launches); 60,000 of 50, 256
+// columns, 980 and 920 us (1,360).  Known slower than in two launches: rounds of 188 columns over 3,000 to 50,000 nodes
+// of 150 to 300 entries, 3 to 4 %.
+static inline int softmax_waves(const retexo_plan* p, int64_t F)
+{
+    return p->nnz * F >= (1ll << 30) || p->nnz >= kLongMean * p->N ? 4 : 8;
 }
 
 // Zero `bytes` (a multiple of 4) at `p` with a small kernel.  The stream-ordered entry points use this
