@@ -98,8 +98,8 @@ static inline int64_t long_rows(const retexo_plan* p, int64_t F, bool own_launch
 // short ones; 2^30 floats gathered take 0.7 ms) or every row is long.  Four leave fewer registers of a compute unit unused:
 // 20 and 28 waves of the backward and the save mode kernel, 16 and 24 in workgroups of eight.  Forward and backward over
 // 1,000,000 nodes of 20 entries, 64 columns: 3.76 ms with four, 4.27 with eight (4.03 in two launches); 60,000 of 50, 256
-// columns, 980 and 920 us (1,360).  Known slower than in two launches: rounds of 188 columns over 3,000 to 50,000 nodes
-// of 150 to 300 entries, 3 to 4 %.
+// columns, 980 and 920 us (1,360).  Known slower than in two launches: 50,000 nodes of 300 entries, whose 538 long
+// rows fill the chip by themselves, with 188 to 256 columns: 2 to 5 %.
 static inline int softmax_waves(const retexo_plan* p, int64_t F)
 {
     return p->nnz * F >= (1ll << 30) || p->nnz >= kLongMean * p->N ? 4 : 8;

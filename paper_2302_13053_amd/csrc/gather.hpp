@@ -91,6 +91,33 @@ __device__ __forceinline__ float wave_sum(float x)
     return x;
 }
 
+// several values at once, step by step: COUNT independent moves are in flight at each of the six steps (one value after the
+// other is a chain of 6 * COUNT of them, which the compiler may or may not interleave)
+template <int COUNT>
+__device__ __forceinline__ void wave_max(float (&x)[COUNT])
+{
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        float t[COUNT];
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) t[i] = __shfl_xor(x[i], m, 64);
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) x[i] = fmaxf(x[i], t[i]);
+    }
+}
+template <int COUNT>
+__device__ __forceinline__ void wave_sum(float (&x)[COUNT])
+{
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        float t[COUNT];
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) t[i] = __shfl_xor(x[i], m, 64);
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) x[i] += t[i];
+    }
+}
+
 __device__ __forceinline__ int bcast_i(int x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
 __device__ __forceinline__ float bcast_f(float x, int lane)
 {
