@@ -13,6 +13,8 @@
 //   * 64-column slabs, one row per 8-lane group, walked source range by source range so that the
 //     slab of the current range stays in L2 (dense graphs; same plan split as the fp32 path)
 //   * edge softmax, whole rows per wave, software-pipelined with per-edge weights in LDS
+#include <algorithm>
+
 #include "common.hpp"
 #include "gather.hpp"
 
@@ -83,27 +85,93 @@ __device__ __forceinline__ uint16_t encode1(float x)
     }
 }
 
-// One row per wave (rows in turn), VEC consecutive columns per lane: 16-byte reads and 8-byte writes where rows allow
-// them.  Bound by its bytes: Reddit-shaped table, 232,965 x 602, 344 -> 149 us = 5.6 TB/s
-// (one element per thread, with a division, before).
-template <int FMT, int VEC>
-__global__ __launch_bounds__(256) void store_rows_kernel(int64_t N, int64_t F, const float* __restrict__ src,
-                                                          int64_t lds, uint16_t* __restrict__ dst, int64_t ldd)
+// `count` (1 to 4) converted elements to p, which is on 8 bytes
+template <int FMT>
+__device__ __forceinline__ void store4(uint16_t* p, const f32x4& x, int count)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t waves = (int64_t)gridDim.x * 4;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < N; r += waves) {
-        const float* from = src + r * lds;
-        uint16_t* to = dst + r * ldd;
-        for (int64_t c = lane * VEC; c < F; c += 64 * VEC) {
-            if (VEC == 4 && c + 4 <= F) {
-                const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(from + c));
-                const u32x2 y = {(uint32_t)encode1<FMT>(x.x) | (uint32_t)encode1<FMT>(x.y) << 16,
-                                 (uint32_t)encode1<FMT>(x.z) | (uint32_t)encode1<FMT>(x.w) << 16};
-                *reinterpret_cast<u32x2*>(to + c) = y;
+    const u32x2 y = {(uint32_t)encode1<FMT>(x.x) | (uint32_t)encode1<FMT>(x.y) << 16,
+                     (uint32_t)encode1<FMT>(x.z) | (uint32_t)encode1<FMT>(x.w) << 16};
+    if (count == 4) *reinterpret_cast<u32x2*>(p) = y;
+    else {
+        if (count >= 2) *reinterpret_cast<uint32_t*>(p) = y.x;
+        if (count == 3) p[2] = (uint16_t)y.y;
+        if (count == 1) p[0] = (uint16_t)y.x;
+    }
+}
+
+// 2^lg lanes per row, VEC consecutive columns per lane (16-byte reads and 8-byte writes where rows allow them), U rows in
+// flight per lane.  Bound by its bytes: Reddit-shaped table, 232,965 x 602, 143 us = 5.9 TB/s.
+// Rows that fewer lanes cover have several of them in a wave: with a wave each most lanes
+// are idle (2,400,000 x 8 without padding 236 us, 20 now; x 41 in rows of 64 491 and 176).
+// STREAM: past the caches, for a table that they cannot hold anyway (2,400,000 x 8 of rows of 128 bytes 159 -> 78 us;
+// 1,000,000 x 8, which the last of them holds, 30 -> 37).
+template <int FMT, int VEC, int U, bool STREAM>
+__global__ __launch_bounds__(256) void store_rows_kernel(int64_t N, int64_t F, const float* __restrict__ src,
+                                                          int64_t lds, uint16_t* __restrict__ dst, int64_t ldd, int lg)
+{
+    const int64_t apart = 256 >> lg, step = (int64_t)gridDim.x * apart * U;      // rows between a thread's
+    const int64_t c0 = (int64_t)(threadIdx.x & ((1u << lg) - 1u)) * VEC, cstep = (int64_t)VEC << lg;
+    for (int64_t r0 = (int64_t)blockIdx.x * apart * U + (threadIdx.x >> lg); r0 < N; r0 += step) {
+        for (int64_t c = c0; c < F; c += cstep) {
+            const float* from = src + r0 * lds + c;
+            uint16_t* to = dst + r0 * ldd + c;
+            const int count = (int)min((int64_t)VEC, F - c);
+            if constexpr (VEC == 4) {
+                f32x4 x[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    if (r0 + t * apart >= N) break;
+                    const float* f = from + t * apart * lds;
+                    // (behind the last columns of a row lies its padding; the last row may end with the buffer)
+                    if (count == 4 || r0 + t * apart < N - 1) {
+                        if constexpr (STREAM) x[t] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(f));
+                        else x[t] = *reinterpret_cast<const f32x4*>(f);
+                    } else {
+                        x[t] = f32x4{f[0], 0.0f, 0.0f, 0.0f};
+                        if (count > 1) x[t].y = f[1];
+                        if (count > 2) x[t].z = f[2];
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    if (r0 + t * apart >= N) break;
+                    store4<FMT>(to + t * apart * ldd, x[t], count);
+                }
             } else {
-                for (int64_t k = c; k < c + VEC && k < F; ++k) to[k] = encode1<FMT>(from[k]);
+                float x[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t) x[t] = r0 + t * apart < N ? from[t * apart * lds] : 0.0f;
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    if (r0 + t * apart < N) to[t * apart * ldd] = encode1<FMT>(x[t]);
             }
+        }
+    }
+}
+
+// the same for rows without padding, which are one run of n elements
+template <int FMT>
+__global__ __launch_bounds__(256) void store_run_kernel(int64_t n, const float* __restrict__ src, uint16_t* __restrict__ dst)
+{
+    constexpr int U = 4;
+    const int64_t step = (int64_t)gridDim.x * 256 * 4;
+    for (int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i0 < n; i0 += step * U) {
+        f32x4 x[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            const int64_t i = i0 + t * step;
+            if (i + 4 <= n) {
+                x[t] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + i));
+            } else if (i < n) {
+                x[t] = f32x4{src[i], 0.0f, 0.0f, 0.0f};
+                if (i + 1 < n) x[t].y = src[i + 1];
+                if (i + 2 < n) x[t].z = src[i + 2];
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            const int64_t i = i0 + t * step;
+            if (i < n) store4<FMT>(dst + i, x[t], (int)min((int64_t)4, n - i));
         }
     }
 }
@@ -1139,16 +1207,37 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
 
 }  // namespace
 
+template <int FMT>
+static void store(int64_t N, int64_t F, const float* src, int64_t lds, uint16_t* dst, int64_t ldd, hipStream_t stream)
+{
+    const bool bases = (uintptr_t)src % 16 == 0 && (uintptr_t)dst % 8 == 0, wide = bases && lds % 4 == 0 && ldd % 4 == 0;
+    auto blocks = [](int64_t items, int64_t per) { return dim3((unsigned)std::min<int64_t>((items + per - 1) / per, 16384)); };
+    if (bases && lds == F && ldd == F) {
+        store_run_kernel<FMT><<<blocks(N * F, 4096), dim3(256), 0, stream>>>(N * F, src, dst);
+        return;
+    }
+    const int64_t vectors = wide ? (F + 3) / 4 : F;
+    int lg = 0;
+    while (lg < 6 && (1 << lg) < vectors) ++lg;
+    auto go = [&](auto kernel, int rows) {
+        kernel<<<blocks(N, (256 >> lg) * rows), dim3(256), 0, stream>>>(N, F, src, lds, dst, ldd, lg);
+    };
+    const bool stream_past = N * lds * 4 > (256ll << 20);
+    // (rows of several column steps have enough in flight by themselves: 232,965 x 602 unaligned 226 us with four rows,
+    // 209 with one; x 256 73 and 90)
+    if (!wide && F <= 256) go(store_rows_kernel<FMT, 1, 4, false>, 4);
+    else if (!wide)        go(store_rows_kernel<FMT, 1, 1, false>, 1);
+    else if (vectors > 64) go(store_rows_kernel<FMT, 4, 1, true>, 1);
+    else if (stream_past)  go(store_rows_kernel<FMT, 4, 4, true>, 4);
+    else                   go(store_rows_kernel<FMT, 4, 4, false>, 4);
+}
+
 int launch_store_rows(int storage, int64_t N, int64_t F, const float* src, int64_t lds, void* dst, int64_t ldd,
                       hipStream_t stream)
 {
     if (N == 0 || F == 0) return RETEXO_OK;
-    const int64_t blocks = (N + 3) / 4;
-    const dim3 grid((unsigned)(blocks < 16384 ? blocks : 16384));
-    const bool wide = lds % 4 == 0 && ldd % 4 == 0 && (uintptr_t)src % 16 == 0 && (uintptr_t)dst % 8 == 0;
-    auto go = [&](auto kernel) { kernel<<<grid, dim3(256), 0, stream>>>(N, F, src, lds, (uint16_t*)dst, ldd); };
-    if (storage == RETEXO_STORE_BF16) { if (wide) go(store_rows_kernel<FMT_BF16, 4>); else go(store_rows_kernel<FMT_BF16, 1>); }
-    else { if (wide) go(store_rows_kernel<FMT_FP16, 4>); else go(store_rows_kernel<FMT_FP16, 1>); }
+    if (storage == RETEXO_STORE_BF16) store<FMT_BF16>(N, F, src, lds, (uint16_t*)dst, ldd, stream);
+    else store<FMT_FP16>(N, F, src, lds, (uint16_t*)dst, ldd, stream);
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
     return RETEXO_OK;
 }
