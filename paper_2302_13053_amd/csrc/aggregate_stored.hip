@@ -375,10 +375,10 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void stored_line
 // float32 kernel 20.1) and the running sums, twice its bytes per slab.  Steps of eight entries: the same within 0.5 %, in 117
 // registers instead of 85.
 // ---------------------------------------------------------------------------
-template <int FMT, bool WEIGHTED>
+template <int FMT, bool WEIGHTED, int U>
 __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(StoredArgs a)
 {
-    constexpr int LPG = 8, G = 64 / LPG, U = 4;
+    constexpr int LPG = 8, G = 64 / LPG;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t bundles = (a.row_count + G - 1) / G;
@@ -1138,8 +1138,12 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
             if (N > n_long) {
                 a.row_begin = n_long;
                 a.row_count = N - n_long;
-                if (a.wsrc) stored_rowgroup_kernel<FMT, true><<<dim3((unsigned)blocks), dim3(64 * kLightWaves), 0, stream>>>(a);
-                else stored_rowgroup_kernel<FMT, false><<<dim3((unsigned)blocks), dim3(64 * kLightWaves), 0, stream>>>(a);
+                const dim3 grid((unsigned)blocks), block(64 * kLightWaves);
+                const bool eight = parts <= 2 || (!a.wsrc && a.nslab == 1);      // entries per step, see the kernel
+                if (a.wsrc && eight)  stored_rowgroup_kernel<FMT, true, 8><<<grid, block, 0, stream>>>(a);
+                else if (a.wsrc)      stored_rowgroup_kernel<FMT, true, 4><<<grid, block, 0, stream>>>(a);
+                else if (eight)       stored_rowgroup_kernel<FMT, false, 8><<<grid, block, 0, stream>>>(a);
+                else                  stored_rowgroup_kernel<FMT, false, 4><<<grid, block, 0, stream>>>(a);
             }
         }
     } else if (!gat) {
