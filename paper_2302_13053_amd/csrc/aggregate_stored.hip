@@ -372,8 +372,12 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void stored_line
 // no weights, and the next step's gathers are issued before the current ones are added up.
 // Reddit-shaped graph, 602 columns, bf16, four ranges: 2.17 -> 1.94 ms per range, long rows 0.335 -> 0.297, the whole mean
 // 10.36 -> 9.05 ms with the store; gcn_sym 13.0 -> 11.9.  What is left is the L2 requests and misses of the gathers (18.8 TB/s; the
-// float32 kernel 20.1) and the running sums, twice its bytes per slab.  Steps of eight entries: the same within 0.5 %, in 117
-// registers instead of 85.
+// float32 kernel 20.1) and the running sums, twice its bytes per slab.
+// U entries per step: eight keep twice as many gathers in flight per wave, four more waves (85 registers instead of 117).
+// Eight where the slab of the table fits L2 or nearly does, so that latency and not misses bounds the call (bf16 mean, 8,847
+// nodes of 328 entries, 256 columns 97 us with eight, 108 with four; 100,000 of 100 438 and 472, gcn_sym 606 and 631), and
+// without weights also where it is the only slab (600,000 nodes of 120, 64 columns 2,240 and 2,572); four otherwise
+// (200 columns 8,279 and 8,101, gcn_sym 10,748 and 9,640; the Reddit-shaped mean of 602 columns 9,081 and 9,034).
 // ---------------------------------------------------------------------------
 template <int FMT, bool WEIGHTED, int U>
 __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(StoredArgs a)
