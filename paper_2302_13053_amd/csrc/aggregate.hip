@@ -216,41 +216,37 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
 // xor-shuffles when the row is done.  Same ownership rules as above: one wave
 // (or one workgroup for long rows) writes an output element, in a fixed order.
 // ---------------------------------------------------------------------------
-// One 64-edge tile of the grouped gather.  Each lane holds one neighbour: the byte offset of its row or, for tables of
-// 4 GiB and more, its id, and its gcn weight.  Step t hands entry t*G + g to group g with a wave shuffle.  All loads of a
-// batch of up to 8 steps are issued before their FMAs, and nothing in the batch branches.
-// What does not exist (entries past the end of a partial tile, columns past the row width):
-//   with weights (BUFFER, below 4 GiB): an offset past the table's end, which fetches nothing (load_entry);
-//   otherwise entries fetch a valid row (id 0) and have the loaded values replaced by zero, where the tile is not FULL, and
-//   columns fetch the last valid vector of the slab and never store.  As offsets, each step had a saturating addition more:
-//   the long rows of 100,000 nodes and 10 million entries, 256 columns, 35.2 us so and 37.0.
-template <int LPG, bool FULL, bool WEIGHTED, bool OFF32>
+// One 64-edge tile of the grouped gather.  Each lane holds one neighbour: the byte offset of its row (kNoEntry past the
+// end of a partial tile) or, for tables of 4 GiB and more, its id, and its gcn weight.  Step t hands entry t*G + g to
+// group g with a wave shuffle.  All loads of a batch of up to 8 steps are issued before their FMAs, and nothing in the
+// batch branches.
+//   OFF32: every row offset fits 32 bits, so the table is a buffer and what does not exist fetches nothing (load_entry);
+//   otherwise lanes past the end fetch a valid address (id 0) and have the loaded values replaced by zero, and lanes past
+//   the row width fetch the last valid vector of the slab and never store
+// Without weights the masked form of both, with one for whole tiles that tests nothing, takes 72 registers instead of 60 and
+// so a workgroup less per CU: long rows of the Reddit-shaped graph 88.7 us per range and slab group so, 86.7 as offsets; where
+// a wave has one or two tiles (100,000 nodes and 10 million entries, 256 columns) 35.2 so and 37.0.
+template <int LPG, bool WEIGHTED, bool OFF32>
 __device__ __forceinline__ void grouped_tile(const char* zbase, table_t table, uint32_t colbytes, int64_t rowbytes,
                                              uint32_t my_off, int my_u, float my_w, int cnt, int g,
                                              float (&acc)[4])
 {
-    constexpr bool BUFFER = OFF32 && WEIGHTED;
     constexpr int G = 64 / LPG;
     constexpr int STEPS = 64 / G;
     constexpr int U = STEPS < 8 ? STEPS : 8;
 #pragma unroll
     for (int t0 = 0; t0 < STEPS; t0 += U) {
-        if (!FULL && t0 * G >= cnt) break;
+        if (t0 * G >= cnt) break;
         f32x4 z[U];
         float w[U];
 #pragma unroll
         for (int t = 0; t < U; ++t) {
             const int j = (t0 + t) * G + g;
-            if constexpr (BUFFER) {
+            if constexpr (OFF32) {
                 z[t] = __builtin_bit_cast(f32x4, load_entry(table, (uint32_t)__shfl((int)my_off, j, 64), colbytes));
-            } else if constexpr (OFF32) {
-                const uint32_t off = (uint32_t)__shfl((int)my_off, j, 64) + colbytes;
-                z[t] = *reinterpret_cast<const f32x4*>(zbase + off);
             } else {
                 const int u = __shfl(my_u, j, 64);
                 z[t] = *reinterpret_cast<const f32x4*>(zbase + (int64_t)u * rowbytes + colbytes);
-            }
-            if constexpr (!BUFFER && !FULL) {
                 const bool ok = j < cnt;
                 z[t].x = ok ? z[t].x : 0.0f;
                 z[t].y = ok ? z[t].y : 0.0f;
@@ -307,9 +303,8 @@ __global__ __launch_bounds__(64 * NW) void agg_grouped_kernel(AggArgs a)
     const bool writer = act && g == 0 && wave == 0;
     const int valid = (int)min((int64_t)4, a.F - col);
     const char* zbase = reinterpret_cast<const char*>(a.Z);
-    constexpr bool BUFFER = OFF32 && WEIGHTED;
-    const table_t table = buffer_table(a.Z, BUFFER ? a.table_bytes : 0u);
-    const uint32_t colbytes = act ? (uint32_t)(col * 4) : BUFFER ? kNoEntry : (uint32_t)((a.F - 1) / 4 * 16);
+    const table_t table = buffer_table(a.Z, OFF32 ? a.table_bytes : 0u);
+    const uint32_t colbytes = act ? (uint32_t)(col * 4) : OFF32 ? kNoEntry : (uint32_t)((a.F - 1) / 4 * 16);
     const int64_t rowbytes = a.ldz * 4;
     float* orow = a.out + (int64_t)v * a.ldo;
 
@@ -340,12 +335,8 @@ __global__ __launch_bounds__(64 * NW) void agg_grouped_kernel(AggArgs a)
             nxt_w = WEIGHTED ? (en < hi ? a.wsrc[nxt_u] : 0.0f) : 1.0f;
         }
         const int cnt = min(64, hi - base);
-        const uint32_t off = OFF32 ? (uint32_t)my_u * (uint32_t)rowbytes : 0u;
-        const uint32_t my_off = BUFFER && base + lane >= hi ? kNoEntry : off;
-        if (!BUFFER && cnt == 64)
-            grouped_tile<LPG, true, WEIGHTED, OFF32>(zbase, table, colbytes, rowbytes, my_off, my_u, my_w, cnt, g, acc);
-        else
-            grouped_tile<LPG, false, WEIGHTED, OFF32>(zbase, table, colbytes, rowbytes, my_off, my_u, my_w, cnt, g, acc);
+        const uint32_t my_off = base + lane < hi ? (uint32_t)my_u * (uint32_t)rowbytes : kNoEntry;
+        grouped_tile<LPG, WEIGHTED, OFF32>(zbase, table, colbytes, rowbytes, my_off, my_u, my_w, cnt, g, acc);
     }
     // combine the lane groups, then the waves (in wave order)
 #pragma unroll

@@ -446,7 +446,8 @@ __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(Store
     const int gaddr = (lane - li) * 4;          // ds_bpermute byte address of this group's lane 0
     // Neighbour ids: every lane of a group fetches eight consecutive ids at a time, so a group reads col_idx in
     // whole cache lines (64 entries) a block ahead of its use; entry e of a block sits in component e % 8 of the
-    // group's lane e / 8.  Past the end of a row: id 0 with weight zero.
+    // group's lane e / 8.  Past the end of a row: id -1, which becomes kNoEntry and fetches zeros, so that nothing of an
+    // unrelated row can reach the sum.
     constexpr int IPL = 8, BLOCK = IPL * LPG;
     typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));      // 4-byte aligned 16-byte load
     int nxt_u[IPL];
