@@ -104,6 +104,7 @@ struct Thresholds { int t[kPlanThresholdCount]; };
 struct RowStats {
     uint32_t at_least[kPlanThresholdCount];
     uint32_t largest, bad;
+    uint32_t top;                        // rows of kTopDegree entries and more (larger graphs only)
 };
 __device__ __forceinline__ void add_row(RowStats& st, int32_t d, const Thresholds& th)
 {
@@ -127,6 +128,7 @@ __device__ __forceinline__ void gather_stats(const RowStats& st, RowStats* all)
     for (int m = 32; m >= 1; m >>= 1) top = max(top, __shfl_xor(top, m, 64));
     if (lane == 0) atomicMax(&all->largest, top);
     if (st.bad) atomicOr(&all->bad, 1u);
+    if (st.top) atomicAdd(&all->top, st.top);
     __syncthreads();
 }
 
@@ -213,26 +215,41 @@ __global__ __launch_bounds__(kOrderThreads) void small_order_kernel(
     }
 }
 
-// Larger graphs: up to kOrderBlocks workgroups of consecutive rows, two launches per digit of 10 bits: every
-// workgroup counts its rows' digits, then every workgroup adds up the counts before its own and moves its rows.
+// Larger graphs: workgroups of consecutive rows, two launches per digit of 10 bits: every workgroup counts its rows'
+// digits, then every workgroup adds up the counts before its own and moves its rows.
 // The first launch also makes the degrees; its largest says which digit is the last (later launches find nothing
-// to do).  A whole plan of 19,717 rows 90 -> 45 us, 232,965 155 -> 95, 2,449,029 229 -> 180.  128 workgroups, since each
-// reads every workgroup's counts (64: 85 us and 247), of at least 2,048 rows, or 1,024 up to 32,768 rows (100,000 rows in
-// pieces of 1,024: 83 us, of 2,048: 72).
+// to do).  A whole plan of 19,717 rows 90 -> 45 us, 232,965 155 -> 95, 2,449,029 229 -> 180.
+// Degrees take part up to kTopDegree, two digits.  A graph of less than 2^31 entries has at most kTopRows rows that are
+// longer: the first pass that moves rows lists them, and the last puts each where its rank in the list says.  (With a third digit,
+// two more passes over all rows: 4,000,000 rows, one of three million entries 348 us, 233 now, 240 with a 32-bit radix sort;
+// 100,000,000 6,562, 2,231 and 3,388.)
+// Workgroups (order_blocks): each reads all others' counts, so 128 of at least 2,048 rows, or 1,024 up to 32,768 rows
+// (64 workgroups: 232,965 rows 85 us longer; 100,000 rows in pieces of 1,024: 83 us, of 2,048: 72); they leave half the chip idle,
+// which outweighs that from some six million rows on (4,000,000 rows, two digits: 242 us, 240 with 256; 7,000,000 349 and
+// 293; 20,000,000 867 and 585), and 512 from some sixty (40,000,000 1,078 with 256, 1,065 with 512; one digit 546 and 579;
+// 100,000,000 2,441 and 2,193).
 constexpr int kOrderBits = 10, kOrderBins = 1 << kOrderBits;
 static_assert(kOrderBins == kOrderThreads, "one bin per thread");
-constexpr int kOrderBlocks = 128;
+constexpr uint32_t kTopDegree = (1u << (2 * kOrderBits)) - 1u;
+constexpr int kTopRows = 2048;
+static_assert((int64_t)kTopRows * kTopDegree <= 0x7fffffffll && (int64_t)(kTopRows + 1) * kTopDegree > 0x7fffffffll, "rows of a plan");
+constexpr int kOrderBlocks = 512;        // at most
+static int64_t order_blocks(int64_t N) { return N < 6000000 ? 128 : N < 60000000 ? 256 : kOrderBlocks; }
 struct OrderArgs {
     int64_t N, per_block;                // per_block: multiple of kOrderThreads
-    int passes;                          // digits that a row of nnz entries has
+    int passes;                          // digits that a row of nnz entries has, one or two
     const int32_t* deg;
-    uint2* pairs[2];                     // (degree, id) between the passes
+    uint2* pairs;                        // (degree, id) between the passes
     int32_t* order;
     uint32_t* counts;                    // [blocks][kOrderBins]
     RowStats* stats;                     // [blocks]
+    uint2* top;                          // [kTopRows] (degree, id) of rows of kTopDegree entries and more, in any order
 };
 
-__device__ __forceinline__ uint32_t order_digit(uint32_t d, int shift) { return (kOrderBins - 1) - ((d >> shift) & (kOrderBins - 1)); }
+__device__ __forceinline__ uint32_t order_digit(uint32_t d, int shift)
+{
+    return (kOrderBins - 1) - ((min(d, kTopDegree) >> shift) & (kOrderBins - 1));
+}
 
 __global__ __launch_bounds__(kOrderThreads) void degree_kernel(
     OrderArgs a, int64_t nnz, const int64_t* __restrict__ row_ptr, int32_t* __restrict__ deg, float* __restrict__ dinv,
@@ -253,6 +270,7 @@ __global__ __launch_bounds__(kOrderThreads) void degree_kernel(
         deg[v] = d;
         dinv[v] = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
         add_row(st, d, th);
+        st.top += (uint32_t)d >= kTopDegree ? 1u : 0u;
         atomicAdd(&hist[order_digit((uint32_t)d, 0)], 1u);
     }
     st.bad = bad ? 1u : 0u;
@@ -276,7 +294,7 @@ __device__ __forceinline__ uint32_t largest_degree(const RowStats* stats, int bl
     return top;
 }
 
-// digits of the second and later passes
+// digits of the second pass
 __global__ __launch_bounds__(kOrderThreads) void order_count_kernel(OrderArgs a, int pass)
 {
     __shared__ uint32_t hist[kOrderBins];
@@ -286,7 +304,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_count_kernel(OrderArgs a,
     hist[tid] = 0u;
     __syncthreads();
     const int64_t begin = (int64_t)blockIdx.x * a.per_block, end = min(begin + a.per_block, a.N);
-    const uint2* from = a.pairs[(pass & 1) ^ 1];
+    const uint2* from = a.pairs;
 #pragma unroll 4
     for (int64_t i = begin + tid; i < end; i += kOrderThreads) atomicAdd(&hist[order_digit(from[i].x, shift)], 1u);
     __syncthreads();
@@ -297,6 +315,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_move_kernel(OrderArgs a, 
 {
     __shared__ uint32_t counters[kOrderWaves][kOrderBins];
     __shared__ uint32_t sc[kOrderWaves];
+    __shared__ uint32_t top_at, top_rows;        // where this workgroup's rows go in the list a.top, and how many it holds
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, shift = pass * kOrderBits;
     const int blocks = gridDim.x;
     const uint32_t largest = largest_degree(a.stats, blocks, sc);
@@ -314,9 +333,18 @@ __global__ __launch_bounds__(kOrderThreads) void order_move_kernel(OrderArgs a, 
         }
     }
     if (pass > 0 && (largest >> shift) == 0) return;
-    // (a row_ptr that is refused may claim more entries in a row than there are: the order is a permutation all the same)
+    // (a row_ptr that is refused may claim more entries in a row than there are: the order is a permutation all the same,
+    // since a row is placed by its rank only where all of them are in the list)
     const bool last = pass + 1 == a.passes || (largest >> (shift + kOrderBits)) == 0;
     for (int i = tid; i < kOrderWaves * kOrderBins; i += kOrderThreads) (&counters[0][0])[i] = 0u;
+    if (largest >= kTopDegree) {                             // (uniform)
+        if (tid == 0) top_at = top_rows = 0u;
+        __syncthreads();                                     // (more barriers lie between the counts and their use)
+        if (tid < blocks && a.stats[tid].top) {
+            atomicAdd(&top_rows, a.stats[tid].top);
+            if (tid < (int)blockIdx.x) atomicAdd(&top_at, a.stats[tid].top);
+        }
+    }
     // rows of bin tid: in the workgroups before this one, and in all
     uint32_t before = 0, all = 0;
 #pragma unroll 16
@@ -329,8 +357,8 @@ __global__ __launch_bounds__(kOrderThreads) void order_move_kernel(OrderArgs a, 
 
     const int64_t per_wave = a.per_block / kOrderWaves;      // multiple of 64
     const int64_t begin = (int64_t)blockIdx.x * a.per_block + wave * per_wave, end = min(begin + per_wave, a.N);
-    const uint2* from = a.pairs[(pass & 1) ^ 1];
-    uint2* to = a.pairs[pass & 1];
+    const uint2* from = a.pairs;
+    uint2* to = a.pairs;                                     // (only a pass that is not the last writes them)
     auto entry = [&](int64_t i) { return pass == 0 ? make_uint2((uint32_t)a.deg[i], (uint32_t)i) : from[i]; };
 #pragma unroll 4
     for (int64_t i = begin + lane; i < end; i += 64) atomicAdd(&counters[wave][order_digit(entry(i).x, shift)], 1u);
@@ -342,6 +370,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_move_kernel(OrderArgs a, 
         at += c;
     }
     __syncthreads();
+    const bool ranked = last && pass > 0 && largest >= kTopDegree && top_rows <= (uint32_t)kTopRows;
     constexpr int AHEAD = 4;                                 // rows in flight per lane
     for (int64_t i0 = begin; i0 < end; i0 += 64 * AHEAD) {
         uint2 e[AHEAD];
@@ -355,9 +384,22 @@ __global__ __launch_bounds__(kOrderThreads) void order_move_kernel(OrderArgs a, 
             if (i0 + 64 * t >= end) break;                   // (uniform)
             const bool have = i0 + 64 * t + lane < end;
             const uint32_t q = take_position<kOrderBits>(counters[wave], order_digit(e[t].x, shift), have);
+            const bool longest = have && e[t].x >= kTopDegree;
             if (have) {
-                if (last) a.order[q] = (int32_t)e[t].y;
-                else to[q] = e[t];
+                if (!last) to[q] = e[t];
+                else if (!(longest && ranked)) a.order[q] = (int32_t)e[t].y;
+            }
+            if (longest && !last) {
+                const uint32_t at = atomicAdd(&top_at, 1u);
+                if (at < (uint32_t)kTopRows) a.top[at] = e[t];
+            }
+            if (longest && ranked) {                         // by degree, then id
+                uint32_t rank = 0;
+                for (uint32_t i = 0; i < top_rows; ++i) {
+                    const uint2 o = a.top[i];
+                    rank += o.x > e[t].x || (o.x == e[t].x && o.y < e[t].y) ? 1u : 0u;
+                }
+                a.order[rank] = (int32_t)e[t].y;
             }
         }
     }
@@ -418,7 +460,7 @@ __global__ __launch_bounds__(kThreads) void split_rows_kernel(
 struct PlanLayout {
     bool split;
     int64_t o_deg, o_dinv, o_order, o_part, keep_bytes;            // what the plan keeps
-    int64_t s_rb, s_pairs, s_counts, s_stats, scratch_bytes;       // what only its construction needs
+    int64_t s_rb, s_pairs, s_counts, s_stats, s_top, scratch_bytes;   // what only its construction needs
     bool small;
     int passes, blocks;                                            // of the order sort
     int64_t per_block;
@@ -439,17 +481,17 @@ int plan_layout(int64_t N, int64_t nnz, unsigned flags, PlanLayout& L)
     L.keep_bytes = L.o_part + (L.split ? align_up(4 * N * (kMaxParts + 1), 256) : 0);
     // scratch: readback block, and for larger graphs the pairs, counts and sums of the order sort
     L.small = N <= kSmallRows;
-    const int64_t share = (n1 + kOrderBlocks - 1) / kOrderBlocks;
+    const int64_t share = (n1 + order_blocks(N) - 1) / order_blocks(N);
     L.per_block = align_up(N > 32768 && share < 2048 ? 2048 : share, kOrderThreads);
     L.blocks = (int)((N + L.per_block - 1) / L.per_block);
-    L.passes = 1;
-    while (L.passes * kOrderBits < 31 && nnz >> (L.passes * kOrderBits)) ++L.passes;       // digits that a degree can have
+    L.passes = nnz >> kOrderBits ? 2 : 1;                          // digits that a degree can have
     L.s_rb = 0;
     L.s_pairs = 256;
     const int64_t pairs = L.small ? 0 : align_up(8 * n1, 256);
-    L.s_counts = L.s_pairs + pairs * (L.passes > 2 ? 2 : 1);
+    L.s_counts = L.s_pairs + pairs;
     L.s_stats = L.s_counts + (L.small ? 0 : 4ll * L.blocks * kOrderBins);
-    L.scratch_bytes = L.s_stats + (L.small ? 0 : align_up((int64_t)sizeof(RowStats) * L.blocks, 256)) + 256;
+    L.s_top = L.s_stats + (L.small ? 0 : align_up((int64_t)sizeof(RowStats) * L.blocks, 256));
+    L.scratch_bytes = L.s_top + (L.small ? 0 : (int64_t)sizeof(uint2) * kTopRows) + 256;
     return RETEXO_OK;
 }
 
@@ -476,8 +518,8 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
         a.per_block = L.per_block;
         a.passes = L.passes;
         a.deg = p->deg;
-        a.pairs[0] = (uint2*)(sc + L.s_pairs);
-        a.pairs[1] = (uint2*)(sc + L.s_pairs + (L.passes > 2 ? align_up(8 * N, 256) : 0));
+        a.pairs = (uint2*)(sc + L.s_pairs);
+        a.top = (uint2*)(sc + L.s_top);
         a.order = p->order;
         a.counts = (uint32_t*)(sc + L.s_counts);
         a.stats = (RowStats*)(sc + L.s_stats);

@@ -1,5 +1,6 @@
-"""The plan's row schedule where its sort can go wrong: either side of the sizes that take one workgroup, partial pieces
-of a wave and of a workgroup, and degrees of one, two, three and four digits."""
+"""The plan's row schedule where its sort can go wrong: either side of the sizes that take one workgroup or more of them,
+partial pieces of a wave and of a workgroup, degrees of one to four digits and rows longer than two digits of ten bits
+(2^20 - 1 entries), which are placed by rank; and that a plan of very many rows takes a few passes over them."""
 import numpy as np
 import pytest
 import torch
@@ -26,7 +27,7 @@ def degrees(n, kind, rng):
 
 @pytest.mark.parametrize("kind", ["ties", "empty", "bytes", "long"])
 @pytest.mark.parametrize("n", [1, 63, 65, 1024, 1025, 4095, 4096, 4097, 18433, 32769, 270001])
-def test_order_counts_and_normalisers(n, kind):
+def test_order_and_normalisers(n, kind):
     deg = degrees(n, kind, np.random.default_rng(n)).astype(np.int64)
     rp = np.zeros(n + 1, np.int64)
     np.cumsum(deg, out=rp[1:])
@@ -55,3 +56,70 @@ def test_refused_row_offsets(n):
     st, _ = B.retexo_plan_create_in(n, n, g.row_ptr.data_ptr(), g.col_idx.data_ptr(), B.F_SPLIT_ROWS, ws.data_ptr(),
                                     ws.numel(), Hn._stream_ptr())
     assert st == B.E_CSR
+
+
+def plan_of(deg, workspace=None):
+    """A plan whose rows have these lengths (device, int64)."""
+    n, rp = deg.numel(), torch.zeros(deg.numel() + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(deg, 0, out=rp[1:])
+    nnz = int(rp[-1])
+    col = torch.zeros(max(nnz, 1), dtype=torch.int32, device="cuda")
+    return Hn.make_plan(Hn.DeviceGraph(n_nodes=n, nnz=nnz, row_ptr=rp, col_idx=col), workspace=workspace)
+
+
+@pytest.mark.parametrize("n,long", [(4097, 1), (4097, 40), (20000, 300), (300001, 700), (5_999_999, 3), (6_000_001, 60), (60_000_001, 5)])
+def test_longest_rows_and_many_rows(n, long):
+    g = torch.Generator(device="cuda").manual_seed(n + long)
+    deg = torch.randint(0, 3, (n,), generator=g, device="cuda")
+    top = (1 << 20) - 1
+    values = torch.tensor([top - 1, top, top + 1, top, top + 2, 1 << 21], device="cuda")
+    deg[torch.randperm(n, generator=g, device="cuda")[:long]] = values[torch.randint(0, 6, (long,), generator=g, device="cuda")]
+    want = torch.sort(deg, descending=True, stable=True).indices.to(torch.int32)
+    plan = plan_of(deg)
+    try:
+        order = torch.empty(n, dtype=torch.int32, device="cuda")
+        B.check(B.retexo_plan_export(plan.plan, 0, 0, order.data_ptr(), Hn._stream_ptr()), "retexo_plan_export")
+        assert torch.equal(order, want)
+        assert B.retexo_plan_max_degree(plan.plan) == int(deg.max())
+    finally:
+        plan.destroy()
+
+
+def test_no_rows():
+    ws = Hn.ws_tensor(B.retexo_plan_workspace_bytes(0, 0, B.F_SPLIT_ROWS))
+    rp = torch.zeros(1, dtype=torch.int64, device="cuda")
+    st, plan = B.retexo_plan_create_in(0, 0, rp.data_ptr(), 0, B.F_SPLIT_ROWS, ws.data_ptr(), ws.numel(), Hn._stream_ptr())
+    assert st == B.OK and B.retexo_plan_num_nodes(plan) == 0 and B.retexo_plan_max_degree(plan) == 0
+    B.retexo_plan_destroy(plan)
+
+
+def test_many_rows_take_few_passes():
+    """40 million rows, one of three million entries: as long as 9 copies of the row offsets on an MI355X; with 128 workgroups
+    and a pass for every digit of the longest row as long as 23.  The line lies between."""
+    n = 40_000_000
+    deg = torch.ones(n, dtype=torch.int64, device="cuda")
+    deg[n // 3] = 3_000_000
+    ws = Hn.ws_tensor(B.retexo_plan_workspace_bytes(n, n + 3_000_000, 0))
+    plan_of(deg, ws).destroy()
+    rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    torch.cumsum(deg, 0, out=rp[1:])
+    nnz = int(rp[-1])
+    graph = Hn.DeviceGraph(n_nodes=n, nnz=nnz, row_ptr=rp, col_idx=torch.zeros(nnz, dtype=torch.int32, device="cuda"))
+    other = torch.empty_like(rp)
+
+    def best(run):
+        t = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            run()
+            b.record()
+            b.synchronize()
+            t = min(t, a.elapsed_time(b))
+        return t
+
+    def plan():
+        Hn.make_plan(graph, workspace=ws)
+        graph.destroy()
+    copy, build = best(lambda: other.copy_(rp)), best(plan)
+    assert build <= 14 * copy, (build, copy)
