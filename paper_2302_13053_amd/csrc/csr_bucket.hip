@@ -766,14 +766,21 @@ __device__ __forceinline__ uint32_t sort_keys(SortShared& sh, Load load, uint32_
 
 // A bucket that does not fit, i.e. one bin whose rows alone hold more.
 //
-// Dense ones (up to 512 possible keys per entry) are marked in a map of 2^19 bits at a time, which drops the repeats and
-// puts the rest in order by itself; every stretch of the map reads all entries again (from L2).
-// The others are worked through in key ranges [lo, hi], lowest first: a range that fits is gathered and sorted; one
+// Dense ones are marked in a map of 2^19 bits at a time, which drops the repeats and puts the rest in order by itself;
+// every stretch of the map reads all entries again (from L2).  The others are worked through in key ranges [lo, hi], lowest first: a range that fits is gathered and sorted; one
 // that does not is an aligned block of 2^bits keys, which is counted in 64 pieces by its next key bits; neighbouring
 // pieces are put together into ranges that fit, and a piece that still does not fit is split again (or is a single
 // repeated key).  Each level removes 6 key bits, so the stack stays below kStack.
 // Out of line: its registers and the sort's copy in it are then no concern of the buckets that fit.
 // Reddit-shaped graph, 667 such buckets of eight rows: the sort kernel 1,024 us with key ranges alone, 820 with the map.
+//
+// Key ranges read all entries for every range too, some E / 8,000 of them beside their sorts, so the line is a number of
+// stretches in proportion to E: up to one per kStretchEntries.  Whole constructions in us, map and key ranges: 4 stretches of
+// 12,000 entries (200 such buckets) 282 and 285, of 40,000 458 and 643; 16 of 17,000 508 and 330, of 40,000 686 and 635, of
+// 65,000 (100) 676 and 819; 64 of 66,000 (100) 1,724 and 854, of 130,000 (50) 2,151 and 1,939, of 260,000 (20) 2,423 and 4,854;
+// 256 of 270,000 (20) 11,263 and 5,003, of a million (two) 22,400 and 58,200; 1,024 of a million (two) 102,000 and 75,200,
+// of four million (one) 370,000 and 727,000; 4,096 of 4.3 million (one) 1,610,000 and 914,000.
+constexpr uint32_t kStretchEntries = kBucketMax / 4;
 __device__ __noinline__ uint32_t sort_oversized(SortShared& sh, BucketHeader* hdr, const uint32_t* __restrict__ in, uint32_t E,
                                                 int nrows, int cbits, uint32_t* __restrict__ out)
 {
@@ -781,10 +788,10 @@ __device__ __noinline__ uint32_t sort_oversized(SortShared& sh, BucketHeader* hd
     uint32_t out_cursor = 0;
     // the bits that the bucket's keys really use (its rows, then the columns)
     const uint32_t kb = (uint32_t)cbits + (nrows > 1 ? 32u - (uint32_t)__clz((uint32_t)(nrows - 1)) : 0u);
-    if (cbits >= 5 && (uint64_t)E << 9 >= 1ull << kb) {
+    const uint32_t stretches = kb > (uint32_t)kMapBits ? 1u << (kb - kMapBits) : 1u;
+    if (cbits >= 5 && E / kStretchEntries >= stretches) {
         constexpr uint32_t WORDS = (1u << kMapBits) / 32, PER_WAVE = WORDS / kSortWaves;
         uint32_t* map = sh.keys;                             // runs on into bins and rowmeta
-        const uint32_t stretches = kb > (uint32_t)kMapBits ? 1u << (kb - kMapBits) : 1u;
         constexpr int AHEAD = 8;
         for (uint32_t st = 0; st < stretches; ++st) {
             for (uint32_t i = tid; i < WORDS; i += kSortThreads) map[i] = 0u;
