@@ -1827,7 +1827,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
         const GatRoute route = gat_route(c);
         const bool off32 = route.off32, flash = route.flash, in_rows = route.in_rows;
         const int g = a.Dh / 4;
-        const int waves = softmax_waves(p, c.F);
+        const int waves = softmax_waves(p, c.F, c.save && !flash);
         if (c.el_ready && !(in_rows && !c.save && a.nslab == 1)) return RETEXO_E_FLAGS;   // the round asked gat_fold_plan
         a.el_stride = in_rows ? c.ldz : hp;
         if (in_rows) el = const_cast<float*>(c.Z) + c.F;

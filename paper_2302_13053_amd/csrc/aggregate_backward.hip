@@ -957,7 +957,7 @@ int launch_aggregate_backward(const AggBackwardCall& c, hipStream_t stream)
     a.row_count = 0;
     a.n_rows = N;
     a.heavy_rows = long_rows(p, F, false, true);
-    a.waves = softmax_waves(p, F);
+    a.waves = softmax_waves(p, F, false);
     a.F = F;
     a.heads = c.heads;
     a.Dh = (int)(F / c.heads);

@@ -94,15 +94,23 @@ static inline int64_t long_rows(const retexo_plan* p, int64_t F, bool own_launch
 }
 
 // Waves per workgroup of the edge softmax kernels whose one launch covers both classes of rows: eight, which share a long
-// row, or four where the short rows take far longer than the longest row shared by four (0.07 us per entry, beside the
-// short ones; 2^30 floats gathered take 0.7 ms) or every row is long.  Four leave fewer registers of a compute unit unused:
-// 20 and 28 waves of the backward and the save mode kernel, 16 and 24 in workgroups of eight.  Forward and backward over
-// 1,000,000 nodes of 20 entries, 64 columns: 3.76 ms with four, 4.27 with eight (4.03 in two launches); 60,000 of 50, 256
-// columns, 980 and 920 us (1,360).  Known slower than in two launches: 50,000 nodes of 300 entries, whose 538 long
-// rows fill the chip by themselves, with 188 to 256 columns: 2 to 5 %.
-static inline int softmax_waves(const retexo_plan* p, int64_t F)
+// row, or four, which leave fewer registers of a compute unit unused, where all rows take longer than the longest one shared by
+// four, or where every row is long.  The chip walks 750 entries while four waves walk one of their row; 530 in save mode
+// with scores from the table (`table_save`: 16 waves on a compute unit, 8 in workgroups of eight), whose rows of more than 256
+// columns are walked faster in workgroups of eight always.
+// Forward, save mode and backward after it in us, four waves and eight, by entries per entry of the longest row: 60,000 nodes
+// of 50, 275, 100 columns 377 and 217, 404 and 368, 535 and 336, 256 columns 454 and 335, 507 and 364, 656 and 445; 704, 100
+// columns 201 and 209, 280 and 364, 303 and 316, 256 columns 379 and 370, 408 and 387, 512 and 477; 1,080, 100 columns 201 and
+// 209, 278 and 364, 303 and 316, 256 columns 366 and 371, 393 and 392, 484 and 475, 376 columns 674 and 706, 1,213 and 1,028,
+// 896 and 927; 1,000,000 of 20, 570, 100 columns 2,300 and 2,377, 3,442 and 4,479, 3,080 and 3,180, 256 columns 3,418 and 3,007,
+// 3,930 and 3,558, 4,472 and 4,476; 112, 188 columns 8,967 and 5,071, 9,378 and 5,256, 10,708 and 6,558 (two launches: 6,496,
+// 8,004, 8,124).  Known slower than in two launches: the forward of 188 columns over 50,000 nodes of 300 entries, 1,140 and
+// 1,168, and over 20,000 of 200, 195 and 199.
+static inline int softmax_waves(const retexo_plan* p, int64_t F, bool table_save)
 {
-    return p->nnz * F >= (1ll << 30) || p->nnz >= kLongMean * p->N ? 4 : 8;
+    if (p->nnz >= kLongMean * p->N) return 4;
+    if (table_save && F > 256) return 8;
+    return p->nnz >= (table_save ? 530 : 750) * (int64_t)p->max_degree ? 4 : 8;
 }
 
 // Zero `bytes` (a multiple of 4) at `p` with a small kernel.  The stream-ordered entry points use this
