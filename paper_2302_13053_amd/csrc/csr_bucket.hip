@@ -590,9 +590,14 @@ constexpr int kBinWords = kSortBins / 2 + 1;             // two 16-bit counters 
 constexpr int kMapBits = 19;             // bits of the map that a dense oversized bucket is marked in at a time
 typedef uint16_t __attribute__((may_alias)) half_t;
 struct SortShared {
-    uint32_t keys[kBucketMax + 4];       // (the rank loop looks at four keys at a time)
-    uint32_t bins[kBinWords];
-    uint32_t rowmeta[kRowSpan];          // entries of a row in the keys being sorted, then: its first bin | column shift << 16
+    union {
+        struct {
+            uint32_t keys[kBucketMax + 4];   // (the rank loop looks at four keys at a time)
+            uint32_t bins[kBinWords];
+            uint32_t rowmeta[kRowSpan];      // entries of a row in the keys being sorted, then: its first bin | column shift << 16
+        };
+        uint32_t map[(1 << kMapBits) / 32];
+    };
     uint32_t rowcnt[kRowSpan];           // entries kept per row so far
     uint32_t stk_lo[kStack], stk_hi[kStack], stk_bits[kStack], stk_cnt[kStack];
     uint32_t sc[2 * kSortWaves + 1];
@@ -600,7 +605,6 @@ struct SortShared {
     uint32_t n, sp;
 };
 static_assert(sizeof(SortShared) <= 81920, "two workgroups per CU");
-static_assert(kBucketMax + 4 + kBinWords + kRowSpan >= (1 << kMapBits) / 32, "keys, bins and rowmeta together hold the map");
 static_assert(kRowSpan <= kSortThreads, "one row per thread");
 
 // Sort the n <= kBucketMax keys load(0 .. n), drop repeats, append the columns to out[out_cursor ...) and add
@@ -791,7 +795,7 @@ __device__ __noinline__ uint32_t sort_oversized(SortShared& sh, BucketHeader* hd
     const uint32_t stretches = kb > (uint32_t)kMapBits ? 1u << (kb - kMapBits) : 1u;
     if (cbits >= 5 && E / kStretchEntries >= stretches) {
         constexpr uint32_t WORDS = (1u << kMapBits) / 32, PER_WAVE = WORDS / kSortWaves;
-        uint32_t* map = sh.keys;                             // runs on into bins and rowmeta
+        uint32_t* map = sh.map;                              // (over the keys, bins and rowmeta)
         constexpr int AHEAD = 8;
         for (uint32_t st = 0; st < stretches; ++st) {
             for (uint32_t i = tid; i < WORDS; i += kSortThreads) map[i] = 0u;
