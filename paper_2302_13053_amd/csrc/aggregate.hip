@@ -1640,7 +1640,7 @@ int gather_vec(const AggCall& c)
 struct GatRoute {
     int vec;
     bool off32;     // every byte offset into Z fits 32 bits
-    bool flash;     // rows of ordinary length: source scores from the gathered rows themselves
+    bool flash;     // source scores from the gathered rows themselves
     bool in_rows;   // source scores kept in the unused columns of Z's own rows
 };
 GatRoute gat_route(const AggCall& c)

@@ -51,7 +51,7 @@ struct AggOptions {
     int64_t heavy_degree = kHeavyDegree;   // the default stands for "at most this": see long_rows
     int64_t max_vec = 4;        // cap on floats per lane per gather (experiments)
     int64_t gat_fast = 1;       // pipelined edge-softmax kernel (0: the plain one)
-    int64_t gat_flash = 1;      // ordinary rows: source scores from the gathered rows (0: from the table)
+    int64_t gat_flash = 1;      // where heads allow it: source scores from the gathered rows (0: from the table)
     int64_t gat_fold = 1;       // retexo_round: source scores as extra output columns of a linear transform (0: score kernel)
     int64_t gat_in_rows = 1;    // retexo_round: source scores in the unused columns of its own Z rows (0: table)
     int64_t wide_offsets = 0;   // 1: use the 64-bit row-offset code paths even when 32 bits would do (tests)

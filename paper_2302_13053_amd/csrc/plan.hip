@@ -133,8 +133,10 @@ __device__ __forceinline__ void gather_stats(const RowStats& st, RowStats* all)
 }
 
 // Small graphs, N <= kSmallRows: degrees, normalisers, order and counts in one launch by one workgroup, degrees and
-// ids in LDS (136 KB), 8 bits of the degree per pass and no more passes than the largest degree has.
-// 2,708 rows: 6 launches and 30 us of a plan's 85 before; 16,384 rows: see kSmallRows.
+// ids in LDS (40 KB), 8 bits of the degree per pass and no more passes than the largest degree has.  2,708 rows: 6 launches and
+// 30 us of a plan's 85 before.  The line: whole plans this way and by the kernels for larger graphs in us, 5,000 rows of up to
+// 200 entries 36.2 and 38.1, up to 1,000 44.5 and 38.0; 8,192 rows 41.5 and 40.6, 53.9 and 40.6; 16,384 55.8 and 40.8, 79.1 and
+// 41.0 (4,096 here: 34.0 and 41.1).
 constexpr int kSmallRows = 4096;
 constexpr int kSmallSteps = kSmallRows / kOrderThreads;
 struct SmallShared {
