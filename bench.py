@@ -298,7 +298,7 @@ def bench_workload(index, args):
         return None if nbytes is None else nbytes / agg_ms / 1e6 / HBM_PEAK_GBS
     roofline = {
         "bound": "hbm",
-        "kernel": ("agg_gat_flash_kernel (wave per row, eight waves per long row; scores formed from the gathered "
+        "kernel": ("agg_gat_flash_kernel (wave per row, a workgroup per long row; scores formed from the gathered "
                    "rows; other head widths: gat_scores_kernel + agg_gat_fast_kernel with a score table)"
                    if gat else
                    "aggregation call = agg_rowgroup_kernel + agg_grouped_kernel per source range (narrow slabs) "
