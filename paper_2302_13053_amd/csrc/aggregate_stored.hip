@@ -376,8 +376,11 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void stored_line
 // U entries per step: eight keep twice as many gathers in flight per wave, four more waves (85 registers instead of 117).
 // Eight where the slab of the table fits L2 or nearly does, so that latency and not misses bounds the call (bf16 mean, 8,847
 // nodes of 328 entries, 256 columns 97 us with eight, 108 with four; 100,000 of 100 438 and 472, gcn_sym 606 and 631), and
-// without weights also where it is the only slab (600,000 nodes of 120, 64 columns 2,240 and 2,572); four otherwise
-// (200 columns 8,279 and 8,101, gcn_sym 10,748 and 9,640; the Reddit-shaped mean of 602 columns 9,081 and 9,034).
+// without weights also where it is the only slab and a row of a range is walked longer than all others of the launch take:
+// eight walk it in half the steps.  That is a share of 64 entries per range the table is cut into, or more (64 columns, eight and
+// four: 600,000 nodes of 120, sixteen ranges, longest row 26,500 2,240 and 2,583, 9,640 2,059 and 1,941, all rows alike 2,163
+// and 2,008; 300,000 of 120, eight ranges, longest 31,600 798 and 984, 5,000 535 and 651, 3,100 531 and 494, 1,100 538 and 496).
+// Four otherwise (200 columns 8,279 and 8,101, gcn_sym 10,748 and 9,640; the Reddit-shaped mean of 602 columns 9,081 and 9,034).
 // ---------------------------------------------------------------------------
 template <int FMT, bool WEIGHTED, int U>
 __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(StoredArgs a)
@@ -1144,7 +1147,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
                 a.row_begin = n_long;
                 a.row_count = N - n_long;
                 const dim3 grid((unsigned)blocks), block(64 * kLightWaves);
-                const bool eight = parts <= 2 || (!a.wsrc && a.nslab == 1);      // entries per step, see the kernel
+                const bool eight = parts <= 2 || (!a.wsrc && a.nslab == 1 && p->max_degree >= 64 * parts * parts);   // see the kernel
                 if (a.wsrc && eight)  stored_rowgroup_kernel<FMT, true, 8><<<grid, block, 0, stream>>>(a);
                 else if (a.wsrc)      stored_rowgroup_kernel<FMT, true, 4><<<grid, block, 0, stream>>>(a);
                 else if (eight)       stored_rowgroup_kernel<FMT, false, 8><<<grid, block, 0, stream>>>(a);
