@@ -57,6 +57,8 @@ struct AggArgs {
     int64_t F;
     int nslab;
     int slab_major;
+    int slab_cols;         // columns of a slab, and workgroups that it takes (edge softmax, several rows per wave)
+    uint32_t slab_blocks;
     int scale;             // SCALE_*
     int heads;
     int Dh;
@@ -1505,6 +1507,273 @@ __global__ __launch_bounds__(64 * NW) void agg_gat_flash_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same for rows, or slabs of whole heads, of up to 64 columns: P = 8 or 16 lanes of four floats hold a row, and the R = 64 / P groups of a
+// wave take R consecutive rows of the schedule, or shares of one long row, in lock step (EntryWalk).  One entry per
+// instruction leaves 64 - P lanes idle there, and a row of twenty entries waits for memory five times, whatever its width;
+// here that is five times for R rows.  Scores, online softmax and save mode as above; a group whose row has ended weighs
+// its batches' entries with zero.  The shares of a long row are merged over the groups first, then over the waves, in order.
+// One row per wave and several, in us: 32 columns 2,449,029 nodes of 50 entries 5,025 and 2,388 (7.1 TB/s of whole lines), save mode 7,153 and 2,695;
+// 200,000 of 100 749 and 254, 1,083 and 281; 200,000 of 20 188 and 67; 64 columns 196 and 135, 1,000,000 of 8 641 and 390.
+// (32 lanes, for 65 to 128 columns: 200,000 of 20 267 and 279, 5,000 of 20 13.4 and 17.4, so those keep a row per wave.)
+// ---------------------------------------------------------------------------
+template <int G, int P, bool TRAIN, int NW>
+__global__ __launch_bounds__(64 * NW) void agg_gat_rows_kernel(
+    AggArgs a, const float* __restrict__ attn_src, const float* __restrict__ attn_dst, int er_stride)
+{
+    constexpr int U = 4, R = 64 / P;
+    constexpr float kLog2e = 1.4426950408889634f;
+    constexpr float kIn = TRAIN ? 1.0f : kLog2e;       // factor on the scores as they are formed
+    constexpr float kEx = TRAIN ? kLog2e : 1.0f;       // factor inside the exponentials
+    const int lane = threadIdx.x & 63, li = lane % P, g = lane / P;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // one slab of heads after the other, long rows first in each
+    const uint32_t slab = blockIdx.x / a.slab_blocks, block = blockIdx.x % a.slab_blocks;
+    const bool heavy = block < a.heavy_rows;          // uniform over the workgroup
+    const int64_t first = heavy ? (int64_t)block : a.heavy_rows + ((int64_t)(block - (uint32_t)a.heavy_rows) * NW + wave) * R;
+    if (first >= a.n_rows) return;
+    const int64_t slot = heavy ? first : first + g;
+    const bool have = slot < a.n_rows;
+    int v = 0;
+    uint32_t lo = 0, hi = 0;
+    if (have) {
+        v = a.order[slot];
+        lo = (uint32_t)a.row_ptr[v];
+        hi = (uint32_t)a.row_ptr[v + 1];
+    }
+    constexpr uint32_t kTile = EntryWalk<P>::kTile;
+    EntryWalk<P> walk;
+    const uint32_t rowbytes = (uint32_t)(a.ldz * 4);
+    const int batches = heavy ? walk.start(a.col_idx, lo + kTile * (wave * R + g), hi, kTile * NW * R, rowbytes)
+                              : walk.start(a.col_idx, lo, hi, kTile, rowbytes);
+
+    const int col = (int)slab * a.slab_cols + li * 4;
+    const bool act = li * 4 < a.slab_cols && col < a.F;
+    const table_t table = buffer_table(a.Z, a.table_bytes);
+    const uint32_t colbytes = act ? (uint32_t)col * 4 : kNoEntry;      // (columns past the row width fetch nothing)
+    const int h = min(col / a.Dh, a.heads - 1);
+    f32x4 as = {0.0f, 0.0f, 0.0f, 0.0f};
+    float erv = 0.0f;
+    if (act) {
+        as = *reinterpret_cast<const f32x4*>(attn_src + col);        // [heads, Dh] is F contiguous floats
+        as.x *= kIn; as.y *= kIn; as.z *= kIn; as.w *= kIn;
+        if (!attn_dst && have) erv = a.er[(int64_t)v * er_stride + h] * kIn;
+    }
+    if (attn_dst) {
+        f32x4 ad = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (act) ad = *reinterpret_cast<const f32x4*>(attn_dst + col);
+        const f32x4 zv = __builtin_bit_cast(f32x4, load_entry(table, have ? (uint32_t)v * rowbytes : kNoEntry, colbytes));
+        float d = (ad.x * kIn) * zv.x;
+        d = fmaf(ad.y * kIn, zv.y, d);
+        d = fmaf(ad.z * kIn, zv.z, d);
+        d = fmaf(ad.w * kIn, zv.w, d);
+        erv = group_sum<G>(d);
+    }
+
+    const bool empty = (heavy ? lo + kTile * (wave * R + g) : lo) >= hi;      // no entry: its maximum stays -infinity
+    float m = -INFINITY, s = 0.0f, sp = 0.0f, sn = 0.0f;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, accp = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 z[2][U];
+    uint32_t on[2][U];
+    auto issue = [&](int j, f32x4 (&zz)[U], uint32_t (&oo)[U]) {
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            oo[t] = walk.at(j, t);
+            zz[t] = __builtin_bit_cast(f32x4, load_entry(table, oo[t], colbytes));
+        }
+    };
+    auto consume = [&](const f32x4 (&zq)[U], const uint32_t (&oo)[U]) {
+        float x[U], sc[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            float d = as.x * zq[t].x;
+            d = fmaf(as.y, zq[t].y, d);
+            d = fmaf(as.z, zq[t].z, d);
+            d = fmaf(as.w, zq[t].w, d);
+            x[t] = group_sum<G>(d) + erv;
+            sc[t] = oo[t] != kNoEntry ? (x[t] > 0.0f ? x[t] : a.slope * x[t]) : -INFINITY;
+        }
+        float mn = m;
+#pragma unroll
+        for (int t = 0; t < U; ++t) mn = fmaxf(mn, sc[t]);
+        const float mr = empty ? 0.0f : mn;
+        const float scale = __builtin_amdgcn_exp2f((m - mr) * kEx);
+        float pw[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) pw[t] = __builtin_amdgcn_exp2f((sc[t] - mr) * kEx);
+        float ps = 0.0f;
+#pragma unroll
+        for (int t = 0; t < U; ++t) ps += pw[t];
+        s = s * scale + ps;
+        acc.x *= scale; acc.y *= scale; acc.z *= scale; acc.w *= scale;
+        if constexpr (TRAIN) {
+            float pps = 0.0f, pns = 0.0f;
+            accp.x *= scale; accp.y *= scale; accp.z *= scale; accp.w *= scale;
+#pragma unroll
+            for (int t = 0; t < U; ++t) {
+                const float pp = x[t] > 0.0f ? pw[t] : 0.0f, pn = x[t] > 0.0f ? 0.0f : pw[t];
+                pps += pp;
+                pns += pn;
+                accp.x = fmaf(pp, zq[t].x, accp.x);
+                accp.y = fmaf(pp, zq[t].y, accp.y);
+                accp.z = fmaf(pp, zq[t].z, accp.z);
+                accp.w = fmaf(pp, zq[t].w, accp.w);
+                acc.x = fmaf(pn, zq[t].x, acc.x);
+                acc.y = fmaf(pn, zq[t].y, acc.y);
+                acc.z = fmaf(pn, zq[t].z, acc.z);
+                acc.w = fmaf(pn, zq[t].w, acc.w);
+            }
+            sp = sp * scale + pps;
+            sn = sn * scale + pns;
+        } else {
+#pragma unroll
+            for (int t = 0; t < U; ++t) {
+                acc.x = fmaf(pw[t], zq[t].x, acc.x);
+                acc.y = fmaf(pw[t], zq[t].y, acc.y);
+                acc.z = fmaf(pw[t], zq[t].z, acc.z);
+                acc.w = fmaf(pw[t], zq[t].w, acc.w);
+            }
+        }
+        m = mn;
+    };
+    // the gathers of a batch are issued before the batch before it is added up
+    auto step = [&](int k, f32x4 (&zn)[U], uint32_t (&no)[U]) {       // batch k
+        if (k % P == 0 && k > 0) walk.take();
+        issue(k % P, zn, no);
+    };
+    if (batches > 0) step(0, z[0], on[0]);
+    for (int k = 0; k < batches; k += 2) {
+        if (k + 1 < batches) step(k + 1, z[1], on[1]);
+        consume(z[0], on[0]);
+        if (k + 1 >= batches) break;
+        if (k + 2 < batches) step(k + 2, z[0], on[0]);
+        consume(z[1], on[1]);
+    }
+
+    if (heavy) {
+        // merge the shares: groups of the wave, then the waves; one that saw no entry has m = -inf and weighs nothing
+        auto weight = [&](float mw, float mm) { return mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((mw - mm) * kEx); };
+#pragma unroll
+        for (int b = P; b < 64; b <<= 1) {
+            const float mo = __shfl_xor(m, b, 64), mm = fmaxf(m, mo), fa = weight(m, mm), fb = weight(mo, mm);
+            auto join = [&](float x) { return x * fa + __shfl_xor(x, b, 64) * fb; };
+            s = join(s);
+            acc = f32x4{join(acc.x), join(acc.y), join(acc.z), join(acc.w)};
+            if constexpr (TRAIN) {
+                sp = join(sp);
+                sn = join(sn);
+                accp = f32x4{join(accp.x), join(accp.y), join(accp.z), join(accp.w)};
+            }
+            m = mm;
+        }
+        __shared__ float red[NW][TRAIN ? 12 : 6][P];
+        if (g == 0) {
+            red[wave][0][li] = m;
+            red[wave][1][li] = s;
+            red[wave][2][li] = acc.x;
+            red[wave][3][li] = acc.y;
+            red[wave][4][li] = acc.z;
+            red[wave][5][li] = acc.w;
+            if constexpr (TRAIN) {
+                red[wave][6][li] = sp;
+                red[wave][7][li] = sn;
+                red[wave][8][li] = accp.x;
+                red[wave][9][li] = accp.y;
+                red[wave][10][li] = accp.z;
+                red[wave][11][li] = accp.w;
+            }
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        float mm = red[0][0][li];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) mm = fmaxf(mm, red[w][0][li]);
+        s = sp = sn = 0.0f;
+        acc = accp = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float f = weight(red[w][0][li], mm);
+            s = fmaf(red[w][1][li], f, s);
+            acc.x = fmaf(red[w][2][li], f, acc.x);
+            acc.y = fmaf(red[w][3][li], f, acc.y);
+            acc.z = fmaf(red[w][4][li], f, acc.z);
+            acc.w = fmaf(red[w][5][li], f, acc.w);
+            if constexpr (TRAIN) {
+                sp = fmaf(red[w][6][li], f, sp);
+                sn = fmaf(red[w][7][li], f, sn);
+                accp.x = fmaf(red[w][8][li], f, accp.x);
+                accp.y = fmaf(red[w][9][li], f, accp.y);
+                accp.z = fmaf(red[w][10][li], f, accp.z);
+                accp.w = fmaf(red[w][11][li], f, accp.w);
+            }
+        }
+        m = mm;
+    }
+
+    if (!have || (heavy && g != 0)) return;
+    if constexpr (TRAIN) {
+        // statistics: one lane per head; the padded heads carry no columns and look like a uniform softmax
+        if (act && (li % G) == 0) {
+            const bool any = s > 0.0f;
+            const float rs = any ? 1.0f / s : 0.0f;
+            a.save_stats[(int64_t)v * er_stride + h] = f32x4{any ? m : 0.0f, rs, sp * rs, sn * rs};
+        }
+        if (li == 0 && slab == 0) {
+            const bool any = hi > lo;
+            const f32x4 t = {0.0f, any ? 1.0f / (float)(hi - lo) : 0.0f, 0.0f, any ? 1.0f : 0.0f};
+            for (int k = a.heads; k < er_stride; ++k) a.save_stats[(int64_t)v * er_stride + k] = t;
+        }
+    }
+    if (!act) return;
+    float* orow = a.out + (int64_t)v * a.ldo;
+    float r[4];
+    if constexpr (TRAIN) {
+        float rp[4], rn[4];
+        const float ap[4] = {accp.x, accp.y, accp.z, accp.w}, an[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            r[k] = s > 0.0f ? (an[k] + ap[k]) / s : 0.0f;
+            rp[k] = s > 0.0f ? ap[k] / s : 0.0f;
+            rn[k] = s > 0.0f ? an[k] / s : 0.0f;
+        }
+        store_row<4>(a.save_pos + (int64_t)v * a.ld_pos + col, rp, 4, true);
+        store_row<4>(a.save_neg + (int64_t)v * a.ld_pos + col, rn, 4, true);
+    } else {
+        r[0] = s > 0.0f ? acc.x / s : 0.0f;
+        r[1] = s > 0.0f ? acc.y / s : 0.0f;
+        r[2] = s > 0.0f ? acc.z / s : 0.0f;
+        r[3] = s > 0.0f ? acc.w / s : 0.0f;
+    }
+    store_row<4>(orow + a.ocol + col, r, 4, a.out_vec != 0, a.out_half != 0);
+    if (a.copy_self) {
+        float zs[4];
+        load_row<4>(a.Z + (int64_t)v * a.ldz + col, zs);
+        store_row<4>(orow + col, zs, 4, a.self_vec != 0);
+    }
+}
+
+template <int G, int P, bool TRAIN>
+void launch_gat_rows(const AggArgs& base, int64_t n_heavy, int64_t N, const float* attn_src, const float* attn_dst, int hp,
+                     int waves, hipStream_t stream)
+{
+    if constexpr (G <= P && G * kMaxHeads > P / 2) {
+        AggArgs a = base;
+        const int64_t rows = (int64_t)waves * (64 / P);
+        a.heavy_rows = n_heavy;
+        a.slab_blocks = (uint32_t)(n_heavy + (N - n_heavy + rows - 1) / rows);
+        const dim3 grid((unsigned)(a.slab_blocks * (unsigned)a.nslab)), block(64 * waves);
+        if (waves == 4) agg_gat_rows_kernel<G, P, TRAIN, 4><<<grid, block, 0, stream>>>(a, attn_src, attn_dst, hp);
+        else            agg_gat_rows_kernel<G, P, TRAIN, 8><<<grid, block, 0, stream>>>(a, attn_src, attn_dst, hp);
+    }
+}
+template <int G, bool TRAIN>
+void dispatch_gat_rows(int lanes, const AggArgs& a, int64_t n_heavy, int64_t N, const float* attn_src, const float* attn_dst,
+                       int hp, int waves, hipStream_t stream)
+{
+    if (lanes == 8) launch_gat_rows<G, 8, TRAIN>(a, n_heavy, N, attn_src, attn_dst, hp, waves, stream);
+    else            launch_gat_rows<G, 16, TRAIN>(a, n_heavy, N, attn_src, attn_dst, hp, waves, stream);
+}
+
 template <int VEC, int NC, int HP, bool HU>
 void launch_gat_pair(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t stream)
 {
@@ -1663,6 +1932,24 @@ GatRoute gat_route(const AggCall& c)
     r.in_rows = c.z_padding_free && !r.flash && r.vec == 4 && r.off32 && opt.gat_fast && opt.gat_in_rows &&
                 c.F % 4 == 0 && c.ldz - c.F >= hp && c.F % 32 != 0 && (c.F % 32) + hp <= 32;
     return r;
+}
+
+// Heads that a slab of agg_gat_rows_kernel holds; 0: the call takes one row per wave.
+// Up to 64 columns are one slab.  Wider rows of heads of up to 64 columns are walked a slab of 64 after the other where
+// the table is much larger than an L2 (24 MB): a fourth of the columns at a time leaves four times as many of the nodes that are
+// gathered most in each L2.  That has to outweigh reading the ids, and a row's own start, once per slab: from 48 entries per row
+// and 4 GB of gathers on (shorter calls gain from it too, 60,000 of 50 in save mode 475 and 360, but are left to one row per
+// wave: its time there is the unit that the table kernel's workgroups are held to).
+// One row per wave and slabs, in us: 2,449,029 nodes of 50 entries, 256 columns 20,400 and 18,700, save mode 22,050 and 20,900;
+// 200,000 of 100 2,626 and 2,113; 50,000 of 400 2,030 and 1,166; 65,000 of 100 743 and 639; 128 columns 2,449,029 of 50
+// 9,330 and 8,740, 200,000 of 100 1,199 and 1,079.  The other way: 100,000 of 40, 192 columns, save mode 365 and 406; 1,000,000 of
+// 8, 256 columns 1,483 and 1,651; known slower with slabs: 1,500,000 of 70, 128 columns 7,307 and 7,506.
+int gat_rows_heads(const AggCall& c, int Dh)
+{
+    const retexo_plan* p = c.plan;
+    if (c.F <= 64) return c.save || p->nnz >= kRowsFewest ? c.heads : 0;
+    if (Dh > 64 || p->nnz < 48 * p->N || p->N * c.F * 4 < (24ll << 20) || p->nnz * c.F * 4 < (4ll << 30)) return 0;
+    return 64 / Dh < c.heads ? 64 / Dh : c.heads;
 }
 
 // One wave per row of W (and one for b): copy the row and append its products with the heads of a_src.
@@ -1852,7 +2139,27 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
             a.save_neg = (float*)((char*)c.workspace + w.neg);
             a.ld_pos = w.ld_pos;
         }
-        if (flash) {
+        // several rows per wave: whole heads of up to 64 columns at a time
+        const int slab_heads = flash ? gat_rows_heads(c, a.Dh) : 0;
+        if (slab_heads) {
+            a.table_bytes = (uint32_t)(((N - 1) * c.ldz + c.F) * 4);
+            a.slab_cols = slab_heads * a.Dh;
+            a.nslab = (c.heads + slab_heads - 1) / slab_heads;
+            const float* ad = no_table ? c.attn_dst : nullptr;
+            const int lanes = row_lanes(a.slab_cols);
+            auto go = [&](auto gtag) {
+                constexpr int GG = decltype(gtag)::value;
+                if (c.save) dispatch_gat_rows<GG, true>(lanes, a, n_heavy, N, c.attn_src, nullptr, hp, waves, stream);
+                else        dispatch_gat_rows<GG, false>(lanes, a, n_heavy, N, c.attn_src, ad, hp, waves, stream);
+            };
+            switch (g) {
+                case 1:  go(std::integral_constant<int, 1>{}); break;
+                case 2:  go(std::integral_constant<int, 2>{}); break;
+                case 4:  go(std::integral_constant<int, 4>{}); break;
+                case 8:  go(std::integral_constant<int, 8>{}); break;
+                default: go(std::integral_constant<int, 16>{}); break;
+            }
+        } else if (flash) {
             AggArgs f = a;
             f.nslab = 1;
             const dim3 grid(both_classes(f, n_heavy, N, waves)), block(64 * waves);

@@ -93,6 +93,11 @@ static inline int64_t long_rows(const retexo_plan* p, int64_t F, bool own_launch
     return 0;
 }
 
+// Entries from which the plain edge softmax over rows of up to 64 columns walks several rows per wave; below, a call takes 7
+// to 9 us, in which a row per wave starts sooner (32 columns, one row per wave and several, in us: 1,000 nodes of 4 entries 7.3
+// and 8.0, 3,000 of 5 9.0 and 9.2, 2,000 of 10 9.9 and 9.6, 5,000 of 20 12.4 and 9.7).
+constexpr int64_t kRowsFewest = 16384;
+
 // Waves per workgroup of the edge softmax kernels whose one launch covers both classes of rows: eight, which share a long
 // row, or four, which leave fewer registers of a compute unit unused, where all rows take longer than the longest one shared by
 // four, or where every row is long.  The chip walks 750 entries while four waves walk one of their row; 530 in save mode

@@ -77,6 +77,79 @@ __device__ __forceinline__ u32x4 load_entry(table_t t, uint32_t row, uint32_t co
     return __builtin_amdgcn_raw_buffer_load_b128(t, __builtin_elementwise_add_sat(row, col), 0, 0);
 }
 
+// Rows narrower than a wave: P lanes of four floats each hold a row (P = 8 or 16), and the R = 64 / P groups of a
+// wave walk a list of entries each, in lock step: R rows of neighbouring length, or R shares of one long row.  A
+// gather instruction so carries R entries, where one entry per instruction leaves 64 - P lanes idle and the kernels wait
+// for as many round trips to memory as a row has batches.
+// Every lane fetches four consecutive ids at a time (a tile of 4 P entries per group, whole cache lines of col_idx, a tile
+// ahead of its use); entry t of the four in lane l of the group is entry 4 l + t of the tile.  A batch is the four entries
+// of one lane.  What does not exist is the offset kNoEntry and fetches nothing.
+// KEEP_ID: the ids themselves as well (for a second table).
+template <int P, bool KEEP_ID = false>
+struct EntryWalk {
+    static constexpr uint32_t kTile = 4 * P;
+    const int32_t* __restrict__ col;
+    uint32_t hi, ahead, step;            // end of the list; first entry of the tile in `nxt`; distance of a group's tiles
+    uint32_t rowbytes;
+    int li, gaddr;
+    uint32_t off[4], nxt[4];             // byte offsets of the current tile's entries; ids of the one after it
+    uint32_t id[KEEP_ID ? 4 : 1];
+
+    __device__ __forceinline__ void fetch()
+    {
+        typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+        const uint32_t at = ahead + 4 * li;          // (entry counts stay below 2^31)
+        if (at + 4 <= hi) {
+            const i32x4u t = *reinterpret_cast<const i32x4u*>(col + at);
+            nxt[0] = (uint32_t)t.x; nxt[1] = (uint32_t)t.y; nxt[2] = (uint32_t)t.z; nxt[3] = (uint32_t)t.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) nxt[k] = at + k < hi ? (uint32_t)col[at + k] : kNoEntry;
+        }
+    }
+    // The group's entries: tiles that start at first, first + step_, ... up to hi_.  Returns the number of batches of the
+    // wave's longest list (uniform).
+    __device__ __forceinline__ int start(const int32_t* col_idx, uint32_t first, uint32_t hi_, uint32_t step_, uint32_t rowbytes_)
+    {
+        const int lane = threadIdx.x & 63;
+        col = col_idx; hi = hi_; ahead = min(first, hi_); step = step_; rowbytes = rowbytes_;
+        li = lane % P; gaddr = (lane - li) * 4;
+        fetch();
+        int n = 0;
+        if (first < hi) {
+            const uint32_t tiles = (hi - first - 1) / step, rest = hi - (first + tiles * step);
+            n = (int)(tiles * P + (min(rest, kTile) + 3) / 4);
+        }
+#pragma unroll
+        for (int m = P; m < 64; m <<= 1) n = max(n, __shfl_xor(n, m, 64));
+        take();
+        return __builtin_amdgcn_readfirstlane(n);
+    }
+    // the tile that was fetched becomes the current one, the next is requested
+    __device__ __forceinline__ void take()
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            off[k] = nxt[k] == kNoEntry ? kNoEntry : nxt[k] * rowbytes;
+            if constexpr (KEEP_ID) id[k] = nxt[k];
+        }
+        ahead = hi - ahead > step ? ahead + step : hi;
+        fetch();
+    }
+    // byte offset of entry t of batch j of the current tile
+    __device__ __forceinline__ uint32_t at(int j, int t) const
+    {
+        return (uint32_t)__builtin_amdgcn_ds_bpermute(gaddr + 4 * j, (int)off[t]);
+    }
+    __device__ __forceinline__ uint32_t id_at(int j, int t) const
+    {
+        return (uint32_t)__builtin_amdgcn_ds_bpermute(gaddr + 4 * j, (int)id[t]);
+    }
+};
+
+// lanes that hold a row of F columns, four floats each, in the kernels whose waves walk several rows; 0: one row per wave
+inline int row_lanes(int64_t F) { return F <= 32 ? 8 : F <= 64 ? 16 : F <= 128 ? 32 : 64; }
+
 __device__ __forceinline__ float wave_max(float x)
 {
 #pragma unroll

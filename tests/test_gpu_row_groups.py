@@ -1,0 +1,89 @@
+"""Edge softmax over narrow rows, several rows of the schedule (or shares of a long row) per wave: forward, save mode and the
+backward after it against the fp64 oracle.  Rows that end with a wave, a group or a tile of the walk (32 and 64 entries), row
+counts that leave groups without a row, empty rows, long rows shared by a workgroup, rows padded or not."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2302_13053_amd import binding as B
+from paper_2302_13053_amd import harness as Hn
+from paper_2302_13053_amd import workloads as wl
+from parity import assert_close
+from test_gpu_softmax_rows import decided_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def graphs():
+    """few: below the line from which the plain forward takes the kernel; edges: rows of 31 to 33, 63 to 65 and 127 to 129
+    entries, and the row of their centres; skewed: most of 16,501 rows short, some empty, one of thousands of entries"""
+    src, dst, at = [], [], 600
+    for c, d in enumerate((31, 32, 33, 63, 64, 65, 127, 128, 129, 4, 5, 8, 9)):
+        for leaf in range(d):
+            src.append(c), dst.append(20 + (at + leaf) % 1000)
+        at += d
+    ring = np.arange(1021)
+    for k in range(1, 9):
+        src.extend(20 + ring[:1000]), dst.extend(20 + (ring[:1000] + 7 * k) % 1000)
+    specs = {"few": (1003, *wl.random_pairs(1003, 5000, 1, skew=1.0)),
+             "edges": (1030, np.array(src, np.int32), np.array(dst, np.int32)),
+             "skewed": (16501, *wl.random_pairs(16501, 60000, 2, skew=3.0))}
+    out = {}
+    for name, (n, s, d) in specs.items():
+        g = Hn.make_plan(Hn.csr_from_coo(Hn.dev(s), Hn.dev(d), n, False))
+        out[name] = (g, *oracle.csr_from_coo(s, d, n, False))
+    assert out["few"][1][-1] < 16384 <= out["edges"][1][-1]
+    assert (np.diff(out["skewed"][1]) == 0).any() and np.diff(out["skewed"][1]).max() > 2000
+    yield out
+    for g, _, _ in out.values():
+        g.destroy()
+
+
+@pytest.mark.parametrize("name", ["few", "edges", "skewed"])
+@pytest.mark.parametrize("heads,dh,pad", [(1, 4, 0), (8, 4, 0), (3, 8, 8), (1, 32, 0), (3, 16, 0), (8, 8, 4), (1, 64, 0),
+                                          (3, 32, 0), (8, 16, 0), (8, 32, 0)])
+def test_row_groups(graphs, name, heads, dh, pad):
+    g, rp, ci = graphs[name]
+    n, F = g.n_nodes, heads * dh
+    a = [wl.random_matrix(heads, dh, k) * np.float32(0.1) for k in (1, 2)]
+    Zh = decided_rows(rp, ci, heads, dh, a)[:, :F]
+    Zh = np.ascontiguousarray(np.pad(Zh, ((0, 0), (0, pad)), constant_values=np.nan))      # padding that must not be read
+    Gh = wl.random_matrix(n, F, F + 1)
+    Z, G, As, Ad = (Hn.dev(x) for x in (Zh, Gh, *a))
+    kw = dict(heads=heads, a_src=As, a_dst=Ad)
+    plain = Hn.aggregate(g, "gat_softmax", Z, F, **kw)
+    ws = Hn.ws_tensor(B.retexo_workspace_bytes(g.plan, F, B.MODES["gat_softmax"], heads, B.F_SAVE))
+    out = Hn.aggregate(g, "gat_softmax", Z, F, workspace=ws, save=True, **kw)
+    got = Hn.aggregate_backward(g, "gat_softmax", F, G, Z=Z, saved=ws, **kw)
+    okw = dict(heads=heads, a_src=a[0], a_dst=a[1])
+    fwd = oracle.aggregate("gat_softmax", rp, ci, Zh[:, :F], F, **okw)
+    want = oracle.aggregate_backward("gat_softmax", rp, ci, Zh[:, :F], F, Gh, **okw)
+    assert_close(plain.cpu().numpy()[:, :F], fwd, what="forward")
+    assert_close(out.cpu().numpy()[:, :F], fwd, what="save mode")
+    # rows of a few columns have no robust magnitude: one ratio over all rows
+    assert_close(got[0].cpu().numpy()[:, :F].reshape(1, -1), want[0].reshape(1, -1), what="backward")
+    if F >= 64:
+        assert_close(got[0].cpu().numpy()[:, :F], want[0], what="backward, row by row")
+    for grad, ref, what in zip(got[1:], want[1:], ("source", "destination")):
+        assert_close(grad.cpu().numpy().reshape(1, -1), ref.reshape(1, -1), what=what + " attention vector")
+
+
+@pytest.mark.parametrize("heads,dh", [(4, 64), (5, 32), (2, 64)])
+def test_slabs_of_heads(heads, dh):
+    """Rows of several slabs (of one head; of two heads with a last one of one): 50,001 nodes of 180
+    entries, one row of thousands."""
+    n, F = 50001, heads * dh
+    src, dst = wl.random_pairs(n, 4700000, 5, skew=1.2)
+    g = Hn.make_plan(Hn.csr_from_coo(Hn.dev(src), Hn.dev(dst), n, False))
+    rp, ci = oracle.csr_from_coo(src, dst, n, False)
+    assert rp[-1] >= 48 * n and n * F * 4 >= 24 << 20 and rp[-1] * F * 4 >= 4 << 30
+    a = [wl.random_matrix(heads, dh, k) * np.float32(0.1) for k in (1, 2)]
+    Zh = wl.random_matrix(n, F, 7)
+    kw = dict(heads=heads, a_src=Hn.dev(a[0]), a_dst=Hn.dev(a[1]), concat=True)
+    Z = Hn.dev(Zh)
+    ws = Hn.ws_tensor(B.retexo_workspace_bytes(g.plan, F, B.MODES["gat_softmax"], heads, B.F_SAVE))
+    want = oracle.aggregate("gat_softmax", rp, ci, Zh, F, heads=heads, a_src=a[0], a_dst=a[1], self_concat=True)
+    for what, save in (("forward", {}), ("save mode", dict(save=True, workspace=ws))):
+        assert_close(Hn.aggregate(g, "gat_softmax", Z, F, **kw, **save).cpu().numpy()[:, :2 * F], want, what=what)
+    g.destroy()
