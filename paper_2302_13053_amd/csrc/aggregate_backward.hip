@@ -29,6 +29,8 @@
 //    by edge: each lane accumulates weight * (its own columns' share of the
 //    product) and the lanes of a head are summed once per row.
 //    Nothing is accumulated with atomics; every sum has a fixed order.
+#include <type_traits>
+
 #include "common.hpp"
 #include "gather.hpp"
 
@@ -583,6 +585,134 @@ __global__ __launch_bounds__(64 * NW) void gat_bwd_src_kernel(BwdArgs a)
 }
 
 // ---------------------------------------------------------------------------
+// The "src" pass where heads are power-of-two groups of G lanes: P lanes of four floats hold a row, and the R = 64 / P groups
+// of a wave walk R rows of the schedule, or shares of one long row, in lock step (EntryWalk): a gather instruction carries
+// R entries, and R rows wait for memory together.  A lane reads its head's statistics of the neighbour itself (16 bytes, one
+// line for all heads) and forms the entry's weight from them, instead of one lane per entry for all lanes through LDS.
+// src_by_rows says where it is taken, and what it measures.
+// ---------------------------------------------------------------------------
+template <int G, int P, int NW>
+__global__ __launch_bounds__(64 * NW) void gat_bwd_src_rows_kernel(BwdArgs a, int hp, uint32_t g_bytes, uint32_t nbr_bytes)
+{
+    constexpr int U = 4, R = 64 / P;
+    const int lane = threadIdx.x & 63, li = lane % P, g = lane / P;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool heavy = blockIdx.x < a.heavy_rows;     // uniform over the workgroup
+    const int64_t first = heavy ? (int64_t)blockIdx.x : a.heavy_rows + (((int64_t)blockIdx.x - a.heavy_rows) * NW + wave) * R;
+    if (first >= a.n_rows) return;
+    const int64_t slot = heavy ? first : first + g;
+    const bool have = slot < a.n_rows;
+    int u = 0;
+    uint32_t lo = 0, hi = 0;
+    if (have) {
+        u = a.order[slot];
+        lo = (uint32_t)a.row_ptr[u];
+        hi = (uint32_t)a.row_ptr[u + 1];
+    }
+    constexpr uint32_t kTile = EntryWalk<P, true>::kTile;
+    EntryWalk<P, true> walk;
+    const uint32_t rowbytes = (uint32_t)(a.ldg * 4);
+    const int batches = heavy ? walk.start(a.col_idx, lo + kTile * (wave * R + g), hi, kTile * NW * R, rowbytes)
+                              : walk.start(a.col_idx, lo, hi, kTile, rowbytes);
+
+    const int col = li * 4;
+    const bool act = have && col < a.F;
+    const int h = min(col / a.Dh, a.heads - 1);
+    const table_t grads = buffer_table(a.G, g_bytes), stats = buffer_table(a.nbr, nbr_bytes);
+    const uint32_t colbytes = act ? (uint32_t)col * 4 : kNoEntry;      // (columns past the row width fetch nothing)
+    float zo[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float elu = 0.0f;
+    if (act) {
+        load_row<4>(a.Z + (int64_t)u * a.ldz + col, zo);
+        elu = a.el[(int64_t)u * hp + h];
+    }
+
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q = 0.0f, tc = 0.0f;
+    f32x4 gr[2][U], nb[2][U];
+    uint32_t on[2][U];
+    auto issue = [&](int k, f32x4 (&gg)[U], f32x4 (&nn)[U], uint32_t (&oo)[U]) {       // batch k
+        const int j = k % P;
+        if (j == 0 && k > 0) walk.take();
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            oo[t] = walk.at(j, t);
+            gg[t] = __builtin_bit_cast(f32x4, load_entry(grads, oo[t], colbytes));
+            // (an id that does not exist lies past the table's end however it is scaled)
+            const uint32_t id = walk.id_at(j, t);
+            nn[t] = __builtin_bit_cast(f32x4, load_entry(stats, oo[t] == kNoEntry ? kNoEntry : id * (uint32_t)(hp * 16), (uint32_t)h * 16));
+        }
+    };
+    auto consume = [&](const f32x4 (&gg)[U], const f32x4 (&nn)[U], const uint32_t (&oo)[U]) {
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            const float x = elu + nn[t].x;
+            const float sc = x > 0.0f ? x : a.slope * x;
+            const float al = oo[t] != kNoEntry ? expf(sc - nn[t].y) * nn[t].z : 0.0f;   // sc <= nn.y: row v's maximum covers this entry
+            const float w = x > 0.0f ? al : a.slope * al;
+            tc = fmaf(w, nn[t].w, tc);
+            float pd = 0.0f;
+            acc[0] = fmaf(al, gg[t].x, acc[0]); pd = fmaf(gg[t].x, zo[0], pd);
+            acc[1] = fmaf(al, gg[t].y, acc[1]); pd = fmaf(gg[t].y, zo[1], pd);
+            acc[2] = fmaf(al, gg[t].z, acc[2]); pd = fmaf(gg[t].z, zo[2], pd);
+            acc[3] = fmaf(al, gg[t].w, acc[3]); pd = fmaf(gg[t].w, zo[3], pd);
+            q = fmaf(w, pd, q);
+        }
+    };
+    if (batches > 0) issue(0, gr[0], nb[0], on[0]);
+    for (int k = 0; k < batches; k += 2) {
+        if (k + 1 < batches) issue(k + 1, gr[1], nb[1], on[1]);
+        consume(gr[0], nb[0], on[0]);
+        if (k + 1 >= batches) break;
+        if (k + 2 < batches) issue(k + 2, gr[0], nb[0], on[0]);
+        consume(gr[1], nb[1], on[1]);
+    }
+
+    float ds = group_sum<G>(q) - tc;
+    if (heavy) {
+        // the shares: groups of the wave, then the waves
+#pragma unroll
+        for (int b = P; b < 64; b <<= 1) {
+            ds += __shfl_xor(ds, b, 64);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], b, 64);
+        }
+        __shared__ float red[NW][5][P];
+        if (g == 0) {
+            red[wave][4][li] = ds;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) red[wave][k][li] = acc[k];
+        }
+        __syncthreads();
+        if (wave != 0 || g != 0) return;
+        ds = red[0][4][li];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) ds += red[w][4][li];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            acc[k] = red[0][k][li];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) acc[k] += red[w][k][li];
+        }
+    }
+    if (!have) return;
+    if (li == 0)
+        for (int k = a.heads; k < hp; ++k) a.dsrc[(int64_t)u * hp + k] = 0.0f;
+    if (!act) return;
+    if (li % G == 0) a.dsrc[(int64_t)u * hp + h] = ds;
+    const float dd = a.ddst[(int64_t)u * hp + h];
+    float as[4], ad[4], gs[4], r[4];
+    load_row<4>(a.a_src + col, as);
+    load_row<4>(a.a_dst + col, ad);
+    if (a.Gself) load_row<4>(a.Gself + (int64_t)u * a.ldg + col, gs);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        r[k] = acc[k] + as[k] * ds + ad[k] * dd;
+        if (a.Gself) r[k] += gs[k];
+    }
+    store_row<4>(a.dZ + (int64_t)u * a.lddz + col, r, 4, true);
+}
+
+// ---------------------------------------------------------------------------
 // What the "dst" pass produces, from what a forward pass in save mode left behind instead of a
 // second gather over Z:  A+- = <G_v, out+-_v> (out+, out-: the parts of the aggregate from entries
 // with a positive / non-positive score),  c_v = A+ + A-,  P+-: the saved shares of the softmax sum.
@@ -802,11 +932,57 @@ void launch_dst_flash(const BwdArgs& a, int hp, unsigned blocks, hipStream_t str
     gat_bwd_dst_flash_kernel<G><<<dim3(blocks), dim3(64 * kLightWaves), 0, stream>>>(a, hp);
 }
 
+// Where gat_bwd_src_rows_kernel is the faster one (whole backward in us, gat_bwd_src_kernel and it):
+//  up to 64 columns always: 2,449,029 nodes of 50 entries, 32 columns 8,782 and 5,545, 64 columns 9,661 and 7,488; 200,000 of
+//  20 405 and 231, 425 and 310; 5,000 of 20 64 and 54;
+//  up to 128, where rows are short (1,000,000 of 8 1,953 and 1,539, 2,449,029 of 50 13,499 and 12,943, but 200,000 of 100
+//  1,622 and 1,708) or there are more than four heads, whose statistics the other kernel's lanes read and weigh for every entry
+//  (200,000 of 100 1,808 and 1,688, 1,000,000 of 8 3,391 and 1,628);
+//  up to 256 with more than four heads (1,000,000 of 8 3,821 and 2,831, 2,449,029 of 50 28,837 and 25,432, 20,000 of 200 445
+//  and 442; with four or fewer equal within 3 %), but for small graphs (5,000 of 20 99 and 113).
+bool src_by_rows(int64_t F, int hp, int64_t N, int64_t nnz)
+{
+    if (F <= 64) return true;
+    if (F <= 128) return hp == 8 || nnz < 64 * N;
+    return hp == 8 && N >= 16384;
+}
+
+template <int G, int P>
+void launch_src_rows_as(const BwdArgs& a, int hp, int64_t N, hipStream_t stream)
+{
+    if constexpr (G <= P && G * kMaxHeads > P / 2) {
+        const int64_t rows = (int64_t)a.waves * (64 / P);
+        const dim3 grid((unsigned)(a.heavy_rows + (N - a.heavy_rows + rows - 1) / rows)), block(64 * a.waves);
+        const uint32_t g_bytes = (uint32_t)(((N - 1) * a.ldg + a.F) * 4), nbr_bytes = (uint32_t)(N * hp * 16);
+        if (a.waves == 4) gat_bwd_src_rows_kernel<G, P, 4><<<grid, block, 0, stream>>>(a, hp, g_bytes, nbr_bytes);
+        else              gat_bwd_src_rows_kernel<G, P, 8><<<grid, block, 0, stream>>>(a, hp, g_bytes, nbr_bytes);
+    }
+}
+void launch_src_rows(const BwdArgs& a, int hp, int G, int64_t N, hipStream_t stream)
+{
+    auto go = [&](auto tag) {
+        constexpr int GG = decltype(tag)::value;
+        if (row_lanes(a.F) == 8)       launch_src_rows_as<GG, 8>(a, hp, N, stream);
+        else if (row_lanes(a.F) == 16) launch_src_rows_as<GG, 16>(a, hp, N, stream);
+        else if (row_lanes(a.F) == 32) launch_src_rows_as<GG, 32>(a, hp, N, stream);
+        else                           launch_src_rows_as<GG, 64>(a, hp, N, stream);
+    };
+    switch (G) {
+        case 1:  go(std::integral_constant<int, 1>{}); break;
+        case 2:  go(std::integral_constant<int, 2>{}); break;
+        case 4:  go(std::integral_constant<int, 4>{}); break;
+        case 8:  go(std::integral_constant<int, 8>{}); break;
+        case 16: go(std::integral_constant<int, 16>{}); break;
+        case 32: go(std::integral_constant<int, 32>{}); break;
+        default: go(std::integral_constant<int, 64>{}); break;
+    }
+}
+
 // first_pass 0: the "dst" pass then the "src" pass; 1: the "src" pass alone (statistics already in place).
 // flash_g > 0: ordinary rows of the "dst" pass compute the source scores from the gathered rows, flash_g
 // lanes per head.
 template <int VEC, int NC, int HP, bool HU>
-void launch_passes(const BwdArgs& base, int first_pass, int64_t n_heavy, int64_t N, hipStream_t stream, int flash_g = 0)
+void launch_passes(const BwdArgs& base, int first_pass, int64_t n_heavy, int64_t N, hipStream_t stream, int64_t nnz = 0, int flash_g = 0)
 {
     if (first_pass == 0) {
         if (n_heavy > 0) {
@@ -835,15 +1011,22 @@ void launch_passes(const BwdArgs& base, int first_pass, int64_t n_heavy, int64_t
             }
         }
     }
+    if constexpr (VEC == 4 && NC == 1 && HU) {
+        if (flash_g > 0 && src_by_rows(base.F, HP, N, nnz) && N * base.ldg * 4 < (1ll << 32) && N * HP * 16 < (1ll << 32) &&
+            !agg_options().wide_offsets) {
+            launch_src_rows(base, HP, flash_g, N, stream);
+            return;
+        }
+    }
     const unsigned blocks = (unsigned)(base.heavy_rows + (N - base.heavy_rows + base.waves - 1) / base.waves);
     if (base.waves == 4) gat_bwd_src_kernel<VEC, NC, 4, HP, HU><<<dim3(blocks), dim3(64 * 4), 0, stream>>>(base);
     else                 gat_bwd_src_kernel<VEC, NC, 8, HP, HU><<<dim3(blocks), dim3(64 * 8), 0, stream>>>(base);
 }
 
 template <int VEC, int HP, bool HU>
-void dispatch_nc(int nc, const BwdArgs& a, int fp, int64_t nh, int64_t N, hipStream_t s, int flash_g = 0)
+void dispatch_nc(int nc, const BwdArgs& a, int fp, int64_t nh, int64_t N, hipStream_t s, int64_t nnz = 0, int flash_g = 0)
 {
-    if (nc == 1) launch_passes<VEC, 1, HP, HU>(a, fp, nh, N, s, flash_g);
+    if (nc == 1) launch_passes<VEC, 1, HP, HU>(a, fp, nh, N, s, nnz, flash_g);
     else if (nc == 2) launch_passes<VEC, 2, HP, HU>(a, fp, nh, N, s);
     else launch_passes<VEC, 4, HP, HU>(a, fp, nh, N, s);
 }
@@ -1009,8 +1192,8 @@ int launch_aggregate_backward(const AggBackwardCall& c, hipStream_t stream)
         // group of four-float lanes (see the kernel)
         const int g = a.Dh / 4;
         const int flash_g = (opt.gat_flash && nc == 1 && hu && g <= 64 && (g & (g - 1)) == 0) ? g : 0;
-        if (hp == 4) { if (hu) dispatch_nc<4, 4, true>(nc, a, first_pass, n_heavy, N, stream, flash_g); else dispatch_nc<4, 4, false>(nc, a, first_pass, n_heavy, N, stream); }
-        else         { if (hu) dispatch_nc<4, 8, true>(nc, a, first_pass, n_heavy, N, stream, flash_g); else dispatch_nc<4, 8, false>(nc, a, first_pass, n_heavy, N, stream); }
+        if (hp == 4) { if (hu) dispatch_nc<4, 4, true>(nc, a, first_pass, n_heavy, N, stream, p->nnz, flash_g); else dispatch_nc<4, 4, false>(nc, a, first_pass, n_heavy, N, stream); }
+        else         { if (hu) dispatch_nc<4, 8, true>(nc, a, first_pass, n_heavy, N, stream, p->nnz, flash_g); else dispatch_nc<4, 8, false>(nc, a, first_pass, n_heavy, N, stream); }
     } else {
         const int nc = (int)((F + 63) / 64);
         if (hp == 4) dispatch_wide<4>(nc, a, first_pass, n_heavy, N, stream);
