@@ -580,6 +580,145 @@ __global__ __launch_bounds__(64 * kLightWaves) void agg_rowgroup_kernel(AggArgs 
 }
 
 // ---------------------------------------------------------------------------
+// sum / mean / gcn_sym of rows, or slabs, of 4 P columns: P = 8, 16 or 32 lanes of four floats hold a row, and the R = 64 / P
+// groups of a wave walk R rows of the schedule, or shares of one long row, in lock step (EntryWalk).  Long rows first in every
+// slab, one per workgroup, their shares added up over the groups and then over the waves in order; one launch for both classes.
+// Bound by memory latency on small graphs, where R rows wait together, and by the gathered lines on large ones (2,449,029
+// nodes of 50 entries, 32 columns 2,330 us, 6.7 TB/s of lines).  linear_route says where it is taken, and what it measures.
+// ---------------------------------------------------------------------------
+template <int P, bool WEIGHTED>
+__global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
+{
+    constexpr int U = 8, R = 64 / P, NW = kHeavyWaves, PER = U / 4;    // entries and lanes of a batch
+    const int lane = threadIdx.x & 63, li = lane % P, g = lane / P;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t slab = blockIdx.x / a.slab_blocks, block = blockIdx.x % a.slab_blocks;
+    const bool heavy = block < a.heavy_rows;          // uniform over the workgroup
+    const int64_t first = heavy ? (int64_t)block : a.heavy_rows + ((int64_t)(block - (uint32_t)a.heavy_rows) * NW + wave) * R;
+    if (first >= a.n_rows) return;
+    const int64_t slot = heavy ? first : first + g;
+    const bool have = slot < a.n_rows;
+    int v = 0;
+    uint32_t lo = 0, hi = 0;
+    if (have) {
+        v = a.order[slot];
+        lo = (uint32_t)a.row_ptr[v];
+        hi = (uint32_t)a.row_ptr[v + 1];
+    }
+    typedef EntryWalk<P, WEIGHTED> Walk;
+    Walk walk;
+    const uint32_t rowbytes = (uint32_t)(a.ldz * 4);
+    int batches = heavy ? walk.start(a.col_idx, lo + Walk::kTile * (wave * R + g), hi, Walk::kTile * NW * R, rowbytes)
+                        : walk.start(a.col_idx, lo, hi, Walk::kTile, rowbytes);
+    batches = (batches + PER - 1) / PER;
+    // the weights of the current tile's entries, requested with its first gathers, and of the one before it
+    float w_cur[WEIGHTED ? 4 : 1], w_prev[WEIGHTED ? 4 : 1];
+    auto weights = [&]() {
+        if constexpr (WEIGHTED) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                w_prev[k] = w_cur[k];
+                w_cur[k] = walk.id[k] != kNoEntry ? a.wsrc[walk.id[k]] : 0.0f;
+            }
+        }
+    };
+    if constexpr (WEIGHTED) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w_cur[k] = 0.0f;
+    }
+    weights();
+
+    const int col = (int)slab * (4 * P) + li * 4;
+    const bool act = col < a.F;
+    const int valid = min(4, (int)a.F - col);
+    const table_t table = buffer_table(a.Z, a.table_bytes);
+    const uint32_t colbytes = act ? (uint32_t)col * 4 : kNoEntry;      // (columns past the row width fetch nothing)
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 z[2][U];
+    constexpr int kBatches = P / PER;                                   // of a tile
+    auto issue = [&](int k, f32x4 (&zz)[U]) {                           // batch k
+        const int j = k % kBatches;
+        if (j == 0 && k > 0) {
+            walk.take();
+            weights();
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+            zz[t] = __builtin_bit_cast(f32x4, load_entry(table, walk.at(j * PER + t / 4, t % 4), colbytes));
+    };
+    auto consume = [&](int k, const f32x4 (&zz)[U]) {
+        float w[U];
+        if constexpr (WEIGHTED) {
+            // (the next tile's weights have taken the place of this one's when its last batch is added up)
+            const bool old = (k + 1) % kBatches == 0 && k + 1 < batches;
+#pragma unroll
+            for (int t = 0; t < U; ++t)
+                w[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(walk.gaddr + 4 * (k % kBatches * PER + t / 4),
+                                                                   __float_as_int(old ? w_prev[t % 4] : w_cur[t % 4])));
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            if constexpr (WEIGHTED) {
+                acc[0] = fmaf(w[t], zz[t].x, acc[0]);
+                acc[1] = fmaf(w[t], zz[t].y, acc[1]);
+                acc[2] = fmaf(w[t], zz[t].z, acc[2]);
+                acc[3] = fmaf(w[t], zz[t].w, acc[3]);
+            } else {
+                acc[0] += zz[t].x;
+                acc[1] += zz[t].y;
+                acc[2] += zz[t].z;
+                acc[3] += zz[t].w;
+            }
+        }
+    };
+    if (batches > 0) issue(0, z[0]);
+    for (int k = 0; k < batches; k += 2) {
+        if (k + 1 < batches) issue(k + 1, z[1]);
+        consume(k, z[0]);
+        if (k + 1 >= batches) break;
+        if (k + 2 < batches) issue(k + 2, z[0]);
+        consume(k + 1, z[1]);
+    }
+
+    if (heavy) {
+#pragma unroll
+        for (int b = P; b < 64; b <<= 1)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], b, 64);
+        __shared__ float red[NW][4][P];
+        if (g == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) red[wave][k][li] = acc[k];
+        }
+        __syncthreads();
+        if (wave != 0 || g != 0) return;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            acc[k] = red[0][k][li];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) acc[k] += red[w][k][li];
+        }
+    }
+    if (!have || !act) return;
+    const int d = (int)(hi - lo);
+    float* orow = a.out + (int64_t)v * a.ldo;
+    float r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        float x = acc[k];
+        if (a.scale == SCALE_MEAN) x = d > 0 ? x / (float)d : 0.0f;
+        else if (a.scale == SCALE_GCN) x = x * a.dinv[v];
+        r[k] = x;
+    }
+    store_row<4>(orow + a.ocol + col, r, valid, a.out_vec != 0, a.out_half != 0);
+    if (a.copy_self) {
+        float zs[4];
+        load_row<4>(a.Z + (int64_t)v * a.ldz + col, zs);
+        store_row<4>(orow + col, zs, valid, a.self_vec != 0);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // attention scores  el[v,h] = <a_src[h], z_v,h>,  er[v,h] = <a_dst[h], z_v,h>
 // one wave per node; padded heads (h >= heads) get 0
 // ---------------------------------------------------------------------------
@@ -1227,6 +1366,19 @@ void launch_linear(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t 
     AggArgs a = base;
     const unsigned blocks = both_classes(a, n_heavy, N);
     agg_linear_kernel<VEC, NC, MAXOP><<<dim3(blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
+}
+
+template <int P>
+void launch_rows(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t stream)
+{
+    AggArgs a = base;
+    const int64_t rows = kHeavyWaves * (64 / P);
+    a.heavy_rows = n_heavy;
+    a.nslab = (int)((a.F + 4 * P - 1) / (4 * P));
+    a.slab_blocks = (uint32_t)(n_heavy + (N - n_heavy + rows - 1) / rows);
+    const dim3 grid(a.slab_blocks * (unsigned)a.nslab), block(64 * kHeavyWaves);
+    if (a.wsrc) agg_rows_kernel<P, true><<<grid, block, 0, stream>>>(a);
+    else        agg_rows_kernel<P, false><<<grid, block, 0, stream>>>(a);
 }
 
 template <int LPG, bool WEIGHTED, bool OFF32>
@@ -1905,6 +2057,66 @@ int gather_vec(const AggCall& c)
     return vec;
 }
 
+// Which kernels a sum, mean or gcn_sym over rows of at least 16-byte alignment takes: the range walk over narrow slabs, row
+// groups of `lanes` lanes over slabs of 4 * lanes columns, or (neither) whole rows.
+struct LinearRoute {
+    bool ranges;
+    int lanes;
+};
+// Measured over 23 graphs of 3,000 to 2,449,029 nodes and 5 to 500 entries per row at 32 to 602 columns, and over some
+// thousands of drawn calls (us, mean unless said, ranges against the others):
+//  Ranges pay where a range's slab is near an L2's size and rows are long: 232,965 nodes of 492 entries, 602 columns 13,440 and
+//  26,270; 400,000 of 250 (31 in each of 8 ranges) 17,200 and 27,660; 427,947 of 189, 192 columns 5,323 and 7,965; 50,000 of 400,
+//  64 columns 242 and 334; 476,789 of 205, 32 columns 1,180 and 1,572.  The other way 1,000,000 of 100 (6 in each of 16 ranges)
+//  47,760 and 30,750, 200,000 of 100, 64 columns 636 and 523, 32 columns 455 and 242, 60,000 of 40, 256 columns 257 and 232,
+//  2,449,029 of 50, 256 columns (whose one range is 300 MB) 18,430 and 17,360, with weights 30,780 and (whole rows) 20,470.
+//  They are two launches per range, so the call has to be long enough: 20,000 of 200, 256 columns 240 and 216, 602 columns
+//  468 and 526.  Where neither gains much the lines lie on the side of the ranges.
+//  Row groups for all rows of up to 64 columns: 1,000,000 of 20, 32 columns 394 against 773 in whole rows, of 8 187 and 489,
+//  3,000 of 5 5.2 and 8.0; 64 columns 733 and 898, 377 and 543, 5.5 and 8.0.
+//  Wider rows in slabs of 64 from 16 entries per row on, which leaves more of the nodes that are gathered most in an L2: 200,000
+//  of 20, 256 columns 489 and 587, 500,000 of 40 2,614 and 2,738; of 8 entries 1,568 and 1,300; 128 columns (two slabs) from 64
+//  entries on (20,000 of 200 112 and 123; 22,000 of 30, 96 columns 44 and 35).  Graphs that fit anyway in slabs of 128:
+//  10,000 of 400, 256 columns 152 and 189.  With weights, read again for every slab, where all of them stay in an L2: 200,000
+//  of 100, 256 columns 2,305 and 2,779, 30,000 of 40 111 and 132 (slabs of 128; 122 of 64), but 1,000,000 of 20 3,837 and 3,176.
+//  Slabs are taken where they are three quarters full (6,051 of 223, 192 columns in two of 128 85 and 76).
+LinearRoute linear_route(const AggCall& c, int vec, int parts)
+{
+    const retexo_plan* p = c.plan;
+    const AggOptions& opt = agg_options();
+    const int64_t N = p->N, nnz = p->nnz, F = c.F, work = nnz * (F < 32 ? 32 : F);
+    const bool weighted = c.mode == RETEXO_GCN_SYM;
+    if (vec != 4 || c.mode == RETEXO_MAX || c.mode == RETEXO_GAT_SOFTMAX || opt.slab_cols != 0) return {false, 0};
+    const LinearRoute ranges = {true, 0}, whole = {false, 0};
+    if (p->part_ptr && opt.parts >= 0) return ranges;              // (the caller said how many)
+    const bool dense = p->part_ptr || (nnz >= 32 * N && N * c.ldz * 4 > (4ll << 20));
+    auto mean_is = [&](int64_t entries) { return nnz >= entries * N; };
+    if (dense && N >= 16384 && N * 128 <= parts * (64ll << 20) && 2 * nnz >= 25 * N * parts) {
+        const bool enough = N >= 24000 || work >= 1200000000ll || mean_is(300);
+        if (F >= 100 ? enough && work >= 700000000ll && (mean_is(160) || mean_is((weighted ? 25 : 15) * parts))
+            : F > 32 ? enough && work >= 600000000ll && mean_is(N >= 200000 ? 105 : 140)
+                     : N >= 30000 && mean_is(N >= 200000 ? 170 : N >= 110000 ? 230 : N >= 40000 ? 255 : 350))
+            return ranges;
+    }
+    // one range of a large table: nearly the same (2,449,029 of 50, 32 columns, 729,742 of 36 476 and 516, 554,648 of 32, 64
+    // columns 562 and 619)
+    if (dense && !p->part_ptr && (F <= 32 ? N >= 350000 : F <= 64 && !weighted && N >= 200000 && N < 1000000)) return ranges;
+    if ((N * c.ldz + F) * 4 >= (1ll << 32) || opt.wide_offsets)              // (row groups have 32-bit offsets)
+        return dense && !(weighted && parts == 1) ? ranges : whole;
+    auto in_slabs = [&](int lanes) {
+        const int64_t slabs = (F + 4 * lanes - 1) / (4 * lanes);
+        if (4 * F >= 3 * slabs * (4 * lanes)) return LinearRoute{false, lanes};
+        return dense && mean_is(100) ? ranges : whole;
+    };
+    if (F <= 64) return {false, F <= 32 ? 8 : 16};
+    if (N < 16384) {
+        if (F > 256 || N < 8192 || !mean_is(64)) return dense && (F > 128 || mean_is(100)) ? ranges : whole;
+        return in_slabs(32);
+    }
+    if (weighted) return N < 300000 && mean_is(F <= 128 ? 100 : 32) ? in_slabs(N < 100000 ? 32 : 16) : whole;
+    return mean_is(F <= 128 ? 64 : 16) ? in_slabs(16) : whole;
+}
+
 // Which edge-softmax kernels a call takes.
 struct GatRoute {
     int vec;
@@ -2062,18 +2274,21 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     const bool own_launch = gat && !(vec == 4 && opt.gat_fast && gat_route(c).off32);
     int64_t n_heavy = long_rows(p, c.F, own_launch, gat);
 
+    // source-id ranges that the table is walked in, sized so that a range's slab (one 128-byte line per row) stays in L2
+    int parts = (int)opt.parts;
+    if (parts < 0) {
+        parts = 1;
+        while (p->part_ptr && parts < kMaxParts && N * 32 * 4 > (int64_t)parts * (8ll << 20)) parts *= 2;
+    }
+    const LinearRoute linear = linear_route(c, vec, parts);
     // narrow slabs (32/64/128 columns) use the grouped gather; they need float4 gathers
     // (the maximum is only implemented on whole rows)
     int64_t narrow = (!gat && vec == 4 && c.mode != RETEXO_MAX) ? opt.slab_cols : -1;
-    // default for graphs the plan split by source range (dense, table larger than L2): one
-    // 128-byte line per row and slab, ranges sized so that a range's slab stays in L2
-    // ... and for dense graphs whose table does not fit L2 although one slab of it does
-    if (narrow == 0 && (p->part_ptr || (p->nnz >= 32 * N && N * c.ldz * 4 > (4ll << 20)))) narrow = 32;
+    if (linear.ranges) narrow = 32;
     if (narrow == 32 || narrow == 64 || narrow == 128) {
         a.nslab = (int)((c.F + narrow - 1) / narrow);
         a.slab_major = opt.slab_major < 0 ? 1 : (int)opt.slab_major;
-        int parts = (int)opt.parts;
-        if (parts < 0) {
+        if (opt.parts < 0 && narrow != 32) {
             parts = 1;
             while (parts < kMaxParts && N * narrow * 4 > (int64_t)parts * (8ll << 20)) parts *= 2;
         }
@@ -2101,6 +2316,11 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
             else if (narrow == 64) dispatch_grouped<16>(a, n_heavy, N, wtd, off32, stream);
             else dispatch_grouped<32>(a, n_heavy, N, wtd, off32, stream);
         }
+    } else if (linear.lanes) {
+        a.table_bytes = (uint32_t)(((N - 1) * c.ldz + align_up(c.F, 4)) * 4);
+        if (linear.lanes == 8)       launch_rows<8>(a, n_heavy, N, stream);
+        else if (linear.lanes == 16) launch_rows<16>(a, n_heavy, N, stream);
+        else                         launch_rows<32>(a, n_heavy, N, stream);
     } else if (!gat) {
         const bool maxop = c.mode == RETEXO_MAX;
         if (vec == 4) dispatch_linear<4>(nc, maxop, a, n_heavy, N, stream);

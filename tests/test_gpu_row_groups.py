@@ -1,5 +1,5 @@
-"""Edge softmax over narrow rows, several rows of the schedule (or shares of a long row) per wave: forward, save mode and the
-backward after it against the fp64 oracle.  Rows that end with a wave, a group or a tile of the walk (32 and 64 entries), row
+"""Narrow rows, several rows of the schedule (or shares of a long row) per wave: edge softmax forward, save mode and the backward
+after it, and sum, mean and gcn_sym, whose wider rows are walked in slabs, against the fp64 oracle.  Rows that end with a wave, a group or a tile of the walk (32 and 64 entries), row
 counts that leave groups without a row, empty rows, long rows shared by a workgroup, rows padded or not."""
 import numpy as np
 import pytest
@@ -8,7 +8,7 @@ import oracle
 from paper_2302_13053_amd import binding as B
 from paper_2302_13053_amd import harness as Hn
 from paper_2302_13053_amd import workloads as wl
-from parity import assert_close
+from parity import assert_close, assert_cond_close
 from test_gpu_softmax_rows import decided_rows
 
 pytestmark = pytest.mark.gpu
@@ -28,7 +28,9 @@ def graphs():
         src.extend(20 + ring[:1000]), dst.extend(20 + (ring[:1000] + 7 * k) % 1000)
     specs = {"few": (1003, *wl.random_pairs(1003, 5000, 1, skew=1.0)),
              "edges": (1030, np.array(src, np.int32), np.array(dst, np.int32)),
-             "skewed": (16501, *wl.random_pairs(16501, 60000, 2, skew=3.0))}
+             "skewed": (16501, *wl.random_pairs(16501, 60000, 2, skew=3.0)),
+             "dense": (9001, *wl.random_pairs(9001, 400000, 3, skew=0.5)),
+             "mid": (17003, *wl.random_pairs(17003, 190000, 4, skew=0.5))}
     out = {}
     for name, (n, s, d) in specs.items():
         g = Hn.make_plan(Hn.csr_from_coo(Hn.dev(s), Hn.dev(d), n, False))
@@ -67,6 +69,26 @@ def test_row_groups(graphs, name, heads, dh, pad):
         assert_close(got[0].cpu().numpy()[:, :F], want[0], what="backward, row by row")
     for grad, ref, what in zip(got[1:], want[1:], ("source", "destination")):
         assert_close(grad.cpu().numpy().reshape(1, -1), ref.reshape(1, -1), what=what + " attention vector")
+
+
+@pytest.mark.parametrize("name,F", [("few", 1), ("few", 33), ("edges", 3), ("edges", 32), ("edges", 45), ("edges", 64), ("skewed", 8),
+                                    ("skewed", 31), ("skewed", 61), ("dense", 30), ("dense", 64), ("dense", 125), ("dense", 250),
+                                    ("mid", 200), ("mid", 185), ("mid", 602)])
+@pytest.mark.parametrize("mode", ["sum", "mean", "gcn_sym"])
+def test_linear(graphs, name, F, mode):
+    """One group size and slab count after the other: 8 lanes, 16, slabs of 32 lanes ("dense", 250: two) and of 16 ("mid" without
+    weights: four, three with a last one of 57 columns, and ten), beside whole rows in slabs of 256 columns ("mid" with weights)."""
+    g, rp, ci = graphs[name]
+    n, ld = g.n_nodes, (F + 3) // 4 * 4
+    Zh = np.full((n, ld + 4), np.nan, np.float32)             # what lies past a row is fetched with its last vector, and no more
+    Zh[:, :F] = wl.random_matrix(n, F, F)
+    out = Hn.aggregate(g, mode, Hn.dev(Zh), F, concat=F % 2 == 1, ld_out=2 * F + 3)
+    got = out.cpu().numpy()
+    kw = dict(self_concat=F % 2 == 1)
+    want = oracle.aggregate(mode, rp, ci, Zh[:, :F], F, **kw)
+    assert_cond_close(got[:, :want.shape[1]], want, oracle.aggregate_abs(mode, rp, ci, Zh[:, :F], F, **kw), what=mode)
+    again = Hn.aggregate(g, mode, Hn.dev(Zh), F, concat=F % 2 == 1, ld_out=2 * F + 3).cpu().numpy()
+    assert np.array_equal(got[:, :want.shape[1]], again[:, :want.shape[1]])
 
 
 @pytest.mark.parametrize("heads,dh", [(4, 64), (5, 32), (2, 64)])
