@@ -2226,6 +2226,17 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     if (opt.slab_cols > 0) nc = (int)((opt.slab_cols + 64 * vec - 1) / (64 * vec));
     else nc = (int)((c.F + 64 * vec - 1) / (64 * vec));
     nc = nc < 1 ? 1 : nc > max_nc ? max_nc : nc;
+    // Whole rows of more than 256 columns a slab of 256 after the other: one load per entry and slab leaves eight entries in
+    // flight per lane and twice the waves (mean in us, slabs of up to 768 and of 256: 1,000,000 nodes of 20 entries, 500 columns
+    // 6,697 and 5,886, 640 columns 8,647 and 7,367; 2,708 of 4, 640 columns 13.3 and 8.2, 1,433 columns 17.2 and 13.5; 50,000 of
+    // 10, 1,433 columns 577 and 416).  Not where the last slab would be nearly empty (288 columns, 1,000,000 of 20 3,440 and
+    // 3,715; 544, 81,938 of 5 157 and 179), nor for rows of a few entries over a large table (300,000 of 4, 640 columns 577 and
+    // 607), nor for the maximum (19,717 of 5, 500 columns 31 and 39).
+    const int64_t last_slab = c.F % 256 == 0 ? 256 : c.F % 256;
+    if (!gat && vec == 4 && c.mode != RETEXO_MAX && opt.slab_cols == 0 && c.F > 256 &&
+        last_slab >= (c.F > 512 ? 64 : c.mode == RETEXO_GCN_SYM ? 192 : 128) &&
+        !(p->nnz < 10 * N && N >= 100000 && (c.F > 512 || c.mode == RETEXO_GCN_SYM)))
+        nc = 1;
     const int64_t slab_w = 64 * (int64_t)vec * nc;
 
     AggArgs a;
