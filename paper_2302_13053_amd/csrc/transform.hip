@@ -510,6 +510,127 @@ __global__ __launch_bounds__(512) void transform_few_rows_kernel(
     }
 }
 
+// The same for long sums: 32 x 32 tiles, sixteen waves, operands through LDS.  The kernel above asks for sixteen
+// bytes of 32 rows at a time and for single floats of W, which keeps the address units busy for as long as the matrix cores (2,708
+// x 2,866 -> 64: 28.2 us; without its products, without W or without H 20.6, 20.6, 18.6).  Here chunks of 128 k come in whole
+// lines, two ahead, and each wave multiplies eight k of every chunk: 23.7 us there (27.4 in the same loop), 1,433 columns 15.2 ->
+// 13.8, 2,866 -> 256 80 -> 62, 300 -> 200 13.7 -> 11.8.  Now bound by the float32 instruction.  Shorter sums stay above: where
+// every compute unit has a tile at the most 500 columns 6.5 -> 6.7, 128 3.3 -> 3.8.
+constexpr int kStagedOne = 768, kStagedMany = 256;       // k from which it is taken, up to 256 tiles and more
+template <bool MASKED>
+__global__ __launch_bounds__(1024) void transform_few_staged_kernel(
+    int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
+    const float* __restrict__ W, const float* __restrict__ bias, int relu,
+    float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm, float* __restrict__ colsums)
+{
+    constexpr int NW = 16, KC = 128, SLICE = KC / NW;
+    constexpr int PH = KC + 4, PW = 36;          // row pitches in LDS: a wave's reads meet no bank twice
+    union Shared {
+        struct { float h[2][32 * PH], w[2][KC * PW]; };
+        float part[NW / 2][32][33];
+        float sums[1024];
+    };
+    __shared__ __align__(16) Shared sh;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lrow = lane & 31, lk = lane >> 5;
+    const int64_t m0 = (int64_t)blockIdx.x * 32;
+    const int n0 = blockIdx.y * 32;
+    const int chunks = (D_in + KC - 1) / KC;
+    // A thread's piece of a chunk: four k of a row of H, four columns of a row of W.  All are loaded without a branch (the
+    // loads of two chunks stay in flight): a piece that reaches over the end of its row is loaded from four floats before
+    // that (D_in, D_out >= 4) and moved into place, with zeroes behind it, on its way to LDS.
+    const int hr = tid / (KC / 4), hk = tid % (KC / 4) * 4, wk = tid / 8, wc = n0 + tid % 8 * 4;
+    const float* hp = H + (m0 + hr < N ? m0 + hr : N - 1) * ldh;           // rows past the end repeat the last one; never stored
+    const float* wp = W + min(wc, D_out - 4);
+    const int w_over = min(max(wc + 4 - D_out, 0), 4);
+    const bool whole_columns = n0 + 32 <= D_out;                           // (uniform)
+    auto moved = [](f32x4 t, int over) {         // elements past the row's end: zero
+        f32x4 r = t;
+        if (over & 1) r = f32x4{r[1], r[2], r[3], 0.0f};
+        if (over & 2) r = f32x4{r[2], r[3], 0.0f, 0.0f};
+        if (over & 4) r = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        return r;
+    };
+
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    f32x4 rh[2], rw[2];
+    auto load = [&](int ch, int slot) {
+        const int k0 = min(ch, chunks - 1) * KC;
+        rh[slot] = *reinterpret_cast<const f32x4_any*>(hp + min(k0 + hk, D_in - 4));
+        rw[slot] = *reinterpret_cast<const f32x4_any*>(wp + (int64_t)min(k0 + wk, D_in - 1) * D_out);
+    };
+    // chunk `ch`, which the registers of `slot` hold, goes to its LDS buffer (last read two chunks ago: the barrier of the
+    // chunk between lies behind every wave by then); the chunk two ahead takes the registers
+    auto chunk = [&](int ch, int slot) {
+        f32x4 h = rh[slot], w = rw[slot];
+        if (ch == chunks - 1) {                  // (uniform)
+            h = moved(h, min(max(ch * KC + hk + 4 - D_in, 0), 4));
+            w = ch * KC + wk < D_in ? w : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        if (!whole_columns) w = moved(w, w_over);
+        *reinterpret_cast<f32x4*>(&sh.h[slot][hr * PH + hk]) = h;
+        *reinterpret_cast<f32x4*>(&sh.w[slot][wk * PW + (wc - n0)]) = w;
+        load(ch + 2, slot);
+        __syncthreads();
+        const int kb = wave * SLICE + 4 * lk;    // lower half-wave: the slice's first four k, upper: the others
+        const f32x4 a = *reinterpret_cast<const f32x4*>(&sh.h[slot][lrow * PH + kb]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], sh.w[slot][(kb + q) * PW + lrow], acc, 0, 0, 0);
+    };
+    load(0, 0);
+    load(1, 1);
+    int ch = 0;
+    for (; ch + 1 < chunks; ch += 2) {
+        chunk(ch, 0);
+        chunk(ch + 1, 1);
+    }
+    if (ch < chunks) chunk(ch, 0);
+
+    __syncthreads();                             // the partial tiles lie over the operands
+    auto put = [&](int slot) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sh.part[slot][8 * (r / 4) + 4 * lk + (r % 4)][lrow] = acc[r];
+    };
+    if (wave >= NW / 2) put(wave - NW / 2);
+    __syncthreads();
+    if (wave < NW / 2) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] += sh.part[wave][8 * (r / 4) + 4 * lk + (r % 4)][lrow];
+    }
+    __syncthreads();
+    if (wave < NW / 2) put(wave);
+    __syncthreads();
+
+    const int r = tid / 32, c = tid % 32;        // one output per thread
+    const int64_t orow = m0 + r;
+    const int ocol = n0 + c;
+    float x = sh.part[0][r][c];
+#pragma unroll
+    for (int w = 1; w < NW / 2; ++w) x += sh.part[w][r][c];
+    const bool inside = orow < N && ocol < D_out;
+    if (inside) {
+        x += bias ? bias[ocol] : 0.0f;
+        if (relu) x = fmaxf(x, 0.0f);
+        if constexpr (MASKED) x = mask[orow * ldm + ocol] > 0.0f ? x : 0.0f;
+        Z[orow * ldz + ocol] = x;
+    }
+    if constexpr (MASKED) {                      // column sums of the 32 rows, as in the block kernel
+        __syncthreads();
+        sh.sums[tid] = inside ? x : 0.0f;
+        __syncthreads();
+        if (tid < 32 && n0 + tid < D_out) {
+            float t[4] = {};
+#pragma unroll
+            for (int i = 0; i < 32; ++i) t[i % 4] += sh.sums[i * 32 + tid];
+            colsums[(int64_t)blockIdx.x * D_out + n0 + tid] = (t[0] + t[1]) + (t[2] + t[3]);
+        }
+    }
+}
+
 // D_in == 0: the product is empty and every row is act(b); H and W are not touched (they may be NULL)
 __global__ void bias_rows_kernel(int64_t N, int D_out, const float* __restrict__ bias, int relu,
                                  float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm)
@@ -548,6 +669,11 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
 {
     const int r = relu ? 1 : 0;
     const unsigned gx = (unsigned)((N + 31) / 32);
+    if (D_out >= 4 && D_in >= (gx * ((D_out + 31) / 32) > 256 ? kStagedMany : kStagedOne)) {
+        const dim3 grid(gx, (unsigned)((D_out + 31) / 32));
+        transform_few_staged_kernel<MASKED><<<grid, dim3(1024), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
+        return;
+    }
     // 32-column tiles when 64-column ones would not give every compute unit a workgroup
     if (D_out <= 32 || (int64_t)gx * ((D_out + 63) / 64) < 256) {
         dim3 grid(gx, (unsigned)((D_out + 31) / 32));
@@ -558,14 +684,33 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
     }
 }
 
-// Fewer 128-row blocks (times the column blocks) than the "transform_few_blocks" setting, 128 unless changed:
-// the few-rows kernel.  The choice depends on the shape only, never on alignment, so one shape always takes
-// one order of additions.
+// Which kernel a shape takes, by the shape only, never by alignment, so that one shape always takes one order of additions.
+//  Few rows: up to 832 tiles of 32 x 32.  A compute unit takes some 9 ns per k and tile there, and 29 to 59 ns per k for one block
+//  of 128 rows, whose loop waits for memory when it is alone: 8,000 x 600 -> 41 (500 tiles) 12.6 us and 20.9, 2,708 x 2,866 -> 256
+//  (680) 61.8 and 83.9, 20,000 x 500 -> 20 (625) 14.7 and 18.3, 26,000 x 1,000 -> 32 (813) 32.9 and 33.3, 4,000 x 2,000 -> 200 (875)
+//  59.5 and 59.6, 14,000 x 500 -> 41 (876) 19.8 and 18.5, 5,000 x 500 -> 300 (1,570) 32.0 and 20.3, 2,708 x 256 -> 1,000
+//  (2,720) 29.7 and 16.7.  (The "transform_few_blocks" setting, unless it is 128: fewer row blocks times column blocks than
+//  it says.)
+//  Blocks: as wide as the output up to 256 columns; narrower, so that H is read more than once, where that gives up to 256 blocks
+//  instead of fewer (14,000 x 500 -> 256 in 110 blocks 37.3, 220 of 128 columns 30.4; 8,000 x 1,000 -> 256 in 63 65.3, 252 of 64
+//  38.9; 19,717 x 500 -> 256 in 155 36.6, 310 of 128 42.6), and half as wide where the widest are a few more than compute units
+//  (2,708 x 64 -> 2,866 in 264 19.1, 506 of 128 12.9; 40,000 x 256 -> 256 in 313 44.6, 626 40.3).
 int64_t block_width(int64_t D_out) { return D_out <= 32 ? 32 : D_out <= 64 ? 64 : D_out <= 128 ? 128 : D_out <= 192 ? 192 : 256; }
+int64_t blocks_of(int64_t N, int64_t D_out, int64_t bn) { return (N + 127) / 128 * ((D_out + bn - 1) / bn); }
 bool takes_few_rows(int64_t N, int64_t D_out)
 {
-    const int64_t bn = block_width(D_out);
-    return (N + 127) / 128 * ((D_out + bn - 1) / bn) < agg_options().few_blocks;
+    const int64_t few = agg_options().few_blocks;
+    if (few == 128) return (N + 31) / 32 * ((D_out + 31) / 32) <= 832;
+    return blocks_of(N, D_out, block_width(D_out)) < few;
+}
+int64_t block_width_for(int64_t N, int64_t D_out)
+{
+    const int64_t widest = block_width(D_out), blocks = blocks_of(N, D_out, widest);
+    if (blocks > 256) return widest == 256 && blocks <= 400 ? 128 : widest;
+    int64_t bn = widest;
+    for (int64_t narrower : {128, 64, 32})
+        if (narrower < bn && blocks_of(N, D_out, narrower) <= 256) bn = narrower;
+    return bn;
 }
 
 template <bool MASKED>
@@ -580,7 +725,7 @@ void launch_by_width(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
     auto go = [&](auto width) {
         launch<decltype(width)::value, MASKED>(N, D_in, D_out, H, ldh, W, b, relu, Z, ldz, mask, ldm, keep_sign, colsums, stream);
     };
-    const int64_t bn = block_width(D_out);
+    const int64_t bn = block_width_for(N, D_out);
     if (bn == 32)       go(std::integral_constant<int, 32>{});
     else if (bn == 64)  go(std::integral_constant<int, 64>{});
     else if (bn == 128) go(std::integral_constant<int, 128>{});
