@@ -608,9 +608,14 @@ __global__ __launch_bounds__(1024) void transform_few_staged_kernel(
     const int r = tid / 32, c = tid % 32;        // one output per thread
     const int64_t orow = m0 + r;
     const int ocol = n0 + c;
-    float x = sh.part[0][r][c];
+    float t[NW / 2];                             // added in pairs: the fewest roundings
 #pragma unroll
-    for (int w = 1; w < NW / 2; ++w) x += sh.part[w][r][c];
+    for (int w = 0; w < NW / 2; ++w) t[w] = sh.part[w][r][c];
+#pragma unroll
+    for (int w = NW / 4; w >= 1; w /= 2)
+#pragma unroll
+        for (int i = 0; i < w; ++i) t[i] += t[i + w];
+    float x = t[0];
     const bool inside = orow < N && ocol < D_out;
     if (inside) {
         x += bias ? bias[ocol] : 0.0f;
@@ -685,12 +690,12 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
 }
 
 // Which kernel a shape takes, by the shape only, never by alignment, so that one shape always takes one order of additions.
-//  Few rows: up to 832 tiles of 32 x 32.  A compute unit takes some 9 ns per k and tile there, and 29 to 59 ns per k for one block
-//  of 128 rows, whose loop waits for memory when it is alone: 8,000 x 600 -> 41 (500 tiles) 12.6 us and 20.9, 2,708 x 2,866 -> 256
-//  (680) 61.8 and 83.9, 20,000 x 500 -> 20 (625) 14.7 and 18.3, 26,000 x 1,000 -> 32 (813) 32.9 and 33.3, 4,000 x 2,000 -> 200 (875)
-//  59.5 and 59.6, 14,000 x 500 -> 41 (876) 19.8 and 18.5, 5,000 x 500 -> 300 (1,570) 32.0 and 20.3, 2,708 x 256 -> 1,000
-//  (2,720) 29.7 and 16.7.  (The "transform_few_blocks" setting, unless it is 128: fewer row blocks times column blocks than
-//  it says.)
+//  Few rows: up to 832 tiles of 32 x 32 and fewer than 128 blocks.  A compute unit takes some 9 ns per k and tile there, and
+//  29 to 59 ns per k for one block of 128 rows, whose loop waits for memory when it is alone: 8,000 x 600 -> 41 (500 tiles)
+//  12.6 us and 20.9, 2,708 x 2,866 -> 256 (680) 61.8 and 83.9, 4,000 x 2,000 -> 200 (875) 59.5 and 59.6, 14,000 x 500 -> 41 (876)
+//  19.8 and 18.5, 5,000 x 500 -> 300 (1,570) 32.0 and 20.3, 2,708 x 256 -> 1,000 (2,720) 29.7 and 16.7.  More blocks keep the
+//  split products, whose sums are a quarter closer, although few rows are faster (20,000 x 500 -> 20 14.7 and 18.3).  (The
+//  "transform_few_blocks" setting, unless it is 128: fewer blocks than it says.)
 //  Blocks: as wide as the output up to 256 columns; narrower, so that H is read more than once, where that gives up to 256 blocks
 //  instead of fewer (14,000 x 500 -> 256 in 110 blocks 37.3, 220 of 128 columns 30.4; 8,000 x 1,000 -> 256 in 63 65.3, 252 of 64
 //  38.9; 19,717 x 500 -> 256 in 155 36.6, 310 of 128 42.6), and half as wide where the widest are a few more than compute units
@@ -700,8 +705,7 @@ int64_t blocks_of(int64_t N, int64_t D_out, int64_t bn) { return (N + 127) / 128
 bool takes_few_rows(int64_t N, int64_t D_out)
 {
     const int64_t few = agg_options().few_blocks;
-    if (few == 128) return (N + 31) / 32 * ((D_out + 31) / 32) <= 832;
-    return blocks_of(N, D_out, block_width(D_out)) < few;
+    return blocks_of(N, D_out, block_width(D_out)) < few && (few != 128 || (N + 31) / 32 * ((D_out + 31) / 32) <= 832);
 }
 int64_t block_width_for(int64_t N, int64_t D_out)
 {
