@@ -517,7 +517,7 @@ __global__ __launch_bounds__(512) void transform_few_rows_kernel(
 // 13.8, 2,866 -> 256 80 -> 62, 300 -> 200 13.7 -> 11.8.  Now bound by the float32 instruction.  Shorter sums stay above: where
 // every compute unit has a tile at the most 500 columns 6.5 -> 6.7, 128 3.3 -> 3.8.
 constexpr int kStagedOne = 768, kStagedMany = 256;       // k from which it is taken, up to 256 tiles and more
-template <bool MASKED>
+template <bool MASKED, bool HALVES>
 __global__ __launch_bounds__(1024) void transform_few_staged_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
@@ -553,9 +553,12 @@ __global__ __launch_bounds__(1024) void transform_few_staged_kernel(
         return r;
     };
 
-    f32x16 acc;
+    // HALVES: the halves of a sum apart, where the registers cost nothing (one workgroup per compute unit; otherwise 2,708 x 2,866
+    // -> 256 62 -> 69 us).  A layer's input is often [self | aggregate], and terms of unlike size round each other: 2,866 -> 64 on
+    // such an input, 1 % of it not zero, 7.8e-8 off 64 bits without, 6.9e-8 so (the kernel above 7.4e-8).
+    f32x16 acc, first;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    for (int r = 0; r < 16; ++r) acc[r] = first[r] = 0.0f;
     f32x4 rh[2], rw[2];
     auto load = [&](int ch, int slot) {
         const int k0 = min(ch, chunks - 1) * KC;
@@ -564,7 +567,7 @@ __global__ __launch_bounds__(1024) void transform_few_staged_kernel(
     };
     // chunk `ch`, which the registers of `slot` hold, goes to its LDS buffer (last read two chunks ago: the barrier of the
     // chunk between lies behind every wave by then); the chunk two ahead takes the registers
-    auto chunk = [&](int ch, int slot) {
+    auto chunk = [&](int ch, int slot, f32x16& to) {
         f32x4 h = rh[slot], w = rw[slot];
         if (ch == chunks - 1) {                  // (uniform)
             h = moved(h, min(max(ch * KC + hk + 4 - D_in, 0), 4));
@@ -579,16 +582,24 @@ __global__ __launch_bounds__(1024) void transform_few_staged_kernel(
         const f32x4 a = *reinterpret_cast<const f32x4*>(&sh.h[slot][lrow * PH + kb]);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], sh.w[slot][(kb + q) * PW + lrow], acc, 0, 0, 0);
+            to = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], sh.w[slot][(kb + q) * PW + lrow], to, 0, 0, 0);
     };
     load(0, 0);
     load(1, 1);
     int ch = 0;
-    for (; ch + 1 < chunks; ch += 2) {
-        chunk(ch, 0);
-        chunk(ch + 1, 1);
+    for (const int half = HALVES ? chunks / 4 * 2 : 0; ch < half; ch += 2) {
+        chunk(ch, 0, first);
+        chunk(ch + 1, 1, first);
     }
-    if (ch < chunks) chunk(ch, 0);
+    for (; ch + 1 < chunks; ch += 2) {
+        chunk(ch, 0, acc);
+        chunk(ch + 1, 1, acc);
+    }
+    if (ch < chunks) chunk(ch, 0, acc);
+    if constexpr (HALVES) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] += first[r];
+    }
 
     __syncthreads();                             // the partial tiles lie over the operands
     auto put = [&](int slot) {
@@ -674,9 +685,11 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
 {
     const int r = relu ? 1 : 0;
     const unsigned gx = (unsigned)((N + 31) / 32);
-    if (D_out >= 4 && D_in >= (gx * ((D_out + 31) / 32) > 256 ? kStagedMany : kStagedOne)) {
+    const bool many = gx * ((D_out + 31) / 32) > 256;
+    if (D_out >= 4 && D_in >= (many ? kStagedMany : kStagedOne)) {
         const dim3 grid(gx, (unsigned)((D_out + 31) / 32));
-        transform_few_staged_kernel<MASKED><<<grid, dim3(1024), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
+        if (many) transform_few_staged_kernel<MASKED, false><<<grid, dim3(1024), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
+        else      transform_few_staged_kernel<MASKED, true><<<grid, dim3(1024), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
         return;
     }
     // 32-column tiles when 64-column ones would not give every compute unit a workgroup
