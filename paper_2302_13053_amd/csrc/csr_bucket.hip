@@ -29,10 +29,12 @@
 //
 // Integer arithmetic only.  The order in which atomics hand out positions inside a bucket is
 // arbitrary, but the sorted, repeat-free result is not, so the output is bitwise reproducible.
+#include <string.h>
 #include <type_traits>
 
 #include "common.hpp"
 #include "csr_bucket.hpp"
+#include "report.hpp"
 
 namespace {
 
@@ -990,11 +992,15 @@ __global__ __launch_bounds__(256) void emit_kernel(
     BucketHeader* hdr, const uint32_t* __restrict__ bucket_off, const uint32_t* __restrict__ bucket_bin0,
     const uint32_t* __restrict__ bucket_out, const uint32_t* __restrict__ cols_tmp, const int32_t* __restrict__ row_unique,
     const uint32_t* __restrict__ bucket_total, int64_t col_capacity,
-    int s, int64_t N, int64_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx)
+    int s, int64_t N, int64_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx, BucketHeader* report)
 {
     constexpr int RPT = kRowSpan / 256;                      // rows per thread
     __shared__ uint32_t sc[2 * 4 + 1];
-    if (hdr->bad_id || hdr->internal || (!SUM && hdr->overflow)) return;
+    const bool reports = report && blockIdx.x == 0 && threadIdx.x == 0;
+    if (hdr->bad_id || hdr->internal || (!SUM && hdr->overflow)) {
+        if (reports) *report = *hdr;
+        return;
+    }
     const uint32_t b = blockIdx.x, n = hdr->n_buckets;
     if (b >= n) return;
     uint32_t out0, nnz;
@@ -1012,9 +1018,11 @@ __global__ __launch_bounds__(256) void emit_kernel(
         if (b == 0 && threadIdx.x == 0) {
             hdr->nnz = (int64_t)nnz;
             hdr->overflow = (int64_t)nnz > col_capacity ? 1u : 0u;
+            if (reports) *report = *hdr;
         }
         if ((int64_t)nnz > col_capacity) return;
     } else {
+        if (reports) *report = *hdr;
         out0 = bucket_out[b];
         nnz = (uint32_t)hdr->nnz;
     }
@@ -1164,7 +1172,7 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
     if (L.small) {
         plan(std::true_type{});
     } else {
-        RETEXO_HIP_TRY(hipMemsetAsync(hdr, 0, (size_t)(L.counts - L.header), stream));      // header and bin counts
+        if (int e = launch_zero(hdr, (size_t)(L.counts - L.header), stream)) return e;      // header and bin counts
         hist_kernel<<<dim3((unsigned)L.hist_blocks), dim3(kThreads), 0, stream>>>(
             n_pairs, d_src, d_dst, N, L.n_items, L.items_per_block, L.s, L.nbins, u32(L.counts), hdr);
         colsum_kernel<<<dim3((unsigned)((L.nbins + 255) / 256), kColsumSlices), dim3(256), 0, stream>>>(
@@ -1189,10 +1197,12 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
     sort_kernel<<<dim3((unsigned)L.bucket_bound), dim3(kSortThreads), 0, stream>>>(
         hdr, pa.bucket_off, pa.bucket_bin0, u32(L.buf_c), u32(L.buf_a), (int32_t*)(ws + L.row_unique),
         u32(L.bucket_total), L.cbits, L.s, N);
+    HostReport report;
+    static_assert(sizeof(BucketHeader) <= kReportBytes, "a report holds it");
     auto emit = [&](auto sum) {
         emit_kernel<decltype(sum)::value><<<dim3((unsigned)L.bucket_bound), dim3(256), 0, stream>>>(
             hdr, pa.bucket_off, pa.bucket_bin0, u32(L.bucket_out), u32(L.buf_a), (const int32_t*)(ws + L.row_unique),
-            u32(L.bucket_total), col_capacity, L.s, N, d_row_ptr, d_col_idx);
+            u32(L.bucket_total), col_capacity, L.s, N, d_row_ptr, d_col_idx, (BucketHeader*)report.get());
     };
     if (L.bucket_bound <= kFewBuckets) {
         emit(std::true_type{});
@@ -1202,8 +1212,9 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
     }
     RETEXO_HIP_TRY(hipGetLastError());
     BucketHeader h;
-    RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
+    if (!report.get()) RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
     RETEXO_HIP_TRY(hipStreamSynchronize(stream));
+    if (report.get()) memcpy(&h, report.get(), sizeof(h));
     if (h.bad_id) return RETEXO_E_CSR;
     if (h.internal) return RETEXO_E_HIP;
     if (h_nnz) *h_nnz = h.nnz;

@@ -27,14 +27,17 @@
 
 #include <rocprim/device/device_scan.hpp>
 
+#include <string.h>
+
 #include "common.hpp"
+#include "report.hpp"
 
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxWorkers = 64;       // one bit per worker in a 64-bit mask
 
-struct ShareHeader {                  // start of the workspace; copied to the host
+struct ShareHeader {                  // start of the workspace; read by the host
     uint32_t bad_part;                // a partition id outside [0, n_parts)
     uint32_t pad;
     int64_t n_inner, n_halo, nnz_local, n_send;
@@ -336,19 +339,20 @@ __global__ __launch_bounds__(kThreads) void list_count_kernel(int64_t N, int n_p
 
 // the header's sizes, N >= 1: a list's offset is its first block's position; block_entries becomes its exclusive prefix sum
 __global__ __launch_bounds__(kLdsThreads) void totals_kernel(int n_parts, int64_t blocks, const uint32_t* __restrict__ list_at,
-                                                             int64_t* __restrict__ block_entries, ShareHeader* hdr)
+                                                             int64_t* __restrict__ block_entries, const ShareHeader* hdr,
+                                                             ShareHeader* report)
 {
     __shared__ int64_t sums[kLdsWaves];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto at = [&](int l) { return list_at[(int64_t)l * blocks]; };         // (differences are exact modulo 2^32)
     for (int l = tid; l <= n_parts; l += kLdsThreads) {
-        hdr->send_off[l] = at(l);
-        hdr->recv_off[l] = (int64_t)(at(n_parts + l) - at(n_parts));
+        report->send_off[l] = at(l);
+        report->recv_off[l] = (int64_t)(at(n_parts + l) - at(n_parts));
     }
     if (tid == 0) {
-        hdr->n_inner = (int64_t)(at(2 * n_parts + 1) - at(2 * n_parts));
-        hdr->n_halo = (int64_t)(at(2 * n_parts + 2) - at(2 * n_parts + 1));
-        hdr->n_send = at(n_parts);
+        report->n_inner = (int64_t)(at(2 * n_parts + 1) - at(2 * n_parts));
+        report->n_halo = (int64_t)(at(2 * n_parts + 2) - at(2 * n_parts + 1));
+        report->n_send = at(n_parts);
     }
     int64_t before = 0;
     for (int64_t b0 = 0; b0 < blocks; b0 += kLdsThreads) {
@@ -370,7 +374,10 @@ __global__ __launch_bounds__(kLdsThreads) void totals_kernel(int n_parts, int64_
         before += all;
         __syncthreads();
     }
-    if (tid == 0) hdr->nnz_local = before;
+    if (tid == 0) {
+        report->nnz_local = before;
+        report->bad_part = hdr->bad_part;
+    }
 }
 
 // local numbering, global ids, degrees and row offsets of the local nodes, and the members of the lists: a wave's members of a
@@ -700,7 +707,10 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     uint32_t* list_at = (uint32_t*)(ws + L.list_at);
     void* tmp = ws + L.tmp;
 
-    RETEXO_HIP_TRY(hipMemsetAsync(hdr, 0, sizeof(ShareHeader), stream));
+    if (int e = launch_zero(hdr, sizeof(ShareHeader), stream)) return e;
+    HostReport report;
+    static_assert(sizeof(ShareHeader) <= kReportBytes && sizeof(ShareHeader) % 4 == 0, "a report holds it");
+    const bool direct = N > 0 && report.get();
     const dim3 node_grid((unsigned)L.blocks);
     if (N > 0) {
         uint32_t* owners = (uint32_t*)(ws + L.owners);
@@ -727,11 +737,13 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
         size_t tb = L.tmp_bytes;
         RETEXO_HIP_TRY(rocprim::exclusive_scan(tmp, tb, counts, list_at, 0u, (size_t)((2 * n_parts + 2) * L.blocks + 1),
                                                rocprim::plus<uint32_t>(), stream));
-        totals_kernel<<<dim3(1), dim3(kLdsThreads), 0, stream>>>(n_parts, L.blocks, list_at, block_entries, hdr);
+        totals_kernel<<<dim3(1), dim3(kLdsThreads), 0, stream>>>(n_parts, L.blocks, list_at, block_entries, hdr,
+                                                               direct ? (ShareHeader*)report.get() : hdr);
     }
     ShareHeader h;
-    RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
+    if (!direct) RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
     RETEXO_HIP_TRY(hipStreamSynchronize(stream));
+    if (direct) memcpy(&h, report.get(), sizeof(h));
     if (h.bad_part) return RETEXO_E_PARTITION;
     h_sizes[0] = h.n_inner;
     h_sizes[1] = h.n_halo;

@@ -15,12 +15,13 @@
 #include <new>
 
 #include "common.hpp"
+#include "report.hpp"
 
 namespace {
 
 constexpr int kThreads = 256;
 
-// What the host reads back.
+// What the host reads back: written by one kernel, to a HostReport or to device memory.
 struct Readback {
     int64_t counts[kPlanThresholdCount + 1];      // rows of at least kPlanThresholds[i] entries ... and the largest degree
     uint32_t bad;
@@ -507,6 +508,11 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
     p->order = (int32_t*)((char*)keep + L.o_order);
     char* sc = (char*)scratch;
     Readback* rb = (Readback*)(sc + L.s_rb);
+    const bool check = (flags & RETEXO_F_VALIDATE) && nnz > 0;         // (its atomics need device memory)
+    HostReport report;
+    static_assert(sizeof(Readback) <= kReportBytes, "a report holds it");
+    const bool direct = N > 0 && !check && report.get();
+    if (direct) rb = (Readback*)report.get();
     Thresholds th;
     for (int i = 0; i < kPlanThresholdCount; ++i) th.t[i] = kPlanThresholds[i];
     if (N == 0) {
@@ -540,13 +546,14 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
         split_rows_kernel<<<dim3((unsigned)((N + rows_per_block - 1) / rows_per_block)), dim3(kThreads), 0, stream>>>(
             N, nnz, p->part_span, p->row_ptr, p->col_idx, p->order, p->part_ptr);
     }
-    if ((flags & RETEXO_F_VALIDATE) && nnz > 0)
+    if (check)
         check_columns<<<dim3((unsigned)((nnz + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream>>>(
             nnz, N, p->col_idx, &rb->bad);
     RETEXO_HIP_TRY(hipGetLastError());
     Readback h;
-    RETEXO_HIP_TRY(hipMemcpyAsync(&h, rb, sizeof(h), hipMemcpyDeviceToHost, stream));
+    if (!direct) RETEXO_HIP_TRY(hipMemcpyAsync(&h, rb, sizeof(h), hipMemcpyDeviceToHost, stream));
     RETEXO_HIP_TRY(hipStreamSynchronize(stream));
+    if (direct) memcpy(&h, rb, sizeof(h));
     if (h.bad) return RETEXO_E_CSR;
     for (int i = 0; i < kPlanThresholdCount; ++i) p->rows_at_least[i] = h.counts[i];
     p->max_degree = (int32_t)h.counts[kPlanThresholdCount];

@@ -1,0 +1,50 @@
+#include "report.hpp"
+
+#include <hip/hip_runtime.h>
+#include <mutex>
+#include <stdint.h>
+
+namespace {
+
+constexpr int kPieces = 32;
+
+struct Pool {
+    std::mutex lock;
+    char* memory = nullptr;
+    uint32_t taken = 0;          // bit per piece
+};
+// never destroyed: a thread may still hold a piece when the process ends
+Pool& pool()
+{
+    static Pool* p = new Pool;
+    return *p;
+}
+
+}  // namespace
+
+HostReport::HostReport()
+{
+    Pool& p = pool();
+    std::lock_guard<std::mutex> guard(p.lock);
+    if (!p.memory) {
+        // readable and writable by every device, coherent: what a kernel has written is there once the stream has been waited for
+        void* m = nullptr;
+        if (hipHostMalloc(&m, kPieces * kReportBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        p.memory = (char*)m;
+    }
+    if (p.taken == 0xffffffffu) return;
+    index_ = __builtin_ctz(~p.taken);
+    p.taken |= 1u << index_;
+    piece_ = p.memory + (size_t)index_ * kReportBytes;
+}
+
+HostReport::~HostReport()
+{
+    if (index_ < 0) return;
+    Pool& p = pool();
+    std::lock_guard<std::mutex> guard(p.lock);
+    p.taken &= ~(1u << index_);
+}
