@@ -579,6 +579,11 @@ __global__ __launch_bounds__(64 * kLightWaves) void agg_rowgroup_kernel(AggArgs 
     }
 }
 
+// A lane's four columns from `col` on, moved back to end with the row where they would reach over its end: nothing past a row is
+// read, at whatever pitch rows lie.  The lane then stores only those from `col` on (store_own).  Rows of fewer than four columns
+// are read with their padding.
+__device__ __forceinline__ int64_t own_columns(int64_t col, int64_t F) { return F >= 4 ? min(col, F - 4) : col; }
+
 // ---------------------------------------------------------------------------
 // sum / mean / gcn_sym of rows, or slabs, of 4 P columns: P = 8, 16 or 32 lanes of four floats hold a row, and the R = 64 / P
 // groups of a wave walk R rows of the schedule, or shares of one long row, in lock step (EntryWalk).  Long rows first in every
@@ -628,9 +633,9 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
     }
     weights();
 
-    const int col = (int)slab * (4 * P) + li * 4;
-    const bool act = col < a.F;
-    const int valid = min(4, (int)a.F - col);
+    const bool act = (int)slab * (4 * P) + li * 4 < a.F;
+    const int col = (int)own_columns((int)slab * (4 * P) + li * 4, a.F);
+    const int skip = (int)slab * (4 * P) + li * 4 - col, valid = min(4, (int)a.F);
     const table_t table = buffer_table(a.Z, a.table_bytes);
     const uint32_t colbytes = act ? (uint32_t)col * 4 : kNoEntry;      // (columns past the row width fetch nothing)
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -710,11 +715,11 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
         else if (a.scale == SCALE_GCN) x = x * a.dinv[v];
         r[k] = x;
     }
-    store_row<4>(orow + a.ocol + col, r, valid, a.out_vec != 0, a.out_half != 0);
+    store_own(orow + a.ocol + col, r, skip, valid, a.out_vec != 0, a.out_half != 0);
     if (a.copy_self) {
-        float zs[4];
-        load_row<4>(a.Z + (int64_t)v * a.ldz + col, zs);
-        store_row<4>(orow + col, zs, valid, a.self_vec != 0);
+        const f32x4u t = *reinterpret_cast<const f32x4u*>(a.Z + (int64_t)v * a.ldz + col);
+        const float zs[4] = {t.x, t.y, t.z, t.w};
+        store_own(orow + col, zs, skip, valid, a.self_vec != 0);
     }
 }
 
@@ -2045,19 +2050,32 @@ void launch_gat_scores(int64_t N, int64_t F, int heads, const float* Z, int64_t 
 
 namespace {
 
-// widest gather the layout of Z allows; a partial last vector may read
-// padding columns of the same row, so the padded width must fit in ldz
+// rows of Z start at 16-byte addresses and their last vector may read padding columns of the same row
+bool rows_padded(const AggCall& c) { return aligned_for(c.Z, c.ldz, 4) && align_up(c.F, 4) <= c.ldz; }
+
+// Sums, means and gcn_sym of up to 48 columns in row groups take four floats at any float's address, none of them past a row's end
+// (own_columns), where rows are neither aligned nor padded: mean in us, before and now, 1,000,000 nodes of 20 entries, 5
+// columns 645 and 367, 17 columns 631 and 520; 62 columns 1,030 and 1,050.  (Wider ones touch a line more per entry and slab: 301
+// columns in slabs of 64 4,106 and 5,180.)
+bool narrow_unpadded(const AggCall& c)
+{
+    const AggOptions& opt = agg_options();
+    return c.mode != RETEXO_GAT_SOFTMAX && c.mode != RETEXO_MAX && c.F >= 4 && c.F <= 48 && !rows_padded(c) &&
+           (c.plan->N * c.ldz + c.F) * 4 < (1ll << 32) && !opt.wide_offsets && opt.slab_cols == 0 && opt.max_vec >= 4 &&
+           !(c.plan->part_ptr && opt.parts >= 0);
+}
+
+// widest gather the layout of Z allows
 int gather_vec(const AggCall& c)
 {
-    int vec = 1;
-    if (aligned_for(c.Z, c.ldz, 4) && align_up(c.F, 4) <= c.ldz) vec = 4;
-    else if (aligned_for(c.Z, c.ldz, 2) && align_up(c.F, 2) <= c.ldz) vec = 2;
+    const bool two = aligned_for(c.Z, c.ldz, 2) && align_up(c.F, 2) <= c.ldz;
+    int vec = rows_padded(c) || narrow_unpadded(c) ? 4 : two ? 2 : 1;
     if (vec > agg_options().max_vec) vec = agg_options().max_vec >= 2 ? 2 : 1;
     if (c.mode == RETEXO_GAT_SOFTMAX && vec == 2) vec = 1;
     return vec;
 }
 
-// Which kernels a sum, mean or gcn_sym over rows of at least 16-byte alignment takes: the range walk over narrow slabs, row
+// Which kernels a sum, mean or gcn_sym takes whose rows are gathered four floats at a time: the range walk over narrow slabs, row
 // groups of `lanes` lanes over slabs of 4 * lanes columns, or (neither) whole rows.
 struct LinearRoute {
     bool ranges;
@@ -2088,6 +2106,7 @@ LinearRoute linear_route(const AggCall& c, int vec, int parts)
     const bool weighted = c.mode == RETEXO_GCN_SYM;
     if (vec != 4 || c.mode == RETEXO_MAX || c.mode == RETEXO_GAT_SOFTMAX || opt.slab_cols != 0) return {false, 0};
     const LinearRoute ranges = {true, 0}, whole = {false, 0};
+    if (narrow_unpadded(c)) return {false, F <= 32 ? 8 : 16};
     if (p->part_ptr && opt.parts >= 0) return ranges;              // (the caller said how many)
     const bool dense = p->part_ptr || (nnz >= 32 * N && N * c.ldz * 4 > (4ll << 20));
     auto mean_is = [&](int64_t entries) { return nnz >= entries * N; };
@@ -2095,7 +2114,7 @@ LinearRoute linear_route(const AggCall& c, int vec, int parts)
         const bool enough = N >= 24000 || work >= 1200000000ll || mean_is(300);
         if (F >= 100 ? enough && work >= 700000000ll && (mean_is(160) || mean_is((weighted ? 25 : 15) * parts))
             : F > 32 ? enough && work >= 600000000ll && mean_is(N >= 200000 ? 105 : 140)
-                     : N >= 30000 && mean_is(N >= 200000 ? 170 : N >= 110000 ? 230 : N >= 40000 ? 255 : 350))
+                     : N >= 30000 && mean_is(N >= 200000 ? 170 : N >= 110000 ? 230 : N >= 40000 || weighted ? 255 : 350))
             return ranges;
     }
     // one range of a large table: nearly the same (2,449,029 of 50, 32 columns, 729,742 of 36 476 and 516, 554,648 of 32, 64
@@ -2328,7 +2347,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
             else dispatch_grouped<32>(a, n_heavy, N, wtd, off32, stream);
         }
     } else if (linear.lanes) {
-        a.table_bytes = (uint32_t)(((N - 1) * c.ldz + align_up(c.F, 4)) * 4);
+        a.table_bytes = (uint32_t)(((N - 1) * c.ldz + (c.F < 4 ? 4 : c.F)) * 4);
         if (linear.lanes == 8)       launch_rows<8>(a, n_heavy, N, stream);
         else if (linear.lanes == 16) launch_rows<16>(a, n_heavy, N, stream);
         else                         launch_rows<32>(a, n_heavy, N, stream);

@@ -8,6 +8,7 @@ namespace {
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // at any float's address
 
 constexpr int kLightWaves = 4;   // independent rows per workgroup in the light kernels
 constexpr int kHeavyWaves = 8;   // cooperating waves per row in the heavy kernels
@@ -54,6 +55,19 @@ __device__ __forceinline__ void store_row(float* p, const float (&v)[VEC], int v
 #pragma unroll
         for (int k = 0; k < VEC; ++k)
             if (k < valid) p[k] = v[k];
+    }
+}
+
+// those of four floats that are the lane's own (see own_columns): [skip, valid)
+__device__ __forceinline__ void store_own(float* p, const float (&v)[4], int skip, int valid, bool vec_ok, bool half_ok = false)
+{
+    if (skip == 0 && valid == 4) {
+        if (vec_ok || half_ok) store_row<4>(p, v, 4, vec_ok, half_ok);
+        else *reinterpret_cast<f32x4u*>(p) = f32x4u{v[0], v[1], v[2], v[3]};
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k >= skip && k < valid) p[k] = v[k];
     }
 }
 

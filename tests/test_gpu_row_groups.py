@@ -3,6 +3,7 @@ after it, and sum, mean and gcn_sym, whose wider rows are walked in slabs, again
 counts that leave groups without a row, empty rows, long rows shared by a workgroup, rows padded or not."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2302_13053_amd import binding as B
@@ -89,6 +90,27 @@ def test_linear(graphs, name, F, mode):
     assert_cond_close(got[:, :want.shape[1]], want, oracle.aggregate_abs(mode, rp, ci, Zh[:, :F], F, **kw), what=mode)
     again = Hn.aggregate(g, mode, Hn.dev(Zh), F, concat=F % 2 == 1, ld_out=2 * F + 3).cpu().numpy()
     assert np.array_equal(got[:, :want.shape[1]], again[:, :want.shape[1]])
+
+
+@pytest.mark.parametrize("name", ["few", "edges", "skewed"])
+@pytest.mark.parametrize("F,ld,offset", [(4, 5, 1), (5, 5, 0), (7, 7, 2), (31, 31, 1), (33, 34, 0), (45, 45, 3), (48, 49, 0), (49, 49, 0)])
+def test_linear_unpadded(graphs, name, F, ld, offset):
+    """Rows at any float's address whose last four columns lie over the ones before them; the table ends with its last row's last
+    column, and what lies between the rows must not reach a sum."""
+    g, rp, ci = graphs[name]
+    n = g.n_nodes
+    Zh = np.full((n, ld), np.nan, np.float32)
+    Zh[:, :F] = wl.random_matrix(n, F, F)
+    buf = torch.zeros(offset + (n - 1) * ld + F, device="cuda")
+    Z = torch.as_strided(buf, (n, F), (ld, 1), offset)
+    Z.copy_(torch.from_numpy(Zh[:, :F].copy()))
+    for mode in ("sum", "mean", "gcn_sym"):
+        out = torch.full((n, 2 * F + 1), 777.0, device="cuda")
+        got = Hn.aggregate(g, mode, Z, F, concat=True, out=out).cpu().numpy()
+        want = oracle.aggregate(mode, rp, ci, Zh[:, :F], F, self_concat=True)
+        mag = oracle.aggregate_abs(mode, rp, ci, Zh[:, :F], F, self_concat=True)
+        assert_cond_close(got[:, :2 * F], want, mag, what=mode)
+        assert np.array_equal(got[:, :F], Zh[:, :F]) and np.all(got[:, 2 * F:] == 777.0)
 
 
 @pytest.mark.parametrize("heads,dh", [(4, 64), (5, 32), (2, 64)])
