@@ -10,6 +10,7 @@
 //
 // Kernels (each decodes 16-byte loads of eight elements per lane):
 //   * whole rows per wave, for sum / mean / gcn_sym / max        (any shape; scalar loads when unaligned)
+//   * several rows, or slabs of rows, per wave for sum / mean / gcn_sym (up to 128 columns; any width at 4-byte addresses)
 //   * 64-column slabs, one row per 8-lane group, walked source range by source range so that the
 //     slab of the current range stays in L2 (dense graphs; same plan split as the fp32 path)
 //   * edge softmax, whole rows per wave, software-pipelined with per-edge weights in LDS
@@ -253,7 +254,10 @@ struct StoredArgs {
     int64_t n_rows;
     int part_lo, part_hi;
     int first, last;
-    uint32_t table_bytes;    // up to the end of the last row's last vector (narrow slabs: below 4 GiB)
+    uint32_t table_bytes;    // up to the end of the last row's last vector (narrow slabs and row groups: below 4 GiB)
+    int own_rows;            // rows hold whole vectors of eight elements (see stored_rows_kernel)
+    uint32_t slab_blocks;    // workgroups per slab of stored_rows_kernel, heavy_rows of them with one row each
+    int64_t heavy_rows;
 };
 
 // ---------------------------------------------------------------------------
@@ -525,6 +529,141 @@ __global__ __launch_bounds__(64 * kLightWaves) void stored_rowgroup_kernel(Store
         float zs[8];
         load_stored<FMT, 8>(a.Z + (int64_t)v * a.ldz + col, zs);
         store_floats<8>(orow + col, zs, valid, a.self_vec != 0);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// sum / mean / gcn_sym of rows, or slabs, of 8 P columns: P lanes of eight elements hold a row, and the R = 64 / P groups of a
+// wave walk R rows of the schedule, or shares of one long row, in lock step (EntryWalk).  Long rows first in every slab, one per
+// workgroup, their shares added up over the groups and then over the waves in order; one launch for both classes.
+// Bound by memory latency on small graphs, where R rows wait together, and by the gathered lines on large ones.
+// rows_lanes says where it is taken, and what it measures.
+// ---------------------------------------------------------------------------
+template <int FMT, int P, bool WEIGHTED>
+__global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArgs a)
+{
+    constexpr int U = 8, R = 64 / P, NW = kHeavyWaves, PER = U / 4;    // entries and lanes of a batch
+    const int lane = threadIdx.x & 63, li = lane % P, g = lane / P;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t slab = blockIdx.x / a.slab_blocks, block = blockIdx.x % a.slab_blocks;
+    const bool heavy = block < a.heavy_rows;          // uniform over the workgroup
+    const int64_t first = heavy ? (int64_t)block : a.heavy_rows + ((int64_t)(block - (uint32_t)a.heavy_rows) * NW + wave) * R;
+    if (first >= a.n_rows) return;
+    const int64_t slot = heavy ? first : first + g;
+    const bool have = slot < a.n_rows;
+    int v = 0;
+    uint32_t lo = 0, hi = 0;
+    if (have) {
+        v = a.order[slot];
+        lo = (uint32_t)a.row_ptr[v];
+        hi = (uint32_t)a.row_ptr[v + 1];
+    }
+    typedef EntryWalk<P, WEIGHTED> Walk;
+    Walk walk;
+    const uint32_t rowbytes = (uint32_t)(a.ldz * 2);
+    int batches = heavy ? walk.start(a.col_idx, lo + Walk::kTile * (wave * R + g), hi, Walk::kTile * NW * R, rowbytes)
+                        : walk.start(a.col_idx, lo, hi, Walk::kTile, rowbytes);
+    batches = (batches + PER - 1) / PER;
+    // the weights of the current tile's entries, requested with its first gathers, and of the one before it
+    float w_cur[4] = {0.0f, 0.0f, 0.0f, 0.0f}, w_prev[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto weights = [&]() {
+        if constexpr (WEIGHTED) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                w_prev[k] = w_cur[k];
+                w_cur[k] = walk.id[k] != kNoEntry ? a.wsrc[walk.id[k]] : 0.0f;
+            }
+        }
+    };
+    weights();
+
+    // eight columns from `col` on, moved back to end with the row where its padding does not hold them all (see own_columns)
+    const int col0 = (int)slab * (8 * P) + li * 8, F = (int)a.F;
+    const bool act = col0 < F;
+    const int col = a.own_rows ? col0 : min(col0, F - 8), skip = col0 - col, valid = min(8, F - col);
+    const table_t table = buffer_table(a.Z, a.table_bytes);
+    const uint32_t colbytes = act ? (uint32_t)col * 2 : kNoEntry;      // (columns past the row width fetch nothing)
+    const float one = WEIGHTED ? 1.0f : register_one();
+    float acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+    u32x4 z[2][U];
+    constexpr int kBatches = P / PER;                                   // of a tile
+    auto issue = [&](int k, u32x4 (&zz)[U]) {                           // batch k
+        const int j = k % kBatches;
+        if (j == 0 && k > 0) {
+            walk.take();
+            weights();
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t) zz[t] = load_entry(table, walk.at(j * PER + t / 4, t % 4), colbytes);
+    };
+    auto consume = [&](int k, const u32x4 (&zz)[U]) {
+        // (the next tile's weights have taken the place of this one's when its last batch is added up)
+        const bool old = (k + 1) % kBatches == 0 && k + 1 < batches;
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            float w = one;
+            if constexpr (WEIGHTED)
+                w = __int_as_float(__builtin_amdgcn_ds_bpermute(walk.gaddr + 4 * (k % kBatches * PER + t / 4),
+                                                                __float_as_int(old ? w_prev[t % 4] : w_cur[t % 4])));
+            add8<FMT, WEIGHTED>(zz[t], w, acc);
+        }
+    };
+    if (batches > 0) issue(0, z[0]);
+    for (int k = 0; k < batches; k += 2) {
+        if (k + 1 < batches) issue(k + 1, z[1]);
+        consume(k, z[0]);
+        if (k + 1 >= batches) break;
+        if (k + 2 < batches) issue(k + 2, z[0]);
+        consume(k + 1, z[1]);
+    }
+
+    if (heavy) {
+#pragma unroll
+        for (int b = P; b < 64; b <<= 1)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc[k] += __shfl_xor(acc[k], b, 64);
+        __shared__ float red[NW][8][P];
+        if (g == 0) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) red[wave][k][li] = acc[k];
+        }
+        __syncthreads();
+        if (wave != 0 || g != 0) return;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            acc[k] = red[0][k][li];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) acc[k] += red[w][k][li];
+        }
+    }
+    if (!have || !act) return;
+    const int d = (int)(hi - lo);
+    float* orow = a.out + (int64_t)v * a.ldo;
+    const float dinv = a.scale == 2 ? a.dinv[v] : 1.0f;
+    float r[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        float x = acc[k];
+        if (a.scale == 1) x = d > 0 ? x / (float)d : 0.0f;
+        else if (a.scale == 2) x = x * dinv;
+        r[k] = x;
+    }
+    auto store = [&](float* p, const float (&x)[8], bool vec_ok, bool half_ok) {
+        if (skip == 0) {
+            store_floats<8>(p, x, valid, vec_ok, half_ok);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k >= skip) p[k] = x[k];
+        }
+    };
+    store(orow + a.ocol + col, r, a.out_vec != 0, a.out_half != 0);
+    if (a.copy_self) {
+        float zs[8];
+        decode8<FMT>(load_entry(table, (uint32_t)v * rowbytes, colbytes), zs);
+        store(orow + col, zs, a.self_vec != 0, false);
     }
 }
 
@@ -1039,6 +1178,19 @@ void dispatch_linear(int nc, const StoredArgs& a, int64_t nh, int64_t N, hipStre
     else launch_pair(stored_linear_kernel<FMT, E, 2, 1, MAXOP>, stored_linear_kernel<FMT, E, 2, kHeavyWaves, MAXOP>, a, nh, N, s);
 }
 
+template <int FMT, int P>
+void launch_rows(const StoredArgs& base, const retexo_plan* p, hipStream_t stream)
+{
+    StoredArgs a = base;
+    const int64_t rows = kHeavyWaves * (64 / P), N = p->N, n_heavy = long_rows(p, a.F, false);
+    a.heavy_rows = n_heavy;
+    a.nslab = (int)((a.F + 8 * P - 1) / (8 * P));
+    a.slab_blocks = (uint32_t)(n_heavy + (N - n_heavy + rows - 1) / rows);
+    const dim3 grid(a.slab_blocks * (unsigned)a.nslab), block(64 * kHeavyWaves);
+    if (a.wsrc) stored_rows_kernel<FMT, P, true><<<grid, block, 0, stream>>>(a);
+    else        stored_rows_kernel<FMT, P, false><<<grid, block, 0, stream>>>(a);
+}
+
 template <int FMT, int E, int HP, bool HU>
 void dispatch_gat(int nc, const StoredArgs& a, int64_t nh, int64_t N, hipStream_t s)
 {
@@ -1049,6 +1201,39 @@ void dispatch_gat(int nc, const StoredArgs& a, int64_t nh, int64_t N, hipStream_
 bool aligned_rows(const void* p, int64_t ld_elems, int bytes_per_elem)
 {
     return ((uintptr_t)p % 16) == 0 && (ld_elems * bytes_per_elem) % 16 == 0;
+}
+
+// Lanes of eight elements that hold a row, or a slab, of a sum, mean or gcn_sym in row groups; 0: the range walk (`ranges`, over
+// `parts` ranges) or whole rows.  bf16 mean in us, row groups against the others, over 29 graphs of 3,000 to 2,400,000 nodes:
+//  Rows that 16-byte loads can't take whole (an element per lane in whole rows): always, 1,000,000 nodes of 20 entries, 30
+//  columns 521 and 639, 232,965 of 490 1,075 and 2,430; 60,000 of 250, 130 columns 381 and 767, 250 columns 838 and 1,039.
+//  Others of up to 128 columns instead of whole rows: 1,000,000 of 20, 32 columns 395 and 745, 64 columns 432 and 790, 128
+//  columns 778 and 960; 100,000 of 8 15 and 48, 22 and 49, 40 and 51; 30,000 of 300, 64 columns 55 and 255.  Wider ones of
+//  graphs with a few long rows, which are walked here beside the others (19,677 of 30, longest 1,743, 512 columns 87 and 310;
+//  172,021 of 10, 608 columns 492 and 1,166), but 1,330,144 of 5, 512 columns 2,846 and 2,385, and with all rows alike 1,000,000
+//  of 8, 256 columns 947 and 912: the line is where drawn calls stop to gain (0.53
+//  of the time at 65,000 nodes, 0.83 at 260,000, 1.03 at 520,000).
+//  Instead of the range walk where a row's share of a range is short: 600,000 of 120 (7 per range) 1,127 and 1,448, 1,003,546
+//  of 80 (5), 64 columns 1,483 and 3,670, 576,484 of 113 (7), 96 columns 2,069 and 3,946; the other way 400,000 of 150 (19) 800
+//  and 678, 150,000 of 200 (50), 64 columns 355 and 251, with weights 386,048 of 112 (14) 1,012 and 832.  Not in one range, which
+//  takes the longest rows apart: 59,657 of 263, longest 5,419, 265 and 110; but 1,330,759 of 85, 104 columns 5,328 and 5,836.
+int rows_lanes(const StoredCall& c, bool wide, bool own_rows, bool ranges, int parts)
+{
+    const retexo_plan* p = c.plan;
+    const AggOptions& opt = agg_options();
+    const int64_t N = p->N, nnz = p->nnz, F = c.F;
+    const bool weighted = c.mode == RETEXO_GCN_SYM;
+    if (opt.slab_cols != 0 || opt.max_vec < 4 || (p->part_ptr && opt.parts >= 0)) return 0;      // (the caller said how)
+    const int lanes = F <= 32 ? 4 : F <= 64 ? 8 : F <= 128 ? 16 : 32;
+    if (weighted && F > 64 && N < 8192 && nnz < 100 * N) return 0;      // (weights wait for ids: 3,000 of 60, 128 columns 10.4 and 9.9)
+    if (!wide) {
+        const bool any = (uintptr_t)c.Z % 4 == 0 && c.ldz % 2 == 0 && (own_rows || (F >= 8 && F % 2 == 0));
+        return any ? lanes : 0;
+    }
+    if (!ranges) return F <= 128 || N < 250000 ? lanes : 0;
+    if (F > 128) return 0;
+    if (parts > 1) return nnz < N * parts * (weighted ? 12 : F > 32 ? 14 : 10) ? lanes : 0;
+    return F > 64 && N >= 600000 ? lanes : 0;
 }
 
 template <int FMT>
@@ -1097,6 +1282,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     a.first = 1;
     a.last = 1;
     a.table_bytes = 0;
+    a.own_rows = align_up(F, 8) <= c.ldz;
 
     const int64_t n_heavy = long_rows(p, F, true);
 
@@ -1112,15 +1298,25 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     bool narrow = linear_sum && wide && off32 && (p->part_ptr || (p->nnz >= 32 * N && N * c.ldz * 2 > (4ll << 20)));
     if (opt.slab_cols > 64) narrow = false;
     if (opt.slab_cols == 64 && linear_sum && wide && off32) narrow = true;
-    if (narrow) {
-        a.table_bytes = (uint32_t)(((N - 1) * c.ldz + align_up(F, 8)) * 2);
-        a.nslab = (int)((F + 63) / 64);
-        int parts = (int)opt.parts;
+    // workgroups of the range walk read their share of one source range after the other
+    int parts = 1;
+    if (narrow && p->part_ptr) {
+        parts = (int)opt.parts;
         if (parts < 0) {
             parts = 1;
             while (parts < kMaxParts && N * 128 > (int64_t)parts * (8ll << 20)) parts *= 2;
         }
-        if (!p->part_ptr || (parts != 2 && parts != 4 && parts != 8 && parts != 16)) parts = 1;
+        if (parts != 2 && parts != 4 && parts != 8 && parts != 16) parts = 1;
+    }
+    if (const int lanes = linear_sum && off32 ? rows_lanes(c, wide, a.own_rows != 0, narrow, parts) : 0) {
+        a.table_bytes = (uint32_t)(((N - 1) * c.ldz + (a.own_rows ? align_up(F, 8) : F)) * 2);
+        if (lanes == 4)       launch_rows<FMT, 4>(a, p, stream);
+        else if (lanes == 8)  launch_rows<FMT, 8>(a, p, stream);
+        else if (lanes == 16) launch_rows<FMT, 16>(a, p, stream);
+        else                  launch_rows<FMT, 32>(a, p, stream);
+    } else if (narrow) {
+        a.table_bytes = (uint32_t)(((N - 1) * c.ldz + align_up(F, 8)) * 2);
+        a.nslab = (int)((F + 63) / 64);
         if (parts > 1) a.part_ptr = p->part_ptr;
         // rows whose share of one range is long get a workgroup each
         int64_t n_long = 0;

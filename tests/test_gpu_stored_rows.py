@@ -1,0 +1,56 @@
+"""Sum, mean and gcn_sym over 16-bit tables, several rows (or shares of a long row) per wave: one lane count after the other, rows
+that end with a lane's batch, a group or a tile of the walk, empty rows, long rows shared by a workgroup, slabs with a last one
+that is not full, rows padded or, at 4-byte addresses, with their last eight columns over the ones before them."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import storage as ost
+from paper_2302_13053_amd import harness as Hn
+from paper_2302_13053_amd import workloads as wl
+from parity import assert_cond_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def graphs():
+    src, dst, at = [], [], 600
+    for c, d in enumerate((15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 7, 8, 9)):
+        for leaf in range(d):
+            src.append(c), dst.append(20 + (at + leaf) % 1000)
+        at += d
+    specs = {"edges": (1027, np.array(src, np.int32), np.array(dst, np.int32)),
+             "skewed": (9001, *wl.random_pairs(9001, 40000, 2, skew=3.0)),
+             "dense": (3001, *wl.random_pairs(3001, 180000, 3, skew=0.5))}
+    out = {}
+    for name, (n, s, d) in specs.items():
+        out[name] = (Hn.make_plan(Hn.csr_from_coo(Hn.dev(s), Hn.dev(d), n, False)), *oracle.csr_from_coo(s, d, n, False))
+    assert (np.diff(out["edges"][1]) == 0).any() and np.diff(out["skewed"][1]).max() > 1000
+    yield out
+    for g, _, _ in out.values():
+        g.destroy()
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+@pytest.mark.parametrize("name", ["edges", "skewed", "dense"])
+@pytest.mark.parametrize("F,ld,offset", [(1, 8, 0), (8, 8, 0), (31, 32, 0), (32, 34, 2), (33, 40, 0), (64, 64, 0), (50, 50, 0),
+                                         (65, 72, 0), (130, 130, 2), (200, 200, 0), (300, 302, 0), (602, 602, 0)])
+def test_stored_row_groups(graphs, name, fmt, F, ld, offset):
+    g, rp, ci = graphs[name]
+    n = g.n_nodes
+    Zh = wl.random_matrix(n, F, F)
+    bits = ost.store(Zh, fmt)
+    stored = ost.load(bits, fmt)
+    # what lies between the rows (NaN) must not reach a result; without padding the table ends with its last row's last column
+    padded = -(-F // 8) * 8 <= ld
+    buf = torch.full((offset + (n - 1) * ld + (ld if padded else F),), -1, dtype=torch.int16, device="cuda")
+    Z = torch.as_strided(buf, (n, F), (ld, 1), offset)
+    Z.copy_(torch.from_numpy(bits.view(np.int16)))
+    for mode in ("sum", "mean", "gcn_sym"):
+        out = torch.full((n, 2 * F + 1), 777.0, device="cuda")
+        got = Hn.aggregate_stored(g, mode, Z, F, fmt, concat=True, out=out).cpu().numpy()
+        want = oracle.aggregate(mode, rp, ci, stored, F, self_concat=True)
+        assert_cond_close(got[:, :2 * F], want, oracle.aggregate_abs(mode, rp, ci, stored, F, self_concat=True), what=mode)
+        assert np.array_equal(got[:, :F].astype(np.float64), want[:, :F]) and np.all(got[:, 2 * F:] == 777.0)
