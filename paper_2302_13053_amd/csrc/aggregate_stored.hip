@@ -14,6 +14,7 @@
 //   * 64-column slabs, one row per 8-lane group, walked source range by source range so that the
 //     slab of the current range stays in L2 (dense graphs; same plan split as the fp32 path)
 //   * edge softmax, whole rows per wave, software-pipelined with per-edge weights in LDS
+//   * edge softmax, several rows per wave, scores from the gathered rows (heads of a power of two of four-element lanes)
 #include <algorithm>
 
 #include "common.hpp"
@@ -1151,6 +1152,167 @@ __global__ __launch_bounds__(64 * kLightWaves) void stored_gat_flash_kernel(Stor
 }
 
 // ---------------------------------------------------------------------------
+// The same for several rows per wave: P lanes of four elements hold a row, and the R = 64 / P groups of a wave walk R rows of the
+// schedule, or shares of one long row, in lock step (EntryWalk); a group whose row has ended weighs its batches' entries with
+// zero.  Destination scores come from a row's own elements, so nothing is launched before it, and long rows, one per workgroup
+// with their shares merged over the groups and then over the waves in order, run beside the others.
+// bf16 in us, scores, long rows and a wave per row before, and now: 32 columns 2,145,631 nodes of 7 entries 1,946 and 537,
+// 15,346 of 12 84 and 15; 64 columns 2,222,171 of 51 7,527 and 2,379 (6.2 TB/s of lines), 164,453 of 436 4,188 and 987; 128
+// columns 475,093 of 56 1,894 and 939; 256 columns, where a wave is a row either way, 29,969 of 22, longest 2,604, 186 and 90,
+// 1,911,625 of 60 9,910 and 8,877.  1,685 drawn calls: 0.47 of the time.
+// ---------------------------------------------------------------------------
+template <int FMT, int G, int P>
+__global__ __launch_bounds__(64 * kHeavyWaves) void stored_gat_rows_kernel(StoredArgs a, const float* __restrict__ attn_src,
+                                                                           const float* __restrict__ attn_dst)
+{
+    constexpr int U = 4, R = 64 / P, NW = kHeavyWaves;
+    constexpr float kLog2e = 1.4426950408889634f;
+    const int lane = threadIdx.x & 63, li = lane % P, g = lane / P;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool heavy = blockIdx.x < a.heavy_rows;     // uniform over the workgroup
+    const int64_t first = heavy ? (int64_t)blockIdx.x : a.heavy_rows + ((int64_t)(blockIdx.x - (uint32_t)a.heavy_rows) * NW + wave) * R;
+    if (first >= a.n_rows) return;
+    const int64_t slot = heavy ? first : first + g;
+    const bool have = slot < a.n_rows;
+    int v = 0;
+    uint32_t lo = 0, hi = 0;
+    if (have) {
+        v = a.order[slot];
+        lo = (uint32_t)a.row_ptr[v];
+        hi = (uint32_t)a.row_ptr[v + 1];
+    }
+    constexpr uint32_t kTile = EntryWalk<P>::kTile;
+    EntryWalk<P> walk;
+    const uint32_t rowbytes = (uint32_t)(a.ldz * 2);
+    const int batches = heavy ? walk.start(a.col_idx, lo + kTile * (wave * R + g), hi, kTile * NW * R, rowbytes)
+                              : walk.start(a.col_idx, lo, hi, kTile, rowbytes);
+
+    const int col = li * 4;
+    const bool act = col < a.F;
+    const table_t table = buffer_table(a.Z, a.table_bytes);
+    const uint32_t colbytes = act ? (uint32_t)col * 2 : kNoEntry;      // (columns past the row width fetch nothing)
+    auto load = [&](uint32_t row) {
+        return __builtin_amdgcn_raw_buffer_load_b64(table, __builtin_elementwise_add_sat(row, colbytes), 0, 0);
+    };
+    auto decode = [&](const u32x2& raw, float (&z)[4]) {
+        if constexpr (FMT == FMT_BF16) {
+            z[0] = __uint_as_float(raw.x << 16); z[1] = __uint_as_float(raw.x & 0xffff0000u);
+            z[2] = __uint_as_float(raw.y << 16); z[3] = __uint_as_float(raw.y & 0xffff0000u);
+        } else {
+            z[0] = decode1<FMT>((uint16_t)raw.x); z[1] = decode1<FMT>((uint16_t)(raw.x >> 16));
+            z[2] = decode1<FMT>((uint16_t)raw.y); z[3] = decode1<FMT>((uint16_t)(raw.y >> 16));
+        }
+    };
+    auto dot = [](const f32x4& w, const float (&z)[4]) {
+        float d = w.x * z[0];
+        d = fmaf(w.y, z[1], d);
+        d = fmaf(w.z, z[2], d);
+        return fmaf(w.w, z[3], d);
+    };
+    // exponents are kept in units of log2(e): exp(x) = exp2(x * log2(e)), and the leaky step commutes with the factor
+    f32x4 as = {0.0f, 0.0f, 0.0f, 0.0f}, ad = as;
+    if (act) {
+        as = *reinterpret_cast<const f32x4*>(attn_src + col) * kLog2e;        // [heads, Dh] is F contiguous floats
+        ad = *reinterpret_cast<const f32x4*>(attn_dst + col) * kLog2e;
+    }
+    float own[4];
+    const u32x2 own_raw = load(have ? (uint32_t)v * rowbytes : kNoEntry);
+    decode(own_raw, own);
+    const float erv = group_sum<G>(dot(ad, own));
+
+    const bool empty = (heavy ? lo + kTile * (wave * R + g) : lo) >= hi;      // no entry: its maximum stays -infinity
+    float m = -INFINITY, s = 0.0f;
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    u32x2 z[2][U];
+    uint32_t on[2][U];
+    auto consume = [&](const u32x2 (&zz)[U], const uint32_t (&oo)[U]) {
+        float zq[U][4], sc[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            decode(zz[t], zq[t]);
+            const float x = group_sum<G>(dot(as, zq[t])) + erv;
+            sc[t] = oo[t] != kNoEntry ? (x > 0.0f ? x : a.slope * x) : -INFINITY;
+        }
+        float mn = m;
+#pragma unroll
+        for (int t = 0; t < U; ++t) mn = fmaxf(mn, sc[t]);
+        const float mr = empty ? 0.0f : mn;
+        const float scale = __builtin_amdgcn_exp2f(m - mr);
+        float pw[U], ps = 0.0f;
+#pragma unroll
+        for (int t = 0; t < U; ++t) { pw[t] = __builtin_amdgcn_exp2f(sc[t] - mr); ps += pw[t]; }
+        s = s * scale + ps;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] *= scale;
+#pragma unroll
+        for (int t = 0; t < U; ++t)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] = fmaf(pw[t], zq[t][k], acc[k]);
+        m = mn;
+    };
+    // the gathers of a batch are issued before the batch before it is added up
+    auto step = [&](int k, u32x2 (&zn)[U], uint32_t (&no)[U]) {       // batch k
+        if (k % P == 0 && k > 0) walk.take();
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            no[t] = walk.at(k % P, t);
+            zn[t] = load(no[t]);
+        }
+    };
+    if (batches > 0) step(0, z[0], on[0]);
+    for (int k = 0; k < batches; k += 2) {
+        if (k + 1 < batches) step(k + 1, z[1], on[1]);
+        consume(z[0], on[0]);
+        if (k + 1 >= batches) break;
+        if (k + 2 < batches) step(k + 2, z[0], on[0]);
+        consume(z[1], on[1]);
+    }
+
+    if (heavy) {
+        // merge the shares: groups of the wave, then the waves; one that saw no entry has m = -inf and weighs nothing
+        auto weight = [](float mw, float mm) { return mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - mm); };
+#pragma unroll
+        for (int b = P; b < 64; b <<= 1) {
+            const float mo = __shfl_xor(m, b, 64), mm = fmaxf(m, mo), fa = weight(m, mm), fb = weight(mo, mm);
+            auto join = [&](float x) { return x * fa + __shfl_xor(x, b, 64) * fb; };
+            s = join(s);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] = join(acc[k]);
+            m = mm;
+        }
+        __shared__ float red[NW][6][P];
+        if (g == 0) {
+            red[wave][0][li] = m;
+            red[wave][1][li] = s;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) red[wave][2 + k][li] = acc[k];
+        }
+        __syncthreads();
+        if (wave != 0 || g != 0) return;
+        float mm = red[0][0][li];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) mm = fmaxf(mm, red[w][0][li]);
+        s = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float f = weight(red[w][0][li], mm);
+            s = fmaf(red[w][1][li], f, s);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[k] = fmaf(red[w][2 + k][li], f, acc[k]);
+        }
+    }
+    if (!have || !act) return;
+    float* orow = a.out + (int64_t)v * a.ldo;
+    float r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = s > 0.0f ? acc[k] / s : 0.0f;
+    store_floats<4>(orow + a.ocol + col, r, 4, a.out_vec != 0, a.out_half != 0);
+    if (a.copy_self) store_floats<4>(orow + col, own, 4, a.self_vec != 0);
+}
+
+// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 template <typename K, typename KH>
@@ -1189,6 +1351,28 @@ void launch_rows(const StoredArgs& base, const retexo_plan* p, hipStream_t strea
     const dim3 grid(a.slab_blocks * (unsigned)a.nslab), block(64 * kHeavyWaves);
     if (a.wsrc) stored_rows_kernel<FMT, P, true><<<grid, block, 0, stream>>>(a);
     else        stored_rows_kernel<FMT, P, false><<<grid, block, 0, stream>>>(a);
+}
+
+template <int FMT, int G, int P>
+void launch_gat_rows(const StoredArgs& base, const retexo_plan* p, const float* attn_src, const float* attn_dst, hipStream_t stream)
+{
+    if constexpr (G <= P && G * kMaxHeads > P / 2) {
+        StoredArgs a = base;
+        const int64_t rows = kHeavyWaves * (64 / P), N = p->N, n_heavy = long_rows(p, a.F, false, true);
+        a.heavy_rows = n_heavy;
+        const unsigned blocks = (unsigned)(n_heavy + (N - n_heavy + rows - 1) / rows);
+        stored_gat_rows_kernel<FMT, G, P><<<dim3(blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a, attn_src, attn_dst);
+    }
+}
+template <int FMT, int G>
+void dispatch_gat_rows(const StoredArgs& a, const retexo_plan* p, const float* as, const float* ad, hipStream_t stream)
+{
+    switch (row_lanes(a.F)) {
+        case 8:  launch_gat_rows<FMT, G, 8>(a, p, as, ad, stream); break;
+        case 16: launch_gat_rows<FMT, G, 16>(a, p, as, ad, stream); break;
+        case 32: launch_gat_rows<FMT, G, 32>(a, p, as, ad, stream); break;
+        default: launch_gat_rows<FMT, G, 64>(a, p, as, ad, stream); break;
+    }
 }
 
 template <int FMT, int E, int HP, bool HU>
@@ -1356,6 +1540,26 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
         else if (E == 4) { if (maxop) dispatch_linear<FMT, 4, true>(nc, a, n_heavy, N, stream); else dispatch_linear<FMT, 4, false>(nc, a, n_heavy, N, stream); }
         else             { if (maxop) dispatch_linear<FMT, 1, true>(nc, a, n_heavy, N, stream); else dispatch_linear<FMT, 1, false>(nc, a, n_heavy, N, stream); }
     } else {
+        // rows of ordinary length compute the source scores from the gathered rows (see the kernel)
+        const int g = a.Dh / 4;
+        const bool flash = E == 4 && opt.gat_flash && a.Dh % 4 == 0 && g <= 64 && (g & (g - 1)) == 0 &&
+                           (uintptr_t)c.attn_src % 16 == 0;
+        // (not over 4 GiB and more, whose byte offsets take 64 bits)
+        const bool rows = flash && off32 && (uintptr_t)c.attn_dst % 16 == 0;
+        if (rows) {
+            a.table_bytes = (uint32_t)(((N - 1) * c.ldz + align_up(F, 4)) * 2);
+            switch (g) {
+                case 1:  dispatch_gat_rows<FMT, 1>(a, p, c.attn_src, c.attn_dst, stream); break;
+                case 2:  dispatch_gat_rows<FMT, 2>(a, p, c.attn_src, c.attn_dst, stream); break;
+                case 4:  dispatch_gat_rows<FMT, 4>(a, p, c.attn_src, c.attn_dst, stream); break;
+                case 8:  dispatch_gat_rows<FMT, 8>(a, p, c.attn_src, c.attn_dst, stream); break;
+                case 16: dispatch_gat_rows<FMT, 16>(a, p, c.attn_src, c.attn_dst, stream); break;
+                case 32: dispatch_gat_rows<FMT, 32>(a, p, c.attn_src, c.attn_dst, stream); break;
+                default: dispatch_gat_rows<FMT, 64>(a, p, c.attn_src, c.attn_dst, stream); break;
+            }
+            if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;
+            return RETEXO_OK;
+        }
         const int hp = heads_padded(c.heads);
         const GatWorkspace w = gat_workspace(N, F, c.heads, false);
         float* el = (float*)((char*)c.workspace + w.el);
@@ -1374,10 +1578,6 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
             else stored_scores_kernel<FMT, 8><<<dim3(gb), dim3(256), 0, stream>>>(N, F, a.Dh, Z, c.ldz, c.attn_src, c.attn_dst, el, er);
         }
         const bool hu = (a.Dh % E) == 0;
-        // rows of ordinary length compute the source scores from the gathered rows (see the kernel)
-        const int g = a.Dh / 4;
-        const bool flash = E == 4 && opt.gat_flash && a.Dh % 4 == 0 && g <= 64 && (g & (g - 1)) == 0 &&
-                           (uintptr_t)c.attn_src % 16 == 0;
         int64_t n_table = N;          // rows [0, n_table) of the schedule go through the table kernels
         if (flash && N > n_heavy) {
             StoredArgs f = a;

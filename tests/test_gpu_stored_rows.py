@@ -1,4 +1,4 @@
-"""Sum, mean and gcn_sym over 16-bit tables, several rows (or shares of a long row) per wave: one lane count after the other, rows
+"""Sum, mean, gcn_sym and edge softmax over 16-bit tables, several rows (or shares of a long row) per wave: one lane count after the other, rows
 that end with a lane's batch, a group or a tile of the walk, empty rows, long rows shared by a workgroup, slabs with a last one
 that is not full, rows padded or, at 4-byte addresses, with their last eight columns over the ones before them."""
 import numpy as np
@@ -9,7 +9,7 @@ import oracle
 from oracle import storage as ost
 from paper_2302_13053_amd import harness as Hn
 from paper_2302_13053_amd import workloads as wl
-from parity import assert_cond_close
+from parity import assert_close, assert_cond_close
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +54,28 @@ def test_stored_row_groups(graphs, name, fmt, F, ld, offset):
         want = oracle.aggregate(mode, rp, ci, stored, F, self_concat=True)
         assert_cond_close(got[:, :2 * F], want, oracle.aggregate_abs(mode, rp, ci, stored, F, self_concat=True), what=mode)
         assert np.array_equal(got[:, :F].astype(np.float64), want[:, :F]) and np.all(got[:, 2 * F:] == 777.0)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+@pytest.mark.parametrize("name", ["edges", "skewed", "dense"])
+@pytest.mark.parametrize("heads,dh,pad", [(1, 4, 0), (3, 8, 8), (8, 4, 0), (1, 64, 0), (3, 16, 0), (5, 16, 4), (2, 64, 0),
+                                          (1, 256, 0), (3, 64, 8), (8, 32, 0)])
+def test_stored_softmax_row_groups(graphs, name, fmt, heads, dh, pad):
+    """Groups of 8, 16, 32 and 64 lanes, full and not, the smallest and largest heads in each."""
+    g, rp, ci = graphs[name]
+    n, F = g.n_nodes, heads * dh
+    ld = -(-F // 8) * 8 + pad
+    Zh = wl.random_matrix(n, F, F)
+    bits = np.full((n, ld), -1, np.int16)                     # NaN between the rows
+    bits[:, :F] = ost.store(Zh, fmt).view(np.int16)
+    stored = ost.load(ost.store(Zh, fmt), fmt)
+    a = [wl.random_matrix(heads, dh, k) * np.float32(0.3) for k in (1, 2)]
+    out = torch.full((n, 2 * F + 1), 777.0, device="cuda")
+    kw = dict(heads=heads, a_src=Hn.dev(a[0]), a_dst=Hn.dev(a[1]))
+    got = Hn.aggregate_stored(g, "gat_softmax", torch.from_numpy(bits).cuda(), F, fmt, concat=True, out=out, **kw).cpu().numpy()
+    okw = dict(heads=heads, a_src=a[0], a_dst=a[1], self_concat=True)
+    want = oracle.aggregate("gat_softmax", rp, ci, stored, F, **okw)
+    assert_cond_close(got[:, :2 * F], want, oracle.aggregate_abs("gat_softmax", rp, ci, stored, F, **okw), what="softmax")
+    if F >= 64:
+        assert_close(got[:, :2 * F], want, what="softmax, row by row")
+    assert np.array_equal(got[:, :F].astype(np.float64), want[:, :F]) and np.all(got[:, 2 * F:] == 777.0)
