@@ -2118,8 +2118,9 @@ LinearRoute linear_route(const AggCall& c, int vec, int parts)
             return ranges;
     }
     // one range of a large table: nearly the same (2,449,029 of 50, 32 columns, 729,742 of 36 476 and 516, 554,648 of 32, 64
-    // columns 562 and 619)
-    if (dense && !p->part_ptr && (F <= 32 ? N >= 350000 : F <= 64 && !weighted && N >= 200000 && N < 1000000)) return ranges;
+    // columns 562 and 619), where half of a row's lane group is idle from fewer nodes on (drawn calls of 250,000 to 350,000 nodes of
+    // 32 to 64 entries, row groups against it: up to 16 columns 1.06 of the time, 17 to 32 columns 0.95)
+    if (dense && !p->part_ptr && (F <= 32 ? N >= (F <= 16 ? 200000 : 350000) : F <= 64 && !weighted && N >= 200000 && N < 1000000)) return ranges;
     if ((N * c.ldz + F) * 4 >= (1ll << 32) || opt.wide_offsets)              // (row groups have 32-bit offsets)
         return dense && !(weighted && parts == 1) ? ranges : whole;
     auto in_slabs = [&](int lanes) {

@@ -71,7 +71,7 @@ AggOptions& agg_options();
 // graph of 108,393 entries and 256 columns the longest row's 320 entries alone took 57 us of an aggregation that needs 20.
 // Kernels that need a launch of their own for the long rows, one after the other (own_launch), pay for it with a launch
 // and with the time in which the long rows run alone: the line lies four times as high for the smallest, twice otherwise
-// (edge softmax of 16-bit tables or unaligned rows, and the backward's first pass).  The edge softmax in one launch
+// (whole rows of 16-bit tables, edge softmax of unaligned rows, and the backward's first pass).  The edge softmax in one launch
 // (`softmax`) takes the lower line as well, but for graphs whose mean row is long itself
 // (kLongMean entries): there the short rows fill the chip to the end (3,000 nodes of 150 entries, up to 300: 64 columns
 // forward and backward 140 us with the line at twice the mean and eight waves, 124 so, 123 in two launches; 20,000 of 200
