@@ -298,8 +298,9 @@ def bench_workload(index, args):
         return None if nbytes is None else nbytes / agg_ms / 1e6 / HBM_PEAK_GBS
     roofline = {
         "bound": "hbm",
-        "kernel": ("agg_gat_flash_kernel (wave per row, a workgroup per long row; scores formed from the gathered "
-                   "rows; other head widths: gat_scores_kernel + agg_gat_fast_kernel with a score table)"
+        "kernel": ("agg_gat_rows_kernel (slab of one head after the other, four rows per wave) or agg_gat_flash_kernel "
+                   "(wave per row), scores formed from the gathered rows; other head widths: gat_scores_kernel + "
+                   "agg_gat_fast_kernel with a score table"
                    if gat else
                    "aggregation call = agg_rowgroup_kernel + agg_grouped_kernel per source range (narrow slabs) "
                    "or agg_linear_kernel (whole rows), chosen by the plan"),
