@@ -578,7 +578,7 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArg
     };
     weights();
 
-    // eight columns from `col` on, moved back to end with the row where its padding does not hold them all (see own_columns)
+    // eight columns from `col` on, moved back to end with the row where rows don't hold whole vectors (see own_columns)
     const int col0 = (int)slab * (8 * P) + li * 8, F = (int)a.F;
     const bool act = col0 < F;
     const int col = a.own_rows ? col0 : min(col0, F - 8), skip = col0 - col, valid = min(8, F - col);
@@ -1401,7 +1401,7 @@ bool aligned_rows(const void* p, int64_t ld_elems, int bytes_per_elem)
 //  of 80 (5), 64 columns 1,483 and 3,670, 576,484 of 113 (7), 96 columns 2,069 and 3,946; the other way 400,000 of 150 (19) 800
 //  and 678, 150,000 of 200 (50), 64 columns 355 and 251, with weights 386,048 of 112 (14) 1,012 and 832.  Not in one range, which
 //  takes the longest rows apart: 59,657 of 263, longest 5,419, 265 and 110; but 1,330,759 of 85, 104 columns 5,328 and 5,836.
-int rows_lanes(const StoredCall& c, bool wide, bool own_rows, bool ranges, int parts)
+int rows_lanes(const StoredCall& c, bool wide, bool ranges, int parts)
 {
     const retexo_plan* p = c.plan;
     const AggOptions& opt = agg_options();
@@ -1411,8 +1411,8 @@ int rows_lanes(const StoredCall& c, bool wide, bool own_rows, bool ranges, int p
     const int lanes = F <= 32 ? 4 : F <= 64 ? 8 : F <= 128 ? 16 : 32;
     if (weighted && F > 64 && N < 8192 && nnz < 100 * N) return 0;      // (weights wait for ids: 3,000 of 60, 128 columns 10.4 and 9.9)
     if (!wide) {
-        const bool any = (uintptr_t)c.Z % 4 == 0 && c.ldz % 2 == 0 && (own_rows || (F >= 8 && F % 2 == 0));
-        return any ? lanes : 0;
+        // eight elements at 4-byte addresses, none past a row's end: what lies there may not be the caller's
+        return (uintptr_t)c.Z % 4 == 0 && c.ldz % 2 == 0 && F >= 8 && F % 2 == 0 ? lanes : 0;
     }
     if (!ranges) return F <= 128 || N < 250000 ? lanes : 0;
     if (F > 128) return 0;
@@ -1466,7 +1466,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     a.first = 1;
     a.last = 1;
     a.table_bytes = 0;
-    a.own_rows = align_up(F, 8) <= c.ldz;
+    a.own_rows = wide;
 
     const int64_t n_heavy = long_rows(p, F, true);
 
@@ -1492,7 +1492,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
         }
         if (parts != 2 && parts != 4 && parts != 8 && parts != 16) parts = 1;
     }
-    if (const int lanes = linear_sum && off32 ? rows_lanes(c, wide, a.own_rows != 0, narrow, parts) : 0) {
+    if (const int lanes = linear_sum && off32 ? rows_lanes(c, wide, narrow, parts) : 0) {
         a.table_bytes = (uint32_t)(((N - 1) * c.ldz + (a.own_rows ? align_up(F, 8) : F)) * 2);
         if (lanes == 4)       launch_rows<FMT, 4>(a, p, stream);
         else if (lanes == 8)  launch_rows<FMT, 8>(a, p, stream);
