@@ -110,6 +110,8 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
     const int v = __builtin_amdgcn_readfirstlane(a.order[heavy ? slot : a.heavy_rows + slot]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v + 1]);
+    // what a mean divides by: the plan's degree, which retexo_plan_set_degrees may have replaced
+    const int d = !MAXOP && a.scale == SCALE_MEAN ? a.deg[v] : hi - lo;
 
     const int64_t col0 = (int64_t)slab * (64 * VEC * NC) + lane * VEC;
     bool act[NC];
@@ -179,7 +181,6 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
             }
     }
 
-    const int d = hi - lo;
     float* orow = a.out + (int64_t)v * a.ldo;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -603,12 +604,13 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
     if (first >= a.n_rows) return;
     const int64_t slot = heavy ? first : first + g;
     const bool have = slot < a.n_rows;
-    int v = 0;
+    int v = 0, d = 0;
     uint32_t lo = 0, hi = 0;
     if (have) {
         v = a.order[slot];
         lo = (uint32_t)a.row_ptr[v];
         hi = (uint32_t)a.row_ptr[v + 1];
+        if (a.scale == SCALE_MEAN) d = a.deg[v];      // (not hi - lo: see retexo_plan_set_degrees)
     }
     typedef EntryWalk<P, WEIGHTED> Walk;
     Walk walk;
@@ -705,7 +707,6 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
         }
     }
     if (!have || !act) return;
-    const int d = (int)(hi - lo);
     float* orow = a.out + (int64_t)v * a.ldo;
     float r[4];
 #pragma unroll

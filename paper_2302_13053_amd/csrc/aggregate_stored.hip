@@ -278,6 +278,8 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void stored_line
     const int v = __builtin_amdgcn_readfirstlane(a.order[a.row_begin + slot]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v + 1]);
+    // what a mean divides by: the plan's degree, which retexo_plan_set_degrees may have replaced
+    const int d = !MAXOP && a.scale == 1 ? a.deg[v] : hi - lo;
 
     const int64_t col0 = (int64_t)slab * (64 * E * NC) + lane * E;
     bool act[NC];
@@ -341,7 +343,6 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void stored_line
             }
     }
 
-    const int d = hi - lo;
     float* orow = a.out + (int64_t)v * a.ldo;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -552,12 +553,13 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArg
     if (first >= a.n_rows) return;
     const int64_t slot = heavy ? first : first + g;
     const bool have = slot < a.n_rows;
-    int v = 0;
+    int v = 0, d = 0;
     uint32_t lo = 0, hi = 0;
     if (have) {
         v = a.order[slot];
         lo = (uint32_t)a.row_ptr[v];
         hi = (uint32_t)a.row_ptr[v + 1];
+        if (a.scale == 1) d = a.deg[v];      // (not hi - lo: see retexo_plan_set_degrees)
     }
     typedef EntryWalk<P, WEIGHTED> Walk;
     Walk walk;
@@ -640,7 +642,6 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArg
         }
     }
     if (!have || !act) return;
-    const int d = (int)(hi - lo);
     float* orow = a.out + (int64_t)v * a.ldo;
     const float dinv = a.scale == 2 ? a.dinv[v] : 1.0f;
     float r[8];
