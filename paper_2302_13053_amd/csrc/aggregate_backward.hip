@@ -655,7 +655,8 @@ __global__ __launch_bounds__(64 * NW) void gat_bwd_src_rows_kernel(BwdArgs a, in
             acc[1] = fmaf(al, gg[t].y, acc[1]); pd = fmaf(gg[t].y, zo[1], pd);
             acc[2] = fmaf(al, gg[t].z, acc[2]); pd = fmaf(gg[t].z, zo[2], pd);
             acc[3] = fmaf(al, gg[t].w, acc[3]); pd = fmaf(gg[t].w, zo[3], pd);
-            q = fmaf(w, pd, q);
+            // (zero times an infinite row of the group's own would be NaN, for a row without entries as well)
+            q = oo[t] != kNoEntry ? fmaf(w, pd, q) : q;
         }
     };
     if (batches > 0) issue(0, gr[0], nb[0], on[0]);

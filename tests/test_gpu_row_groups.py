@@ -131,3 +131,25 @@ def test_slabs_of_heads(heads, dh):
     for what, save in (("forward", {}), ("save mode", dict(save=True, workspace=ws))):
         assert_close(Hn.aggregate(g, "gat_softmax", Z, F, **kw, **save).cpu().numpy()[:, :2 * F], want, what=what)
     g.destroy()
+
+
+@pytest.mark.parametrize("name", ["edges", "skewed"])
+@pytest.mark.parametrize("heads,dh", [(1, 4), (3, 8), (1, 64), (8, 16), (8, 32)])
+def test_values_that_no_entry_reads(graphs, name, heads, dh):
+    """The own row of a node without entries reaches no gradient of Z, whatever it holds and whichever rows share its wave."""
+    g, rp, _ = graphs[name]
+    n, F = g.n_nodes, heads * dh
+    empty = np.flatnonzero(np.diff(rp) == 0)
+    a = [Hn.dev(wl.random_matrix(heads, dh, k) * np.float32(0.1)) for k in (1, 2)]
+    Zh = wl.random_matrix(n, F, F)
+    G = Hn.dev(wl.random_matrix(n, F, F + 1))
+    kw = dict(heads=heads, a_src=a[0], a_dst=a[1])
+    want = Hn.aggregate_backward(g, "gat_softmax", F, G, Z=Hn.dev(Zh), **kw)[0].cpu().numpy()[:, :F]
+    Zh[empty] = np.array([np.inf, -np.inf, np.nan], np.float32)[np.arange(empty.size) % 3, None]
+    Z = Hn.dev(Zh)
+    plain = Hn.aggregate_backward(g, "gat_softmax", F, G, Z=Z, **kw)[0].cpu().numpy()[:, :F]
+    ws = Hn.ws_tensor(B.retexo_workspace_bytes(g.plan, F, B.MODES["gat_softmax"], heads, B.F_SAVE))
+    Hn.aggregate(g, "gat_softmax", Z, F, workspace=ws, save=True, **kw)
+    saved = Hn.aggregate_backward(g, "gat_softmax", F, G, Z=Z, saved=ws, **kw)[0].cpu().numpy()[:, :F]
+    assert empty.size and np.array_equal(plain, want) and np.array_equal(saved[empty], want[empty])
+    assert np.all(np.isfinite(saved))
