@@ -1321,13 +1321,13 @@ int csr_build_bucketed(int64_t n_pairs, const int32_t* d_src, const int32_t* d_d
                   u32(L.group_bin0), u32(L.group_off), u32(L.group_cursor), u32(L.group_tile0),
                   (uint16_t*)(ws + L.coarse_group)};
 
-    HostReport report;
+    HostReport report(stream);
     static_assert(sizeof(BucketHeader) <= kReportBytes, "a report holds it");
     auto finish = [&]() -> int {
         RETEXO_HIP_TRY(hipGetLastError());
         BucketHeader h;
         if (!report.get()) RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
-        RETEXO_HIP_TRY(hipStreamSynchronize(stream));
+        RETEXO_HIP_TRY(report.wait());
         if (report.get()) memcpy(&h, report.get(), sizeof(h));
         if (h.bad_id) return RETEXO_E_CSR;
         if (h.internal) return RETEXO_E_HIP;

@@ -708,7 +708,7 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     void* tmp = ws + L.tmp;
 
     if (int e = launch_zero(hdr, sizeof(ShareHeader), stream)) return e;
-    HostReport report;
+    HostReport report(stream);
     static_assert(sizeof(ShareHeader) <= kReportBytes && sizeof(ShareHeader) % 4 == 0, "a report holds it");
     const bool direct = N > 0 && report.get();
     const dim3 node_grid((unsigned)L.blocks);
@@ -742,7 +742,7 @@ extern "C" int retexo_partition_share(int64_t N, const int64_t* d_row_ptr, const
     }
     ShareHeader h;
     if (!direct) RETEXO_HIP_TRY(hipMemcpyAsync(&h, hdr, sizeof(h), hipMemcpyDeviceToHost, stream));
-    RETEXO_HIP_TRY(hipStreamSynchronize(stream));
+    RETEXO_HIP_TRY(report.wait());
     if (direct) memcpy(&h, report.get(), sizeof(h));
     if (h.bad_part) return RETEXO_E_PARTITION;
     h_sizes[0] = h.n_inner;

@@ -509,7 +509,7 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
     char* sc = (char*)scratch;
     Readback* rb = (Readback*)(sc + L.s_rb);
     const bool check = (flags & RETEXO_F_VALIDATE) && nnz > 0;         // (its atomics need device memory)
-    HostReport report;
+    HostReport report(stream);
     static_assert(sizeof(Readback) <= kReportBytes, "a report holds it");
     const bool direct = N > 0 && !check && report.get();
     if (direct) rb = (Readback*)report.get();
@@ -552,7 +552,7 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
     RETEXO_HIP_TRY(hipGetLastError());
     Readback h;
     if (!direct) RETEXO_HIP_TRY(hipMemcpyAsync(&h, rb, sizeof(h), hipMemcpyDeviceToHost, stream));
-    RETEXO_HIP_TRY(hipStreamSynchronize(stream));
+    RETEXO_HIP_TRY(report.wait());
     if (direct) memcpy(&h, rb, sizeof(h));
     if (h.bad) return RETEXO_E_CSR;
     for (int i = 0; i < kPlanThresholdCount; ++i) p->rows_at_least[i] = h.counts[i];

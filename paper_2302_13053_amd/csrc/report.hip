@@ -1,6 +1,5 @@
 #include "report.hpp"
 
-#include <hip/hip_runtime.h>
 #include <mutex>
 #include <stdint.h>
 
@@ -22,7 +21,7 @@ Pool& pool()
 
 }  // namespace
 
-HostReport::HostReport()
+HostReport::HostReport(hipStream_t stream) : stream_(stream)
 {
     Pool& p = pool();
     std::lock_guard<std::mutex> guard(p.lock);
@@ -41,9 +40,16 @@ HostReport::HostReport()
     piece_ = p.memory + (size_t)index_ * kReportBytes;
 }
 
+hipError_t HostReport::wait()
+{
+    const hipError_t e = hipStreamSynchronize(stream_);
+    waited_ = e == hipSuccess;
+    return e;
+}
+
 HostReport::~HostReport()
 {
-    if (index_ < 0) return;
+    if (index_ < 0 || (!waited_ && wait() != hipSuccess)) return;
     Pool& p = pool();
     std::lock_guard<std::mutex> guard(p.lock);
     p.taken &= ~(1u << index_);

@@ -2,22 +2,29 @@
 // A copy of device memory to the host is a launch of its own, and one to unpinned memory waits for it besides: a plan of
 // 2,708 nodes 32 us, 24 so, a construction of 5,429 pairs 50, 42; a whole pass over that graph 167, 135.
 #pragma once
+#include <hip/hip_runtime.h>
 #include <stddef.h>
 
 constexpr size_t kReportBytes = 2048;
 
-// One piece of kReportBytes of pinned memory, from its construction to its destruction; get() is NULL where none is to be
-// had (all taken by other threads, or no such memory): the caller then copies from device memory instead.  Pieces come from one
+// One piece of kReportBytes of pinned memory, for kernels on one stream; get() is NULL where none is to be had (all
+// taken by other threads, or no such memory): the caller then copies from device memory instead.  Pieces come from one
 // allocation per process, made on first use and kept.
+// A piece is another call's next, so it goes back only once the stream has been waited for: by wait(), or else by the
+// destructor, on the way out of a call that launched kernels and then failed.  Where that fails too, the piece stays out.
 class HostReport {
 public:
-    HostReport();
+    explicit HostReport(hipStream_t stream);
     ~HostReport();
     HostReport(const HostReport&) = delete;
     HostReport& operator=(const HostReport&) = delete;
     void* get() const { return piece_; }
+    // after it, what the stream's kernels wrote to the piece is there
+    hipError_t wait();
 
 private:
+    hipStream_t stream_;
     void* piece_ = nullptr;
     int index_ = -1;
+    bool waited_ = false;
 };
