@@ -22,8 +22,10 @@
  *     retexo_plan_create synchronise the stream once; retexo_plan_create also
  *     allocates the plan's own small arrays.  The result words of construction,
  *     plan and share come back through 64 KiB of pinned host memory that the
- *     first such call of a process allocates and the process keeps (where that
- *     fails, or more than 32 threads are in such calls, by a copy).
+ *     first such call of a process allocates, unless it is retexo_plan_create_in,
+ *     and the process keeps (where there is none, or more than 32 threads are
+ *     in such calls, by a copy; hipDeviceReset, which would free it, is for a
+ *     process that has done with the library).
  *   - Every entry point documented as "Enqueues on `stream`" only launches kernels there: no
  *     allocation, no host synchronisation, no memset or copy nodes.  A caller may therefore record
  *     a sequence of them (a round, a training step) into a HIP graph by stream capture and

@@ -509,7 +509,7 @@ int plan_fill(retexo_plan* p, const PlanLayout& L, unsigned flags, void* keep, v
     char* sc = (char*)scratch;
     Readback* rb = (Readback*)(sc + L.s_rb);
     const bool check = (flags & RETEXO_F_VALIDATE) && nnz > 0;         // (its atomics need device memory)
-    HostReport report(stream);
+    HostReport report(stream, p->block != nullptr);                    // (retexo_plan_create_in does not allocate)
     static_assert(sizeof(Readback) <= kReportBytes, "a report holds it");
     const bool direct = N > 0 && !check && report.get();
     if (direct) rb = (Readback*)report.get();

@@ -21,14 +21,20 @@ Pool& pool()
 
 }  // namespace
 
-HostReport::HostReport(hipStream_t stream) : stream_(stream)
+HostReport::HostReport(hipStream_t stream, bool allocate) : stream_(stream)
 {
     Pool& p = pool();
     std::lock_guard<std::mutex> guard(p.lock);
     if (!p.memory) {
+        if (!allocate) return;
+        // (an allocation would end a capture that another thread has begun in the global mode)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         // readable and writable by every device, coherent: what a kernel has written is there once the stream has been waited for
         void* m = nullptr;
-        if (hipHostMalloc(&m, kPieces * kReportBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        const hipError_t e = hipHostMalloc(&m, kPieces * kReportBytes, hipHostMallocPortable | hipHostMallocMapped);
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) {
             (void)hipGetLastError();
             return;
         }

@@ -9,12 +9,13 @@ constexpr size_t kReportBytes = 2048;
 
 // One piece of kReportBytes of pinned memory, for kernels on one stream; get() is NULL where none is to be had (all
 // taken by other threads, or no such memory): the caller then copies from device memory instead.  Pieces come from one
-// allocation per process, made on first use and kept.
+// allocation per process, made on first use and kept; `allocate` false, for an entry point that is documented not to allocate:
+// there is a piece only if another call has made that allocation.
 // A piece is another call's next, so it goes back only once the stream has been waited for: by wait(), or else by the
 // destructor, on the way out of a call that launched kernels and then failed.  Where that fails too, the piece stays out.
 class HostReport {
 public:
-    explicit HostReport(hipStream_t stream);
+    explicit HostReport(hipStream_t stream, bool allocate = true);
     ~HostReport();
     HostReport(const HostReport&) = delete;
     HostReport& operator=(const HostReport&) = delete;

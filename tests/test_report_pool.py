@@ -15,11 +15,20 @@ typedef int hipError_t;
 typedef struct stream_* hipStream_t;
 enum { hipSuccess = 0, hipErrorUnknown = 999 };
 enum { hipHostMallocPortable = 1, hipHostMallocMapped = 2 };
+enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
+inline hipStreamCaptureMode capture_mode = hipStreamCaptureModeGlobal;
+inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m)
+{
+    const hipStreamCaptureMode t = capture_mode;
+    capture_mode = *m;
+    *m = t;
+    return hipSuccess;
+}
 inline int waits = 0, allocations = 0, last_error = hipSuccess;
 inline bool no_memory = false, stream_broken = false, pending = false;      // pending: a kernel still writes to a piece
 inline hipError_t hipHostMalloc(void** p, size_t n, unsigned)
 {
-    if (no_memory) return last_error = hipErrorUnknown;
+    if (no_memory || capture_mode != hipStreamCaptureModeRelaxed) return last_error = hipErrorUnknown;
     ++allocations;
     *p = malloc(n);
     return hipSuccess;
@@ -79,6 +88,13 @@ CASES = {
     CHECK(hipGetLastError() == hipSuccess);
     no_memory = false;
     { HostReport r(nullptr); CHECK(r.get()); }
+    CHECK(capture_mode == hipStreamCaptureModeGlobal);
+""",
+    "a call that must not allocate": """
+    { HostReport r(nullptr, false); CHECK(!r.get()); CHECK(r.wait() == hipSuccess); }
+    CHECK(allocations == 0);
+    { HostReport r(nullptr); first = r.get(); CHECK(first); }
+    { HostReport r(nullptr, false); CHECK(r.get() == first); }
 """,
 }
 
