@@ -39,6 +39,7 @@ struct AggArgs {
     const int32_t* col_idx;
     const int32_t* order;
     const int32_t* deg;
+    const int32_t* set_deg;  // what a mean divides by where it is not the row's length (retexo_plan_set_degrees); else NULL: a load less
     const float* dinv;
     const float* wsrc;     // per-source weight of every gathered row, or NULL (all 1)
     const float* Z;
@@ -60,6 +61,7 @@ struct AggArgs {
     int slab_cols;         // columns of a slab, and workgroups that it takes (edge softmax, several rows per wave)
     uint32_t slab_blocks;
     int scale;             // SCALE_*
+    int levels;            // sums in levels (see BatchSums)
     int heads;
     int Dh;
     float slope;
@@ -93,10 +95,11 @@ struct AggArgs {
 // row of five entries waits for memory once, not once for four and once more.  Bound by memory latency on small graphs
 // (19,717 rows, 108,393 entries, 256 columns: see long_rows) and by the gathers' bytes on large ones.
 // ---------------------------------------------------------------------------
-template <int VEC, int NC, bool MAXOP>
+template <int VEC, int NC, bool MAXOP, bool LEVELS>
 __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
 {
     constexpr int U = NC * VEC <= 8 ? 8 : 4;          // entries in flight per lane: up to 64 registers
+    static_assert(!LEVELS || U == 8, "levels of 16 and 128 entries");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool heavy = blockIdx.x < a.heavy_items;    // uniform over the workgroup
@@ -110,8 +113,7 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
     const int v = __builtin_amdgcn_readfirstlane(a.order[heavy ? slot : a.heavy_rows + slot]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v + 1]);
-    // what a mean divides by: the plan's degree, which retexo_plan_set_degrees may have replaced
-    const int d = !MAXOP && a.scale == SCALE_MEAN ? a.deg[v] : hi - lo;
+    const int d = a.set_deg ? a.set_deg[v] : hi - lo;
 
     const int64_t col0 = (int64_t)slab * (64 * VEC * NC) + lane * VEC;
     bool act[NC];
@@ -121,6 +123,23 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
         act[c] = col0 + c * 64 * VEC < a.F;
 #pragma unroll
         for (int k = 0; k < VEC; ++k) acc[c][k] = MAXOP ? -INFINITY : 0.0f;
+    }
+    float sum[NC][VEC], tile[NC][VEC];                // (LEVELS)
+    int batches = 0;
+    auto raise = [&](float (&from)[NC][VEC], float (&to)[NC][VEC]) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                to[c][k] += from[c][k];
+                from[c][k] = 0.0f;
+            }
+    };
+    if constexpr (LEVELS) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) sum[c][k] = tile[c][k] = 0.0f;
     }
     const float* zl = a.Z + col0;
     const bool weighted = a.wsrc != nullptr;
@@ -151,14 +170,25 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_linear_kernel(AggArgs a)
                 for (int c = 0; c < NC; ++c)
                     if (act[c]) {
 #pragma unroll
-                        for (int k = 0; k < VEC; ++k)
-                            acc[c][k] = MAXOP ? fmaxf(acc[c][k], z[t][c][k]) : fmaf(w, z[t][c][k], acc[c][k]);
+                        for (int k = 0; k < VEC; ++k) {
+                            float& x = LEVELS ? sum[c][k] : acc[c][k];
+                            x = MAXOP ? fmaxf(x, z[t][c][k]) : fmaf(w, z[t][c][k], x);
+                        }
                     }
+            }
+            if constexpr (LEVELS) {
+                ++batches;                            // (uniform)
+                if (batches % 2 == 0) raise(sum, tile);
+                if (batches % 16 == 0) raise(tile, acc);
             }
         };
         int j = 0;
         for (; j + U <= cnt; j += U) batch(j, std::true_type{});
         if (j < cnt) batch(j, std::false_type{});
+    }
+    if constexpr (LEVELS) {
+        raise(sum, tile);
+        raise(tile, acc);
     }
 
     __shared__ float red[kHeavyWaves][NC * VEC][64];
@@ -592,7 +622,7 @@ __device__ __forceinline__ int64_t own_columns(int64_t col, int64_t F) { return 
 // Bound by memory latency on small graphs, where R rows wait together, and by the gathered lines on large ones (2,449,029
 // nodes of 50 entries, 32 columns 2,330 us, 6.7 TB/s of lines).  linear_route says where it is taken, and what it measures.
 // ---------------------------------------------------------------------------
-template <int P, bool WEIGHTED>
+template <int P, bool WEIGHTED, bool LEVELS>
 __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
 {
     constexpr int U = 8, R = 64 / P, NW = kHeavyWaves, PER = U / 4;    // entries and lanes of a batch
@@ -610,7 +640,7 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
         v = a.order[slot];
         lo = (uint32_t)a.row_ptr[v];
         hi = (uint32_t)a.row_ptr[v + 1];
-        if (a.scale == SCALE_MEAN) d = a.deg[v];      // (not hi - lo: see retexo_plan_set_degrees)
+        if constexpr (!WEIGHTED) d = a.set_deg ? a.set_deg[v] : (int)(hi - lo);
     }
     typedef EntryWalk<P, WEIGHTED> Walk;
     Walk walk;
@@ -640,7 +670,7 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
     const int skip = (int)slab * (4 * P) + li * 4 - col, valid = min(4, (int)a.F);
     const table_t table = buffer_table(a.Z, a.table_bytes);
     const uint32_t colbytes = act ? (uint32_t)col * 4 : kNoEntry;      // (columns past the row width fetch nothing)
-    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    BatchSums<4, LEVELS> sums;
     f32x4 z[2][U];
     constexpr int kBatches = P / PER;                                   // of a tile
     auto issue = [&](int k, f32x4 (&zz)[U]) {                           // batch k
@@ -653,39 +683,39 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
         for (int t = 0; t < U; ++t)
             zz[t] = __builtin_bit_cast(f32x4, load_entry(table, walk.at(j * PER + t / 4, t % 4), colbytes));
     };
-    auto consume = [&](int k, const f32x4 (&zz)[U]) {
-        float w[U];
+    auto consume = [&](int k, const f32x4 (&zz)[U], float (&sum)[4]) {  // sum of batch k
         if constexpr (WEIGHTED) {
             // (the next tile's weights have taken the place of this one's when its last batch is added up)
             const bool old = (k + 1) % kBatches == 0 && k + 1 < batches;
 #pragma unroll
-            for (int t = 0; t < U; ++t)
-                w[t] = __int_as_float(__builtin_amdgcn_ds_bpermute(walk.gaddr + 4 * (k % kBatches * PER + t / 4),
-                                                                   __float_as_int(old ? w_prev[t % 4] : w_cur[t % 4])));
-        }
+            for (int t = 0; t < U; ++t) {
+                const float w = __int_as_float(__builtin_amdgcn_ds_bpermute(walk.gaddr + 4 * (k % kBatches * PER + t / 4),
+                                                                            __float_as_int(old ? w_prev[t % 4] : w_cur[t % 4])));
 #pragma unroll
-        for (int t = 0; t < U; ++t) {
-            if constexpr (WEIGHTED) {
-                acc[0] = fmaf(w[t], zz[t].x, acc[0]);
-                acc[1] = fmaf(w[t], zz[t].y, acc[1]);
-                acc[2] = fmaf(w[t], zz[t].z, acc[2]);
-                acc[3] = fmaf(w[t], zz[t].w, acc[3]);
-            } else {
-                acc[0] += zz[t].x;
-                acc[1] += zz[t].y;
-                acc[2] += zz[t].z;
-                acc[3] += zz[t].w;
+                for (int c = 0; c < 4; ++c) sum[c] = t == 0 ? w * zz[t][c] : fmaf(w, zz[t][c], sum[c]);
             }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                sum[c] = ((zz[0][c] + zz[1][c]) + (zz[2][c] + zz[3][c])) + ((zz[4][c] + zz[5][c]) + (zz[6][c] + zz[7][c]));
         }
     };
+    float sum[4];
     if (batches > 0) issue(0, z[0]);
     for (int k = 0; k < batches; k += 2) {
         if (k + 1 < batches) issue(k + 1, z[1]);
-        consume(k, z[0]);
-        if (k + 1 >= batches) break;
+        consume(k, z[0], sum);
+        sums.even(sum);
+        if (k + 1 >= batches) {
+            sums.last_even();
+            break;
+        }
         if (k + 2 < batches) issue(k + 2, z[0]);
-        consume(k + 1, z[1]);
+        consume(k + 1, z[1], sum);
+        sums.odd(k, sum);
     }
+    sums.flush();
+    float (&acc)[4] = sums.all;
 
     if (heavy) {
 #pragma unroll
@@ -712,8 +742,8 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void agg_rows_kernel(AggArgs a)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         float x = acc[k];
-        if (a.scale == SCALE_MEAN) x = d > 0 ? x / (float)d : 0.0f;
-        else if (a.scale == SCALE_GCN) x = x * a.dinv[v];
+        if constexpr (WEIGHTED) x = x * a.dinv[v];
+        else if (a.scale == SCALE_MEAN) x = d > 0 ? x / (float)d : 0.0f;
         r[k] = x;
     }
     store_own(orow + a.ocol + col, r, skip, valid, a.out_vec != 0, a.out_half != 0);
@@ -1371,7 +1401,13 @@ void launch_linear(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t 
 {
     AggArgs a = base;
     const unsigned blocks = both_classes(a, n_heavy, N);
-    agg_linear_kernel<VEC, NC, MAXOP><<<dim3(blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
+    if constexpr (!MAXOP && VEC == 4 && NC <= 2) {          // (the widest slabs have no registers for them)
+        if (a.levels) {
+            agg_linear_kernel<VEC, NC, MAXOP, true><<<dim3(blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
+            return;
+        }
+    }
+    agg_linear_kernel<VEC, NC, MAXOP, false><<<dim3(blocks), dim3(64 * kHeavyWaves), 0, stream>>>(a);
 }
 
 template <int P>
@@ -1383,8 +1419,10 @@ void launch_rows(const AggArgs& base, int64_t n_heavy, int64_t N, hipStream_t st
     a.nslab = (int)((a.F + 4 * P - 1) / (4 * P));
     a.slab_blocks = (uint32_t)(n_heavy + (N - n_heavy + rows - 1) / rows);
     const dim3 grid(a.slab_blocks * (unsigned)a.nslab), block(64 * kHeavyWaves);
-    if (a.wsrc) agg_rows_kernel<P, true><<<grid, block, 0, stream>>>(a);
-    else        agg_rows_kernel<P, false><<<grid, block, 0, stream>>>(a);
+    if (a.wsrc && a.levels) agg_rows_kernel<P, true, true><<<grid, block, 0, stream>>>(a);
+    else if (a.wsrc)        agg_rows_kernel<P, true, false><<<grid, block, 0, stream>>>(a);
+    else if (a.levels)      agg_rows_kernel<P, false, true><<<grid, block, 0, stream>>>(a);
+    else                    agg_rows_kernel<P, false, false><<<grid, block, 0, stream>>>(a);
 }
 
 template <int LPG, bool WEIGHTED, bool OFF32>
@@ -2076,6 +2114,13 @@ int gather_vec(const AggCall& c)
     return vec;
 }
 
+// graphs that the range walk can be for: the plan split them, or they are dense and their table does not fit an L2
+bool dense_for_ranges(const AggCall& c)
+{
+    const retexo_plan* p = c.plan;
+    return p->part_ptr || (p->nnz >= 32 * p->N && p->N * c.ldz * 4 > (4ll << 20));
+}
+
 // Which kernels a sum, mean or gcn_sym takes whose rows are gathered four floats at a time: the range walk over narrow slabs, row
 // groups of `lanes` lanes over slabs of 4 * lanes columns, or (neither) whole rows.
 struct LinearRoute {
@@ -2109,7 +2154,7 @@ LinearRoute linear_route(const AggCall& c, int vec, int parts)
     const LinearRoute ranges = {true, 0}, whole = {false, 0};
     if (narrow_unpadded(c)) return {false, F <= 32 ? 8 : 16};
     if (p->part_ptr && opt.parts >= 0) return ranges;              // (the caller said how many)
-    const bool dense = p->part_ptr || (nnz >= 32 * N && N * c.ldz * 4 > (4ll << 20));
+    const bool dense = dense_for_ranges(c);
     auto mean_is = [&](int64_t entries) { return nnz >= entries * N; };
     if (dense && N >= 16384 && N * 128 <= parts * (64ll << 20) && 2 * nnz >= 25 * N * parts) {
         const bool enough = N >= 24000 || work >= 1200000000ll || mean_is(300);
@@ -2258,6 +2303,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
         last_slab >= (c.F > 512 ? 64 : c.mode == RETEXO_GCN_SYM ? 192 : 128) &&
         !(p->nnz < 10 * N && N >= 100000 && (c.F > 512 || c.mode == RETEXO_GCN_SYM)))
         nc = 1;
+    if (!gat && vec == 4 && c.mode != RETEXO_MAX && nc == 3 && opt.slab_cols == 0 && dense_for_ranges(c)) nc = 2;      // (has levels)
     const int64_t slab_w = 64 * (int64_t)vec * nc;
 
     AggArgs a;
@@ -2265,6 +2311,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     a.col_idx = p->col_idx;
     a.order = p->order;
     a.deg = p->deg;
+    a.set_deg = p->degrees_set && c.mode == RETEXO_MEAN ? p->deg : nullptr;
     a.dinv = p->dinv;
     a.wsrc = c.mode == RETEXO_GCN_SYM ? p->dinv : nullptr;
     a.Z = c.Z;
@@ -2284,6 +2331,7 @@ int launch_aggregate(const AggCall& c, hipStream_t stream)
     a.nslab = (int)((c.F + slab_w - 1) / slab_w);
     a.slab_major = opt.slab_major < 0 ? 1 : (int)opt.slab_major;
     a.scale = c.mode == RETEXO_MEAN ? SCALE_MEAN : c.mode == RETEXO_GCN_SYM ? SCALE_GCN : SCALE_SUM;
+    a.levels = dense_for_ranges(c) ? 1 : 0;
     a.heads = c.heads;
     a.Dh = gat ? (int)(c.F / c.heads) : (int)c.F;
     a.slope = c.slope;

@@ -16,6 +16,7 @@
 //   * edge softmax, whole rows per wave, software-pipelined with per-edge weights in LDS
 //   * edge softmax, several rows per wave, scores from the gathered rows (heads of a power of two of four-element lanes)
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "gather.hpp"
@@ -64,6 +65,15 @@ __device__ __forceinline__ void add8(const u32x4& raw, float w, float (&acc)[8])
     decode8<FMT>(raw, z);
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc[k] = WEIGHTED || FMT == FMT_FP16 ? fmaf(w, z[k], acc[k]) : acc[k] + z[k];
+}
+// the first term of a sum
+template <int FMT, bool WEIGHTED>
+__device__ __forceinline__ void first8(const u32x4& raw, float w, float (&acc)[8])
+{
+    float z[8];
+    decode8<FMT>(raw, z);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = WEIGHTED ? w * z[k] : FMT == FMT_FP16 ? fmaf(w, z[k], 0.0f) : z[k];
 }
 __device__ __forceinline__ float register_one()
 {
@@ -232,6 +242,7 @@ struct StoredArgs {
     const int32_t* col_idx;
     const int32_t* order;
     const int32_t* deg;
+    const int32_t* set_deg;  // what a mean divides by where it is not the row's length (retexo_plan_set_degrees); else NULL: a load less
     const float* dinv;
     const float* wsrc;       // per-source weights (gcn_sym: dinv) or NULL
     const uint16_t* Z;
@@ -278,8 +289,7 @@ __global__ __launch_bounds__(64 * (NW == 1 ? kLightWaves : NW)) void stored_line
     const int v = __builtin_amdgcn_readfirstlane(a.order[a.row_begin + slot]);
     const int lo = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v]);
     const int hi = __builtin_amdgcn_readfirstlane((int)a.row_ptr[v + 1]);
-    // what a mean divides by: the plan's degree, which retexo_plan_set_degrees may have replaced
-    const int d = !MAXOP && a.scale == 1 ? a.deg[v] : hi - lo;
+    const int d = a.set_deg ? a.set_deg[v] : hi - lo;
 
     const int64_t col0 = (int64_t)slab * (64 * E * NC) + lane * E;
     bool act[NC];
@@ -559,7 +569,7 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArg
         v = a.order[slot];
         lo = (uint32_t)a.row_ptr[v];
         hi = (uint32_t)a.row_ptr[v + 1];
-        if (a.scale == 1) d = a.deg[v];      // (not hi - lo: see retexo_plan_set_degrees)
+        if constexpr (!WEIGHTED) d = a.set_deg ? a.set_deg[v] : (int)(hi - lo);
     }
     typedef EntryWalk<P, WEIGHTED> Walk;
     Walk walk;
@@ -587,13 +597,51 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArg
     const table_t table = buffer_table(a.Z, a.table_bytes);
     const uint32_t colbytes = act ? (uint32_t)col * 2 : kNoEntry;      // (columns past the row width fetch nothing)
     const float one = WEIGHTED ? 1.0f : register_one();
-    float acc[8];
+    // Running sums in levels (see BatchSums): 16 entries, 128 entries, and the 128s, which lie in LDS since most rows have none.
+    // With weights, which take registers too, the second level lies there as well (otherwise a compute unit holds one workgroup
+    // instead of two: bf16, 1,000,000 nodes of 8 entries, 64 columns 321 us and 261).
+    float sum[8], tile[WEIGHTED ? 1 : 8];
+    __shared__ float far[WEIGHTED ? 2 : 1][8][64 * NW];
+    auto put = [&](int n) {                // the sum of the list's n-th 16 entries, others follow
+        if constexpr (WEIGHTED) {
+            if (n % 8 != 0) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+                for (int c = 0; c < 8; ++c) sum[c] += far[1][c][threadIdx.x];
+            }
+            if (n % 8 != 7) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) far[1][c][threadIdx.x] = sum[c];
+                return;
+            }
+            if (n > 7) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) sum[c] += far[0][c][threadIdx.x];
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c) far[0][c][threadIdx.x] = sum[c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) tile[c] += sum[c];
+            if (n % 8 != 7) return;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                far[0][c][threadIdx.x] = n > 7 ? far[0][c][threadIdx.x] + tile[c] : tile[c];
+                tile[c] = 0.0f;
+            }
+        }
+    };
+    if constexpr (!WEIGHTED) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) tile[c] = 0.0f;
+    }
     u32x4 z[2][U];
     constexpr int kBatches = P / PER;                                   // of a tile
-    auto issue = [&](int k, u32x4 (&zz)[U]) {                           // batch k
-        const int j = k % kBatches;
+    // batch k of an even number and the next (which is never a tile's first): its place in the tile
+    auto place = [](int k, auto odd) { return (k & ~1) % kBatches + (decltype(odd)::value ? 1 : 0); };
+    constexpr std::false_type even;
+    constexpr std::true_type odd;
+    auto issue = [&](int k, u32x4 (&zz)[U], auto is_odd) {
+        const int j = place(k, is_odd);
         if (j == 0 && k > 0) {
             walk.take();
             weights();
@@ -601,25 +649,43 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArg
 #pragma unroll
         for (int t = 0; t < U; ++t) zz[t] = load_entry(table, walk.at(j * PER + t / 4, t % 4), colbytes);
     };
-    auto consume = [&](int k, const u32x4 (&zz)[U]) {
+    auto consume = [&](int k, const u32x4 (&zz)[U], auto is_odd) {
+        const int j = place(k, is_odd);
         // (the next tile's weights have taken the place of this one's when its last batch is added up)
-        const bool old = (k + 1) % kBatches == 0 && k + 1 < batches;
+        const bool old = (j + 1) % kBatches == 0 && k + 1 < batches;
 #pragma unroll
         for (int t = 0; t < U; ++t) {
             float w = one;
             if constexpr (WEIGHTED)
-                w = __int_as_float(__builtin_amdgcn_ds_bpermute(walk.gaddr + 4 * (k % kBatches * PER + t / 4),
+                w = __int_as_float(__builtin_amdgcn_ds_bpermute(walk.gaddr + 4 * (j * PER + t / 4),
                                                                 __float_as_int(old ? w_prev[t % 4] : w_cur[t % 4])));
-            add8<FMT, WEIGHTED>(zz[t], w, acc);
+            if (t == 0 && !decltype(is_odd)::value) first8<FMT, WEIGHTED>(zz[t], w, sum);
+            else add8<FMT, WEIGHTED>(zz[t], w, sum);
         }
     };
-    if (batches > 0) issue(0, z[0]);
+    if (batches > 0) issue(0, z[0], even);
     for (int k = 0; k < batches; k += 2) {
-        if (k + 1 < batches) issue(k + 1, z[1]);
-        consume(k, z[0]);
+        if (k + 1 < batches) issue(k + 1, z[1], odd);
+        if (k > 0) put(k / 2 - 1);
+        consume(k, z[0], even);
         if (k + 1 >= batches) break;
-        if (k + 2 < batches) issue(k + 2, z[0]);
-        consume(k + 1, z[1]);
+        if (k + 2 < batches) issue(k + 2, z[0], even);
+        consume(k + 1, z[1], odd);
+    }
+    float acc[8];
+    const int before = (batches + 1) / 2 - 1;                           // sums that were put away
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        acc[c] = batches > 0 ? sum[c] : 0.0f;
+        if constexpr (!WEIGHTED) acc[c] += tile[c];
+    }
+    if (WEIGHTED && before > 0 && before % 8 != 0) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[c] += far[1][c][threadIdx.x];
+    }
+    if (before >= 8) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[c] += far[0][c][threadIdx.x];
     }
 
     if (heavy) {
@@ -643,13 +709,13 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void stored_rows_kernel(StoredArg
     }
     if (!have || !act) return;
     float* orow = a.out + (int64_t)v * a.ldo;
-    const float dinv = a.scale == 2 ? a.dinv[v] : 1.0f;
+    const float dinv = WEIGHTED ? a.dinv[v] : 1.0f;
     float r[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         float x = acc[k];
-        if (a.scale == 1) x = d > 0 ? x / (float)d : 0.0f;
-        else if (a.scale == 2) x = x * dinv;
+        if constexpr (WEIGHTED) x = x * dinv;
+        else if (a.scale == 1) x = d > 0 ? x / (float)d : 0.0f;
         r[k] = x;
     }
     auto store = [&](float* p, const float (&x)[8], bool vec_ok, bool half_ok) {
@@ -1440,6 +1506,7 @@ int launch_stored(const StoredCall& c, hipStream_t stream)
     a.col_idx = p->col_idx;
     a.order = p->order;
     a.deg = p->deg;
+    a.set_deg = p->degrees_set && c.mode == RETEXO_MEAN ? p->deg : nullptr;
     a.dinv = p->dinv;
     a.wsrc = c.mode == RETEXO_GCN_SYM ? p->dinv : nullptr;
     a.Z = Z;

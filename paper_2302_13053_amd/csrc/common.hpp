@@ -24,6 +24,7 @@ struct retexo_plan {
     const int64_t* row_ptr = nullptr;
     const int32_t* col_idx = nullptr;
     int32_t* deg = nullptr;       // [N]
+    bool degrees_set = false;     // deg and dinv were replaced: they are not those of the rows
     float* dinv = nullptr;        // [N]
     int32_t* order = nullptr;     // [N] row ids, longest rows first (ties: ascending id)
     // [kMaxParts + 1][N] CSR positions splitting every row by source-id range, stored in

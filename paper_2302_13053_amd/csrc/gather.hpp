@@ -161,6 +161,63 @@ struct EntryWalk {
     }
 };
 
+// The running sum of a list of entries that a lane group walks by itself, from the sums of its batches of eight.  LEVELS: of two
+// batches, of eight such pairs (128 entries), then of the 128s.  One sum over the whole list loses more the longer it is: terms of
+// one sign, 2-norm of the error, 70, 100 and 300 entries 1.2e-7, 1.5e-7 and 2.4e-7, so 4.9e-8, 5.5e-8 and 4.9e-8, where a walk in
+// source ranges that each add to the result, which takes such lists too, gives 5.4e-8 and 6.0e-8 (70 in eight, 100 in four).  A list of a few
+// entries pays for it (1,000,000 rows of 8, 64 columns, with weights 459 us and 481), so the calls that could take ranges have it.
+template <int K, bool LEVELS>
+struct BatchSums {
+    float all[K], tile[LEVELS ? K : 1], pair[LEVELS ? K : 1];
+    __device__ __forceinline__ BatchSums()
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            all[k] = 0.0f;
+            if constexpr (LEVELS) tile[k] = 0.0f;
+        }
+    }
+    // batch i, i even; its sum
+    __device__ __forceinline__ void even(const float (&sum)[K])
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if constexpr (LEVELS) pair[k] = sum[k];
+            else all[k] += sum[k];
+        }
+    }
+    // ... and that of batch i + 1
+    __device__ __forceinline__ void odd(int i, const float (&sum)[K])
+    {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if constexpr (LEVELS) tile[k] += pair[k] + sum[k];
+            else all[k] += sum[k];
+        }
+        if constexpr (LEVELS) {
+            if ((i & 14) == 14) flush();         // (uniform)
+        }
+    }
+    // an even batch without an odd one after it
+    __device__ __forceinline__ void last_even()
+    {
+        if constexpr (LEVELS) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) tile[k] += pair[k];
+        }
+    }
+    __device__ __forceinline__ void flush()
+    {
+        if constexpr (LEVELS) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                all[k] += tile[k];
+                tile[k] = 0.0f;
+            }
+        }
+    }
+};
+
 // lanes that hold a row of F columns, four floats each, in the kernels whose waves walk several rows; 0: one row per wave
 inline int row_lanes(int64_t F) { return F <= 32 ? 8 : F <= 64 ? 16 : F <= 128 ? 32 : 64; }
 

@@ -807,6 +807,7 @@ extern "C" int retexo_plan_set_degrees(retexo_plan* plan, const int32_t* d_deg, 
     if (!plan) return RETEXO_E_NULL;
     if (plan->N > 0 && !d_deg) return RETEXO_E_NULL;
     if (plan->N == 0) return RETEXO_OK;
+    plan->degrees_set = true;
     set_degrees_kernel<<<dim3((unsigned)((plan->N + kThreads - 1) / kThreads)), dim3(kThreads), 0, (hipStream_t)stream>>>(
         plan->N, d_deg, plan->deg, plan->dinv);
     if (hipGetLastError() != hipSuccess) return RETEXO_E_HIP;

@@ -1,0 +1,54 @@
+"""How close the sums over long lists of entries are: terms of one sign, where one running sum over 300 of them is off by 2.4e-7
+(2-norm).  Sums of 16, of 128 and of those make roundings whose partial sums' squares add up to at most 3.2 times the total's, each
+off by 2^-24 / sqrt(3) of its partial sum in the mean: 6.2e-8, and half of that again for weights and the mean's division."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import storage as ost
+from paper_2302_13053_amd import harness as Hn
+from paper_2302_13053_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+BOUND = 9.3e-8
+
+
+@pytest.fixture(scope="module")
+def graphs():
+    """Rows of about 300 entries, of up to 3,000 (shared by a workgroup from some hundred on), and of 1 to 60."""
+    specs = {"even": (3001, *wl.random_pairs(3001, 450000, 1, skew=1.0)), "skewed": (9001, *wl.random_pairs(9001, 600000, 2, skew=3.0)),
+             "short": (20011, *wl.random_pairs(20011, 300000, 3, skew=1.0))}
+    out = {}
+    for name, (n, s, d) in specs.items():
+        out[name] = (Hn.make_plan(Hn.csr_from_coo(Hn.dev(s), Hn.dev(d), n, False)), *oracle.csr_from_coo(s, d, n, False))
+    yield out
+    for g, _, _ in out.values():
+        g.destroy()
+
+
+@pytest.mark.parametrize("name,F", [("even", 24), ("even", 64), ("skewed", 24), ("skewed", 64), ("skewed", 128), ("skewed", 200), ("short", 24),
+                                    ("short", 64), ("short", 200)])
+@pytest.mark.parametrize("mode", ["sum", "mean", "gcn_sym"])
+@pytest.mark.parametrize("fmt", ["fp32", "bf16", "fp16"])
+def test_sums(graphs, name, F, mode, fmt):
+    """Row groups of every lane count, slabs of them, whole rows over tables that do not fit an L2."""
+    g, rp, ci = graphs[name]
+    n, ld = g.n_nodes, (F + 7) // 8 * 8
+    if fmt != "fp32" and F > 128:
+        pytest.skip("whole rows of a 16-bit table are one running sum")
+    Zh = np.abs(wl.random_matrix(n, F, F)) + np.float32(0.01)
+    if fmt == "fp32":
+        Z = torch.zeros(n, ld, device="cuda")
+        Z[:, :F] = torch.from_numpy(Zh)
+        got = Hn.aggregate(g, mode, Z, F)
+    else:
+        bits = ost.store(Zh, fmt)
+        Zh = ost.load(bits, fmt)
+        Z = torch.zeros(n, ld, dtype=torch.int16, device="cuda")
+        Z[:, :F] = torch.from_numpy(bits.view(np.int16))
+        got = Hn.aggregate_stored(g, mode, Z, F, fmt)
+    want = oracle.aggregate(mode, rp, ci, Zh, F)
+    err = np.linalg.norm(got.cpu().numpy()[:, :F] - want) / np.linalg.norm(want)
+    assert err <= BOUND, "%.2e" % err
