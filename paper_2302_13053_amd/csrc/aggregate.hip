@@ -2121,6 +2121,25 @@ bool dense_for_ranges(const AggCall& c)
     return p->part_ptr || (p->nnz >= 32 * p->N && p->N * c.ldz * 4 > (4ll << 20));
 }
 
+// Times the mean row that the longest one may have for the rows to count as alike: then no node is gathered much more often than
+// others, nothing but a range's slab stays in an L2, and a range's launches end together.  Over rows on whole 128-byte lines, mean in
+// us, ranges against the others: 200,000 nodes of 100 entries (longest 151) 64 columns 444 and 645, 32 columns 235 and 294; 228,965 of
+// 165 (592), 32 columns 343 and 529; 60,000 of 40 (79), 256 columns 200 and 259; 64,053 of 54 (91), 192 columns 239 and 325; with
+// weights 200,000 of 100, 256 columns 2,300 and 2,637.  The other way, longest rows of twenty times the mean and more: see
+// linear_route.  Tables of many ranges are faster in row groups whatever the rows (1,000,000 of 100, longest 154, 64 columns 5,391 and
+// 3,461), and so are narrow rows of few nodes.  The lines are where 12,662 drawn calls over dense graphs change sides, by nodes and
+// columns: against the kernels that took them before row groups 1,054 were more than 4 % slower, at most by a factor of 2.1, and 222 are,
+// all of them together 0.912 of the time and 0.901.
+int64_t alike_rows(int64_t N, int64_t nnz, int64_t F, bool weighted)
+{
+    const bool long_rows = nnz >= 100 * N;
+    if (N <= 32768) return F > 64 ? 3 : 0;
+    if (N <= 65536) return F <= 128 ? 6 : 10;
+    if (N <= 131072) return F <= 32 ? 8 : weighted ? 10 : 20;
+    if (N <= 262144) return !weighted ? (F <= 32 ? 10 : 20) : long_rows || F <= 16 ? 10 : F <= 64 ? 0 : 3;
+    return N <= 524288 && long_rows && !weighted ? 10 : 0;
+}
+
 // Which kernels a sum, mean or gcn_sym takes whose rows are gathered four floats at a time: the range walk over narrow slabs, row
 // groups of `lanes` lanes over slabs of 4 * lanes columns, or (neither) whole rows.
 struct LinearRoute {
@@ -2143,7 +2162,8 @@ struct LinearRoute {
 //  entries on (20,000 of 200 112 and 123; 22,000 of 30, 96 columns 44 and 35).  Graphs that fit anyway in slabs of 128:
 //  10,000 of 400, 256 columns 152 and 189.  With weights, read again for every slab, where all of them stay in an L2: 200,000
 //  of 100, 256 columns 2,305 and 2,779, 30,000 of 40 111 and 132 (slabs of 128; 122 of 64), but 1,000,000 of 20 3,837 and 3,176.
-//  Slabs are taken where they are three quarters full (6,051 of 223, 192 columns in two of 128 85 and 76).
+//  Slabs are taken where they are three quarters full (6,051 of 223, 192 columns in two of 128 85 and 76) and, on graphs that are not
+//  dense, over rows on whole 128-byte lines, of which each slab otherwise touches one more (210,122 of 29, 260 columns 1,299 and 972).
 LinearRoute linear_route(const AggCall& c, int vec, int parts)
 {
     const retexo_plan* p = c.plan;
@@ -2156,6 +2176,8 @@ LinearRoute linear_route(const AggCall& c, int vec, int parts)
     if (p->part_ptr && opt.parts >= 0) return ranges;              // (the caller said how many)
     const bool dense = dense_for_ranges(c);
     auto mean_is = [&](int64_t entries) { return nnz >= entries * N; };
+    const bool lines = aligned_for(c.Z, c.ldz, 32);                 // rows on whole 128-byte lines
+    if (dense && lines && p->max_degree * N < alike_rows(N, nnz, F, weighted) * nnz) return ranges;
     if (dense && N >= 16384 && N * 128 <= parts * (64ll << 20) && 2 * nnz >= 25 * N * parts) {
         const bool enough = N >= 24000 || work >= 1200000000ll || mean_is(300);
         if (F >= 100 ? enough && work >= 700000000ll && (mean_is(160) || mean_is((weighted ? 25 : 15) * parts))
@@ -2171,7 +2193,7 @@ LinearRoute linear_route(const AggCall& c, int vec, int parts)
         return dense && !(weighted && parts == 1) ? ranges : whole;
     auto in_slabs = [&](int lanes) {
         const int64_t slabs = (F + 4 * lanes - 1) / (4 * lanes);
-        if (4 * F >= 3 * slabs * (4 * lanes)) return LinearRoute{false, lanes};
+        if (4 * F >= 3 * slabs * (4 * lanes) && (dense || lines || F <= 128)) return LinearRoute{false, lanes};
         return dense && mean_is(100) ? ranges : whole;
     };
     if (F <= 64) return {false, F <= 32 ? 8 : 16};

@@ -1459,11 +1459,14 @@ bool aligned_rows(const void* p, int64_t ld_elems, int bytes_per_elem)
 //  Rows that 16-byte loads can't take whole (an element per lane in whole rows): always, 1,000,000 nodes of 20 entries, 30
 //  columns 521 and 639, 232,965 of 490 1,075 and 2,430; 60,000 of 250, 130 columns 381 and 767, 250 columns 838 and 1,039.
 //  Others of up to 128 columns instead of whole rows: 1,000,000 of 20, 32 columns 395 and 745, 64 columns 432 and 790, 128
-//  columns 778 and 960; 100,000 of 8 15 and 48, 22 and 49, 40 and 51; 30,000 of 300, 64 columns 55 and 255.  Wider ones of
-//  graphs with a few long rows, which are walked here beside the others (19,677 of 30, longest 1,743, 512 columns 87 and 310;
-//  172,021 of 10, 608 columns 492 and 1,166), but 1,330,144 of 5, 512 columns 2,846 and 2,385, and with all rows alike 1,000,000
-//  of 8, 256 columns 947 and 912: the line is where drawn calls stop to gain (0.53
-//  of the time at 65,000 nodes, 0.83 at 260,000, 1.03 at 520,000).
+//  columns 778 and 960; 100,000 of 8 15 and 48, 22 and 49, 40 and 51; 30,000 of 300, 64 columns 55 and 255.  Wider ones where a few
+//  long rows, which are walked here beside the others, outlast the rest (19,677 of 30, longest 1,743, 512 columns 87 and 310;
+//  172,021 of 10, 608 columns 492 and 1,166), not where all are alike (1,000,000 of 8, 256 columns 947 and 912; 78,691 of 6, longest
+//  18, 288 columns 83 and 57; 66,237 of 7, longest 94, 342 columns with weights 86 and 67): from a longest row of 48 entries and of
+//  1/300 of the nodes on, 1/100 where the last slab is less than three quarters of the columns; up to 250,000 nodes.  Of 16,248 drawn calls
+//  over 16-bit tables 806 were more than 4 % slower than in whole rows when all of up to 250,000 nodes came here, 83 are.
+//  With weights, which wait for ids, from 8,192 nodes on, or a longest row of 48 (of up to 64 columns) or a mean of 100 (above): 2,340
+//  of 14, longest 28, 32 columns 5.9 and 4.8; 3,000 of 60, 128 columns 10.4 and 9.9.
 //  Instead of the range walk where a row's share of a range is short: 600,000 of 120 (7 per range) 1,127 and 1,448, 1,003,546
 //  of 80 (5), 64 columns 1,483 and 3,670, 576,484 of 113 (7), 96 columns 2,069 and 3,946; the other way 400,000 of 150 (19) 800
 //  and 678, 150,000 of 200 (50), 64 columns 355 and 251, with weights 386,048 of 112 (14) 1,012 and 832.  Not in one range, which
@@ -1476,12 +1479,15 @@ int rows_lanes(const StoredCall& c, bool wide, bool ranges, int parts)
     const bool weighted = c.mode == RETEXO_GCN_SYM;
     if (opt.slab_cols != 0 || opt.max_vec < 4 || (p->part_ptr && opt.parts >= 0)) return 0;      // (the caller said how)
     const int lanes = F <= 32 ? 4 : F <= 64 ? 8 : F <= 128 ? 16 : 32;
-    if (weighted && F > 64 && N < 8192 && nnz < 100 * N) return 0;      // (weights wait for ids: 3,000 of 60, 128 columns 10.4 and 9.9)
+    if (weighted && N < 8192 && (F > 64 ? nnz < 100 * N : p->max_degree < 48)) return 0;
     if (!wide) {
         // eight elements at 4-byte addresses, none past a row's end: what lies there may not be the caller's
         return (uintptr_t)c.Z % 4 == 0 && c.ldz % 2 == 0 && F >= 8 && F % 2 == 0 ? lanes : 0;
     }
-    if (!ranges) return F <= 128 || N < 250000 ? lanes : 0;
+    if (!ranges) {
+        const bool filled = 4 * F >= 3 * align_up(F, 256);
+        return F <= 128 || (N < 250000 && p->max_degree >= 48 && (filled ? 300 : 100) * (int64_t)p->max_degree >= N) ? lanes : 0;
+    }
     if (F > 128) return 0;
     if (parts > 1) return nnz < N * parts * (weighted ? 12 : F > 32 ? 14 : 10) ? lanes : 0;
     return F > 64 && N >= 600000 ? lanes : 0;

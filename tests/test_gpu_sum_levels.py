@@ -35,7 +35,7 @@ def graphs():
 def test_sums(graphs, name, F, mode, fmt):
     """Row groups of every lane count, slabs of them, whole rows over tables that do not fit an L2."""
     g, rp, ci = graphs[name]
-    n, ld = g.n_nodes, (F + 7) // 8 * 8
+    n, ld = g.n_nodes, (F + 31) // 32 * 32
     if fmt != "fp32" and F > 128:
         pytest.skip("whole rows of a 16-bit table are one running sum")
     Zh = np.abs(wl.random_matrix(n, F, F)) + np.float32(0.01)
