@@ -210,9 +210,11 @@ __device__ __forceinline__ void decide_near_zero(f32x16 (&acc)[TN], const float 
 // take 128 registers): four waves, or eight for the tiles wider than 128; any alignment and leading dimension.
 // MASKED (the backward of a ReLU layer) also leaves the column sums of every 128-row block, which the bias gradient is made
 // of, as long as the values are in registers: a pass of its own over them takes 45 us for 232,965 x 256.
+// HALVES: the halves of K apart, for one workgroup per compute unit, which has the registers: a layer's input is often [self |
+// aggregate], and terms of unlike size round each other (in_halves).
 template <int BN> constexpr int transform_waves = BN > 128 ? 8 : 4;
-template <int BN, bool MASKED, bool KEEP_SIGN>
-__global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void transform_kernel(
+template <int BN, bool MASKED, bool KEEP_SIGN, bool HALVES>
+__global__ __launch_bounds__(64 * transform_waves<BN>, HALVES ? 1 : BN <= 64 ? 3 : 2) void transform_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
     float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm, float* __restrict__ colsums)
@@ -247,19 +249,20 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void tr
 #pragma unroll
     for (int v = 0; v < HP; ++v) ph[v] = H + min(m0 + hr + 16 * WAVES * v, N - 1) * ldh + hk;
     f32x4 ra[SETS][HP];
+    int k0 = 0, K = HALVES ? D_in / 2 : D_in, nk = (K + kTileK - 1) / kTileK;      // the k of the sums at hand: [k0, k0 + K)
     auto fetch_h = [&](int kt, int v, auto set_tag, auto edge) {
         constexpr int set = decltype(set_tag)::value;
         const float* p = ph[v] + kt * kTileK;
-        if (!decltype(edge)::value || (kt + 1) * kTileK <= D_in) {
+        if (!decltype(edge)::value || (kt + 1) * kTileK <= K) {
             ra[set][v] = *reinterpret_cast<const f32x4_any*>(p);
         } else {
-            const int last = D_in - 1 - kt * kTileK - hk;        // the row's last element, from p on (may lie before it)
+            const int last = K - 1 - kt * kTileK - hk;           // the row's last element, from p on (may lie before it)
 #pragma unroll
             for (int q = 0; q < 4; ++q) ra[set][v][q] = p[min(q, last)];
         }
     };
     WStage sw;
-    sw.init(W, D_out, 0, D_in, n0, D_out, wave, lane);
+    sw.init(W, D_out, 0, K, n0, D_out, wave, lane);
 
     float bv[TN];
 #pragma unroll
@@ -268,7 +271,6 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void tr
         bv[j] = (bias && col < D_out) ? bias[col] : 0.0f;
     }
 
-    const int nk = (D_in + kTileK - 1) / kTileK;
     constexpr int A_MICROS = HP * 4, MICROS = A_MICROS + WStage::count * WStage::steps;
     typedef uint32_t part_t __attribute__((ext_vector_type(2)));
     part_t part_h[3];
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void tr
         u32x4* base = lds + buf * T::units;
         if constexpr (EDGE && m < A_MICROS && m % 4 == 0) {          // what lies past the row's end counts as zero (see KMajorStage)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) ra[set][m / 4][q] = kt * kTileK + hk + q < D_in ? ra[set][m / 4][q] : 0.0f;
+            for (int q = 0; q < 4; ++q) ra[set][m / 4][q] = kt * kTileK + hk + q < K ? ra[set][m / 4][q] : 0.0f;
         }
         if constexpr (KEEP_SIGN && m < A_MICROS && m % 4 == 0) {
 #pragma unroll
@@ -313,11 +315,35 @@ __global__ __launch_bounds__(64 * transform_waves<BN>, BN <= 64 ? 3 : 2) void tr
         for (int v = 0; v < HP; ++v) fetch_h(kt, v, set_tag, edge);
         each<WStage::count>([&](auto i) { sw.template fetch<decltype(i)::value, decltype(set_tag)::value, true>(kt); });
     };
-    fetch_all(0, first);
-    if (SETS == 2 && nk > 1) fetch_all(1, std::integral_constant<int, SETS - 1>{});
-    each<MICROS>([&](auto m) { micro(m, first, 0, edge); });
-    __syncthreads();
-    split_k_loop<TN, BM, BN, MICROS, SETS>(acc, lds, nk, D_in / kTileK, a0, b0, lane, micro);
+    f32x16 early[HALVES ? TN : 1];                       // the first half's sums
+    for (int half = 0;; ++half) {
+        fetch_all(0, first);
+        if (SETS == 2 && nk > 1) fetch_all(1, std::integral_constant<int, SETS - 1>{});
+        each<MICROS>([&](auto m) { micro(m, first, 0, edge); });
+        __syncthreads();
+        split_k_loop<TN, BM, BN, MICROS, SETS>(acc, lds, nk, K / kTileK, a0, b0, lane, micro);
+        if (!HALVES || half == 1) break;
+#pragma unroll
+        for (int j = 0; j < (HALVES ? TN : 1); ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                early[j][r] = acc[j][r];
+                acc[j][r] = 0.0f;
+            }
+        k0 = K;
+        K = D_in - K;
+        nk = (K + kTileK - 1) / kTileK;
+#pragma unroll
+        for (int v = 0; v < HP; ++v) ph[v] += k0;
+        sw.init(W, D_out, k0, D_in, n0, D_out, wave, lane);
+        __syncthreads();                                 // every wave is done with the last tile
+    }
+    if constexpr (HALVES) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[j][r] += early[j][r];
+    }
 
     each<TN>([&](auto at) {
         constexpr int j = decltype(at)::value;
@@ -513,30 +539,32 @@ __global__ __launch_bounds__(512) void transform_few_rows_kernel(
 // The same for long sums: 32 x 32 tiles, sixteen waves, operands through LDS.  The kernel above asks for sixteen
 // bytes of 32 rows at a time and for single floats of W, which keeps the address units busy for as long as the matrix cores (2,708
 // x 2,866 -> 64: 28.2 us; without its products, without W or without H 20.6, 20.6, 18.6).  Here chunks of 128 k come in whole
-// lines, two ahead, and each wave multiplies eight k of every chunk: 23.7 us there (27.4 in the same loop), 1,433 columns 15.2 ->
-// 13.8, 2,866 -> 256 80 -> 62, 300 -> 200 13.7 -> 11.8.  Now bound by the float32 instruction.  Shorter sums stay above: where
-// every compute unit has a tile at the most 500 columns 6.5 -> 6.7, 128 3.3 -> 3.8.
-constexpr int kStagedOne = 768, kStagedMany = 256;       // k from which it is taken, up to 256 tiles and more
+// lines, two ahead, and each wave multiplies eight k of every chunk: 24.3 us there (27.9), 1,433 columns 15.7 ->
+// 14.4, 2,866 -> 256 82 -> 71.  Its products are 10 of the 24 us (1,433 float32 instructions of 64 cycles per tile, over four
+// SIMDs); the rest is 23 chunks with a barrier and a round trip through LDS each.  Less work stays above: 2,708 x 1,433 -> 7 12.4
+// and 14.0, 2,000 x 1,300 -> 64 11.6 and 12.9, 1,400 x 2,500 -> 32 20.1 and 21.2; where compute units have two tiles, 2,708 x 500 ->
+// 256 18.2 and 19.5, 8,000 x 600 -> 41 15.5 and 17.1, 2,708 x 1,400 -> 256 42.7 and 40.6, 1,053 x 1,421 -> 765 46.6 and 53.9.
+constexpr int64_t kStagedWork = 250000;      // tiles times k from which it is taken, up to 256 tiles
+constexpr int kStagedMany = 1200;            // k from which it is taken, up to kStagedMost tiles
+constexpr int64_t kStagedMost = 700;
 template <bool MASKED, bool HALVES>
-__global__ __launch_bounds__(1024) void transform_few_staged_kernel(
+__global__ __launch_bounds__(1024, HALVES ? 4 : 8) void transform_few_staged_kernel(
     int64_t N, int D_in, int D_out, const float* __restrict__ H, int64_t ldh,
     const float* __restrict__ W, const float* __restrict__ bias, int relu,
     float* __restrict__ Z, int64_t ldz, const float* __restrict__ mask, int64_t ldm, float* __restrict__ colsums)
 {
     constexpr int NW = 16, KC = 128, SLICE = KC / NW;
     constexpr int PH = KC + 4, PW = 36;          // row pitches in LDS: a wave's reads meet no bank twice
-    union Shared {
-        struct { float h[2][32 * PH], w[2][KC * PW]; };
-        float part[NW / 2][32][33];
-        float sums[1024];
-    };
-    __shared__ __align__(16) Shared sh;
+    struct Operands { float h[32 * PH], w[KC * PW]; };
+    typedef float parts_t[NW / 2][32][33];       // partial tiles, over the operands of a chunk
+    static_assert(sizeof(parts_t) <= sizeof(Operands), "they fit there");
+    __shared__ __align__(16) Operands sh[2];
+    __shared__ float early[HALVES ? 1 : 1024];   // the first half's sums
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lrow = lane & 31, lk = lane >> 5;
     const int64_t m0 = (int64_t)blockIdx.x * 32;
     const int n0 = blockIdx.y * 32;
-    const int chunks = (D_in + KC - 1) / KC;
     // A thread's piece of a chunk: four k of a row of H, four columns of a row of W.  All are loaded without a branch (the
     // loads of two chunks stay in flight): a piece that reaches over the end of its row is loaded from four floats before
     // that (D_in, D_out >= 4) and moved into place, with zeroes behind it, on its way to LDS.
@@ -553,80 +581,103 @@ __global__ __launch_bounds__(1024) void transform_few_staged_kernel(
         return r;
     };
 
-    // HALVES: the halves of a sum apart, where the registers cost nothing (one workgroup per compute unit; otherwise 2,708 x 2,866
-    // -> 256 62 -> 69 us).  A layer's input is often [self | aggregate], and terms of unlike size round each other: 2,866 -> 64 on
-    // such an input, 1 % of it not zero, 7.8e-8 off 64 bits without, 6.9e-8 so (the kernel above 7.4e-8).
+    // The halves of a sum apart: a layer's input is often [self | aggregate], and terms of unlike size round each other ([self | mean
+    // of 12 neighbours], 2 % of self not zero, 2,866 -> 256, error against 64 bits 1.3e-7 in one sum, 7.2e-8 so, the kernel above
+    // 8.6e-8).  HALVES: in registers of their own, where those cost nothing (one workgroup per compute unit; otherwise 2,708 x 2,866
+    // -> 256 62 -> 69 us); without, one half after the other.
+    const int half = D_in / 8 * 4;               // (whole pieces)
+    int k_begin = 0, k_end = HALVES ? D_in : half, chunks = (k_end + KC - 1) / KC;
     f32x16 acc, first;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = first[r] = 0.0f;
+    parts_t& part = *reinterpret_cast<parts_t*>(&sh[0]);
+    auto put = [&](int slot) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[slot][8 * (r / 4) + 4 * lk + (r % 4)][lrow] = acc[r];
+    };
+    // the sixteen waves' partial tiles in `acc`, added in pairs (the fewest roundings): this thread's output, row tid / 32, column
+    // tid % 32.  Begins where no wave uses the operands, ends with a barrier.
+    auto reduce = [&]() {
+        if (wave >= NW / 2) put(wave - NW / 2);
+        __syncthreads();
+        if (wave < NW / 2) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] += part[wave][8 * (r / 4) + 4 * lk + (r % 4)][lrow];
+        }
+        __syncthreads();
+        if (wave < NW / 2) put(wave);
+        __syncthreads();
+        float t[NW / 2];
+#pragma unroll
+        for (int w = 0; w < NW / 2; ++w) t[w] = part[w][tid / 32][tid % 32];
+#pragma unroll
+        for (int w = NW / 4; w >= 1; w /= 2)
+#pragma unroll
+            for (int i = 0; i < w; ++i) t[i] += t[i + w];
+        __syncthreads();
+        return t[0];
+    };
     f32x4 rh[2], rw[2];
     auto load = [&](int ch, int slot) {
-        const int k0 = min(ch, chunks - 1) * KC;
+        const int k0 = k_begin + min(ch, chunks - 1) * KC;
         rh[slot] = *reinterpret_cast<const f32x4_any*>(hp + min(k0 + hk, D_in - 4));
         rw[slot] = *reinterpret_cast<const f32x4_any*>(wp + (int64_t)min(k0 + wk, D_in - 1) * D_out);
     };
-    // chunk `ch`, which the registers of `slot` hold, goes to its LDS buffer (last read two chunks ago: the barrier of the
-    // chunk between lies behind every wave by then); the chunk two ahead takes the registers
-    auto chunk = [&](int ch, int slot, f32x16& to) {
+    // one chunk of the k of [k_begin, k_end): the registers of `slot` go to its LDS buffer (last read two chunks ago: the barrier of
+    // the chunk between lies behind every wave by then); the chunk two ahead takes the registers
+    auto chunk = [&](int ch, int slot) {
         f32x4 h = rh[slot], w = rw[slot];
         if (ch == chunks - 1) {                  // (uniform)
-            h = moved(h, min(max(ch * KC + hk + 4 - D_in, 0), 4));
-            w = ch * KC + wk < D_in ? w : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            const int k = k_begin + ch * KC;
+            h = moved(h, k + hk >= k_end ? 4 : max(k + hk + 4 - D_in, 0));
+            w = k + wk < k_end ? w : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         }
         if (!whole_columns) w = moved(w, w_over);
-        *reinterpret_cast<f32x4*>(&sh.h[slot][hr * PH + hk]) = h;
-        *reinterpret_cast<f32x4*>(&sh.w[slot][wk * PW + (wc - n0)]) = w;
+        *reinterpret_cast<f32x4*>(&sh[slot].h[hr * PH + hk]) = h;
+        *reinterpret_cast<f32x4*>(&sh[slot].w[wk * PW + (wc - n0)]) = w;
         load(ch + 2, slot);
         __syncthreads();
-        const int kb = wave * SLICE + 4 * lk;    // lower half-wave: the slice's first four k, upper: the others
-        const f32x4 a = *reinterpret_cast<const f32x4*>(&sh.h[slot][lrow * PH + kb]);
+        auto multiply = [&](f32x16& to) {
+            const int kb = wave * SLICE + 4 * lk;    // lower half-wave: the slice's first four k, upper: the others
+            const f32x4 a = *reinterpret_cast<const f32x4*>(&sh[slot].h[lrow * PH + kb]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            to = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], sh.w[slot][(kb + q) * PW + lrow], to, 0, 0, 0);
+            for (int q = 0; q < 4; ++q)
+                to = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], sh[slot].w[(kb + q) * PW + lrow], to, 0, 0, 0);
+        };
+        if (HALVES && ch * KC + wave * SLICE < half) multiply(first);      // (uniform over the wave)
+        else multiply(acc);
     };
-    load(0, 0);
-    load(1, 1);
-    int ch = 0;
-    for (const int half = HALVES ? chunks / 4 * 2 : 0; ch < half; ch += 2) {
-        chunk(ch, 0, first);
-        chunk(ch + 1, 1, first);
-    }
-    for (; ch + 1 < chunks; ch += 2) {
-        chunk(ch, 0, acc);
-        chunk(ch + 1, 1, acc);
-    }
-    if (ch < chunks) chunk(ch, 0, acc);
-    if constexpr (HALVES) {
+    float x;
+    for (;;) {
+        load(0, 0);
+        load(1, 1);
+        int ch = 0;
+        for (; ch + 1 < chunks; ch += 2) {
+            chunk(ch, 0);
+            chunk(ch + 1, 1);
+        }
+        if (ch < chunks) chunk(ch, 0);
+        if constexpr (HALVES) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] += first[r];
+            for (int r = 0; r < 16; ++r) acc[r] += first[r];
+        }
+        __syncthreads();                         // every wave is done with the operands
+        x = reduce();
+        if (k_end == D_in) break;
+        if constexpr (!HALVES) early[tid] = x;
+        k_begin = k_end;
+        k_end = D_in;
+        chunks = (k_end - k_begin + KC - 1) / KC;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
     }
 
-    __syncthreads();                             // the partial tiles lie over the operands
-    auto put = [&](int slot) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sh.part[slot][8 * (r / 4) + 4 * lk + (r % 4)][lrow] = acc[r];
-    };
-    if (wave >= NW / 2) put(wave - NW / 2);
-    __syncthreads();
-    if (wave < NW / 2) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] += sh.part[wave][8 * (r / 4) + 4 * lk + (r % 4)][lrow];
-    }
-    __syncthreads();
-    if (wave < NW / 2) put(wave);
-    __syncthreads();
-
-    const int r = tid / 32, c = tid % 32;        // one output per thread
+    if constexpr (!HALVES) x += early[tid];
+    int out = tid;                               // one output per thread (its place is not kept in registers meanwhile)
+    asm("" : "+v"(out));
+    const int r = out / 32, c = out % 32;
     const int64_t orow = m0 + r;
     const int ocol = n0 + c;
-    float t[NW / 2];                             // added in pairs: the fewest roundings
-#pragma unroll
-    for (int w = 0; w < NW / 2; ++w) t[w] = sh.part[w][r][c];
-#pragma unroll
-    for (int w = NW / 4; w >= 1; w /= 2)
-#pragma unroll
-        for (int i = 0; i < w; ++i) t[i] += t[i + w];
-    float x = t[0];
     const bool inside = orow < N && ocol < D_out;
     if (inside) {
         x += bias ? bias[ocol] : 0.0f;
@@ -635,13 +686,13 @@ __global__ __launch_bounds__(1024) void transform_few_staged_kernel(
         Z[orow * ldz + ocol] = x;
     }
     if constexpr (MASKED) {                      // column sums of the 32 rows, as in the block kernel
-        __syncthreads();
-        sh.sums[tid] = inside ? x : 0.0f;
+        float* sums = &sh[0].h[0];
+        sums[tid] = inside ? x : 0.0f;
         __syncthreads();
         if (tid < 32 && n0 + tid < D_out) {
             float t[4] = {};
 #pragma unroll
-            for (int i = 0; i < 32; ++i) t[i % 4] += sh.sums[i * 32 + tid];
+            for (int i = 0; i < 32; ++i) t[i % 4] += sums[i * 32 + tid];
             colsums[(int64_t)blockIdx.x * D_out + n0 + tid] = (t[0] + t[1]) + (t[2] + t[3]);
         }
     }
@@ -662,6 +713,42 @@ __global__ void bias_rows_kernel(int64_t N, int D_out, const float* __restrict__
     }
 }
 
+// Which kernel a shape takes, by the shape only, never by alignment, so that one shape always takes one order of additions.
+//  Few rows: fewer than 128 blocks, and up to 832 tiles of 32 x 32 or 512 workgroups of 64 columns, two for each compute unit.  A
+//  compute unit takes some 9 ns per k and tile there, and 29 to 59 ns per k for one block of 128 rows, whose loop waits for memory
+//  when it is alone: 8,000 x 600 -> 41 (500 tiles) 15.5 us and 20.9, 15,488 x 212 -> 64 (968 tiles, 484 workgroups) 11.0 and 13.3,
+//  14,500 x 32 -> 64 5.7 and 5.3; with a third workgroup 9,070 x 2,219 -> 96 (852, 568) 95.8 and 70, 4,227 x 882 -> 216 (931, 532)
+//  44.2 and 31.9, 2,708 x 32 -> 500 (1,360, 680) 8.2 and 6.9.  From 128 blocks the split products stay in one sum, which is a quarter
+//  closer on inputs of one size, although few rows are faster (20,000 x 500 -> 20 14.7 and 18.3).  (The "transform_few_blocks"
+//  setting, unless it is 128: fewer blocks than it says, however many tiles.)
+//  Blocks: as wide as the output up to 256 columns; narrower, so that H is read more than once, where that gives up to 256 blocks
+//  instead of fewer (14,000 x 500 -> 256 in 110 blocks 37.3, 220 of 128 columns 30.4; 8,000 x 1,000 -> 256 in 63 65.3, 252 of 64
+//  38.9; 19,717 x 500 -> 256 in 155 36.6, 310 of 128 42.6), and half as wide where the widest are a few more than compute units
+//  (2,708 x 64 -> 2,866 in 264 19.1, 506 of 128 12.9; 40,000 x 256 -> 256 in 313 44.6, 626 40.3), up to three of the narrower for
+//  each (49,542 x 86 -> 256 in 388 26.8, 776 of 128 30.2).
+int64_t block_width(int64_t D_out) { return D_out <= 32 ? 32 : D_out <= 64 ? 64 : D_out <= 128 ? 128 : D_out <= 192 ? 192 : 256; }
+int64_t blocks_of(int64_t N, int64_t D_out, int64_t bn) { return (N + 127) / 128 * ((D_out + bn - 1) / bn); }
+bool takes_few_rows(int64_t N, int64_t D_out)
+{
+    const int64_t few = agg_options().few_blocks, gx = (N + 31) / 32;
+    if (blocks_of(N, D_out, block_width(D_out)) >= few) return false;
+    return few != 128 || gx * ((D_out + 31) / 32) <= 832 || gx * ((D_out + 63) / 64) <= 512;
+}
+// The split products of shapes that few rows took before: the halves of K apart (see transform_kernel).  [self | mean of 12
+// neighbours], 2 % of self not zero, 2,866 columns, error against 64 bits: few rows 8.6e-8, one sum 1.9e-7, so 5.4e-8; rectified
+// normal columns 2.8e-7, 3.2e-7, 1.7e-7; of 127 columns 5.2e-8, 7.3e-8, 3.5e-8, of 16 2.9e-8, 3.4e-8, 2.7e-8.  5,000 x 500 -> 300
+// 20.8 us in one sum, 23.1 so; 8,000 x 1,000 -> 256 38.5 and 42.0; 2,708 x 64 -> 500 6.6 and 8.3 (few rows 9.8).
+bool in_halves(int64_t N, int64_t D_in, int64_t D_out) { return D_in >= 2 && blocks_of(N, D_out, block_width(D_out)) < 128; }
+int64_t block_width_for(int64_t N, int64_t D_out)
+{
+    const int64_t widest = block_width(D_out), blocks = blocks_of(N, D_out, widest);
+    if (blocks > 256) return widest == 256 && blocks <= 384 ? 128 : widest;
+    int64_t bn = widest;
+    for (int64_t narrower : {128, 64, 32})
+        if (narrower < bn && blocks_of(N, D_out, narrower) <= 256) bn = narrower;
+    return bn;
+}
+
 template <int BN, bool MASKED>
 void launch(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh, const float* W,
             const float* b, bool relu, float* Z, int64_t ldz, const float* mask, int64_t ldm, bool keep_sign,
@@ -669,13 +756,24 @@ void launch(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh,
 {
     const dim3 grid((unsigned)((N + 127) / 128), (unsigned)((D_out + BN - 1) / BN)), block(64 * transform_waves<BN>);
     const int r = relu ? 1 : 0;
-    if constexpr (!MASKED) {
-        if (keep_sign) {
-            transform_kernel<BN, false, true><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
-            return;
+    auto go = [&](auto sign, auto halves) {
+        transform_kernel<BN, MASKED, decltype(sign)::value, decltype(halves)::value><<<grid, block, 0, stream>>>(
+            N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    if constexpr (BN <= 128) {                   // (wider ones are not for so few blocks)
+        if (in_halves(N, D_in, D_out)) {
+            if constexpr (!MASKED) {
+                if (keep_sign) return go(yes, yes);
+            }
+            return go(no, yes);
         }
     }
-    transform_kernel<BN, MASKED, false><<<grid, block, 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
+    if constexpr (!MASKED) {
+        if (keep_sign) return go(yes, no);
+    }
+    go(no, no);
 }
 
 template <bool MASKED>
@@ -685,8 +783,9 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
 {
     const int r = relu ? 1 : 0;
     const unsigned gx = (unsigned)((N + 31) / 32);
-    const bool many = gx * ((D_out + 31) / 32) > 256;
-    if (D_out >= 4 && D_in >= (many ? kStagedMany : kStagedOne)) {
+    const int64_t tiles = gx * ((D_out + 31) / 32);
+    const bool many = tiles > 256;
+    if (D_out >= 4 && (many ? D_in >= kStagedMany && tiles <= kStagedMost : tiles * D_in >= kStagedWork)) {
         const dim3 grid(gx, (unsigned)((D_out + 31) / 32));
         if (many) transform_few_staged_kernel<MASKED, false><<<grid, dim3(1024), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
         else      transform_few_staged_kernel<MASKED, true><<<grid, dim3(1024), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
@@ -700,34 +799,6 @@ void launch_few_rows(int64_t N, int64_t D_in, int64_t D_out, const float* H, int
         dim3 grid(gx, (unsigned)((D_out + 63) / 64));
         transform_few_rows_kernel<2, MASKED><<<grid, dim3(512), 0, stream>>>(N, (int)D_in, (int)D_out, H, ldh, W, b, r, Z, ldz, mask, ldm, colsums);
     }
-}
-
-// Which kernel a shape takes, by the shape only, never by alignment, so that one shape always takes one order of additions.
-//  Few rows: up to 832 tiles of 32 x 32 and fewer than 128 blocks.  A compute unit takes some 9 ns per k and tile there, and
-//  29 to 59 ns per k for one block of 128 rows, whose loop waits for memory when it is alone: 8,000 x 600 -> 41 (500 tiles)
-//  12.6 us and 20.9, 2,708 x 2,866 -> 256 (680) 61.8 and 83.9, 4,000 x 2,000 -> 200 (875) 59.5 and 59.6, 14,000 x 500 -> 41 (876)
-//  19.8 and 18.5, 5,000 x 500 -> 300 (1,570) 32.0 and 20.3, 2,708 x 256 -> 1,000 (2,720) 29.7 and 16.7.  More blocks keep the
-//  split products, whose sums are a quarter closer, although few rows are faster (20,000 x 500 -> 20 14.7 and 18.3).  (The
-//  "transform_few_blocks" setting, unless it is 128: fewer blocks than it says.)
-//  Blocks: as wide as the output up to 256 columns; narrower, so that H is read more than once, where that gives up to 256 blocks
-//  instead of fewer (14,000 x 500 -> 256 in 110 blocks 37.3, 220 of 128 columns 30.4; 8,000 x 1,000 -> 256 in 63 65.3, 252 of 64
-//  38.9; 19,717 x 500 -> 256 in 155 36.6, 310 of 128 42.6), and half as wide where the widest are a few more than compute units
-//  (2,708 x 64 -> 2,866 in 264 19.1, 506 of 128 12.9; 40,000 x 256 -> 256 in 313 44.6, 626 40.3).
-int64_t block_width(int64_t D_out) { return D_out <= 32 ? 32 : D_out <= 64 ? 64 : D_out <= 128 ? 128 : D_out <= 192 ? 192 : 256; }
-int64_t blocks_of(int64_t N, int64_t D_out, int64_t bn) { return (N + 127) / 128 * ((D_out + bn - 1) / bn); }
-bool takes_few_rows(int64_t N, int64_t D_out)
-{
-    const int64_t few = agg_options().few_blocks;
-    return blocks_of(N, D_out, block_width(D_out)) < few && (few != 128 || (N + 31) / 32 * ((D_out + 31) / 32) <= 832);
-}
-int64_t block_width_for(int64_t N, int64_t D_out)
-{
-    const int64_t widest = block_width(D_out), blocks = blocks_of(N, D_out, widest);
-    if (blocks > 256) return widest == 256 && blocks <= 400 ? 128 : widest;
-    int64_t bn = widest;
-    for (int64_t narrower : {128, 64, 32})
-        if (narrower < bn && blocks_of(N, D_out, narrower) <= 256) bn = narrower;
-    return bn;
 }
 
 template <bool MASKED>

@@ -55,3 +55,31 @@ def test_bias_gradients_and_loss(n, h, c):
     again = Hn.layer_grad(X, d_in, y, W1, b1, Wc, bc)
     for a, b in zip((loss, gW1, gb1, gWc, gbc), again):
         assert a is None or torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,d_in,h,c", [(8000, 300, 256, 160), (5003, 131, 300, 131), (2708, 201, 500, 140)])
+def test_products_in_halves(n, d_in, h, c):
+    """Shapes of fewer than 128 blocks whose products are formed in halves of the sum, all three kinds: the forward, whose signs are
+    decided, the product behind the ReLU's mask with its column sums, the input's gradient."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *s: torch.empty(s, dtype=torch.float32, device="cuda").uniform_(-1.0, 1.0, generator=g)
+    X, W1 = (rnd(n, d_in) * 8).round() / 8, (rnd(d_in, h) * 16).round() / 16              # (exact hidden sums, as above)
+    b1 = ((rnd(h) * 64).round() * 2 + 1) / 256
+    Wc, bc = rnd(h, c) / 8, rnd(c)
+    y = torch.randint(0, c, (n,), generator=g, device="cuda", dtype=torch.int32)
+    y[torch.rand(n, generator=g, device="cuda") < 0.4] = -1
+    gX = torch.empty(n, d_in, device="cuda")
+    loss, gW1, gb1, gWc, gbc = Hn.layer_grad(X, d_in, y, W1, b1, Wc, bc, gX=gX)
+    want, sums = step64(X, y, W1, b1, Wc, bc)
+    assert abs(float(loss[0]) - float(want)) <= 1e-5 * abs(float(want))
+    for got, (total, size) in zip([gbc, gb1], sums):
+        assert bool(((got.double() - total).abs() <= 1e-5 * size + 1e-30).all())
+    act = (y >= 0)
+    pre = X.double() @ W1.double() + b1.double()
+    dL = torch.softmax(pre.clamp(min=0) @ Wc.double() + bc.double(), 1)
+    dL.scatter_add_(1, y.clamp(min=0).long()[:, None], torch.full_like(dL[:, :1], -1.0))
+    dL *= act.double()[:, None] / int(act.sum())
+    dA = (dL @ Wc.double().T) * (pre > 0)
+    size = (dL.abs() @ Wc.double().abs().T) * (pre > 0)
+    for got, total, terms in ((gX, dA @ W1.double().T, size @ W1.double().abs().T), (gW1, X.double().T @ dA, X.double().abs().T @ size)):
+        assert bool(((got.double() - total).abs() <= 1e-5 * terms + 1e-30).all())
