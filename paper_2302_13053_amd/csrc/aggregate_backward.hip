@@ -29,6 +29,7 @@
 //    by edge: each lane accumulates weight * (its own columns' share of the
 //    product) and the lanes of a head are summed once per row.
 //    Nothing is accumulated with atomics; every sum has a fixed order.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -1102,10 +1103,11 @@ void dispatch_wide(int nc, const BwdArgs& a, int fp, int64_t nh, int64_t N, hipS
 
 constexpr int64_t kParamBlocks = 2048;
 
-int64_t param_blocks(int64_t N) { return N <= 0 ? 1 : (N + 31) / 32 < kParamBlocks ? (N + 31) / 32 : kParamBlocks; }
-
+// `partial`, the attention vectors' partial sums, begins with nbr, which the "src" pass is the last to read: one block of sums
+// per 32 rows fits there and in what one per 256 rows takes behind it (fewer only in rows of more than 292 columns, 585 with
+// more than four heads).
 struct SoftmaxWorkspace {
-    int64_t el, er, nbr, ddst, dsrc, partial, total;
+    int64_t el, er, nbr, ddst, dsrc, partial, blocks, total;
 };
 
 SoftmaxWorkspace softmax_workspace(int64_t N, int64_t F, int heads)
@@ -1118,8 +1120,10 @@ SoftmaxWorkspace softmax_workspace(int64_t N, int64_t F, int heads)
     w.er = off; off += per;
     w.ddst = off; off += per;
     w.dsrc = off; off += per;
-    w.nbr = off; off += align_up(n * hp * 16, 256);
-    w.partial = off; off += align_up(param_blocks(N) * 2 * (F > 0 ? F : 1) * (int64_t)sizeof(float), 256);
+    w.nbr = w.partial = off; off += align_up(n * hp * 16, 256);
+    const int64_t sums = 2 * (F > 0 ? F : 1) * (int64_t)sizeof(float);
+    off += align_up(std::min((n + 255) / 256, kParamBlocks) * sums, 256);
+    w.blocks = std::min({(n + 31) / 32, kParamBlocks, (off - w.partial) / sums});
     w.total = off;
     return w;
 }
@@ -1260,7 +1264,7 @@ int launch_aggregate_backward(const AggBackwardCall& c, hipStream_t stream)
         else dispatch_wide<8>(nc, a, first_pass, n_heavy, N, stream);
     }
 
-    const int64_t nblk = param_blocks(N);
+    const int64_t nblk = w.blocks;
     const int64_t rows_per_block = (N + nblk - 1) / nblk;
     float* partial = (float*)(ws + w.partial);
     if (v4 && a.Dh % 4 == 0)
