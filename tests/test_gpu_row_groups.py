@@ -133,6 +133,54 @@ def test_slabs_of_heads(heads, dh):
     g.destroy()
 
 
+@pytest.mark.parametrize("heads,dh", [(4, 64), (5, 32), (2, 64)])
+def test_backward_from_the_state_of_slabs(heads, dh):
+    """What save mode leaves in slabs of heads: statistics of every slab's heads and of the padded ones, positive and negative parts
+    at their columns.  Values and vectors are small multiples of 1/8 and 1/32, so that a score is exact and has the same sign
+    here and in the oracle."""
+    n, F = 50001, heads * dh
+    src, dst = wl.random_pairs(n, 4700000, 5, skew=1.2)
+    g = Hn.make_plan(Hn.csr_from_coo(Hn.dev(src), Hn.dev(dst), n, False))
+    rp, ci = oracle.csr_from_coo(src, dst, n, False)
+    assert rp[-1] >= 48 * n and n * F * 4 >= 24 << 20 and rp[-1] * F * 4 >= 4 << 30
+    a = [np.rint(wl.random_matrix(heads, dh, k) * 4).astype(np.float32) / 32 for k in (1, 2)]
+    Zh, Gh = np.rint(wl.random_matrix(n, F, 7) * 8).astype(np.float32) / 8, wl.random_matrix(n, F, 8)
+    kw = dict(heads=heads, a_src=Hn.dev(a[0]), a_dst=Hn.dev(a[1]))
+    Z = Hn.dev(Zh)
+    ws = Hn.ws_tensor(B.retexo_workspace_bytes(g.plan, F, B.MODES["gat_softmax"], heads, B.F_SAVE))
+    Hn.aggregate(g, "gat_softmax", Z, F, save=True, workspace=ws, **kw)
+    got = Hn.aggregate_backward(g, "gat_softmax", F, Hn.dev(Gh), Z=Z, saved=ws, **kw)
+    want = oracle.aggregate_backward("gat_softmax", rp, ci, Zh, F, Gh, heads=heads, a_src=a[0], a_dst=a[1])
+    assert_close(got[0].cpu().numpy()[:, :F], want[0], what="gradient of Z")
+    for grad, ref, what in zip(got[1:], want[1:], ("source", "destination")):
+        assert_close(grad.cpu().numpy(), ref, what=what + " attention vector, head by head")
+    g.destroy()
+
+
+@pytest.mark.parametrize("name", ["few", "edges", "skewed"])
+@pytest.mark.parametrize("heads,dh", [(1, 4), (8, 4), (3, 8), (1, 32), (3, 16)])
+def test_backward_of_narrow_rows_by_length(graphs, name, heads, dh):
+    """Rows of a few columns have no robust magnitude of their own: one ratio over the rows of similar length, so that the long
+    ones, whose gradients are the largest, hide no error in the short ones."""
+    g, rp, ci = graphs[name]
+    n, F = g.n_nodes, heads * dh
+    a = [wl.random_matrix(heads, dh, k) * np.float32(0.1) for k in (1, 2)]
+    Zh = np.ascontiguousarray(decided_rows(rp, ci, heads, dh, a)[:, :F])
+    Gh = wl.random_matrix(n, F, F + 2)
+    Z, G, As, Ad = (Hn.dev(x) for x in (Zh, Gh, *a))
+    kw = dict(heads=heads, a_src=As, a_dst=Ad)
+    ws = Hn.ws_tensor(B.retexo_workspace_bytes(g.plan, F, B.MODES["gat_softmax"], heads, B.F_SAVE))
+    Hn.aggregate(g, "gat_softmax", Z, F, workspace=ws, save=True, **kw)
+    want = oracle.aggregate_backward("gat_softmax", rp, ci, Zh, F, Gh, heads=heads, a_src=a[0], a_dst=a[1])[0]
+    deg = np.diff(rp)
+    for what, saved in (("plain", None), ("saved", ws)):
+        got = Hn.aggregate_backward(g, "gat_softmax", F, G, Z=Z, saved=saved, **kw)[0].cpu().numpy()[:, :F]
+        for lo, hi in ((0, 1), (1, 2), (2, 5), (5, 9), (9, 17), (17, 33), (33, 129), (129, 1025), (1025, n + 1)):
+            at = (deg >= lo) & (deg < hi)
+            if at.any():
+                assert_close(got[at].reshape(1, -1), want[at].reshape(1, -1), what="%s, %d to %d entries" % (what, lo, hi - 1))
+
+
 @pytest.mark.parametrize("name", ["edges", "skewed"])
 @pytest.mark.parametrize("heads,dh", [(1, 4), (3, 8), (1, 64), (8, 16), (8, 32)])
 def test_values_that_no_entry_reads(graphs, name, heads, dh):
