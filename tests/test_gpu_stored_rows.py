@@ -7,6 +7,7 @@ import torch
 
 import oracle
 from oracle import storage as ost
+from paper_2302_13053_amd import binding as B
 from paper_2302_13053_amd import harness as Hn
 from paper_2302_13053_amd import workloads as wl
 from parity import assert_close, assert_cond_close
@@ -79,4 +80,35 @@ def test_stored_softmax_row_groups(graphs, name, fmt, heads, dh, pad):
     assert_cond_close(got[:, :2 * F], want, oracle.aggregate_abs("gat_softmax", rp, ci, stored, F, **okw), what="softmax")
     if F >= 64:
         assert_close(got[:, :2 * F], want, what="softmax, row by row")
+    assert np.array_equal(got[:, :F].astype(np.float64), want[:, :F]) and np.all(got[:, 2 * F:] == 777.0)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+@pytest.mark.parametrize("name", ["edges", "skewed", "dense"])
+@pytest.mark.parametrize("heads,dh", [(1, 4), (8, 4), (3, 8), (5, 16), (2, 32), (8, 32), (3, 64), (2, 128), (1, 256)])
+@pytest.mark.parametrize("how", ["offsets", "vector"])
+def test_stored_softmax_one_row_per_wave(graphs, name, fmt, heads, dh, how):
+    """What row groups do not take: rows with 64-bit offsets (tables of 4 GiB and more) and a destination vector that is not at a
+    16-byte address; every width of a head."""
+    g, rp, ci = graphs[name]
+    n, F = g.n_nodes, heads * dh
+    ld = -(-F // 8) * 8
+    Zh = wl.random_matrix(n, F, F + 1)
+    bits = np.full((n, ld), -1, np.int16)                     # NaN between the rows
+    bits[:, :F] = ost.store(Zh, fmt).view(np.int16)
+    stored = ost.load(ost.store(Zh, fmt), fmt)
+    a = [wl.random_matrix(heads, dh, k) * np.float32(0.3) for k in (1, 2)]
+    vector = torch.zeros(F + 1, device="cuda")[1:].view(heads, dh) if how == "vector" else torch.zeros((heads, dh), device="cuda")
+    vector.copy_(torch.from_numpy(a[1]))
+    out = torch.full((n, 2 * F + 1), 777.0, device="cuda")
+    try:
+        B.check(B.retexo_set_option("agg_wide_offsets", 1 if how == "offsets" else 0), "set_option")
+        Hn.aggregate_stored(g, "gat_softmax", torch.from_numpy(bits).cuda(), F, fmt, concat=True, out=out, heads=heads,
+                            a_src=Hn.dev(a[0]), a_dst=vector)
+    finally:
+        B.check(B.retexo_set_option("agg_wide_offsets", 0), "set_option")
+    got = out.cpu().numpy()
+    okw = dict(heads=heads, a_src=a[0], a_dst=a[1], self_concat=True)
+    want = oracle.aggregate("gat_softmax", rp, ci, stored, F, **okw)
+    assert_cond_close(got[:, :2 * F], want, oracle.aggregate_abs("gat_softmax", rp, ci, stored, F, **okw), what="softmax")
     assert np.array_equal(got[:, :F].astype(np.float64), want[:, :F]) and np.all(got[:, 2 * F:] == 777.0)
