@@ -1466,7 +1466,11 @@ bool aligned_rows(const void* p, int64_t ld_elems, int bytes_per_elem)
 //  1/300 of the nodes on, 1/100 where the last slab is less than three quarters of the columns; up to 250,000 nodes.  Of 16,248 drawn calls
 //  over 16-bit tables 806 were more than 4 % slower than in whole rows when all of up to 250,000 nodes came here, 83 are.
 //  With weights, which wait for ids, from 8,192 nodes on, or a longest row of 48 (of up to 64 columns) or a mean of 100 (above): 2,340
-//  of 14, longest 28, 32 columns 5.9 and 4.8; 3,000 of 60, 128 columns 10.4 and 9.9.
+//  of 14, longest 28, 32 columns 5.9 and 4.8; 3,000 of 60, 128 columns 10.4 and 9.9.  Fewer nodes whose rows are alike, on which
+//  the chip waits for one row as for another, in whole rows: with weights up to 3,500 and a longest row of three times the mean
+//  (430 of 36, longest 52, 2 columns 7.6 and 6.0; 1,986 of 81, longest 115, 32 columns 13.0 and 11.2; the other way 4,308 of 89,
+//  longest 121, 14.0 and 16.6; 1,799 of 109, longest 339, 22.2 and 27.7), without up to 4,500 and a longest row of 44 entries
+//  (1,299 of 7, 64 columns 4.2 and 3.7; 4,187 of 5 4.4 and 4.0; the other way 5,056 of 8 4.2 and 4.6, 2,261 of 34, longest 54, 6.5 and 7.0).
 //  Instead of the range walk where a row's share of a range is short: 600,000 of 120 (7 per range) 1,127 and 1,448, 1,003,546
 //  of 80 (5), 64 columns 1,483 and 3,670, 576,484 of 113 (7), 96 columns 2,069 and 3,946; the other way 400,000 of 150 (19) 800
 //  and 678, 150,000 of 200 (50), 64 columns 355 and 251, with weights 386,048 of 112 (14) 1,012 and 832.  Not in one range, which
@@ -1484,6 +1488,7 @@ int rows_lanes(const StoredCall& c, bool wide, bool ranges, int parts)
         // eight elements at 4-byte addresses, none past a row's end: what lies there may not be the caller's
         return (uintptr_t)c.Z % 4 == 0 && c.ldz % 2 == 0 && F >= 8 && F % 2 == 0 ? lanes : 0;
     }
+    if (!ranges && F <= 128 && (weighted ? N < 3500 && F <= 64 && p->max_degree * N < 3 * nnz : N < 4500 && p->max_degree < 44)) return 0;
     if (!ranges) {
         const bool filled = 4 * F >= 3 * align_up(F, 256);
         return F <= 128 || (N < 250000 && p->max_degree >= 48 && (filled ? 300 : 100) * (int64_t)p->max_degree >= N) ? lanes : 0;
