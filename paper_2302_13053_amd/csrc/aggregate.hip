@@ -2133,11 +2133,31 @@ bool dense_for_ranges(const AggCall& c)
 int64_t alike_rows(int64_t N, int64_t nnz, int64_t F, bool weighted)
 {
     const bool long_rows = nnz >= 100 * N;
-    if (N <= 32768) return F > 64 ? 3 : 0;
+    if (N <= 32768) return F > 64 ? 3 : F > 32 && N > 24000 && !weighted ? 2 : 0;
     if (N <= 65536) return F <= 128 ? 6 : 10;
     if (N <= 131072) return F <= 32 ? 8 : weighted ? 10 : 20;
     if (N <= 262144) return !weighted ? (F <= 32 ? 10 : 20) : long_rows || F <= 16 ? 10 : F <= 64 ? 0 : 3;
     return N <= 524288 && long_rows && !weighted ? 10 : 0;
+}
+// The same over padded rows that are not whole lines, which are narrow where ranges gain.  Rows of 17 to 32 columns, up to eight
+// ranges of 128-byte pieces, from 56 to 85 entries on (24 columns, ranges against row groups: 160,491 nodes of 109 203 and 298,
+// 114,026 of 210, longest 3.9 times the mean, 210 and 313; ratios: 164,000 of 196, 15.8 times, 1.61, 119,289 of 225, 14.2 times,
+// 1.25, 127,881 of 107, 14.7 times, 1.25, 101,000 of 102, 13.9 times, 0.85, nine ranges and more 0.6 to 0.75).  Rows of 9 to 16 columns, which are half idle in
+// row groups too, where they are long: with weights 96,411 of 219 1.17, 61,000 of 221 1.01; without 178,272 of 166 1.16, 254,000 of
+// 107 1.30, 309,000 of 152 1.15, but 325,193 of 80 0.80.  Wider rows, without weights, in four ranges: 40 columns, 193,000 of
+// 121 1.12, 56 columns, 166,429 of 120, 16 times, 1.13.
+int64_t alike_off_lines(int64_t N, int64_t nnz, int64_t F, bool weighted)
+{
+    auto mean_is = [&](int64_t entries) { return nnz >= entries * N; };
+    if (N <= 32768 || N > 524288 || F <= 8 || F > 64) return 0;
+    if (F > 16 && F <= 32) {
+        if (!mean_is(N <= 131072 ? 56 : weighted && N > 262144 ? 85 : 64)) return 0;
+        return N <= 65536 ? 6 : N <= 104000 && !mean_is(140) ? 8 : 24;
+    }
+    if (F > 32) return !weighted && N > 131072 && N <= 262144 && mean_is(110) ? 20 : 0;
+    if (weighted) return N <= 262144 && mean_is(130) ? 5 : 0;
+    if (N <= 200000) return N > 150000 && mean_is(160) ? 10 : 0;
+    return mean_is(N <= 262144 ? 75 : 100) ? 10 : 0;
 }
 
 // Which kernels a sum, mean or gcn_sym takes whose rows are gathered four floats at a time: the range walk over narrow slabs, row
@@ -2177,7 +2197,8 @@ LinearRoute linear_route(const AggCall& c, int vec, int parts)
     const bool dense = dense_for_ranges(c);
     auto mean_is = [&](int64_t entries) { return nnz >= entries * N; };
     const bool lines = aligned_for(c.Z, c.ldz, 32);                 // rows on whole 128-byte lines
-    if (dense && lines && p->max_degree * N < alike_rows(N, nnz, F, weighted) * nnz) return ranges;
+    const int64_t alike = lines ? alike_rows(N, nnz, F, weighted) : alike_off_lines(N, nnz, F, weighted);
+    if (dense && p->max_degree * N < alike * nnz) return ranges;
     if (dense && N >= 16384 && N * 128 <= parts * (64ll << 20) && 2 * nnz >= 25 * N * parts) {
         const bool enough = N >= 24000 || work >= 1200000000ll || mean_is(300);
         if (F >= 100 ? enough && work >= 700000000ll && (mean_is(160) || mean_is((weighted ? 25 : 15) * parts))

@@ -113,6 +113,23 @@ def test_linear_unpadded(graphs, name, F, ld, offset):
         assert np.array_equal(got[:, :F], Zh[:, :F]) and np.all(got[:, 2 * F:] == 777.0)
 
 
+@pytest.mark.parametrize("n,entries,F", [(52433, 59, 20), (52433, 59, 25), (52433, 59, 37), (70001, 132, 12), (150017, 164, 9)])
+def test_linear_over_flat_graphs(n, entries, F):
+    """Nodes of nearly equal degrees, padded rows that are not whole lines: in ranges or in row groups."""
+    src, dst = wl.random_pairs(n, n * entries // 2, 6, skew=0.0)
+    g = Hn.make_plan(Hn.csr_from_coo(Hn.dev(src), Hn.dev(dst), n, False))
+    rp, ci = oracle.csr_from_coo(src, dst, n, False)
+    ld = (F + 3) // 4 * 4
+    Zh = np.full((n, ld), np.nan, np.float32)
+    Zh[:, :F] = wl.random_matrix(n, F, F)
+    for mode in ("mean", "gcn_sym"):
+        got = Hn.aggregate(g, mode, Hn.dev(Zh), F, concat=True, ld_out=2 * F + 3).cpu().numpy()
+        want = oracle.aggregate(mode, rp, ci, Zh[:, :F], F, self_concat=True)
+        mag = oracle.aggregate_abs(mode, rp, ci, Zh[:, :F], F, self_concat=True)
+        assert_cond_close(got[:, :2 * F], want, mag, what=mode)
+    g.destroy()
+
+
 @pytest.mark.parametrize("heads,dh", [(4, 64), (5, 32), (2, 64)])
 def test_slabs_of_heads(heads, dh):
     """Rows of several slabs (of one head; of two heads with a last one of one): 50,001 nodes of 180
