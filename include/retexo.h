@@ -492,8 +492,10 @@ double retexo_gamma(double B, double R, double H0, double sum_H, double sum_C, d
  *       "csr_sorted_keys" (1: retexo_csr_from_coo uses its general sorted-key construction, which
  *       otherwise only graphs of more than 2^23 nodes take, instead of the bucketing one),
  *       "transform_few_blocks" (retexo_transform and the transforms inside retexo_round: a matrix
- *       with fewer 128-row blocks, times column blocks, than this takes the kernel that splits K
- *       over the waves of 32-row workgroups; default 128, 0 = never; RETEXO_E_SIZE if negative).
+ *       with fewer 128-row blocks, times column blocks, than this takes the kernels that split K
+ *       over the waves of 32-row workgroups; default 128, at which it also has to have at most 832
+ *       tiles of 32 x 32 or 512 of 32 x 64, a limit that no other value has; 0 = never;
+ *       RETEXO_E_SIZE if negative).
  * Returns RETEXO_E_FLAGS for an unknown name.
  */
 int retexo_set_option(const char* name, int64_t value);

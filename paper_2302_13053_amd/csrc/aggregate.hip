@@ -2167,7 +2167,8 @@ struct LinearRoute {
     int lanes;
 };
 // Measured over 23 graphs of 3,000 to 2,449,029 nodes and 5 to 500 entries per row at 32 to 602 columns, and over some
-// thousands of drawn calls (us, mean unless said, ranges against the others):
+// thousands of drawn calls (us, mean unless said, ranges against the others; limits without a figure here are where those calls
+// change sides):
 //  Ranges pay where a range's slab is near an L2's size and rows are long: 232,965 nodes of 492 entries, 602 columns 13,440 and
 //  26,270; 400,000 of 250 (31 in each of 8 ranges) 17,200 and 27,660; 427,947 of 189, 192 columns 5,323 and 7,965; 50,000 of 400,
 //  64 columns 242 and 334; 476,789 of 205, 32 columns 1,180 and 1,572.  The other way 1,000,000 of 100 (6 in each of 16 ranges)
@@ -2256,11 +2257,11 @@ GatRoute gat_route(const AggCall& c)
 }
 
 // Heads that a slab of agg_gat_rows_kernel holds; 0: the call takes one row per wave.
-// Up to 64 columns are one slab.  Wider rows of heads of up to 64 columns are walked a slab of 64 after the other where
-// the table is much larger than an L2 (24 MB): a fourth of the columns at a time leaves four times as many of the nodes that are
-// gathered most in each L2.  That has to outweigh reading the ids, and a row's own start, once per slab: from 48 entries per row
-// and 4 GB of gathers on (shorter calls gain from it too, 60,000 of 50 in save mode 475 and 360, but are left to one row per
-// wave: its time there is the unit that the table kernel's workgroups are held to).
+// Up to 64 columns are one slab.  Wider rows of heads of up to 64 columns are walked a slab of 64 after the other over tables
+// much larger than an L2 (24 MB) from 48 entries per row and 4 GB of gathers on.  What gains is four rows in flight per wave; hits
+// in L2 hardly do (2,449,029 nodes of 50 entries, 256 columns: hit rate 0.039 and 0.052, traffic 133.7 and 132.7 GB, the time a
+// tenth less).  It has to outweigh reading the ids, and a row's own start, once per slab.  The lines are no crossover: shorter calls
+// gain as well (60,000 of 50 in save mode 475 and 360), down to a size that has not been measured.
 // One row per wave and slabs, in us: 2,449,029 nodes of 50 entries, 256 columns 20,400 and 18,700, save mode 22,050 and 20,900;
 // 200,000 of 100 2,626 and 2,113; 50,000 of 400 2,030 and 1,166; 65,000 of 100 743 and 639; 128 columns 2,449,029 of 50
 // 9,330 and 8,740, 200,000 of 100 1,199 and 1,079.  The other way: 100,000 of 40, 192 columns, save mode 365 and 406; 1,000,000 of

@@ -125,8 +125,9 @@ int launch_zero(void* p, size_t bytes, hipStream_t stream);
 
 // internal launchers (no argument validation; the C entry points did it)
 // keep_sign: which outputs are positive is decided by float32 sums, however the products are formed (a training step goes by
-// it: see train.hip): one sum with k in ascending order in the block kernel, the few-rows kernel's own sums (of eight
-// slices of K) where that takes the call; an exact zero among the block kernel's sums of split products is not positive
+// it: see train.hip): one sum with k in ascending order in the block kernel, the few-rows kernels' own sums (of eight slices of
+// K; over long sums of sixteen interleaved ones in each half of K) where they take the call; an exact zero among the block
+// kernel's sums of split products is not positive
 int launch_transform(int64_t N, int64_t D_in, int64_t D_out, const float* H, int64_t ldh,
                      const float* W, const float* b, bool relu, float* Z, int64_t ldz,
                      hipStream_t stream, const float* mask = nullptr, int64_t ldm = 0, bool keep_sign = false,

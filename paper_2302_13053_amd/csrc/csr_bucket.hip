@@ -1065,7 +1065,8 @@ __global__ __launch_bounds__(256) void emit_kernel(
 // ---------------------------------------------------------------------------
 // Graphs of up to kTinyItems pairs and loops over up to kTinyRows nodes: one workgroup, one launch.  Bound by latencies, not
 // work: counting, moving, sorting and emitting in four dependent launches took 31 us of a construction of 42 over 2,708 nodes
-// and 5,429 pairs, which takes 32 so.  Entries are counted per row in LDS, which also says where in its row each goes; a row of up to
+// and 5,429 pairs, which takes 32 so.  The lines are what LDS holds; near them 8,049 nodes and 8,021 pairs took 64.2 and 58.9, 1,076
+// and 8,025, whose rows are mostly long, 61.2 and 60.8.  Entries are counted per row in LDS, which also says where in its row each goes; a row of up to
 // kTinyShort entries is sorted and cleaned in the registers of one thread, a longer one is marked in a bit map of the nodes by a
 // wave, which drops its repeats and orders it.
 constexpr int kTinyItems = 8192, kTinyRows = 8192;

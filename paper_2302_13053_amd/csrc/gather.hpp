@@ -91,8 +91,8 @@ __device__ __forceinline__ u32x4 load_entry(table_t t, uint32_t row, uint32_t co
     return __builtin_amdgcn_raw_buffer_load_b128(t, __builtin_elementwise_add_sat(row, col), 0, 0);
 }
 
-// Rows narrower than a wave: P lanes of four floats each hold a row (P = 8 or 16), and the R = 64 / P groups of a
-// wave walk a list of entries each, in lock step: R rows of neighbouring length, or R shares of one long row.  A
+// Rows, or slabs of rows, that a wave need not hold alone: P lanes (4 to 64) of four floats, or of four or eight 16-bit elements, hold
+// one, and the R = 64 / P groups of a wave walk a list of entries each, in lock step: R rows of neighbouring length, or R shares of one long row.  A
 // gather instruction so carries R entries, where one entry per instruction leaves 64 - P lanes idle and the kernels wait
 // for as many round trips to memory as a row has batches.
 // Every lane fetches four consecutive ids at a time (a tile of 4 P entries per group, whole cache lines of col_idx, a tile
@@ -218,7 +218,7 @@ struct BatchSums {
     }
 };
 
-// lanes that hold a row of F columns, four floats each, in the kernels whose waves walk several rows; 0: one row per wave
+// lanes that hold a row of F columns, up to 256, four columns each
 inline int row_lanes(int64_t F) { return F <= 32 ? 8 : F <= 64 ? 16 : F <= 128 ? 32 : 64; }
 
 __device__ __forceinline__ float wave_max(float x)
