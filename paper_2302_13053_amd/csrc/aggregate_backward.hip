@@ -628,7 +628,11 @@ __global__ __launch_bounds__(64 * NW) void gat_bwd_src_rows_kernel(BwdArgs a, in
         elu = a.el[(int64_t)u * hp + h];
     }
 
-    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q = 0.0f, tc = 0.0f;
+    // The score's gradient, q = sum of w (<g, z> - c), is small beside its two halves, so the difference is taken batch by batch
+    // (10,905 nodes of 117 entries, 32 columns, values of one sign, 2-norm of the error of dZ 4.1e-7 with the halves in a running
+    // sum each, 2.4e-7 in the kernel above, which adds the second one up over the lanes; entry by entry 22,257 nodes of 68 entries
+    // take 65 us, so 56, with two running sums 55).
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, q = 0.0f;
     f32x4 gr[2][U], nb[2][U];
     uint32_t on[2][U];
     auto issue = [&](int k, f32x4 (&gg)[U], f32x4 (&nn)[U], uint32_t (&oo)[U]) {       // batch k
@@ -644,6 +648,7 @@ __global__ __launch_bounds__(64 * NW) void gat_bwd_src_rows_kernel(BwdArgs a, in
         }
     };
     auto consume = [&](const f32x4 (&gg)[U], const f32x4 (&nn)[U], const uint32_t (&oo)[U]) {
+        float qb = 0.0f, tc = 0.0f;
 #pragma unroll
         for (int t = 0; t < U; ++t) {
             const float x = elu + nn[t].x;
@@ -657,8 +662,9 @@ __global__ __launch_bounds__(64 * NW) void gat_bwd_src_rows_kernel(BwdArgs a, in
             acc[2] = fmaf(al, gg[t].z, acc[2]); pd = fmaf(gg[t].z, zo[2], pd);
             acc[3] = fmaf(al, gg[t].w, acc[3]); pd = fmaf(gg[t].w, zo[3], pd);
             // (zero times an infinite row of the group's own would be NaN, for a row without entries as well)
-            q = oo[t] != kNoEntry ? fmaf(w, pd, q) : q;
+            qb = oo[t] != kNoEntry ? fmaf(w, pd, qb) : qb;
         }
+        q += group_sum<G>(qb) - tc;
     };
     if (batches > 0) issue(0, gr[0], nb[0], on[0]);
     for (int k = 0; k < batches; k += 2) {
@@ -669,7 +675,7 @@ __global__ __launch_bounds__(64 * NW) void gat_bwd_src_rows_kernel(BwdArgs a, in
         consume(gr[1], nb[1], on[1]);
     }
 
-    float ds = group_sum<G>(q) - tc;
+    float ds = q;
     if (heavy) {
         // the shares: groups of the wave, then the waves
 #pragma unroll
